@@ -1,10 +1,12 @@
-"""Builds libgraft.so (the C-ABI library) from the HIP sources with hipcc for gfx950."""
+"""Builds libgraft.so (the C-ABI library) from the HIP sources with hipcc for gfx950, and _native.so
+(the native half of the Python binding, host code only) with g++."""
 from __future__ import annotations
 
 import os
 import re
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -14,6 +16,7 @@ INCLUDE = os.path.join(ROOT, "include")
 OBJ_DIR = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libgraft.so")
 LIB_TIMING = os.path.join(PKG, "libgraft_timing.so")     # the same library with the attention kernel's time stamps
+NATIVE = os.path.join(PKG, "_native.so")                 # tensor marshalling of the Python binding (csrc/binding.cpp)
 SOURCES = ["api.hip", "retrieve.hip", "tree_mask.hip", "tree_attn.hip", "accept.hip", "matrix.hip", "kv_compact.hip", "prune.hip"]
 
 # packed-fp32 code generation is switched off for every device compile; VGPR spills must not
@@ -205,11 +208,33 @@ def _link(objects, lib: str) -> str:
     return lib
 
 
+def build_native() -> str:
+    """_native.so: plain C++ against the headers of PyTorch and Python.  It resolves libgraft.so at run
+    time (bind()), and PyTorch's libraries are the ones `import torch` has loaded."""
+    import torch
+    base = os.path.dirname(os.path.abspath(torch.__file__))
+    inc, libs = os.path.join(base, "include"), os.path.join(base, "lib")
+    tmp = NATIVE + ".tmp%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-sign-compare", "-I", INCLUDE,
+           "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"],
+           "-isystem", "/opt/rocm/include",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+           os.path.join(CSRC, "binding.cpp"), "-o", tmp, "-L", libs, "-ltorch_python", "-ltorch_hip", "-ltorch_cpu", "-lc10_hip", "-lc10", "-ldl"]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("the native binding does not build:\n" + r.stdout)
+    os.replace(tmp, NATIVE)
+    return NATIVE
+
+
 def build(verbose: bool = False, extra_flags=()) -> str:
-    """Compile every HIP source and link libgraft.so next to the package. Always recompiles."""
+    """Compile every HIP source and link libgraft.so next to the package, and build _native.so.  Always recompiles."""
     os.makedirs(OBJ_DIR, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(9, len(SOURCES) + 1)) as ex:
+        native = ex.submit(build_native)
         results = list(ex.map(lambda s: _compile(s, list(extra_flags)), SOURCES))
+        native.result()
     if verbose:
         for _, w in results:
             if w:
