@@ -172,7 +172,8 @@ int32_t graft_build_tree_mask(const int32_t* parent, const int32_t* n_nodes, con
  * scale                       softmax scale, normally 1/sqrt(D)
  * dtype                       GRAFT_F32: fp32 storage and arithmetic throughout.
  *                             GRAFT_BF16: bf16 storage, fp32 scores/softmax/accumulation,
- *                             probabilities rounded to bf16 for the P.V product; where the
+ *                             probabilities rounded to bf16 for the P.V product (D = 128;
+ *                             D = 64 keeps 17 bits of them); where, with D = 128, the
  *                             keys are split over workgroups, each split's normalised
  *                             partial row passes through memory as fp16 scaled by a power
  *                             of two to its largest entry: 11 bits for entries within
@@ -180,8 +181,10 @@ int32_t graft_build_tree_mask(const int32_t* parent, const int32_t* n_nodes, con
  *                             the result), an absolute 2^-25 of it below that.
  * workspace                   at least graft_tree_attn_workspace_bytes(...) bytes,
  *                             256-byte aligned; contents are scratch.  The size is 0 (and
- *                             workspace may be NULL) for the fp32 / D = 64 path and where
- *                             the keys of a sequence are not split over workgroups.
+ *                             workspace may be NULL) where the keys of a sequence are not
+ *                             split over workgroups.  With GRAFT_F32 or D = 64 the workspace
+ *                             is optional: without it (NULL or too small) the keys are not
+ *                             split, which is slower for few sequences with long prefixes.
  *
  * Requires D in {64,128}, Hq % Hkv == 0, Hq/Hkv <= 16, page_size == GRAFT_PAGE_SIZE,
  * 1 <= K_max <= GRAFT_MAX_NODES, 1 <= max_pages <= 262144 (4 Mi tokens),

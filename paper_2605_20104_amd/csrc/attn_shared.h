@@ -1,0 +1,97 @@
+// What the attention translation units share: kernel parameters, launch plans, launch helpers.
+#pragma once
+#include <hip/hip_ext.h>
+
+#include "common.h"
+
+namespace graft {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef short short4_t __attribute__((ext_vector_type(4)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+
+struct AttnParams {
+    const void* q;
+    const void* k;
+    const void* v;
+    void* out;
+    const int32_t* block_table;
+    const int32_t* prefix_len;
+    const int32_t* n_nodes;
+    const u64* mask;
+    unsigned short* ws_o;   // fp16 [B][Hkv][splits][R_pad/16][D/32] blocks of 1 KB: [lane][2][4], lane = MFMA
+                            // accumulator lane, two adjacent 16-dim tiles per block
+    float* ws_ml;       // [B][Hkv][splits][R_pad][4]  (max in log2 units, sum, scale of the stored row, 0)
+    int64_t page_stride, token_stride, head_stride;
+    int32_t max_pages, B, K_max, Hq, Hkv, G, R, R_pad, n_splits, n_row_tiles;
+    int32_t g_magic;    // ceil(2^16 / G): r / G == (r * g_magic) >> 16 for r < 4096, G <= 16
+    float scale;        // softmax scale
+    float scale_log2e;  // scale * log2(e)
+    unsigned long long* stamps;   // timing build: AT_STAMPS values per workgroup, or null (always null otherwise)
+};
+
+// Workgroups go to the 8 XCDs (each with its own L2 and its own compute units) round-robin by their
+// linear index.  Work items are numbered with the row tiles of one (sequence, KV head, split), which
+// read the same keys and values, next to each other, and every XCD takes one contiguous eighth of
+// them: tiles that share keys run side by side on one L2, and the XCDs' shares differ by one item
+// at most (a share that holds whole units only can be a third larger than the average, a second
+// round for a job that was planned to fill the chip once).
+inline unsigned xcd_grid(int64_t n_work) { return static_cast<unsigned>((n_work + 7) / 8 * 8); }
+__device__ __forceinline__ int xcd_work_index(int n_work) {      // -1: padding of the grid
+    const int q = n_work >> 3, rem = n_work & 7, xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    if (slot >= q + (xcd < rem ? 1 : 0)) return -1;
+    return xcd * q + (xcd < rem ? xcd : rem) + slot;
+}
+
+// Compute units of the current device (256 when it cannot be asked, e.g. without a GPU).
+int device_compute_units();
+
+// The direct path (tree_attn_direct.hip): launch shape and launch.
+struct DirectPlan {
+    int mb, rg, n_row_tiles, n_splits, r_pad;
+    size_t ws_o_bytes, ws_bytes;
+    double cost;        // estimated cycles
+};
+DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages, int32_t dtype,
+                       bool may_split);
+int32_t launch_direct(const DirectPlan& pl, AttnParams p, int32_t D, int32_t dtype, void* workspace, hipStream_t s);
+
+// Profiling hook state (per host thread): event pairs attached to the main kernel's dispatch
+// (hipExtLaunchKernelGGL: the events then carry the kernel's own begin and end time stamps,
+// without the dispatch latency that events recorded around a launch would include).
+struct ProfileHook {
+    hipEvent_t* start = nullptr;
+    hipEvent_t* stop = nullptr;
+    int32_t n = 0, i = 0;
+};
+extern thread_local ProfileHook g_prof;
+
+template <class Kernel, class... Args>
+static void launch_main(Kernel kernel, dim3 grid, dim3 block, unsigned lds_bytes, hipStream_t s, Args... args) {
+    if (g_prof.i < g_prof.n) {
+        hipExtLaunchKernelGGL(kernel, grid, block, lds_bytes, s, g_prof.start[g_prof.i], g_prof.stop[g_prof.i], 0, args...);
+        ++g_prof.i;
+    } else {
+        hipLaunchKernelGGL(kernel, grid, block, lds_bytes, s, args...);
+    }
+}
+
+__device__ __forceinline__ float bf16_bits_to_float(unsigned short b) {
+    return __uint_as_float(static_cast<unsigned>(b) << 16);
+}
+__device__ __forceinline__ unsigned short float_to_bf16_bits(float f) {
+    unsigned u = __float_as_uint(f);
+    u += 0x7fffu + ((u >> 16) & 1u);           // round to nearest even (finite inputs)
+    return static_cast<unsigned short>(u >> 16);
+}
+// Two fp32 -> one packed pair of bf16 (round to nearest even): v_cvt_pk_bf16_f32.
+__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
+    typedef float floatx2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{lo, hi}, bf16x2));
+}
+
+}  // namespace graft

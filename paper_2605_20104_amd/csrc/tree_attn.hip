@@ -43,22 +43,12 @@
 //     O / sum as fp16 rows with a per-row scale) go to the workspace; a small combine
 //     kernel merges the splits and writes bf16.
 //
-// (2) everything else (fp32 storage, or D = 64): a plain one-workgroup-per-
-//     (node, head) kernel in fp32.  It serves the tiny fp32 configuration and as
-//     an independent GPU cross-check of path (1).
+// (2) everything else (fp32 storage, or D = 64): tree_attn_direct.hip.
 #include <type_traits>
 
-#include <hip/hip_ext.h>
-
-#include "common.h"
+#include "attn_shared.h"
 
 namespace graft {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef short short4_t __attribute__((ext_vector_type(4)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
 constexpr int AT_THREADS = 256;
 constexpr int AT_WAVES = 4;
@@ -69,28 +59,6 @@ constexpr int AT_ROW_BYTES = AT_D * 2;
 constexpr int AT_MAX_MB = 5;            // 16-row MFMA blocks per wavefront (5 * 48 = 240 of 256 AccVGPRs)
 constexpr int AT_MAX_SPLITS = 64;
 constexpr float AT_LAZY_LOG2 = 24.0f;  // a row keeps its reference while exponents stay below 2^24
-
-struct AttnParams {
-    const void* q;
-    const void* k;
-    const void* v;
-    void* out;
-    const int32_t* block_table;
-    const int32_t* prefix_len;
-    const int32_t* n_nodes;
-    const u64* mask;
-    unsigned short* ws_o;   // fp16 [B][Hkv][splits][R_pad/16][D/32] blocks of 1 KB: [lane][2][4], lane = MFMA
-                            // accumulator lane, two adjacent 16-dim tiles per block
-    float* ws_ml;       // [B][Hkv][splits][R_pad][4]  (max in log2 units, sum, scale of the stored row, 0)
-    int64_t page_stride, token_stride, head_stride;
-    int32_t max_pages, B, K_max, Hq, Hkv, G, R, R_pad, n_splits, n_row_tiles;
-    int32_t g_magic;    // ceil(2^16 / G): r / G == (r * g_magic) >> 16 for r < 4096, G <= 16
-    float scale;        // softmax scale
-    float scale_log2e;  // scale * log2(e)
-#ifdef GRAFT_ATTN_STAMPS
-    unsigned long long* stamps;   // timing build: AT_STAMPS values per workgroup, or null
-#endif
-};
 
 // Timing build (-DGRAFT_ATTN_STAMPS, a library of its own: see build.py): the MFMA kernel
 // records when each workgroup passed the points below and writes them to a buffer the caller
@@ -145,15 +113,6 @@ enum AttnStamp {
 #define GRAFT_SPAN_END(k) ((void)0)
 #define GRAFT_STAMPS_WRITE(p, n_stages) ((void)0)
 #endif
-
-__device__ __forceinline__ float bf16_bits_to_float(unsigned short b) {
-    return __uint_as_float(static_cast<unsigned>(b) << 16);
-}
-__device__ __forceinline__ unsigned short float_to_bf16_bits(float f) {
-    unsigned u = __float_as_uint(f);
-    u += 0x7fffu + ((u >> 16) & 1u);           // round to nearest even (finite inputs)
-    return static_cast<unsigned short>(u >> 16);
-}
 
 // ---------------------------------------------------------------------------
 // path (1): MFMA split-KV kernel
@@ -335,12 +294,6 @@ __device__ __forceinline__ void mfma_rowsum(floatx4& l, const bf16x8& ones, cons
         asm volatile(GRAFT_MFMA_GUARD "v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(l) : "v"(ones), "v"(pb));
     else
         asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(l) : "v"(ones), "v"(pb));
-}
-// Two fp32 -> one packed pair of bf16 (round to nearest even): v_cvt_pk_bf16_f32.
-__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
-    typedef float floatx2 __attribute__((ext_vector_type(2)));
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{lo, hi}, bf16x2));
 }
 // A register holding a bit pattern the compiler cannot see through (so it is kept, not
 // rematerialised in front of an MFMA that reads it).
@@ -792,14 +745,10 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(AttnParams p
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave_u = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lg = lane >> 4;
-    // Workgroups go to the 8 XCDs (each with its own L2) round-robin by their linear index.
-    // The row tiles of one (sequence, KV head, split) read the same keys and values: they get
-    // the same XCD and neighbouring slots on it, so that they run side by side and all but the
-    // first reader find the stage in that XCD's L2.
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int rt = slot % p.n_row_tiles;
-    const int unit = (slot / p.n_row_tiles) * 8 + xcd;           // over B * Hkv * n_splits
-    if (unit >= p.B * p.Hkv * p.n_splits) return;                 // grid padding (whole workgroup)
+    const int work = xcd_work_index(p.B * p.Hkv * p.n_splits * p.n_row_tiles);
+    if (work < 0) return;                                         // grid padding (whole workgroup)
+    const int rt = work % p.n_row_tiles;
+    const int unit = work / p.n_row_tiles;                        // over B * Hkv * n_splits
     const int split = unit % p.n_splits;
     const int g = (unit / p.n_splits) % p.Hkv, b = unit / (p.n_splits * p.Hkv);
 
@@ -1313,131 +1262,14 @@ __global__ __launch_bounds__(64 * CB_MAX_WAVES) void tree_attn_combine_kernel(At
 }
 
 // ---------------------------------------------------------------------------
-// path (2): plain fp32 kernel, one workgroup per (head, node, sequence)
-// ---------------------------------------------------------------------------
-template <typename T> __device__ __forceinline__ float load_as_float(const T* p, int64_t i);
-template <> __device__ __forceinline__ float load_as_float<float>(const float* p, int64_t i) { return p[i]; }
-template <> __device__ __forceinline__ float load_as_float<unsigned short>(const unsigned short* p, int64_t i) {
-    return bf16_bits_to_float(p[i]);
-}
-template <typename T> __device__ __forceinline__ void store_from_float(T* p, int64_t i, float v);
-template <> __device__ __forceinline__ void store_from_float<float>(float* p, int64_t i, float v) { p[i] = v; }
-template <> __device__ __forceinline__ void store_from_float<unsigned short>(unsigned short* p, int64_t i, float v) {
-    p[i] = float_to_bf16_bits(v);
-}
-
-__device__ __forceinline__ float block_max_256(float v, float* red) {
-#pragma unroll
-    for (int s = 32; s >= 1; s >>= 1) v = fmaxf(v, __shfl_xor(v, s));
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-}
-__device__ __forceinline__ float block_sum_256(float v, float* red) {
-#pragma unroll
-    for (int s = 32; s >= 1; s >>= 1) v += __shfl_xor(v, s);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    return (red[0] + red[1]) + (red[2] + red[3]);
-}
-
-constexpr int SM_THREADS = 256;
-
-template <typename T, int D>
-__global__ __launch_bounds__(SM_THREADS) void tree_attn_simple_kernel(AttnParams p) {
-    const int h = blockIdx.x, i = blockIdx.y, b = blockIdx.z;
-    const int tid = threadIdx.x;
-    __shared__ float qs[D];
-    __shared__ float ps[SM_THREADS];
-    __shared__ float accs[SM_THREADS];
-    __shared__ float red[SM_THREADS / 64];
-    const int64_t row = (static_cast<int64_t>(b) * p.K_max + i) * p.Hq + h;
-    T* outp = static_cast<T*>(p.out) + row * D;
-    int n = p.n_nodes[b];
-    if (n < 1 || n > p.K_max) n = 0;
-    if (i >= n) {
-        if (tid < D) store_from_float<T>(outp, tid, 0.f);
-        return;
-    }
-    const int cap = p.max_pages * GRAFT_PAGE_SIZE;
-    int P = p.prefix_len[b];
-    P = P < 0 ? 0 : (P > cap ? cap : P);
-    const int total = (P + n) < cap ? (P + n) : cap;
-    const int g = h / p.G;
-    const T* qp = static_cast<const T*>(p.q) + row * D;
-    const T* kc = static_cast<const T*>(p.k);
-    const T* vc = static_cast<const T*>(p.v);
-    const int32_t* table = p.block_table + static_cast<size_t>(b) * p.max_pages;
-    const u64* mp = p.mask + (static_cast<size_t>(b) * p.K_max + i) * GRAFT_MASK_WORDS;
-    const u64 mk0 = mp[0], mk1 = mp[1];
-    if (tid < D) qs[tid] = load_as_float<T>(qp, tid);
-    __syncthreads();
-
-    constexpr int PARTS = SM_THREADS / D;
-    const int d = tid % D, part = tid / D;
-    float acc = 0.f, m_run = -INFINITY, l_run = 0.f;
-    for (int t0 = 0; t0 < total; t0 += SM_THREADS) {
-        const int t = t0 + tid;
-        bool valid = t < P;
-        if (!valid && t < total) {
-            const int j = t - P;
-            valid = ((j < 64 ? mk0 : mk1) >> (j & 63)) & 1ull;
-        }
-        float s = -INFINITY;
-        if (valid) {
-            const int64_t base = static_cast<int64_t>(table[t / GRAFT_PAGE_SIZE]) * p.page_stride +
-                                 static_cast<int64_t>(t % GRAFT_PAGE_SIZE) * p.token_stride +
-                                 static_cast<int64_t>(g) * p.head_stride;
-            float dot = 0.f;
-#pragma unroll 8
-            for (int e = 0; e < D; ++e) dot = __builtin_fmaf(qs[e], load_as_float<T>(kc, base + e), dot);
-            s = dot * p.scale;
-        }
-        const float mt = block_max_256(s, red);
-        const float m_new = fmaxf(m_run, mt);
-        const float pr = (valid && m_new != -INFINITY) ? __expf(s - m_new) : 0.f;
-        const float alpha = (m_run == -INFINITY) ? 0.f : __expf(m_run - m_new);
-        ps[tid] = pr;
-        const float lsum = block_sum_256(pr, red);        // its barriers also publish ps[]
-        acc *= alpha;
-        l_run = l_run * alpha + lsum;
-        const int lim = (total - t0) < SM_THREADS ? (total - t0) : SM_THREADS;
-        for (int tt = part; tt < lim; tt += PARTS) {
-            const float pp = ps[tt];
-            if (pp != 0.f) {
-                const int tk = t0 + tt;
-                const int64_t base = static_cast<int64_t>(table[tk / GRAFT_PAGE_SIZE]) * p.page_stride +
-                                     static_cast<int64_t>(tk % GRAFT_PAGE_SIZE) * p.token_stride +
-                                     static_cast<int64_t>(g) * p.head_stride;
-                acc = __builtin_fmaf(pp, load_as_float<T>(vc, base + d), acc);
-            }
-        }
-        m_run = m_new;
-        __syncthreads();
-    }
-    accs[tid] = acc;
-    __syncthreads();
-    if (tid < D) {
-        float sum = 0.f;
-#pragma unroll
-        for (int k = 0; k < PARTS; ++k) sum += accs[k * D + tid];
-        store_from_float<T>(outp, tid, l_run > 0.f ? sum / l_run : 0.f);
-    }
-}
-
-// ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
 struct AttnPlan {
-    bool mfma;
     int mb, n_row_tiles, n_splits, r_pad;
     size_t ws_o_bytes, ws_bytes;
 };
 
-// Compute units of the current device (256 when it cannot be asked, e.g. without a GPU).
-static int device_compute_units() {
+int device_compute_units() {
     static int cached = 0;
     if (cached == 0) {
         int dev = 0, n = 0;
@@ -1455,6 +1287,9 @@ static int device_compute_units() {
 static thread_local int g_force_splits = 0, g_force_row_tiles = 0;
 #endif
 
+// bf16, D = 128 goes to path (1)
+static bool mfma_shape(int32_t D, int32_t dtype) { return dtype == GRAFT_BF16 && D == AT_D; }
+
 // Launch shape of the MFMA path.  One workgroup per compute unit is resident at a time, so
 // the job runs in ceil(workgroups / CUs) rounds, each as long as one workgroup's pass: a
 // fixed part (set-up, Q conversion, writing the partial results) plus its stages.  The
@@ -1462,11 +1297,8 @@ static thread_local int g_force_splits = 0, g_force_row_tiles = 0;
 // 3300 MB + 8000); the plan takes the row tiling (MB <= 5 row blocks per wavefront) and the
 // number of splits (<= 64, each with at most AT_MAX_SPLIT_PAGES pages) that make the
 // estimate smallest.  It depends on the capacity max_pages, not on the actual lengths.
-static AttnPlan make_plan(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages,
-                          int32_t dtype) {
+static AttnPlan make_plan(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t max_pages) {
     AttnPlan pl{};
-    pl.mfma = (dtype == GRAFT_BF16 && D == AT_D);
-    if (!pl.mfma) return pl;
     const int R = K_max * (Hq / Hkv);
     const int rows_per_mb = AT_WAVES * 16;                       // rows a workgroup covers per MB
     const int64_t stages = (static_cast<int64_t>(max_pages) * GRAFT_PAGE_SIZE + AT_STAGE - 1) / AT_STAGE;
@@ -1517,26 +1349,11 @@ static bool attn_shape_ok(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int
            max_pages <= AT_MAX_SPLITS * AT_MAX_SPLIT_PAGES;    // 64 splits x 4096 pages = 4 Mi tokens
 }
 
-// Profiling hook state (per host thread): event pairs attached to the main kernel's dispatch
-// (hipExtLaunchKernelGGL: the events then carry the kernel's own begin and end time stamps,
-// without the dispatch latency that events recorded around a launch would include).
-static thread_local hipEvent_t* g_prof_start = nullptr;
-static thread_local hipEvent_t* g_prof_stop = nullptr;
-static thread_local int32_t g_prof_n = 0, g_prof_i = 0;
+thread_local ProfileHook g_prof;
 #ifdef GRAFT_ATTN_STAMPS
 static thread_local unsigned long long* g_stamps = nullptr;      // device buffer of the timing build
 static thread_local size_t g_stamps_bytes = 0;
 #endif
-
-template <class Kernel>
-static void launch_main(Kernel kernel, dim3 grid, dim3 block, hipStream_t s, const AttnParams& p) {
-    if (g_prof_i < g_prof_n) {
-        hipExtLaunchKernelGGL(kernel, grid, block, 0, s, g_prof_start[g_prof_i], g_prof_stop[g_prof_i], 0, p);
-        ++g_prof_i;
-    } else {
-        hipLaunchKernelGGL(kernel, grid, block, 0, s, p);
-    }
-}
 
 }  // namespace graft
 
@@ -1544,15 +1361,13 @@ extern "C" size_t graft_tree_attn_workspace_bytes(int32_t B, int32_t K_max, int3
                                                   int32_t D, int32_t max_pages, int32_t dtype) {
     if (!graft::attn_shape_ok(B, K_max, Hq, Hkv, D, max_pages)) return 0;
     if (dtype != GRAFT_F32 && dtype != GRAFT_BF16) return 0;
-    return graft::make_plan(B, K_max, Hq, Hkv, D, max_pages, dtype).ws_bytes;
+    if (!graft::mfma_shape(D, dtype)) return graft::plan_direct(B, K_max, Hq, Hkv, D, max_pages, dtype, true).ws_bytes;
+    return graft::make_plan(B, K_max, Hq, Hkv, max_pages).ws_bytes;
 }
 
 extern "C" int32_t graft_attn_profile_events(void** start_events, void** stop_events, int32_t n) {
     if (n < 0 || (n > 0 && (!start_events || !stop_events))) return GRAFT_ERR_NULL;
-    graft::g_prof_start = reinterpret_cast<hipEvent_t*>(start_events);
-    graft::g_prof_stop = reinterpret_cast<hipEvent_t*>(stop_events);
-    graft::g_prof_n = n;
-    graft::g_prof_i = 0;
+    graft::g_prof = {reinterpret_cast<hipEvent_t*>(start_events), reinterpret_cast<hipEvent_t*>(stop_events), n, 0};
     return GRAFT_OK;
 }
 
@@ -1644,9 +1459,6 @@ extern "C" int32_t graft_tree_attn(const void* q, const void* k_cache, const voi
         page_stride < 1 || token_stride < D || token_stride >= (1 << 26) || head_stride < D || token_stride % 8 != 0 ||
         head_stride % 8 != 0 || page_stride % 8 != 0 || !(scale > 0.f) || !(scale < 1e30f))
         return GRAFT_ERR_SHAPE;
-    const AttnPlan pl = make_plan(B, K_max, Hq, Hkv, D, max_pages, dtype);
-    if (pl.ws_bytes > 0 && (!workspace || workspace_bytes < pl.ws_bytes)) return GRAFT_ERR_WORKSPACE;
-
     AttnParams p{};
     p.q = q; p.k = k_cache; p.v = v_cache; p.out = out;
     p.block_table = block_table; p.prefix_len = prefix_len; p.n_nodes = n_nodes;
@@ -1659,31 +1471,30 @@ extern "C" int32_t graft_tree_attn(const void* q, const void* k_cache, const voi
     p.scale_log2e = scale * 1.4426950408889634f;
     hipStream_t s = static_cast<hipStream_t>(stream);
 
-    if (!pl.mfma) {
-        dim3 grid(Hq, K_max, B);
-        if (dtype == GRAFT_F32) {
-            if (D == 64) launch_main(tree_attn_simple_kernel<float, 64>, grid, dim3(SM_THREADS), s, p);
-            else launch_main(tree_attn_simple_kernel<float, 128>, grid, dim3(SM_THREADS), s, p);
-        } else {
-            launch_main(tree_attn_simple_kernel<unsigned short, 64>, grid, dim3(SM_THREADS), s, p);
-        }
-        return check_launch();
+    if (!mfma_shape(D, dtype)) {
+        // these shapes have always run without a workspace: a caller that brings none, or too
+        // little, gets a launch that does not split the keys over workgroups
+        DirectPlan dp = plan_direct(B, K_max, Hq, Hkv, D, max_pages, dtype, true);
+        if (dp.ws_bytes > 0 && (!workspace || workspace_bytes < dp.ws_bytes))
+            dp = plan_direct(B, K_max, Hq, Hkv, D, max_pages, dtype, false);
+        return launch_direct(dp, p, D, dtype, workspace, s);
     }
 
+    const AttnPlan pl = make_plan(B, K_max, Hq, Hkv, max_pages);
+    if (pl.ws_bytes > 0 && (!workspace || workspace_bytes < pl.ws_bytes)) return GRAFT_ERR_WORKSPACE;
     p.R_pad = pl.r_pad; p.n_splits = pl.n_splits; p.n_row_tiles = pl.n_row_tiles;
     p.ws_o = static_cast<unsigned short*>(workspace);
     p.ws_ml = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + pl.ws_o_bytes);
-    const int64_t n_units = static_cast<int64_t>(B) * Hkv * pl.n_splits;
-    dim3 grid(static_cast<unsigned>(((n_units + 7) / 8) * 8 * pl.n_row_tiles));
+    const dim3 grid(xcd_grid(static_cast<int64_t>(B) * Hkv * pl.n_splits * pl.n_row_tiles));
 #ifdef GRAFT_ATTN_STAMPS
     p.stamps = static_cast<size_t>(grid.x) * AT_STAMPS * sizeof(unsigned long long) <= g_stamps_bytes ? g_stamps : nullptr;
 #endif
     switch (pl.mb) {
-        case 1: launch_main(tree_attn_mfma_kernel<1>, grid, dim3(AT_THREADS), s, p); break;
-        case 2: launch_main(tree_attn_mfma_kernel<2>, grid, dim3(AT_THREADS), s, p); break;
-        case 3: launch_main(tree_attn_mfma_kernel<3>, grid, dim3(AT_THREADS), s, p); break;
-        case 4: launch_main(tree_attn_mfma_kernel<4>, grid, dim3(AT_THREADS), s, p); break;
-        default: launch_main(tree_attn_mfma_kernel<5>, grid, dim3(AT_THREADS), s, p); break;
+        case 1: launch_main(tree_attn_mfma_kernel<1>, grid, dim3(AT_THREADS), 0, s, p); break;
+        case 2: launch_main(tree_attn_mfma_kernel<2>, grid, dim3(AT_THREADS), 0, s, p); break;
+        case 3: launch_main(tree_attn_mfma_kernel<3>, grid, dim3(AT_THREADS), 0, s, p); break;
+        case 4: launch_main(tree_attn_mfma_kernel<4>, grid, dim3(AT_THREADS), 0, s, p); break;
+        default: launch_main(tree_attn_mfma_kernel<5>, grid, dim3(AT_THREADS), 0, s, p); break;
     }
     int32_t rc = check_launch();
     if (rc != GRAFT_OK || pl.n_splits == 1) return rc;

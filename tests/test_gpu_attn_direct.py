@@ -1,0 +1,105 @@
+"""GPU parity of the attention path for fp32 storage and for bf16 with head size 64, at the sizes
+where its tiling can go wrong, against the CPU oracle (MI355X only).
+
+Bounds.  fp32: 1e-4, as for every fp32 case.  bf16: scores, softmax and sums are fp32 and the
+probabilities keep 17 bits, so what is left is the rounding of the result to bf16: 8 significant
+bits, so at most 2^-8 of the value (half of the spacing 2^-7 right above a power of two), plus 1e-4
+for everything before it."""
+import numpy as np
+import pytest
+import torch
+
+import inputs
+import oracle
+import paper_2605_20104_amd as graft
+from gpu_util import dev, host
+from test_gpu_attn import gpu_mask, shape_workload
+
+pytestmark = pytest.mark.gpu
+
+# (dtype, D, B, K, Hq, Hkv, P, layout, workspace): tiles are 32 keys (bf16) or 16 (fp32)
+CASES = [
+    ("f32", 64, 1, 1, 1, 1, 0, "head_major", True),            # a lone root, empty prefix
+    ("f32", 128, 1, 1, 2, 1, 15, "head_major", True),          # exactly one tile
+    ("f32", 128, 1, 2, 2, 1, 15, "token_major", True),         # one key more
+    ("f32", 64, 2, 17, 6, 2, 300, "head_major", True),         # rows and keys off every boundary
+    ("f32", 128, 1, 40, 32, 8, 1000, "head_major", True),
+    ("f32", 128, 2, 128, 32, 2, 90, "head_major", True),       # 2048 rows: the most row tiles, both mask words
+    ("f32", 64, 1, 4, 1, 1, 9000, "head_major", False),        # one workgroup for all keys: a wavefront walks many tiles
+    ("f32", 128, 3, 9, 4, 4, 2500, "token_major", False),
+    ("bf16", 64, 1, 1, 1, 1, 0, "head_major", True),
+    ("bf16", 64, 1, 1, 4, 4, 31, "head_major", True),
+    ("bf16", 64, 1, 2, 4, 4, 31, "token_major", True),
+    ("bf16", 64, 2, 33, 8, 2, 700, "head_major", True),
+    ("bf16", 64, 1, 60, 32, 8, 2048, "token_major", True),
+    ("bf16", 64, 4, 128, 16, 1, 500, "head_major", True),      # 2048 rows
+    ("bf16", 64, 1, 3, 2, 1, 9001, "head_major", False),
+    ("bf16", 64, 16, 24, 16, 8, 333, "head_major", True),      # enough units for one split
+    ("bf16", 64, 1, 64, 16, 2, 12000, "head_major", True),     # many splits, wide row tiles
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "%s_D%d_B%d_K%d_Hq%d_Hkv%d_P%d_%s_%s" % c)
+def test_direct_path(case):
+    dtype, D, B, K, Hq, Hkv, P, layout, with_ws = case
+    w = shape_workload(B, K, Hq, Hkv, D, P, dtype=dtype)
+    rng = np.random.default_rng(P + K)
+    att = inputs.make_attention_inputs(w, seed=P + K, layout=layout)
+    parent = np.stack([inputs.random_recursive_tree(rng, K, 8) for _ in range(B)])
+    n_nodes, prefix = np.full(B, K, np.int32), np.full(B, P, np.int32)
+    if B > 1:                                                  # ragged: fewer nodes, shorter prefixes, one absent tree
+        n_nodes[1:] = rng.integers(1, K + 1, B - 1)
+        prefix[1:] = rng.integers(0, P + 1, B - 1)
+        n_nodes[-1] = 0 if B > 2 else n_nodes[-1]
+    mask = gpu_mask(parent, n_nodes, prefix)
+    ws = None if with_ws else torch.empty(0, dtype=torch.uint8, device="cuda")
+    out = torch.full((B, K, Hq, D), 7.0, dtype=torch.float32 if dtype == "f32" else torch.bfloat16, device="cuda")
+    graft.graft_tree_attn(dev(att["q"][0], dtype), dev(att["k_cache"][0], dtype), dev(att["v_cache"][0], dtype), att["strides"],
+                          dev(att["block_table"]), dev(prefix), dev(n_nodes), mask, Hkv, att["scale"], out=out, workspace=ws)
+    got = host(out).astype(np.float64)
+    rows = None
+    if B * K * Hq * (P + K) > 3_000_000:                       # a sample that has the first and the last row of every sequence
+        rows = [(b, int(rng.integers(K)), int(rng.integers(Hq))) for b in range(B) for _ in range(24)]
+        rows += [(b, i, h) for b in range(B) for i in (0, K - 1) for h in (0, Hq - 1)]
+    ref = oracle.tree_attn(att["q"][0], att["k_cache"][0], att["v_cache"][0], dtype, att["strides"], att["block_table"], prefix,
+                           n_nodes, parent, Hq, Hkv, D, 16, att["scale"], rows=rows)
+    sel = got if rows is None else np.stack([got[r] for r in rows])
+    bound = 1e-4 + (0.0 if dtype == "f32" else 2.0 ** -8) * np.abs(ref)
+    err = np.abs(sel - ref)
+    assert np.isfinite(got).all()
+    assert (err <= bound).all(), "error %.3e, bound there %.3e" % (err.max(), bound.flat[(err - bound).argmax()])
+    for b in range(B):
+        assert (got[b, n_nodes[b]:] == 0).all()                # rows of absent nodes
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 64)])
+def test_scores_that_keep_rising(dtype, D):
+    """Scores rising by far more than the lazy bound along the sequence: the reference is raised again and
+    again; falling scores keep the first one.  Bound: a dot product of D equal terms summed in fp32 is off by
+    at most D/2 * 2^-24 of itself (D partial sums, half of the full one on average), which moves a weight by
+    that fraction of the largest score and the result by as much times the largest |v|; plus, for bf16, the
+    rounding of the result."""
+    w = shape_workload(1, 24, 4, 2, D, 1500, dtype=dtype)
+    att = inputs.make_attention_inputs(w, seed=3)
+    conv = (lambda a: a) if dtype == "f32" else inputs.bf16_bits_to_f32
+    back = (lambda a: a.astype(np.float32)) if dtype == "f32" else inputs.f32_to_bf16_bits
+    k, q = conv(att["k_cache"][0]).copy(), conv(att["q"][0]).copy()
+    for lp in range(att["pages_per_seq"]):
+        t = lp * 16 + np.arange(16)
+        k[att["block_table"][0, lp]] = (t * 0.05)[None, :, None]
+    q[:] = 1.0
+    q[:, :, 1::2, :] = -1.0
+    att["k_cache"], att["q"] = [back(k)], [back(q)]
+    parent = np.stack([inputs.random_recursive_tree(np.random.default_rng(3), w.K, 8)])
+    n, p = np.array([w.K], np.int32), np.array([w.P], np.int32)
+    for ws in (None, torch.empty(0, dtype=torch.uint8, device="cuda")):
+        out = graft.graft_tree_attn(dev(att["q"][0], dtype), dev(att["k_cache"][0], dtype), dev(att["v_cache"][0], dtype),
+                                    att["strides"], dev(att["block_table"]), dev(p), dev(n), gpu_mask(parent, n, p), w.Hkv,
+                                    att["scale"], workspace=ws)
+        ref = oracle.tree_attn(att["q"][0], att["k_cache"][0], att["v_cache"][0], dtype, att["strides"], att["block_table"], p, n,
+                               parent, w.Hq, w.Hkv, w.D, 16, att["scale"])
+        err = np.abs(host(out).astype(np.float64) - ref)
+        s_max = w.P * 0.05 * D * att["scale"]
+        bound = D / 2 * 2.0 ** -24 * s_max * np.abs(conv(att["v_cache"][0])).max()
+        print("largest score %.0f, bound %.1e, max error %.1e" % (s_max, bound, err.max()))
+        assert (err <= bound + (0.0 if dtype == "f32" else 2.0 ** -8) * np.abs(ref)).all(), err.max()
