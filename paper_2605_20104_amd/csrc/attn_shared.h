@@ -8,6 +8,7 @@ namespace graft {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
@@ -90,7 +91,6 @@ __device__ __forceinline__ unsigned short float_to_bf16_bits(float f) {
 // Two fp32 -> one packed pair of bf16 (round to nearest even): v_cvt_pk_bf16_f32.
 __device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
     typedef float floatx2 __attribute__((ext_vector_type(2)));
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     return __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{lo, hi}, bf16x2));
 }
 

@@ -1,11 +1,9 @@
 // graft_tree_attn, direct path: fp32 storage (any head size) and bf16 with D = 64.
 //
-// Keys and values go from memory straight into registers, in the layout the matrix
-// instructions take them in; no LDS staging and no barrier inside the loop.  That is possible
-// because a wavefront owns its keys: the wavefronts of a workgroup split a key range between
-// them (kg key groups), as well as the query rows (rg row groups of MB 16-row blocks), and
-// merge at the end through LDS, so that a short prefix is spread over the chip with few or no
-// partial results in memory.
+// A wavefront owns its keys: the wavefronts of a workgroup split a key range between them (kg
+// key groups), as well as the query rows (rg row groups of MB 16-row blocks), walk their tiles (32
+// keys in bf16, 16 in fp32) without a barrier and merge at the end through LDS, so that a short
+// prefix is spread over the chip with few or no partial results in memory.
 //   fp32 : v_mfma_f32_16x16x4_f32 (full fp32 products and sums, 32 cycles each).  The kernel is
 //          bound by them: 64 (D = 128) or 32 (D = 64) per 16 keys and 16 rows.
 //   bf16 : v_mfma_f32_16x16x32_bf16 on raw Q and K (exact products, fp32 sums); the softmax scale
@@ -15,15 +13,21 @@
 // Operand layouts (lane = 16 lg + l16).  First product: S^T = K Q^T, A = K (key l16), B = Q^T
 // (row l16), so a lane gets 4 keys (4 lg + i) of one row, and these are the B operand of the
 // second product O^T = V^T P^T without any exchange between lanes: its contraction index runs
-// over the same keys (16 c + 4 lg + i).  Its A operand wants, per lane, one dim of those keys: the
-// assignment of dims to the MFMA's 16 rows is free, so a lane loads a row piece of D/16 (fp32: 4)
-// consecutive dims per key with one wide load and uses one of them per MFMA; bf16 pairs of keys
-// are interleaved with v_perm_b32.
+// over the same keys (16 c + 4 lg + i).  Its A operand wants one dim of those keys per lane: in
+// fp32 a lane loads four consecutive dims of a key and uses one per MFMA (the assignment of dims
+// to the MFMA's 16 rows is free), in bf16 the LDS transpose read does it.
+//
+// Neighbouring lanes of the K operand are different keys, a row apart in memory: loaded like that,
+// every lane's 16 bytes are an access of their own to the vector cache, and the loads bound the
+// kernel (3000 cycles per tile of all eight wavefronts, whatever the arithmetic).  So K, and V in
+// bf16, are loaded as they lie in memory, 1 KB of consecutive rows per instruction, and turned
+// in a wavefront-private piece of LDS (no barrier), K chunks and V segments XOR-swizzled with the
+// row.  The next tile's loads are issued as soon as the registers of the current one have gone to
+// LDS.
 //
 // Latency: lengths -> page table -> first keys are three dependent trips; Q and the ancestor
 // masks travel with the lengths.  The table entries of a wavefront's tiles sit in one vector
-// register (lane = tile and page), one trip for 32 (fp32: 64) tiles.  The next tile's keys and
-// values are requested before the current tile is computed.
+// register (lane = tile and page), one trip for 32 (fp32: 64) tiles.
 #include <type_traits>
 
 #include "attn_shared.h"
@@ -34,6 +38,12 @@ constexpr int DR_WAVES = 8;                     // wavefronts per workgroup, two
 constexpr int DR_THREADS = 64 * DR_WAVES;
 constexpr float DR_LAZY_LOG2 = 16.0f;           // a row keeps its reference while exponents stay below 2^16
 constexpr int DR_MAX_SPLITS = 32;
+constexpr int DR_MASK_BYTES = 2048;             // ancestor masks of a sequence
+constexpr int DR_LDS_BYTES = 160 * 1024;
+
+__device__ __forceinline__ unsigned lds_offset(const void* p) {
+    return static_cast<unsigned>(reinterpret_cast<size_t>((const __attribute__((address_space(3))) unsigned char*)(p)));
+}
 
 __device__ __forceinline__ float rows_sum_f32(float v) {
     {
@@ -49,51 +59,74 @@ __device__ __forceinline__ float rows_sum_f32(float v) {
     return v;
 }
 
-// Per storage type: keys per tile, registers of a tile's keys and values, the two products.
+// Per storage type: tile shape, LDS layout, the two products.
 template <typename T, int D> struct DirectOps;
+
+// K of a tile on its way from memory to LDS: 1 KB of consecutive rows per instruction.
+template <int ROW, int TK> struct StagedKeys {
+    static constexpr int N = TK * ROW / 1024, RPI = 1024 / ROW, CPR = ROW / 16;
+    uintx4 r[N];
+    static constexpr int page(int j) { return j * RPI / GRAFT_PAGE_SIZE; }
+    static constexpr int row0(int j) { return j * RPI % GRAFT_PAGE_SIZE; }
+    // row r of K to LDS, its 16-byte chunks in the order chunk ^ (r & 7)
+    __device__ __forceinline__ void stage(unsigned char* Ks, int lane) const {
+        const int lrow = lane / CPR, chunk = lane % CPR;
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const int row = j * RPI + lrow;
+            *reinterpret_cast<uintx4*>(Ks + row * ROW + ((chunk ^ (row & 7)) * 16)) = r[j];
+        }
+    }
+};
 
 template <int D> struct DirectOps<float, D> {
     static constexpr int TK = 16;               // keys per tile
     static constexpr int NO = D / 16;           // floatx4 accumulators per row block
     static constexpr int NC = 1;                // score tiles of 16 keys
+    static constexpr int ROW = D * 4;           // bytes
+    static constexpr bool SUM_MFMA = false;
     struct Q { floatx4 v[D / 16]; };
-    struct K { floatx4 r[D / 16]; };
-    struct V { floatx4 r[4][D / 64]; };
     static __device__ __forceinline__ void load_q(Q& q, const float* row, int lg) {
 #pragma unroll
         for (int s = 0; s < D / 16; ++s) q.v[s] = *reinterpret_cast<const floatx4*>(row + 16 * s + 4 * lg);
     }
-    // a lane's byte offset inside its key's row, for K and for V
-    static __device__ __forceinline__ unsigned k_lane(int lg) { return 16 * lg; }
-    static __device__ __forceinline__ unsigned v_lane(int l16) { return 16 * l16; }
-    static __device__ __forceinline__ void load_k(K& t, int, const char* base, unsigned off) {
+    template <int MB>
+    static __device__ __forceinline__ void scores(const unsigned char* Ks, const Q (&q)[MB], floatx4 (&s)[MB][NC], int l16, int lg) {
+        const unsigned char* row = Ks + l16 * ROW;
+        const int x = ((lg ^ l16) & 3) * 16 + (l16 & 4) * 16;      // chunk (4 d + lg) ^ (l16 & 7): bits 0-1 and, for even d, bit 2
 #pragma unroll
-        for (int s = 0; s < D / 16; ++s) t.r[s] = *reinterpret_cast<const floatx4*>(base + off + 64 * s);
+        for (int d = 0; d < D / 16; ++d) {
+            const floatx4 k = *reinterpret_cast<const floatx4*>(row + ((x ^ ((d & 1) * 64)) + (d >> 1) * 128));
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int rb = 0; rb < MB; ++rb)
+                    s[rb][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(k[j], q[rb].v[d][j], d == 0 && j == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : s[rb][0], 0, 0, 0);
+        }
     }
-    // values of key i (of this lane's four)
-    static __device__ __forceinline__ void load_v(V& t, int, int i, const char* base, unsigned off) {
+    static constexpr bool V_STAGED = false;     // values come in operand layout already: 256 bytes of a row per 16 lanes
+    struct V { floatx4 r[4][D / 64]; };         // key 4 lg + i, dims 64 h + 4 l16 ..
+    static __device__ __forceinline__ unsigned v_lane(int lane) { return 16 * (lane & 15); }
+    static __device__ __forceinline__ int v_row(int lane, int j) { return 4 * (lane >> 4) + j; }
+    static constexpr int NV = 4;                // row groups of a tile's values, page of each, its first row in the page
+    static constexpr int v_page(int) { return 0; }
+    static constexpr int v_row0(int j) { return j; }
+    static __device__ __forceinline__ void load_v(V& t, int j, const char* base, unsigned off) {
 #pragma unroll
-        for (int h = 0; h < D / 64; ++h) t.r[i][h] = *reinterpret_cast<const floatx4*>(base + off + 256 * h);
+        for (int h = 0; h < D / 64; ++h) t.r[j][h] = *reinterpret_cast<const floatx4*>(base + off + 256 * h);
     }
-    static __device__ __forceinline__ void scores(const K& t, const Q& q, floatx4 (&s)[NC]) {
-        s[0] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int d = 0; d < D / 16; ++d)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) s[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.r[d][j], q.v[d][j], s[0], 0, 0, 0);
-    }
-    static constexpr bool SUM_MFMA = false;
-    static constexpr bool FREES_V = false;      // accumulate() still reads the loaded values
-    struct A {};
-    static __device__ __forceinline__ void arrange(const V&, A&) {}
-    static __device__ __forceinline__ void accumulate(const V& t, const A&, const floatx4 (&p)[NC], floatx4 (&o)[NO], floatx4&) {
+    template <int MB>
+    static __device__ __forceinline__ void accumulate(const V& t, const unsigned char*, const floatx4 (&p)[MB][NC], floatx4 (&o)[MB][NO],
+                                                      floatx4 (&)[MB], int, int) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int h = 0; h < D / 64; ++h)
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    o[4 * h + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.r[i][h][j], p[0][i], o[4 * h + j], 0, 0, 0);
+#pragma unroll
+                    for (int rb = 0; rb < MB; ++rb)
+                        o[rb][4 * h + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.r[i][h][j], p[rb][0][i], o[rb][4 * h + j], 0, 0, 0);
     }
     // the four consecutive dims starting at dim(u, lg), u < D/16
     static __device__ __forceinline__ int dim(int u, int lg) { return 64 * (u >> 2) + 16 * lg + 4 * (u & 3); }
@@ -107,87 +140,94 @@ template <int D> struct DirectOps<__bf16, D> {
     static constexpr int TK = 32;
     static constexpr int NO = D / 16;
     static constexpr int NC = 2;
-    static constexpr int W = D / 32;            // 32-bit words of a lane's row piece (D/16 dims)
+    static constexpr int ROW = D * 2;
+    static constexpr bool SUM_MFMA = true;      // row sums through the matrix cores, which have time left here
+    static constexpr int SEG = ROW / 32 - 1;    // V rows: 32-byte segment ^ (row & SEG)
     struct Q { bf16x8 v[D / 32]; };
-    struct K { bf16x8 r[2][D / 32]; };
-    struct V { unsigned r[8][W]; };
     static __device__ __forceinline__ void load_q(Q& q, const __bf16* row, int lg) {
 #pragma unroll
         for (int s = 0; s < D / 32; ++s) q.v[s] = *reinterpret_cast<const bf16x8*>(row + 32 * s + 8 * lg);
     }
-    static __device__ __forceinline__ unsigned k_lane(int lg) { return 16 * lg; }
-    static __device__ __forceinline__ unsigned v_lane(int l16) { return 4 * W * l16; }
-    static __device__ __forceinline__ void load_k(K& t, int c, const char* base, unsigned off) {
-#pragma unroll
-        for (int s = 0; s < D / 32; ++s) t.r[c][s] = *reinterpret_cast<const bf16x8*>(base + off + 64 * s);
+    static constexpr bool V_STAGED = true;
+    static constexpr int NV = TK * ROW / 1024, RPI = 1024 / ROW;       // instructions, rows per instruction
+    struct V { uintx4 r[NV]; };
+    static __device__ __forceinline__ unsigned v_lane(int lane) { return 16 * (lane % (ROW / 16)); }
+    static __device__ __forceinline__ int v_row(int lane, int j) { return v_row0(j) + lane / (ROW / 16); }
+    static constexpr int v_page(int j) { return j * RPI / GRAFT_PAGE_SIZE; }
+    static constexpr int v_row0(int j) { return j * RPI % GRAFT_PAGE_SIZE; }
+    static __device__ __forceinline__ void load_v(V& t, int j, const char* base, unsigned off) {
+        t.r[j] = *reinterpret_cast<const uintx4*>(base + off);
     }
-    static __device__ __forceinline__ void load_v(V& t, int c, int i, const char* base, unsigned off) {
-        if constexpr (W == 2) {
-            const uintx2 x = *reinterpret_cast<const uintx2*>(base + off);
-            t.r[4 * c + i][0] = x[0];
-            t.r[4 * c + i][1] = x[1];
-        } else {
-            const uintx4 x = *reinterpret_cast<const uintx4*>(base + off);
+    // row r of V to LDS, its 32-byte segments in the order segment ^ (r & SEG)
+    static __device__ __forceinline__ void stage_v(const V& t, unsigned char* Vs, int lane) {
+        const int lrow = lane / (ROW / 16), chunk = lane % (ROW / 16);
 #pragma unroll
-            for (int w = 0; w < W; ++w) t.r[4 * c + i][w] = x[w];
+        for (int j = 0; j < NV; ++j) {
+            const int row = j * RPI + lrow;
+            *reinterpret_cast<uintx4*>(Vs + row * ROW + ((chunk ^ ((row & SEG) << 1)) * 16)) = t.r[j];
         }
     }
-    static __device__ __forceinline__ void scores(const K& t, const Q& q, floatx4 (&s)[NC]) {
+    template <int MB>
+    static __device__ __forceinline__ void scores(const unsigned char* Ks, const Q (&q)[MB], floatx4 (&s)[MB][NC], int l16, int lg) {
+        const unsigned char* row = Ks + l16 * ROW;
+        const int x = ((lg ^ l16) & 3) * 16 + (l16 & 4) * 16;
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            s[c] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int c = 0; c < 2; ++c)
 #pragma unroll
-            for (int d = 0; d < D / 32; ++d) s[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t.r[c][d], q.v[d], s[c], 0, 0, 0);
-        }
-    }
-    // V^T operands: one dim, eight keys per lane
-    static constexpr bool SUM_MFMA = true;      // row sums through the matrix cores, which have time left here
-    static constexpr bool FREES_V = true;       // arrange() copies: the next values can be requested after it
-    struct A { uintx4 a[NO]; };
-    static __device__ __forceinline__ void arrange(const V& t, A& v) {
+            for (int d = 0; d < D / 32; ++d) {
+                const bf16x8 k = *reinterpret_cast<const bf16x8*>(row + ((x ^ ((d & 1) * 64)) + (d >> 1) * 128 + c * 16 * ROW));
 #pragma unroll
-        for (int w = 0; w < W; ++w)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                v.a[2 * w][j] = __builtin_amdgcn_perm(t.r[2 * j + 1][w], t.r[2 * j][w], 0x05040100u);
-                v.a[2 * w + 1][j] = __builtin_amdgcn_perm(t.r[2 * j + 1][w], t.r[2 * j][w], 0x07060302u);
+                for (int rb = 0; rb < MB; ++rb)
+                    s[rb][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k, q[rb].v[d], d == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : s[rb][c], 0, 0, 0);
             }
     }
-    static __device__ __forceinline__ void accumulate(const V&, const A& v, const floatx4 (&p)[NC], floatx4 (&o)[NO], floatx4& sum) {
-        uintx4 hi, lo;                          // p = hi + lo, both bf16 (hi: truncated, so p - hi is exact)
+    template <int MB>
+    static __device__ __forceinline__ void accumulate(const V&, const unsigned char* Vs, const floatx4 (&p)[MB][NC], floatx4 (&o)[MB][NO],
+                                                      floatx4 (&sum)[MB], int l16, int lg) {
+        bf16x8 ph[MB], pl[MB];                  // p = hi + lo, both bf16 (hi: truncated, so p - hi is exact)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float p0 = p[j >> 1][2 * (j & 1)], p1 = p[j >> 1][2 * (j & 1) + 1];
-            const unsigned b0 = __float_as_uint(p0), b1 = __float_as_uint(p1);
-            hi[j] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
-            lo[j] = pack_bf16(p0 - __uint_as_float(b0 & 0xffff0000u), p1 - __uint_as_float(b1 & 0xffff0000u));
+        for (int rb = 0; rb < MB; ++rb) {
+            uintx4 hi, lo;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float p0 = p[rb][j >> 1][2 * (j & 1)], p1 = p[rb][j >> 1][2 * (j & 1) + 1];
+                const unsigned b0 = __float_as_uint(p0), b1 = __float_as_uint(p1);
+                hi[j] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
+                lo[j] = pack_bf16(p0 - __uint_as_float(b0 & 0xffff0000u), p1 - __uint_as_float(b1 & 0xffff0000u));
+            }
+            ph[rb] = __builtin_bit_cast(bf16x8, hi);
+            pl[rb] = __builtin_bit_cast(bf16x8, lo);
         }
-        const bf16x8 ph = __builtin_bit_cast(bf16x8, hi), pl = __builtin_bit_cast(bf16x8, lo);
+        // rows 16 c + 4 lg + (l16 >> 2): the transpose read turns 4 keys x 16 dims into "lane = dim, 4 keys"
+        const int row0 = 4 * lg + (l16 >> 2);
+        const unsigned base = lds_offset(Vs) + row0 * ROW + ((row0 & SEG) << 5) + 8 * (l16 & 3);
+#pragma unroll
+        for (int e = 0; e < NO; ++e) {
+            bf16x8 a;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const short4_t r = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (short4_t __attribute__((address_space(3)))*)(static_cast<size_t>((base ^ (e << 5)) + c * 16 * ROW)));
+                const bf16x4 r4 = __builtin_bit_cast(bf16x4, r);
+                a[4 * c] = r4[0];
+                a[4 * c + 1] = r4[1];
+                a[4 * c + 2] = r4[2];
+                a[4 * c + 3] = r4[3];
+            }
+#pragma unroll
+            for (int rb = 0; rb < MB; ++rb) o[rb][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ph[rb], o[rb][e], 0, 0, 0);
+#pragma unroll
+            for (int rb = 0; rb < MB; ++rb) o[rb][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, pl[rb], o[rb][e], 0, 0, 0);
+        }
         const bf16x8 ones = __builtin_bit_cast(bf16x8, uintx4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
-        sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, ph, sum, 0, 0, 0);
 #pragma unroll
-        for (int e = 0; e < NO; ++e) {
-            const bf16x8 a = __builtin_bit_cast(bf16x8, v.a[e]);
-            o[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ph, o[e], 0, 0, 0);
+        for (int rb = 0; rb < MB; ++rb) {
+            sum[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, ph[rb], sum[rb], 0, 0, 0);
+            sum[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pl[rb], sum[rb], 0, 0, 0);
         }
-#pragma unroll
-        for (int e = 0; e < NO; ++e) {
-            const bf16x8 a = __builtin_bit_cast(bf16x8, v.a[e]);
-            o[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, pl, o[e], 0, 0, 0);
-        }
-        sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pl, sum, 0, 0, 0);
     }
-    // dims (4 lg + i) * D/16 + e: D/4 consecutive dims per lane
-    static __device__ __forceinline__ int dim(int u, int lg) { return lg * (D / 4) + 4 * u; }
-    static __device__ __forceinline__ floatx4 piece(const floatx4 (&o)[NO], int u) {
-        floatx4 r;
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            const int f = 4 * u + x;
-            r[x] = o[f % NO][f / NO];
-        }
-        return r;
-    }
+    static __device__ __forceinline__ int dim(int u, int lg) { return 16 * u + 4 * lg; }
+    static __device__ __forceinline__ floatx4 piece(const floatx4 (&o)[NO], int u) { return o[u]; }
 };
 
 __device__ __forceinline__ void store4(float* p, const floatx4& v) { *reinterpret_cast<floatx4*>(p) = v; }
@@ -199,13 +239,17 @@ __device__ __forceinline__ void store4(__bf16* p, const floatx4& v) {
 template <typename T, int D, int MB>
 __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_direct_kernel(AttnParams p, int32_t rg) {
     using Ops = DirectOps<T, D>;
-    constexpr int TK = Ops::TK, NO = Ops::NO, NC = Ops::NC;
-    // the next tile in registers of its own while the current one is computed, where they suffice
-    constexpr bool DOUBLE = MB * D <= 128;
-    constexpr bool MASK_HELD = MB <= 2;         // the rows' ancestor masks in registers, else in LDS
+    constexpr int TK = Ops::TK, NO = Ops::NO, NC = Ops::NC, ROW = Ops::ROW;
+    using Keys = StagedKeys<ROW, TK>;
+    using Values = typename Ops::V;
+    constexpr int STAGE = TK * ROW * (Ops::V_STAGED ? 2 : 1);   // a wavefront's piece of LDS: K, then V
     constexpr int PITCH = D + 4;                // LDS row pitch of the merge: 16 rows at consecutive 16-byte slots
-    // with more than one key group [wave][16 MB][PITCH], then (m, l) [wave][16 MB]; then the ancestor masks if they are held here
-    extern __shared__ __attribute__((aligned(16))) float merge_lds[];
+    constexpr bool MASK_HELD = MB <= 2;         // the rows' ancestor masks in registers, else in LDS
+    // the wavefronts' pieces; after the loop, with more than one key group, [wave][16 MB][PITCH]
+    // partial rows and (m, l) [wave][16 MB].  In front of it the ancestor masks, if they are held here.
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    unsigned char* const pieces = lds + (MASK_HELD ? 0 : DR_MASK_BYTES);
+    float* const merge_lds = reinterpret_cast<float*>(pieces);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -236,11 +280,11 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_direct_kernel(AttnPar
             mw[rb] = *reinterpret_cast<const uintx4*>(p.mask + (static_cast<size_t>(b) * p.K_max + node[rb]) * GRAFT_MASK_WORDS);
     }
 
-    uintx4* mask_lds = reinterpret_cast<uintx4*>(merge_lds + (kg == 1 ? 0 : DR_WAVES * 16 * MB * (PITCH + 2)));
+    const uintx4* mask_lds = reinterpret_cast<const uintx4*>(lds);
     if constexpr (!MASK_HELD) {
         static_assert(GRAFT_MAX_NODES * 4 <= DR_THREADS, "one mask word per thread");
         if (tid < p.K_max * 4)
-            reinterpret_cast<unsigned*>(mask_lds)[tid] =
+            reinterpret_cast<unsigned*>(lds)[tid] =
                 reinterpret_cast<const unsigned*>(p.mask + static_cast<size_t>(b) * p.K_max * GRAFT_MASK_WORDS)[tid];
         __syncthreads();
     }
@@ -293,44 +337,56 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_direct_kernel(AttnPar
         auto page_base = [&](int it, int c) {
             return static_cast<int64_t>(__builtin_amdgcn_readlane(tb, (it & (TPR - 1)) * PAGES + c)) * p.page_stride * static_cast<int64_t>(sizeof(T));
         };
-        const unsigned k_off = l16 * ts + Ops::k_lane(lg), v_off = 4 * lg * ts + Ops::v_lane(l16);
-        auto load_keys = [&](typename Ops::K& t, int it) {
+        const unsigned k_lane = 16 * (lane % Keys::CPR), k_off = lane / Keys::CPR * ts + k_lane;
+        const unsigned v_lane = Ops::v_lane(lane), v_off = (Ops::v_row(lane, 0) - Ops::v_row0(0)) * ts + v_lane;
+        auto load_keys = [&](Keys& t, int it) {
+            unsigned off = k_off;
+            asm volatile("" : "+v"(off));                         // (kept apart from the scalar base: no 64-bit vector additions)
 #pragma unroll
-            for (int c = 0; c < NC; ++c) Ops::load_k(t, c, kc + page_base(it, c), k_off);
+            for (int j = 0; j < Keys::N; ++j)
+                t.r[j] = *reinterpret_cast<const uintx4*>(kc + page_base(it, Keys::page(j)) + static_cast<int64_t>(Keys::row0(j)) * ts + off);
         };
-        auto load_values = [&](typename Ops::V& t, int it) {
+        auto load_values = [&](Values& t, int it) {
+            unsigned off = v_off;
+            asm volatile("" : "+v"(off));
 #pragma unroll
-            for (int c = 0; c < NC; ++c)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    Ops::load_v(t, c, i, vc + page_base(it, c) + static_cast<int64_t>(i) * ts, v_off);
+            for (int j = 0; j < Ops::NV; ++j)
+                Ops::load_v(t, j, vc + page_base(it, Ops::v_page(j)) + static_cast<int64_t>(Ops::v_row0(j)) * ts, off);
         };
         // a tile that may reach past the end: keys past the last token read the last token again
         // (its values are finite, and its probability there is zero)
-        auto load_clamped = [&](typename Ops::K& kt, typename Ops::V& vt, int it) {
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                const int t_page = tile_at(it) * TK + 16 * c;
+        auto load_clamped = [&](Keys& kt, Values& vt, int it) {
+            auto row_off = [&](int page, int k) {
+                const int t_page = tile_at(it) * TK + 16 * page;
                 const int lim = last - (t_page < last ? t_page : (last & ~15));
-                Ops::load_k(kt, c, kc + page_base(it, c), static_cast<unsigned>(l16 < lim ? l16 : lim) * ts + Ops::k_lane(lg));
+                return static_cast<unsigned>(k < lim ? k : lim) * ts;
+            };
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int k = 4 * lg + i;
-                    Ops::load_v(vt, c, i, vc + page_base(it, c), static_cast<unsigned>(k < lim ? k : lim) * ts + Ops::v_lane(l16));
-                }
-            }
+            for (int j = 0; j < Keys::N; ++j)
+                kt.r[j] = *reinterpret_cast<const uintx4*>(kc + page_base(it, Keys::page(j)) +
+                                                           (row_off(Keys::page(j), Keys::row0(j) + lane / Keys::CPR) + k_lane));
+#pragma unroll
+            for (int j = 0; j < Ops::NV; ++j)
+                Ops::load_v(vt, j, vc + page_base(it, Ops::v_page(j)), row_off(Ops::v_page(j), Ops::v_row(lane, j)) + v_lane);
         };
+        unsigned char* const Ks = pieces + wave * STAGE;
+        unsigned char* const Vs = Ks + TK * ROW;
         const float sc = p.scale_log2e;
-        // One tile, in kt and vt.  With one register set (!DOUBLE) the next tile's keys and values are
-        // requested here, each as soon as the current ones are out of their registers.
-        auto step = [&](typename Ops::K& kt, typename Ops::V& vt, int it, auto more_) {
-            constexpr bool more = decltype(more_)::value && !DOUBLE;
+        // One tile: through LDS where it has to be turned, the next one requested behind it.
+        Keys kt;
+        Values vt;
+        auto step = [&](int it, auto more_) {
+            constexpr bool more = decltype(more_)::value;
+            kt.stage(Ks, lane);
+            if constexpr (more) load_keys(kt, it + 1);
             const int t0 = tile_at(it) * TK;
             const bool masked = t0 + TK > P;
             floatx4 s[MB][NC];
-#pragma unroll
-            for (int rb = 0; rb < MB; ++rb) Ops::scores(kt, q[rb], s[rb]);
-            if constexpr (more) load_keys(kt, it + 1);
+            Ops::template scores<MB>(Ks, q, s, l16, lg);
+            if constexpr (Ops::V_STAGED) {
+                Ops::stage_v(vt, Vs, lane);
+                if constexpr (more) load_values(vt, it + 1);
+            }
             if (__builtin_expect(masked, 0)) {
 #pragma unroll
                 for (int rb = 0; rb < MB; ++rb) {
@@ -370,9 +426,6 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_direct_kernel(AttnPar
                     for (int e = 0; e < NO; ++e) o[rb][e] *= a;
                 }
             }
-            typename Ops::A va;
-            Ops::arrange(vt, va);
-            if constexpr (more && Ops::FREES_V) load_values(vt, it + 1);
 #pragma unroll
             for (int rb = 0; rb < MB; ++rb) {
                 const float neg = m[rb] == -INFINITY ? 0.f : -m[rb];
@@ -385,38 +438,18 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_direct_kernel(AttnPar
                         if constexpr (!Ops::SUM_MFMA) sum += s[rb][c][i];
                     }
                 l[rb] += sum;
-                Ops::accumulate(vt, va, s[rb], o[rb], lv[rb]);
             }
-            if constexpr (more && !Ops::FREES_V) load_values(vt, it + 1);
+            asm volatile("" ::: "memory");                        // (the transpose reads stay behind the writes above)
+            Ops::template accumulate<MB>(vt, Vs, s, o, lv, l16, lg);
+            if constexpr (more && !Ops::V_STAGED) load_values(vt, it + 1);
         };
         // chunks of the tiles that one table register covers
         for (int it = 0; it < count;) {
             const int end = it + TPR < count ? it + TPR : count;
-            typename Ops::K ka, kb;
-            typename Ops::V va, vb;
             load_table(it);
-            load_clamped(ka, va, it);
-            if constexpr (DOUBLE) {
-                for (; it + 2 < end; it += 2) {
-                    load_keys(kb, it + 1);
-                    load_values(vb, it + 1);
-                    step(ka, va, it, std::false_type{});
-                    load_keys(ka, it + 2);
-                    load_values(va, it + 2);
-                    step(kb, vb, it + 1, std::false_type{});
-                }
-                if (it + 1 < end) {
-                    load_keys(kb, it + 1);
-                    load_values(vb, it + 1);
-                    step(ka, va, it, std::false_type{});
-                    step(kb, vb, it + 1, std::false_type{});
-                } else {
-                    step(ka, va, it, std::false_type{});
-                }
-            } else {
-                for (; it + 1 < end; ++it) step(ka, va, it, std::true_type{});
-                step(ka, va, it, std::false_type{});
-            }
+            load_clamped(kt, vt, it);
+            for (; it + 1 < end; ++it) step(it, std::true_type{});
+            step(it, std::false_type{});
             it = end;
         }
 #pragma unroll
@@ -454,6 +487,7 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_direct_kernel(AttnPar
         }
         return;
     }
+    __syncthreads();                                              // no wavefront reads its piece any more
     float* ml_lds = merge_lds + DR_WAVES * 16 * MB * PITCH;
 #pragma unroll
     for (int rb = 0; rb < MB; ++rb) {
@@ -550,15 +584,20 @@ __global__ __launch_bounds__(256) void tree_attn_direct_merge_kernel(AttnParams 
 // ---------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------
-static size_t direct_lds_bytes(int mb, int rg, int D) {
+static size_t direct_lds_bytes(int mb, int rg, int32_t D, int32_t dtype) {
+    const size_t pieces = static_cast<size_t>(DR_WAVES) * (dtype == GRAFT_F32 ? 16 * D * 4 : 2 * 32 * D * 2);
     const size_t merge = rg == DR_WAVES ? 0 : static_cast<size_t>(DR_WAVES) * 16 * mb * (D + 4 + 2) * sizeof(float);
-    return merge + (mb > 2 ? GRAFT_MAX_NODES * GRAFT_MASK_WORDS * sizeof(u64) : 0);
+    return (pieces > merge ? pieces : merge) + (mb > 2 ? DR_MASK_BYTES : 0);
 }
 
 // Launch shape: row blocks per wavefront, row groups per workgroup and splits that make the
 // estimated time smallest.  One workgroup of eight wavefronts (two per SIMD) is resident per
-// compute unit, so the job runs in ceil(workgroups / CUs) rounds of a fixed part plus the tiles of
-// a wavefront, times two for the SIMD's other wavefront.
+// compute unit, so the job runs in ceil(workgroups / CUs) rounds of a fixed part plus a step per
+// tile of a wavefront.  Measured cycles of a step (eight wavefronts, one tile each): fp32 4700 / 8200
+// (D = 128, one / two row blocks) and 2650 (D = 64), against 4096 / 8192 and 2048 of MFMAs on a SIMD;
+// bf16 1700 / 2500 / 3850 for one / two / four row blocks.  Set-up and the merge through LDS take
+// 6500 + 2000 per row block and 64 dims; the merge of splits is a launch of its own (6000) and its
+// traffic, 8 bytes per partial value at 3200 bytes per cycle.
 DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages, int32_t dtype,
                        bool may_split) {
     DirectPlan best{};
@@ -567,9 +606,11 @@ DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_
     const int TK = dtype == GRAFT_F32 ? 16 : 32;
     const int64_t tiles = (static_cast<int64_t>(max_pages) * GRAFT_PAGE_SIZE + TK - 1) / TK;
     const int64_t cus = device_compute_units();
-    const int mb_max = dtype == GRAFT_F32 ? (D == 128 ? 1 : 2) : 4;   // (what the registers hold)
+    const int mb_max = dtype != GRAFT_F32 ? 4 : (D == 128 ? 2 : 1);
     for (int mb = 1; mb <= mb_max; mb *= 2) {
-        const double c_tile = 2.0 * (dtype == GRAFT_F32 ? 200.0 + mb * D * 16.5 : 150.0 + mb * 350.0);
+        double c_step = D == 64 ? 2650.0 : (mb == 1 ? 4700.0 : 8200.0);
+        if (dtype != GRAFT_F32) c_step = mb == 4 ? 3850.0 : (mb == 2 ? 2500.0 : 1700.0);
+        const double c_fixed = 6500.0 + 2000.0 * mb * (D / 64);
         for (int rg = 1; rg <= DR_WAVES; rg *= 2) {
             const int kg = DR_WAVES / rg;
             const int n_rt = (blocks + rg * mb - 1) / (rg * mb);
@@ -579,7 +620,7 @@ DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_
                 const int64_t per = (tiles + static_cast<int64_t>(sp) * kg - 1) / (static_cast<int64_t>(sp) * kg);
                 const int64_t rounds = (units * sp + cus - 1) / cus;
                 const double rows = static_cast<double>(B) * Hkv * R;
-                const double cost = rounds * (9000.0 + per * c_tile) + (sp > 1 ? 8000.0 + sp * rows * D / (256.0 * 10.0) : 0.0);
+                const double cost = rounds * (c_fixed + per * c_step) + (sp > 1 ? 6000.0 + sp * rows * D / 400.0 : 0.0);
                 if (best.cost < 0.0 || cost < best.cost) {
                     best.cost = cost;
                     best.mb = mb;
@@ -601,15 +642,15 @@ DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_
 }
 
 template <typename T, int D, int MB>
-static int32_t launch_one(const DirectPlan& pl, const AttnParams& p, hipStream_t s) {
+static int32_t launch_one(const DirectPlan& pl, const AttnParams& p, int32_t dtype, hipStream_t s) {
     auto kernel = tree_attn_direct_kernel<T, D, MB>;
-    const unsigned lds = static_cast<unsigned>(direct_lds_bytes(MB, pl.rg, D));
+    const unsigned lds = static_cast<unsigned>(direct_lds_bytes(MB, pl.rg, D, dtype));
     if (lds > 65536) {                                            // more than the default limit needs opting in, once per device
         static thread_local int done_device = -1;
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess) dev = 0;
         if (done_device != dev) {
-            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, DR_LDS_BYTES);
             done_device = dev;
         }
     }
@@ -631,11 +672,11 @@ int32_t launch_direct(const DirectPlan& pl, AttnParams p, int32_t D, int32_t dty
     p.ws_o = static_cast<unsigned short*>(workspace);
     p.ws_ml = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + pl.ws_o_bytes);
     if (dtype == GRAFT_F32) {
-        if (D == 64) return pl.mb == 1 ? launch_one<float, 64, 1>(pl, p, s) : launch_one<float, 64, 2>(pl, p, s);
-        return launch_one<float, 128, 1>(pl, p, s);
+        if (D == 64) return launch_one<float, 64, 1>(pl, p, dtype, s);
+        return pl.mb == 1 ? launch_one<float, 128, 1>(pl, p, dtype, s) : launch_one<float, 128, 2>(pl, p, dtype, s);
     }
-    if (pl.mb == 4) return launch_one<__bf16, 64, 4>(pl, p, s);
-    return pl.mb == 1 ? launch_one<__bf16, 64, 1>(pl, p, s) : launch_one<__bf16, 64, 2>(pl, p, s);
+    if (pl.mb == 4) return launch_one<__bf16, 64, 4>(pl, p, dtype, s);
+    return pl.mb == 1 ? launch_one<__bf16, 64, 1>(pl, p, dtype, s) : launch_one<__bf16, 64, 2>(pl, p, dtype, s);
 }
 
 }  // namespace graft
