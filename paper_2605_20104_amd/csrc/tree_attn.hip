@@ -2,7 +2,7 @@
 //
 // Two code paths.
 //
-// (1) bf16, D = 128: split-KV MFMA kernel + log-sum-exp combine.
+// (1) bf16, D = 128, except where the keys are few: split-KV MFMA kernel + log-sum-exp combine.
 //     All R = K_max * (Hq/Hkv) query rows of one KV head share every K/V element
 //     that is streamed, so K and V are read from HBM once per head; the
 //     arithmetic intensity is R flop per byte, which puts the tree-verify shapes
@@ -43,7 +43,7 @@
 //     O / sum as fp16 rows with a per-row scale) go to the workspace; a small combine
 //     kernel merges the splits and writes bf16.
 //
-// (2) everything else (fp32 storage, or D = 64): tree_attn_direct.hip.
+// (2) fp32 storage, D = 64, and bf16 with D = 128 where the keys are few: tree_attn_direct.hip.
 #include <type_traits>
 
 #include "attn_shared.h"
@@ -1267,6 +1267,7 @@ __global__ __launch_bounds__(64 * CB_MAX_WAVES) void tree_attn_combine_kernel(At
 struct AttnPlan {
     int mb, n_row_tiles, n_splits, r_pad;
     size_t ws_o_bytes, ws_bytes;
+    double cost;                    // estimated cycles
 };
 
 int device_compute_units() {
@@ -1286,9 +1287,6 @@ int device_compute_units() {
 #ifdef GRAFT_ATTN_STAMPS
 static thread_local int g_force_splits = 0, g_force_row_tiles = 0;
 #endif
-
-// bf16, D = 128 goes to path (1)
-static bool mfma_shape(int32_t D, int32_t dtype) { return dtype == GRAFT_BF16 && D == AT_D; }
 
 // Launch shape of the MFMA path.  One workgroup per compute unit is resident at a time, so
 // the job runs in ceil(workgroups / CUs) rounds, each as long as one workgroup's pass: a
@@ -1322,6 +1320,7 @@ static AttnPlan make_plan(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int
                 pl.n_row_tiles = rt;
                 pl.mb = mb;
                 pl.n_splits = static_cast<int>(sp);
+                pl.cost = cost + (sp > 1 ? 11500.0 - 200.0 * sp : 0.0);   // with the merge launch, as measured
             }
         }
     }
@@ -1343,6 +1342,28 @@ static AttnPlan make_plan(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int
     return pl;
 }
 
+// Which path, and its plan.  bf16 with D = 128 has two.  Measured, the direct one is faster where one
+// launch of it covers the keys (few of them, or many sequences and heads: 6.3 us against 10 to 12 us for
+// the MFMA path's two launches) and even with it, within a few per cent, around 2K keys for 8 heads; the
+// MFMA path wins from there on, up to 1.5 times on large problems.  Both costs are calibrated to about
+// 5 per cent, so the direct path has to be ahead by that much.
+struct PathChoice {
+    bool direct;
+    AttnPlan mfma;
+    DirectPlan dir;
+};
+static PathChoice choose_path(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages, int32_t dtype) {
+    PathChoice c{};
+    c.dir = plan_direct(B, K_max, Hq, Hkv, D, max_pages, dtype, true);
+    if (dtype != GRAFT_BF16 || D != AT_D) {
+        c.direct = true;
+        return c;
+    }
+    c.mfma = make_plan(B, K_max, Hq, Hkv, max_pages);
+    c.direct = c.dir.cost < 0.95 * c.mfma.cost;
+    return c;
+}
+
 static bool attn_shape_ok(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages) {
     return B >= 1 && B <= 65535 && K_max >= 1 && K_max <= GRAFT_MAX_NODES && Hq >= 1 && Hkv >= 1 &&
            Hkv <= 65535 && Hq % Hkv == 0 && Hq / Hkv <= 16 && (D == 64 || D == 128) && max_pages >= 1 &&
@@ -1361,8 +1382,8 @@ extern "C" size_t graft_tree_attn_workspace_bytes(int32_t B, int32_t K_max, int3
                                                   int32_t D, int32_t max_pages, int32_t dtype) {
     if (!graft::attn_shape_ok(B, K_max, Hq, Hkv, D, max_pages)) return 0;
     if (dtype != GRAFT_F32 && dtype != GRAFT_BF16) return 0;
-    if (!graft::mfma_shape(D, dtype)) return graft::plan_direct(B, K_max, Hq, Hkv, D, max_pages, dtype, true).ws_bytes;
-    return graft::make_plan(B, K_max, Hq, Hkv, max_pages).ws_bytes;
+    const graft::PathChoice c = graft::choose_path(B, K_max, Hq, Hkv, D, max_pages, dtype);
+    return c.direct ? c.dir.ws_bytes : c.mfma.ws_bytes;
 }
 
 extern "C" int32_t graft_attn_profile_events(void** start_events, void** stop_events, int32_t n) {
@@ -1471,16 +1492,19 @@ extern "C" int32_t graft_tree_attn(const void* q, const void* k_cache, const voi
     p.scale_log2e = scale * 1.4426950408889634f;
     hipStream_t s = static_cast<hipStream_t>(stream);
 
-    if (!mfma_shape(D, dtype)) {
-        // these shapes have always run without a workspace: a caller that brings none, or too
-        // little, gets a launch that does not split the keys over workgroups
-        DirectPlan dp = plan_direct(B, K_max, Hq, Hkv, D, max_pages, dtype, true);
-        if (dp.ws_bytes > 0 && (!workspace || workspace_bytes < dp.ws_bytes))
+    const PathChoice choice = choose_path(B, K_max, Hq, Hkv, D, max_pages, dtype);
+    if (choice.direct) {
+        DirectPlan dp = choice.dir;
+        if (dp.ws_bytes > 0 && (!workspace || workspace_bytes < dp.ws_bytes)) {
+            if (dtype == GRAFT_BF16 && D == AT_D) return GRAFT_ERR_WORKSPACE;
+            // the other shapes have always run without a workspace: a caller that brings none, or too
+            // little, gets a launch that does not split the keys over workgroups
             dp = plan_direct(B, K_max, Hq, Hkv, D, max_pages, dtype, false);
+        }
         return launch_direct(dp, p, D, dtype, workspace, s);
     }
 
-    const AttnPlan pl = make_plan(B, K_max, Hq, Hkv, max_pages);
+    const AttnPlan& pl = choice.mfma;
     if (pl.ws_bytes > 0 && (!workspace || workspace_bytes < pl.ws_bytes)) return GRAFT_ERR_WORKSPACE;
     p.R_pad = pl.r_pad; p.n_splits = pl.n_splits; p.n_row_tiles = pl.n_row_tiles;
     p.ws_o = static_cast<unsigned short*>(workspace);

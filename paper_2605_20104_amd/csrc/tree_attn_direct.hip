@@ -1,4 +1,5 @@
-// graft_tree_attn, direct path: fp32 storage (any head size) and bf16 with D = 64.
+// graft_tree_attn, direct path: fp32 storage (any head size), bf16 with D = 64, and bf16 with D = 128
+// where the keys are few.
 //
 // A wavefront owns its keys: the wavefronts of a workgroup split a key range between them (kg
 // key groups), as well as the query rows (rg row groups of MB 16-row blocks), walk their tiles (32
@@ -7,9 +8,10 @@
 //   fp32 : v_mfma_f32_16x16x4_f32 (full fp32 products and sums, 32 cycles each).  The kernel is
 //          bound by them: 64 (D = 128) or 32 (D = 64) per 16 keys and 16 rows.
 //   bf16 : v_mfma_f32_16x16x32_bf16 on raw Q and K (exact products, fp32 sums); the softmax scale
-//          is applied in fp32, and probabilities enter the second product as the sum of two bf16
-//          numbers (relative error 2^-17: far below the rounding of the result).  Bound by the
-//          vector ALUs (exp2 and the packing of probabilities).
+//          is applied in fp32.  With D = 64 probabilities enter the second product as the sum of two
+//          bf16 numbers (relative error 2^-17: far below the rounding of the result), with D = 128
+//          rounded to one, as on the path this stands in for.  Bound by the vector ALUs (exp2 and the
+//          packing of probabilities).
 // Operand layouts (lane = 16 lg + l16).  First product: S^T = K Q^T, A = K (key l16), B = Q^T
 // (row l16), so a lane gets 4 keys (4 lg + i) of one row, and these are the B operand of the
 // second product O^T = V^T P^T without any exchange between lanes: its contraction index runs
@@ -142,6 +144,7 @@ template <int D> struct DirectOps<__bf16, D> {
     static constexpr int NC = 2;
     static constexpr int ROW = D * 2;
     static constexpr bool SUM_MFMA = true;      // row sums through the matrix cores, which have time left here
+    static constexpr bool SPLIT_P = D == 64;    // probabilities as two bf16 numbers (D = 128: rounded to one)
     static constexpr int SEG = ROW / 32 - 1;    // V rows: 32-byte segment ^ (row & SEG)
     struct Q { bf16x8 v[D / 32]; };
     static __device__ __forceinline__ void load_q(Q& q, const __bf16* row, int lg) {
@@ -184,16 +187,20 @@ template <int D> struct DirectOps<__bf16, D> {
     template <int MB>
     static __device__ __forceinline__ void accumulate(const V&, const unsigned char* Vs, const floatx4 (&p)[MB][NC], floatx4 (&o)[MB][NO],
                                                       floatx4 (&sum)[MB], int l16, int lg) {
-        bf16x8 ph[MB], pl[MB];                  // p = hi + lo, both bf16 (hi: truncated, so p - hi is exact)
+        bf16x8 ph[MB], pl[MB];                  // SPLIT_P: p = hi + lo, both bf16 (hi: truncated, so p - hi is exact)
 #pragma unroll
         for (int rb = 0; rb < MB; ++rb) {
-            uintx4 hi, lo;
+            uintx4 hi, lo = uintx4{0u, 0u, 0u, 0u};
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const float p0 = p[rb][j >> 1][2 * (j & 1)], p1 = p[rb][j >> 1][2 * (j & 1) + 1];
-                const unsigned b0 = __float_as_uint(p0), b1 = __float_as_uint(p1);
-                hi[j] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
-                lo[j] = pack_bf16(p0 - __uint_as_float(b0 & 0xffff0000u), p1 - __uint_as_float(b1 & 0xffff0000u));
+                if constexpr (SPLIT_P) {
+                    const unsigned b0 = __float_as_uint(p0), b1 = __float_as_uint(p1);
+                    hi[j] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
+                    lo[j] = pack_bf16(p0 - __uint_as_float(b0 & 0xffff0000u), p1 - __uint_as_float(b1 & 0xffff0000u));
+                } else {
+                    hi[j] = pack_bf16(p0, p1);
+                }
             }
             ph[rb] = __builtin_bit_cast(bf16x8, hi);
             pl[rb] = __builtin_bit_cast(bf16x8, lo);
@@ -216,14 +223,16 @@ template <int D> struct DirectOps<__bf16, D> {
             }
 #pragma unroll
             for (int rb = 0; rb < MB; ++rb) o[rb][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ph[rb], o[rb][e], 0, 0, 0);
+            if constexpr (SPLIT_P) {
 #pragma unroll
-            for (int rb = 0; rb < MB; ++rb) o[rb][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, pl[rb], o[rb][e], 0, 0, 0);
+                for (int rb = 0; rb < MB; ++rb) o[rb][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, pl[rb], o[rb][e], 0, 0, 0);
+            }
         }
         const bf16x8 ones = __builtin_bit_cast(bf16x8, uintx4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
 #pragma unroll
         for (int rb = 0; rb < MB; ++rb) {
             sum[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, ph[rb], sum[rb], 0, 0, 0);
-            sum[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pl[rb], sum[rb], 0, 0, 0);
+            if constexpr (SPLIT_P) sum[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pl[rb], sum[rb], 0, 0, 0);
         }
     }
     static __device__ __forceinline__ int dim(int u, int lg) { return 16 * u + 4 * lg; }
@@ -244,7 +253,7 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_direct_kernel(AttnPar
     using Values = typename Ops::V;
     constexpr int STAGE = TK * ROW * (Ops::V_STAGED ? 2 : 1);   // a wavefront's piece of LDS: K, then V
     constexpr int PITCH = D + 4;                // LDS row pitch of the merge: 16 rows at consecutive 16-byte slots
-    constexpr bool MASK_HELD = MB <= 2;         // the rows' ancestor masks in registers, else in LDS
+    constexpr bool MASK_HELD = MB * D < 256;        // the rows' ancestor masks in registers, else in LDS
     // the wavefronts' pieces; after the loop, with more than one key group, [wave][16 MB][PITCH]
     // partial rows and (m, l) [wave][16 MB].  In front of it the ancestor masks, if they are held here.
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
@@ -587,7 +596,7 @@ __global__ __launch_bounds__(256) void tree_attn_direct_merge_kernel(AttnParams 
 static size_t direct_lds_bytes(int mb, int rg, int32_t D, int32_t dtype) {
     const size_t pieces = static_cast<size_t>(DR_WAVES) * (dtype == GRAFT_F32 ? 16 * D * 4 : 2 * 32 * D * 2);
     const size_t merge = rg == DR_WAVES ? 0 : static_cast<size_t>(DR_WAVES) * 16 * mb * (D + 4 + 2) * sizeof(float);
-    return (pieces > merge ? pieces : merge) + (mb > 2 ? DR_MASK_BYTES : 0);
+    return (pieces > merge ? pieces : merge) + (mb * D >= 256 ? DR_MASK_BYTES : 0);
 }
 
 // Launch shape: row blocks per wavefront, row groups per workgroup and splits that make the
@@ -595,9 +604,9 @@ static size_t direct_lds_bytes(int mb, int rg, int32_t D, int32_t dtype) {
 // compute unit, so the job runs in ceil(workgroups / CUs) rounds of a fixed part plus a step per
 // tile of a wavefront.  Measured cycles of a step (eight wavefronts, one tile each): fp32 4700 / 8200
 // (D = 128, one / two row blocks) and 2650 (D = 64), against 4096 / 8192 and 2048 of MFMAs on a SIMD;
-// bf16 1700 / 2500 / 3850 for one / two / four row blocks.  Set-up and the merge through LDS take
-// 6500 + 2000 per row block and 64 dims; the merge of splits is a launch of its own (6000) and its
-// traffic, 8 bytes per partial value at 3200 bytes per cycle.
+// bf16 2600 (D = 128) and, for D = 64, 1700 / 2500 / 3850 for one / two / four row blocks.  Set-up and
+// the merge through LDS take 6500 + 2000 per row block and 64 dims; the merge of splits is a launch of
+// its own, 8000 + 600 per split and its traffic, 8 bytes per partial value at 3200 bytes per cycle.
 DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages, int32_t dtype,
                        bool may_split) {
     DirectPlan best{};
@@ -606,10 +615,11 @@ DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_
     const int TK = dtype == GRAFT_F32 ? 16 : 32;
     const int64_t tiles = (static_cast<int64_t>(max_pages) * GRAFT_PAGE_SIZE + TK - 1) / TK;
     const int64_t cus = device_compute_units();
-    const int mb_max = dtype != GRAFT_F32 ? 4 : (D == 128 ? 2 : 1);
+    const int mb_max = dtype == GRAFT_F32 ? (D == 128 ? 2 : 1) : (D == 128 ? 1 : 4);
     for (int mb = 1; mb <= mb_max; mb *= 2) {
         double c_step = D == 64 ? 2650.0 : (mb == 1 ? 4700.0 : 8200.0);
-        if (dtype != GRAFT_F32) c_step = mb == 4 ? 3850.0 : (mb == 2 ? 2500.0 : 1700.0);
+        if (dtype != GRAFT_F32 && D == 128) c_step = 2600.0;
+        else if (dtype != GRAFT_F32) c_step = mb == 4 ? 3850.0 : (mb == 2 ? 2500.0 : 1700.0);
         const double c_fixed = 6500.0 + 2000.0 * mb * (D / 64);
         for (int rg = 1; rg <= DR_WAVES; rg *= 2) {
             const int kg = DR_WAVES / rg;
@@ -620,7 +630,7 @@ DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_
                 const int64_t per = (tiles + static_cast<int64_t>(sp) * kg - 1) / (static_cast<int64_t>(sp) * kg);
                 const int64_t rounds = (units * sp + cus - 1) / cus;
                 const double rows = static_cast<double>(B) * Hkv * R;
-                const double cost = rounds * (c_fixed + per * c_step) + (sp > 1 ? 6000.0 + sp * rows * D / 400.0 : 0.0);
+                const double cost = rounds * (c_fixed + per * c_step) + (sp > 1 ? 8000.0 + 600.0 * sp + sp * rows * D / 400.0 : 0.0);
                 if (best.cost < 0.0 || cost < best.cost) {
                     best.cost = cost;
                     best.mb = mb;
@@ -675,6 +685,7 @@ int32_t launch_direct(const DirectPlan& pl, AttnParams p, int32_t D, int32_t dty
         if (D == 64) return launch_one<float, 64, 1>(pl, p, dtype, s);
         return pl.mb == 1 ? launch_one<float, 128, 1>(pl, p, dtype, s) : launch_one<float, 128, 2>(pl, p, dtype, s);
     }
+    if (D == 128) return launch_one<__bf16, 128, 1>(pl, p, dtype, s);
     if (pl.mb == 4) return launch_one<__bf16, 64, 4>(pl, p, dtype, s);
     return pl.mb == 1 ? launch_one<__bf16, 64, 1>(pl, p, dtype, s) : launch_one<__bf16, 64, 2>(pl, p, dtype, s);
 }

@@ -13,7 +13,7 @@ import inputs
 import oracle
 import paper_2605_20104_amd as graft
 from gpu_util import dev, host
-from test_gpu_attn import gpu_mask, shape_workload
+from test_gpu_attn import check_case, gpu_mask, shape_workload
 
 pytestmark = pytest.mark.gpu
 
@@ -103,3 +103,17 @@ def test_scores_that_keep_rising(dtype, D):
         bound = D / 2 * 2.0 ** -24 * s_max * np.abs(conv(att["v_cache"][0])).max()
         print("largest score %.0f, bound %.1e, max error %.1e" % (s_max, bound, err.max()))
         assert (err <= bound + (0.0 if dtype == "f32" else 2.0 ** -8) * np.abs(ref)).all(), err.max()
+
+
+# bf16 with D = 128 takes the direct path where the keys are few (the probabilities are rounded to bf16
+# there, relative 2^-8 each with random sign, and so is the result: the 2e-2 of every D = 128 test)
+@pytest.mark.parametrize("case", [(1, 1, 1, 1, 0), (1, 20, 8, 8, 300), (2, 33, 6, 2, 63), (1, 78, 8, 1, 37), (3, 128, 32, 2, 20),
+                                  (8, 24, 32, 8, 500), (1, 40, 32, 8, 700)], ids=lambda c: "B%d_K%d_Hq%d_Hkv%d_P%d" % c)
+@pytest.mark.parametrize("layout", ["head_major", "token_major"])
+def test_head_128_with_few_keys(case, layout):
+    B, K, Hq, Hkv, P = case
+    w = shape_workload(B, K, Hq, Hkv, 128, P)
+    rng = np.random.default_rng(K)
+    n_nodes = None if B == 1 else np.concatenate([[K], rng.integers(1, K + 1, B - 1)]).astype(np.int32)
+    prefix = None if B == 1 else np.concatenate([[P], rng.integers(0, P + 1, B - 1)]).astype(np.int32)
+    check_case(w, seed=K + P, layout=layout, n_nodes=n_nodes, prefix=prefix)
