@@ -35,16 +35,24 @@ struct AttnParams {
 };
 
 // Workgroups go to the 8 XCDs (each with its own L2 and its own compute units) round-robin by their
-// linear index.  Work items are numbered with the row tiles of one (sequence, KV head, split), which
-// read the same keys and values, next to each other, and every XCD takes one contiguous eighth of
-// them: tiles that share keys run side by side on one L2, and the XCDs' shares differ by one item
-// at most (a share that holds whole units only can be a third larger than the average, a second
-// round for a job that was planned to fill the chip once).
-inline unsigned xcd_grid(int64_t n_work) { return static_cast<unsigned>((n_work + 7) / 8 * 8); }
-__device__ __forceinline__ int xcd_work_index(int n_work) {      // -1: padding of the grid
-    const int q = n_work >> 3, rem = n_work & 7, xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    if (slot >= q + (xcd < rem ? 1 : 0)) return -1;
-    return xcd * q + (xcd < rem ? xcd : rem) + slot;
+// linear index.  The row tiles of a unit, one (sequence, KV head, split), read the same keys and
+// values: they get the same XCD and neighbouring slots on it, so that all but the first reader find
+// them in that XCD's L2.  Units are dealt round-robin, eight at a time; the row tiles of what is left
+// over are dealt one by one, so that the XCDs' shares differ by one workgroup at most (with whole
+// units only, 50 units of 5 tiles put 35 workgroups on two XCDs of 32 compute units: a second round
+// for a job that was planned to fill the chip once, 71 us instead of 42).
+struct WorkItem { int unit, row_tile; };                         // unit < 0: padding of the grid
+inline unsigned xcd_grid(int64_t n_units, int64_t n_row_tiles) {
+    return static_cast<unsigned>(8 * ((n_units / 8) * n_row_tiles + (n_units % 8 * n_row_tiles + 7) / 8));
+}
+__device__ __forceinline__ WorkItem xcd_work_item(int n_units, int n_row_tiles) {
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int whole = (n_units >> 3) * n_row_tiles;               // slots of an XCD that take whole units
+    const bool left = slot >= whole;
+    const int s = left ? (slot - whole) * 8 + xcd : slot;
+    const int u = s / n_row_tiles, t = s - u * n_row_tiles;
+    const int unit = left ? (n_units & ~7) + u : u * 8 + xcd;
+    return {unit < n_units ? unit : -1, t};
 }
 
 // Compute units of the current device (256 when it cannot be asked, e.g. without a GPU).
@@ -78,6 +86,24 @@ static void launch_main(Kernel kernel, dim3 grid, dim3 block, unsigned lds_bytes
     } else {
         hipLaunchKernelGGL(kernel, grid, block, lds_bytes, s, args...);
     }
+}
+
+// Which of the 32 tokens from tree slot s on (s = token - prefix length, negative inside the prefix) a
+// row sees, as bits: all of the prefix, of the n tree slots those in the row's ancestor mask.  word(k)
+// returns the mask's 32-bit word k, 0 <= k < 4.  s and n are wavefront-uniform, so that the words are
+// picked by scalar conditions and a row costs one funnel shift and one AND.
+template <class Word>
+__device__ __forceinline__ unsigned visible_window(int s, int n, Word&& word) {
+    const int w = s >> 5, left = n - s;
+    const unsigned lo = w < 0 ? ~0u : (w < 4 ? word(w) : 0u);
+    const unsigned hi = w < -1 ? ~0u : (w < 3 ? word(w + 1) : 0u);
+    const unsigned slots = left >= 32 ? ~0u : (left <= 0 ? 0u : (1u << left) - 1u);
+    return __builtin_amdgcn_alignbit(hi, lo, static_cast<unsigned>(s) & 31u) & slots;
+}
+// x where bit `bit` of the window is set, -inf elsewhere: a bit-field extract and a bit select.
+__device__ __forceinline__ float keep_visible(float x, unsigned window, int bit) {
+    const unsigned m = static_cast<unsigned>(__builtin_amdgcn_sbfe(static_cast<int>(window), bit, 1));
+    return __uint_as_float((__float_as_uint(x) & m) | (0xff800000u & ~m));
 }
 
 __device__ __forceinline__ float bf16_bits_to_float(unsigned short b) {

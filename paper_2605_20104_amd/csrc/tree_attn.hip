@@ -44,6 +44,7 @@
 //     kernel merges the splits and writes bf16.
 //
 // (2) fp32 storage, D = 64, and bf16 with D = 128 where the keys are few: tree_attn_direct.hip.
+#include <cstring>
 #include <type_traits>
 
 #include "attn_shared.h"
@@ -545,27 +546,17 @@ __device__ __forceinline__ bool apply_tree_mask(floatx4 (&x)[MB][2], const WaveR
     for (int rb = 0; rb < MB; ++rb) {
         const int r = r_base + rb * 16 + l16;
         const int node = (r * g_magic) >> 16;              // r / G
-        const bool live = r < R && node < n;
-        const int nd = live ? node : 0;
-        unsigned wd[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) wd[k] = live ? Ms[4 * nd + k] : 0u;
+        const unsigned* row = Ms + 4 * (r < R && node < n ? node : 0);     // (rows of absent nodes: any finite mask will do)
+        const unsigned win = visible_window(t_sub0 - P, n, [&](int k) { return row[k]; }) >> (4 * lg);
+        reserve_acc_registers<MB>();                          // no temporaries of the compiler's in the accumulators
         float mx = -INFINITY;
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            reserve_acc_registers<MB>();                      // no temporaries of the compiler's in the accumulators
-            const int j0 = t_sub0 + 16 * c + 4 * lg - P;      // tree slot of element i = 0
+        for (int c = 0; c < 2; ++c)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int j = j0 + i;
-                const int wi = (j >> 5) & 3;
-                const unsigned word = wi == 0 ? wd[0] : (wi == 1 ? wd[1] : (wi == 2 ? wd[2] : wd[3]));
-                const bool bit = (word >> (j & 31)) & 1u;
-                const bool valid = (j < 0) | ((j < n) & bit);
-                x[rb][c][i] = valid ? x[rb][c][i] : -INFINITY;
+                x[rb][c][i] = keep_visible(x[rb][c][i], win, 16 * c + i);
                 mx = fmaxf(mx, x[rb][c][i]);
             }
-        }
         lm[rb] = mx;
         grow = grow || (mx > w.thr[rb]);
     }
@@ -745,10 +736,9 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(AttnParams p
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave_u = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lg = lane >> 4;
-    const int work = xcd_work_index(p.B * p.Hkv * p.n_splits * p.n_row_tiles);
-    if (work < 0) return;                                         // grid padding (whole workgroup)
-    const int rt = work % p.n_row_tiles;
-    const int unit = work / p.n_row_tiles;                        // over B * Hkv * n_splits
+    const WorkItem item = xcd_work_item(p.B * p.Hkv * p.n_splits, p.n_row_tiles);
+    if (item.unit < 0) return;                                    // grid padding (whole workgroup)
+    const int rt = item.row_tile, unit = item.unit;              // unit over B * Hkv * n_splits
     const int split = unit % p.n_splits;
     const int g = (unit / p.n_splits) % p.Hkv, b = unit / (p.n_splits * p.Hkv);
 
@@ -1352,7 +1342,7 @@ struct PathChoice {
     AttnPlan mfma;
     DirectPlan dir;
 };
-static PathChoice choose_path(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages, int32_t dtype) {
+static PathChoice make_choice(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages, int32_t dtype) {
     PathChoice c{};
     c.dir = plan_direct(B, K_max, Hq, Hkv, D, max_pages, dtype, true);
     if (dtype != GRAFT_BF16 || D != AT_D) {
@@ -1362,6 +1352,25 @@ static PathChoice choose_path(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv,
     c.mfma = make_plan(B, K_max, Hq, Hkv, max_pages);
     c.direct = c.dir.cost < 0.95 * c.mfma.cost;
     return c;
+}
+
+// The last shape's choice is kept per host thread: all layers of a model ask for the same one, and
+// working the cost models out takes a few microseconds, as long as a launch.
+static const PathChoice& choose_path(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages, int32_t dtype) {
+    struct Kept {
+        int32_t key[8];
+        PathChoice choice;
+    };
+    static thread_local Kept kept{};
+    int32_t key[8] = {B, K_max, Hq, Hkv, D, max_pages, dtype, 1};
+#ifdef GRAFT_ATTN_STAMPS
+    key[7] += g_force_splits * 8192 + g_force_row_tiles * 2;
+#endif
+    if (std::memcmp(key, kept.key, sizeof key) != 0) {
+        kept.choice = make_choice(B, K_max, Hq, Hkv, D, max_pages, dtype);
+        std::memcpy(kept.key, key, sizeof key);
+    }
+    return kept.choice;
 }
 
 static bool attn_shape_ok(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages) {
@@ -1382,7 +1391,7 @@ extern "C" size_t graft_tree_attn_workspace_bytes(int32_t B, int32_t K_max, int3
                                                   int32_t D, int32_t max_pages, int32_t dtype) {
     if (!graft::attn_shape_ok(B, K_max, Hq, Hkv, D, max_pages)) return 0;
     if (dtype != GRAFT_F32 && dtype != GRAFT_BF16) return 0;
-    const graft::PathChoice c = graft::choose_path(B, K_max, Hq, Hkv, D, max_pages, dtype);
+    const graft::PathChoice& c = graft::choose_path(B, K_max, Hq, Hkv, D, max_pages, dtype);
     return c.direct ? c.dir.ws_bytes : c.mfma.ws_bytes;
 }
 
@@ -1492,7 +1501,7 @@ extern "C" int32_t graft_tree_attn(const void* q, const void* k_cache, const voi
     p.scale_log2e = scale * 1.4426950408889634f;
     hipStream_t s = static_cast<hipStream_t>(stream);
 
-    const PathChoice choice = choose_path(B, K_max, Hq, Hkv, D, max_pages, dtype);
+    const PathChoice& choice = choose_path(B, K_max, Hq, Hkv, D, max_pages, dtype);
     if (choice.direct) {
         DirectPlan dp = choice.dir;
         if (dp.ws_bytes > 0 && (!workspace || workspace_bytes < dp.ws_bytes)) {
@@ -1509,7 +1518,7 @@ extern "C" int32_t graft_tree_attn(const void* q, const void* k_cache, const voi
     p.R_pad = pl.r_pad; p.n_splits = pl.n_splits; p.n_row_tiles = pl.n_row_tiles;
     p.ws_o = static_cast<unsigned short*>(workspace);
     p.ws_ml = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + pl.ws_o_bytes);
-    const dim3 grid(xcd_grid(static_cast<int64_t>(B) * Hkv * pl.n_splits * pl.n_row_tiles));
+    const dim3 grid(xcd_grid(static_cast<int64_t>(B) * Hkv * pl.n_splits, pl.n_row_tiles));
 #ifdef GRAFT_ATTN_STAMPS
     p.stamps = static_cast<size_t>(grid.x) * AT_STAMPS * sizeof(unsigned long long) <= g_stamps_bytes ? g_stamps : nullptr;
 #endif

@@ -265,9 +265,9 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_direct_kernel(AttnPar
     const int l16 = lane & 15, lg = lane >> 4;
     const int kg = DR_WAVES / rg;
     const int rgi = wave % rg, kgi = wave / rg;
-    const int work = xcd_work_index(p.B * p.Hkv * p.n_splits * p.n_row_tiles);
-    if (work < 0) return;                                         // grid padding (whole workgroup)
-    const int rt = work % p.n_row_tiles, unit = work / p.n_row_tiles;
+    const WorkItem item = xcd_work_item(p.B * p.Hkv * p.n_splits, p.n_row_tiles);
+    if (item.unit < 0) return;                                    // grid padding (whole workgroup)
+    const int rt = item.row_tile, unit = item.unit;
     const int split = unit % p.n_splits;
     const int g = (unit / p.n_splits) % p.Hkv, b = unit / (p.n_splits * p.Hkv);
 
@@ -399,17 +399,14 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_direct_kernel(AttnPar
             if (__builtin_expect(masked, 0)) {
 #pragma unroll
                 for (int rb = 0; rb < MB; ++rb) {
-                    if constexpr (!MASK_HELD) mw[rb] = mask_lds[node[rb]];
+                    const uintx4 words = MASK_HELD ? mw[rb] : mask_lds[node[rb]];
+                    const unsigned win = visible_window(t0 - P, n, [&](int k) {
+                        return k == 0 ? words[0] : (k == 1 ? words[1] : (k == 2 ? words[2] : words[3]));
+                    }) >> (4 * lg);
 #pragma unroll
                     for (int c = 0; c < NC; ++c)
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const int j = t0 + 16 * c + 4 * lg + i - P;            // tree slot
-                            const int wi = (j >> 5) & 3;
-                            const unsigned word = wi == 0 ? mw[rb][0] : (wi == 1 ? mw[rb][1] : (wi == 2 ? mw[rb][2] : mw[rb][3]));
-                            const bool valid = (j < 0) | ((j < n) & ((word >> (j & 31)) & 1u));
-                            s[rb][c][i] = valid ? s[rb][c][i] : -INFINITY;
-                        }
+                        for (int i = 0; i < 4; ++i) s[rb][c][i] = keep_visible(s[rb][c][i], win, 16 * c + i);
                 }
             }
             float mx[MB];
@@ -664,7 +661,7 @@ static int32_t launch_one(const DirectPlan& pl, const AttnParams& p, int32_t dty
             done_device = dev;
         }
     }
-    const dim3 grid(xcd_grid(static_cast<int64_t>(p.B) * p.Hkv * pl.n_splits * pl.n_row_tiles));
+    const dim3 grid(xcd_grid(static_cast<int64_t>(p.B) * p.Hkv * pl.n_splits, pl.n_row_tiles));
     launch_main(kernel, grid, dim3(DR_THREADS), lds, s, p, pl.rg);
     int32_t rc = check_launch();
     if (rc != GRAFT_OK || pl.n_splits == 1) return rc;
