@@ -371,9 +371,10 @@ template <int MB> constexpr int rows_early() { return MB >= 2 ? MB - 1 : MB; }
 // is the first region of a stage (FIRST): the stage is only known to have landed after the
 // barrier in front of it, so it reads its own first operands and the region before it (LAST)
 // reads nothing ahead.
-// How many groups (of MB MFMAs, 16.4 cycles each) an operand is read from LDS ahead of its use.
-// Three (the most the ring allows) was measured 2 % slower than two with three row blocks.
-template <int MB> constexpr int read_ahead() { return 2; }
+// How many groups (of MB MFMAs, 16.4 cycles each) an operand is read from LDS ahead of its use: three
+// is the most the ring allows (1 % less time than two on 2K tokens, one row block; 0.4 % on 32K, five;
+// with three row blocks it is 1 % more on 64K tokens; four to eight groups with a larger ring give no more).
+template <int MB> constexpr int read_ahead() { return MB == 3 ? 2 : 3; }
 
 // Pipeline region 1: the matrix cores compute the exponents of the NEXT sub-tile
 // (X^T = K Q'^T - m_ref into xn) while the vector ALUs turn the CURRENT sub-tile's exponents
