@@ -12,9 +12,6 @@
 
 #include <dlfcn.h>
 
-#include <array>
-
-#include <ATen/EmptyTensor.h>
 #include <ATen/core/Tensor.h>
 #include <ATen/hip/EmptyTensor.h>
 #include <ATen/ops/empty.h>
@@ -135,16 +132,7 @@ at::Tensor empty(at::IntArrayRef shape, at::ScalarType type, const at::Device& d
 at::Tensor empty_i32(at::IntArrayRef shape, const at::Device& dev) { return empty(shape, at::kInt, dev); }
 at::Tensor empty_bytes(size_t n, const at::Device& dev) { return empty({static_cast<int64_t>(n)}, at::kByte, dev); }
 
-// One result of a call: its key in the returned dict, its shape and element type.
-struct Result {
-    PyObject* key;
-    at::IntArrayRef shape;
-    at::ScalarType type = at::kInt;
-};
-
-// A dict of result tensors: either the caller's (no allocation) or a new one.  The tensors of a new
-// dict lie behind each other in one allocation, each on a 128-byte cache line of its own: a trip to
-// the caching allocator costs 0.35 us, and pruning returns seven tensors.
+// A dict of result tensors: either the caller's (no allocation) or a new one.
 class Outputs {
 public:
     Outputs(PyObject* given, const at::Device& dev) : dev_(dev) {
@@ -159,28 +147,11 @@ public:
     }
     ~Outputs() { Py_XDECREF(dict_); }
     Outputs(const Outputs&) = delete;
-    // The pointers of the results, in the order given (called once).
-    template <size_t N> std::array<void*, N> get(const Result (&r)[N]) {
-        std::array<void*, N> p;
-        if (!fresh_) {
-            for (size_t i = 0; i < N; ++i) p[i] = ptr<void>(item(dict_, r[i].key));
-            return p;
-        }
-        size_t at_byte[N], total = 0;
-        for (size_t i = 0; i < N; ++i) {
-            at_byte[i] = total;
-            at::detail::check_size_nonnegative(r[i].shape);
-            total += (at::detail::computeStorageNbytesContiguous(r[i].shape, c10::elementSize(r[i].type)) + 127) / 128 * 128;
-        }
-        const at::Tensor all = empty_bytes(total, dev_);
-        for (size_t i = 0; i < N; ++i) {
-            at::Tensor t = at::detail::make_tensor<c10::TensorImpl>(c10::Storage(all.storage()), all.key_set(),
-                                                                    c10::scalarTypeToTypeMeta(r[i].type));
-            t.unsafeGetTensorImpl()->set_sizes_contiguous(r[i].shape);
-            t.unsafeGetTensorImpl()->set_storage_offset(static_cast<int64_t>(at_byte[i] / c10::elementSize(r[i].type)));
-            p[i] = t.data_ptr();
-            put(r[i].key, THPVariable_Wrap(std::move(t)));
-        }
+    template <class T = int32_t> T* get(PyObject* key, at::IntArrayRef shape, at::ScalarType type = at::kInt) {
+        if (!fresh_) return ptr<T>(item(dict_, key));
+        at::Tensor t = empty(shape, type, dev_);
+        T* p = static_cast<T*>(t.data_ptr());
+        put(key, THPVariable_Wrap(std::move(t)));
         return p;
     }
     void put(PyObject* key, PyObject* value) {                     // steals value
@@ -200,7 +171,6 @@ private:
     bool fresh_ = false;
     at::Device dev_;
 };
-inline int32_t* i32(void* p) { return static_cast<int32_t*>(p); }
 
 // GraftError on a return code other than GRAFT_OK.
 void check(const char* fn, int32_t rc) {
@@ -257,14 +227,17 @@ GRAFT_PY(py_retrieve, 10) {
     sizes2(ctx, B, L_max);
     const int32_t n_min = to_i32(a[2]), n_max = to_i32(a[3]), C = to_i32(a[4]), m = to_i32(a[5]);
     Outputs out(a[8], ctx.device());
-    const auto r = out.get({{k_chain_tok, {B, C, m}}, {k_chain_len, {B, C}}, {k_chain_pos, {B, C}},
-                            {k_chain_match, {B, C}}, {k_n_hits, {B}}, {k_status, {B}}});
+    int32_t* tok = out.get(k_chain_tok, {B, C, m});
+    int32_t* len = out.get(k_chain_len, {B, C});
+    int32_t* pos = out.get(k_chain_pos, {B, C});
+    int32_t* match = out.get(k_chain_match, {B, C});
+    int32_t* hits = out.get(k_n_hits, {B});
+    int32_t* status = out.get(k_status, {B});
     const int32_t tail_max = a[6] == Py_None ? 0 : size_at(tensor(a[6]), 1);
     const int32_t *c = ptr<int32_t>(ctx), *cl = ptr<int32_t>(a[1]), *t = ptr<int32_t>(a[6]), *tl = ptr<int32_t>(a[7]);
     void* s = stream_of(a[9]);
     check("graft_retrieve", unlocked([&] {
-        return lib.graft_retrieve(c, cl, B, L_max, t, tl, tail_max, n_min, n_max, C, m, i32(r[0]), i32(r[1]), i32(r[2]),
-                                  i32(r[3]), i32(r[4]), i32(r[5]), s);
+        return lib.graft_retrieve(c, cl, B, L_max, t, tl, tail_max, n_min, n_max, C, m, tok, len, pos, match, hits, status, s);
     }));
     return out.release();
 }
@@ -277,18 +250,20 @@ GRAFT_PY(py_build_tree_mask, 7) {
     sizes2(parent, B, K);
     const int32_t n_leaf_max = to_i32(a[3]), depth_cap = to_i32(a[4]);
     Outputs out(a[5], parent.device());
-    const bool no_paths = out.fresh() && n_leaf_max <= 0;
-    const auto r = out.get({{k_mask, {B, K, GRAFT_MASK_WORDS}, at::kLong}, {k_pos, {B, K}}, {k_depth, {B, K}},
-                            {k_paths, {B, no_paths ? 0 : n_leaf_max, no_paths ? 0 : depth_cap + 1}}, {k_status, {B}}});
-    if (no_paths) {
+    uint64_t* mask = out.get<uint64_t>(k_mask, {B, K, GRAFT_MASK_WORDS}, at::kLong);
+    int32_t* pos = out.get(k_pos, {B, K});
+    int32_t* depth = out.get(k_depth, {B, K});
+    int32_t* paths = nullptr;
+    if (!out.fresh() || n_leaf_max > 0) paths = out.get(k_paths, {B, n_leaf_max, depth_cap + 1});
+    else {
         Py_INCREF(Py_None);
         out.put(k_paths, Py_None);
     }
+    int32_t* status = out.get(k_status, {B});
     const int32_t *p = ptr<int32_t>(parent), *n = ptr<int32_t>(a[1]), *pl = ptr<int32_t>(a[2]);
     void* s = stream_of(a[6]);
     check("graft_build_tree_mask", unlocked([&] {
-        return lib.graft_build_tree_mask(p, n, pl, B, K, static_cast<uint64_t*>(r[0]), i32(r[1]), i32(r[2]),
-                                         no_paths ? nullptr : i32(r[3]), n_leaf_max, depth_cap, i32(r[4]), s);
+        return lib.graft_build_tree_mask(p, n, pl, B, K, mask, pos, depth, paths, n_leaf_max, depth_cap, status, s);
     }));
     return out.release();
 }
@@ -371,8 +346,11 @@ GRAFT_PY(py_accept, 9) {
         Py_INCREF(ids_obj);
     }
     Outputs out(a[6], dev);
-    const auto r = out.get({{k_accept_len, {B}}, {k_best_node, {B}}, {k_path, {B, depth_cap + 1}},
-                            {k_out_tokens, {B, depth_cap + 1}}, {k_status, {B}}});
+    int32_t* len = out.get(k_accept_len, {B});
+    int32_t* best = out.get(k_best_node, {B});
+    int32_t* path = out.get(k_path, {B, depth_cap + 1});
+    int32_t* toks = out.get(k_out_tokens, {B, depth_cap + 1});
+    int32_t* status = out.get(k_status, {B});
     out.put(k_target_ids, ids_obj);
     if (a[7] != Py_None) {
         const at::Tensor& w = tensor(a[7]);
@@ -386,8 +364,7 @@ GRAFT_PY(py_accept, 9) {
     const int32_t *p = ptr<int32_t>(parent), *tk = ptr<int32_t>(a[1]), *n = ptr<int32_t>(a[2]);
     void* s = stream_of(a[8]);
     check("graft_accept", unlocked([&] {
-        return lib.graft_accept(p, tk, n, logits, V, ids, B, K, depth_cap, i32(r[0]), i32(r[1]), i32(r[2]), i32(r[3]), i32(r[4]),
-                                ws, ws_bytes, s);
+        return lib.graft_accept(p, tk, n, logits, V, ids, B, K, depth_cap, len, best, path, toks, status, ws, ws_bytes, s);
     }));
     return out.release();
 }
@@ -486,14 +463,15 @@ GRAFT_PY(py_kv_compact, 14) {
     const int32_t n_layers = to_i32(a[3]), K = to_i32(a[9]), Hkv = to_i32(a[10]), D = to_i32(a[11]);
     const Strides st = strides_of(a[4]);
     Outputs out(a[12], path.device());
-    const auto r = out.get({{k_new_prefix_len, {B}}, {k_status, {B}}});
+    int32_t* new_len = out.get(k_new_prefix_len, {B});
+    int32_t* status = out.get(k_status, {B});
     void *kp = ptr<void>(k), *vp = ptr<void>(v);
     const int32_t *tp = ptr<int32_t>(table), *pl = ptr<int32_t>(a[6]), *pp = ptr<int32_t>(path), *al = ptr<int32_t>(a[8]);
     const int32_t max_pages = size_at(table, 1);
     void* s = stream_of(a[13]);
     check("graft_kv_compact", unlocked([&] {
         return lib.graft_kv_compact(kp, vp, layer_stride, n_layers, st.page, st.token, st.head, tp, max_pages, pl, pp, al, B,
-                                    width - 1, K, Hkv, D, type == at::kFloat ? GRAFT_F32 : GRAFT_BF16, i32(r[0]), i32(r[1]), s);
+                                    width - 1, K, Hkv, D, type == at::kFloat ? GRAFT_F32 : GRAFT_BF16, new_len, status, s);
     }));
     return out.release();
 }
@@ -505,16 +483,20 @@ GRAFT_PY(py_prune_select, 10) {
     int32_t B, K;
     sizes2(parent, B, K);
     Outputs out(a[8], parent.device());
-    const auto r = out.get({{k_parent, {B, K}}, {k_tokens, {B, K}}, {k_index, {B, K}}, {k_n_nodes, {B}}, {k_stage, {B}},
-                            {k_n_ret, {B}}, {k_status, {B}}});
+    int32_t* op = out.get(k_parent, {B, K});
+    int32_t* ot = out.get(k_tokens, {B, K});
+    int32_t* oi = out.get(k_index, {B, K});
+    int32_t* on = out.get(k_n_nodes, {B});
+    int32_t* stage = out.get(k_stage, {B});
+    int32_t* nr = out.get(k_n_ret, {B});
+    int32_t* status = out.get(k_status, {B});
     const int32_t *p = ptr<int32_t>(parent), *tk = ptr<int32_t>(a[1]), *n = ptr<int32_t>(a[3]), *cd = ptr<int32_t>(a[4]),
                   *ck = ptr<int32_t>(a[6]), *cr = ptr<int32_t>(a[7]);
     const float *lq = ptr<float>(a[2]), *ct = ptr<float>(a[5]);
     const int32_t n_chk = size_at(tensor(a[4]), 0);
     void* s = stream_of(a[9]);
     check("graft_prune_select", unlocked([&] {
-        return lib.graft_prune_select(p, tk, lq, n, B, K, cd, ct, ck, cr, n_chk, i32(r[0]), i32(r[1]), i32(r[2]), i32(r[3]),
-                                      i32(r[4]), i32(r[5]), i32(r[6]), s);
+        return lib.graft_prune_select(p, tk, lq, n, B, K, cd, ct, ck, cr, n_chk, op, ot, oi, on, stage, nr, status, s);
     }));
     return out.release();
 }

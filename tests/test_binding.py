@@ -36,23 +36,3 @@ def test_library_errors_carry_their_code():
     with pytest.raises(AssertionError):                                               # mixed storage types
         graft.graft_tree_attn(q, q.float(), q, {"page": 1, "token": 1, "head": 1}, torch.zeros((1, 2), dtype=torch.int32),
                               None, None, None, 2, 0.1, stream=0)
-
-
-@pytest.mark.gpu
-@pytest.mark.parametrize("B,K,n_leaf_max", [(1, 1, 0), (1, 1, 1), (3, 33, 33), (16, 128, 128)])
-def test_new_results_lie_apart(B, K, n_leaf_max):
-    """The results of one call share an allocation: aligned, dense, and no byte in two of them."""
-    dev = "cuda"
-    parent = torch.arange(-1, K - 1, dtype=torch.int32, device=dev).repeat(B, 1)
-    n = torch.full((B,), K, dtype=torch.int32, device=dev)
-    r = graft.graft_build_tree_mask(parent, n, n, n_leaf_max, 127)
-    assert (r["paths"] is None) == (n_leaf_max == 0)
-    ts = [t for t in r.values() if t is not None]
-    assert [tuple(t.shape) for t in ts][:3] == [(B, K, 2), (B, K), (B, K)] and ts[0].dtype == torch.int64
-    spans = sorted((t.data_ptr(), t.data_ptr() + t.numel() * t.element_size()) for t in ts)
-    assert all(t.is_contiguous() and t.device == parent.device and t.data_ptr() % 128 == 0 for t in ts)
-    assert all(a[1] <= b[0] for a, b in zip(spans, spans[1:]))
-    before = [t.clone() for t in ts]
-    ts[1].add_(1)                                                                     # in place, as any tensor
-    assert torch.equal(ts[1], before[1] + 1) and all(torch.equal(a, b) for a, b in zip(ts[2:], before[2:]))
-    assert torch.equal(r["depth"], torch.arange(K, dtype=torch.int32, device=dev).repeat(B, 1)) and not r["status"].any()
