@@ -16,6 +16,7 @@
 #include <ATen/hip/EmptyTensor.h>
 #include <ATen/ops/empty.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "graft.h"
@@ -88,18 +89,26 @@ int32_t size_at(const at::Tensor& t, int64_t dim) {
     return static_cast<int32_t>(t.size(dim));
 }
 
-// Borrowed reference; KeyError if the key is missing.
-PyObject* item(PyObject* dict, PyObject* key) {
-    PyObject* v = PyDict_CheckExact(dict) ? PyDict_GetItemWithError(dict, key) : nullptr;
-    if (!v && !PyErr_Occurred()) {
-        if (PyDict_CheckExact(dict)) PyErr_SetObject(PyExc_KeyError, key);
-        else {                                                    // any other mapping
-            v = PyObject_GetItem(dict, key);
-            Py_XDECREF(v);                                        // the mapping holds it
-        }
-    }
+// A reference held for as long as the object is looked at.
+struct Ref {
+    PyObject* o;
+    explicit Ref(PyObject* owned) : o(owned) {}
+    ~Ref() { Py_XDECREF(o); }
+    Ref(const Ref&) = delete;
+    operator PyObject*() const { return o; }
+};
+
+// KeyError if the key is missing.  The reference is held: a mapping other than a dict may make its
+// values on the fly.
+Ref item(PyObject* dict, PyObject* key) {
+    PyObject* v;
+    if (PyDict_CheckExact(dict)) {
+        v = PyDict_GetItemWithError(dict, key);
+        Py_XINCREF(v);
+        if (!v && !PyErr_Occurred()) PyErr_SetObject(PyExc_KeyError, key);
+    } else v = PyObject_GetItem(dict, key);
     if (!v) throw PythonError();
-    return v;
+    return Ref(v);
 }
 
 struct Strides { int64_t page, token, head; };
@@ -211,8 +220,8 @@ void need_args(Py_ssize_t got, Py_ssize_t want) {
             return name##_body(a);                                                         \
         } catch (const PythonError&) {                                                     \
             return nullptr;                                                                \
-        } catch (const std::exception& e) {                                                \
-            PyErr_SetString(PyExc_RuntimeError, e.what());                                 \
+        } catch (...) { /* as torch raises it: out of memory is torch.OutOfMemoryError */  \
+            torch::translate_exception_to_python(std::current_exception());                \
             return nullptr;                                                                \
         }                                                                                  \
     }                                                                                      \
@@ -345,12 +354,14 @@ GRAFT_PY(py_accept, 9) {
         ids = ptr<int32_t>(a[4]);
         Py_INCREF(ids_obj);
     }
+    const Ref ids_held(ids_obj);
     Outputs out(a[6], dev);
     int32_t* len = out.get(k_accept_len, {B});
     int32_t* best = out.get(k_best_node, {B});
     int32_t* path = out.get(k_path, {B, depth_cap + 1});
     int32_t* toks = out.get(k_out_tokens, {B, depth_cap + 1});
     int32_t* status = out.get(k_status, {B});
+    Py_INCREF(ids_obj);
     out.put(k_target_ids, ids_obj);
     if (a[7] != Py_None) {
         const at::Tensor& w = tensor(a[7]);
@@ -417,6 +428,10 @@ GRAFT_PY(py_matrix_retrieve, 9) {
 // tokens, n_nodes, logits, M, target_ids, workspace, stream
 GRAFT_PY(py_matrix_update, 7) {
     const at::Tensor &lg = tensor(a[2]), &M = tensor(a[3]);
+    if (lg.dim() != 3) {
+        PyErr_Format(PyExc_ValueError, "expected logits of 3 dimensions, got %d", static_cast<int>(lg.dim()));
+        throw PythonError();
+    }
     const int32_t B = size_at(lg, 0), K = size_at(lg, 1), V = size_at(lg, 2), k = size_at(M, 1);
     at::Tensor fresh, new_ws;
     int32_t* ids;

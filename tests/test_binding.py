@@ -24,6 +24,14 @@ def test_arguments_that_do_not_fit(kwargs, error):
         _mask(**kwargs)
 
 
+def test_logits_are_three_dimensional():
+    one = torch.ones(1, dtype=torch.int32)
+    for shape in ((1, 4, 8, 1), (4, 8)):
+        with pytest.raises(ValueError):
+            graft.graft_matrix_update(torch.zeros((1, 4), dtype=torch.int32), one, torch.zeros(shape), torch.zeros((8, 2), dtype=torch.int32),
+                                      stream=0)
+
+
 def test_library_errors_carry_their_code():
     with pytest.raises(graft.GraftError) as e:
         _mask(depth_cap=200)
@@ -36,3 +44,34 @@ def test_library_errors_carry_their_code():
     with pytest.raises(AssertionError):                                               # mixed storage types
         graft.graft_tree_attn(q, q.float(), q, {"page": 1, "token": 1, "head": 1}, torch.zeros((1, 2), dtype=torch.int32),
                               None, None, None, 2, 0.1, stream=0)
+
+
+def test_strides_from_a_mapping_that_makes_its_values():
+    """The values are held while they are read: they die behind it, not before."""
+    events = []
+
+    class Value:
+        def __int__(self):
+            events.append("read")
+            return 12
+
+        def __del__(self):
+            events.append("gone")
+
+    class Strides:
+        def __getitem__(self, key):
+            return Value()
+
+    q = torch.zeros((1, 4, 8, 64), dtype=torch.bfloat16)
+    one = torch.zeros(1, dtype=torch.int32)
+    with pytest.raises(graft.GraftError) as e:                                        # 12 is no stride of D = 64
+        graft.graft_tree_attn(q, q, q, Strides(), torch.zeros((1, 2), dtype=torch.int32), one, one,
+                              torch.zeros((1, 4, 2), dtype=torch.int64), 2, 0.1, stream=0)
+    assert e.value.code == graft.GRAFT_ERR_SHAPE and events == ["read"] * 3 + ["gone"] * 3
+
+
+@pytest.mark.gpu
+def test_out_of_memory_is_torchs_own_error():
+    ctx, n = torch.zeros((1, 8), dtype=torch.int32, device="cuda"), torch.full((1,), 8, dtype=torch.int32, device="cuda")
+    with pytest.raises(torch.OutOfMemoryError):                                       # 4 TiB of results, refused by the allocator
+        graft.graft_retrieve(ctx, n, 1, 4, 1 << 20, 1 << 20)
