@@ -1503,10 +1503,13 @@ extern "C" int32_t graft_tree_attn(const void* q, const void* k_cache, const voi
     hipStream_t s = static_cast<hipStream_t>(stream);
 
     const PathChoice& choice = choose_path(B, K_max, Hq, Hkv, D, max_pages, dtype);
-    if (choice.direct) {
+    const auto fits = [&](size_t need) { return need == 0 || (workspace && workspace_bytes >= need); };
+    const bool either = dtype == GRAFT_BF16 && D == AT_D;
+    // bf16 with D = 128 and a workspace too small for the direct plan: the MFMA path if its own plan needs no more
+    if (choice.direct && (!either || fits(choice.dir.ws_bytes) || !fits(choice.mfma.ws_bytes))) {
         DirectPlan dp = choice.dir;
-        if (dp.ws_bytes > 0 && (!workspace || workspace_bytes < dp.ws_bytes)) {
-            if (dtype == GRAFT_BF16 && D == AT_D) return GRAFT_ERR_WORKSPACE;
+        if (!fits(dp.ws_bytes)) {
+            if (either) return GRAFT_ERR_WORKSPACE;
             // the other shapes have always run without a workspace: a caller that brings none, or too
             // little, gets a launch that does not split the keys over workgroups
             dp = plan_direct(B, K_max, Hq, Hkv, D, max_pages, dtype, false);
@@ -1515,7 +1518,7 @@ extern "C" int32_t graft_tree_attn(const void* q, const void* k_cache, const voi
     }
 
     const AttnPlan& pl = choice.mfma;
-    if (pl.ws_bytes > 0 && (!workspace || workspace_bytes < pl.ws_bytes)) return GRAFT_ERR_WORKSPACE;
+    if (!fits(pl.ws_bytes)) return GRAFT_ERR_WORKSPACE;
     p.R_pad = pl.r_pad; p.n_splits = pl.n_splits; p.n_row_tiles = pl.n_row_tiles;
     p.ws_o = static_cast<unsigned short*>(workspace);
     p.ws_ml = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + pl.ws_o_bytes);

@@ -117,3 +117,25 @@ def test_head_128_with_few_keys(case, layout):
     n_nodes = None if B == 1 else np.concatenate([[K], rng.integers(1, K + 1, B - 1)]).astype(np.int32)
     prefix = None if B == 1 else np.concatenate([[P], rng.integers(0, P + 1, B - 1)]).astype(np.int32)
     check_case(w, seed=K + P, layout=layout, n_nodes=n_nodes, prefix=prefix)
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
+def test_tensors_that_start_at_any_element(dtype, D):
+    """Rows are 16 bytes apart or a multiple of it, but a tensor may start at any element: the bits are those of the
+    same data at the start of an allocation (the same path, hence the same order of every sum)."""
+    w = shape_workload(1, 20, 8, 8, D, 100, dtype=dtype)
+    att = inputs.make_attention_inputs(w, seed=9)
+    parent = np.stack([inputs.random_recursive_tree(np.random.default_rng(9), w.K, 8)])
+    n, p = np.array([w.K], np.int32), np.array([w.P], np.int32)
+    mask = gpu_mask(parent, n, p)
+    tensors = [dev(att[k][0], dtype) for k in ("q", "k_cache", "v_cache")] + [torch.zeros_like(dev(att["q"][0], dtype))]
+
+    def moved(t):
+        u = torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")[1:].view(t.shape)
+        return u.copy_(t)
+
+    def run(q, k, v, out):
+        return graft.graft_tree_attn(q, k, v, att["strides"], dev(att["block_table"]), dev(p), dev(n), mask, w.Hkv, att["scale"], out=out)
+
+    a, b = run(*tensors), run(*[moved(t) for t in tensors])
+    assert torch.equal(a, b)
