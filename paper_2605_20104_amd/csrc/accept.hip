@@ -14,6 +14,8 @@
 namespace graft {
 
 constexpr int AM_THREADS = 256;
+constexpr int AM_WAVES = AM_THREADS / 64;
+constexpr int AM_QUADS = 12;                     // 16-byte loads in flight per thread: a whole chunk up to V = 196608
 constexpr int AC_THREADS = GRAFT_MAX_NODES;
 
 struct ArgPartial { float val; int32_t idx; };
@@ -23,6 +25,10 @@ __device__ __forceinline__ void arg_take(float& bv, int32_t& bi, float v, int32_
     if (v > bv || (v == bv && i < bi)) { bv = v; bi = i; }
 }
 
+// Bound by the logits' way from HBM: a workgroup requests its whole chunk before it looks at any of it, keeps
+// only the maximum (one max3 per two elements) and looks for its index in the registers of the lane that
+// has it.  8 x 48 rows of 151936 (233 MB): 48.0 -> 46.3 us for the call, 5.0 TB/s, the walk kernel and the gap
+// before it included; four loads in flight and an (index, value) pair kept per element before.
 __global__ __launch_bounds__(AM_THREADS) void argmax_chunk_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ n_nodes, int32_t K_max, int32_t V,
     ArgPartial* __restrict__ partial) {
@@ -34,53 +40,53 @@ __global__ __launch_bounds__(AM_THREADS) void argmax_chunk_kernel(
         if (tid == 0) { out->val = -INFINITY; out->idx = 0x7fffffff; }
         return;
     }
-    // chunk boundaries in units of 4 elements so that aligned rows can use 16-byte loads
-    const int32_t quads = (V + 3) / 4;
-    const int32_t per = (quads + GRAFT_ARGMAX_CHUNKS - 1) / GRAFT_ARGMAX_CHUNKS;
-    const int32_t q0 = chunk * per;
-    const int32_t q1 = (q0 + per) < quads ? (q0 + per) : quads;
     const float* row = logits + (static_cast<size_t>(b) * K_max + i) * V;
-    float bv = -INFINITY;
+    const RowChunk c = row_chunk(row, V, chunk);
+    __shared__ float sv[AM_WAVES + 4];
+    __shared__ int32_t si[AM_WAVES + 4];
+    if (tid < c.edge) { sv[AM_WAVES + tid] = row[c.edge_at + tid]; si[AM_WAVES + tid] = c.edge_at + tid; }
+    float bv = -INFINITY;                        // the wavefront's maximum so far and its first index
     int32_t bi = 0x7fffffff;
-    const bool vec = (V % 4 == 0);               // then every row start is 16-byte aligned
-    if (vec) {
-        const float4* row4 = reinterpret_cast<const float4*>(row);
-        constexpr int U = 4;                         // 16-byte loads in flight per thread
-        for (int32_t qd = q0 + tid; qd < q1; qd += U * AM_THREADS) {
-            float4 x[U];
+    for (int32_t s0 = c.q0; s0 < c.q1; s0 += AM_QUADS * AM_THREADS) {
+        float4 x[AM_QUADS];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int32_t qu = qd + u * AM_THREADS;
-                x[u] = row4[qu < q1 ? qu : qd];      // a lane past the end re-reads its first quad (skipped below)
-            }
+        for (int u = 0; u < AM_QUADS; ++u) {
+            const int32_t qu = s0 + tid + u * AM_THREADS;
+            x[u] = qu < c.q1 ? c.quad[qu] : float4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        }
+        float m = -INFINITY;                     // (fmax passes over NaN, as the comparisons do)
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int32_t qu = qd + u * AM_THREADS;
-                if (qu < q1) {
-                    const int32_t base = qu * 4;
-                    arg_take(bv, bi, x[u].x, base);
-                    arg_take(bv, bi, x[u].y, base + 1);
-                    arg_take(bv, bi, x[u].z, base + 2);
-                    arg_take(bv, bi, x[u].w, base + 3);
+        for (int u = 0; u < AM_QUADS; ++u)
+            m = __builtin_fmaxf(__builtin_fmaxf(__builtin_fmaxf(m, x[u].x), __builtin_fmaxf(x[u].y, x[u].z)), x[u].w);
+        const float wm = wave_max_f32(m);
+        if (wm > bv || bi == 0x7fffffff) {       // uniform over the wavefront
+            int32_t at = 0x7fffffff;
+            if (m == wm) {                       // hardly ever more than one lane
+#pragma unroll
+                for (int u = AM_QUADS - 1; u >= 0; --u) {
+                    const int32_t qu = s0 + tid + u * AM_THREADS;
+                    const int32_t e = c.head + 4 * qu;
+                    if (qu < c.q1) {
+                        at = x[u].w == wm ? e + 3 : at;
+                        at = x[u].z == wm ? e + 2 : at;
+                        at = x[u].y == wm ? e + 1 : at;
+                        at = x[u].x == wm ? e : at;
+                    }
                 }
             }
-        }
-    } else {
-        const int32_t e0 = q0 * 4, e1 = (q1 * 4) < V ? (q1 * 4) : V;
-        for (int32_t e = e0 + tid; e < e1; e += AM_THREADS) arg_take(bv, bi, row[e], e);
-    }
 #pragma unroll
-    for (int s = 32; s >= 1; s >>= 1) {
-        float ov = __shfl_xor(bv, s);
-        int32_t oi = __shfl_xor(bi, s);
-        arg_take(bv, bi, ov, oi);
+            for (int s = 32; s >= 1; s >>= 1) {
+                const int32_t other = __shfl_xor(at, s);
+                at = other < at ? other : at;
+            }
+            bv = wm;
+            bi = at;
+        }
     }
-    __shared__ float sv[AM_THREADS / 64];
-    __shared__ int32_t si[AM_THREADS / 64];
     if ((tid & 63) == 0) { sv[tid >> 6] = bv; si[tid >> 6] = bi; }
     __syncthreads();
     if (tid == 0) {
-        for (int w = 1; w < AM_THREADS / 64; ++w) arg_take(bv, bi, sv[w], si[w]);
+        for (int w = 1; w < AM_WAVES + c.edge; ++w) arg_take(bv, bi, sv[w], si[w]);
         out->val = bv;
         out->idx = bi;
     }

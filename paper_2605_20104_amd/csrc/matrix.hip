@@ -105,35 +105,29 @@ __device__ __forceinline__ void topk_insert(u64 (&top)[KK], float& worst, float 
     }
 }
 
-// The scan of one thread's share of a chunk.  take(value, id) is called for every element in
-// order of id.
+// The scan of one thread's share of a chunk: take(value, id) for every element.
 template <class Take>
-__device__ __forceinline__ void scan_chunk(const float* __restrict__ row, int32_t V, int32_t q0, int32_t q1,
-                                           int tid, Take&& take) {
-    if (V % 4 == 0) {                               // every row start is 16-byte aligned
-        const float4* row4 = reinterpret_cast<const float4*>(row);
-        constexpr int U = 4;                        // 16-byte loads in flight per thread
-        for (int32_t qd = q0 + tid; qd < q1; qd += U * MU_THREADS) {
-            float4 x[U];
+__device__ __forceinline__ void scan_chunk(const float* __restrict__ row, const RowChunk& c, int tid, Take&& take) {
+    if (tid < c.edge) take(row[c.edge_at + tid], c.edge_at + tid);
+    constexpr int U = 4;                            // 16-byte loads in flight per thread
+    for (int32_t qd = c.q0 + tid; qd < c.q1; qd += U * MU_THREADS) {
+        float4 x[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int32_t qu = qd + u * MU_THREADS;
-                x[u] = row4[qu < q1 ? qu : qd];     // a lane past the end re-reads its first quad (skipped below)
-            }
+        for (int u = 0; u < U; ++u) {
+            const int32_t qu = qd + u * MU_THREADS;
+            x[u] = c.quad[qu < c.q1 ? qu : qd];     // a lane past the end re-reads its first quad (skipped below)
+        }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int32_t qu = qd + u * MU_THREADS;
-                if (qu < q1) {
-                    take(x[u].x, qu * 4);
-                    take(x[u].y, qu * 4 + 1);
-                    take(x[u].z, qu * 4 + 2);
-                    take(x[u].w, qu * 4 + 3);
-                }
+        for (int u = 0; u < U; ++u) {
+            const int32_t qu = qd + u * MU_THREADS;
+            if (qu < c.q1) {
+                const int32_t e = c.head + qu * 4;
+                take(x[u].x, e);
+                take(x[u].y, e + 1);
+                take(x[u].z, e + 2);
+                take(x[u].w, e + 3);
             }
         }
-    } else {
-        const int32_t e0 = q0 * 4, e1 = (q1 * 4) < V ? (q1 * 4) : V;
-        for (int32_t e = e0 + tid; e < e1; e += MU_THREADS) take(row[e], e);
     }
 }
 
@@ -164,8 +158,8 @@ __device__ __forceinline__ int select_rounds(u64 (&top)[KK], int k, u64 (&red)[2
 
 // Chunk scan: workgroup (chunk, node, sequence) -> its chunk's k best keys, best first.
 //
-// Fast path (aligned rows whose chunk fits in registers, MU_REG_QUADS 16-byte loads per
-// thread, all issued before anything else):
+// Fast path (chunks that fit in registers, MU_REG_QUADS 16-byte loads per thread and at most one
+// edge element, all issued before anything else):
 //   1. every thread takes the maximum of its elements (one max3 per two elements);
 //   2. every wavefront finds the k-th largest of its 64 maxima (k rounds of a float max in
 //      registers; equal maxima leave together, which only lowers the result) and T is the
@@ -190,29 +184,28 @@ __global__ __launch_bounds__(MU_THREADS) void topk_chunk_kernel(
         if (tid < k) out[tid] = 0;
         return;
     }
-    const int32_t quads = (V + 3) / 4;
-    const int32_t per = (quads + GRAFT_ARGMAX_CHUNKS - 1) / GRAFT_ARGMAX_CHUNKS;
-    const int32_t q0 = chunk * per;
-    const int32_t q1 = (q0 + per) < quads ? (q0 + per) : quads;
     const float* row = logits + (static_cast<size_t>(b) * K_max + i) * V;
+    const RowChunk c = row_chunk(row, V, chunk);
+    const int32_t q0 = c.q0, q1 = c.q1;
     __shared__ u64 red[2][MU_WAVES];
     __shared__ u64 list[MU_LIST];
     __shared__ int32_t list_n;
 
     bool exact = true;
-    if (V % 4 == 0 && per <= MU_REG_QUADS * MU_THREADS) {           // uniform over the grid
-        const float4* row4 = reinterpret_cast<const float4*>(row);
+    if (q1 - q0 <= MU_REG_QUADS * MU_THREADS) {                      // uniform over the workgroup
         float4 x[MU_REG_QUADS];
+        const float xe = tid < c.edge ? row[c.edge_at + tid] : -INFINITY;
 #pragma unroll
         for (int u = 0; u < MU_REG_QUADS; ++u) {
             const int32_t qu = q0 + tid + u * MU_THREADS;
-            x[u] = qu < q1 ? row4[qu] : float4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+            x[u] = qu < q1 ? c.quad[qu] : float4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
         }
         if (tid == 0) list_n = 0;
         float m = -INFINITY;
 #pragma unroll
         for (int u = 0; u < MU_REG_QUADS; ++u)
             m = __builtin_fmaxf(__builtin_fmaxf(__builtin_fmaxf(m, x[u].x), __builtin_fmaxf(x[u].y, x[u].z)), x[u].w);
+        m = __builtin_fmaxf(m, xe);                                  // (last: it was requested last)
         // T = the largest over the wavefronts of "k-th largest of the wavefront's maxima"
         float mm = m, tw = -INFINITY;
         for (int j = 0; j < k; ++j) {
@@ -223,6 +216,10 @@ __global__ __launch_bounds__(MU_THREADS) void topk_chunk_kernel(
         if (lane == 0) tws[wave] = tw;
         __syncthreads();                                             // also orders list_n = 0 before the appends
         const float T = __builtin_fmaxf(__builtin_fmaxf(tws[0], tws[1]), __builtin_fmaxf(tws[2], tws[3]));
+        if (tid < c.edge && xe >= T) {
+            const int slot = atomicAdd(&list_n, 1);
+            if (slot < MU_LIST) list[slot] = rank_key(xe, c.edge_at + tid);
+        }
 #pragma unroll
         for (int u = 0; u < MU_REG_QUADS; ++u) {
             const int32_t qu = q0 + tid + u * MU_THREADS;
@@ -232,7 +229,7 @@ __global__ __launch_bounds__(MU_THREADS) void topk_chunk_kernel(
                 for (int t = 0; t < 4; ++t) {
                     if (e[t] >= T) {
                         const int slot = atomicAdd(&list_n, 1);
-                        if (slot < MU_LIST) list[slot] = rank_key(e[t], qu * 4 + t);
+                        if (slot < MU_LIST) list[slot] = rank_key(e[t], c.head + qu * 4 + t);
                     }
                 }
             }
@@ -266,7 +263,7 @@ __global__ __launch_bounds__(MU_THREADS) void topk_chunk_kernel(
 #pragma unroll
     for (int j = 0; j < KK; ++j) top[j] = 0;
     float worst = -INFINITY;
-    scan_chunk(row, V, q0, q1, tid, [&](float v, int32_t id) { topk_insert<KK>(top, worst, v, id); });
+    scan_chunk(row, c, tid, [&](float v, int32_t id) { topk_insert<KK>(top, worst, v, id); });
     select_rounds<KK>(top, k, red, out, tid, lane, wave);
 }
 

@@ -1,0 +1,59 @@
+"""The scans of logits rows (acceptance, matrix refresh) at every cut of a row into 16-byte groups: lengths and
+addresses that are no multiple of it, rows shorter than the workgroups that share them, chunks longer than
+the registers, runs of equal values, -inf and NaN.  Whole numbers: exact (MI355X only)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2605_20104_amd as graft
+
+pytestmark = pytest.mark.gpu
+
+# 196608 = 16 chunks of 12 16-byte loads by 256 threads
+LENGTHS = [1, 2, 3, 4, 5, 7, 16, 63, 64, 67, 1000, 4099, 16385, 50257, 151936, 196608, 196609, 196615, 262147]
+
+
+def best(row, k):
+    """Ids of the k largest, the smaller id first among equals; NaN is never chosen, -1 where nothing is left."""
+    order = np.lexsort((np.arange(len(row)), -row))
+    return (order[~np.isnan(row[order])][:k].tolist() + [-1] * k)[:k]
+
+
+@pytest.mark.parametrize("V", LENGTHS)
+@pytest.mark.parametrize("shift", [0, 1, 2, 3])
+def test_rows_of_any_length_and_address(V, shift):
+    rng = np.random.default_rng(V + shift)
+    B, K, k = 2, 5, min(8, V)
+    logits = rng.standard_normal((B, K, V)).astype(np.float32)
+    logits[0, 1, -1] = logits[0, 1, 0] = 9.0                               # first and last element, equal
+    logits[0, 2] = np.round(logits[0, 2])                                  # long runs of equal values
+    logits[0, 3, : V - 1] = -np.inf
+    logits[1, 0, V // 2:] = 7.0
+    logits[1, 1, ::2] = np.nan
+    logits[1, 1, V - 1] = 20.0
+    logits[1, 3, : max(0, V - 2)] = logits[1, 3, : max(0, V - 2)].clip(max=3.0)
+    logits[1, 3, -1] = 11.0                                                # the tail alone
+    buf = torch.full((logits.size + shift + 4,), 100.0, device="cuda")     # what lies around the rows is larger
+    lg = buf[shift:shift + logits.size].view(B, K, V)
+    lg.copy_(torch.from_numpy(logits))
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda()
+    parent = np.tile(np.arange(-1, K - 1), (B, 1))
+    tokens = np.stack([(np.arange(K) + 5 * b) % V for b in range(B)])
+    n = up([K, K - 1])
+    want = np.array([[best(logits[b, i], 1)[0] if i < K - b else -1 for i in range(K)] for b in range(B)])
+
+    acc = graft.graft_accept(up(parent), up(tokens), n, 8, logits=lg)
+    assert (acc["target_ids"].cpu().numpy() == want).all()
+
+    M = torch.full((V, k), -7, dtype=torch.int32, device="cuda")
+    ids = graft.graft_matrix_update(up(tokens), n, lg, M)
+    assert (ids.cpu().numpy() == want).all()
+    rows = {}
+    for b in range(B):
+        for i in range(K - b):
+            rows[int(tokens[b, i])] = best(logits[b, i], k)
+    if len(set(tokens.ravel().tolist())) == B * K:                          # (a token met twice: the order is pinned elsewhere)
+        got = M.cpu().numpy()
+        for t, r in rows.items():
+            valid = [x for x in r if x >= 0]
+            assert got[t][:len(valid)].tolist() == valid
