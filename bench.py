@@ -417,7 +417,7 @@ def run_workload(args, name, steps, warmup, light):
         "per_call_us": {k: round(v, 2) for k, v in per_call_us.items()},
         "extended": extended,
         "roofline": {
-            "kernel": "tree_attn_mfma_kernel" if (w.dtype == "bf16" and w.D == 128) else "tree_attn_simple_kernel",
+            "kernel": "tree_attn_mfma_kernel" if (w.dtype == "bf16" and w.D == 128) else "tree_attn_direct_kernel",
             "bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
             "kernel_avg_us": round(kernel_avg_ms * 1e3, 3), "launches_timed": n_ev,
