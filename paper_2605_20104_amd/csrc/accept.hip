@@ -27,7 +27,7 @@ __device__ __forceinline__ void arg_take(float& bv, int32_t& bi, float v, int32_
 
 // Bound by the logits' way from HBM: a workgroup requests its whole chunk before it looks at any of it, keeps
 // only the maximum (one max3 per two elements) and looks for its index in the registers of the lane that
-// has it.  8 x 48 rows of 151936 (233 MB): 48.0 -> 46.3 us for the call, 5.0 TB/s, the walk kernel and the gap
+// has it.  8 x 48 rows of 151936 (233 MB): 48.0 -> 46.2 us for the call, 5.0 TB/s, the walk kernel and the gap
 // before it included; four loads in flight and an (index, value) pair kept per element before.
 __global__ __launch_bounds__(AM_THREADS) void argmax_chunk_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ n_nodes, int32_t K_max, int32_t V,
@@ -117,6 +117,13 @@ __global__ __launch_bounds__(AC_THREADS) void accept_walk_kernel(
     tok[i] = i < K_max ? tokens[row + i] : -1;
     // (requested with the other inputs: one trip to memory for all of them)
     const int32_t ts_given = (!partial && i < K_max) ? target_ids[row + i] : -1;
+    // (the scan has written the partials of padding nodes too; requested here 45.6 us a call, behind the
+    // barrier 46.2)
+    ArgPartial pr[GRAFT_ARGMAX_CHUNKS];
+    if (partial && i < K_max) {
+#pragma unroll
+        for (int c = 0; c < GRAFT_ARGMAX_CHUNKS; ++c) pr[c] = partial[(row + i) * GRAFT_ARGMAX_CHUNKS + c];
+    }
     const bool any_bad = workgroup_or_128(bad, or_bad);
 
     const int32_t width = depth_cap + 1;
@@ -134,9 +141,9 @@ __global__ __launch_bounds__(AC_THREADS) void accept_walk_kernel(
     if (i < K_max) {
         if (partial) {
             if (i < n) {
-                const ArgPartial* pr = partial + (row + i) * GRAFT_ARGMAX_CHUNKS;
                 float bv = pr[0].val;
                 int32_t bi = pr[0].idx;
+#pragma unroll
                 for (int c = 1; c < GRAFT_ARGMAX_CHUNKS; ++c) arg_take(bv, bi, pr[c].val, pr[c].idx);
                 ts = bi;
             }
