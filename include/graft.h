@@ -172,8 +172,8 @@ int32_t graft_build_tree_mask(const int32_t* parent, const int32_t* n_nodes, con
  * scale                       softmax scale, normally 1/sqrt(D)
  * dtype                       GRAFT_F32: fp32 storage and arithmetic throughout.
  *                             GRAFT_BF16: bf16 storage, fp32 scores/softmax/accumulation,
- *                             probabilities rounded to bf16 for the P.V product (D = 128;
- *                             D = 64 keeps 17 bits of them); where, with D = 128, the
+ *                             probabilities rounded to bf16 for the P.V product (D = 128
+ *                             only: D = 64 keeps them whole); where, with D = 128, the
  *                             keys are split over workgroups, each split's normalised
  *                             partial row passes through memory as fp16 scaled by a power
  *                             of two to its largest entry: 11 bits for entries within

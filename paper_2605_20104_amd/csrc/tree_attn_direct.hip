@@ -8,9 +8,9 @@
 //   fp32 : v_mfma_f32_16x16x4_f32 (full fp32 products and sums, 32 cycles each).  The kernel is
 //          bound by them: 64 (D = 128) or 32 (D = 64) per 16 keys and 16 rows.
 //   bf16 : v_mfma_f32_16x16x32_bf16 on raw Q and K (exact products, fp32 sums); the softmax scale
-//          is applied in fp32.  With D = 64 probabilities enter the second product as the sum of two
-//          bf16 numbers (relative error 2^-17: far below the rounding of the result), with D = 128
-//          rounded to one, as on the path this stands in for.  Bound by the vector ALUs (exp2 and the
+//          is applied in fp32.  With D = 64 probabilities enter the second product whole, as the sum of
+//          three bf16 numbers (two, 17 bits, put the results further from a 64-bit reference), with
+//          D = 128 rounded to one, as on the path this stands in for.  Bound by the vector ALUs (exp2 and the
 //          packing of probabilities).
 // Operand layouts (lane = 16 lg + l16).  First product: S^T = K Q^T, A = K (key l16), B = Q^T
 // (row l16), so a lane gets 4 keys (4 lg + i) of one row, and these are the B operand of the
@@ -143,8 +143,8 @@ template <int D> struct DirectOps<__bf16, D> {
     static constexpr int NO = D / 16;
     static constexpr int NC = 2;
     static constexpr int ROW = D * 2;
-    static constexpr bool SUM_MFMA = true;      // row sums through the matrix cores, which have time left here
-    static constexpr bool SPLIT_P = D == 64;    // probabilities as two bf16 numbers (D = 128: rounded to one)
+    static constexpr int P_PARTS = D == 64 ? 3 : 1;     // bf16 numbers that make up a probability (D = 128: rounded to one)
+    static constexpr bool SUM_MFMA = P_PARTS == 1;      // row sums of the rounded probabilities, through the matrix cores
     static constexpr int SEG = ROW / 32 - 1;    // V rows: 32-byte segment ^ (row & SEG)
     struct Q { bf16x8 v[D / 32]; };
     static __device__ __forceinline__ void load_q(Q& q, const __bf16* row, int lg) {
@@ -187,53 +187,56 @@ template <int D> struct DirectOps<__bf16, D> {
     template <int MB>
     static __device__ __forceinline__ void accumulate(const V&, const unsigned char* Vs, const floatx4 (&p)[MB][NC], floatx4 (&o)[MB][NO],
                                                       floatx4 (&sum)[MB], int l16, int lg) {
-        bf16x8 ph[MB], pl[MB];                  // SPLIT_P: p = hi + lo, both bf16 (hi: truncated, so p - hi is exact)
-#pragma unroll
-        for (int rb = 0; rb < MB; ++rb) {
-            uintx4 hi, lo = uintx4{0u, 0u, 0u, 0u};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float p0 = p[rb][j >> 1][2 * (j & 1)], p1 = p[rb][j >> 1][2 * (j & 1) + 1];
-                if constexpr (SPLIT_P) {
-                    const unsigned b0 = __float_as_uint(p0), b1 = __float_as_uint(p1);
-                    hi[j] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
-                    lo[j] = pack_bf16(p0 - __uint_as_float(b0 & 0xffff0000u), p1 - __uint_as_float(b1 & 0xffff0000u));
-                } else {
-                    hi[j] = pack_bf16(p0, p1);
-                }
-            }
-            ph[rb] = __builtin_bit_cast(bf16x8, hi);
-            pl[rb] = __builtin_bit_cast(bf16x8, lo);
-        }
         // rows 16 c + 4 lg + (l16 >> 2): the transpose read turns 4 keys x 16 dims into "lane = dim, 4 keys"
         const int row0 = 4 * lg + (l16 >> 2);
         const unsigned base = lds_offset(Vs) + row0 * ROW + ((row0 & SEG) << 5) + 8 * (l16 & 3);
+        bf16x8 a[NO];
 #pragma unroll
-        for (int e = 0; e < NO; ++e) {
-            bf16x8 a;
+        for (int e = 0; e < NO; ++e)
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
                 const short4_t r = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
                     (short4_t __attribute__((address_space(3)))*)(static_cast<size_t>((base ^ (e << 5)) + c * 16 * ROW)));
                 const bf16x4 r4 = __builtin_bit_cast(bf16x4, r);
-                a[4 * c] = r4[0];
-                a[4 * c + 1] = r4[1];
-                a[4 * c + 2] = r4[2];
-                a[4 * c + 3] = r4[3];
+                a[e][4 * c] = r4[0];
+                a[e][4 * c + 1] = r4[1];
+                a[e][4 * c + 2] = r4[2];
+                a[e][4 * c + 3] = r4[3];
             }
+        // D = 64: p = part 0 + part 1 + part 2, each the leading 8 bits of what the ones before it leave.  Both
+        // differences are exact, so no bit of p is lost: its products with the bf16 values are those of fp32.  A part's
+        // MFMAs run while the next one is split off (four sequences of 2048 keys, 32 heads on 8: 15.5 us; 16.9 with
+        // all parts split off first and the row sums from the matrix cores, 14.8 with two parts, 17 bits of p).
+        floatx4 left[MB][NC];
 #pragma unroll
-            for (int rb = 0; rb < MB; ++rb) o[rb][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ph[rb], o[rb][e], 0, 0, 0);
-            if constexpr (SPLIT_P) {
+        for (int rb = 0; rb < MB; ++rb)
 #pragma unroll
-                for (int rb = 0; rb < MB; ++rb) o[rb][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, pl[rb], o[rb][e], 0, 0, 0);
+            for (int c = 0; c < NC; ++c) left[rb][c] = p[rb][c];
+#pragma unroll
+        for (int t = 0; t < P_PARTS; ++t)
+#pragma unroll
+            for (int rb = 0; rb < MB; ++rb) {
+                uintx4 part;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float p0 = left[rb][j >> 1][2 * (j & 1)], p1 = left[rb][j >> 1][2 * (j & 1) + 1];
+                    if constexpr (P_PARTS == 1) {
+                        part[j] = pack_bf16(p0, p1);
+                    } else {
+                        const unsigned b0 = __float_as_uint(p0), b1 = __float_as_uint(p1);
+                        part[j] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
+                        left[rb][j >> 1][2 * (j & 1)] = p0 - __uint_as_float(b0 & 0xffff0000u);
+                        left[rb][j >> 1][2 * (j & 1) + 1] = p1 - __uint_as_float(b1 & 0xffff0000u);
+                    }
+                }
+                const bf16x8 pp = __builtin_bit_cast(bf16x8, part);
+#pragma unroll
+                for (int e = 0; e < NO; ++e) o[rb][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[e], pp, o[rb][e], 0, 0, 0);
+                if constexpr (SUM_MFMA) {
+                    const bf16x8 ones = __builtin_bit_cast(bf16x8, uintx4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
+                    sum[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pp, sum[rb], 0, 0, 0);
+                }
             }
-        }
-        const bf16x8 ones = __builtin_bit_cast(bf16x8, uintx4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
-#pragma unroll
-        for (int rb = 0; rb < MB; ++rb) {
-            sum[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, ph[rb], sum[rb], 0, 0, 0);
-            if constexpr (SPLIT_P) sum[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pl[rb], sum[rb], 0, 0, 0);
-        }
     }
     static __device__ __forceinline__ int dim(int u, int lg) { return 16 * u + 4 * lg; }
     static __device__ __forceinline__ floatx4 piece(const floatx4 (&o)[NO], int u) { return o[u]; }
@@ -601,7 +604,7 @@ static size_t direct_lds_bytes(int mb, int rg, int32_t D, int32_t dtype) {
 // compute unit, so the job runs in ceil(workgroups / CUs) rounds of a fixed part plus a step per
 // tile of a wavefront.  Measured cycles of a step (eight wavefronts, one tile each): fp32 4700 / 8200
 // (D = 128, one / two row blocks) and 2650 (D = 64), against 4096 / 8192 and 2048 of MFMAs on a SIMD;
-// bf16 2600 (D = 128) and, for D = 64, 1700 / 2500 / 3850 for one / two / four row blocks.  Set-up and
+// bf16 2600 (D = 128) and, for D = 64, 1700 / 2750 / 4550 for one / two / four row blocks.  Set-up and
 // the merge through LDS take 6500 + 2000 per row block and 64 dims; the merge of splits is a launch of
 // its own, 8000 + 600 per split and its traffic, 8 bytes per partial value at 3200 bytes per cycle.
 DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages, int32_t dtype,
@@ -616,7 +619,7 @@ DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_
     for (int mb = 1; mb <= mb_max; mb *= 2) {
         double c_step = D == 64 ? 2650.0 : (mb == 1 ? 4700.0 : 8200.0);
         if (dtype != GRAFT_F32 && D == 128) c_step = 2600.0;
-        else if (dtype != GRAFT_F32) c_step = mb == 4 ? 3850.0 : (mb == 2 ? 2500.0 : 1700.0);
+        else if (dtype != GRAFT_F32) c_step = mb == 4 ? 4550.0 : (mb == 2 ? 2750.0 : 1700.0);
         const double c_fixed = 6500.0 + 2000.0 * mb * (D / 64);
         for (int rg = 1; rg <= DR_WAVES; rg *= 2) {
             const int kg = DR_WAVES / rg;

@@ -1,8 +1,8 @@
 """GPU parity of the attention path for fp32 storage and for bf16 with head size 64, at the sizes
 where its tiling can go wrong, against the CPU oracle (MI355X only).
 
-Bounds.  fp32: 1e-4, as for every fp32 case.  bf16: scores, softmax and sums are fp32 and the
-probabilities keep 17 bits, so what is left is the rounding of the result to bf16: 8 significant
+Bounds.  fp32: 1e-4, as for every fp32 case.  bf16: scores, softmax, probabilities and sums are
+fp32, so what is left is the rounding of the result to bf16: 8 significant
 bits, so at most 2^-8 of the value (half of the spacing 2^-7 right above a power of two), plus 1e-4
 for everything before it."""
 import numpy as np
@@ -139,3 +139,49 @@ def test_tensors_that_start_at_any_element(dtype, D):
 
     a, b = run(*tensors), run(*[moved(t) for t in tensors])
     assert torch.equal(a, b)
+
+
+def test_probabilities_keep_their_32_bits_with_head_64():
+    """Values chosen so that the weighted sum all but cancels: what is left of it shows every bit a probability
+    loses on its way into the product with the values.  Four keys, scores that fp32 holds exactly (queries and
+    keys have one nonzero element), results far smaller than their terms.  Bound: the exponent x = (s - max) log2 e
+    is below 16 with one rounding (16 * 2^-24 ln 2 of p) and exp2 is good to 2^-23, so a probability is off by at
+    most 2^-20 of itself, four sums add 2^-22 of the terms; plus the rounding of the result.  Probabilities of
+    17 bits are off by up to 2^-17."""
+    B, K, H, D, P = 4, 1, 32, 64, 3
+    rng = np.random.default_rng(17)
+    w = shape_workload(B, K, H, H, D, P)
+    att = inputs.make_attention_inputs(w, seed=17)
+    k, v = np.zeros_like(inputs.bf16_bits_to_f32(att["k_cache"][0])), np.zeros_like(inputs.bf16_bits_to_f32(att["v_cache"][0]))
+    q = np.zeros((B, K, H, D), np.float32)
+    q[..., 0] = 1.0
+    bits = inputs.f32_to_bf16_bits
+    round_bf16 = lambda a: inputs.bf16_bits_to_f32(bits(np.asarray(a, np.float32))).astype(np.float64)
+    for b in range(B):
+        page = att["block_table"][b, 0]
+        s = round_bf16(rng.uniform(-6, 0, (H, 4)))
+        p = np.exp(s - s.max(axis=1, keepdims=True))
+        vals = np.zeros((H, 4, D))
+        order = np.argsort(-p, axis=1)                         # each value cancels what the heavier keys leave, to 8 bits
+        vals[np.arange(H), order[:, 0]] = round_bf16(rng.uniform(1, 2, (H, D)))
+        for j in range(1, 4):
+            at = order[:, j]
+            left = np.einsum("ht,htd->hd", p, vals)
+            vals[np.arange(H), at] = round_bf16(-left / p[np.arange(H), at][:, None])
+        k[page, :, :4, 0] = s                                  # [page][head][token][dim]
+        v[page, :, :4] = vals
+    att["k_cache"], att["v_cache"], att["q"] = [bits(k)], [bits(v)], [bits(q)]
+    parent, n, prefix = np.full((B, K), -1, np.int32), np.full(B, K, np.int32), np.full(B, P, np.int32)
+    out = graft.graft_tree_attn(dev(att["q"][0], "bf16"), dev(att["k_cache"][0], "bf16"), dev(att["v_cache"][0], "bf16"),
+                                att["strides"], dev(att["block_table"]), dev(prefix), dev(n), gpu_mask(parent, n, prefix), H, 1.0)
+    got = host(out).astype(np.float64)[:, 0]
+    for b in range(B):
+        page = att["block_table"][b, 0]
+        s, vals = k[page, :, :4, 0].astype(np.float64), v[page, :, :4].astype(np.float64)
+        p = np.exp(s - s.max(axis=1, keepdims=True))
+        p /= p.sum(axis=1, keepdims=True)
+        ref, size = np.einsum("ht,htd->hd", p, vals), np.einsum("ht,htd->hd", p, np.abs(vals))
+        err = np.abs(got[b] - ref)
+        bound = (2.0 ** -20 + 2.0 ** -22) * size + 2.0 ** -8 * np.abs(ref)
+        print("largest error / bound %.2f, median of result / terms %.1e" % ((err / bound).max(), np.median(np.abs(ref) / size)))
+        assert (err <= bound).all(), (err / bound).max()
