@@ -3,7 +3,9 @@
 Argument marshalling only: every step of the verification path runs in the HIP
 kernels behind the entry points.  PyTorch is used for device memory and streams; tensors are
 passed as raw device pointers.  The marshalling itself is native (csrc/binding.cpp, built as
-_native.so next to the library).  There is no CPU fallback: if the library is not built the
+_native.so next to the library).  A workspace that a call has to allocate belongs to the stream
+the call runs on (`stream`, by default the current one); results that it allocates belong to
+the current stream, as every tensor does, so with another `stream` they are kept until it is done.  There is no CPU fallback: if the library is not built the
 first call raises.
 """
 from __future__ import annotations

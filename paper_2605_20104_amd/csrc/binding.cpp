@@ -116,22 +116,49 @@ Strides strides_of(PyObject* d) {
     return {to_i64(item(d, s_page)), to_i64(item(d, s_token)), to_i64(item(d, s_head))};
 }
 
-// The stream to launch on: the given one (an object with a cuda_stream attribute, or the handle
+at::Tensor empty_bytes(size_t n, const at::Device& dev);
+
+// The stream a call launches on: the given one (an object with a cuda_stream attribute, or the handle
 // itself), else the current stream of the current device.
-void* stream_of(PyObject* o) {
-    if (o == Py_None) return c10::hip::getCurrentHIPStream().stream();
-    PyObject* h = PyObject_GetAttr(o, s_cuda_stream);
-    if (!h) {
-        PyErr_Clear();
-        return reinterpret_cast<void*>(to_i64(o));
+class LaunchStream {
+public:
+    LaunchStream(PyObject* given, const at::Device& dev) : dev_(dev), given_(given != Py_None) {
+        if (!given_) {
+            handle_ = c10::hip::getCurrentHIPStream().stream();
+            return;
+        }
+        PyObject* h = PyObject_GetAttr(given, s_cuda_stream);
+        if (!h) {
+            PyErr_Clear();
+            handle_ = reinterpret_cast<void*>(to_i64(given));
+            return;
+        }
+        PyObject* i = PyNumber_Long(h);
+        Py_DECREF(h);
+        if (!i) throw PythonError();
+        handle_ = PyLong_AsVoidPtr(i);
+        Py_DECREF(i);
     }
-    PyObject* i = PyNumber_Long(h);
-    Py_DECREF(h);
-    if (!i) throw PythonError();
-    void* p = PyLong_AsVoidPtr(i);
-    Py_DECREF(i);
-    return p;
-}
+    void* handle() const { return handle_; }
+    // Scratch memory of the call.  It is given back when the call returns, with its kernels still to run, so
+    // it has to belong to the stream they run on: the allocator hands a block out again in the order of the
+    // stream it was taken for.  Taken for the current stream, two calls on two other streams get the
+    // same block, and so does whatever is allocated next.
+    at::Tensor scratch(size_t n) const {
+        if (!given_ || !dev_.is_cuda()) return empty_bytes(n, dev_);
+        struct Restore {
+            c10::hip::HIPStream before;
+            ~Restore() { c10::hip::setCurrentHIPStream(before); }
+        } restore{c10::hip::getCurrentHIPStream(dev_.index())};
+        c10::hip::setCurrentHIPStream(c10::hip::getStreamFromExternal(static_cast<hipStream_t>(handle_), dev_.index()));
+        return empty_bytes(n, dev_);
+    }
+
+private:
+    at::Device dev_;
+    bool given_;
+    void* handle_;
+};
 
 // ---- results -------------------------------------------------------------------------------
 at::Tensor empty(at::IntArrayRef shape, at::ScalarType type, const at::Device& dev) {
@@ -244,7 +271,7 @@ GRAFT_PY(py_retrieve, 10) {
     int32_t* status = out.get(k_status, {B});
     const int32_t tail_max = a[6] == Py_None ? 0 : size_at(tensor(a[6]), 1);
     const int32_t *c = ptr<int32_t>(ctx), *cl = ptr<int32_t>(a[1]), *t = ptr<int32_t>(a[6]), *tl = ptr<int32_t>(a[7]);
-    void* s = stream_of(a[9]);
+    void* s = LaunchStream(a[9], ctx.device()).handle();
     check("graft_retrieve", unlocked([&] {
         return lib.graft_retrieve(c, cl, B, L_max, t, tl, tail_max, n_min, n_max, C, m, tok, len, pos, match, hits, status, s);
     }));
@@ -270,7 +297,7 @@ GRAFT_PY(py_build_tree_mask, 7) {
     }
     int32_t* status = out.get(k_status, {B});
     const int32_t *p = ptr<int32_t>(parent), *n = ptr<int32_t>(a[1]), *pl = ptr<int32_t>(a[2]);
-    void* s = stream_of(a[6]);
+    void* s = LaunchStream(a[6], parent.device()).handle();
     check("graft_build_tree_mask", unlocked([&] {
         return lib.graft_build_tree_mask(p, n, pl, B, K, mask, pos, depth, paths, n_leaf_max, depth_cap, status, s);
     }));
@@ -296,6 +323,7 @@ GRAFT_PY(py_tree_attn, 13) {
     const double scale = PyFloat_AsDouble(a[9]);
     if (scale == -1.0 && PyErr_Occurred()) throw PythonError();
     const Strides st = strides_of(a[3]);
+    const LaunchStream stream(a[12], q.device());
     at::Tensor new_out, new_ws;
     void* out;
     if (a[10] == Py_None) {
@@ -307,7 +335,7 @@ GRAFT_PY(py_tree_attn, 13) {
     if (a[11] == Py_None) {
         ws_bytes = lib.graft_tree_attn_workspace_bytes(B, K, Hq, Hkv, D, max_pages, dtype);
         if (ws_bytes > 0) {
-            new_ws = empty_bytes(ws_bytes, q.device());
+            new_ws = stream.scratch(ws_bytes);
             ws = new_ws.data_ptr();
         }
     } else {
@@ -318,7 +346,7 @@ GRAFT_PY(py_tree_attn, 13) {
     const void *qp = ptr<void>(q), *kp = ptr<void>(k), *vp = ptr<void>(v);
     const int32_t *tp = ptr<int32_t>(table), *pl = ptr<int32_t>(a[5]), *n = ptr<int32_t>(a[6]);
     const uint64_t* mask = ptr<uint64_t>(a[7]);
-    void* s = stream_of(a[12]);
+    void* s = stream.handle();
     check("graft_tree_attn", unlocked([&] {
         return lib.graft_tree_attn(qp, kp, vp, st.page, st.token, st.head, tp, max_pages, pl, n, mask, B, K, Hq, Hkv, D,
                                    GRAFT_PAGE_SIZE, static_cast<float>(scale), dtype, out, ws, ws_bytes, s);
@@ -336,6 +364,7 @@ GRAFT_PY(py_accept, 9) {
     sizes2(parent, B, K);
     const int32_t depth_cap = to_i32(a[3]);
     const at::Device dev = parent.device();
+    const LaunchStream stream(a[8], dev);
     const float* logits = nullptr;
     int32_t* ids;
     PyObject* ids_obj = a[4];
@@ -369,11 +398,11 @@ GRAFT_PY(py_accept, 9) {
         ws_bytes = static_cast<size_t>(w.numel());
     } else if (logits) {
         ws_bytes = lib.graft_accept_workspace_bytes(B, K, V);
-        new_ws = empty_bytes(ws_bytes, dev);
+        new_ws = stream.scratch(ws_bytes);
         ws = new_ws.data_ptr();
     }
     const int32_t *p = ptr<int32_t>(parent), *tk = ptr<int32_t>(a[1]), *n = ptr<int32_t>(a[2]);
-    void* s = stream_of(a[8]);
+    void* s = stream.handle();
     check("graft_accept", unlocked([&] {
         return lib.graft_accept(p, tk, n, logits, V, ids, B, K, depth_cap, len, best, path, toks, status, ws, ws_bytes, s);
     }));
@@ -393,7 +422,7 @@ GRAFT_PY(py_accept_noalloc, 8) {
             *path = ptr<int32_t>(item(a[4], k_path)), *toks = ptr<int32_t>(item(a[4], k_out_tokens)),
             *status = ptr<int32_t>(item(a[4], k_status));
     const int32_t *p = ptr<int32_t>(parent), *tk = ptr<int32_t>(a[1]), *n = ptr<int32_t>(a[2]);
-    void* s = stream_of(a[7]);
+    void* s = LaunchStream(a[7], parent.device()).handle();
     check("graft_accept_noalloc", unlocked([&] {
         return lib.graft_accept_noalloc(p, tk, n, logits, V, ids, B, K, depth_cap, len, best, path, toks, status, s);
     }));
@@ -416,7 +445,7 @@ GRAFT_PY(py_matrix_retrieve, 9) {
     const int32_t *M = ptr<int32_t>(a[0]), *tp = ptr<int32_t>(a[1]), *tr = ptr<int32_t>(a[2]), *nr = ptr<int32_t>(a[3]);
     const int32_t N = size_at(tensor(a[1]), 0);
     int32_t *tk = ptr<int32_t>(tokens), *p = ptr<int32_t>(a[5]), *n = ptr<int32_t>(a[6]);
-    void* s = stream_of(a[8]);
+    void* s = LaunchStream(a[8], tokens.device()).handle();
     check("graft_matrix_retrieve", unlocked([&] {
         return lib.graft_matrix_retrieve(M, V, k, tp, tr, N, nr, B, K, tk, p, n, status, s);
     }));
@@ -433,6 +462,7 @@ GRAFT_PY(py_matrix_update, 7) {
         throw PythonError();
     }
     const int32_t B = size_at(lg, 0), K = size_at(lg, 1), V = size_at(lg, 2), k = size_at(M, 1);
+    const LaunchStream stream(a[6], lg.device());
     at::Tensor fresh, new_ws;
     int32_t* ids;
     if (a[4] == Py_None) {
@@ -444,7 +474,7 @@ GRAFT_PY(py_matrix_update, 7) {
     if (a[5] == Py_None) {
         ws_bytes = lib.graft_matrix_update_workspace_bytes(B, K, V, k);
         ws_bytes = ws_bytes > 8 ? ws_bytes : 8;
-        new_ws = empty_bytes(ws_bytes, lg.device());
+        new_ws = stream.scratch(ws_bytes);
         ws = new_ws.data_ptr();
     } else {
         const at::Tensor& w = tensor(a[5]);
@@ -454,7 +484,7 @@ GRAFT_PY(py_matrix_update, 7) {
     const int32_t *tk = ptr<int32_t>(a[0]), *n = ptr<int32_t>(a[1]);
     const float* logits = ptr<float>(lg);
     int32_t* Mp = ptr<int32_t>(M);
-    void* s = stream_of(a[6]);
+    void* s = stream.handle();
     check("graft_matrix_update", unlocked([&] {
         return lib.graft_matrix_update(tk, n, logits, V, B, K, Mp, k, ids, ws, ws_bytes, s);
     }));
@@ -483,7 +513,7 @@ GRAFT_PY(py_kv_compact, 14) {
     void *kp = ptr<void>(k), *vp = ptr<void>(v);
     const int32_t *tp = ptr<int32_t>(table), *pl = ptr<int32_t>(a[6]), *pp = ptr<int32_t>(path), *al = ptr<int32_t>(a[8]);
     const int32_t max_pages = size_at(table, 1);
-    void* s = stream_of(a[13]);
+    void* s = LaunchStream(a[13], path.device()).handle();
     check("graft_kv_compact", unlocked([&] {
         return lib.graft_kv_compact(kp, vp, layer_stride, n_layers, st.page, st.token, st.head, tp, max_pages, pl, pp, al, B,
                                     width - 1, K, Hkv, D, type == at::kFloat ? GRAFT_F32 : GRAFT_BF16, new_len, status, s);
@@ -509,7 +539,7 @@ GRAFT_PY(py_prune_select, 10) {
                   *ck = ptr<int32_t>(a[6]), *cr = ptr<int32_t>(a[7]);
     const float *lq = ptr<float>(a[2]), *ct = ptr<float>(a[5]);
     const int32_t n_chk = size_at(tensor(a[4]), 0);
-    void* s = stream_of(a[9]);
+    void* s = LaunchStream(a[9], parent.device()).handle();
     check("graft_prune_select", unlocked([&] {
         return lib.graft_prune_select(p, tk, lq, n, B, K, cd, ct, ck, cr, n_chk, op, ot, oi, on, stage, nr, status, s);
     }));

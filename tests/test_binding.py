@@ -75,3 +75,60 @@ def test_out_of_memory_is_torchs_own_error():
     ctx, n = torch.zeros((1, 8), dtype=torch.int32, device="cuda"), torch.full((1,), 8, dtype=torch.int32, device="cuda")
     with pytest.raises(torch.OutOfMemoryError):                                       # 4 TiB of results, refused by the allocator
         graft.graft_retrieve(ctx, n, 1, 4, 1 << 20, 1 << 20)
+
+
+def _attention(seed, B=1, K=20, H=4, D=64, pages=300):
+    """fp32, head size 64, a prefix long enough that the keys are split: (arguments, bytes of workspace)."""
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    q = torch.randn((B, K, H, D), generator=gen, device="cuda")
+    k, v = (torch.randn((pages, H, 16, D), generator=gen, device="cuda") for _ in range(2))
+    table = torch.randperm(pages, generator=gen, device="cuda").to(torch.int32)[None].contiguous()
+    n, prefix = torch.full((B,), K, dtype=torch.int32, device="cuda"), torch.full((B,), pages * 16 - K, dtype=torch.int32, device="cuda")
+    parent = torch.arange(-1, K - 1, dtype=torch.int32, device="cuda")[None].contiguous()
+    mask = graft.graft_build_tree_mask(parent, n, prefix)["mask"]
+    need = graft.graft_tree_attn_workspace_bytes(B, K, H, H, D, pages, graft.GRAFT_F32)
+    return (q, k, v, {"page": H * 16 * D, "token": D, "head": 16 * D}, table, prefix, n, mask, H, 0.125), need
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("call", ["attention", "accept", "matrix_update"])
+def test_workspace_belongs_to_the_stream_of_the_call(call):
+    """The block of a workspace that the call allocates is in a segment of the stream the kernels run on."""
+    one = torch.full((1,), 16, dtype=torch.int32, device="cuda")
+    tree = torch.arange(-1, 15, dtype=torch.int32, device="cuda")[None].contiguous()
+    logits = torch.randn((1, 16, 5000), device="cuda")
+    M = torch.full((5000, 8), -1, dtype=torch.int32, device="cuda")
+    args, need = _attention(1)
+    if call != "attention":
+        need = graft.graft_accept_workspace_bytes(1, 16, 5000) if call == "accept" else graft.graft_matrix_update_workspace_bytes(1, 16, 5000, 8)
+    assert need > 0
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    on_side = lambda: sum(s["total_size"] for s in torch.cuda.memory_snapshot() if s["stream"] == side.cuda_stream)
+    before = on_side()
+    if call == "attention":
+        graft.graft_tree_attn(*args, stream=side)
+    elif call == "accept":
+        graft.graft_accept(tree, tree, one, 8, logits=logits, stream=side)
+    else:
+        graft.graft_matrix_update(tree, one, logits, M, stream=side.cuda_stream)     # the handle itself
+    torch.cuda.synchronize()
+    assert side.cuda_stream != torch.cuda.current_stream().cuda_stream and on_side() - before >= need
+
+
+@pytest.mark.gpu
+def test_calls_on_two_streams_without_a_workspace():
+    """Calls in flight on two streams keep their partial results apart: the bits are those of calls one by one."""
+    problems = [_attention(s)[0] for s in (2, 3)]
+    alone = [graft.graft_tree_attn(*p) for p in problems]
+    streams = [torch.cuda.Stream() for _ in problems]
+    outs = [[torch.empty_like(a) for _ in range(20)] for a in alone]
+    torch.cuda.synchronize()
+    for i in range(20):
+        for p, s, o in zip(problems, streams, outs):
+            graft.graft_tree_attn(*p, out=o[i], stream=s)
+    torch.cuda.synchronize()
+    for a, o in zip(alone, outs):
+        for x in o:
+            assert torch.equal(a, x)
