@@ -87,6 +87,7 @@ template <int D> struct DirectOps<float, D> {
     static constexpr int NC = 1;                // score tiles of 16 keys
     static constexpr int ROW = D * 4;           // bytes
     static constexpr bool SUM_MFMA = false;
+    static constexpr bool ALONE = true;         // values of unseen slots do not reach a row even if they are not finite
     struct Q { floatx4 v[D / 16]; };
     static __device__ __forceinline__ void load_q(Q& q, const float* row, int lg) {
 #pragma unroll
@@ -130,6 +131,33 @@ template <int D> struct DirectOps<float, D> {
                     for (int rb = 0; rb < MB; ++rb)
                         o[rb][4 * h + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.r[i][h][j], p[rb][0][i], o[rb][4 * h + j], 0, 0, 0);
     }
+    // keys of the tile with an infinite or NaN value among this lane's, as bits
+    static __device__ __forceinline__ unsigned nonfinite_keys(const V& t, int lane) {
+        unsigned keys = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            bool bad = false;
+#pragma unroll
+            for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) bad = bad || !__builtin_isfinite(t.r[j][h][i]);
+            keys |= bad ? 1u << j : 0u;
+        }
+        return keys << (4 * (lane >> 4));
+    }
+    static __device__ __forceinline__ void clear_key(V& t, unsigned char*, int key, int lane) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (4 * (lane >> 4) + j == key)
+#pragma unroll
+                for (int h = 0; h < D / 64; ++h) t.r[j][h] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    static __device__ __forceinline__ floatx4 load_dims(const char* p) { return *reinterpret_cast<const floatx4*>(p); }
+    static __device__ __forceinline__ void add_piece(floatx4 (&o)[NO], int u, const floatx4& x) {
+        const int h = u >> 2, i = u & 3;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[4 * h + j][i] += x[j];
+    }
     // the four consecutive dims starting at dim(u, lg), u < D/16
     static __device__ __forceinline__ int dim(int u, int lg) { return 64 * (u >> 2) + 16 * lg + 4 * (u & 3); }
     static __device__ __forceinline__ floatx4 piece(const floatx4 (&o)[NO], int u) {
@@ -145,6 +173,7 @@ template <int D> struct DirectOps<__bf16, D> {
     static constexpr int ROW = D * 2;
     static constexpr int P_PARTS = D == 64 ? 3 : 1;     // bf16 numbers that make up a probability (D = 128: rounded to one)
     static constexpr bool SUM_MFMA = P_PARTS == 1;      // row sums of the rounded probabilities, through the matrix cores
+    static constexpr bool ALONE = D == 64;      // (D = 128 asks for finite values, as the path this stands in for does)
     static constexpr int SEG = ROW / 32 - 1;    // V rows: 32-byte segment ^ (row & SEG)
     struct Q { bf16x8 v[D / 32]; };
     static __device__ __forceinline__ void load_q(Q& q, const __bf16* row, int lg) {
@@ -238,6 +267,29 @@ template <int D> struct DirectOps<__bf16, D> {
                 }
             }
     }
+    static __device__ __forceinline__ unsigned nonfinite_keys(const V& t, int lane) {
+        unsigned keys = 0;
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            bool bad = false;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const unsigned x = t.r[j][i];
+                bad = bad || (x & 0x7f80u) == 0x7f80u || (x & 0x7f800000u) == 0x7f800000u;
+            }
+            keys |= bad ? 1u << (j * RPI) : 0u;
+        }
+        return keys << (lane / (ROW / 16));
+    }
+    static __device__ __forceinline__ void clear_key(V&, unsigned char* Vs, int key, int lane) {
+        if (lane < ROW / 16) *reinterpret_cast<uintx4*>(Vs + key * ROW + 16 * lane) = uintx4{0u, 0u, 0u, 0u};
+    }
+    static __device__ __forceinline__ floatx4 load_dims(const char* p) {
+        const uintx2 x = *reinterpret_cast<const uintx2*>(p);
+        return floatx4{__uint_as_float(x[0] << 16), __uint_as_float(x[0] & 0xffff0000u), __uint_as_float(x[1] << 16),
+                       __uint_as_float(x[1] & 0xffff0000u)};
+    }
+    static __device__ __forceinline__ void add_piece(floatx4 (&o)[NO], int u, const floatx4& x) { o[u] += x; }
     static __device__ __forceinline__ int dim(int u, int lg) { return 16 * u + 4 * lg; }
     static __device__ __forceinline__ floatx4 piece(const floatx4 (&o)[NO], int u) { return o[u]; }
 };
@@ -247,9 +299,10 @@ __device__ __forceinline__ void store4(__bf16* p, const floatx4& v) {
     *reinterpret_cast<uintx2*>(p) = uintx2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
 }
 
-// p.R_pad = rows covered by the row tiles; rg (row groups) and the rest of the shape as below
+// p.R_pad = rows covered by the row tiles; rg (row groups) and the rest of the shape as below.  One row block
+// with D = 64 leaves room for a second workgroup on the compute unit.
 template <typename T, int D, int MB>
-__global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_direct_kernel(AttnParams p, int32_t rg) {
+__global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_direct_kernel(AttnParams p, int32_t rg) {
     using Ops = DirectOps<T, D>;
     constexpr int TK = Ops::TK, NO = Ops::NO, NC = Ops::NC, ROW = Ops::ROW;
     using Keys = StagedKeys<ROW, TK>;
@@ -319,14 +372,17 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_direct_kernel(AttnPar
     float m[MB], l[MB];
     floatx4 lv[MB];                             // row sums where the matrix cores take them (every entry the row's sum)
     floatx4 o[MB][NO];
+    auto clear_rows = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int rb = 0; rb < MB; ++rb) {
-        m[rb] = -INFINITY;
-        l[rb] = 0.f;
-        lv[rb] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int rb = 0; rb < MB; ++rb) {
+            m[rb] = -INFINITY;
+            l[rb] = 0.f;
+            lv[rb] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int e = 0; e < NO; ++e) o[rb][e] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
+            for (int e = 0; e < NO; ++e) o[rb][e] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    clear_rows();
 
     if (count > 0) {
         constexpr int PAGES = TK / GRAFT_PAGE_SIZE, TPR = 64 / PAGES;      // pages per tile, tiles per table register
@@ -340,25 +396,25 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_direct_kernel(AttnPar
         // the sequence that can reach past its end is only ever the first of a wavefront.  Loads
         // inside the loop then need no branch; with one, the compiler no longer knows how many
         // transfers are in flight and waits for most of what it has just requested.
-        auto tile_at = [&](int it) { return first + kg * (it == 0 ? count - 1 : it - 1); };
-        auto load_table = [&](int it) {
+        auto tile_at = [&](int it) __attribute__((always_inline)) { return first + kg * (it == 0 ? count - 1 : it - 1); };
+        auto load_table = [&](int it) __attribute__((always_inline)) {
             const int pg = tile_at(it + lane / PAGES) * PAGES + lane % PAGES;
             tb = table[pg < last_pg ? pg : last_pg];
         };
         // (the wavefront-uniform part of an address is scalar, the lane's part loop-invariant)
-        auto page_base = [&](int it, int c) {
+        auto page_base = [&](int it, int c) __attribute__((always_inline)) {
             return static_cast<int64_t>(__builtin_amdgcn_readlane(tb, (it & (TPR - 1)) * PAGES + c)) * p.page_stride * static_cast<int64_t>(sizeof(T));
         };
         const unsigned k_lane = 16 * (lane % Keys::CPR), k_off = lane / Keys::CPR * ts + k_lane;
         const unsigned v_lane = Ops::v_lane(lane), v_off = (Ops::v_row(lane, 0) - Ops::v_row0(0)) * ts + v_lane;
-        auto load_keys = [&](Keys& t, int it) {
+        auto load_keys = [&](Keys& t, int it) __attribute__((always_inline)) {
             unsigned off = k_off;
             asm volatile("" : "+v"(off));                         // (kept apart from the scalar base: no 64-bit vector additions)
 #pragma unroll
             for (int j = 0; j < Keys::N; ++j)
                 t.r[j] = *reinterpret_cast<const uintx4*>(kc + page_base(it, Keys::page(j)) + static_cast<int64_t>(Keys::row0(j)) * ts + off);
         };
-        auto load_values = [&](Values& t, int it) {
+        auto load_values = [&](Values& t, int it) __attribute__((always_inline)) {
             unsigned off = v_off;
             asm volatile("" : "+v"(off));
 #pragma unroll
@@ -366,20 +422,20 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_direct_kernel(AttnPar
                 Ops::load_v(t, j, vc + page_base(it, Ops::v_page(j)) + static_cast<int64_t>(Ops::v_row0(j)) * ts, off);
         };
         // a tile that may reach past the end: keys past the last token read the last token again
-        // (its values are finite, and its probability there is zero)
-        auto load_clamped = [&](Keys& kt, Values& vt, int it) {
-            auto row_off = [&](int page, int k) {
-                const int t_page = tile_at(it) * TK + 16 * page;
-                const int lim = last - (t_page < last ? t_page : (last & ~15));
-                return static_cast<unsigned>(k < lim ? k : lim) * ts;
-            };
+        // (its probability there is zero)
+        auto row_off = [&](int it, int page, int k) __attribute__((always_inline)) {
+            const int t_page = tile_at(it) * TK + 16 * page;
+            const int lim = last - (t_page < last ? t_page : (last & ~15));
+            return static_cast<unsigned>(k < lim ? k : lim) * ts;
+        };
+        auto load_clamped = [&](Keys& kt, Values& vt, int it) __attribute__((always_inline)) {
 #pragma unroll
             for (int j = 0; j < Keys::N; ++j)
                 kt.r[j] = *reinterpret_cast<const uintx4*>(kc + page_base(it, Keys::page(j)) +
-                                                           (row_off(Keys::page(j), Keys::row0(j) + lane / Keys::CPR) + k_lane));
+                                                           (row_off(it, Keys::page(j), Keys::row0(j) + lane / Keys::CPR) + k_lane));
 #pragma unroll
             for (int j = 0; j < Ops::NV; ++j)
-                Ops::load_v(vt, j, vc + page_base(it, Ops::v_page(j)), row_off(Ops::v_page(j), Ops::v_row(lane, j)) + v_lane);
+                Ops::load_v(vt, j, vc + page_base(it, Ops::v_page(j)), row_off(it, Ops::v_page(j), Ops::v_row(lane, j)) + v_lane);
         };
         unsigned char* const Ks = pieces + wave * STAGE;
         unsigned char* const Vs = Ks + TK * ROW;
@@ -387,14 +443,21 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_direct_kernel(AttnPar
         // One tile: through LDS where it has to be turned, the next one requested behind it.
         Keys kt;
         Values vt;
-        auto step = [&](int it, auto more_) {
-            constexpr bool more = decltype(more_)::value;
+        auto step = [&](int it, auto more_, auto careful_) __attribute__((always_inline)) {
+            constexpr bool more = decltype(more_)::value, careful = decltype(careful_)::value;
             kt.stage(Ks, lane);
             if constexpr (more) load_keys(kt, it + 1);
             const int t0 = tile_at(it) * TK;
             const bool masked = t0 + TK > P;
             floatx4 s[MB][NC];
             Ops::template scores<MB>(Ks, q, s, l16, lg);
+            unsigned odd = 0;                                     // keys with an infinite or NaN value
+            if constexpr (careful) {
+                odd = Ops::nonfinite_keys(vt, lane);
+#pragma unroll
+                for (int x = 32; x >= 1; x >>= 1) odd |= __shfl_xor(odd, x);
+                odd = __builtin_amdgcn_readfirstlane(odd);
+            }
             if constexpr (Ops::V_STAGED) {
                 Ops::stage_v(vt, Vs, lane);
                 if constexpr (more) load_values(vt, it + 1);
@@ -448,6 +511,26 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_direct_kernel(AttnPar
                     }
                 l[rb] += sum;
             }
+            // the values of such a key leave the product and are added to the rows that see it
+            for (unsigned left = odd; careful && left != 0; left &= left - 1) {
+                const int key = __builtin_ctz(left), page = key >> 4, at = (key >> 4) * 4 + (key & 3);
+                Ops::clear_key(vt, Vs, key, lane);
+                const char* vrow = vc + page_base(it, page) + row_off(it, page, key & 15);
+#pragma unroll
+                for (int rb = 0; rb < MB; ++rb) {
+                    float pk = s[rb][0][0];
+#pragma unroll
+                    for (int c = 0; c < NC; ++c)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) pk = at == 4 * c + i ? s[rb][c][i] : pk;
+                    pk = __shfl(pk, 16 * ((key >> 2) & 3) + l16);
+#pragma unroll
+                    for (int u = 0; u < D / 16; ++u) {
+                        if (pk != 0.f) Ops::add_piece(o[rb], u, Ops::load_dims(vrow + Ops::dim(u, lg) * sizeof(T)) * pk);
+                        asm volatile("" ::: "memory");            // (one load at a time: registers are short here)
+                    }
+                }
+            }
             asm volatile("" ::: "memory");                        // (the transpose reads stay behind the writes above)
             Ops::template accumulate<MB>(vt, Vs, s, o, lv, l16, lg);
             if constexpr (more && !Ops::V_STAGED) load_values(vt, it + 1);
@@ -457,9 +540,29 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_direct_kernel(AttnPar
             const int end = it + TPR < count ? it + TPR : count;
             load_table(it);
             load_clamped(kt, vt, it);
-            for (; it + 1 < end; ++it) step(it, std::true_type{});
-            step(it, std::false_type{});
+            for (; it + 1 < end; ++it) step(it, std::true_type{}, std::false_type{});
+            step(it, std::false_type{}, std::false_type{});
             it = end;
+        }
+        // ALONE: an infinite or NaN value in a tree slot makes the product NaN in the rows that do not see the slot as well
+        // (0 * inf).  Such a wavefront, if there ever is one, takes its tiles once more, with the values of such
+        // keys kept out of the product.  (The same looked for in every step: 2 % on two row blocks with D = 64.)
+        if (Ops::ALONE && (first + kg * (count - 1) + 1) * TK > P) {
+            float t = 0.f;                                        // NaN if a sum is not finite
+#pragma unroll
+            for (int rb = 0; rb < MB; ++rb)
+#pragma unroll
+                for (int e = 0; e < NO; ++e)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) t = __builtin_fmaf(o[rb][e][i], 0.f, t);
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(t != t) != 0, 0)) {
+                clear_rows();
+                for (int it = 0; it < count; ++it) {
+                    if (it % TPR == 0) load_table(it);
+                    load_clamped(kt, vt, it);
+                    step(it, std::false_type{}, std::true_type{});
+                }
+            }
         }
 #pragma unroll
         for (int rb = 0; rb < MB; ++rb) l[rb] = Ops::SUM_MFMA ? lv[rb][0] : rows_sum_f32(l[rb]);

@@ -185,3 +185,46 @@ def test_probabilities_keep_their_32_bits_with_head_64():
         bound = (2.0 ** -20 + 2.0 ** -22) * size + 2.0 ** -8 * np.abs(ref)
         print("largest error / bound %.2f, median of result / terms %.1e" % ((err / bound).max(), np.median(np.abs(ref) / size)))
         assert (err <= bound).all(), (err / bound).max()
+
+
+@pytest.mark.parametrize("dtype,D,K,Hq,P", [("f32", 64, 40, 8, 300), ("f32", 128, 23, 4, 77), ("f32", 128, 128, 64, 1500), ("bf16", 64, 40, 8, 300),
+                                            ("bf16", 64, 128, 64, 3000)])
+def test_values_that_are_not_finite_stay_with_the_nodes_that_see_them(dtype, D, K, Hq, P):
+    """Infinite and NaN values in tree slots, the last one among them: rows that do not see the slot have the bits of a
+    run without them, rows that do get inf or NaN in that dim alone."""
+    B, Hkv = 2, 4
+    w = shape_workload(B, K, Hq, Hkv, D, P, dtype=dtype)
+    att = inputs.make_attention_inputs(w, seed=D + K)
+    rng = np.random.default_rng(D + K)
+    parent = np.stack([inputs.random_recursive_tree(rng, K, 8) for _ in range(B)])
+    n, p = np.full(B, K, np.int32), np.full(B, P, np.int32)
+    mask = gpu_mask(parent, n, p)
+    words = host(mask)
+    sees = np.array([[[int(words[b, i, j // 64]) >> (j % 64) & 1 for j in range(K)] for i in range(K)] for b in range(B)], bool)
+    v = dev(att["v_cache"][0], dtype)                                      # [page][head][token][dim]
+    planted = [(K - 1, 3, np.inf), (K // 2, 0, -np.inf), (K // 2, 5, np.nan), (1, D - 1, np.nan), (K // 3, 3, np.inf), (2, 5, -np.inf)]
+
+    def run(values):
+        return graft.graft_tree_attn(dev(att["q"][0], dtype), dev(att["k_cache"][0], dtype), values, att["strides"], dev(att["block_table"]),
+                                     dev(p), dev(n), mask, Hkv, att["scale"])
+
+    clean, bad = run(v), v.clone()
+    touched = np.zeros((B, K), bool)
+    want = np.zeros((B, K, D))                                             # inf, -inf or NaN where a seen value is
+    for b in range(B):
+        for slot, dim, x in planted:
+            bad[int(att["block_table"][b, (P + slot) // 16]), :, (P + slot) % 16, dim] = float(x)
+            touched[b] |= sees[b, :, slot]
+            want[b, sees[b, :, slot], dim] += x
+    got = run(bad)
+    assert not touched.all()
+    bits = torch.int32 if dtype == "f32" else torch.int16
+    same = torch.from_numpy(~touched).cuda()
+    assert torch.equal(got[same].view(bits), clean[same].view(bits))
+    g, c = host(got).astype(np.float64), host(clean).astype(np.float64)
+    want = np.broadcast_to(want[:, :, None], g.shape)
+    odd = ~np.isfinite(want) | np.isnan(want)
+    assert ((g == want) | (np.isnan(g) & np.isnan(want)))[odd].all()
+    # the rest of a row that sees such a slot: the same sum in another order
+    assert np.isfinite(g[~odd]).all()
+    assert (np.abs(g - c)[~odd] <= (1e-5 if dtype == "f32" else 2.0 ** -7) * (1 + np.abs(c[~odd]))).all()
