@@ -89,7 +89,7 @@ static void launch_main(Kernel kernel, dim3 grid, dim3 block, unsigned lds_bytes
 }
 
 // Which of the 32 tokens from tree slot s on (s = token - prefix length, negative inside the prefix) a
-// row sees, as bits: all of the prefix, of the n tree slots those in the row's ancestor mask.  word(k)
+// row sees, as bits: all of the prefix, of the first n tree slots those in the row's ancestor mask.  word(k)
 // returns the mask's 32-bit word k, 0 <= k < 4.  s and n are wavefront-uniform, so that the words are
 // picked by scalar conditions and a row costs one funnel shift and one AND.
 template <class Word>

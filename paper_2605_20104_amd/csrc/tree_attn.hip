@@ -536,10 +536,12 @@ __device__ __forceinline__ bool region_pv_max(const unsigned char* __restrict__ 
 }
 
 // Ancestor masking of an exponent tile that reaches past the prefix (tree slots and the
-// tail): masked entries become -inf; the lane-local maxima are recomputed.
+// tail): masked entries become -inf; the lane-local maxima are recomputed.  slots is the number of
+// tree slots that the block table has room for, n if the caller keeps to it: what lies past them
+// repeats the last token.
 template <int MB>
 __device__ __forceinline__ bool apply_tree_mask(floatx4 (&x)[MB][2], const WaveRows<MB>& w, float (&lm)[MB],
-                                                int lane, int t_sub0, int P, int n, int r_base, int R, int g_magic,
+                                                int lane, int t_sub0, int P, int n, int slots, int r_base, int R, int g_magic,
                                                 const unsigned* __restrict__ Ms) {
     const int l16 = lane & 15, lg = lane >> 4;
     bool grow = false;
@@ -548,7 +550,7 @@ __device__ __forceinline__ bool apply_tree_mask(floatx4 (&x)[MB][2], const WaveR
         const int r = r_base + rb * 16 + l16;
         const int node = (r * g_magic) >> 16;              // r / G
         const unsigned* row = Ms + 4 * (r < R && node < n ? node : 0);     // (rows of absent nodes: any finite mask will do)
-        const unsigned win = visible_window(t_sub0 - P, n, [&](int k) { return row[k]; }) >> (4 * lg);
+        const unsigned win = visible_window(t_sub0 - P, slots, [&](int k) { return row[k]; }) >> (4 * lg);
         reserve_acc_registers<MB>();                          // no temporaries of the compiler's in the accumulators
         float mx = -INFINITY;
 #pragma unroll
@@ -1015,7 +1017,7 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(AttnParams p
         // (where the exponents change after region 2 has turned the late row block's into
         //  probabilities, those are redone)
         if (__builtin_expect(t0 + AT_SUB > sr.P, 0)) {
-            grow = apply_tree_mask<MB>(xa, w, lm, lane, t0, sr.P, sr.n, r_base, p.R, p.g_magic, Ms);
+            grow = apply_tree_mask<MB>(xa, w, lm, lane, t0, sr.P, sr.n, sr.total - sr.P, r_base, p.R, p.g_magic, Ms);
             late_probabilities<MB>(xa, pla);
         }
         if (__builtin_expect(grow, 0)) {
@@ -1027,7 +1029,7 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(AttnParams p
         region_qk_exp<MB, false>(cur + K_OFF + SUB, cur + V_OFF, w, xb, xa, pb, ring, lane);
         grow = region_pv_max<MB, true>(cur + V_OFF, nullptr, w, pb, pla, plb, xb, ones, ninf, lm, ring, lane);
         if (__builtin_expect(t0 + 2 * AT_SUB > sr.P, 0)) {
-            grow = apply_tree_mask<MB>(xb, w, lm, lane, t0 + AT_SUB, sr.P, sr.n, r_base, p.R, p.g_magic, Ms);
+            grow = apply_tree_mask<MB>(xb, w, lm, lane, t0 + AT_SUB, sr.P, sr.n, sr.total - sr.P, r_base, p.R, p.g_magic, Ms);
             late_probabilities<MB>(xb, plb);
         }
         if (__builtin_expect(grow, 0)) {
@@ -1072,7 +1074,7 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(AttnParams p
             }
             const int t_sub0 = sr.st0 * AT_STAGE + j * AT_SUB;
             if (t_sub0 + AT_SUB > sr.P)
-                apply_tree_mask<MB>(xa, w, lm, lane, t_sub0, sr.P, sr.n, r_base, p.R, p.g_magic, Ms);
+                apply_tree_mask<MB>(xa, w, lm, lane, t_sub0, sr.P, sr.n, sr.total - sr.P, r_base, p.R, p.g_magic, Ms);
 #pragma unroll
             for (int rb = 0; rb < MB; ++rb) {
                 float mx = lm[rb];

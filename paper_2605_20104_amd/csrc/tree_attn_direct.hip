@@ -466,7 +466,7 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
 #pragma unroll
                 for (int rb = 0; rb < MB; ++rb) {
                     const uintx4 words = MASK_HELD ? mw[rb] : mask_lds[node[rb]];
-                    const unsigned win = visible_window(t0 - P, n, [&](int k) {
+                    const unsigned win = visible_window(t0 - P, total - P, [&](int k) {
                         return k == 0 ? words[0] : (k == 1 ? words[1] : (k == 2 ? words[2] : words[3]));
                     }) >> (4 * lg);
 #pragma unroll

@@ -228,3 +228,30 @@ def test_values_that_are_not_finite_stay_with_the_nodes_that_see_them(dtype, D, 
     # the rest of a row that sees such a slot: the same sum in another order
     assert np.isfinite(g[~odd]).all()
     assert (np.abs(g - c)[~odd] <= (1e-5 if dtype == "f32" else 2.0 ** -7) * (1 + np.abs(c[~odd]))).all()
+
+
+@pytest.mark.parametrize("dtype,D,P,pages", [("bf16", 64, 170, 11), ("bf16", 64, 176, 11), ("bf16", 64, 200, 11), ("bf16", 128, 170, 11),
+                                             ("bf16", 128, 8330, 521), ("f32", 64, 170, 11)])
+def test_tree_slots_past_the_block_table_do_not_count(dtype, D, P, pages):
+    """A tree that does not fit its table (an odd number of pages, so that the last tile of 32 or 64 keys reaches past it)
+    is cut at the capacity: no token counts twice."""
+    K, H = 24, 2
+    w = shape_workload(1, K, H, H, D, pages * 16 - K, dtype=dtype)
+    att = inputs.make_attention_inputs(w, seed=P)
+    assert att["block_table"].shape[1] == pages
+    parent = np.arange(-1, K - 1, dtype=np.int32)[None]                    # a chain: every node sees all slots before it
+    n, p = np.array([K], np.int32), np.array([P], np.int32)
+    out = graft.graft_tree_attn(*(dev(att[x][0], dtype) for x in ("q", "k_cache", "v_cache")), att["strides"], dev(att["block_table"]), dev(p),
+                                dev(n), gpu_mask(parent, n, p), H, att["scale"])
+    f = (lambda a: a.astype(np.float64)) if dtype == "f32" else (lambda a: inputs.bf16_bits_to_f32(a).astype(np.float64))
+    q, k, v = (f(att[x][0]) for x in ("q", "k_cache", "v_cache"))
+    k, v = (x[att["block_table"][0]].transpose(1, 0, 2, 3).reshape(H, pages * 16, D) for x in (k, v))
+    got = host(out).astype(np.float64)
+    for i in range(K):
+        seen = min(P + i + 1, pages * 16)
+        for h in range(H):
+            s = k[h, :seen] @ q[0, i, h] * att["scale"]
+            e = np.exp(s - s.max())
+            ref = e @ v[h, :seen] / e.sum()
+            bound = 1e-4 if dtype == "f32" else (2e-2 if D == 128 else 1e-4 + 2.0 ** -8 * np.abs(ref))
+            assert (np.abs(got[0, i, h] - ref) <= bound).all(), (i, h, np.abs(got[0, i, h] - ref).max())
