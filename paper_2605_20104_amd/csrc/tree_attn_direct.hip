@@ -446,6 +446,8 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
         auto step = [&](int it, auto more_, auto careful_) __attribute__((always_inline)) {
             constexpr bool more = decltype(more_)::value, careful = decltype(careful_)::value;
             kt.stage(Ks, lane);
+            asm volatile("" ::: "memory");                        // (lanes read each other's rows: no read moves in front of a write.
+                                                                  // Behind the next loads instead, it costs fp32 2 %.)
             if constexpr (more) load_keys(kt, it + 1);
             const int t0 = tile_at(it) * TK;
             const bool masked = t0 + TK > P;
