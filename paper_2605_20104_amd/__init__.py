@@ -17,6 +17,7 @@ import torch  # noqa: F401  (device memory and streams; its libraries must be lo
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libgraft.so")
+NATIVE_PATH = os.path.join(_PKG, "_native.so")
 
 GRAFT_MAX_NODES = 128
 GRAFT_MASK_WORDS = 2
@@ -71,28 +72,36 @@ class GraftError(RuntimeError):
         super().__init__(msg)
 
 
+def _built(path):
+    if not os.path.exists(path):
+        raise FileNotFoundError(
+            "%s is missing: build it with `python -m paper_2605_20104_amd.build` "
+            "(there is no fallback path)" % path)
+    return path
+
+
 def load_library():
-    """dlopen libgraft.so and declare its signatures.  Raises if it has not been built."""
-    global _lib, _bound
+    """dlopen libgraft.so and declare its signatures (the C ABI; the calls below also need _native.so).
+    Raises if it has not been built."""
+    global _lib
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise FileNotFoundError(
-                "%s is missing: build it with `python -m paper_2605_20104_amd.build` "
-                "(there is no fallback path)" % LIB_PATH)
-        lib = ctypes.CDLL(LIB_PATH)
+        lib = ctypes.CDLL(_built(LIB_PATH))
         for name, (res, args) in _SIGNATURES.items():
             f = getattr(lib, name)
             f.restype, f.argtypes = res, args
-        from . import _native
-        _native.bind(LIB_PATH, GraftError)
-        _lib, _bound = lib, _native
+        _lib = lib
     return _lib
 
 
 def _calls():
     """The native marshalling functions, bound to the library."""
+    global _bound
     if _bound is None:
         load_library()
+        _built(NATIVE_PATH)
+        from . import _native
+        _native.bind(LIB_PATH, GraftError)
+        _bound = _native
     return _bound
 
 

@@ -1,5 +1,7 @@
 """The native marshalling of the Python binding (no GPU): arguments that do not fit are Python errors,
 argument errors of the library are GraftError, and nothing is launched in either case."""
+import sys
+
 import pytest
 import torch
 
@@ -68,6 +70,19 @@ def test_strides_from_a_mapping_that_makes_its_values():
         graft.graft_tree_attn(q, q, q, Strides(), torch.zeros((1, 2), dtype=torch.int32), one, one,
                               torch.zeros((1, 4, 2), dtype=torch.int64), 2, 0.1, stream=0)
     assert e.value.code == graft.GRAFT_ERR_SHAPE and events == ["read"] * 3 + ["gone"] * 3
+
+
+def test_the_c_abi_loads_without_the_native_module(monkeypatch):
+    """Users of the C ABI alone need libgraft.so alone; the Python calls say what to build."""
+    monkeypatch.setattr(graft, "_lib", None)
+    monkeypatch.setattr(graft, "_bound", None)
+    monkeypatch.setattr(graft, "NATIVE_PATH", "/nonexistent/_native.so", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2605_20104_amd._native", None)             # as if it were not there
+    monkeypatch.delattr(graft, "_native", raising=False)
+    assert graft.load_library().graft_version() >= 100
+    assert graft.graft_accept_workspace_bytes(1, 16, 1000) > 0
+    with pytest.raises(FileNotFoundError, match="paper_2605_20104_amd.build"):
+        _mask()
 
 
 @pytest.mark.gpu
