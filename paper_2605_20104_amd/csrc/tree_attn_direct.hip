@@ -769,12 +769,29 @@ static int32_t launch_one(const DirectPlan& pl, const AttnParams& p, int32_t dty
             done_device = dev;
         }
     }
-    const dim3 grid(xcd_grid(static_cast<int64_t>(p.B) * p.Hkv * pl.n_splits, pl.n_row_tiles));
-    launch_main(kernel, grid, dim3(DR_THREADS), lds, s, p, pl.rg);
-    int32_t rc = check_launch();
-    if (rc != GRAFT_OK || pl.n_splits == 1) return rc;
+    // A launch holds fewer than 2^32 work-items.  Batches that need more go in pieces of whole sequences: one
+    // sequence has at most 65535 * 128 workgroups (KV heads, row tiles), which fits.
+    constexpr int64_t max_workgroups = ((int64_t{1} << 32) - 1) / DR_THREADS - 8;
+    const int64_t per_sequence = static_cast<int64_t>(p.Hkv) * pl.n_splits * pl.n_row_tiles;
+    const int64_t piece = max_workgroups / per_sequence;
+    AttnParams part = p;
+    for (int64_t b = 0; b < p.B; b += piece) {
+        part.B = static_cast<int32_t>(p.B - b < piece ? p.B - b : piece);
+        const size_t elements = static_cast<size_t>(b) * p.K_max * p.Hq * D;
+        part.q = static_cast<const T*>(p.q) + elements;
+        part.out = static_cast<T*>(p.out) + elements;
+        part.block_table = p.block_table + b * p.max_pages;
+        part.prefix_len = p.prefix_len + b;
+        part.n_nodes = p.n_nodes + b;
+        part.mask = p.mask + b * p.K_max * GRAFT_MASK_WORDS;
+        launch_main(kernel, dim3(xcd_grid(static_cast<int64_t>(part.B) * p.Hkv * pl.n_splits, pl.n_row_tiles)), dim3(DR_THREADS), lds, s,
+                    part, pl.rg);
+        const int32_t rc = check_launch();
+        if (rc != GRAFT_OK) return rc;
+    }
+    if (pl.n_splits == 1) return GRAFT_OK;
+    // (keys are split only while the chip is not full: one piece, few rows)
     const int64_t n_rows = static_cast<int64_t>(p.B) * p.Hkv * p.R;
-    if (n_rows * (D / 4) > 0x7fffffff) return GRAFT_ERR_SHAPE;
     hipLaunchKernelGGL((tree_attn_direct_merge_kernel<T, D>), dim3(static_cast<unsigned>((n_rows * (D / 4) + 255) / 256)), dim3(256), 0, s,
                        p, static_cast<int32_t>(n_rows));
     return check_launch();

@@ -255,3 +255,21 @@ def test_tree_slots_past_the_block_table_do_not_count(dtype, D, P, pages):
             ref = e @ v[h, :seen] / e.sum()
             bound = 1e-4 if dtype == "f32" else (2e-2 if D == 128 else 1e-4 + 2.0 ** -8 * np.abs(ref))
             assert (np.abs(got[0, i, h] - ref) <= bound).all(), (i, h, np.abs(got[0, i, h] - ref).max())
+
+
+def test_more_workgroups_than_one_launch_holds():
+    """65535 sequences of 130 heads, one node each: 8.5 million workgroups of 512 threads, and a launch holds fewer than 2^32
+    work-items.  All sequences share one page; every row is checked."""
+    B, H, D, P = 65535, 130, 64, 3
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    q = torch.randn((B, 1, H, D), generator=gen, device="cuda", dtype=torch.bfloat16)
+    k, v = (torch.randn((1, H, 16, D), generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    ints = lambda x: torch.full((B,), x, dtype=torch.int32, device="cuda")
+    mask = torch.tensor([1, 0], dtype=torch.int64, device="cuda").expand(B, 1, 2).contiguous()
+    out = graft.graft_tree_attn(q, k, v, {"page": H * 16 * D, "token": D, "head": 16 * D}, torch.zeros((B, 1), dtype=torch.int32, device="cuda"),
+                                ints(P), ints(1), mask, H, 0.125)
+    for h in range(H):
+        kk, vv = k[0, h, :P + 1].float(), v[0, h, :P + 1].float()
+        ref = torch.softmax(q[:, 0, h].float() @ kk.T * 0.125, -1) @ vv
+        err = (out[:, 0, h].float() - ref).abs()
+        assert bool((err <= 1e-4 + 2.0 ** -8 * ref.abs()).all()), (h, float(err.max()))
