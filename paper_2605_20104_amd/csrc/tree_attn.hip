@@ -1344,12 +1344,14 @@ struct PathChoice {
     bool direct;
     AttnPlan mfma;
     DirectPlan dir;
+    DirectPlan unsplit;             // fp32 and D = 64: for callers without a workspace
 };
 static PathChoice make_choice(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages, int32_t dtype) {
     PathChoice c{};
     c.dir = plan_direct(B, K_max, Hq, Hkv, D, max_pages, dtype, true);
     if (dtype != GRAFT_BF16 || D != AT_D) {
         c.direct = true;
+        c.unsplit = c.dir.n_splits > 1 ? plan_direct(B, K_max, Hq, Hkv, D, max_pages, dtype, false) : c.dir;
         return c;
     }
     c.mfma = make_plan(B, K_max, Hq, Hkv, max_pages);
@@ -1357,23 +1359,34 @@ static PathChoice make_choice(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv,
     return c;
 }
 
-// The last shape's choice is kept per host thread: all layers of a model ask for the same one, and
-// working the cost models out takes a few microseconds, as long as a launch.
+// The choices of the last eight shapes are kept per host thread: all layers of a model ask for the same one, a
+// draft and a target model or two batch sizes take turns, and working the cost models out takes about a
+// microsecond, a sixth of a small launch (two shapes in turn, workspace query through ctypes: 1.2 to 1.4 us with one
+// kept choice, 0.33 with eight).  The reference returned is good until the thread's next call.
 static const PathChoice& choose_path(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages, int32_t dtype) {
     struct Kept {
         int32_t key[8];
         PathChoice choice;
     };
-    static thread_local Kept kept{};
+    constexpr int KEPT = 8;
+    static thread_local Kept kept[KEPT]{};
+    static thread_local int last = 0, oldest = 0;
     int32_t key[8] = {B, K_max, Hq, Hkv, D, max_pages, dtype, 1};
 #ifdef GRAFT_ATTN_STAMPS
     key[7] += g_force_splits * 8192 + g_force_row_tiles * 2;
 #endif
-    if (std::memcmp(key, kept.key, sizeof key) != 0) {
-        kept.choice = make_choice(B, K_max, Hq, Hkv, D, max_pages, dtype);
-        std::memcpy(kept.key, key, sizeof key);
+    for (int i = 0; i < KEPT; ++i) {
+        const int at = (last + i) % KEPT;
+        if (std::memcmp(key, kept[at].key, sizeof key) == 0) {
+            last = at;
+            return kept[at].choice;
+        }
     }
-    return kept.choice;
+    last = oldest;
+    oldest = (oldest + 1) % KEPT;
+    kept[last].choice = make_choice(B, K_max, Hq, Hkv, D, max_pages, dtype);
+    std::memcpy(kept[last].key, key, sizeof key);
+    return kept[last].choice;
 }
 
 static bool attn_shape_ok(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages) {
@@ -1509,14 +1522,11 @@ extern "C" int32_t graft_tree_attn(const void* q, const void* k_cache, const voi
     const bool either = dtype == GRAFT_BF16 && D == AT_D;
     // bf16 with D = 128 and a workspace too small for the direct plan: the MFMA path if its own plan needs no more
     if (choice.direct && (!either || fits(choice.dir.ws_bytes) || !fits(choice.mfma.ws_bytes))) {
-        DirectPlan dp = choice.dir;
-        if (!fits(dp.ws_bytes)) {
-            if (either) return GRAFT_ERR_WORKSPACE;
-            // the other shapes have always run without a workspace: a caller that brings none, or too
-            // little, gets a launch that does not split the keys over workgroups
-            dp = plan_direct(B, K_max, Hq, Hkv, D, max_pages, dtype, false);
-        }
-        return launch_direct(dp, p, D, dtype, workspace, s);
+        const bool enough = fits(choice.dir.ws_bytes);
+        if (!enough && either) return GRAFT_ERR_WORKSPACE;
+        // (the other shapes have always run without a workspace: a caller that brings none, or too
+        // little, gets a launch that does not split the keys over workgroups)
+        return launch_direct(enough ? choice.dir : choice.unsplit, p, D, dtype, workspace, s);
     }
 
     const AttnPlan& pl = choice.mfma;

@@ -149,6 +149,31 @@ def test_tree_attn_validation_and_workspace(lib):
     assert ws(64, 16, 8, 8, 128, 40, g.GRAFT_BF16) == 0   # enough (sequence, head) units to fill the chip: one split
 
 
+def test_attention_plans_of_shapes_that_take_turns(lib):
+    """The plan of a shape does not depend on what was asked before, with more shapes in turn than are kept, and
+    two shapes in turn cost about what one costs (with one kept plan they took twice as long)."""
+    import time
+    ws = lib.graft_tree_attn_workspace_bytes
+    shapes = [(1 + b, 20 + 4 * b, 32, 8, d, 130 + b, t) for b in range(6) for d, t in ((64, 1), (128, 1), (128, 0))]
+    alone = [ws(*s) for s in shapes]
+    assert len(set(alone)) > 4
+    for _ in range(3):
+        assert [ws(*s) for s in shapes] == alone
+        assert [ws(*s) for s in reversed(shapes)] == alone[::-1]
+
+    def fastest(turns, n=2000):
+        best = 1e9
+        for _ in range(20):
+            t = time.perf_counter()
+            for i in range(n):
+                ws(*turns[i % len(turns)])
+            best = min(best, time.perf_counter() - t)
+        return best
+
+    pair = [(4, 60, 32, 8, 64, 132, 1), (1, 40, 32, 8, 128, 130, 0)]
+    assert fastest(pair) < 1.5 * max(fastest(pair[:1]), fastest(pair[1:]))
+
+
 def test_accept_validation(lib):
     import paper_2605_20104_amd as g
     f = lib.graft_accept
