@@ -550,14 +550,17 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
         // (0 * inf).  Such a wavefront, if there ever is one, takes its tiles once more, with the values of such
         // keys kept out of the product.  (The same looked for in every step: 2 % on two row blocks with D = 64.)
         if (Ops::ALONE && (first + kg * (count - 1) + 1) * TK > P) {
-            float t = 0.f;                                        // NaN if a sum is not finite
+            bool odd = false;
 #pragma unroll
-            for (int rb = 0; rb < MB; ++rb)
+            for (int rb = 0; rb < MB; ++rb) {
+                float t = 0.f;                                    // NaN if a sum is not finite
 #pragma unroll
                 for (int e = 0; e < NO; ++e)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) t = __builtin_fmaf(o[rb][e][i], 0.f, t);
-            if (__builtin_expect(__builtin_amdgcn_ballot_w64(t != t) != 0, 0)) {
+                odd = odd || (t != t && node[rb] < n);            // (queries of absent nodes may be anything)
+            }
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd) != 0, 0)) {
                 clear_rows();
                 for (int it = 0; it < count; ++it) {
                     if (it % TPR == 0) load_table(it);

@@ -257,6 +257,22 @@ def test_tree_slots_past_the_block_table_do_not_count(dtype, D, P, pages):
             assert (np.abs(got[0, i, h] - ref) <= bound).all(), (i, h, np.abs(got[0, i, h] - ref).max())
 
 
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
+def test_queries_of_absent_nodes_may_be_anything(dtype, D):
+    """NaN and infinities in the query rows behind n_nodes: the other rows keep their bits, these are zeros."""
+    w = shape_workload(2, 33, 8, 2, D, 300, dtype=dtype)
+    att = inputs.make_attention_inputs(w, seed=5)
+    parent = np.stack([inputs.random_recursive_tree(np.random.default_rng(b), w.K, 8) for b in range(w.B)])
+    n, p = np.array([20, 33], np.int32), np.array([300, 117], np.int32)
+    mask = gpu_mask(parent, n, p)
+    q = dev(att["q"][0], dtype)
+    wild = q.clone()
+    wild[0, 20::2], wild[0, 21::2] = float("nan"), float("inf")
+    clean, got = (graft.graft_tree_attn(x, dev(att["k_cache"][0], dtype), dev(att["v_cache"][0], dtype), att["strides"],
+                                        dev(att["block_table"]), dev(p), dev(n), mask, w.Hkv, att["scale"]) for x in (q, wild))
+    assert torch.equal(clean, got) and bool((got[0, 20:] == 0).all())
+
+
 def test_more_workgroups_than_one_launch_holds():
     """65535 sequences of 130 heads, one node each: 8.5 million workgroups of 512 threads, and a launch holds fewer than 2^32
     work-items.  All sequences share one page; every row is checked."""
