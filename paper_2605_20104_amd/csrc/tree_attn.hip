@@ -1480,6 +1480,18 @@ extern "C" int32_t graft_attn_stamp_buffer(void* device_buffer, size_t bytes) {
     return GRAFT_OK;
 }
 extern "C" int32_t graft_attn_stamp_count(void) { return graft::AT_STAMPS; }
+// What a call of this shape launches: {1 for the MFMA path, 0 for the direct one; row blocks per wavefront; row tiles; splits}.
+extern "C" int32_t graft_attn_plan(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages, int32_t dtype,
+                                   int32_t* plan) {
+    if (!plan) return GRAFT_ERR_NULL;
+    if (!graft::attn_shape_ok(B, K_max, Hq, Hkv, D, max_pages)) return GRAFT_ERR_SHAPE;
+    const graft::PathChoice& c = graft::choose_path(B, K_max, Hq, Hkv, D, max_pages, dtype);
+    plan[0] = c.direct ? 0 : 1;
+    plan[1] = c.direct ? c.dir.mb : c.mfma.mb;
+    plan[2] = c.direct ? c.dir.n_row_tiles : c.mfma.n_row_tiles;
+    plan[3] = c.direct ? c.dir.n_splits : c.mfma.n_splits;
+    return GRAFT_OK;
+}
 // Holds the launch plan of this host thread's following calls (workspace query included) at
 // n_splits splits and n_row_tiles row tiles where the shape allows them; zeros give the plan
 // back to the cost model.

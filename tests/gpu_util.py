@@ -1,8 +1,12 @@
 """Helpers for the GPU parity tests: host<->device transfers and workload runners."""
+import collections
+import ctypes
+
 import numpy as np
 import torch
 
 import paper_2605_20104_amd as graft
+from paper_2605_20104_amd import build
 
 
 def dev(a, dtype="i32"):
@@ -48,3 +52,23 @@ def run_attn(att, dtype, prefix_len, n_nodes, mask, Hkv, layer=0, kv=0):
                                 dev(n_nodes), mask, Hkv, att["scale"])
     torch.cuda.synchronize()
     return host(out).astype(np.float32)
+
+
+AttnPlan = collections.namedtuple("AttnPlan", "path row_blocks row_tiles splits")
+
+
+def attn_plan(B, K, Hq, Hkv, D, max_pages, dtype):
+    """The path ("mfma" or "direct") and launch shape of an attention call, as the timing build tells it: the product
+    library plans with the same code."""
+    lib = ctypes.CDLL(build.LIB_TIMING)
+    plan = (ctypes.c_int32 * 4)()
+    assert lib.graft_attn_plan(B, K, Hq, Hkv, D, max_pages, graft.GRAFT_F32 if dtype == "f32" else graft.GRAFT_BF16, plan) == 0
+    return AttnPlan(("direct", "mfma")[plan[0]], *plan[1:])
+
+
+def widened(att, pages):
+    """The same inputs with a block table of more pages (the launch is planned from its capacity); what is added is not used."""
+    table = att["block_table"]
+    wide = np.zeros((table.shape[0], pages), np.int32)
+    wide[:, :table.shape[1]] = table
+    return dict(att, block_table=wide)

@@ -43,7 +43,7 @@ def test_timing_build_is_the_same_interface_plus_its_own_calls(lib):
     timing = ctypes.CDLL(build.LIB_TIMING)
     for n in declared_functions():
         assert getattr(timing, n) is not None
-    for n in ("graft_attn_stamp_buffer", "graft_attn_stamp_count", "graft_attn_force_plan", "graft_mfma_calibration"):
+    for n in ("graft_attn_stamp_buffer", "graft_attn_stamp_count", "graft_attn_force_plan", "graft_attn_plan", "graft_mfma_calibration"):
         assert getattr(timing, n) is not None
         assert not hasattr(lib, n), n
     assert timing.graft_attn_stamp_count() == 24

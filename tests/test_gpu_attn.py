@@ -81,9 +81,10 @@ def test_c1_fp32_full():
     assert np.abs(got - ref.astype(np.float32)).max() <= TOL_F32
 
 
-# (B, K, Hq, Hkv, P): chosen to hit every (row blocks per wavefront) variant of the MFMA kernel,
-# both mask words, ragged prefixes (not a multiple of 16, 32 or 64), and several KV splits.
-MFMA_CASES = [
+# (B, K, Hq, Hkv, P): small and odd sizes, both mask words, ragged prefixes (not a multiple of 16, 32 or
+# 64), on the path that the library takes for them, the direct one for most.  test_gpu_attn_mfma.py has the
+# same sizes on the MFMA kernel, and every number of row blocks of it.
+BF16_CASES = [
     (1, 1, 1, 1, 0),          # a lone root, empty prefix
     (1, 1, 8, 8, 5),
     (2, 16, 8, 2, 333),       # R = 64
@@ -100,8 +101,8 @@ MFMA_CASES = [
 ]
 
 
-@pytest.mark.parametrize("case", MFMA_CASES, ids=lambda c: "B%d_K%d_Hq%d_Hkv%d_P%d" % c)
-def test_bf16_mfma_shapes(case):
+@pytest.mark.parametrize("case", BF16_CASES, ids=lambda c: "B%d_K%d_Hq%d_Hkv%d_P%d" % c)
+def test_bf16_shapes(case):
     B, K, Hq, Hkv, P = case
     w = shape_workload(B, K, Hq, Hkv, 128, P)
     check_case(w, seed=1000 + K + P)
@@ -163,9 +164,9 @@ def test_bf16_head_dim_64_and_fp32_head_dim_128():
     check_case(shape_workload(2, 12, 8, 4, 64, 600, dtype="f32"), seed=10, tol=TOL_F32)
 
 
-def test_mfma_matches_plain_kernel_on_gpu():
-    """Cross-check of the two GPU paths: same bf16 inputs through the MFMA kernel and, widened to
-    fp32, through the plain kernel."""
+def test_bf16_matches_fp32_on_gpu():
+    """The same bf16 inputs as bf16 and widened to fp32, each on the path the library takes
+    (test_gpu_attn_mfma.py compares the two paths)."""
     w = shape_workload(1, 24, 8, 2, 128, 450)
     got, ref, _ = check_case(w, seed=11)
     att = inputs.make_attention_inputs(w, seed=11)
@@ -175,9 +176,9 @@ def test_mfma_matches_plain_kernel_on_gpu():
     rng = np.random.default_rng(11)
     parent = np.stack([inputs.random_recursive_tree(rng, w.K, 8)])
     mask = gpu_mask(parent, [w.K], [w.P])
-    plain = run_attn(wide, "f32", np.array([w.P], np.int32), np.array([w.K], np.int32), mask, w.Hkv)
-    assert np.abs(plain - ref.astype(np.float32)).max() <= TOL_F32
-    assert np.abs(plain - got).max() <= TOL_BF16
+    f32 = run_attn(wide, "f32", np.array([w.P], np.int32), np.array([w.K], np.int32), mask, w.Hkv)
+    assert np.abs(f32 - ref.astype(np.float32)).max() <= TOL_F32
+    assert np.abs(f32 - got).max() <= TOL_BF16
 
 
 def test_large_scores_stay_finite():
@@ -198,9 +199,9 @@ def test_large_scores_stay_finite():
 
 
 def test_scores_that_outgrow_the_reference():
-    """Scores rising steadily along the sequence (by far more than the lazy bound of the fast
-    path) force the exact running-max fallback; falling scores must stay on the fast path.
-    Both must match the oracle."""
+    """Scores rising steadily along the sequence, by far more than the lazy bound of either path, raise
+    a row's reference again and again; falling scores keep the first one.  Both must match the oracle
+    (test_gpu_attn_mfma.py has the same on the MFMA kernel)."""
     w = shape_workload(2, 24, 8, 2, 128, 700)
     att = inputs.make_attention_inputs(w, seed=13)
     pages = att["pages_per_seq"]
@@ -259,8 +260,7 @@ def test_value_magnitudes_across_the_bf16_range(log2_scale):
 
 def test_scores_that_outgrow_the_reference_in_long_splits():
     """The same rising and falling scores with many (sequence, head) units, so that every workgroup
-    runs several stages: wavefronts leave the fast path in the middle of their split, at an even or
-    an odd sub-tile, while transfers of later stages are still to be issued."""
+    walks many tiles, from another place in every sequence."""
     w = shape_workload(8, 16, 8, 8, 128, 1500)
     att = inputs.make_attention_inputs(w, seed=14)
     pages = att["pages_per_seq"]

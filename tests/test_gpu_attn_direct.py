@@ -12,7 +12,7 @@ import torch
 import inputs
 import oracle
 import paper_2605_20104_amd as graft
-from gpu_util import dev, host
+from gpu_util import attn_plan, dev, host
 from test_gpu_attn import check_case, gpu_mask, shape_workload
 
 pytestmark = pytest.mark.gpu
@@ -107,11 +107,12 @@ def test_scores_that_keep_rising(dtype, D):
 
 # bf16 with D = 128 takes the direct path where the keys are few (the probabilities are rounded to bf16
 # there, relative 2^-8 each with random sign, and so is the result: the 2e-2 of every D = 128 test)
-@pytest.mark.parametrize("case", [(1, 1, 1, 1, 0), (1, 20, 8, 8, 300), (2, 33, 6, 2, 63), (1, 78, 8, 1, 37), (3, 128, 32, 2, 20),
+@pytest.mark.parametrize("case", [(1, 1, 1, 1, 100), (1, 20, 8, 8, 300), (2, 33, 6, 2, 63), (1, 78, 8, 1, 37), (3, 128, 32, 2, 20),
                                   (8, 24, 32, 8, 500), (1, 40, 32, 8, 700)], ids=lambda c: "B%d_K%d_Hq%d_Hkv%d_P%d" % c)
 @pytest.mark.parametrize("layout", ["head_major", "token_major"])
 def test_head_128_with_few_keys(case, layout):
     B, K, Hq, Hkv, P = case
+    assert attn_plan(B, K, Hq, Hkv, 128, (P + K + 15) // 16, "bf16").path == "direct"
     w = shape_workload(B, K, Hq, Hkv, 128, P)
     rng = np.random.default_rng(K)
     n_nodes = None if B == 1 else np.concatenate([[K], rng.integers(1, K + 1, B - 1)]).astype(np.int32)
@@ -239,6 +240,7 @@ def test_tree_slots_past_the_block_table_do_not_count(dtype, D, P, pages):
     w = shape_workload(1, K, H, H, D, pages * 16 - K, dtype=dtype)
     att = inputs.make_attention_inputs(w, seed=P)
     assert att["block_table"].shape[1] == pages
+    assert attn_plan(1, K, H, H, D, pages, dtype).path == ("mfma" if pages > 500 else "direct")
     parent = np.arange(-1, K - 1, dtype=np.int32)[None]                    # a chain: every node sees all slots before it
     n, p = np.array([K], np.int32), np.array([P], np.int32)
     out = graft.graft_tree_attn(*(dev(att[x][0], dtype) for x in ("q", "k_cache", "v_cache")), att["strides"], dev(att["block_table"]), dev(p),
@@ -271,6 +273,63 @@ def test_queries_of_absent_nodes_may_be_anything(dtype, D):
     clean, got = (graft.graft_tree_attn(x, dev(att["k_cache"][0], dtype), dev(att["v_cache"][0], dtype), att["strides"],
                                         dev(att["block_table"]), dev(p), dev(n), mask, w.Hkv, att["scale"]) for x in (q, wild))
     assert torch.equal(clean, got) and bool((got[0, 20:] == 0).all())
+
+
+def test_first_call_inside_a_capture_with_more_than_64_kb_of_lds():
+    """The opt-in for more LDS than the default limit comes with a host thread's first such launch: here that is inside a
+    capture.  Every replay gives the bits of an eager call, with eager work in between."""
+    import threading
+    w = shape_workload(2, 40, 16, 4, 128, 600, dtype="f32")
+    plan = attn_plan(w.B, w.K, w.Hq, w.Hkv, w.D, (w.P + w.K + 15) // 16, "f32")
+    assert plan.path == "direct" and 8 * 16 * w.D * 4 >= 65536          # the staged keys alone; with the merge more
+    att = inputs.make_attention_inputs(w, seed=2)
+    parent = np.stack([inputs.random_recursive_tree(np.random.default_rng(2), w.K, 8) for _ in range(w.B)])
+    n, p = np.full(w.B, w.K, np.int32), np.full(w.B, w.P, np.int32)
+    args = [dev(att[x][0], "f32") for x in ("q", "k_cache", "v_cache")] + [att["strides"], dev(att["block_table"]), dev(p), dev(n),
+                                                                           gpu_mask(parent, n, p), w.Hkv, att["scale"]]
+    eager = graft.graft_tree_attn(*args)
+    out = torch.zeros_like(eager)
+    need = graft.graft_tree_attn_workspace_bytes(w.B, w.K, w.Hq, w.Hkv, w.D, args[4].shape[1], graft.GRAFT_F32)
+    ws = torch.empty(max(need, 256), dtype=torch.uint8, device="cuda")
+    g, failed = torch.cuda.CUDAGraph(), []
+
+    def capture():
+        try:
+            with torch.cuda.graph(g):
+                graft.graft_tree_attn(*args, out=out, workspace=ws)
+        except Exception as e:                                            # shown below, in the test's thread
+            failed.append(e)
+
+    torch.cuda.synchronize()
+    t = threading.Thread(target=capture)
+    t.start()
+    t.join()
+    assert not failed, failed
+    for _ in range(4):
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager)
+        assert torch.equal(graft.graft_tree_attn(*args), eager)
+
+
+def test_shapes_that_take_turns_on_one_thread():
+    """Calls of ten shapes in turn, more than a thread keeps plans of, with and without a workspace: the bits of the first
+    time, every time."""
+    none = torch.empty(0, dtype=torch.uint8, device="cuda")
+    calls = []
+    for i, (dtype, D) in enumerate([("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128), ("bf16", 64)] * 2):
+        w = shape_workload(1 + i % 3, 12 + 5 * i, 8, 2, D, 300 + 170 * i, dtype=dtype)
+        att = inputs.make_attention_inputs(w, seed=i)
+        parent = np.stack([inputs.random_recursive_tree(np.random.default_rng(i), w.K, 8) for _ in range(w.B)])
+        n, p = np.full(w.B, w.K, np.int32), np.full(w.B, w.P, np.int32)
+        args = [dev(att[x][0], dtype) for x in ("q", "k_cache", "v_cache")] + [att["strides"], dev(att["block_table"]), dev(p), dev(n),
+                                                                               gpu_mask(parent, n, p), w.Hkv, att["scale"]]
+        calls += [(args, None)] + ([(args, none)] if (dtype, D) != ("bf16", 128) else [])
+    first = [graft.graft_tree_attn(*a, workspace=ws) for a, ws in calls]
+    for _ in range(3):
+        for (a, ws), want in zip(calls, first):
+            assert torch.equal(graft.graft_tree_attn(*a, workspace=ws), want)
 
 
 def test_more_workgroups_than_one_launch_holds():
