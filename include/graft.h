@@ -171,7 +171,8 @@ int32_t graft_build_tree_mask(const int32_t* parent, const int32_t* n_nodes, con
  * prefix_len [B], n_nodes [B], mask [B,K_max,GRAFT_MASK_WORDS] (from graft_build_tree_mask)
  *                             With GRAFT_BF16 and D = 128 the values (not the keys) of all
  *                             n_nodes[b] tree slots have to be finite: an infinity or NaN
- *                             reaches nodes that do not see its slot, as 0 * inf.
+ *                             reaches nodes that do not see its slot, as 0 * inf; and values
+ *                             past 2^100 may overflow.
  * scale                       softmax scale, normally 1/sqrt(D)
  * dtype                       GRAFT_F32: fp32 storage and arithmetic throughout.
  *                             GRAFT_BF16: bf16 storage, fp32 scores/softmax/accumulation,

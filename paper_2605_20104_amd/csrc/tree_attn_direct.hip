@@ -38,7 +38,7 @@ namespace graft {
 
 constexpr int DR_WAVES = 8;                     // wavefronts per workgroup, two per SIMD
 constexpr int DR_THREADS = 64 * DR_WAVES;
-constexpr float DR_LAZY_LOG2 = 16.0f;           // a row keeps its reference while exponents stay below 2^16
+constexpr float DR_LAZY_LOG2 = 16.0f;           // a row keeps its reference while exponents stay below 16
 constexpr int DR_MAX_SPLITS = 32;
 constexpr int DR_MASK_BYTES = 2048;             // ancestor masks of a sequence
 constexpr int DR_LDS_BYTES = 160 * 1024;
@@ -87,7 +87,7 @@ template <int D> struct DirectOps<float, D> {
     static constexpr int NC = 1;                // score tiles of 16 keys
     static constexpr int ROW = D * 4;           // bytes
     static constexpr bool SUM_MFMA = false;
-    static constexpr bool ALONE = true;         // values of unseen slots do not reach a row even if they are not finite
+    static constexpr bool ALONE = true;         // values of any size: those of unseen slots do not reach a row even if they are not finite
     struct Q { floatx4 v[D / 16]; };
     static __device__ __forceinline__ void load_q(Q& q, const float* row, int lg) {
 #pragma unroll
@@ -173,7 +173,7 @@ template <int D> struct DirectOps<__bf16, D> {
     static constexpr int ROW = D * 2;
     static constexpr int P_PARTS = D == 64 ? 3 : 1;     // bf16 numbers that make up a probability (D = 128: rounded to one)
     static constexpr bool SUM_MFMA = P_PARTS == 1;      // row sums of the rounded probabilities, through the matrix cores
-    static constexpr bool ALONE = D == 64;      // (D = 128 asks for finite values, as the path this stands in for does)
+    static constexpr bool ALONE = D == 64;      // (D = 128 asks for finite, ordinary values, as the path this stands in for does)
     static constexpr int SEG = ROW / 32 - 1;    // V rows: 32-byte segment ^ (row & SEG)
     struct Q { bf16x8 v[D / 32]; };
     static __device__ __forceinline__ void load_q(Q& q, const __bf16* row, int lg) {
@@ -485,7 +485,7 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
                 if constexpr (NC == 2)
                     x = fmaxf(x, fmaxf(fmaxf(s[rb][1][0], s[rb][1][1]), fmaxf(s[rb][1][2], s[rb][1][3])));
                 mx[rb] = x * sc;
-                raise = raise || mx[rb] > m[rb] + DR_LAZY_LOG2;
+                raise = raise || mx[rb] > m[rb] + (careful ? 0.f : DR_LAZY_LOG2);
             }
             // (rare) a row without a reference, or one that outgrew it: raise it to the maximum seen
             if (__builtin_expect(__builtin_amdgcn_ballot_w64(raise) != 0, 0)) {
@@ -546,19 +546,20 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
             step(it, std::false_type{}, std::false_type{});
             it = end;
         }
-        // ALONE: an infinite or NaN value in a tree slot makes the product NaN in the rows that do not see the slot as well
-        // (0 * inf).  Such a wavefront, if there ever is one, takes its tiles once more, with the values of such
-        // keys kept out of the product.  (The same looked for in every step: 2 % on two row blocks with D = 64.)
-        if (Ops::ALONE && (first + kg * (count - 1) + 1) * TK > P) {
+        // ALONE: an infinite or NaN value in a tree slot makes the product NaN in the rows that do not see the slot as
+        // well (0 * inf), and values past 2^112 can overflow against a lazy reference.  Such a wavefront, if there
+        // ever is one, takes its tiles once more, with the values of such keys kept out of the product and the exact
+        // running maximum.  (The same looked for in every step: 2 % on two row blocks with D = 64.)
+        if constexpr (Ops::ALONE) {
             bool odd = false;
 #pragma unroll
             for (int rb = 0; rb < MB; ++rb) {
-                float t = 0.f;                                    // NaN if a sum is not finite
+                float t = 0.f;                                    // two sums per instruction, NaN is kept
 #pragma unroll
                 for (int e = 0; e < NO; ++e)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) t = __builtin_fmaf(o[rb][e][i], 0.f, t);
-                odd = odd || (t != t && node[rb] < n);            // (queries of absent nodes may be anything)
+                    for (int i = 0; i < 4; ++i) t = __builtin_elementwise_maximum(t, __builtin_fabsf(o[rb][e][i]));
+                odd = odd || (!(t < INFINITY) && node[rb] < n);   // (queries of absent nodes may be anything)
             }
             if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd) != 0, 0)) {
                 clear_rows();
@@ -710,7 +711,7 @@ static size_t direct_lds_bytes(int mb, int rg, int32_t D, int32_t dtype) {
 // Launch shape: row blocks per wavefront, row groups per workgroup and splits that make the
 // estimated time smallest.  One workgroup of eight wavefronts (two per SIMD) is resident per
 // compute unit, so the job runs in ceil(workgroups / CUs) rounds of a fixed part plus a step per
-// tile of a wavefront.  Measured cycles of a step (eight wavefronts, one tile each): fp32 4700 / 8200
+// tile of a wavefront.  Cycles of a step (eight wavefronts, one tile each): fp32 4700 / 8200
 // (D = 128, one / two row blocks) and 2650 (D = 64), against 4096 / 8192 and 2048 of MFMAs on a SIMD;
 // bf16 2600 (D = 128) and, for D = 64, 1700 / 2750 / 4550 for one / two / four row blocks.  Set-up and
 // the merge through LDS take 6500 + 2000 per row block and 64 dims; the merge of splits is a launch of

@@ -191,8 +191,10 @@ def test_probabilities_keep_their_32_bits_with_head_64():
 @pytest.mark.parametrize("dtype,D,K,Hq,P", [("f32", 64, 40, 8, 300), ("f32", 128, 23, 4, 77), ("f32", 128, 128, 64, 1500), ("bf16", 64, 40, 8, 300),
                                             ("bf16", 64, 128, 64, 3000)])
 def test_values_that_are_not_finite_stay_with_the_nodes_that_see_them(dtype, D, K, Hq, P):
-    """Infinite and NaN values in tree slots, the last one among them: rows that do not see the slot have the bits of a
-    run without them, rows that do get inf or NaN in that dim alone."""
+    """Infinite and NaN values in tree slots, the last one among them: rows that do not see the slot are those of a run
+    without them, rows that do get inf or NaN in that dim alone.  Bound: the walk that keeps such values out takes the exact
+    running maximum as a row's reference, the other one may lag behind it, so the sums are rounded elsewhere: fp32 within
+    1e-5, bf16 results within one unit in the last place, 2^-7."""
     B, Hkv = 2, 4
     w = shape_workload(B, K, Hq, Hkv, D, P, dtype=dtype)
     att = inputs.make_attention_inputs(w, seed=D + K)
@@ -219,14 +221,10 @@ def test_values_that_are_not_finite_stay_with_the_nodes_that_see_them(dtype, D, 
             want[b, sees[b, :, slot], dim] += x
     got = run(bad)
     assert not touched.all()
-    bits = torch.int32 if dtype == "f32" else torch.int16
-    same = torch.from_numpy(~touched).cuda()
-    assert torch.equal(got[same].view(bits), clean[same].view(bits))
     g, c = host(got).astype(np.float64), host(clean).astype(np.float64)
     want = np.broadcast_to(want[:, :, None], g.shape)
     odd = ~np.isfinite(want) | np.isnan(want)
     assert ((g == want) | (np.isnan(g) & np.isnan(want)))[odd].all()
-    # the rest of a row that sees such a slot: the same sum in another order
     assert np.isfinite(g[~odd]).all()
     assert (np.abs(g - c)[~odd] <= (1e-5 if dtype == "f32" else 2.0 ** -7) * (1 + np.abs(c[~odd]))).all()
 
@@ -348,3 +346,25 @@ def test_more_workgroups_than_one_launch_holds():
         ref = torch.softmax(q[:, 0, h].float() @ kk.T * 0.125, -1) @ vv
         err = (out[:, 0, h].float() - ref).abs()
         assert bool((err <= 1e-4 + 2.0 ** -8 * ref.abs()).all()), (h, float(err.max()))
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 64)])
+def test_values_near_the_top_of_the_range(dtype, D):
+    """Values of 2^118 under scores that lie 15 (in log2 units) above those of the keys taken first, too little for a row to
+    raise its reference: a weight of 2^15 relative to that reference must not overflow.  All values are equal, so
+    every row is that value."""
+    K, H, P = 12, 2, 500
+    w = shape_workload(1, K, H, H, D, P, dtype=dtype)
+    att = inputs.make_attention_inputs(w, seed=4)
+    back = (lambda a: a.astype(np.float32)) if dtype == "f32" else inputs.f32_to_bf16_bits
+    q, k, v = (np.zeros(att[x][0].shape, np.float32) for x in ("q", "k_cache", "v_cache"))
+    q[..., 0] = 1.0
+    for lp in range(att["pages_per_seq"]):
+        k[att["block_table"][0, lp], :, :, 0] = np.where(lp * 16 + np.arange(16) < 300, 15 * 0.6931, 0.0)
+    v[:] = 2.0 ** 118
+    parent, n, p = np.arange(-1, K - 1, dtype=np.int32)[None], np.array([K], np.int32), np.array([P], np.int32)
+    for ws in (None, torch.empty(0, dtype=torch.uint8, device="cuda")):
+        out = graft.graft_tree_attn(*(dev(back(x), dtype) for x in (q, k, v)), att["strides"], dev(att["block_table"]), dev(p), dev(n),
+                                    gpu_mask(parent, n, p), H, 1.0, workspace=ws)
+        got = host(out).astype(np.float64) / 2.0 ** 118
+        assert (np.abs(got - 1) <= (1e-5 if dtype == "f32" else 2.0 ** -8)).all(), got.ravel()[:8]
