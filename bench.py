@@ -417,7 +417,7 @@ def run_workload(args, name, steps, warmup, light):
         "per_call_us": {k: round(v, 2) for k, v in per_call_us.items()},
         "extended": extended,
         "roofline": {
-            "kernel": "tree_attn_mfma_kernel" if (w.dtype == "bf16" and w.D == 128) else "tree_attn_direct_kernel",
+            "kernel": attention_kernel_name(w, att["block_table"].shape[1]),
             "bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
             "kernel_avg_us": round(kernel_avg_ms * 1e3, 3), "launches_timed": n_ev,
@@ -431,6 +431,17 @@ def run_workload(args, name, steps, warmup, light):
     del kc, vc, q
     torch.cuda.empty_cache()
     return result
+
+
+def attention_kernel_name(w, max_pages):
+    """The main attention kernel of a workload, as the timing build, which plans with the library's code, tells it."""
+    from paper_2605_20104_amd import build
+    if not os.path.exists(build.LIB_TIMING):
+        return "graft_tree_attn main kernel"
+    plan = (ctypes.c_int32 * 4)()
+    rc = ctypes.CDLL(build.LIB_TIMING).graft_attn_plan(w.B, w.K, w.Hq, w.Hkv, w.D, max_pages, 0 if w.dtype == "f32" else 1, plan)
+    assert rc == 0, rc
+    return "tree_attn_mfma_kernel" if plan[0] else "tree_attn_direct_kernel"
 
 
 def cpu_baseline(w, s, att, att_bytes, budget_s):

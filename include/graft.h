@@ -179,12 +179,14 @@ int32_t graft_build_tree_mask(const int32_t* parent, const int32_t* n_nodes, con
  *                             probabilities rounded to bf16 for the P.V product (D = 128
  *                             only: D = 64 keeps them whole); where, with D = 128, the
  *                             keys are split over workgroups, each split's normalised
- *                             partial row passes through memory as fp16 scaled by a power
+ *                             partial row may pass through memory as fp16 scaled by a power
  *                             of two to its largest entry: 11 bits for entries within
  *                             2^-14 of the row's largest (finer than the bf16 rounding of
- *                             the result), an absolute 2^-25 of it below that.
+ *                             the result), an absolute 2^-25 of it below that (long
+ *                             prefixes; for few keys, as with D = 64, it stays fp32).
  * workspace                   at least graft_tree_attn_workspace_bytes(...) bytes,
- *                             256-byte aligned; contents are scratch.  The size is 0 (and
+ *                             256-byte aligned; contents are scratch (calls in flight on
+ *                             two streams need one each).  The size is 0 (and
  *                             workspace may be NULL) where the keys of a sequence are not
  *                             split over workgroups.  With GRAFT_F32 or D = 64 the workspace
  *                             is optional: without it (NULL or too small) the keys are not

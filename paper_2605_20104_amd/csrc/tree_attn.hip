@@ -30,8 +30,8 @@
 //               MFMA per row block with an all-ones A operand.
 //       pipeline: over 32-token sub-tiles, MFMAs of one sub-tile interleaved slot
 //               by slot with the exp2 / pack / max work of its neighbours; the
-//               MFMA operands are read from LDS two groups ahead, across the
-//               boundary between the two regions of a step.
+//               MFMA operands are read from LDS two or three groups ahead,
+//               across the boundary between the two regions of a step.
 //       mask  : only sub-tiles that reach past the prefix take the masked path
 //               (ancestor bits from graft_build_tree_mask); the prefix is dense.
 //       softmax: a row's reference is the maximum of the first sub-tile that gives
@@ -372,8 +372,10 @@ template <int MB> constexpr int rows_early() { return MB >= 2 ? MB - 1 : MB; }
 // barrier in front of it, so it reads its own first operands and the region before it (LAST)
 // reads nothing ahead.
 // How many groups (of MB MFMAs, 16.4 cycles each) an operand is read from LDS ahead of its use: three
-// is the most the ring allows (1 % less time than two on 2K tokens, one row block; 0.4 % on 32K, five;
-// with three row blocks it is 1 % more on 64K tokens; four to eight groups with a larger ring give no more).
+// is the most the ring allows.  Time of a call with three against two, over shapes of each number of row
+// blocks, same box, in turn: one 0.981 to 0.995, two 0.985 to 1.002, three 0.996 to 1.018, four 0.999 to 1.005,
+// five 0.996 to 1.000 (and the whole 32K round 64.5 against 64.9 us); four to eight groups with a larger
+// ring give no more.
 template <int MB> constexpr int read_ahead() { return MB == 3 ? 2 : 3; }
 
 // Pipeline region 1: the matrix cores compute the exponents of the NEXT sub-tile
@@ -475,7 +477,7 @@ __device__ __forceinline__ bool region_pv_max(const unsigned char* __restrict__ 
             if constexpr (rb < E) mfma_o<o_reg(rb, db), (db == 0 && rb == 0)>(ring[db & 3], pb[rb]);
             else mfma_o<o_reg(rb, db), (db == 0 && rb == 0)>(ring[db & 3], pl_cur);
             // The slot's vector work, at most 8 cycles of it where the slots suffice.
-            // LDS reads of the operand two groups ahead: one half in each of the first two slots.
+            // LDS reads of the operand read_ahead<MB>() groups ahead: one half in each of the first two slots.
             if constexpr (rb == 0) {
                 if constexpr (db + PF < 8) load_v_half<0>(ring[(db + PF) & 3], Vs, db + PF, l16, lg);
                 else if constexpr (!LAST) ring[(db + PF) & 3] = load_k_operand(Knext, db + PF - 8, l16, lg);
@@ -1525,7 +1527,6 @@ extern "C" int32_t graft_tree_attn(const void* q, const void* k_cache, const voi
     p.max_pages = max_pages; p.B = B; p.K_max = K_max; p.Hq = Hq; p.Hkv = Hkv; p.G = Hq / Hkv;
     p.R = K_max * p.G;
     p.g_magic = (65536 + p.G - 1) / p.G;
-    p.scale = scale;
     p.scale_log2e = scale * 1.4426950408889634f;
     hipStream_t s = static_cast<hipStream_t>(stream);
 
