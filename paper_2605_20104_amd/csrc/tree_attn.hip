@@ -538,12 +538,10 @@ __device__ __forceinline__ bool region_pv_max(const unsigned char* __restrict__ 
 }
 
 // Ancestor masking of an exponent tile that reaches past the prefix (tree slots and the
-// tail): masked entries become -inf; the lane-local maxima are recomputed.  slots is the number of
-// tree slots that the block table has room for, n if the caller keeps to it: what lies past them
-// repeats the last token.
+// tail): masked entries become -inf; the lane-local maxima are recomputed.
 template <int MB>
 __device__ __forceinline__ bool apply_tree_mask(floatx4 (&x)[MB][2], const WaveRows<MB>& w, float (&lm)[MB],
-                                                int lane, int t_sub0, int P, int n, int slots, int r_base, int R, int g_magic,
+                                                int lane, int t_sub0, int P, int n, int r_base, int R, int g_magic,
                                                 const unsigned* __restrict__ Ms) {
     const int l16 = lane & 15, lg = lane >> 4;
     bool grow = false;
@@ -552,7 +550,7 @@ __device__ __forceinline__ bool apply_tree_mask(floatx4 (&x)[MB][2], const WaveR
         const int r = r_base + rb * 16 + l16;
         const int node = (r * g_magic) >> 16;              // r / G
         const unsigned* row = Ms + 4 * (r < R && node < n ? node : 0);     // (rows of absent nodes: any finite mask will do)
-        const unsigned win = visible_window(t_sub0 - P, slots, [&](int k) { return row[k]; }) >> (4 * lg);
+        const unsigned win = visible_window(t_sub0 - P, n, [&](int k) { return row[k]; }) >> (4 * lg);
         reserve_acc_registers<MB>();                          // no temporaries of the compiler's in the accumulators
         float mx = -INFINITY;
 #pragma unroll
@@ -838,8 +836,13 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(AttnParams p
     // Everything that came from memory goes to LDS now, so that no load the compiler tracks is
     // outstanding when the first transfers are issued (it counts its own loads only, and a
     // wait for one of them behind the transfers would wait for the transfers as well).
-    if (tid < n_mask_words) Ms[tid] = mw0;
-    if (tid + AT_THREADS < n_mask_words) Ms[tid + AT_THREADS] = mw1;
+    // Bits of tree slots that the block table has no room for are dropped (none, if the caller keeps to it): what
+    // lies past the table's end repeats the last token.  (Here and not where the masks are applied: as one more
+    // argument of the loop that cost 1.6 % with three row blocks.)
+    const int left = sr.total - sr.P - 32 * (tid & 3);
+    const unsigned room = left >= 32 ? ~0u : (left <= 0 ? 0u : (1u << left) - 1u);
+    if (tid < n_mask_words) Ms[tid] = mw0 & room;
+    if (tid + AT_THREADS < n_mask_words) Ms[tid + AT_THREADS] = mw1 & room;
 #pragma unroll
     for (int u = 0; u < 4; ++u)
         if (tid + u * AT_THREADS < n_pg) Tb[tid + u * AT_THREADS] = tbv[u];
@@ -1019,7 +1022,7 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(AttnParams p
         // (where the exponents change after region 2 has turned the late row block's into
         //  probabilities, those are redone)
         if (__builtin_expect(t0 + AT_SUB > sr.P, 0)) {
-            grow = apply_tree_mask<MB>(xa, w, lm, lane, t0, sr.P, sr.n, sr.total - sr.P, r_base, p.R, p.g_magic, Ms);
+            grow = apply_tree_mask<MB>(xa, w, lm, lane, t0, sr.P, sr.n, r_base, p.R, p.g_magic, Ms);
             late_probabilities<MB>(xa, pla);
         }
         if (__builtin_expect(grow, 0)) {
@@ -1031,7 +1034,7 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(AttnParams p
         region_qk_exp<MB, false>(cur + K_OFF + SUB, cur + V_OFF, w, xb, xa, pb, ring, lane);
         grow = region_pv_max<MB, true>(cur + V_OFF, nullptr, w, pb, pla, plb, xb, ones, ninf, lm, ring, lane);
         if (__builtin_expect(t0 + 2 * AT_SUB > sr.P, 0)) {
-            grow = apply_tree_mask<MB>(xb, w, lm, lane, t0 + AT_SUB, sr.P, sr.n, sr.total - sr.P, r_base, p.R, p.g_magic, Ms);
+            grow = apply_tree_mask<MB>(xb, w, lm, lane, t0 + AT_SUB, sr.P, sr.n, r_base, p.R, p.g_magic, Ms);
             late_probabilities<MB>(xb, plb);
         }
         if (__builtin_expect(grow, 0)) {
@@ -1076,7 +1079,7 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(AttnParams p
             }
             const int t_sub0 = sr.st0 * AT_STAGE + j * AT_SUB;
             if (t_sub0 + AT_SUB > sr.P)
-                apply_tree_mask<MB>(xa, w, lm, lane, t_sub0, sr.P, sr.n, sr.total - sr.P, r_base, p.R, p.g_magic, Ms);
+                apply_tree_mask<MB>(xa, w, lm, lane, t_sub0, sr.P, sr.n, r_base, p.R, p.g_magic, Ms);
 #pragma unroll
             for (int rb = 0; rb < MB; ++rb) {
                 float mx = lm[rb];
