@@ -147,3 +147,4 @@ def test_calls_on_two_streams_without_a_workspace():
     for a, o in zip(alone, outs):
         for x in o:
             assert torch.equal(a, x)
+    assert torch.equal(graft.graft_tree_attn(*problems[0], stream=0), alone[0])          # the null stream, by its handle
