@@ -20,10 +20,13 @@ NATIVE = os.path.join(PKG, "_native.so")                 # tensor marshalling of
 SOURCES = ["api.hip", "retrieve.hip", "tree_mask.hip", "tree_attn.hip", "tree_attn_direct.hip", "accept.hip", "matrix.hip", "kv_compact.hip", "prune.hip"]
 
 # packed-fp32 code generation is switched off for every device compile; VGPR spills must not
-# land in AccVGPRs (the attention kernel manages those by hand)
+# land in AccVGPRs (the attention kernel manages those by hand).  Kernel arguments: the first 14 words arrive in
+# scalar registers with the wavefront instead of being loaded by it, a cold trip to memory in front of every kernel's
+# first request (0.4 us a launch: a round of four small kernels 19.0 -> 18.5 us, a layer's attention and merge with 2K keys
+# 15.0 -> 14.0), so kernels take what that request needs first.
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I", INCLUDE, "-I", CSRC,
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-               "-mllvm", "-amdgpu-spill-vgpr-to-agpr=0",
+               "-mllvm", "-amdgpu-spill-vgpr-to-agpr=0", "-mllvm", "-amdgpu-kernarg-preload-count=16",
                "-Wno-unused-command-line-argument"]
 
 

@@ -43,16 +43,26 @@ struct AttnParams {
 // over are dealt one by one, so that the XCDs' shares differ by one workgroup at most (with whole
 // units only, 50 units of 5 tiles put 35 workgroups on two XCDs of 32 compute units: a second round
 // for a job that was planned to fill the chip once, 71 us instead of 42).
+// Division by a number that the host knows: x / d == (x * magic31(d)) >> 31 for 0 <= x < 2^24, 1 <= d <= 128.  A
+// division is some thirty dependent instructions, and several stand in front of a workgroup's first requests.
+inline uint32_t magic31(uint32_t d) { return ((1u << 31) + d - 1u) / d; }
+__device__ __forceinline__ int div31(int x, uint32_t magic) {
+    return static_cast<int>((static_cast<u64>(static_cast<unsigned>(x)) * magic) >> 31);
+}
+// x / d for x, d < 2^24, by a number that has no such bound.
+__device__ __forceinline__ int div24(int x, int d) {
+    return static_cast<int>((static_cast<unsigned>(x) & 0xffffffu) / (static_cast<unsigned>(d) & 0xffffffu));
+}
 struct WorkItem { int unit, row_tile; };                         // unit < 0: padding of the grid
 inline unsigned xcd_grid(int64_t n_units, int64_t n_row_tiles) {
     return static_cast<unsigned>(8 * ((n_units / 8) * n_row_tiles + (n_units % 8 * n_row_tiles + 7) / 8));
 }
-__device__ __forceinline__ WorkItem xcd_work_item(int n_units, int n_row_tiles) {
+__device__ __forceinline__ WorkItem xcd_work_item(int n_units, int n_row_tiles, uint32_t row_tiles_magic) {
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int whole = (n_units >> 3) * n_row_tiles;               // slots of an XCD that take whole units
     const bool left = slot >= whole;
     const int s = left ? (slot - whole) * 8 + xcd : slot;
-    const int u = s / n_row_tiles, t = s - u * n_row_tiles;
+    const int u = div31(s, row_tiles_magic), t = s - u * n_row_tiles;
     const int unit = left ? (n_units & ~7) + u : u * 8 + xcd;
     return {unit < n_units ? unit : -1, t};
 }
@@ -88,6 +98,37 @@ static void launch_main(Kernel kernel, dim3 grid, dim3 block, unsigned lds_bytes
     } else {
         hipLaunchKernelGGL(kernel, grid, block, lds_bytes, s, args...);
     }
+}
+
+// The main kernels' first arguments arrive in scalar registers (the build's kernarg preload) where the rest is a trip to
+// memory: they are what a workgroup needs to find its sequence and to request its lengths.  n_splits <= 64, row tiles <= 128
+// and, from the limit on a launch's work-items, fewer than 2^24 workgroups, as div31 wants it.
+#define GRAFT_ATTN_ARGS                                                                                                        \
+    const int32_t *n_nodes, const int32_t *prefix_len, int32_t n_units, int32_t n_row_tiles, uint32_t row_tiles_magic, int32_t n_splits, \
+        uint32_t splits_magic, int32_t n_kv_heads, int32_t row_groups, uint32_t row_groups_magic, int32_t key_groups,                \
+        uint32_t key_groups_magic, AttnParams p
+template <class Kernel>
+static void launch_attn(Kernel kernel, dim3 grid, dim3 block, unsigned lds_bytes, hipStream_t s, const AttnParams& p, int32_t row_groups,
+                        int32_t key_groups) {
+    launch_main(kernel, grid, block, lds_bytes, s, p.n_nodes, p.prefix_len, p.B * p.Hkv * p.n_splits, p.n_row_tiles,
+                magic31(static_cast<uint32_t>(p.n_row_tiles)), p.n_splits, magic31(static_cast<uint32_t>(p.n_splits)), p.Hkv, row_groups,
+                magic31(static_cast<uint32_t>(row_groups)), key_groups, magic31(static_cast<uint32_t>(key_groups)), p);
+}
+
+// The rest of AttnParams that the set-up reads, requested at once at the top of the kernel.  Left to itself the compiler
+// loads each argument where it is first used, and in a chain of dependent trips (lengths, page table, first keys) every
+// such load is a trip of its own.
+__device__ __forceinline__ void await_setup_args(const AttnParams& p) {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" : : "s"(p.q), "s"(p.k), "s"(p.v), "s"(p.block_table), "s"(p.mask), "s"(p.page_stride), "s"(p.token_stride),
+                 "s"(p.head_stride), "s"(p.max_pages), "s"(p.K_max), "s"(p.Hq), "s"(p.G), "s"(p.R), "s"(p.g_magic), "s"(p.scale_log2e));
+}
+
+// A wavefront-uniform value that the compiler takes for one that differs between lanes: what is loaded with it stays in
+// a vector register until it is asked for, instead of being waited for and moved to a scalar register on the spot.
+__device__ __forceinline__ int per_lane(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
 }
 
 // Which of the 32 tokens from tree slot s on (s = token - prefix length, negative inside the prefix) a

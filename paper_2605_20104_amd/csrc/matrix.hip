@@ -24,10 +24,9 @@ constexpr int MU_WAVES = MU_THREADS / 64;
 constexpr int MM_UNROLL = 8;
 
 __global__ __launch_bounds__(MR_THREADS) void matrix_retrieve_kernel(
-    const int32_t* __restrict__ M, int32_t V, int32_t k, const int32_t* __restrict__ tpl_parent,
-    const int32_t* __restrict__ tpl_rank, int32_t N, const int32_t* __restrict__ n_ret, int32_t K_max,
-    int32_t* __restrict__ tokens, int32_t* __restrict__ parent, int32_t* __restrict__ n_nodes,
-    int32_t* __restrict__ status) {
+    int32_t* __restrict__ n_nodes, const int32_t* __restrict__ n_ret, int32_t* __restrict__ tokens, int32_t K_max, int32_t N,
+    const int32_t* __restrict__ tpl_parent, const int32_t* __restrict__ tpl_rank, const int32_t* __restrict__ M, int32_t V, int32_t k,
+    int32_t* __restrict__ parent, int32_t* __restrict__ status) {
     const int b = blockIdx.x, u = threadIdx.x;
     __shared__ int32_t x[GRAFT_MAX_NODES];        // token of template node u
     __shared__ int32_t done[GRAFT_MAX_NODES];
@@ -339,8 +338,8 @@ extern "C" int32_t graft_matrix_retrieve(const int32_t* M, int32_t V, int32_t k,
         K_max > GRAFT_MAX_NODES)
         return GRAFT_ERR_SHAPE;
     hipLaunchKernelGGL(graft::matrix_retrieve_kernel, dim3(B), dim3(graft::MR_THREADS), 0,
-                       static_cast<hipStream_t>(stream), M, V, k, tpl_parent, tpl_rank, N, n_ret, K_max,
-                       tokens, parent, n_nodes, status);
+                       static_cast<hipStream_t>(stream), n_nodes, n_ret, tokens, K_max, N, tpl_parent, tpl_rank, M, V, k,
+                       parent, status);
     return graft::check_launch();
 }
 

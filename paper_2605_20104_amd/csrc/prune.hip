@@ -19,9 +19,9 @@ constexpr int PS_PATH = 16;                        // ancestors a thread records
 
 __global__ __launch_bounds__(PS_THREADS) void prune_select_kernel(
     const int32_t* __restrict__ parent, const int32_t* __restrict__ tokens, const float* __restrict__ logq,
-    const int32_t* __restrict__ n_nodes, int32_t K_max, const int32_t* __restrict__ chk_depth,
+    const int32_t* __restrict__ n_nodes, int32_t K_max, int32_t n_chk, const int32_t* __restrict__ chk_depth,
     const float* __restrict__ chk_log_tau, const int32_t* __restrict__ chk_keep,
-    const int32_t* __restrict__ chk_ret, int32_t n_chk, int32_t* __restrict__ out_parent,
+    const int32_t* __restrict__ chk_ret, int32_t* __restrict__ out_parent,
     int32_t* __restrict__ out_tokens, int32_t* __restrict__ out_index, int32_t* __restrict__ out_n_nodes,
     int32_t* __restrict__ stage, int32_t* __restrict__ n_ret, int32_t* __restrict__ status) {
     const int b = blockIdx.x, i = threadIdx.x;
@@ -182,8 +182,8 @@ extern "C" int32_t graft_prune_select(const int32_t* parent, const int32_t* toke
     if (B < 1 || K_max < 1 || K_max > GRAFT_MAX_NODES || n_chk < 0 || n_chk > GRAFT_MAX_CHECKPOINTS)
         return GRAFT_ERR_SHAPE;
     hipLaunchKernelGGL(graft::prune_select_kernel, dim3(B), dim3(graft::PS_THREADS), 0,
-                       static_cast<hipStream_t>(stream), parent, tokens, logq, n_nodes, K_max, chk_depth,
-                       chk_log_tau, chk_keep, chk_ret, n_chk, out_parent, out_tokens, out_index, out_n_nodes,
+                       static_cast<hipStream_t>(stream), parent, tokens, logq, n_nodes, K_max, n_chk, chk_depth,
+                       chk_log_tau, chk_keep, chk_ret, out_parent, out_tokens, out_index, out_n_nodes,
                        stage, n_ret, status);
     return graft::check_launch();
 }

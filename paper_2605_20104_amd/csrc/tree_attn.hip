@@ -729,7 +729,7 @@ __device__ __forceinline__ unsigned scale_bf16_pair(unsigned q2, float f) {
 }
 
 template <int MB>
-__global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(AttnParams p) {
+__global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(GRAFT_ATTN_ARGS) {
     __shared__ __attribute__((aligned(1024))) unsigned char kv[AT_NBUF][AT_STAGE_BYTES];
     __shared__ unsigned Ms[GRAFT_MAX_NODES * GRAFT_MASK_WORDS * 2];   // ancestor masks as 32-bit words
     __shared__ int32_t Tb[AT_MAX_SPLIT_PAGES];                         // this split's block-table entries
@@ -739,18 +739,21 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(AttnParams p
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave_u = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lg = lane >> 4;
-    const WorkItem item = xcd_work_item(p.B * p.Hkv * p.n_splits, p.n_row_tiles);
-    if (item.unit < 0) return;                                    // grid padding (whole workgroup)
-    const int rt = item.row_tile, unit = item.unit;              // unit over B * Hkv * n_splits
-    const int split = unit % p.n_splits;
-    const int g = (unit / p.n_splits) % p.Hkv, b = unit / (p.n_splits * p.Hkv);
+    const WorkItem item = xcd_work_item(n_units, n_row_tiles, row_tiles_magic);
+    const bool padding = item.unit < 0;          // of the grid (whole workgroup): it leaves behind the first requests, which
+                                                 // a branch in front of them would delay
+    const int rt = item.row_tile, unit = padding ? 0 : item.unit;             // unit over B * Hkv * n_splits
+    const int bg = div31(unit, splits_magic), split = unit - bg * n_splits;
+    const int b = div24(bg, n_kv_heads), g = bg - b * n_kv_heads;
 
     // The set-up is a chain of dependent trips to memory (lengths -> block table -> first
     // keys), so everything that does not depend on the lengths is requested alongside them:
     // the lengths first (vector memory returns in order, and they are waited for first), then
     // this wavefront's Q rows and the sequence's ancestor masks.
-    const int n_raw = p.n_nodes[b];
-    const int P_raw = p.prefix_len[b];
+    const int b_lane = per_lane(b);              // (requested here, waited for behind the requests below)
+    const int n_lane = n_nodes[b_lane], P_lane = prefix_len[b_lane];
+    await_setup_args(p);
+    if (padding) return;
     // Q rows of this wavefront (rows past R read row 0 and are zeroed when converted)
     const int r_base = rt * (AT_WAVES * 16 * MB) + wave_u * (16 * MB);
     uintx4 qd[MB][4];
@@ -772,6 +775,8 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(AttnParams p
     const unsigned mw0 = tid < n_mask_words ? mask_words[tid] : 0u;
     const unsigned mw1 = tid + AT_THREADS < n_mask_words ? mask_words[tid + AT_THREADS] : 0u;
 
+    __builtin_amdgcn_sched_barrier(0);
+    const int n_raw = __builtin_amdgcn_readfirstlane(n_lane), P_raw = __builtin_amdgcn_readfirstlane(P_lane);
     SplitRange sr;
     int n = n_raw;
     if (n < 1 || n > p.K_max) n = 0;
@@ -782,7 +787,7 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(AttnParams p
     sr.P = P;
     sr.total = n ? ((P + n) < cap ? (P + n) : cap) : 0;
     const int n_stages = (sr.total + AT_STAGE - 1) / AT_STAGE;
-    const int spt = (n_stages + p.n_splits - 1) / p.n_splits;
+    const int spt = div31(n_stages + n_splits - 1, splits_magic);
     sr.st0 = split * spt;
     sr.st1 = (sr.st0 + spt) < n_stages ? (sr.st0 + spt) : n_stages;
     if (sr.st1 < sr.st0) sr.st1 = sr.st0;
@@ -1093,7 +1098,7 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(AttnParams p
     GRAFT_STAMP(AT_TS_LOOP_END);
     GRAFT_STAMP_CYCLES(AT_TS_CYCLES_END);
 
-    if (p.n_splits == 1) {
+    if (n_splits == 1) {
         // ---- one split: this workgroup holds the whole result of its rows
         // (the lane index goes through an empty asm: otherwise the compiler keeps the row
         //  addressing it computed for the Q loads in registers across the whole loop, registers
@@ -1114,7 +1119,7 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(AttnParams p
     //      lane), so that every store instruction fills 1 KB of consecutive addresses.
     typedef float floatx2 __attribute__((ext_vector_type(2)));
     typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
-    const size_t part = ((static_cast<size_t>(b) * p.Hkv + g) * p.n_splits + split) * p.R_pad;
+    const size_t part = ((static_cast<size_t>(b) * n_kv_heads + g) * n_splits + split) * p.R_pad;
     static_for<0, MB>([&](auto rb_) {
         GRAFT_CONST(rb, rb_);
         const int r0 = r_base + rb * 16;                          // first row of this 16-row block
@@ -1166,36 +1171,36 @@ constexpr int CB_MAX_SPLITS = 16;
 constexpr int CB_MAX_WAVES = 8;          // per workgroup; the host picks a multiple of the wavefronts per tile pair
 
 template <int U>
-__global__ __launch_bounds__(64 * CB_MAX_WAVES) void tree_attn_combine_kernel(AttnParams p, int32_t n_tiles, int32_t wpt) {
+__global__ __launch_bounds__(64 * CB_MAX_WAVES) void tree_attn_combine_kernel(
+    const unsigned short* ws_o, const float* ws_ml, const int32_t* n_nodes, int32_t n_tiles, int32_t wpt, int32_t tiles_per_wg, int32_t R,
+    int32_t R_pad, int32_t n_splits, int32_t n_kv_heads, AttnParams p) {
     typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
     constexpr int CB_SPLITS = U;
     // (m, den, acc[8]) per lane of the helper wavefronts (only U = 16 has helpers)
     __shared__ float xch[U == CB_MAX_SPLITS ? CB_MAX_WAVES : 1][10][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l16 = lane & 15, lg = lane >> 4;
-    const int n_blk = p.R_pad >> 4;                                           // 16-row blocks per (b, g)
-    const int tiles_per_wg = (blockDim.x >> 6) / wpt;
+    const int n_blk = R_pad >> 4;                                           // 16-row blocks per (b, g)
     const int tile = static_cast<int>(blockIdx.x) * tiles_per_wg + wave / wpt;   // over B*Hkv*n_blk*4
     const int part_i = wave % wpt;                                            // which CB_SPLITS splits
     const int dp = tile & 3;                                                  // dims 32 dp .. 32 dp + 31
-    const int blk = (tile >> 2) % n_blk;
-    const int bg = (tile >> 2) / n_blk;                                       // b * Hkv + g
-    const int g = bg % p.Hkv, b = bg / p.Hkv;
+    const int bg = (tile >> 2) / n_blk, blk = (tile >> 2) - bg * n_blk;       // b * Hkv + g, row block
+    const int b = bg / n_kv_heads, g = bg - b * n_kv_heads;
     const int r = blk * 16 + l16;
-    const bool live = tile < n_tiles && r < p.R;                              // not a padding row or tile
-    const int ns = p.n_splits;
+    const bool live = tile < n_tiles && r < R;                              // not a padding row or tile
+    const int ns = n_splits;
     const int s0 = part_i * CB_SPLITS;
 
     float m_run = -INFINITY, den = 0.f;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     int n = 0;
     if (live) {
-        n = p.n_nodes[b];                                                     // needed only at the end
-        const size_t base = static_cast<size_t>(bg) * ns * p.R_pad + blk * 16;     // row index of split 0
-        const float* mlrow = p.ws_ml + (base + l16) * 4;
-        const size_t ml_stride = static_cast<size_t>(p.R_pad) * 4;
-        const unsigned short* otile = p.ws_o + base * AT_D + 512 * dp + 8 * lane;
-        const size_t o_stride = static_cast<size_t>(p.R_pad) * AT_D;
+        n = n_nodes[b];                                                     // needed only at the end
+        const size_t base = static_cast<size_t>(bg) * ns * R_pad + blk * 16;     // row index of split 0
+        const float* mlrow = ws_ml + (base + l16) * 4;
+        const size_t ml_stride = static_cast<size_t>(R_pad) * 4;
+        const unsigned short* otile = ws_o + base * AT_D + 512 * dp + 8 * lane;
+        const size_t o_stride = static_cast<size_t>(R_pad) * AT_D;
         uintx4 ov[CB_SPLITS];
         floatx4 ml[CB_SPLITS];
 #pragma unroll
@@ -1555,11 +1560,11 @@ extern "C" int32_t graft_tree_attn(const void* q, const void* k_cache, const voi
     p.stamps = static_cast<size_t>(grid.x) * AT_STAMPS * sizeof(unsigned long long) <= g_stamps_bytes ? g_stamps : nullptr;
 #endif
     switch (pl.mb) {
-        case 1: launch_main(tree_attn_mfma_kernel<1>, grid, dim3(AT_THREADS), 0, s, p); break;
-        case 2: launch_main(tree_attn_mfma_kernel<2>, grid, dim3(AT_THREADS), 0, s, p); break;
-        case 3: launch_main(tree_attn_mfma_kernel<3>, grid, dim3(AT_THREADS), 0, s, p); break;
-        case 4: launch_main(tree_attn_mfma_kernel<4>, grid, dim3(AT_THREADS), 0, s, p); break;
-        default: launch_main(tree_attn_mfma_kernel<5>, grid, dim3(AT_THREADS), 0, s, p); break;
+        case 1: launch_attn(tree_attn_mfma_kernel<1>, grid, dim3(AT_THREADS), 0, s, p, 1, 1); break;
+        case 2: launch_attn(tree_attn_mfma_kernel<2>, grid, dim3(AT_THREADS), 0, s, p, 1, 1); break;
+        case 3: launch_attn(tree_attn_mfma_kernel<3>, grid, dim3(AT_THREADS), 0, s, p, 1, 1); break;
+        case 4: launch_attn(tree_attn_mfma_kernel<4>, grid, dim3(AT_THREADS), 0, s, p, 1, 1); break;
+        default: launch_attn(tree_attn_mfma_kernel<5>, grid, dim3(AT_THREADS), 0, s, p, 1, 1); break;
     }
     int32_t rc = check_launch();
     if (rc != GRAFT_OK || pl.n_splits == 1) return rc;
@@ -1574,12 +1579,15 @@ extern "C" int32_t graft_tree_attn(const void* q, const void* k_cache, const voi
     const int64_t tpw_max = CB_MAX_WAVES / wpt;
     tpw = tpw < 1 ? 1 : (tpw > tpw_max ? tpw_max : tpw);
     const dim3 cgrid(static_cast<unsigned>((n_tiles + tpw - 1) / tpw)), cblock(static_cast<unsigned>(64 * tpw * wpt));
-    const int32_t nt = static_cast<int32_t>(n_tiles);
+    const auto combine = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, cgrid, cblock, 0, s, p.ws_o, p.ws_ml, n_nodes, static_cast<int32_t>(n_tiles), wpt, static_cast<int32_t>(tpw), p.R,
+                           p.R_pad, p.n_splits, Hkv, p);
+    };
     switch (cb_u) {
-        case 2: hipLaunchKernelGGL(tree_attn_combine_kernel<2>, cgrid, cblock, 0, s, p, nt, wpt); break;
-        case 4: hipLaunchKernelGGL(tree_attn_combine_kernel<4>, cgrid, cblock, 0, s, p, nt, wpt); break;
-        case 8: hipLaunchKernelGGL(tree_attn_combine_kernel<8>, cgrid, cblock, 0, s, p, nt, wpt); break;
-        default: hipLaunchKernelGGL(tree_attn_combine_kernel<16>, cgrid, cblock, 0, s, p, nt, wpt); break;
+        case 2: combine(tree_attn_combine_kernel<2>); break;
+        case 4: combine(tree_attn_combine_kernel<4>); break;
+        case 8: combine(tree_attn_combine_kernel<8>); break;
+        default: combine(tree_attn_combine_kernel<16>); break;
     }
     return check_launch();
 }

@@ -302,7 +302,7 @@ __device__ __forceinline__ void store4(__bf16* p, const floatx4& v) {
 // p.R_pad = rows covered by the row tiles; rg (row groups) and the rest of the shape as below.  One row block
 // with D = 64 leaves room for a second workgroup on the compute unit.
 template <typename T, int D, int MB>
-__global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_direct_kernel(AttnParams p, int32_t rg) {
+__global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_direct_kernel(GRAFT_ATTN_ARGS) {
     using Ops = DirectOps<T, D>;
     constexpr int TK = Ops::TK, NO = Ops::NO, NC = Ops::NC, ROW = Ops::ROW;
     using Keys = StagedKeys<ROW, TK>;
@@ -319,16 +319,19 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lg = lane >> 4;
-    const int kg = DR_WAVES / rg;
-    const int rgi = wave % rg, kgi = wave / rg;
-    const WorkItem item = xcd_work_item(p.B * p.Hkv * p.n_splits, p.n_row_tiles);
-    if (item.unit < 0) return;                                    // grid padding (whole workgroup)
-    const int rt = item.row_tile, unit = item.unit;
-    const int split = unit % p.n_splits;
-    const int g = (unit / p.n_splits) % p.Hkv, b = unit / (p.n_splits * p.Hkv);
+    const int rg = row_groups, kg = key_groups;
+    const int kgi = div31(wave, row_groups_magic), rgi = wave - kgi * rg;
+    const WorkItem item = xcd_work_item(n_units, n_row_tiles, row_tiles_magic);
+    const bool padding = item.unit < 0;          // of the grid (whole workgroup): it leaves behind the first requests, which
+                                                 // a branch in front of them would delay
+    const int rt = item.row_tile, unit = padding ? 0 : item.unit;             // unit over B * Hkv * n_splits
+    const int bg = div31(unit, splits_magic), split = unit - bg * n_splits;
+    const int b = div24(bg, n_kv_heads), g = bg - b * n_kv_heads;
 
-    const int n_raw = p.n_nodes[b];
-    const int P_raw = p.prefix_len[b];
+    const int b_lane = per_lane(b);              // (requested here, waited for behind the requests below)
+    const int n_lane = n_nodes[b_lane], P_lane = prefix_len[b_lane];
+    await_setup_args(p);
+    if (padding) return;
     const int r_base = (rt * rg + rgi) * (16 * MB);
     typename Ops::Q q[MB];
     uintx4 mw[MB];                              // ancestor mask of the row's node
@@ -354,6 +357,8 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
         __syncthreads();
     }
 
+    __builtin_amdgcn_sched_barrier(0);
+    const int n_raw = __builtin_amdgcn_readfirstlane(n_lane), P_raw = __builtin_amdgcn_readfirstlane(P_lane);
     int n = n_raw;
     if (n < 1 || n > p.K_max) n = 0;
     const int cap = p.max_pages * GRAFT_PAGE_SIZE;
@@ -361,13 +366,13 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
     P = P < 0 ? 0 : (P > cap ? cap : P);
     const int total = n ? ((P + n) < cap ? (P + n) : cap) : 0;
     const int n_tiles = (total + TK - 1) / TK;
-    const int per_split = (n_tiles + p.n_splits - 1) / p.n_splits;
+    const int per_split = div31(n_tiles + n_splits - 1, splits_magic);
     const int tile0 = split * per_split;
     const int tile1 = (tile0 + per_split) < n_tiles ? (tile0 + per_split) : n_tiles;
     // this wavefront's tiles: tile0 + kgi, + kg, ...; none if all its rows belong to absent nodes
     const int first = tile0 + kgi;
     const bool rows_live = ((r_base * p.g_magic) >> 16) < n && r_base < p.R;
-    const int count = (rows_live && first < tile1) ? (tile1 - first + kg - 1) / kg : 0;
+    const int count = (rows_live && first < tile1) ? div31(tile1 - first + kg - 1, key_groups_magic) : 0;
 
     float m[MB], l[MB];
     floatx4 lv[MB];                             // row sums where the matrix cores take them (every entry the row's sum)
@@ -577,12 +582,12 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
     // ---- results: this workgroup's rows, merged over its key groups
     T* outp = static_cast<T*>(p.out);
     float* ws_o = reinterpret_cast<float*>(p.ws_o);
-    const size_t part = ((static_cast<size_t>(b) * p.Hkv + g) * p.n_splits + split) * p.R_pad;
+    const size_t part = ((static_cast<size_t>(b) * n_kv_heads + g) * n_splits + split) * p.R_pad;
     if (kg == 1) {
 #pragma unroll
         for (int rb = 0; rb < MB; ++rb) {
             const int r = r_base + rb * 16 + l16;
-            if (p.n_splits == 1) {
+            if (n_splits == 1) {
                 const bool keep = r < p.R && node[rb] < n && l[rb] > 0.f;
                 const float inv = keep ? 1.0f / l[rb] : 0.f;
                 T* row = outp + ((static_cast<size_t>(b) * p.K_max + node[rb]) * p.Hq + g * p.G + (r - node[rb] * p.G)) * D;
@@ -632,7 +637,7 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
             acc += *reinterpret_cast<const floatx4*>(merge_lds + (k * rows + lr) * PITCH + 4 * d4) * f;
         }
         const int r = rt * rows + lr;
-        if (p.n_splits == 1) {
+        if (n_splits == 1) {
             if (r < p.R) {
                 const int i = (r * p.g_magic) >> 16;
                 const bool keep = i < n && den > 0.f;
@@ -651,17 +656,19 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
 
 // Merge of the splits: one thread per four dims of a row, the splits' pieces requested eight at a time.
 template <typename T, int D>
-__global__ __launch_bounds__(256) void tree_attn_direct_merge_kernel(AttnParams p, int32_t n_rows) {
+__global__ __launch_bounds__(256) void tree_attn_direct_merge_kernel(
+    const unsigned short* ws_bits, const float* ws_ml, const int32_t* n_nodes, int32_t n_rows, int32_t R, int32_t R_pad, int32_t n_splits,
+    int32_t n_kv_heads, AttnParams p) {
     const int x = blockIdx.x * 256 + threadIdx.x;
     const int row = x / (D / 4), d4 = x % (D / 4);                // row over B * Hkv * R
     if (row >= n_rows) return;
-    const int r = row % p.R, bg = row / p.R, g = bg % p.Hkv, b = bg / p.Hkv;
-    const int n_raw = p.n_nodes[b];
-    const size_t base = static_cast<size_t>(bg) * p.n_splits * p.R_pad + r;
-    const float* ws_o = reinterpret_cast<const float*>(p.ws_o);
+    const int r = row % R, bg = row / R, g = bg % n_kv_heads, b = bg / n_kv_heads;
+    const int n_raw = n_nodes[b];
+    const size_t base = static_cast<size_t>(bg) * n_splits * R_pad + r;
+    const float* ws_o = reinterpret_cast<const float*>(ws_bits);
     float mm = -INFINITY, den = 0.f;
     floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int s0 = 0; s0 < p.n_splits; s0 += 8) {
+    for (int s0 = 0; s0 < n_splits; s0 += 8) {
         floatx4 ov[8];
         float mv[8], lv[8];
 #pragma unroll
@@ -669,10 +676,10 @@ __global__ __launch_bounds__(256) void tree_attn_direct_merge_kernel(AttnParams 
             ov[u] = floatx4{0.f, 0.f, 0.f, 0.f};
             mv[u] = -INFINITY;
             lv[u] = 0.f;
-            if (s0 + u < p.n_splits) {
-                const size_t i = base + static_cast<size_t>(s0 + u) * p.R_pad;
-                mv[u] = p.ws_ml[2 * i];
-                lv[u] = p.ws_ml[2 * i + 1];
+            if (s0 + u < n_splits) {
+                const size_t i = base + static_cast<size_t>(s0 + u) * R_pad;
+                mv[u] = ws_ml[2 * i];
+                lv[u] = ws_ml[2 * i + 1];
                 ov[u] = *reinterpret_cast<const floatx4*>(ws_o + i * D + 4 * d4);
             }
         }
@@ -790,8 +797,8 @@ static int32_t launch_one(const DirectPlan& pl, const AttnParams& p, int32_t dty
         part.prefix_len = p.prefix_len + b;
         part.n_nodes = p.n_nodes + b;
         part.mask = p.mask + b * p.K_max * GRAFT_MASK_WORDS;
-        launch_main(kernel, dim3(xcd_grid(static_cast<int64_t>(part.B) * p.Hkv * pl.n_splits, pl.n_row_tiles)), dim3(DR_THREADS), lds, s,
-                    part, pl.rg);
+        launch_attn(kernel, dim3(xcd_grid(static_cast<int64_t>(part.B) * p.Hkv * pl.n_splits, pl.n_row_tiles)), dim3(DR_THREADS), lds, s,
+                    part, pl.rg, DR_WAVES / pl.rg);
         const int32_t rc = check_launch();
         if (rc != GRAFT_OK) return rc;
     }
@@ -799,7 +806,7 @@ static int32_t launch_one(const DirectPlan& pl, const AttnParams& p, int32_t dty
     // (keys are split only while the chip is not full: one piece, few rows)
     const int64_t n_rows = static_cast<int64_t>(p.B) * p.Hkv * p.R;
     hipLaunchKernelGGL((tree_attn_direct_merge_kernel<T, D>), dim3(static_cast<unsigned>((n_rows * (D / 4) + 255) / 256)), dim3(256), 0, s,
-                       p, static_cast<int32_t>(n_rows));
+                       p.ws_o, p.ws_ml, p.n_nodes, static_cast<int32_t>(n_rows), p.R, p.R_pad, p.n_splits, p.Hkv, p);
     return check_launch();
 }
 
