@@ -27,9 +27,12 @@
 // 224 -> 202).  The next tile's loads are issued as soon as the registers of the current one have gone to
 // LDS.
 //
-// Latency: lengths -> page table -> first keys are three dependent trips; Q and the ancestor
-// masks travel with the lengths.  The table entries of a wavefront's tiles sit in one vector
-// register (lane = tile and page), one trip for 32 (fp32: 64) tiles.
+// Latency: lengths -> page table -> first keys would be three dependent trips.  The table entries of a wavefront's tiles
+// sit in one vector register (lane = tile and page, one trip for 32, fp32: 64, tiles) and are requested with the
+// lengths, for the tiles the wavefront has if keys are not split over workgroups or the sequence fills its table;
+// otherwise they are requested again.  Q and the ancestor masks follow and are not waited for.  With the pieces of the
+// merge through LDS read all at once: rounds of 16 layers with D = 64 288 -> 272 us, 8 layers in fp32 191 -> 188,
+// one small layer 18.1 -> 17.5.
 #include <type_traits>
 
 #include "attn_shared.h"
@@ -59,6 +62,13 @@ __device__ __forceinline__ float rows_sum_f32(float v) {
         v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
     }
     return v;
+}
+
+// Workgroup barrier that orders LDS traffic only: keys and values on their way stay in flight.
+__device__ __forceinline__ void lds_only_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // Per storage type: tile shape, LDS layout, the two products.
@@ -332,6 +342,16 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
     const int n_lane = n_nodes[b_lane], P_lane = prefix_len[b_lane];
     await_setup_args(p);
     if (padding) return;
+    constexpr int PAGES = TK / GRAFT_PAGE_SIZE, TPR = 64 / PAGES;              // pages per tile, tiles per table register
+    // The page table is requested before the lengths are known, for the tiles this wavefront has if the sequence fills
+    // its table (with keys that are not split over workgroups: whatever its length).  Lane = ordinal of the tile, page.
+    const int32_t* table = p.block_table + static_cast<size_t>(b) * p.max_pages;
+    const int per_full = div31((p.max_pages + PAGES - 1) / PAGES + n_splits - 1, splits_magic);
+    int tb = 0;
+    {
+        const int pg = (split * per_full + kgi + kg * (lane / PAGES)) * PAGES + lane % PAGES;
+        tb = table[pg < p.max_pages ? pg : p.max_pages - 1];
+    }
     const int r_base = (rt * rg + rgi) * (16 * MB);
     typename Ops::Q q[MB];
     uintx4 mw[MB];                              // ancestor mask of the row's node
@@ -348,13 +368,10 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
             mw[rb] = *reinterpret_cast<const uintx4*>(p.mask + (static_cast<size_t>(b) * p.K_max + node[rb]) * GRAFT_MASK_WORDS);
     }
 
-    const uintx4* mask_lds = reinterpret_cast<const uintx4*>(lds);
+    unsigned mask_word = 0;
     if constexpr (!MASK_HELD) {
         static_assert(GRAFT_MAX_NODES * 4 <= DR_THREADS, "one mask word per thread");
-        if (tid < p.K_max * 4)
-            reinterpret_cast<unsigned*>(lds)[tid] =
-                reinterpret_cast<const unsigned*>(p.mask + static_cast<size_t>(b) * p.K_max * GRAFT_MASK_WORDS)[tid];
-        __syncthreads();
+        if (tid < p.K_max * 4) mask_word = reinterpret_cast<const unsigned*>(p.mask + static_cast<size_t>(b) * p.K_max * GRAFT_MASK_WORDS)[tid];
     }
 
     __builtin_amdgcn_sched_barrier(0);
@@ -389,195 +406,215 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
     };
     clear_rows();
 
-    if (count > 0) {
-        constexpr int PAGES = TK / GRAFT_PAGE_SIZE, TPR = 64 / PAGES;      // pages per tile, tiles per table register
-        const int last = total - 1, last_pg = last >> 4;
-        const int32_t* table = p.block_table + static_cast<size_t>(b) * p.max_pages;
-        const char* kc = static_cast<const char*>(p.k) + static_cast<int64_t>(g) * p.head_stride * sizeof(T);
-        const char* vc = static_cast<const char*>(p.v) + static_cast<int64_t>(g) * p.head_stride * sizeof(T);
-        const unsigned ts = static_cast<unsigned>(p.token_stride) * sizeof(T);   // bytes
-        int tb = 0;
-        // Tiles in the order they are taken: the wavefront's last one first, so that the one tile of
-        // the sequence that can reach past its end is only ever the first of a wavefront.  Loads
-        // inside the loop then need no branch; with one, the compiler no longer knows how many
-        // transfers are in flight and waits for most of what it has just requested.
-        auto tile_at = [&](int it) __attribute__((always_inline)) { return first + kg * (it == 0 ? count - 1 : it - 1); };
-        auto load_table = [&](int it) __attribute__((always_inline)) {
-            const int pg = tile_at(it + lane / PAGES) * PAGES + lane % PAGES;
-            tb = table[pg < last_pg ? pg : last_pg];
-        };
-        // (the wavefront-uniform part of an address is scalar, the lane's part loop-invariant)
-        auto page_base = [&](int it, int c) __attribute__((always_inline)) {
-            return static_cast<int64_t>(__builtin_amdgcn_readlane(tb, (it & (TPR - 1)) * PAGES + c)) * p.page_stride * static_cast<int64_t>(sizeof(T));
-        };
-        const unsigned k_lane = 16 * (lane % Keys::CPR), k_off = lane / Keys::CPR * ts + k_lane;
-        const unsigned v_lane = Ops::v_lane(lane), v_off = (Ops::v_row(lane, 0) - Ops::v_row0(0)) * ts + v_lane;
-        auto load_keys = [&](Keys& t, int it) __attribute__((always_inline)) {
-            unsigned off = k_off;
-            asm volatile("" : "+v"(off));                         // (kept apart from the scalar base: no 64-bit vector additions)
+    const int last = total - 1, last_pg = last >> 4;
+    const char* kc = static_cast<const char*>(p.k) + static_cast<int64_t>(g) * p.head_stride * sizeof(T);
+    const char* vc = static_cast<const char*>(p.v) + static_cast<int64_t>(g) * p.head_stride * sizeof(T);
+    const unsigned ts = static_cast<unsigned>(p.token_stride) * sizeof(T);   // bytes
+    // Tiles in the order they are taken: the wavefront's last one first, so that the one tile of
+    // the sequence that can reach past its end is only ever the first of a wavefront.  Loads
+    // inside the loop then need no branch; with one, the compiler no longer knows how many
+    // transfers are in flight and waits for most of what it has just requested.
+    auto tile_at = [&](int it) __attribute__((always_inline)) { return first + kg * (it == 0 ? count - 1 : it - 1); };
+    // (entries of the tiles it, it + 1, ...)
+    auto load_table = [&](int it) __attribute__((always_inline)) {
+        const int pg = tile_at(it + lane / PAGES) * PAGES + lane % PAGES;
+        tb = table[pg < last_pg ? pg : last_pg];
+    };
+    // what was requested in front of the lengths serves if all tiles are in it and it began with the right one
+    const bool in_order = count <= TPR && (n_splits == 1 || per_split == per_full);
+    if (in_order) {
+        if constexpr (PAGES > 1) {                                // a page past the last one repeats it
+            const int tile = tile_at(0), over = last_pg - tile * PAGES;
+            const int at = (count - 1) * PAGES + (over < PAGES - 1 ? over : PAGES - 1);
+            const int entry = __builtin_amdgcn_readlane(tb, at & 63);
+            tb = lane > at ? entry : tb;
+        }
+    } else if (count > 0) {
+        load_table(0);
+        asm volatile("" : "+v"(tb));                              // (waited for here: behind the join it would be for everything requested)
+    }
+    auto table_slot = [&](int it) __attribute__((always_inline)) {
+        return in_order ? (it == 0 ? count - 1 : it - 1) & (TPR - 1) : it & (TPR - 1);
+    };
+    // (the wavefront-uniform part of an address is scalar, the lane's part loop-invariant)
+    auto page_base = [&](int it, int c) __attribute__((always_inline)) {
+        return static_cast<int64_t>(__builtin_amdgcn_readlane(tb, table_slot(it) * PAGES + c)) * p.page_stride * static_cast<int64_t>(sizeof(T));
+    };
+    const unsigned k_lane = 16 * (lane % Keys::CPR), k_off = lane / Keys::CPR * ts + k_lane;
+    const unsigned v_lane = Ops::v_lane(lane), v_off = (Ops::v_row(lane, 0) - Ops::v_row0(0)) * ts + v_lane;
+    auto load_keys = [&](Keys& t, int it) __attribute__((always_inline)) {
+        unsigned off = k_off;
+        asm volatile("" : "+v"(off));                         // (kept apart from the scalar base: no 64-bit vector additions)
 #pragma unroll
-            for (int j = 0; j < Keys::N; ++j)
-                t.r[j] = *reinterpret_cast<const uintx4*>(kc + page_base(it, Keys::page(j)) + static_cast<int64_t>(Keys::row0(j)) * ts + off);
-        };
-        auto load_values = [&](Values& t, int it) __attribute__((always_inline)) {
-            unsigned off = v_off;
-            asm volatile("" : "+v"(off));
+        for (int j = 0; j < Keys::N; ++j)
+            t.r[j] = *reinterpret_cast<const uintx4*>(kc + page_base(it, Keys::page(j)) + static_cast<int64_t>(Keys::row0(j)) * ts + off);
+    };
+    auto load_values = [&](Values& t, int it) __attribute__((always_inline)) {
+        unsigned off = v_off;
+        asm volatile("" : "+v"(off));
 #pragma unroll
-            for (int j = 0; j < Ops::NV; ++j)
-                Ops::load_v(t, j, vc + page_base(it, Ops::v_page(j)) + static_cast<int64_t>(Ops::v_row0(j)) * ts, off);
-        };
-        // a tile that may reach past the end: keys past the last token read the last token again
-        // (its probability there is zero)
-        auto row_off = [&](int it, int page, int k) __attribute__((always_inline)) {
-            const int t_page = tile_at(it) * TK + 16 * page;
-            const int lim = last - (t_page < last ? t_page : (last & ~15));
-            return static_cast<unsigned>(k < lim ? k : lim) * ts;
-        };
-        auto load_clamped = [&](Keys& kt, Values& vt, int it) __attribute__((always_inline)) {
+        for (int j = 0; j < Ops::NV; ++j)
+            Ops::load_v(t, j, vc + page_base(it, Ops::v_page(j)) + static_cast<int64_t>(Ops::v_row0(j)) * ts, off);
+    };
+    // a tile that may reach past the end: keys past the last token read the last token again
+    // (its probability there is zero)
+    auto row_off = [&](int it, int page, int k) __attribute__((always_inline)) {
+        const int t_page = tile_at(it) * TK + 16 * page;
+        const int lim = last - (t_page < last ? t_page : (last & ~15));
+        return static_cast<unsigned>(k < lim ? k : lim) * ts;
+    };
+    auto load_clamped = [&](Keys& kt, Values& vt, int it) __attribute__((always_inline)) {
 #pragma unroll
-            for (int j = 0; j < Keys::N; ++j)
-                kt.r[j] = *reinterpret_cast<const uintx4*>(kc + page_base(it, Keys::page(j)) +
-                                                           (row_off(it, Keys::page(j), Keys::row0(j) + lane / Keys::CPR) + k_lane));
+        for (int j = 0; j < Keys::N; ++j)
+            kt.r[j] = *reinterpret_cast<const uintx4*>(kc + page_base(it, Keys::page(j)) +
+                                                       (row_off(it, Keys::page(j), Keys::row0(j) + lane / Keys::CPR) + k_lane));
 #pragma unroll
-            for (int j = 0; j < Ops::NV; ++j)
-                Ops::load_v(vt, j, vc + page_base(it, Ops::v_page(j)), row_off(it, Ops::v_page(j), Ops::v_row(lane, j)) + v_lane);
-        };
-        unsigned char* const Ks = pieces + wave * STAGE;
-        unsigned char* const Vs = Ks + TK * ROW;
-        const float sc = p.scale_log2e;
-        // One tile: through LDS where it has to be turned, the next one requested behind it.
-        Keys kt;
-        Values vt;
-        auto step = [&](int it, auto more_, auto careful_) __attribute__((always_inline)) {
-            constexpr bool more = decltype(more_)::value, careful = decltype(careful_)::value;
-            kt.stage(Ks, lane);
-            asm volatile("" ::: "memory");                        // (lanes read each other's rows: no read moves in front of a write.
-                                                                  // Behind the next loads instead, it costs fp32 2 %.)
-            if constexpr (more) load_keys(kt, it + 1);
-            const int t0 = tile_at(it) * TK;
-            const bool masked = t0 + TK > P;
-            floatx4 s[MB][NC];
-            Ops::template scores<MB>(Ks, q, s, l16, lg);
-            unsigned odd = 0;                                     // keys with an infinite or NaN value
-            if constexpr (careful) {
-                odd = Ops::nonfinite_keys(vt, lane);
+        for (int j = 0; j < Ops::NV; ++j)
+            Ops::load_v(vt, j, vc + page_base(it, Ops::v_page(j)), row_off(it, Ops::v_page(j), Ops::v_row(lane, j)) + v_lane);
+    };
+    unsigned char* const Ks = pieces + wave * STAGE;
+    unsigned char* const Vs = Ks + TK * ROW;
+    const float sc = p.scale_log2e;
+    Keys kt;
+    Values vt;
+    if (count > 0) load_clamped(kt, vt, 0);
+    const uintx4* mask_lds = reinterpret_cast<const uintx4*>(lds);
+    if constexpr (!MASK_HELD) {                                   // (behind the first keys' request)
+        if (tid < p.K_max * 4) reinterpret_cast<unsigned*>(lds)[tid] = mask_word;
+        lds_only_barrier();
+    }
+    // One tile: through LDS where it has to be turned, the next one requested behind it.
+    auto step = [&](int it, auto more_, auto careful_) __attribute__((always_inline)) {
+        constexpr bool more = decltype(more_)::value, careful = decltype(careful_)::value;
+        kt.stage(Ks, lane);
+        asm volatile("" ::: "memory");                        // (lanes read each other's rows: no read moves in front of a write.
+                                                              // Behind the next loads instead, it costs fp32 2 %.)
+        if constexpr (more) load_keys(kt, it + 1);
+        const int t0 = tile_at(it) * TK;
+        const bool masked = t0 + TK > P;
+        floatx4 s[MB][NC];
+        Ops::template scores<MB>(Ks, q, s, l16, lg);
+        unsigned odd = 0;                                     // keys with an infinite or NaN value
+        if constexpr (careful) {
+            odd = Ops::nonfinite_keys(vt, lane);
 #pragma unroll
-                for (int x = 32; x >= 1; x >>= 1) odd |= __shfl_xor(odd, x);
-                odd = __builtin_amdgcn_readfirstlane(odd);
-            }
-            if constexpr (Ops::V_STAGED) {
-                Ops::stage_v(vt, Vs, lane);
-                if constexpr (more) load_values(vt, it + 1);
-            }
-            if (__builtin_expect(masked, 0)) {
-#pragma unroll
-                for (int rb = 0; rb < MB; ++rb) {
-                    const uintx4 words = MASK_HELD ? mw[rb] : mask_lds[node[rb]];
-                    const unsigned win = visible_window(t0 - P, total - P, [&](int k) {
-                        return k == 0 ? words[0] : (k == 1 ? words[1] : (k == 2 ? words[2] : words[3]));
-                    }) >> (4 * lg);
-#pragma unroll
-                    for (int c = 0; c < NC; ++c)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) s[rb][c][i] = keep_visible(s[rb][c][i], win, 16 * c + i);
-                }
-            }
-            float mx[MB];
-            bool raise = false;
-#pragma unroll
-            for (int rb = 0; rb < MB; ++rb) {
-                float x = fmaxf(fmaxf(s[rb][0][0], s[rb][0][1]), fmaxf(s[rb][0][2], s[rb][0][3]));
-                if constexpr (NC == 2)
-                    x = fmaxf(x, fmaxf(fmaxf(s[rb][1][0], s[rb][1][1]), fmaxf(s[rb][1][2], s[rb][1][3])));
-                mx[rb] = x * sc;
-                raise = raise || mx[rb] > m[rb] + (careful ? 0.f : DR_LAZY_LOG2);
-            }
-            // (rare) a row without a reference, or one that outgrew it: raise it to the maximum seen
-            if (__builtin_expect(__builtin_amdgcn_ballot_w64(raise) != 0, 0)) {
-#pragma unroll
-                for (int rb = 0; rb < MB; ++rb) {
-                    const float mn = fmaxf(m[rb], rows_max_f32(mx[rb]));
-                    const float a = mn == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m[rb] - mn);
-                    m[rb] = mn;
-                    l[rb] *= a;
-                    if constexpr (Ops::SUM_MFMA) lv[rb] *= a;
-#pragma unroll
-                    for (int e = 0; e < NO; ++e) o[rb][e] *= a;
-                }
-            }
+            for (int x = 32; x >= 1; x >>= 1) odd |= __shfl_xor(odd, x);
+            odd = __builtin_amdgcn_readfirstlane(odd);
+        }
+        if constexpr (Ops::V_STAGED) {
+            Ops::stage_v(vt, Vs, lane);
+            if constexpr (more) load_values(vt, it + 1);
+        }
+        if (__builtin_expect(masked, 0)) {
 #pragma unroll
             for (int rb = 0; rb < MB; ++rb) {
-                const float neg = m[rb] == -INFINITY ? 0.f : -m[rb];
-                float sum = 0.f;
+                const uintx4 words = MASK_HELD ? mw[rb] : mask_lds[node[rb]];
+                const unsigned win = visible_window(t0 - P, total - P, [&](int k) {
+                    return k == 0 ? words[0] : (k == 1 ? words[1] : (k == 2 ? words[2] : words[3]));
+                }) >> (4 * lg);
 #pragma unroll
                 for (int c = 0; c < NC; ++c)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        s[rb][c][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[rb][c][i], sc, neg));
-                        if constexpr (!Ops::SUM_MFMA) sum += s[rb][c][i];
-                    }
-                l[rb] += sum;
+                    for (int i = 0; i < 4; ++i) s[rb][c][i] = keep_visible(s[rb][c][i], win, 16 * c + i);
             }
-            // the values of such a key leave the product and are added to the rows that see it
-            for (unsigned left = odd; careful && left != 0; left &= left - 1) {
-                const int key = __builtin_ctz(left), page = key >> 4, at = (key >> 4) * 4 + (key & 3);
-                Ops::clear_key(vt, Vs, key, lane);
-                const char* vrow = vc + page_base(it, page) + row_off(it, page, key & 15);
-#pragma unroll
-                for (int rb = 0; rb < MB; ++rb) {
-                    float pk = s[rb][0][0];
-#pragma unroll
-                    for (int c = 0; c < NC; ++c)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) pk = at == 4 * c + i ? s[rb][c][i] : pk;
-                    pk = __shfl(pk, 16 * ((key >> 2) & 3) + l16);
-#pragma unroll
-                    for (int u = 0; u < D / 16; ++u) {
-                        if (pk != 0.f) Ops::add_piece(o[rb], u, Ops::load_dims(vrow + Ops::dim(u, lg) * sizeof(T)) * pk);
-                        asm volatile("" ::: "memory");            // (one load at a time: registers are short here)
-                    }
-                }
-            }
-            asm volatile("" ::: "memory");                        // (the transpose reads stay behind the writes above)
-            Ops::template accumulate<MB>(vt, Vs, s, o, lv, l16, lg);
-            if constexpr (more && !Ops::V_STAGED) load_values(vt, it + 1);
-        };
-        // chunks of the tiles that one table register covers
-        for (int it = 0; it < count;) {
-            const int end = it + TPR < count ? it + TPR : count;
-            load_table(it);
-            load_clamped(kt, vt, it);
-            for (; it + 1 < end; ++it) step(it, std::true_type{}, std::false_type{});
-            step(it, std::false_type{}, std::false_type{});
-            it = end;
         }
-        // ALONE: an infinite or NaN value in a tree slot makes the product NaN in the rows that do not see the slot as
-        // well (0 * inf), and values past 2^112 can overflow against a lazy reference.  Such a wavefront, if there
-        // ever is one, takes its tiles once more, with the values of such keys kept out of the product and the exact
-        // running maximum.  (The same looked for in every step: 2 % on two row blocks with D = 64.)
-        if constexpr (Ops::ALONE) {
-            bool odd = false;
+        float mx[MB];
+        bool raise = false;
+#pragma unroll
+        for (int rb = 0; rb < MB; ++rb) {
+            float x = fmaxf(fmaxf(s[rb][0][0], s[rb][0][1]), fmaxf(s[rb][0][2], s[rb][0][3]));
+            if constexpr (NC == 2)
+                x = fmaxf(x, fmaxf(fmaxf(s[rb][1][0], s[rb][1][1]), fmaxf(s[rb][1][2], s[rb][1][3])));
+            mx[rb] = x * sc;
+            raise = raise || mx[rb] > m[rb] + (careful ? 0.f : DR_LAZY_LOG2);
+        }
+        // (rare) a row without a reference, or one that outgrew it: raise it to the maximum seen
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(raise) != 0, 0)) {
 #pragma unroll
             for (int rb = 0; rb < MB; ++rb) {
-                float t = 0.f;                                    // two sums per instruction, NaN is kept
+                const float mn = fmaxf(m[rb], rows_max_f32(mx[rb]));
+                const float a = mn == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m[rb] - mn);
+                m[rb] = mn;
+                l[rb] *= a;
+                if constexpr (Ops::SUM_MFMA) lv[rb] *= a;
 #pragma unroll
-                for (int e = 0; e < NO; ++e)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) t = __builtin_elementwise_maximum(t, __builtin_fabsf(o[rb][e][i]));
-                odd = odd || (!(t < INFINITY) && node[rb] < n);   // (queries of absent nodes may be anything)
-            }
-            if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd) != 0, 0)) {
-                clear_rows();
-                for (int it = 0; it < count; ++it) {
-                    if (it % TPR == 0) load_table(it);
-                    load_clamped(kt, vt, it);
-                    step(it, std::false_type{}, std::true_type{});
-                }
+                for (int e = 0; e < NO; ++e) o[rb][e] *= a;
             }
         }
 #pragma unroll
-        for (int rb = 0; rb < MB; ++rb) l[rb] = Ops::SUM_MFMA ? lv[rb][0] : rows_sum_f32(l[rb]);
+        for (int rb = 0; rb < MB; ++rb) {
+            const float neg = m[rb] == -INFINITY ? 0.f : -m[rb];
+            float sum = 0.f;
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    s[rb][c][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[rb][c][i], sc, neg));
+                    if constexpr (!Ops::SUM_MFMA) sum += s[rb][c][i];
+                }
+            l[rb] += sum;
+        }
+        // the values of such a key leave the product and are added to the rows that see it
+        for (unsigned left = odd; careful && left != 0; left &= left - 1) {
+            const int key = __builtin_ctz(left), page = key >> 4, at = (key >> 4) * 4 + (key & 3);
+            Ops::clear_key(vt, Vs, key, lane);
+            const char* vrow = vc + page_base(it, page) + row_off(it, page, key & 15);
+#pragma unroll
+            for (int rb = 0; rb < MB; ++rb) {
+                float pk = s[rb][0][0];
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) pk = at == 4 * c + i ? s[rb][c][i] : pk;
+                pk = __shfl(pk, 16 * ((key >> 2) & 3) + l16);
+#pragma unroll
+                for (int u = 0; u < D / 16; ++u) {
+                    if (pk != 0.f) Ops::add_piece(o[rb], u, Ops::load_dims(vrow + Ops::dim(u, lg) * sizeof(T)) * pk);
+                    asm volatile("" ::: "memory");            // (one load at a time: registers are short here)
+                }
+            }
+        }
+        asm volatile("" ::: "memory");                        // (the transpose reads stay behind the writes above)
+        Ops::template accumulate<MB>(vt, Vs, s, o, lv, l16, lg);
+        if constexpr (more && !Ops::V_STAGED) load_values(vt, it + 1);
+    };
+    // chunks of the tiles that one table register covers
+    for (int it = 0; it < count;) {
+        const int end = it + TPR < count ? it + TPR : count;
+        if (it > 0) {
+            load_table(it);
+            load_clamped(kt, vt, it);
+        }
+        for (; it + 1 < end; ++it) step(it, std::true_type{}, std::false_type{});
+        step(it, std::false_type{}, std::false_type{});
+        it = end;
     }
+    // ALONE: an infinite or NaN value in a tree slot makes the product NaN in the rows that do not see the slot as
+    // well (0 * inf), and values past 2^112 can overflow against a lazy reference.  Such a wavefront, if there
+    // ever is one, takes its tiles once more, with the values of such keys kept out of the product and the exact
+    // running maximum.  (The same looked for in every step: 2 % on two row blocks with D = 64.)
+    if constexpr (Ops::ALONE) {
+        bool odd = false;
+#pragma unroll
+        for (int rb = 0; rb < MB; ++rb) {
+            float t = 0.f;                                    // two sums per instruction, NaN is kept
+#pragma unroll
+            for (int e = 0; e < NO; ++e)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) t = __builtin_elementwise_maximum(t, __builtin_fabsf(o[rb][e][i]));
+            odd = odd || (!(t < INFINITY) && node[rb] < n);   // (queries of absent nodes may be anything)
+        }
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd) != 0, 0)) {
+            clear_rows();
+            for (int it = 0; it < count; ++it) {
+                if (!in_order && it % TPR == 0) load_table(it);
+                load_clamped(kt, vt, it);
+                step(it, std::false_type{}, std::true_type{});
+            }
+        }
+    }
+#pragma unroll
+    for (int rb = 0; rb < MB; ++rb) l[rb] = Ops::SUM_MFMA ? lv[rb][0] : rows_sum_f32(l[rb]);
 
     // ---- results: this workgroup's rows, merged over its key groups
     T* outp = static_cast<T*>(p.out);
@@ -624,34 +661,47 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
     }
     __syncthreads();
     const int rows = rg * 16 * MB;                                // of this workgroup
-    for (int x = tid; x < rows * (D / 4); x += DR_THREADS) {
-        const int lr = x / (D / 4), d4 = x % (D / 4);
-        float mm = -INFINITY;
-        for (int k = 0; k < kg; ++k) mm = fmaxf(mm, ml_lds[2 * (k * rows + lr)]);
-        float den = 0.f;
-        floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
-        for (int k = 0; k < kg; ++k) {
-            const float mk = ml_lds[2 * (k * rows + lr)];
-            const float f = mk == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mk - mm);
-            den += f * ml_lds[2 * (k * rows + lr) + 1];
-            acc += *reinterpret_cast<const floatx4*>(merge_lds + (k * rows + lr) * PITCH + 4 * d4) * f;
-        }
-        const int r = rt * rows + lr;
-        if (n_splits == 1) {
-            if (r < p.R) {
-                const int i = (r * p.g_magic) >> 16;
-                const bool keep = i < n && den > 0.f;
-                const floatx4 y = keep ? acc * (1.0f / den) : floatx4{0.f, 0.f, 0.f, 0.f};
-                store4(outp + ((static_cast<size_t>(b) * p.K_max + i) * p.Hq + g * p.G + (r - i * p.G)) * D + 4 * d4, y);
+    const auto merge = [&](auto kg_) __attribute__((always_inline)) {
+        constexpr int KG = decltype(kg_)::value;                  // (all reads of a piece in flight: one after the other they took 1 us)
+        for (int x = tid; x < rows * (D / 4); x += DR_THREADS) {
+            const int lr = x / (D / 4), d4 = x % (D / 4);
+            float2 ml[KG];
+            floatx4 part_o[KG];
+#pragma unroll
+            for (int k = 0; k < KG; ++k) ml[k] = *reinterpret_cast<const float2*>(ml_lds + 2 * (k * rows + lr));
+#pragma unroll
+            for (int k = 0; k < KG; ++k) part_o[k] = *reinterpret_cast<const floatx4*>(merge_lds + (k * rows + lr) * PITCH + 4 * d4);
+            float mm = -INFINITY;
+#pragma unroll
+            for (int k = 0; k < KG; ++k) mm = fmaxf(mm, ml[k].x);
+            float den = 0.f;
+            floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int k = 0; k < KG; ++k) {
+                const float f = ml[k].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[k].x - mm);
+                den += f * ml[k].y;
+                acc += part_o[k] * f;
             }
-        } else {
-            store4(ws_o + (part + r) * D + 4 * d4, acc);
-            if (d4 == 0) {
-                p.ws_ml[2 * (part + r)] = mm;
-                p.ws_ml[2 * (part + r) + 1] = den;
+            const int r = rt * rows + lr;
+            if (n_splits == 1) {
+                if (r < p.R) {
+                    const int i = (r * p.g_magic) >> 16;
+                    const bool keep = i < n && den > 0.f;
+                    const floatx4 y = keep ? acc * (1.0f / den) : floatx4{0.f, 0.f, 0.f, 0.f};
+                    store4(outp + ((static_cast<size_t>(b) * p.K_max + i) * p.Hq + g * p.G + (r - i * p.G)) * D + 4 * d4, y);
+                }
+            } else {
+                store4(ws_o + (part + r) * D + 4 * d4, acc);
+                if (d4 == 0) {
+                    p.ws_ml[2 * (part + r)] = mm;
+                    p.ws_ml[2 * (part + r) + 1] = den;
+                }
             }
         }
-    }
+    };
+    if (kg == 8) merge(std::integral_constant<int, 8>{});
+    else if (kg == 4) merge(std::integral_constant<int, 4>{});
+    else merge(std::integral_constant<int, 2>{});
 }
 
 // Merge of the splits: one thread per four dims of a row, the splits' pieces requested eight at a time.

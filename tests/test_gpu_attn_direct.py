@@ -229,6 +229,38 @@ def test_values_that_are_not_finite_stay_with_the_nodes_that_see_them(dtype, D, 
     assert (np.abs(g - c)[~odd] <= (1e-5 if dtype == "f32" else 2.0 ** -7) * (1 + np.abs(c[~odd]))).all()
 
 
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
+@pytest.mark.parametrize("P,pages,with_ws", [(0, 3, True), (9, 40, True), (300, 22, True), (600, 200, True), (1500, 98, False), (17000, 1100, False)])
+def test_entries_past_a_sequences_last_page_are_not_followed(dtype, D, P, pages, with_ws):
+    """Table entries are requested before the lengths are known.  Those behind a sequence's last page name a page of NaN
+    here: the rows are those of a table that repeats the last page, bit for bit.  Splits that begin elsewhere than in a
+    full table, wavefronts with more tiles than the request covers, an odd last page."""
+    B, K, H = 3, 20, 2
+    w = shape_workload(B, K, H, H, D, P, dtype=dtype)
+    att = inputs.make_attention_inputs(w, seed=P + 1)
+    n, p = np.array([K, 0, 7], np.int32), np.array([P, P, P // 2], np.int32)
+    used = att["block_table"].shape[1]
+    assert pages >= used
+    spare = np.setdiff1d(np.arange(len(att["k_cache"][0])), att["block_table"].ravel())
+    assert len(spare) > 0
+    caches = [dev(att[x][0], dtype).clone() for x in ("k_cache", "v_cache")]
+    for c in caches:
+        c[int(spare[0])] = float("nan")
+    mask = gpu_mask(np.arange(-1, K - 1, dtype=np.int32)[None].repeat(B, 0), n, p)
+    out = []
+    for poison in (False, True):
+        table = np.zeros((B, pages), np.int32)
+        table[:, :used] = att["block_table"]
+        for b in range(B):
+            last = (p[b] + n[b] - 1) // 16 if n[b] else -1
+            table[b, last + 1:] = spare[0] if poison else table[b, max(last, 0)]
+        out.append(graft.graft_tree_attn(dev(att["q"][0], dtype), *caches, att["strides"], dev(table), dev(p), dev(n), mask, H, att["scale"],
+                                         workspace=None if with_ws else torch.empty(0, dtype=torch.uint8, device="cuda")
+                                         if (dtype, D) != ("bf16", 128) else None))
+    assert torch.isfinite(out[0]).all()
+    assert torch.equal(out[0], out[1])
+
+
 @pytest.mark.parametrize("dtype,D,P,pages", [("bf16", 64, 170, 11), ("bf16", 64, 176, 11), ("bf16", 64, 200, 11), ("bf16", 128, 170, 11),
                                              ("bf16", 128, 8330, 521), ("f32", 64, 170, 11)])
 def test_tree_slots_past_the_block_table_do_not_count(dtype, D, P, pages):
