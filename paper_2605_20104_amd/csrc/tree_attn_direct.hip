@@ -41,6 +41,8 @@ namespace graft {
 
 constexpr int DR_WAVES = 8;                     // wavefronts per workgroup, two per SIMD
 constexpr int DR_THREADS = 64 * DR_WAVES;
+// Rows of a row block: 32 where a wavefront has that many and the products come in that size without a loss
+constexpr int row_block_rows(bool bf16, int D, int mb) { return bf16 && D == 64 && mb >= 2 ? 32 : 16; }
 constexpr float DR_LAZY_LOG2 = 16.0f;           // a row keeps its reference while exponents stay below 16
 constexpr int DR_MAX_SPLITS = 32;
 constexpr int DR_MASK_BYTES = 2048;             // ancestor masks of a sequence
@@ -50,18 +52,22 @@ __device__ __forceinline__ unsigned lds_offset(const void* p) {
     return static_cast<unsigned>(reinterpret_cast<size_t>((const __attribute__((address_space(3))) unsigned char*)(p)));
 }
 
-__device__ __forceinline__ float rows_sum_f32(float v) {
-    {
+// Sum / maximum over the lanes that hold the same row: lane, lane + 32 and, with 16 rows to a block, those 16 apart.
+template <int RB> __device__ __forceinline__ float row_sum(float v) {
+    if constexpr (RB == 16) {
         const unsigned u = __float_as_uint(v);
         const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
         v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
     }
-    {
-        const unsigned u = __float_as_uint(v);
-        const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-        v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-    return v;
+    const unsigned u = __float_as_uint(v);
+    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+template <int RB> __device__ __forceinline__ float row_max(float v) {
+    if constexpr (RB == 16) return rows_max_f32(v);
+    const unsigned u = __float_as_uint(v);
+    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __builtin_fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
 // Workgroup barrier that orders LDS traffic only: keys and values on their way stay in flight.
@@ -71,8 +77,18 @@ __device__ __forceinline__ void lds_only_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Per storage type: tile shape, LDS layout, the two products.
-template <typename T, int D> struct DirectOps;
+// A lane's scores of one row block: 4 T values, value v = t[v / 4][v % 4].
+template <int T> struct ScoreTiles {
+    static constexpr int N = 4 * T;
+    floatx4 t[T];
+    __device__ __forceinline__ float get(int v) const { return t[v >> 2][v & 3]; }
+    __device__ __forceinline__ void set(int v, float x) { t[v >> 2][v & 3] = x; }
+};
+
+constexpr bool shares_queries(bool f32, int D) { return f32 && D == 128; }
+
+// Per storage type, head size and rows of a row block (RB): tile shape, LDS layout, the two products.
+template <typename T, int D, int RB> struct DirectOps;
 
 // K of a tile on its way from memory to LDS: 1 KB of consecutive rows per instruction.
 template <int ROW, int TK> struct StagedKeys {
@@ -91,10 +107,14 @@ template <int ROW, int TK> struct StagedKeys {
     }
 };
 
-template <int D> struct DirectOps<float, D> {
+template <int D> struct DirectOps<float, D, 16> {
     static constexpr int TK = 16;               // keys per tile
-    static constexpr int NO = D / 16;           // floatx4 accumulators per row block
-    static constexpr int NC = 1;                // score tiles of 16 keys
+    using Acc = floatx4;
+    using Scores = ScoreTiles<1>;
+    static constexpr int NO = D / 16, NP = D / 16;                // accumulators per row block, pieces of four dims
+    static constexpr int key(int v) { return v; }                 // key of value v, apart from 4 (lane / RB)
+    static constexpr int value_of(int key) { return key & 3; }    // and back: value, lane group
+    static constexpr int group_of(int key) { return key >> 2 & 3; }
     static constexpr int ROW = D * 4;           // bytes
     static constexpr bool SUM_MFMA = false;
     static constexpr bool ALONE = true;         // values of any size: those of unseen slots do not reach a row even if they are not finite
@@ -103,8 +123,13 @@ template <int D> struct DirectOps<float, D> {
 #pragma unroll
         for (int s = 0; s < D / 16; ++s) q.v[s] = *reinterpret_cast<const floatx4*>(row + 16 * s + 4 * lg);
     }
+    // the same from LDS, where the chunks of row r are in the order chunk ^ (r & 7)
+    static __device__ __forceinline__ void read_q(Q& q, const unsigned char* Qs, int row, int lg) {
+#pragma unroll
+        for (int s = 0; s < D / 16; ++s) q.v[s] = *reinterpret_cast<const floatx4*>(Qs + row * ROW + (((4 * s + lg) ^ (row & 7)) * 16));
+    }
     template <int MB>
-    static __device__ __forceinline__ void scores(const unsigned char* Ks, const Q (&q)[MB], floatx4 (&s)[MB][NC], int l16, int lg) {
+    static __device__ __forceinline__ void scores(const unsigned char* Ks, const Q (&q)[MB], Scores (&s)[MB], int l16, int lg) {
         const unsigned char* row = Ks + l16 * ROW;
         const int x = ((lg ^ l16) & 3) * 16 + (l16 & 4) * 16;      // chunk (4 d + lg) ^ (l16 & 7): bits 0-1 and, for even d, bit 2
 #pragma unroll
@@ -114,7 +139,7 @@ template <int D> struct DirectOps<float, D> {
             for (int j = 0; j < 4; ++j)
 #pragma unroll
                 for (int rb = 0; rb < MB; ++rb)
-                    s[rb][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(k[j], q[rb].v[d][j], d == 0 && j == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : s[rb][0], 0, 0, 0);
+                    s[rb].t[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(k[j], q[rb].v[d][j], d == 0 && j == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : s[rb].t[0], 0, 0, 0);
         }
     }
     static constexpr bool V_STAGED = false;     // values come in operand layout already: 256 bytes of a row per 16 lanes
@@ -129,7 +154,7 @@ template <int D> struct DirectOps<float, D> {
         for (int h = 0; h < D / 64; ++h) t.r[j][h] = *reinterpret_cast<const floatx4*>(base + off + 256 * h);
     }
     template <int MB>
-    static __device__ __forceinline__ void accumulate(const V& t, const unsigned char*, const floatx4 (&p)[MB][NC], floatx4 (&o)[MB][NO],
+    static __device__ __forceinline__ void accumulate(const V& t, const unsigned char*, const Scores (&p)[MB], floatx4 (&o)[MB][NO],
                                                       floatx4 (&)[MB], int, int) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -139,7 +164,7 @@ template <int D> struct DirectOps<float, D> {
                 for (int j = 0; j < 4; ++j)
 #pragma unroll
                     for (int rb = 0; rb < MB; ++rb)
-                        o[rb][4 * h + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.r[i][h][j], p[rb][0][i], o[rb][4 * h + j], 0, 0, 0);
+                        o[rb][4 * h + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.r[i][h][j], p[rb].t[0][i], o[rb][4 * h + j], 0, 0, 0);
     }
     // keys of the tile with an infinite or NaN value among this lane's, as bits
     static __device__ __forceinline__ unsigned nonfinite_keys(const V& t, int lane) {
@@ -176,20 +201,14 @@ template <int D> struct DirectOps<float, D> {
     }
 };
 
-template <int D> struct DirectOps<__bf16, D> {
+// bf16: what does not depend on the rows of a block.
+template <int D> struct DirectOpsBf16 {
     static constexpr int TK = 32;
-    static constexpr int NO = D / 16;
-    static constexpr int NC = 2;
     static constexpr int ROW = D * 2;
     static constexpr int P_PARTS = D == 64 ? 3 : 1;     // bf16 numbers that make up a probability (D = 128: rounded to one)
     static constexpr bool SUM_MFMA = P_PARTS == 1;      // row sums of the rounded probabilities, through the matrix cores
     static constexpr bool ALONE = D == 64;      // (D = 128 asks for finite, ordinary values, as the path this stands in for does)
     static constexpr int SEG = ROW / 32 - 1;    // V rows: 32-byte segment ^ (row & SEG)
-    struct Q { bf16x8 v[D / 32]; };
-    static __device__ __forceinline__ void load_q(Q& q, const __bf16* row, int lg) {
-#pragma unroll
-        for (int s = 0; s < D / 32; ++s) q.v[s] = *reinterpret_cast<const bf16x8*>(row + 32 * s + 8 * lg);
-    }
     static constexpr bool V_STAGED = true;
     static constexpr int NV = TK * ROW / 1024, RPI = 1024 / ROW;       // instructions, rows per instruction
     struct V { uintx4 r[NV]; };
@@ -208,74 +227,6 @@ template <int D> struct DirectOps<__bf16, D> {
             const int row = j * RPI + lrow;
             *reinterpret_cast<uintx4*>(Vs + row * ROW + ((chunk ^ ((row & SEG) << 1)) * 16)) = t.r[j];
         }
-    }
-    template <int MB>
-    static __device__ __forceinline__ void scores(const unsigned char* Ks, const Q (&q)[MB], floatx4 (&s)[MB][NC], int l16, int lg) {
-        const unsigned char* row = Ks + l16 * ROW;
-        const int x = ((lg ^ l16) & 3) * 16 + (l16 & 4) * 16;
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-            for (int d = 0; d < D / 32; ++d) {
-                const bf16x8 k = *reinterpret_cast<const bf16x8*>(row + ((x ^ ((d & 1) * 64)) + (d >> 1) * 128 + c * 16 * ROW));
-#pragma unroll
-                for (int rb = 0; rb < MB; ++rb)
-                    s[rb][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k, q[rb].v[d], d == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : s[rb][c], 0, 0, 0);
-            }
-    }
-    template <int MB>
-    static __device__ __forceinline__ void accumulate(const V&, const unsigned char* Vs, const floatx4 (&p)[MB][NC], floatx4 (&o)[MB][NO],
-                                                      floatx4 (&sum)[MB], int l16, int lg) {
-        // rows 16 c + 4 lg + (l16 >> 2): the transpose read turns 4 keys x 16 dims into "lane = dim, 4 keys"
-        const int row0 = 4 * lg + (l16 >> 2);
-        const unsigned base = lds_offset(Vs) + row0 * ROW + ((row0 & SEG) << 5) + 8 * (l16 & 3);
-        bf16x8 a[NO];
-#pragma unroll
-        for (int e = 0; e < NO; ++e)
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                const short4_t r = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (short4_t __attribute__((address_space(3)))*)(static_cast<size_t>((base ^ (e << 5)) + c * 16 * ROW)));
-                const bf16x4 r4 = __builtin_bit_cast(bf16x4, r);
-                a[e][4 * c] = r4[0];
-                a[e][4 * c + 1] = r4[1];
-                a[e][4 * c + 2] = r4[2];
-                a[e][4 * c + 3] = r4[3];
-            }
-        // D = 64: p = part 0 + part 1 + part 2, each the leading 8 bits of what the ones before it leave.  Both
-        // differences are exact, so no bit of p is lost: its products with the bf16 values are those of fp32.  A part's
-        // MFMAs run while the next one is split off (four sequences of 2048 keys, 32 heads on 8: 15.5 us; 16.9 with
-        // all parts split off first and the row sums from the matrix cores, 14.8 with two parts, 17 bits of p).
-        floatx4 left[MB][NC];
-#pragma unroll
-        for (int rb = 0; rb < MB; ++rb)
-#pragma unroll
-            for (int c = 0; c < NC; ++c) left[rb][c] = p[rb][c];
-#pragma unroll
-        for (int t = 0; t < P_PARTS; ++t)
-#pragma unroll
-            for (int rb = 0; rb < MB; ++rb) {
-                uintx4 part;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const float p0 = left[rb][j >> 1][2 * (j & 1)], p1 = left[rb][j >> 1][2 * (j & 1) + 1];
-                    if constexpr (P_PARTS == 1) {
-                        part[j] = pack_bf16(p0, p1);
-                    } else {
-                        const unsigned b0 = __float_as_uint(p0), b1 = __float_as_uint(p1);
-                        part[j] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
-                        left[rb][j >> 1][2 * (j & 1)] = p0 - __uint_as_float(b0 & 0xffff0000u);
-                        left[rb][j >> 1][2 * (j & 1) + 1] = p1 - __uint_as_float(b1 & 0xffff0000u);
-                    }
-                }
-                const bf16x8 pp = __builtin_bit_cast(bf16x8, part);
-#pragma unroll
-                for (int e = 0; e < NO; ++e) o[rb][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[e], pp, o[rb][e], 0, 0, 0);
-                if constexpr (SUM_MFMA) {
-                    const bf16x8 ones = __builtin_bit_cast(bf16x8, uintx4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
-                    sum[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pp, sum[rb], 0, 0, 0);
-                }
-            }
     }
     static __device__ __forceinline__ unsigned nonfinite_keys(const V& t, int lane) {
         unsigned keys = 0;
@@ -299,9 +250,182 @@ template <int D> struct DirectOps<__bf16, D> {
         return floatx4{__uint_as_float(x[0] << 16), __uint_as_float(x[0] & 0xffff0000u), __uint_as_float(x[1] << 16),
                        __uint_as_float(x[1] & 0xffff0000u)};
     }
+    // What is left of a lane's probabilities and the next part of eight of them.  D = 64: p = part 0 + part 1 + part 2, each
+    // the leading 8 bits of what the ones before it leave.  Both differences are exact, so no bit of p is lost: its products
+    // with the bf16 values are those of fp32.  A part's MFMAs run while the next one is split off (four sequences of 2048
+    // keys, 32 heads on 8: 15.5 us; 16.9 with all parts split off first and the row sums from the matrix cores, 14.8 with two
+    // parts, 17 bits of p).
+    template <class S> static __device__ __forceinline__ bf16x8 take_part(S& left, int v0) {
+        uintx4 part;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float p0 = left.get(v0 + 2 * j), p1 = left.get(v0 + 2 * j + 1);
+            if constexpr (P_PARTS == 1) {
+                part[j] = pack_bf16(p0, p1);
+            } else {
+                const unsigned b0 = __float_as_uint(p0), b1 = __float_as_uint(p1);
+                part[j] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
+                left.set(v0 + 2 * j, p0 - __uint_as_float(b0 & 0xffff0000u));
+                left.set(v0 + 2 * j + 1, p1 - __uint_as_float(b1 & 0xffff0000u));
+            }
+        }
+        return __builtin_bit_cast(bf16x8, part);
+    }
+};
+
+// bf16, 16 rows to a block: 16x16x32 MFMAs
+template <int D> struct DirectOps<__bf16, D, 16> : DirectOpsBf16<D> {
+    using Base = DirectOpsBf16<D>;
+    using typename Base::V;
+    using Base::ROW, Base::P_PARTS, Base::SUM_MFMA, Base::SEG;
+    using Acc = floatx4;
+    using Scores = ScoreTiles<2>;
+    static constexpr int NO = D / 16, NP = D / 16;
+    static constexpr int key(int v) { return 16 * (v >> 2) + (v & 3); }
+    static constexpr int value_of(int key) { return (key >> 4) * 4 + (key & 3); }
+    static constexpr int group_of(int key) { return key >> 2 & 3; }
+    struct Q { bf16x8 v[D / 32]; };
+    static __device__ __forceinline__ void load_q(Q& q, const __bf16* row, int lg) {
+#pragma unroll
+        for (int s = 0; s < D / 32; ++s) q.v[s] = *reinterpret_cast<const bf16x8*>(row + 32 * s + 8 * lg);
+    }
+    template <int MB>
+    static __device__ __forceinline__ void scores(const unsigned char* Ks, const Q (&q)[MB], Scores (&s)[MB], int l16, int lg) {
+        const unsigned char* row = Ks + l16 * ROW;
+        const int x = ((lg ^ l16) & 3) * 16 + (l16 & 4) * 16;
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int d = 0; d < D / 32; ++d) {
+                const bf16x8 k = *reinterpret_cast<const bf16x8*>(row + ((x ^ ((d & 1) * 64)) + (d >> 1) * 128 + c * 16 * ROW));
+#pragma unroll
+                for (int rb = 0; rb < MB; ++rb)
+                    s[rb].t[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k, q[rb].v[d], d == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : s[rb].t[c], 0, 0, 0);
+            }
+    }
+    template <int MB>
+    static __device__ __forceinline__ void accumulate(const V&, const unsigned char* Vs, const Scores (&p)[MB], floatx4 (&o)[MB][NO],
+                                                      floatx4 (&sum)[MB], int l16, int lg) {
+        // rows 16 c + 4 lg + (l16 >> 2): the transpose read turns 4 keys x 16 dims into "lane = dim, 4 keys"
+        const int row0 = 4 * lg + (l16 >> 2);
+        const unsigned base = lds_offset(Vs) + row0 * ROW + ((row0 & SEG) << 5) + 8 * (l16 & 3);
+        bf16x8 a[NO];
+#pragma unroll
+        for (int e = 0; e < NO; ++e)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const short4_t r = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (short4_t __attribute__((address_space(3)))*)(static_cast<size_t>((base ^ (e << 5)) + c * 16 * ROW)));
+                const bf16x4 r4 = __builtin_bit_cast(bf16x4, r);
+                a[e][4 * c] = r4[0];
+                a[e][4 * c + 1] = r4[1];
+                a[e][4 * c + 2] = r4[2];
+                a[e][4 * c + 3] = r4[3];
+            }
+        Scores left[MB];
+#pragma unroll
+        for (int rb = 0; rb < MB; ++rb) left[rb] = p[rb];
+#pragma unroll
+        for (int t = 0; t < P_PARTS; ++t)
+#pragma unroll
+            for (int rb = 0; rb < MB; ++rb) {
+                const bf16x8 pp = Base::take_part(left[rb], 0);
+#pragma unroll
+                for (int e = 0; e < NO; ++e) o[rb][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[e], pp, o[rb][e], 0, 0, 0);
+                if constexpr (SUM_MFMA) {
+                    const bf16x8 ones = __builtin_bit_cast(bf16x8, uintx4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
+                    sum[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pp, sum[rb], 0, 0, 0);
+                }
+            }
+    }
     static __device__ __forceinline__ void add_piece(floatx4 (&o)[NO], int u, const floatx4& x) { o[u] += x; }
     static __device__ __forceinline__ int dim(int u, int lg) { return 16 * u + 4 * lg; }
     static __device__ __forceinline__ floatx4 piece(const floatx4 (&o)[NO], int u) { return o[u]; }
+};
+
+// bf16, 32 rows to a block: 32x32x16 MFMAs.  The kernel is bound by what a SIMD issues: a vector instruction takes 4 cycles, an
+// exp2 8 and an MFMA of either size 8 of the same slots (measured with two and three wavefronts a SIMD; what is left of the
+// MFMA's 16 or 32 cycles is free for others), so the larger ones cost half.  Four sequences of 2048 keys, 32 heads on 8: 15.3
+// -> 14.0 us a layer; 16 sequences of 1024: 25.0 -> 23.0.  A third wavefront per SIMD (12 a workgroup) gains nothing.
+// A: lane = key or dim (lane & 31), the 8 contraction indices of group lane / 32; B: lane = row; a result's value v is row
+// (key or dim) 8 (v / 4) + 4 (lane / 32) + v % 4, so values 8 kk .. 8 kk + 7 are the second product's B operand for the
+// 16 keys from 16 kk on, in the order in which the transpose read brings those of A.
+template <int D> struct DirectOps<__bf16, D, 32> : DirectOpsBf16<D> {
+    using Base = DirectOpsBf16<D>;
+    using typename Base::V;
+    using Base::ROW, Base::P_PARTS, Base::SEG;
+    static_assert(!Base::SUM_MFMA && SEG == 3, "head size 64");
+    using Acc = floatx16;
+    struct Scores {
+        static constexpr int N = 16;
+        floatx16 t;
+        __device__ __forceinline__ float get(int v) const { return t[v]; }
+        __device__ __forceinline__ void set(int v, float x) { t[v] = x; }
+    };
+    static constexpr int NO = D / 32, NP = D / 8;
+    static constexpr int key(int v) { return 8 * (v >> 2) + (v & 3); }
+    static constexpr int value_of(int key) { return (key >> 3) * 4 + (key & 3); }
+    static constexpr int group_of(int key) { return key >> 2 & 1; }
+    struct Q { bf16x8 v[D / 16]; };
+    static __device__ __forceinline__ void load_q(Q& q, const __bf16* row, int half) {
+#pragma unroll
+        for (int s = 0; s < D / 16; ++s) q.v[s] = *reinterpret_cast<const bf16x8*>(row + 16 * s + 8 * half);
+    }
+    template <int NB>
+    static __device__ __forceinline__ void scores(const unsigned char* Ks, const Q (&q)[NB], Scores (&s)[NB], int l32, int half) {
+        const unsigned char* row = Ks + l32 * ROW;
+        const int x = ((half ^ l32) & 7) * 16;                    // chunk (2 d + half) ^ (l32 & 7)
+#pragma unroll
+        for (int d = 0; d < D / 16; ++d) {
+            const bf16x8 k = *reinterpret_cast<const bf16x8*>(row + (x ^ (d * 32)));
+#pragma unroll
+            for (int rb = 0; rb < NB; ++rb) s[rb].t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k, q[rb].v[d], d == 0 ? floatx16{} : s[rb].t, 0, 0, 0);
+        }
+    }
+    template <int NB>
+    static __device__ __forceinline__ void accumulate(const V&, const unsigned char* Vs, const Scores (&p)[NB], floatx16 (&o)[NB][NO],
+                                                      floatx4 (&)[NB], int l32, int half) {
+        // keys 16 kk + 8 c + 4 half + .., dims 32 e + l32: a 16-lane group of the transpose read has 4 keys and 16 dims
+        const int l16 = l32 & 15, row0 = 4 * half + (l16 >> 2);
+        const unsigned base = lds_offset(Vs) + row0 * ROW + (((l32 >> 4) ^ (row0 & SEG)) << 5) + 8 * (l16 & 3);
+        bf16x8 a[NO][2];
+#pragma unroll
+        for (int e = 0; e < NO; ++e)
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const short4_t r = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                        (short4_t __attribute__((address_space(3)))*)(static_cast<size_t>((base ^ (e << 6)) + (16 * kk + 8 * c) * ROW)));
+                    const bf16x4 r4 = __builtin_bit_cast(bf16x4, r);
+                    a[e][kk][4 * c] = r4[0];
+                    a[e][kk][4 * c + 1] = r4[1];
+                    a[e][kk][4 * c + 2] = r4[2];
+                    a[e][kk][4 * c + 3] = r4[3];
+                }
+        Scores left[NB];
+#pragma unroll
+        for (int rb = 0; rb < NB; ++rb) left[rb] = p[rb];
+#pragma unroll
+        for (int t = 0; t < P_PARTS; ++t)
+#pragma unroll
+            for (int rb = 0; rb < NB; ++rb)
+#pragma unroll
+                for (int kk = 0; kk < 2; ++kk) {
+                    const bf16x8 pp = Base::take_part(left[rb], 8 * kk);
+#pragma unroll
+                    for (int e = 0; e < NO; ++e) o[rb][e] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[e][kk], pp, o[rb][e], 0, 0, 0);
+                }
+    }
+    static __device__ __forceinline__ void add_piece(floatx16 (&o)[NO], int u, const floatx4& x) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[u >> 2][4 * (u & 3) + i] += x[i];
+    }
+    static __device__ __forceinline__ int dim(int u, int half) { return 8 * u + 4 * half; }
+    static __device__ __forceinline__ floatx4 piece(const floatx16 (&o)[NO], int u) {
+        const int at = 4 * (u & 3);
+        return floatx4{o[u >> 2][at], o[u >> 2][at + 1], o[u >> 2][at + 2], o[u >> 2][at + 3]};
+    }
 };
 
 __device__ __forceinline__ void store4(float* p, const floatx4& v) { *reinterpret_cast<floatx4*>(p) = v; }
@@ -313,22 +437,28 @@ __device__ __forceinline__ void store4(__bf16* p, const floatx4& v) {
 // with D = 64 leaves room for a second workgroup on the compute unit.
 template <typename T, int D, int MB>
 __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_direct_kernel(GRAFT_ATTN_ARGS) {
-    using Ops = DirectOps<T, D>;
-    constexpr int TK = Ops::TK, NO = Ops::NO, NC = Ops::NC, ROW = Ops::ROW;
+    constexpr int RB = row_block_rows(std::is_same_v<T, __bf16>, D, MB), NB = MB * 16 / RB;       // rows of a row block, row blocks
+    using Ops = DirectOps<T, D, RB>;
+    constexpr int TK = Ops::TK, NO = Ops::NO, NP = Ops::NP, NS = Ops::Scores::N, ROW = Ops::ROW;
     using Keys = StagedKeys<ROW, TK>;
     using Values = typename Ops::V;
     constexpr int STAGE = TK * ROW * (Ops::V_STAGED ? 2 : 1);   // a wavefront's piece of LDS: K, then V
     constexpr int PITCH = D + 4;                // LDS row pitch of the merge: 16 rows at consecutive 16-byte slots
-    constexpr bool MASK_HELD = MB * D < 256;        // the rows' ancestor masks in registers, else in LDS
-    // the wavefronts' pieces; after the loop, with more than one key group, [wave][16 MB][PITCH]
-    // partial rows and (m, l) [wave][16 MB].  In front of it the ancestor masks, if they are held here.
+    // fp32 with D = 128: the wavefronts of a row group request a share of its queries each and exchange them through LDS.  All
+    // of them asking for all 8 KB kept the compute unit's address path busy for a microsecond in front of the first keys
+    // (21.4 -> 20.9 us with 2K keys); with less to ask for, the barrier costs as much or more (D = 64: bf16 14.0 -> 14.4, fp32
+    // 11.3 -> 11.6).  One key group has nothing to share.
+    constexpr bool SHARE_Q = shares_queries(std::is_same_v<T, float>, D);
+    constexpr bool MASK_HELD = MB * D < 256 && !SHARE_Q;          // the rows' ancestor masks in registers, else in LDS
+    // the wavefronts' pieces (and the queries that are shared); after the loop, with more than one key group,
+    // [wave][16 MB][PITCH] partial rows and (m, l) [wave][16 MB].  In front of it the ancestor masks, if they are held here.
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     unsigned char* const pieces = lds + (MASK_HELD ? 0 : DR_MASK_BYTES);
     float* const merge_lds = reinterpret_cast<float*>(pieces);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l16 = lane & 15, lg = lane >> 4;
+    const int lr = lane % RB, lg = lane / RB;                     // row in a block, group of lanes
     const int rg = row_groups, kg = key_groups;
     const int kgi = div31(wave, row_groups_magic), rgi = wave - kgi * rg;
     const WorkItem item = xcd_work_item(n_units, n_row_tiles, row_tiles_magic);
@@ -353,17 +483,29 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
         tb = table[pg < p.max_pages ? pg : p.max_pages - 1];
     }
     const int r_base = (rt * rg + rgi) * (16 * MB);
-    typename Ops::Q q[MB];
-    uintx4 mw[MB];                              // ancestor mask of the row's node
-    int node[MB];
+    const auto query = [&](int r) __attribute__((always_inline)) {             // rows past R read row 0
+        const int rc = r < p.R ? r : 0, i = (rc * p.g_magic) >> 16;
+        return static_cast<const T*>(p.q) + ((static_cast<size_t>(b) * p.K_max + i) * p.Hq + (g * p.G + (rc - i * p.G))) * D;
+    };
+    constexpr int QN = SHARE_Q ? 16 * MB * ROW / 1024 : 2, QR = 1024 / ROW, CPR = ROW / 16;      // 1 KB pieces, rows of one, chunks of a row
+    uintx4 q_share[QN / 2];
+    typename Ops::Q q[NB];
+    uintx4 mw[NB];                              // ancestor mask of the row's node
+    int node[NB];
+    if (SHARE_Q && kg > 1) {
 #pragma unroll
-    for (int rb = 0; rb < MB; ++rb) {
-        const int r = r_base + rb * 16 + l16;
-        const int rc = r < p.R ? r : 0;
-        node[rb] = (rc * p.g_magic) >> 16;
-        const int hl = rc - node[rb] * p.G;
-        Ops::load_q(q[rb], static_cast<const T*>(p.q) +
-                    ((static_cast<size_t>(b) * p.K_max + node[rb]) * p.Hq + (g * p.G + hl)) * D, lg);
+        for (int u = 0; u < QN / 2; ++u) {
+            const int j = kgi + u * kg;
+            if (j < QN) q_share[u] = reinterpret_cast<const uintx4*>(query(r_base + j * QR + lane / CPR))[lane % CPR];
+        }
+    } else {
+#pragma unroll
+        for (int rb = 0; rb < NB; ++rb) Ops::load_q(q[rb], query(r_base + rb * RB + lr), lg);
+    }
+#pragma unroll
+    for (int rb = 0; rb < NB; ++rb) {
+        const int r = r_base + rb * RB + lr;
+        node[rb] = ((r < p.R ? r : 0) * p.g_magic) >> 16;
         if constexpr (MASK_HELD)
             mw[rb] = *reinterpret_cast<const uintx4*>(p.mask + (static_cast<size_t>(b) * p.K_max + node[rb]) * GRAFT_MASK_WORDS);
     }
@@ -391,17 +533,17 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
     const bool rows_live = ((r_base * p.g_magic) >> 16) < n && r_base < p.R;
     const int count = (rows_live && first < tile1) ? div31(tile1 - first + kg - 1, key_groups_magic) : 0;
 
-    float m[MB], l[MB];
-    floatx4 lv[MB];                             // row sums where the matrix cores take them (every entry the row's sum)
-    floatx4 o[MB][NO];
+    float m[NB], l[NB];
+    floatx4 lv[NB];                             // row sums where the matrix cores take them (every entry the row's sum)
+    typename Ops::Acc o[NB][NO];
     auto clear_rows = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int rb = 0; rb < MB; ++rb) {
+        for (int rb = 0; rb < NB; ++rb) {
             m[rb] = -INFINITY;
             l[rb] = 0.f;
             lv[rb] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int e = 0; e < NO; ++e) o[rb][e] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int e = 0; e < NO; ++e) o[rb][e] = typename Ops::Acc{};
         }
     };
     clear_rows();
@@ -481,7 +623,21 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
     const uintx4* mask_lds = reinterpret_cast<const uintx4*>(lds);
     if constexpr (!MASK_HELD) {                                   // (behind the first keys' request)
         if (tid < p.K_max * 4) reinterpret_cast<unsigned*>(lds)[tid] = mask_word;
+        unsigned char* const Qs = pieces + DR_WAVES * STAGE + rgi * (16 * MB * ROW);
+        if (SHARE_Q && kg > 1) {
+#pragma unroll
+            for (int u = 0; u < QN / 2; ++u) {
+                const int j = kgi + u * kg, row = j * QR + lane / CPR;
+                if (j < QN) *reinterpret_cast<uintx4*>(Qs + row * ROW + (((lane % CPR) ^ (row & 7)) * 16)) = q_share[u];
+            }
+        }
         lds_only_barrier();
+        if constexpr (SHARE_Q) {
+            if (kg > 1) {
+#pragma unroll
+                for (int rb = 0; rb < NB; ++rb) Ops::read_q(q[rb], Qs, rb * RB + lr, lg);
+            }
+        }
     }
     // One tile: through LDS where it has to be turned, the next one requested behind it.
     auto step = [&](int it, auto more_, auto careful_) __attribute__((always_inline)) {
@@ -492,8 +648,8 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
         if constexpr (more) load_keys(kt, it + 1);
         const int t0 = tile_at(it) * TK;
         const bool masked = t0 + TK > P;
-        floatx4 s[MB][NC];
-        Ops::template scores<MB>(Ks, q, s, l16, lg);
+        typename Ops::Scores s[NB];
+        Ops::template scores<NB>(Ks, q, s, lr, lg);
         unsigned odd = 0;                                     // keys with an infinite or NaN value
         if constexpr (careful) {
             odd = Ops::nonfinite_keys(vt, lane);
@@ -507,32 +663,31 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
         }
         if (__builtin_expect(masked, 0)) {
 #pragma unroll
-            for (int rb = 0; rb < MB; ++rb) {
+            for (int rb = 0; rb < NB; ++rb) {
                 const uintx4 words = MASK_HELD ? mw[rb] : mask_lds[node[rb]];
                 const unsigned win = visible_window(t0 - P, total - P, [&](int k) {
                     return k == 0 ? words[0] : (k == 1 ? words[1] : (k == 2 ? words[2] : words[3]));
                 }) >> (4 * lg);
 #pragma unroll
-                for (int c = 0; c < NC; ++c)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) s[rb][c][i] = keep_visible(s[rb][c][i], win, 16 * c + i);
+                for (int v = 0; v < NS; ++v) s[rb].set(v, keep_visible(s[rb].get(v), win, Ops::key(v)));
             }
         }
-        float mx[MB];
+        float mx[NB];
         bool raise = false;
 #pragma unroll
-        for (int rb = 0; rb < MB; ++rb) {
-            float x = fmaxf(fmaxf(s[rb][0][0], s[rb][0][1]), fmaxf(s[rb][0][2], s[rb][0][3]));
-            if constexpr (NC == 2)
-                x = fmaxf(x, fmaxf(fmaxf(s[rb][1][0], s[rb][1][1]), fmaxf(s[rb][1][2], s[rb][1][3])));
+        for (int rb = 0; rb < NB; ++rb) {
+            // (two maxima an instruction; a row with a NaN among its scores is NaN either way)
+            float x = s[rb].get(0);
+#pragma unroll
+            for (int v = 1; v < NS; ++v) x = __builtin_elementwise_maximum(x, s[rb].get(v));
             mx[rb] = x * sc;
             raise = raise || mx[rb] > m[rb] + (careful ? 0.f : DR_LAZY_LOG2);
         }
         // (rare) a row without a reference, or one that outgrew it: raise it to the maximum seen
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(raise) != 0, 0)) {
 #pragma unroll
-            for (int rb = 0; rb < MB; ++rb) {
-                const float mn = fmaxf(m[rb], rows_max_f32(mx[rb]));
+            for (int rb = 0; rb < NB; ++rb) {
+                const float mn = fmaxf(m[rb], row_max<RB>(mx[rb]));
                 const float a = mn == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m[rb] - mn);
                 m[rb] = mn;
                 l[rb] *= a;
@@ -542,40 +697,36 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
             }
         }
 #pragma unroll
-        for (int rb = 0; rb < MB; ++rb) {
+        for (int rb = 0; rb < NB; ++rb) {
             const float neg = m[rb] == -INFINITY ? 0.f : -m[rb];
             float sum = 0.f;
 #pragma unroll
-            for (int c = 0; c < NC; ++c)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    s[rb][c][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[rb][c][i], sc, neg));
-                    if constexpr (!Ops::SUM_MFMA) sum += s[rb][c][i];
-                }
+            for (int v = 0; v < NS; ++v) {
+                s[rb].set(v, __builtin_amdgcn_exp2f(__builtin_fmaf(s[rb].get(v), sc, neg)));
+                if constexpr (!Ops::SUM_MFMA) sum += s[rb].get(v);
+            }
             l[rb] += sum;
         }
         // the values of such a key leave the product and are added to the rows that see it
         for (unsigned left = odd; careful && left != 0; left &= left - 1) {
-            const int key = __builtin_ctz(left), page = key >> 4, at = (key >> 4) * 4 + (key & 3);
+            const int key = __builtin_ctz(left), page = key >> 4, at = Ops::value_of(key);
             Ops::clear_key(vt, Vs, key, lane);
             const char* vrow = vc + page_base(it, page) + row_off(it, page, key & 15);
 #pragma unroll
-            for (int rb = 0; rb < MB; ++rb) {
-                float pk = s[rb][0][0];
+            for (int rb = 0; rb < NB; ++rb) {
+                float pk = s[rb].get(0);
 #pragma unroll
-                for (int c = 0; c < NC; ++c)
+                for (int v = 0; v < NS; ++v) pk = at == v ? s[rb].get(v) : pk;
+                pk = __shfl(pk, RB * Ops::group_of(key) + lr);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) pk = at == 4 * c + i ? s[rb][c][i] : pk;
-                pk = __shfl(pk, 16 * ((key >> 2) & 3) + l16);
-#pragma unroll
-                for (int u = 0; u < D / 16; ++u) {
+                for (int u = 0; u < NP; ++u) {
                     if (pk != 0.f) Ops::add_piece(o[rb], u, Ops::load_dims(vrow + Ops::dim(u, lg) * sizeof(T)) * pk);
                     asm volatile("" ::: "memory");            // (one load at a time: registers are short here)
                 }
             }
         }
         asm volatile("" ::: "memory");                        // (the transpose reads stay behind the writes above)
-        Ops::template accumulate<MB>(vt, Vs, s, o, lv, l16, lg);
+        Ops::template accumulate<NB>(vt, Vs, s, o, lv, lr, lg);
         if constexpr (more && !Ops::V_STAGED) load_values(vt, it + 1);
     };
     // chunks of the tiles that one table register covers
@@ -596,12 +747,12 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
     if constexpr (Ops::ALONE) {
         bool odd = false;
 #pragma unroll
-        for (int rb = 0; rb < MB; ++rb) {
+        for (int rb = 0; rb < NB; ++rb) {
             float t = 0.f;                                    // two sums per instruction, NaN is kept
 #pragma unroll
             for (int e = 0; e < NO; ++e)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) t = __builtin_elementwise_maximum(t, __builtin_fabsf(o[rb][e][i]));
+                for (int i = 0; i < 4 * NP / NO; ++i) t = __builtin_elementwise_maximum(t, __builtin_fabsf(o[rb][e][i]));
             odd = odd || (!(t < INFINITY) && node[rb] < n);   // (queries of absent nodes may be anything)
         }
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd) != 0, 0)) {
@@ -614,7 +765,7 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
         }
     }
 #pragma unroll
-    for (int rb = 0; rb < MB; ++rb) l[rb] = Ops::SUM_MFMA ? lv[rb][0] : rows_sum_f32(l[rb]);
+    for (int rb = 0; rb < NB; ++rb) l[rb] = Ops::SUM_MFMA ? lv[rb][0] : row_sum<RB>(l[rb]);
 
     // ---- results: this workgroup's rows, merged over its key groups
     T* outp = static_cast<T*>(p.out);
@@ -622,15 +773,15 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
     const size_t part = ((static_cast<size_t>(b) * n_kv_heads + g) * n_splits + split) * p.R_pad;
     if (kg == 1) {
 #pragma unroll
-        for (int rb = 0; rb < MB; ++rb) {
-            const int r = r_base + rb * 16 + l16;
+        for (int rb = 0; rb < NB; ++rb) {
+            const int r = r_base + rb * RB + lr;
             if (n_splits == 1) {
                 const bool keep = r < p.R && node[rb] < n && l[rb] > 0.f;
                 const float inv = keep ? 1.0f / l[rb] : 0.f;
                 T* row = outp + ((static_cast<size_t>(b) * p.K_max + node[rb]) * p.Hq + g * p.G + (r - node[rb] * p.G)) * D;
                 if (r < p.R) {
 #pragma unroll
-                    for (int u = 0; u < D / 16; ++u) {
+                    for (int u = 0; u < NP; ++u) {
                         floatx4 x = Ops::piece(o[rb], u) * inv;
                         if (!keep) x = floatx4{0.f, 0.f, 0.f, 0.f};
                         store4(row + Ops::dim(u, lg), x);
@@ -638,7 +789,7 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
                 }
             } else {
 #pragma unroll
-                for (int u = 0; u < D / 16; ++u) store4(ws_o + (part + r) * D + Ops::dim(u, lg), Ops::piece(o[rb], u));
+                for (int u = 0; u < NP; ++u) store4(ws_o + (part + r) * D + Ops::dim(u, lg), Ops::piece(o[rb], u));
                 if (lg == 0) {
                     p.ws_ml[2 * (part + r)] = m[rb];
                     p.ws_ml[2 * (part + r) + 1] = l[rb];
@@ -650,13 +801,13 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
     __syncthreads();                                              // no wavefront reads its piece any more
     float* ml_lds = merge_lds + DR_WAVES * 16 * MB * PITCH;
 #pragma unroll
-    for (int rb = 0; rb < MB; ++rb) {
-        float* row = merge_lds + ((wave * MB + rb) * 16 + l16) * PITCH;
+    for (int rb = 0; rb < NB; ++rb) {
+        float* row = merge_lds + (wave * 16 * MB + rb * RB + lr) * PITCH;
 #pragma unroll
-        for (int u = 0; u < D / 16; ++u) store4(row + Ops::dim(u, lg), Ops::piece(o[rb], u));
+        for (int u = 0; u < NP; ++u) store4(row + Ops::dim(u, lg), Ops::piece(o[rb], u));
         if (lg == 0) {
-            ml_lds[2 * ((wave * MB + rb) * 16 + l16)] = m[rb];
-            ml_lds[2 * ((wave * MB + rb) * 16 + l16) + 1] = l[rb];
+            ml_lds[2 * (wave * 16 * MB + rb * RB + lr)] = m[rb];
+            ml_lds[2 * (wave * 16 * MB + rb * RB + lr) + 1] = l[rb];
         }
     }
     __syncthreads();
@@ -760,9 +911,14 @@ __global__ __launch_bounds__(256) void tree_attn_direct_merge_kernel(
 // host side
 // ---------------------------------------------------------------------------------------------
 static size_t direct_lds_bytes(int mb, int rg, int32_t D, int32_t dtype) {
-    const size_t pieces = static_cast<size_t>(DR_WAVES) * (dtype == GRAFT_F32 ? 16 * D * 4 : 2 * 32 * D * 2);
-    const size_t merge = rg == DR_WAVES ? 0 : static_cast<size_t>(DR_WAVES) * 16 * mb * (D + 4 + 2) * sizeof(float);
-    return (pieces > merge ? pieces : merge) + (mb * D >= 256 ? DR_MASK_BYTES : 0);
+    const bool share = shares_queries(dtype == GRAFT_F32, D);
+    const size_t row = static_cast<size_t>(D) * (dtype == GRAFT_F32 ? 4 : 2);
+    size_t loop = static_cast<size_t>(DR_WAVES) * (dtype == GRAFT_F32 ? 16 : 2 * 32) * row, merge = 0;
+    if (rg < DR_WAVES) {
+        if (share) loop += static_cast<size_t>(rg) * 16 * mb * row;
+        merge = static_cast<size_t>(DR_WAVES) * 16 * mb * (D + 4 + 2) * sizeof(float);
+    }
+    return (loop > merge ? loop : merge) + (mb * D >= 256 || share ? DR_MASK_BYTES : 0);
 }
 
 // Launch shape: row blocks per wavefront, row groups per workgroup and splits that make the
