@@ -4,18 +4,21 @@
 // KB, so the call is latency-bound, not bandwidth-bound: what matters is one
 // launch, few dependent memory round trips, and an exact total order on the hits.
 //
-//   1. the context passes through LDS in chunks of 16384 tokens (two buffers, a ring: 128 KB of
-//      the compute unit's 160).  The lengths are requested first and the first two chunks right
-//      behind them, before the lengths are back (every index below L_max is readable); a thread
-//      loads groups of four consecutive tokens with 16-byte loads.  Both chunks and the tail go to
-//      LDS at once, and the query (last n_max tokens of context ++ tail, reversed) is read from
-//      there: a context of up to 32768 tokens costs one memory round trip and three barriers
-//      before the ranking;
+//   1. the lengths are requested first and the first 32768 tokens right behind them, before the
+//      lengths are back (every index below L_max is readable); a thread loads groups of four
+//      consecutive tokens with 16-byte loads.  A context of up to 32768 tokens goes to LDS at once
+//      (128 KB of the compute unit's 160), and the query (last n_max tokens of context ++ tail,
+//      reversed) is read from there: one memory round trip and three barriers before the ranking.
+//      A longer one is scanned from the registers it is loaded into, four units of 8192 tokens in
+//      flight, no barrier and no copy in LDS: what bounds it is the compute unit's load path, 64
+//      bytes a cycle.  (All contexts through LDS in chunks of 16384, two barriers each and at most
+//      one chunk in flight: 131072 tokens 14.1 us, 8.9 now; 40000 tokens 7.9, 6.7 now; 16 sequences
+//      of 200000 26.6, 14.6 now.)
 //   2. scan: one compare per token against the query's last token, and a wavefront in which no
 //      lane has it goes on (in text it is rare).  Otherwise the lanes test the token before as
-//      well (in a register, or for the first of a group in LDS) where a hit needs two tokens, and
-//      a candidate's match length is measured backwards through the ring, eight tokens per round
-//      of independent reads;
+//      well (in a register, or for the first of a group in LDS or from the lane below) where a hit
+//      needs two tokens, and a candidate's match length is measured backwards, eight tokens per
+//      round of independent reads;
 //   3. a hit is the 64-bit key (match_len << 32 | e); each thread keeps its own best C keys in
 //      registers (unrolled insertion, no dynamic indexing);
 //   4. ranking without memory traffic.  The threads that have hits append their best C keys to a
@@ -62,6 +65,8 @@ __device__ __forceinline__ Tok4 load_group(const int32_t* __restrict__ x, int32_
 constexpr int RT_AHEAD = 2;                           // chunks the loads run ahead of the scan
 constexpr int RT_LIST = 128;                          // keys the ranking list holds before the tournament takes over
 constexpr int RT_WALK = 8;                            // tokens compared per round of the backward match
+constexpr int RT_UNIT = 8 * RT_THREADS;               // tokens of a unit of the streamed scan, two groups per thread
+constexpr int RT_SLOTS = 2 * RT_AHEAD;                // units in flight
 
 __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
     const int32_t* __restrict__ ctx, const int32_t* __restrict__ ctx_len, int32_t L_max,
@@ -109,28 +114,27 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
         if (tid == 0) { n_hits[b] = 0; status[b] = GRAFT_STATUS_BAD_LENGTH; }
         return;
     }
+    const int32_t QL = L + T;
+    const int32_t nq = n_max < QL ? n_max : QL, qi = QL - 1 - tid;
+    const bool streamed = L > RT_AHEAD * RT_CHUNK;   // (then L_max is larger as well: no group above was cut short)
+    if (streamed && tid < nq) q_rev[tid] = qi < L ? x[qi] : tail[static_cast<size_t>(b) * tail_max + (qi - L)];
     // Both chunks in flight go to LDS at once (the two buffers are a ring: the token at position p
     // sits at flat index p mod 2 RT_CHUNK), and so do the tail tokens; the query is then read from
     // there: no second trip to memory unless it lies beyond the first two chunks.
     int32_t* ring = &buf[0][0];
+    if (!streamed) {
 #pragma unroll
-    for (int k = 0; k < RT_AHEAD; ++k)
+        for (int k = 0; k < RT_AHEAD; ++k)
 #pragma unroll
-        for (int u = 0; u < RT_GROUPS; ++u)
-            if (k * RT_CHUNK + u * RT_THREADS * 4 < L_max)       // uniform: nothing past the row's end is ever read
-                *reinterpret_cast<int4*>(ring + k * RT_CHUNK + (u * RT_THREADS + tid) * 4) =
-                    int4{v[k][u].t[0], v[k][u].t[1], v[k][u].t[2], v[k][u].t[3]};
+            for (int u = 0; u < RT_GROUPS; ++u)
+                if (k * RT_CHUNK + u * RT_THREADS * 4 < L_max)   // uniform: nothing past the row's end is ever read
+                    *reinterpret_cast<int4*>(ring + k * RT_CHUNK + (u * RT_THREADS + tid) * 4) =
+                        int4{v[k][u].t[0], v[k][u].t[1], v[k][u].t[2], v[k][u].t[3]};
+    }
     tail_s[tid] = tail_tok;
     __syncthreads();
-    const int32_t QL = L + T;
-    const int32_t nq = n_max < QL ? n_max : QL;
-    if (tid < nq) {
-        const int32_t qi = QL - 1 - tid;
-        int32_t q;
-        if (qi < L) q = qi < RT_AHEAD * RT_CHUNK ? ring[qi] : x[qi];
-        else q = (qi - L) < RT_THREADS ? tail_s[qi - L] : tail[static_cast<size_t>(b) * tail_max + (qi - L)];
-        q_rev[tid] = q;
-    }
+    if (!streamed && tid < nq)
+        q_rev[tid] = qi < L ? ring[qi] : ((qi - L) < RT_THREADS ? tail_s[qi - L] : tail[static_cast<size_t>(b) * tail_max + (qi - L)]);
 
     u64 top[GRAFT_MAX_CHAINS];
 #pragma unroll
@@ -140,21 +144,111 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
     // position i holds the token right before continuation start e = i + 1, 1 <= e <= L-1
     const int32_t last_i = L - 2;
     const int32_t n_chunks = last_i >= 0 ? last_i / RT_CHUNK + 1 : 0;
-    for (int32_t c0 = 0; c0 < n_chunks; c0 += RT_AHEAD) {
+    const auto hit = [&](int32_t l, int32_t e) __attribute__((always_inline)) {
+        ++my_hits;
+        u64 key = (static_cast<u64>(l) << 32) | static_cast<u64>(e);
+        // (only the best C of a thread can be among the best C overall)
 #pragma unroll
-        for (int k = 0; k < RT_AHEAD; ++k) {
-            const int32_t c = c0 + k;
-            if (c >= n_chunks) continue;              // uniform over the workgroup (no break: k must stay a constant)
-            if (c >= RT_AHEAD) {                  // (the first RT_AHEAD chunks are in LDS already)
-                int32_t* cur = buf[c & 1];
+        for (int kk = 0; kk < GRAFT_MAX_CHAINS; ++kk) {
+            if (kk >= C) break;                   // uniform
+            if (key > top[kk]) { const u64 u = top[kk]; top[kk] = key; key = u; }
+        }
+    };
+    if (streamed) {
+        // ---- a context that does not fit the ring: scanned from the registers it is loaded into
+        __syncthreads();                          // q_rev visible
+        const int32_t q_last = q_rev[0], q_prev = nq > 1 ? q_rev[1] : 0;
+        const bool one = nq < 2 || n_max < 2;     // a query of one token
+        const auto scan = [&](Tok4 (&g)[2], int32_t unit) __attribute__((always_inline)) {
+            unsigned cand = 0, longer = 0;        // bit 4 u + j: token j of group u is a candidate, the one before it matches too
 #pragma unroll
-                for (int u = 0; u < RT_GROUPS; ++u)
-                    *reinterpret_cast<int4*>(cur + (u * RT_THREADS + tid) * 4) =
-                        int4{v[k][u].t[0], v[k][u].t[1], v[k][u].t[2], v[k][u].t[3]};
-                __syncthreads();                  // chunk c visible; chunk c - 1 still in the other buffer
-            } else if (c == 0) {
-                __syncthreads();                  // q_rev visible
+            for (int u = 0; u < 2; ++u) {
+                const int32_t i0 = unit * RT_UNIT + (u * RT_THREADS + tid) * 4;
+                const bool any = (g[u].t[0] == q_last) | (g[u].t[1] == q_last) | (g[u].t[2] == q_last) | (g[u].t[3] == q_last);
+                if (__builtin_amdgcn_ballot_w64(any) == 0) continue;
+                // the token before the group is the last of the lane below; lane 0 does not know it and lets the walk decide
+                const int32_t below = __shfl_up(g[u].t[3], 1);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const bool more = !one && i0 + j >= 1 && (j == 0 ? lane == 0 || below == q_prev : g[u].t[j - 1] == q_prev);
+                    if (i0 + j <= last_i && g[u].t[j] == q_last && (more || n_min < 2)) {
+                        cand |= 1u << (4 * u + j);
+                        longer |= more ? 1u << (4 * u + j) : 0u;
+                    }
+                }
             }
+            while (cand != 0) {                   // one candidate per lane and pass
+                const int bit = __builtin_ctz(cand);
+                cand &= cand - 1;
+                const int32_t e = unit * RT_UNIT + ((bit >> 2) * RT_THREADS + tid) * 4 + (bit & 3) + 1;
+                const int32_t cap = (longer >> bit & 1) == 0 ? 1 : (n_max < e ? n_max : e);
+                int32_t l = 1;
+                for (int32_t base = 1; base < cap; base += RT_WALK) {
+                    int32_t before[RT_WALK];
+#pragma unroll
+                    for (int jj = 0; jj < RT_WALK; ++jj) before[jj] = x[e - 1 - base - jj >= 0 ? e - 1 - base - jj : 0];
+                    unsigned eq = 0;
+#pragma unroll
+                    for (int jj = 0; jj < RT_WALK; ++jj) eq |= (before[jj] == q_rev[base + jj] && base + jj < cap) ? 1u << jj : 0u;
+                    const int run = __builtin_ctz(~eq);
+                    l += run;
+                    if (run < RT_WALK) break;
+                }
+                if (l >= n_min) hit(l, e);
+            }
+        };
+        const int32_t n_units = last_i / RT_UNIT + 1;             // of 8192 tokens; the first RT_SLOTS are on their way
+        Tok4 slot[RT_SLOTS][2], extra[RT_SLOTS - 1][2];
+#pragma unroll
+        for (int s = 0; s < RT_SLOTS; ++s)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) slot[s][u] = v[s >> 1][2 * (s & 1) + u];
+        const auto fetch = [&](Tok4 (&g)[2], int32_t unit) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int32_t i0 = unit * RT_UNIT + (u * RT_THREADS + tid) * 4;
+                g[u] = *reinterpret_cast<const Tok4*>(x + (i0 < L_max - 4 ? i0 : L_max - 4));
+            }
+        };
+        // the row's last group, if it is not whole, was read from L_max - 4 on
+        const auto shift = [&](Tok4 (&g)[2], int32_t unit) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int32_t by = unit * RT_UNIT + (u * RT_THREADS + tid) * 4 - (L_max - 4);
+#pragma unroll
+                for (int r = 0; r < 3; ++r)
+                    if (r < by) { g[u].t[0] = g[u].t[1]; g[u].t[1] = g[u].t[2]; g[u].t[2] = g[u].t[3]; }
+            }
+        };
+        // No load in the loop is conditional: with a branch around it the compiler no longer knows how many are in
+        // flight and waits for all of them.
+        int32_t c = 0;
+        for (; c + 2 * RT_SLOTS <= n_units; c += RT_SLOTS)
+#pragma unroll
+            for (int s = 0; s < RT_SLOTS; ++s) {
+                scan(slot[s], c + s);
+                fetch(slot[s], c + s + RT_SLOTS);
+            }
+        if (n_units > c + RT_SLOTS) {
+#pragma unroll
+            for (int s = 0; s < RT_SLOTS - 1; ++s) fetch(extra[s], c + s + RT_SLOTS);
+        }
+#pragma unroll
+        for (int s = 0; s < RT_SLOTS; ++s) {
+            shift(slot[s], c + s);
+            scan(slot[s], c + s);
+        }
+#pragma unroll
+        for (int s = 0; s < RT_SLOTS - 1; ++s)
+            if (c + s + RT_SLOTS < n_units) {
+                shift(extra[s], c + s + RT_SLOTS);
+                scan(extra[s], c + s + RT_SLOTS);
+            }
+    } else {
+        __syncthreads();                          // q_rev visible
+#pragma unroll
+        for (int c = 0; c < RT_AHEAD; ++c) {
+            if (c >= n_chunks) continue;          // uniform over the workgroup (no break: c must stay a constant)
             const int32_t q_last = nq > 0 ? q_rev[0] : 0;
             // When a hit needs at least two matching tokens, the token before position i is
             // tested as well before the (divergent) walk: with frequent tokens at the end of
@@ -169,14 +263,14 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
                 if (c * RT_CHUNK + u * RT_THREADS * 4 > last_i) continue;        // uniform: the whole group row is past the end
                 // in text the query's last token is rare: one compare per token, and a wavefront in
                 // which no lane has it skips the rest
-                const bool any = (v[k][u].t[0] == q_last) | (v[k][u].t[1] == q_last) | (v[k][u].t[2] == q_last) |
-                                 (v[k][u].t[3] == q_last);
+                const bool any = (v[c][u].t[0] == q_last) | (v[c][u].t[1] == q_last) | (v[c][u].t[2] == q_last) |
+                                 (v[c][u].t[3] == q_last);
                 if (__builtin_amdgcn_ballot_w64(any) == 0) continue;
                 const int32_t ip = i0 - 1;
                 int32_t prev = ip >= 0 ? buf[(ip / RT_CHUNK) & 1][ip % RT_CHUNK] : ~q_prev;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const int32_t t = v[k][u].t[j];
+                    const int32_t t = v[c][u].t[j];
                     if (i0 + j <= last_i && t == q_last && (!two || (i0 + j >= 1 && prev == q_prev))) cand |= 1u << (4 * u + j);
                     prev = t;
                 }
@@ -205,25 +299,9 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
                         l += run;
                         if (run < RT_WALK) break;
                     }
-                    if (l >= n_min) {
-                        ++my_hits;
-                        u64 key = (static_cast<u64>(l) << 32) | static_cast<u64>(e);
-                        // (only the best C of a thread can be among the best C overall)
-#pragma unroll
-                        for (int kk = 0; kk < GRAFT_MAX_CHAINS; ++kk) {
-                            if (kk >= C) break;          // uniform
-                            if (key > top[kk]) { u64 t = top[kk]; top[kk] = key; key = t; }
-                        }
-                    }
+                    if (l >= n_min) hit(l, e);
                 }
             }
-            if (c + RT_AHEAD < n_chunks) {        // this slot's registers are free: fetch RT_AHEAD chunks ahead
-#pragma unroll
-                for (int u = 0; u < RT_GROUPS; ++u)
-                    v[k][u] = load_group(x, (c + RT_AHEAD) * RT_CHUNK + (u * RT_THREADS + tid) * 4, L_max);
-            }
-            if (c + 1 >= RT_AHEAD && c + 1 < n_chunks)
-                __syncthreads();                  // all walks done before chunk c + 1 overwrites chunk c - 1
         }
     }
 
@@ -300,7 +378,7 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
         const int32_t e = static_cast<int32_t>(key & 0xffffffffu);
         if (key != 0 && e + jj < L) {
             const int32_t pos = e + jj, ch = pos / RT_CHUNK;
-            tok_b[i] = (ch < n_chunks && ch + 2 >= n_chunks) ? buf[ch & 1][pos % RT_CHUNK] : x[pos];
+            tok_b[i] = !streamed && ch < n_chunks ? buf[ch & 1][pos % RT_CHUNK] : x[pos];
         }
     }
 }

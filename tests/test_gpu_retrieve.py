@@ -85,3 +85,26 @@ def test_outputs_fully_overwritten():
     graft.graft_retrieve(dev(s["ctx"]), dev(s["ctx_len"]), w.n_min, w.n_max, 8, 12, dev(s["tail"]),
                          dev(s["tail_len"]), out=out)
     assert_same(host_dict(out), ref, KEYS)
+
+
+@pytest.mark.parametrize("n_min", [1, 2])
+@pytest.mark.parametrize("L", [32768, 32769, 32770, 32771, 40960, 40961, 65537, 73731, 131075])
+def test_contexts_around_and_beyond_the_ring(L, n_min):
+    """Up to 32768 tokens the context is scanned in LDS, beyond that from registers, in units of 8192 tokens: matches that
+    end at the edges of lanes, wavefronts, groups, units and of the row, rows that start at any element."""
+    rng = np.random.default_rng(L + n_min)
+    B, n_max = 3, 9
+    query = rng.integers(100, 200, n_max).astype(np.int32)
+    ctx = rng.integers(0, 100, size=(B, L)).astype(np.int32)
+    ctx[2] = rng.integers(0, 4, L)                                     # and a row that is nothing but candidates
+    ctx_len = np.array([L, L - 1, L - 2], np.int32)
+    tail = np.zeros((B, n_max), np.int32)
+    tail[:2], tail_len = query, np.array([n_max, n_max, 0], np.int32)
+    ends = [0, 1, n_max - 1, 255, 256, 4095, 4096, 8191, 8192, 16383, 16384, 32767, 32768, L - 5, L - 4, L - 3, L - 2, L - 1]
+    for b in range(2):
+        for i in [i for i in (ends[b::2] if n_min == 1 else ends[1 - b::2]) if i < L]:
+            k = int(min(i + 1, rng.integers(1, n_max + 1)))
+            ctx[b, i - k + 1:i + 1] = query[n_max - k:]
+    gpu, ref = both(ctx, ctx_len, n_min, n_max, 8, 6, tail, tail_len)
+    assert_same(gpu, ref, KEYS)
+    assert gpu["n_hits"][0] > 0 and gpu["n_hits"][2] > 1000
