@@ -93,6 +93,10 @@ __global__ __launch_bounds__(AM_THREADS) void argmax_chunk_kernel(
     }
 }
 
+// Bound by its chain of dependent steps, so a node's step up the tree is one LDS read: link[j] is j's parent if j
+// carries the greedy token of its parent, else -1, and a walk ends at the first mismatch.  Each walk notes the
+// nodes it passes as bits; with the best node's bits at hand every node of the path finds its own place (the number of
+// bits below it), where one thread used to walk the path again.
 __global__ __launch_bounds__(AC_THREADS) void accept_walk_kernel(
     const int32_t* __restrict__ parent, const int32_t* __restrict__ tokens,
     const int32_t* __restrict__ n_nodes, const ArgPartial* __restrict__ partial,
@@ -101,23 +105,19 @@ __global__ __launch_bounds__(AC_THREADS) void accept_walk_kernel(
     int32_t* __restrict__ out_tokens, int32_t* __restrict__ status) {
     const int b = blockIdx.x;
     const int i = threadIdx.x;
-    __shared__ int32_t par[AC_THREADS];
-    __shared__ int32_t tok[AC_THREADS];
     __shared__ int32_t tstar[AC_THREADS];
+    __shared__ int32_t link[AC_THREADS];
+    __shared__ uint4 passed[AC_THREADS];         // nodes on an accepted node's path, as bits
     __shared__ u64 red[AC_THREADS / 64];
-    __shared__ int32_t best_d;
     __shared__ int32_t or_bad[2], or_over[2];
 
     const int32_t n = n_nodes[b];
     const bool n_ok = n >= 1 && n <= K_max;
     const size_t row = static_cast<size_t>(b) * K_max;
     const int32_t p = i < K_max ? parent[row + i] : -1;
-    bool bad = !n_ok;
-    if (n_ok && i < n) bad = (i == 0) ? (p != -1) : (p < 0 || p >= i);
-    par[i] = p;
-    tok[i] = i < K_max ? tokens[row + i] : -1;
+    const int32_t tok = i < K_max ? tokens[row + i] : -1;
     // (requested with the other inputs: one trip to memory for all of them)
-    const int32_t ts_given = (!partial && i < K_max) ? target_ids[row + i] : -1;
+    int32_t ts = (!partial && i < K_max) ? target_ids[row + i] : -1;
     // (the scan has written the partials of padding nodes too; requested here and not behind the barrier:
     // 0.6 us less a call)
     ArgPartial pr[GRAFT_ARGMAX_CHUNKS];
@@ -125,6 +125,17 @@ __global__ __launch_bounds__(AC_THREADS) void accept_walk_kernel(
 #pragma unroll
         for (int c = 0; c < GRAFT_ARGMAX_CHUNKS; ++c) pr[c] = partial[(row + i) * GRAFT_ARGMAX_CHUNKS + c];
     }
+    bool bad = !n_ok;
+    if (n_ok && i < n) bad = (i == 0) ? (p != -1) : (p < 0 || p >= i);
+    // the target's greedy token after each node
+    if (partial && i < K_max && i < n) {
+        float bv = pr[0].val;
+        int32_t bi = pr[0].idx;
+#pragma unroll
+        for (int c = 1; c < GRAFT_ARGMAX_CHUNKS; ++c) arg_take(bv, bi, pr[c].val, pr[c].idx);
+        ts = bi;
+    }
+    tstar[i] = ts;
     const bool any_bad = workgroup_or_128(bad, or_bad);
 
     const int32_t width = depth_cap + 1;
@@ -136,58 +147,60 @@ __global__ __launch_bounds__(AC_THREADS) void accept_walk_kernel(
         if (i == 0) { accept_len[b] = 0; best_node[b] = -1; status[b] = GRAFT_STATUS_BAD_TREE; }
         return;
     }
-
-    // the target's greedy token after each node
-    int32_t ts = -1;
-    if (i < K_max) {
-        if (partial) {
-            if (i < n) {
-                float bv = pr[0].val;
-                int32_t bi = pr[0].idx;
-#pragma unroll
-                for (int c = 1; c < GRAFT_ARGMAX_CHUNKS; ++c) arg_take(bv, bi, pr[c].val, pr[c].idx);
-                ts = bi;
-            }
-            target_ids[row + i] = ts;
-        } else {
-            ts = ts_given;
-        }
-    }
-    tstar[i] = ts;
+    if (partial && i < K_max) target_ids[row + i] = ts;
+    link[i] = (i > 0 && i < n && tok == tstar[p]) ? p : -1;
     __syncthreads();
 
     // accepted iff every node on the path below the root carries its parent's greedy token
     bool ok = i < n;
     int32_t d = 0;
+    uint4 bits = uint4{1u, 0u, 0u, 0u};          // the root
     if (ok) {
-        for (int32_t j = i; j != 0; j = par[j]) {
-            ok = ok && tok[j] == tstar[par[j]];
+        int32_t j = i;
+        while (j > 0) {
+            const int32_t up = link[j];
+            const unsigned bit = 1u << (j & 31);
+            const int word = j >> 5;
+            bits.x |= word == 0 ? bit : 0u;
+            bits.y |= word == 1 ? bit : 0u;
+            bits.z |= word == 2 ? bit : 0u;
+            bits.w |= word == 3 ? bit : 0u;
             ++d;
+            j = up;
         }
+        ok = j == 0;
     }
+    passed[i] = bits;
     const int over = (ok && d > depth_cap) ? 1 : 0;
     // key: depth first, then smaller index; 0 = not a candidate (the root gives key >= 1)
-    u64 key = (ok && d <= depth_cap) ? ((static_cast<u64>(d) << 8) | static_cast<u64>(255 - i)) : 0;
-    u64 wmax = wave_max_u64(key);
+    const u64 key = (ok && d <= depth_cap) ? ((static_cast<u64>(d) << 8) | static_cast<u64>(255 - i)) : 0;
+    const u64 wmax = wave_max_u64(key);
     if ((i & 63) == 0) red[i >> 6] = wmax;
     const bool any_over = workgroup_or_128(over != 0, or_over);
-    const u64 gmax = red[0] > red[1] ? red[0] : red[1];
-    if (key == gmax) {                           // unique: the index is part of the key
-        accept_len[b] = d;
+    const unsigned best = static_cast<unsigned>(red[0] > red[1] ? red[0] : red[1]);
+    const int32_t best_i = 255 - static_cast<int32_t>(best & 255u), best_d = static_cast<int32_t>(best >> 8);
+    const uint4 on = passed[best_i];
+    const unsigned words[4] = {on.x, on.y, on.z, on.w};
+    int32_t k = 0;                               // nodes of the path before this one
+    bool mine = false;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const int32_t at = i - 32 * w;
+        k += __popc(at >= 32 ? words[w] : (at > 0 ? words[w] & ((1u << at) - 1u) : 0u));
+        if (at >= 0 && at < 32) mine = (words[w] >> at) & 1u;
+    }
+    if (mine) {                                  // (best_d <= depth_cap)
+        path_b[k] = i;
+        if (k > 0) out_b[k - 1] = tok;
+    }
+    if (i == best_i) {
+        accept_len[b] = best_d;
         best_node[b] = i;
         status[b] = any_over ? GRAFT_STATUS_PATH_OVERFLOW : 0;
-        best_d = d;
-        int32_t k = d;
-        for (int32_t j = i; j != -1; j = par[j]) {
-            path_b[k] = j;
-            if (k > 0) out_b[k - 1] = tok[j];
-            --k;
-        }
-        out_b[d] = ts;
+        out_b[best_d] = ts;
     }
-    __syncthreads();
     // the padding behind the path: all threads, not one after the other
-    for (int32_t k = best_d + 1 + i; k < width; k += AC_THREADS) { path_b[k] = -1; out_b[k] = -1; }
+    for (int32_t q = best_d + 1 + i; q < width; q += AC_THREADS) { path_b[q] = -1; out_b[q] = -1; }
 }
 
 // ---- graft_accept_noalloc: the argmax partials live in a file-scope device array ----------

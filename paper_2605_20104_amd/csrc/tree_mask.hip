@@ -3,12 +3,17 @@
 // One 128-thread workgroup (two wavefronts) per sequence, one thread per tree
 // slot.  The parent list sits in LDS; each thread walks its own ancestor chain
 // (at most K steps), so the whole call is a few hundred LDS reads deep and
-// launch-latency bound.  Leaves are ranked with a wavefront ballot + popcount.
+// launch-latency bound.  Leaves are ranked with a wavefront ballot + popcount and
+// write their paths, read off their masks, into a table of bytes in LDS, which goes
+// to memory as whole 16-byte groups, each entry stored once.
 #include "common.h"
 
 namespace graft {
 
 constexpr int TM_THREADS = GRAFT_MAX_NODES;
+constexpr int TM_TABLE = GRAFT_MAX_NODES * GRAFT_MAX_NODES;       // most path entries of a sequence
+static_assert(GRAFT_MAX_NODES <= 128, "node indices as signed bytes, two wavefronts");
+struct Int4 { int32_t t[4]; };                                    // 16 bytes at any 4-byte boundary
 
 __global__ __launch_bounds__(TM_THREADS) void tree_mask_kernel(
     const int32_t* __restrict__ parent, const int32_t* __restrict__ n_nodes,
@@ -19,7 +24,7 @@ __global__ __launch_bounds__(TM_THREADS) void tree_mask_kernel(
     const int i = threadIdx.x;
     __shared__ int32_t par[TM_THREADS];
     __shared__ int32_t has_child[TM_THREADS];
-    __shared__ int32_t wave_leaves[TM_THREADS / 64];
+    __shared__ __attribute__((aligned(16))) signed char table[TM_TABLE];
     __shared__ int32_t or_bad[2], or_over[2];
 
     const int32_t n = n_nodes[b];
@@ -30,10 +35,13 @@ __global__ __launch_bounds__(TM_THREADS) void tree_mask_kernel(
     if (n_ok && i < n) bad = (i == 0) ? (p != -1) : (p < 0 || p >= i);
     par[i] = p;
     has_child[i] = 0;
+    const int32_t width = depth_cap + 1;
+    const int32_t entries = paths ? n_leaf_max * width : 0;
+    for (int k = 16 * i; k < entries; k += 16 * TM_THREADS)
+        *reinterpret_cast<uint4*>(&table[k]) = uint4{~0u, ~0u, ~0u, ~0u};
     const bool any_bad = workgroup_or_128(bad, or_bad);
 
-    const int32_t width = depth_cap + 1;
-    int32_t* paths_b = paths ? paths + static_cast<size_t>(b) * n_leaf_max * width : nullptr;
+    int32_t* paths_b = paths ? paths + static_cast<size_t>(b) * entries : nullptr;
     u64* mask_b = mask + static_cast<size_t>(b) * K_max * GRAFT_MASK_WORDS;
 
     if (any_bad) {
@@ -44,22 +52,18 @@ __global__ __launch_bounds__(TM_THREADS) void tree_mask_kernel(
             depth[static_cast<size_t>(b) * K_max + i] = -1;
         }
         if (paths_b)
-            for (int k = i; k < n_leaf_max * width; k += TM_THREADS) paths_b[k] = -1;
+            for (int k = i; k < entries; k += TM_THREADS) paths_b[k] = -1;
         if (i == 0) status[b] = GRAFT_STATUS_BAD_TREE;
         return;
     }
 
-    // the path table starts as all -1 (consecutive addresses, all threads; these stores are on
-    // their way during the walk below); the barriers of the leaf ranking order them before the
-    // leaves' own entries
-    if (paths_b)
-        for (int k = i; k < n_leaf_max * width; k += TM_THREADS) paths_b[k] = -1;
+    if (i > 0 && i < n) has_child[p] = 1;              // same value from every writer; read behind the next barrier
 
     int32_t d = -1;
+    unsigned w0 = 0, w1 = 0, w2 = 0, w3 = 0;                  // mask bits 0..31, 32..63, 64..95, 96..127
     if (i < K_max) {
         // (the walk's dependent chain is the LDS read of the parent alone: the mask bits are set in
         //  32-bit words, off that chain)
-        unsigned w0 = 0, w1 = 0, w2 = 0, w3 = 0;              // mask bits 0..31, 32..63, 64..95, 96..127
         if (i < n) {
             for (int32_t j = i; j != -1;) {
                 const int32_t up = par[j];
@@ -79,33 +83,36 @@ __global__ __launch_bounds__(TM_THREADS) void tree_mask_kernel(
         pos[static_cast<size_t>(b) * K_max + i] = i < n ? P + d : -1;
     }
 
-    int overflow = 0;
-    if (paths_b) {
-        if (i > 0 && i < n) has_child[p] = 1;          // same value from every writer
-        __syncthreads();
-        const bool leaf = i < n && has_child[i] == 0;
-        const u64 ballot = __ballot(leaf);
-        const int lane = i & 63, wave = i >> 6;
-        if (lane == 0) wave_leaves[wave] = __popcll(ballot);
-        __syncthreads();
-        int32_t rank = __popcll(ballot & ((1ull << lane) - 1));
-        if (wave == 1) rank += wave_leaves[0];
-        if (leaf) {
-            if (rank >= n_leaf_max) {
-                overflow = 1;                          // dropped
-            } else {
-                int32_t* row = paths_b + static_cast<size_t>(rank) * width;
-                if (d > depth_cap) {
-                    overflow = 1;                      // its row stays -1
-                } else {
-                    int32_t k = d;
-                    for (int32_t j = i; j != -1; j = par[j]) row[k--] = j;
-                }
-            }
-        }
+    if (!paths_b) {
+        if (i == 0) status[b] = 0;
+        return;
     }
-    const bool any_over = workgroup_or_128(overflow != 0, or_over);
-    if (i == 0) status[b] = any_over ? GRAFT_STATUS_PATH_OVERFLOW : 0;
+    // (a node deeper than the cap means a leaf deeper than it)
+    const bool too_deep = workgroup_or_128(d > depth_cap, or_over);
+    const int lane = i & 63;
+    const u64 leaves_lo = __ballot(lane < n && has_child[lane] == 0);             // both wavefronts rank all leaves
+    const u64 leaves_hi = __ballot(64 + lane < n && has_child[64 + lane] == 0);
+    const u64 own = i < 64 ? leaves_lo : leaves_hi;
+    const int32_t rank = __popcll(own & ((1ull << lane) - 1)) + (i < 64 ? 0 : __popcll(leaves_lo));
+    if ((own >> lane & 1) != 0 && rank < n_leaf_max && d <= depth_cap) {
+        // the path is the mask's bits in increasing order (a parent's index is below its child's)
+        signed char* at = table + rank * width;
+        const unsigned words[4] = {w0, w1, w2, w3};
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            for (unsigned left = words[w]; left != 0; left &= left - 1) *at++ = static_cast<signed char>(32 * w + __builtin_ctz(left));
+    }
+    __syncthreads();
+    for (int k = 4 * i; k + 4 <= entries; k += 4 * TM_THREADS) {
+        const int four = *reinterpret_cast<const int*>(&table[k]);
+        Int4 out;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) out.t[u] = static_cast<signed char>(four >> (8 * u));
+        *reinterpret_cast<Int4*>(paths_b + k) = out;
+    }
+    if (i < (entries & 3)) paths_b[(entries & ~3) + i] = table[(entries & ~3) + i];
+    if (i == 0)
+        status[b] = too_deep || __popcll(leaves_lo) + __popcll(leaves_hi) > n_leaf_max ? GRAFT_STATUS_PATH_OVERFLOW : 0;
 }
 
 }  // namespace graft
