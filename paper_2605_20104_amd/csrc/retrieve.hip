@@ -1,6 +1,6 @@
 // graft_retrieve: suffix n-gram lookup over the context token buffer.
 //
-// One 1024-thread workgroup per sequence.  The buffer is at most a few hundred
+// One workgroup per sequence, of 256, 512 or 1024 threads by the length of the rows.  The buffer is at most a few hundred
 // KB, so the call is latency-bound, not bandwidth-bound: what matters is one
 // launch, few dependent memory round trips, and an exact total order on the hits.
 //
@@ -8,7 +8,8 @@
 //      lengths are back (every index below L_max is readable); a thread loads groups of four
 //      consecutive tokens with 16-byte loads.  A context of up to 32768 tokens goes to LDS at once
 //      (128 KB of the compute unit's 160), and the query (last n_max tokens of context ++ tail,
-//      reversed) is read from there: one memory round trip and three barriers before the ranking.
+//      reversed) is read from there, each wavefront into a copy of its own: one memory round trip and
+//      two barriers before the ranking.
 //      A longer one is scanned from the registers it is loaded into, four units of 8192 tokens in
 //      flight, no barrier and no copy in LDS: what bounds it is the compute unit's load path, 64
 //      bytes a cycle.  (All contexts through LDS in chunks of 16384, two barriers each and at most
@@ -27,7 +28,7 @@
 //      is).  A list that overflows (periodic text, tiny alphabets) takes the tournament instead:
 //      each wavefront extracts its best C keys (exactly one lane owns a maximum and pops it),
 //      wavefront 0 merges the 16 x C survivors the same way.  C x m threads then copy the chains,
-//      from LDS where the chunk that holds them is still there.
+//      from LDS where the context is there.
 //
 // Measured on a 32768-token context (cycle stamps): with one position per lane and load, a
 // dependent query load, a tournament in all 16 wavefronts and a serial backward walk the kernel
@@ -35,54 +36,59 @@
 // wavefronts that almost never hold a hit), 2 x 1.5 us the walks of the single wavefront per chunk
 // that had a candidate (250 instructions of signed index arithmetic and per-token branches per
 // round), 0.5 us each the dependent query load, the second chunk's barrier pair and the chain
-// copy from memory.  This form takes 6.1 us.
+// copy from memory.  That form took 6.1 us.  Since then, us a call in a graph: workgroups of four or eight wavefronts
+// for rows of up to 8192 tokens, no branch around each group's load, and query copy and ranking per wavefront in place of
+// two barriers, 2048 tokens 5.3 -> 4.0; all reads of a ranking round in flight (a condition in front of each had
+// made them wait for one another), 4 x 8191 tokens of an alphabet of 20 12.2 -> 7.25.
 #include "common.h"
 
 namespace graft {
 
-constexpr int RT_THREADS = 1024;
-constexpr int RT_WAVES = RT_THREADS / 64;
 constexpr int RT_GROUPS = 4;                          // groups of four consecutive tokens per thread and chunk
-constexpr int RT_UNROLL = 4 * RT_GROUPS;
-constexpr int RT_CHUNK = RT_THREADS * RT_UNROLL;      // tokens per LDS buffer
+constexpr int RT_LIST = 128;                          // keys the ranking list holds before the tournament takes over
+constexpr int RT_WALK = 8;                            // tokens compared per round of the backward match
+constexpr int RT_SLOTS = 4;                           // units of the streamed scan in flight
+constexpr int RT_MOST = 1024;                         // threads of the largest workgroup, the one that streams
+constexpr int rt_chunk(int threads) { return threads * 4 * RT_GROUPS; }     // tokens of a chunk
+// Launch and barriers of a workgroup of sixteen wavefronts take longer than those of four, which shows where the tokens
+// are few: the smallest workgroup whose one chunk holds the rows, by L_max; the largest holds two chunks.  us a call
+// at 256 / 4096 tokens: 256 threads 3.7 / 4.1, 1024 threads 4.4 / 4.7; at 8192: 512 threads 4.3, 1024 threads 4.9.
+constexpr int rt_chunks(int threads) { return threads == RT_MOST ? 2 : 1; }
 // Four consecutive tokens.  The context rows are only known to be 4-byte aligned (L_max is any
 // number), which the hardware's vector loads accept.
 struct __attribute__((packed, aligned(4))) Tok4 { int32_t t[4]; };
 
-// Thread tid's group u of a chunk starts at token (u * RT_THREADS + tid) * 4 of the chunk: one
-// 16-byte load per lane, consecutive lanes consecutive addresses; a group past the end of the row
-// is read token by token.
+// The group of four tokens from i0 on, L_max >= 4: one 16-byte load per lane, consecutive lanes consecutive
+// addresses.  The row's last group, if it is not whole, and those behind it are read from L_max - 4 on; shift_group
+// then brings the tokens to their places (what lies past the row's end is arbitrary and never looked at).
 __device__ __forceinline__ Tok4 load_group(const int32_t* __restrict__ x, int32_t i0, int32_t L_max) {
-    Tok4 r;
-    if (i0 + 3 < L_max) {
-        r = *reinterpret_cast<const Tok4*>(x + i0);
-    } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) r.t[j] = (i0 + j) < L_max ? x[i0 + j] : 0;
-    }
-    return r;
+    return *reinterpret_cast<const Tok4*>(x + (i0 < L_max - 4 ? i0 : L_max - 4));
 }
-constexpr int RT_AHEAD = 2;                           // chunks the loads run ahead of the scan
-constexpr int RT_LIST = 128;                          // keys the ranking list holds before the tournament takes over
-constexpr int RT_WALK = 8;                            // tokens compared per round of the backward match
-constexpr int RT_UNIT = 8 * RT_THREADS;               // tokens of a unit of the streamed scan, two groups per thread
-constexpr int RT_SLOTS = 2 * RT_AHEAD;                // units in flight
+__device__ __forceinline__ void shift_group(Tok4& g, int32_t i0, int32_t L_max) {
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+        if (r < i0 - (L_max - 4)) { g.t[0] = g.t[1]; g.t[1] = g.t[2]; g.t[2] = g.t[3]; }
+}
 
+template <int RT_THREADS>
 __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
     const int32_t* __restrict__ ctx, const int32_t* __restrict__ ctx_len, int32_t L_max,
     const int32_t* __restrict__ tail, const int32_t* __restrict__ tail_len, int32_t tail_max,
     int32_t n_min, int32_t n_max, int32_t C, int32_t m,
     int32_t* __restrict__ chain_tok, int32_t* __restrict__ chain_len, int32_t* __restrict__ chain_pos,
     int32_t* __restrict__ chain_match, int32_t* __restrict__ n_hits, int32_t* __restrict__ status) {
+    constexpr int RT_WAVES = RT_THREADS / 64, RT_CHUNK = rt_chunk(RT_THREADS), RT_AHEAD = rt_chunks(RT_THREADS);
+    constexpr int RT_UNIT = 8 * RT_THREADS;            // tokens of a unit of the streamed scan, two groups per thread
     const int b = blockIdx.x;
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    __shared__ __attribute__((aligned(16))) int32_t buf[2][RT_CHUNK];   // two context chunks
-    __shared__ int32_t q_rev[GRAFT_MAX_NGRAM + RT_WALK];   // q_rev[j] = j-th token from the end of the query (the
-                                                           // backward match reads up to RT_WALK entries past n_max - 1 and ignores them)
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    __shared__ __attribute__((aligned(16))) int32_t ring[RT_AHEAD * RT_CHUNK];   // the context; the walks wrap around at its start
+    // the query from its end, one copy per wavefront (no barrier between writing and reading it); the backward match reads
+    // up to RT_WALK entries past n_max - 1 and ignores them
+    __shared__ int32_t queries[RT_WAVES][GRAFT_MAX_NGRAM + RT_WALK];
     __shared__ u64 red[RT_WAVES * GRAFT_MAX_CHAINS];   // per-wavefront best keys
-    __shared__ u64 win[GRAFT_MAX_CHAINS];              // the C winners
-    __shared__ u64 list[RT_LIST];                      // best keys of the threads that have hits
+    __shared__ u64 winners[RT_WAVES][GRAFT_MAX_CHAINS];   // the C winners, one copy per wavefront
+    __shared__ __attribute__((aligned(16))) u64 list[RT_LIST];   // best keys of the threads that have hits, the rest zeros
     __shared__ u64 counts;                             // low word: keys appended to the list, high word: hits
     __shared__ int32_t tail_s[RT_THREADS];             // the first RT_THREADS tail tokens
 
@@ -92,20 +98,28 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
     const int32_t T = (tail != nullptr && tail_len != nullptr) ? tail_len[b] : 0;
     const int32_t* x = ctx + static_cast<size_t>(b) * L_max;
     Tok4 v[RT_AHEAD][RT_GROUPS];
+    if (L_max >= 4) {
 #pragma unroll
-    for (int k = 0; k < RT_AHEAD; ++k)
+        for (int k = 0; k < RT_AHEAD; ++k)
 #pragma unroll
-        for (int u = 0; u < RT_GROUPS; ++u) v[k][u] = load_group(x, k * RT_CHUNK + (u * RT_THREADS + tid) * 4, L_max);
+            for (int u = 0; u < RT_GROUPS; ++u)
+                if (k * RT_CHUNK + u * RT_THREADS * 4 < L_max)   // uniform: nothing is requested past the row's end
+                    v[k][u] = load_group(x, k * RT_CHUNK + (u * RT_THREADS + tid) * 4, L_max);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[0][0].t[j] = 4 * tid + j < L_max ? x[4 * tid + j] : 0;
+    }
     const int32_t tail_tok = (tail != nullptr && tid < tail_max) ? tail[static_cast<size_t>(b) * tail_max + tid] : 0;
     if (tid == 0) counts = 0;
-    if (tid < GRAFT_MAX_CHAINS) win[tid] = 0;
+    if (tid < RT_LIST) list[tid] = 0;
+    u64* win = winners[wave];
+    if (lane < GRAFT_MAX_CHAINS) win[lane] = 0;
 
     const bool bad = L < 0 || L > L_max || T < 0 || T > tail_max;
 
-    // defaults: no chain
     int32_t* tok_b = chain_tok + static_cast<size_t>(b) * C * m;
-    for (int i = tid; i < C * m; i += RT_THREADS) tok_b[i] = -1;
     if (bad) {                                   // uniform over the workgroup
+        for (int i = tid; i < C * m; i += RT_THREADS) tok_b[i] = -1;
         if (tid < C) {
             chain_len[b * C + tid] = 0;
             chain_pos[b * C + tid] = -1;
@@ -115,26 +129,29 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
         return;
     }
     const int32_t QL = L + T;
-    const int32_t nq = n_max < QL ? n_max : QL, qi = QL - 1 - tid;
-    const bool streamed = L > RT_AHEAD * RT_CHUNK;   // (then L_max is larger as well: no group above was cut short)
-    if (streamed && tid < nq) q_rev[tid] = qi < L ? x[qi] : tail[static_cast<size_t>(b) * tail_max + (qi - L)];
-    // Both chunks in flight go to LDS at once (the two buffers are a ring: the token at position p
-    // sits at flat index p mod 2 RT_CHUNK), and so do the tail tokens; the query is then read from
-    // there: no second trip to memory unless it lies beyond the first two chunks.
-    int32_t* ring = &buf[0][0];
+    const int32_t nq = n_max < QL ? n_max : QL, qi = QL - 1 - lane;
+    static_assert(GRAFT_MAX_NGRAM <= 64, "one query token per lane");
+    int32_t* q_rev = queries[wave];
+    const bool streamed = RT_THREADS == RT_MOST && L > RT_AHEAD * RT_CHUNK;   // (then L_max is larger as well: no group was cut short)
+    if (streamed && lane < nq) q_rev[lane] = qi < L ? x[qi] : tail[static_cast<size_t>(b) * tail_max + (qi - L)];
+    // Both chunks go to LDS at once (the token at position p sits at flat index p), and so do the tail tokens; the
+    // query is then read from there: no second trip to memory.
     if (!streamed) {
 #pragma unroll
         for (int k = 0; k < RT_AHEAD; ++k)
 #pragma unroll
-            for (int u = 0; u < RT_GROUPS; ++u)
-                if (k * RT_CHUNK + u * RT_THREADS * 4 < L_max)   // uniform: nothing past the row's end is ever read
-                    *reinterpret_cast<int4*>(ring + k * RT_CHUNK + (u * RT_THREADS + tid) * 4) =
-                        int4{v[k][u].t[0], v[k][u].t[1], v[k][u].t[2], v[k][u].t[3]};
+            for (int u = 0; u < RT_GROUPS; ++u) {
+                const int32_t row0 = k * RT_CHUNK + u * RT_THREADS * 4;
+                if (row0 >= L_max) continue;                     // uniform
+                if ((L_max & 3) != 0 && L_max >= 4 && row0 + 4 * RT_THREADS > L_max) shift_group(v[k][u], row0 + 4 * tid, L_max);   // uniform
+                *reinterpret_cast<int4*>(ring + row0 + tid * 4) = int4{v[k][u].t[0], v[k][u].t[1], v[k][u].t[2], v[k][u].t[3]};
+            }
     }
     tail_s[tid] = tail_tok;
     __syncthreads();
-    if (!streamed && tid < nq)
-        q_rev[tid] = qi < L ? ring[qi] : ((qi - L) < RT_THREADS ? tail_s[qi - L] : tail[static_cast<size_t>(b) * tail_max + (qi - L)]);
+    if (!streamed && lane < nq)
+        q_rev[lane] = qi < L ? ring[qi] : ((qi - L) < RT_THREADS ? tail_s[qi - L] : tail[static_cast<size_t>(b) * tail_max + (qi - L)]);
+    __builtin_amdgcn_wave_barrier();              // (a wavefront's LDS operations complete in order)
 
     u64 top[GRAFT_MAX_CHAINS];
 #pragma unroll
@@ -156,7 +173,6 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
     };
     if (streamed) {
         // ---- a context that does not fit the ring: scanned from the registers it is loaded into
-        __syncthreads();                          // q_rev visible
         const int32_t q_last = q_rev[0], q_prev = nq > 1 ? q_rev[1] : 0;
         const bool one = nq < 2 || n_max < 2;     // a query of one token
         const auto scan = [&](Tok4 (&g)[2], int32_t unit) __attribute__((always_inline)) {
@@ -205,20 +221,11 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
             for (int u = 0; u < 2; ++u) slot[s][u] = v[s >> 1][2 * (s & 1) + u];
         const auto fetch = [&](Tok4 (&g)[2], int32_t unit) __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int32_t i0 = unit * RT_UNIT + (u * RT_THREADS + tid) * 4;
-                g[u] = *reinterpret_cast<const Tok4*>(x + (i0 < L_max - 4 ? i0 : L_max - 4));
-            }
+            for (int u = 0; u < 2; ++u) g[u] = load_group(x, unit * RT_UNIT + (u * RT_THREADS + tid) * 4, L_max);
         };
-        // the row's last group, if it is not whole, was read from L_max - 4 on
         const auto shift = [&](Tok4 (&g)[2], int32_t unit) __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int32_t by = unit * RT_UNIT + (u * RT_THREADS + tid) * 4 - (L_max - 4);
-#pragma unroll
-                for (int r = 0; r < 3; ++r)
-                    if (r < by) { g[u].t[0] = g[u].t[1]; g[u].t[1] = g[u].t[2]; g[u].t[2] = g[u].t[3]; }
-            }
+            for (int u = 0; u < 2; ++u) shift_group(g[u], unit * RT_UNIT + (u * RT_THREADS + tid) * 4, L_max);
         };
         // No load in the loop is conditional: with a branch around it the compiler no longer knows how many are in
         // flight and waits for all of them.
@@ -245,7 +252,6 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
                 scan(extra[s], c + s + RT_SLOTS);
             }
     } else {
-        __syncthreads();                          // q_rev visible
 #pragma unroll
         for (int c = 0; c < RT_AHEAD; ++c) {
             if (c >= n_chunks) continue;          // uniform over the workgroup (no break: c must stay a constant)
@@ -267,7 +273,7 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
                                  (v[c][u].t[3] == q_last);
                 if (__builtin_amdgcn_ballot_w64(any) == 0) continue;
                 const int32_t ip = i0 - 1;
-                int32_t prev = ip >= 0 ? buf[(ip / RT_CHUNK) & 1][ip % RT_CHUNK] : ~q_prev;
+                int32_t prev = ip >= 0 ? ring[ip] : ~q_prev;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int32_t t = v[c][u].t[j];
@@ -292,7 +298,7 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
 #pragma unroll
                         for (int jj = 0; jj < RT_WALK; ++jj) {
                             // (positions before the buffer's start wrap to some other token of the ring: masked below)
-                            const unsigned pos = static_cast<unsigned>(e - 1 - base - jj) & (2u * RT_CHUNK - 1u);
+                            const unsigned pos = static_cast<unsigned>(e - 1 - base - jj) & (static_cast<unsigned>(RT_AHEAD * RT_CHUNK) - 1u);
                             eq |= (ring[pos] == q_rev[base + jj] && base + jj < cap) ? 1u << jj : 0u;
                         }
                         const int run = __builtin_ctz(~eq);          // matching tokens at the front of this round (<= RT_WALK)
@@ -316,19 +322,31 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
         for (int j = 0; j < GRAFT_MAX_CHAINS; ++j)
             if (j < k && off + j < RT_LIST) list[off + j] = top[j];
     }
-    __syncthreads();                              // (also orders the zeroing of win[] when no chunk was scanned)
+    __syncthreads();
     const u64 counted = counts;
     const int32_t n_list = static_cast<int32_t>(counted & 0xffffffffu);
-    if (n_list <= RT_LIST) {                      // uniform over the workgroup
-        if (tid < n_list) {
-            const u64 key = list[tid];
-            int32_t rank = 0;
-            for (int32_t i0 = 0; i0 < n_list; i0 += 8) {          // eight independent reads per round
+    if (wave * 64 >= C * m && wave > 0 && n_list <= RT_LIST) return;       // nothing to write for this wavefront
+    if (n_list <= RT_LIST) {                      // uniform over the workgroup; every wavefront ranks for itself
+        static_assert(RT_LIST == 128, "two keys per lane");
+        const u64 k0 = list[lane], k1 = list[64 + lane];
+        int32_t r0 = 0, r1 = 0;
+        for (int32_t i0 = 0; i0 < n_list; i0 += 8) {              // eight keys per round, all reads in flight
+            u64 kj[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) rank += (i0 + u < n_list && list[(i0 + u) & (RT_LIST - 1)] > key) ? 1 : 0;
+            for (int u = 0; u < 8; u += 2) {
+                const uint4 t = *reinterpret_cast<const uint4*>(&list[i0 + u]);
+                kj[u] = (static_cast<u64>(t.y) << 32) | t.x;
+                kj[u + 1] = (static_cast<u64>(t.w) << 32) | t.z;
             }
-            if (rank < C) win[rank] = key;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                r0 += kj[u] > k0 ? 1 : 0;
+                r1 += kj[u] > k1 ? 1 : 0;
+            }
         }
+        if (k0 != 0 && r0 < C) win[r0] = k0;
+        if (k1 != 0 && r1 < C) win[r1] = k1;
+        __builtin_amdgcn_wave_barrier();
     } else {
         // the list overflowed: every wavefront extracts its own best C keys (keys are unique because
         // e is, so exactly one lane owns each maximum and pops it), then wavefront 0 merges the
@@ -352,17 +370,17 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
             if (k1 > k0) { const u64 t = k0; k0 = k1; k1 = t; }
             for (int c = 0; c < C; ++c) {
                 const u64 gmax = wave_max_u64(k0);
-                if (lane == 0) win[c] = gmax;
+                if (lane < RT_WAVES) winners[lane][c] = gmax;
                 if (gmax != 0 && k0 == gmax) { k0 = k1; k1 = 0; }
             }
         }
+        __syncthreads();
     }
     if (tid == 0) {
         n_hits[b] = static_cast<int32_t>(counted >> 32);
         status[b] = 0;
     }
-    __syncthreads();
-    // ---- outputs: chain c starts at e = low word of win[c]; the last two chunks scanned are still in LDS
+    // ---- outputs: chain c starts at e = low word of win[c]; a context that fits LDS is still there
     if (tid < C) {
         const u64 key = win[tid];
         const int32_t e = static_cast<int32_t>(key & 0xffffffffu);
@@ -376,10 +394,7 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
         const int c = i / m, jj = i - c * m;
         const u64 key = win[c];
         const int32_t e = static_cast<int32_t>(key & 0xffffffffu);
-        if (key != 0 && e + jj < L) {
-            const int32_t pos = e + jj, ch = pos / RT_CHUNK;
-            tok_b[i] = !streamed && ch < n_chunks ? buf[ch & 1][pos % RT_CHUNK] : x[pos];
-        }
+        tok_b[i] = key == 0 || e + jj >= L ? -1 : (streamed ? x[e + jj] : ring[e + jj]);
     }
 }
 
@@ -397,8 +412,12 @@ extern "C" int32_t graft_retrieve(const int32_t* ctx, const int32_t* ctx_len, in
         n_max > GRAFT_MAX_NGRAM || C < 1 || C > GRAFT_MAX_CHAINS || m < 1 || m > (1 << 20) ||
         tail_max < 0 || (tail != nullptr && tail_max < 1))
         return GRAFT_ERR_SHAPE;
-    hipLaunchKernelGGL(graft::retrieve_kernel, dim3(B), dim3(graft::RT_THREADS), 0,
-                       static_cast<hipStream_t>(stream), ctx, ctx_len, L_max, tail, tail_len, tail_max,
-                       n_min, n_max, C, m, chain_tok, chain_len, chain_pos, chain_match, n_hits, status);
+    const auto launch = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(B), dim3(threads), 0, static_cast<hipStream_t>(stream), ctx, ctx_len, L_max, tail, tail_len,
+                           tail_max, n_min, n_max, C, m, chain_tok, chain_len, chain_pos, chain_match, n_hits, status);
+    };
+    if (L_max <= graft::rt_chunk(256)) launch(graft::retrieve_kernel<256>, 256);
+    else if (L_max <= graft::rt_chunk(512)) launch(graft::retrieve_kernel<512>, 512);
+    else launch(graft::retrieve_kernel<graft::RT_MOST>, graft::RT_MOST);
     return graft::check_launch();
 }

@@ -80,3 +80,24 @@ def test_bad_tree_and_overflow():
     logits = np.zeros((2, 3, 10), np.float32)
     gpu, ref = both(parent, tokens, [3, 3], 1, logits=logits)
     assert_same(gpu, ref, KEYS + ("target_ids",))
+
+
+@pytest.mark.parametrize("breaks_at", [None, 1, 31, 32, 64, 127])
+def test_long_chains_of_accepted_nodes(breaks_at):
+    """Paths through all words of the node bits; a mismatch ends the walks of everything below it."""
+    K = 128
+    parent = np.tile(np.arange(-1, K - 1, dtype=np.int32), (2, 1))
+    parent[1, 96] = 64                                                 # a second branch from node 64 on, as deep as the first
+    tokens = np.tile(np.arange(1000, 1000 + K, dtype=np.int32), (2, 1))
+    target = np.full((2, K), -1, np.int32)
+    for b in range(2):
+        for i in range(1, K):
+            if target[b, parent[b, i]] < 0:
+                target[b, parent[b, i]] = tokens[b, i]
+            else:
+                tokens[b, i] = target[b, parent[b, i]]                 # siblings that both match
+    if breaks_at is not None:
+        tokens[:, breaks_at] += 5000
+    for cap in (127, 126, 31, 0):
+        gpu, ref = both(parent, tokens, [K, K - 1], cap, target_ids=target)
+        assert_same(gpu, ref, KEYS)

@@ -66,3 +66,14 @@ def test_bad_trees_and_dirty_outputs():
     gpu = host_dict(out)
     assert_same(gpu, ref, KEYS + ("paths",))
     assert gpu["status"].tolist() == [2, 2, 2, 2, 0]
+
+
+@pytest.mark.parametrize("n_leaf_max, depth_cap", [(1, 0), (1, 4), (3, 4), (7, 6), (5, 48), (9, 10), (128, 126), (127, 127)])
+def test_path_tables_of_any_size(n_leaf_max, depth_cap):
+    """Tables whose entries are no multiple of four: sequences that start at any element, cut-off last groups."""
+    rng = np.random.default_rng(n_leaf_max * 128 + depth_cap)
+    B, K = 5, 128
+    parent = np.stack([inputs.random_recursive_tree(rng, K, int(rng.integers(3, 60))) for _ in range(B)])
+    n_nodes = np.array([128, 65, 64, 20, 1], np.int32)
+    gpu, ref = both(parent, n_nodes, rng.integers(0, 1000, B).astype(np.int32), n_leaf_max, depth_cap)
+    assert_same(gpu, ref, KEYS + ("paths",))

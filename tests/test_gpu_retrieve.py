@@ -108,3 +108,40 @@ def test_contexts_around_and_beyond_the_ring(L, n_min):
     gpu, ref = both(ctx, ctx_len, n_min, n_max, 8, 6, tail, tail_len)
     assert_same(gpu, ref, KEYS)
     assert gpu["n_hits"][0] > 0 and gpu["n_hits"][2] > 1000
+
+
+@pytest.mark.parametrize("L", [1, 2, 3, 4, 5, 7, 257, 4095, 4096, 4097, 8191, 8192, 8193, 16387])
+def test_rows_around_the_workgroup_sizes(L):
+    """256 threads scan rows of up to 4096 tokens, 512 up to 8192, 1024 what is longer; the last group of four may be cut
+    short, and the query may lie in context and tail."""
+    rng = np.random.default_rng(L)
+    B, n_max = 4, 6
+    query = rng.integers(100, 200, n_max).astype(np.int32)
+    ctx = rng.integers(0, 100, size=(B, L)).astype(np.int32)
+    ctx[3] = rng.integers(0, 20, L)
+    for b in range(3):
+        for i in {0, 1, L // 3, L - 6, L - 3, L - 2, L - 1, 1023, 1024, 4094, 4095} & set(range(L)):
+            k = int(min(i + 1, rng.integers(1, n_max + 1)))
+            ctx[b, i - k + 1:i + 1] = query[n_max - k:]
+    ctx_len = np.array([L, L - 1, max(0, L - 2), L], np.int32)
+    tail = np.tile(query, (B, 60)).astype(np.int32)                    # 360 tokens: more than the smallest workgroup has threads
+    tail_len = np.array([360, 6, 3, 0], np.int32)
+    for n_min in (1, 2):
+        gpu, ref = both(ctx, ctx_len, n_min, n_max, 8, 6, tail, tail_len)
+        assert_same(gpu, ref, KEYS)
+
+
+@pytest.mark.parametrize("hits", [0, 1, 7, 8, 9, 63, 64, 65, 127, 128, 129])
+@pytest.mark.parametrize("L", [4096, 8192, 20000])
+def test_as_many_hits_as_the_ranking_list_holds(L, hits):
+    rng = np.random.default_rng(hits)
+    ctx = rng.integers(0, 100, size=(1, L)).astype(np.int32)
+    for at in rng.permutation(L // 16 - 1)[:hits]:                     # one hit a thread at most, of one to five tokens
+        ctx[0, 16 * at + 9] = 300
+        for k in range(int(rng.integers(0, 5))):
+            ctx[0, 16 * at + 8 - k] = 299 - k
+    tail = np.array([[296, 297, 298, 299, 300]], np.int32)
+    for C, m in ((3, 8), (8, 20)):                                     # (160 tokens: three wavefronts write)
+        gpu, ref = both(ctx, np.array([L], np.int32), 1, 5, C, m, tail, np.array([5], np.int32))
+        assert_same(gpu, ref, KEYS)
+        assert gpu["n_hits"][0] == hits
