@@ -115,3 +115,18 @@ def test_compact_at_the_32k_prefix_size():
              acc=a["accept_len"], K=w.K, Hkv=w.Hkv, D=w.D, B=w.B, dtype="bf16")
     ref = _both(c)
     assert ref["new_prefix_len"][0] == w.P + a["accept_len"][0] + 1
+
+
+@pytest.mark.parametrize("rows", [1, 7, 8, 9, 63, 64, 65, 72, 127])
+@pytest.mark.parametrize("dtype,Hkv,D", [("bf16", 1, 64), ("bf16", 5, 64), ("bf16", 9, 64), ("f32", 3, 128)])
+def test_compact_at_the_edges_of_batches_and_wavefronts(rows, dtype, Hkv, D):
+    """Path lengths around the batches (8 rows) and the lanes (64); rows of 8, 40, 72 and 96 columns of 16 bytes."""
+    c = _case(rows, dtype, 2, Hkv, D, 2, (37, 16), 128, 127, Hkv == 5)
+    rng = np.random.default_rng(rows)
+    for b in range(2):
+        c["path"][b] = -1
+        c["path"][b, 0] = 0
+        c["path"][b, 1:rows + 1] = np.sort(rng.choice(np.arange(1, 128), size=rows, replace=False))
+        c["acc"][b] = rows
+    c["path"][1, rows] = 127 if rows < 127 else c["path"][1, rows]      # the last slot of the table
+    assert (_both(c)["status"] == 0).all()
