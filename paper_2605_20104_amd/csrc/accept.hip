@@ -108,7 +108,7 @@ __global__ __launch_bounds__(AC_THREADS) void accept_walk_kernel(
     __shared__ int32_t tstar[AC_THREADS];
     __shared__ int32_t link[AC_THREADS];
     __shared__ uint4 passed[AC_THREADS];         // nodes on an accepted node's path, as bits
-    __shared__ u64 red[AC_THREADS / 64];
+    __shared__ unsigned red[AC_THREADS / 64];
     __shared__ int32_t or_bad[2], or_over[2];
 
     const int32_t n = n_nodes[b];
@@ -173,11 +173,11 @@ __global__ __launch_bounds__(AC_THREADS) void accept_walk_kernel(
     passed[i] = bits;
     const int over = (ok && d > depth_cap) ? 1 : 0;
     // key: depth first, then smaller index; 0 = not a candidate (the root gives key >= 1)
-    const u64 key = (ok && d <= depth_cap) ? ((static_cast<u64>(d) << 8) | static_cast<u64>(255 - i)) : 0;
-    const u64 wmax = wave_max_u64(key);
+    const unsigned key = (ok && d <= depth_cap) ? ((static_cast<unsigned>(d) << 8) | static_cast<unsigned>(255 - i)) : 0u;
+    const unsigned wmax = wave_max_u32(key);
     if ((i & 63) == 0) red[i >> 6] = wmax;
     const bool any_over = workgroup_or_128(over != 0, or_over);
-    const unsigned best = static_cast<unsigned>(red[0] > red[1] ? red[0] : red[1]);
+    const unsigned best = red[0] > red[1] ? red[0] : red[1];
     const int32_t best_i = 255 - static_cast<int32_t>(best & 255u), best_d = static_cast<int32_t>(best >> 8);
     const uint4 on = passed[best_i];
     const unsigned words[4] = {on.x, on.y, on.z, on.w};

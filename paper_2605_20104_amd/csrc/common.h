@@ -95,6 +95,43 @@ __device__ __forceinline__ float wave_max_f32(float v) {
     return v;
 }
 
+// Maximum of a 32-bit number over one 64-lane wavefront (all lanes get it); same steps again.
+template <int DPP_CTRL>
+__device__ __forceinline__ unsigned max_dpp_u32(unsigned v) {
+    const unsigned o = static_cast<unsigned>(__builtin_amdgcn_update_dpp(static_cast<int>(v), static_cast<int>(v), DPP_CTRL, 0xf, 0xf, false));
+    return o > v ? o : v;
+}
+__device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
+    v = max_dpp_u32<0xB1>(v);
+    v = max_dpp_u32<0x4E>(v);
+    v = max_dpp_u32<0x141>(v);
+    v = max_dpp_u32<0x140>(v);
+    {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        v = r[0] > r[1] ? r[0] : r[1];
+    }
+    {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        v = r[0] > r[1] ? r[0] : r[1];
+    }
+    return v;
+}
+
+// wave_max_u64 for keys whose upper words hardly ever agree: their maximum decides (one instruction a step
+// instead of five), the lower words are compared only where several lanes have it.  In the matrix refresh, which takes
+// k of them per chunk and per row, us a call in a graph: 8 x 96 rows of 32000 logits 50.3 -> 48.1, 8 x 24 18.6 -> 18.0.
+__device__ __forceinline__ u64 wave_max_key(u64 v) {
+    const unsigned hi = static_cast<unsigned>(v >> 32), lo = static_cast<unsigned>(v);
+    const unsigned top = wave_max_u32(hi);
+    const u64 at = __builtin_amdgcn_ballot_w64(hi == top);           // never empty
+    unsigned low;
+    if ((at & (at - 1)) == 0)                                        // uniform
+        low = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(lo), __builtin_ctzll(at)));
+    else
+        low = wave_max_u32(hi == top ? lo : 0u);
+    return (static_cast<u64>(top) << 32) | low;
+}
+
 // Maximum over the four lanes l, l + 16, l + 32, l + 48 (the four 16-lane rows of a wavefront),
 // all four get it: the two lane swaps of gfx950, no trip through the LDS crossbar.
 __device__ __forceinline__ float rows_max_f32(float v) {

@@ -247,7 +247,7 @@ __global__ __launch_bounds__(MU_THREADS) void topk_chunk_kernel(
                     for (int t = 0; t + 1 < 4 - a; ++t)
                         if (c4[t + 1] > c4[t]) { const u64 sw = c4[t]; c4[t] = c4[t + 1]; c4[t + 1] = sw; }
                 for (int j = 0; j < k; ++j) {
-                    const u64 gmax = wave_max_u64(c4[0]);
+                    const u64 gmax = wave_max_key(c4[0]);
                     if (lane == 0) out[j] = gmax;
                     if (gmax != 0 && c4[0] == gmax) { c4[0] = c4[1]; c4[1] = c4[2]; c4[2] = c4[3]; c4[3] = 0; }
                 }
@@ -316,7 +316,7 @@ __global__ __launch_bounds__(64) void matrix_update_merge_kernel(
     }
     const bool write_row = x >= 0 && x < V && __builtin_amdgcn_ballot_w64(later) == 0;
     for (int j = 0; j < k; ++j) {
-        const u64 gmax = wave_max_u64(c[0]);
+        const u64 gmax = wave_max_key(c[0]);
         if (lane == 0) {
             const int32_t id = gmax != 0 ? key_id(gmax) : -1;
             if (j == 0) target_ids[node] = id;
