@@ -9,13 +9,18 @@
 // than that takes one round per depth through LDS.  A node's place in the (score, index) order
 // is counted directly: score and index make one 64-bit key (the float's bits made monotonic,
 // then the index so that equal scores keep index order, parents before children), a node's rank
-// is the number of larger keys - one 64-bit compare per pair, no sort.
+// is the number of larger keys - one 64-bit compare per pair, no sort.  What the two wavefronts have to
+// know of each other (gates opened, candidates, nodes kept) they exchange as ballots, one barrier each; a kept node writes its own entry of the new tree.  us a call in a graph: one tree of 24 nodes
+// 4.29 -> 3.45, 4 of 60 5.87 -> 3.91, 16 of 120 7.68 -> 4.54 (LDS atomics, nine barriers, tokens looked up at the end in
+// a trip of their own, and eight keys per round of the count before).
 #include "common.h"
 
 namespace graft {
 
 constexpr int PS_THREADS = GRAFT_MAX_NODES;
 constexpr int PS_PATH = 16;                        // ancestors a thread records (deeper trees: rounds)
+constexpr int PS_READ = 32;                        // keys read at once by the count
+static_assert(PS_THREADS == 128 && PS_THREADS % PS_READ == 0 && GRAFT_MAX_CHECKPOINTS < 31, "two wavefronts; gates fit a word");
 
 __global__ __launch_bounds__(PS_THREADS) void prune_select_kernel(
     const int32_t* __restrict__ parent, const int32_t* __restrict__ tokens, const float* __restrict__ logq,
@@ -31,36 +36,34 @@ __global__ __launch_bounds__(PS_THREADS) void prune_select_kernel(
     __shared__ float S[PS_THREADS];                                     // scores (deep trees only)
     __shared__ __attribute__((aligned(16))) unsigned char anc[PS_THREADS][PS_PATH];   // anc[i][k]: ancestor at distance k
     __shared__ __attribute__((aligned(16))) u64 keys[PS_THREADS];
-    __shared__ int32_t newi[PS_THREADS];
-    __shared__ int32_t old_of[PS_THREADS];
-    __shared__ int32_t wave_cnt[PS_THREADS / 64];
-    __shared__ int32_t c_depth[GRAFT_MAX_CHECKPOINTS], c_keep[GRAFT_MAX_CHECKPOINTS], c_ret[GRAFT_MAX_CHECKPOINTS];
-    __shared__ float c_tau[GRAFT_MAX_CHECKPOINTS];
-    __shared__ unsigned gates_open, any_deep, orphan;
-    __shared__ int32_t n_cand_s;
-    __shared__ int32_t or_bad[2];
+    __shared__ unsigned open_s[PS_THREADS / 64];                        // a wavefront's gates, bit 31: deep nodes
+    __shared__ int32_t cand_s[PS_THREADS / 64];
+    __shared__ u64 kept_s[PS_THREADS / 64];
+    __shared__ int32_t or_bad[2], or_orphan[2];
     const size_t row = static_cast<size_t>(b) * K_max;
 
-    // every input is requested at once: one trip to memory (the checkpoint parameters included,
-    // thread c takes checkpoint c)
+    // every input is requested at once: one trip to memory (tokens and the checkpoint parameters included; lane
+    // c of each wavefront holds checkpoint c)
     const int32_t n = n_nodes[b];
     const bool n_ok = n >= 1 && n <= K_max;
     const int32_t p = i < K_max ? parent[row + i] : -1;
     const float lq_in = i < K_max ? logq[row + i] : 0.0f;
-    if (i < n_chk) {
-        c_depth[i] = chk_depth[i];
-        c_tau[i] = chk_log_tau[i];
-        c_keep[i] = chk_keep[i];
-        c_ret[i] = chk_ret[i];
+    const int32_t tok = i < K_max ? tokens[row + i] : -1;
+    int32_t c_depth = 0, c_keep = 0, c_ret = 0;
+    float c_tau = 0.0f;
+    if (lane < n_chk) {
+        c_depth = chk_depth[lane];
+        c_tau = chk_log_tau[lane];
+        c_keep = chk_keep[lane];
+        c_ret = chk_ret[lane];
     }
-    if (i == 0) { gates_open = 0u; any_deep = 0u; orphan = 0u; n_cand_s = 0; }
     bool bad = !n_ok;
     if (n_ok && i < n) bad = (i == 0) ? (p != -1) : (p < 0 || p >= i);
     par[i] = p;
     lqs[i] = (i > 0 && n_ok && i < n) ? lq_in : 0.0f;
-    int any_bad = workgroup_or_128(bad, or_bad) ? 1 : 0;
+    bool any_bad = workgroup_or_128(bad, or_bad);
 
-    int32_t st = -1, cnt = 0, nret = 0;
+    int32_t st = -1, cnt = 0, nret = 0, rank = 0, up = -1;
     bool kept = false;
     if (!any_bad) {
         // depth by a walk up, which also records the ancestors: anc[i][0] = i, ..., anc[i][d] = 0
@@ -71,11 +74,9 @@ __global__ __launch_bounds__(PS_THREADS) void prune_select_kernel(
                 if (d < PS_PATH) anc[i][d] = static_cast<unsigned char>(j);
             }
         }
-        if (i < n && d >= PS_PATH) any_deep = 1u;            // same value from every writer
-        __syncthreads();
+        // S_i = (((0 + q[a_{d-1}]) + q[a_{d-2}]) + ...) + q[a_0]: the additions of the definition, in its order
         float s_i = 0.0f;
-        if (any_deep == 0u) {                                // uniform
-            // S_i = (((0 + q[a_{d-1}]) + q[a_{d-2}]) + ...) + q[a_0]: the additions of the definition, in its order
+        {
             const uint4 a4 = *reinterpret_cast<const uint4*>(&anc[i][0]);
             const unsigned aw[4] = {a4.x, a4.y, a4.z, a4.w};
             float q[PS_PATH];
@@ -84,26 +85,41 @@ __global__ __launch_bounds__(PS_THREADS) void prune_select_kernel(
 #pragma unroll
             for (int k = PS_PATH - 1; k >= 0; --k)
                 if (k < d) s_i += q[k];
-        } else {
-            // a tree deeper than the recorded paths: one round per depth
+        }
+        // gate c is open when some node of its depth has a score above its threshold; the first
+        // closed gate is the stage.  All gates at once, behind one barrier.
+        auto opened = [&]() {
+            unsigned open = 0u;
+            for (int32_t c = 0; c < n_chk; ++c) {
+                const int32_t depth_c = __builtin_amdgcn_readlane(c_depth, c);
+                const float tau_c = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c_tau), c));
+                if (__builtin_amdgcn_ballot_w64(i < n && d == depth_c && s_i > tau_c) != 0) open |= 1u << c;
+            }
+            return open;
+        };
+        unsigned open = opened();
+        if (__builtin_amdgcn_ballot_w64(i < n && d >= PS_PATH) != 0) open |= 1u << 31;
+        if (lane == 0) open_s[wave] = open;
+        __syncthreads();
+        open = open_s[0] | open_s[1];
+        if (open >> 31) {                                    // uniform
+            // a tree deeper than the recorded paths: one round per depth, then the gates again
             if (i == 0) S[0] = 0.0f;
             for (int32_t r = 1; __syncthreads_or(d >= r ? 1 : 0); ++r)
                 if (d == r) S[i] = S[p] + lqs[i];
             // the barrier that ended the loop also made the last round's scores visible
             s_i = i < n ? S[i] : 0.0f;
+            open = opened();
+            if (lane == 0) open_s[wave] = open;
+            __syncthreads();
+            open = open_s[0] | open_s[1];
         }
-        // gate c is open when some node of its depth has a score above its threshold; the first
-        // closed gate is the stage.  All gates at once: the nodes set the bits of the gates they open.
-        unsigned mine = 0u;
-        for (int32_t c = 0; c < n_chk; ++c)
-            if (i < n && d == c_depth[c] && s_i > c_tau[c]) mine |= 1u << c;
-        if (mine != 0u) atomicOr(&gates_open, mine);
-        __syncthreads();
-        st = __builtin_ctz(~gates_open | (1u << n_chk));     // first gate that nobody opened, n_chk if none
+        st = __builtin_ctz(~open | (1u << n_chk));           // first gate that nobody opened, n_chk if none
         // A closed gate ends the draft tree at its checkpoint (Sec. 3.1; App. A Alg. 2 prunes at
         // the stage's depth before it keeps the best K_draft): only nodes of depth <= dlim are
         // candidates.  Non-candidates get the key 0, below every candidate's.
-        const int32_t dlim = st == n_chk ? K_max : c_depth[st];
+        const int32_t sl = __builtin_amdgcn_readfirstlane(st);   // (lane n_chk holds zeros, which are not used)
+        const int32_t dlim = st == n_chk ? K_max : __builtin_amdgcn_readlane(c_depth, sl);
         const bool cand = i < n && d <= dlim;
         // (score, index) as one key: the float's bits made monotonic (scores are NaN-free; -0 is
         // folded into +0 first), then the index complemented so that a smaller index ranks higher
@@ -111,57 +127,59 @@ __global__ __launch_bounds__(PS_THREADS) void prune_select_kernel(
         const unsigned mono = (sb & 0x80000000u) ? ~sb : (sb | 0x80000000u);
         const u64 key = cand ? ((static_cast<u64>(mono) << 32) | static_cast<u64>(0xffffffffu - static_cast<unsigned>(i))) : 0ull;
         keys[i] = key;
-        if (cand) atomicAdd(&n_cand_s, 1);
+        const u64 cands = __builtin_amdgcn_ballot_w64(cand);
+        if (lane == 0) cand_s[wave] = __popcll(cands);
         __syncthreads();
-        const int32_t n_cand = n_cand_s;
-        int32_t keep = st == n_chk ? n : c_keep[st];
+        const int32_t n_cand = cand_s[0] + cand_s[1];
+        int32_t keep = st == n_chk ? n : __builtin_amdgcn_readlane(c_keep, sl);
         keep = keep > n_cand ? n_cand : keep;
         keep = keep < 1 ? 1 : keep;
-        nret = st == n_chk ? 0 : c_ret[st];
-        if (cand) {
-            int32_t before = 0;
-            for (int32_t j0 = 0; j0 < n; j0 += 8) {          // eight keys per round of (broadcast) LDS reads
-                u64 kj[8];
+        nret = st == n_chk ? 0 : __builtin_amdgcn_readlane(c_ret, sl);
+        int32_t before = 0;
+        for (int32_t j0 = 0; j0 < n; j0 += PS_READ) {        // (slots past n hold the key 0)
+            u64 kj[PS_READ];
 #pragma unroll
-                for (int u = 0; u < 8; u += 2) {
-                    const uint4 t = *reinterpret_cast<const uint4*>(&keys[(j0 + u) & (PS_THREADS - 1)]);
-                    kj[u] = (static_cast<u64>(t.y) << 32) | t.x;
-                    kj[u + 1] = (static_cast<u64>(t.w) << 32) | t.z;
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) before += (j0 + u < n && kj[u] > key) ? 1 : 0;
+            for (int u = 0; u < PS_READ; u += 2) {
+                const uint4 t = *reinterpret_cast<const uint4*>(&keys[j0 + u]);
+                kj[u] = (static_cast<u64>(t.y) << 32) | t.x;
+                kj[u + 1] = (static_cast<u64>(t.w) << 32) | t.z;
             }
-            kept = before < keep;
+#pragma unroll
+            for (int u = 0; u < PS_READ; ++u) before += kj[u] > key ? 1 : 0;
         }
-        // new index = number of kept nodes with a smaller old index
-        const u64 ballot = __ballot(kept);
-        if (lane == 0) wave_cnt[wave] = __popcll(ballot);
+        kept = cand && before < keep;
+        // new index = number of kept nodes with a smaller old index, for the parent too: from the kept nodes' bits
+        const u64 ballot = __builtin_amdgcn_ballot_w64(kept);
+        if (lane == 0) kept_s[wave] = ballot;
         __syncthreads();
-        int32_t rank = __popcll(ballot & ((1ull << lane) - 1));
-        if (wave == 1) rank += wave_cnt[0];
-        cnt = wave_cnt[0] + wave_cnt[1];
-        newi[i] = kept ? rank : -1;
-        if (kept) old_of[rank] = i;
-        __syncthreads();
-        if (kept && i > 0 && newi[p] < 0) orphan = 1u;       // a kept node lost its parent
-        __syncthreads();
-        any_bad = orphan != 0u ? 1 : 0;
+        const u64 k_lo = kept_s[0], k_hi = kept_s[1];
+        auto place = [&](int32_t j) {
+            const u64 below = (1ull << (j & 63)) - 1;
+            return j < 64 ? __popcll(k_lo & below) : __popcll(k_lo) + __popcll(k_hi & below);
+        };
+        cnt = __popcll(k_lo) + __popcll(k_hi);
+        rank = place(i);
+        bool orphan = false;                                 // a kept node lost its parent
+        if (kept && i > 0) {
+            up = place(p);
+            orphan = (((p < 64 ? k_lo : k_hi) >> (p & 63)) & 1ull) == 0;
+        }
+        any_bad = workgroup_or_128(orphan, or_orphan);
     }
     if (any_bad) {
         if (i < K_max) { out_parent[row + i] = -1; out_tokens[row + i] = -1; out_index[row + i] = -1; }
         if (i == 0) { out_n_nodes[b] = 0; stage[b] = -1; n_ret[b] = 0; status[b] = GRAFT_STATUS_BAD_TREE; }
         return;
     }
-    if (i < K_max) {                                  // thread i writes entry i of the new tree
-        int32_t oi = -1, ot = -1, op = -1;
-        if (i < cnt) {
-            oi = old_of[i];
-            ot = tokens[row + oi];
-            op = oi == 0 ? -1 : newi[par[oi]];
-        }
-        out_index[row + i] = oi;
-        out_tokens[row + i] = ot;
-        out_parent[row + i] = op;
+    if (kept) {                                       // a kept node writes its own entry of the new tree
+        out_index[row + rank] = i;
+        out_tokens[row + rank] = tok;
+        out_parent[row + rank] = up;
+    }
+    if (i >= cnt && i < K_max) {
+        out_index[row + i] = -1;
+        out_tokens[row + i] = -1;
+        out_parent[row + i] = -1;
     }
     if (i == 0) { out_n_nodes[b] = cnt; stage[b] = st; n_ret[b] = nret; status[b] = 0; }
 }

@@ -74,3 +74,17 @@ def test_prune_select_error_paths():
     # (checkpoint at depth 2, so that the node whose positive log q lifts it above its parent is a candidate)
     ref = _both(parent, np.zeros((4, 4), np.int32), logq, [4, 4, 5, 4], [2], [0.0], [2], [7])
     assert ref["status"].tolist() == [graft.GRAFT_STATUS_BAD_TREE] * 4
+
+
+@pytest.mark.parametrize("n", [31, 32, 33, 63, 64, 65, 97, 127, 128])
+def test_prune_select_at_the_edges_of_counts_and_recorded_paths(n):
+    """Node counts around the count's reads (32 keys) and the wavefronts (64); depths around the 16 recorded ancestors."""
+    rng = np.random.default_rng(n)
+    deepest = (15, 16, 17)
+    parent = np.stack([np.concatenate([np.arange(-1, d), rng.integers(0, d + 1, 128 - d - 1)])[:128] for d in deepest]).astype(np.int32)
+    parent[:, n:] = -1
+    parent[:, 0] = -1
+    tokens = rng.integers(0, 150000, (3, 128)).astype(np.int32)
+    logq = -np.round(rng.random((3, 128)) * 4).astype(np.float32) / 4                # many equal scores
+    for log_tau in ([-50.0, -50.0], [-50.0, 0.5], [0.5, 0.5]):
+        _both(parent, tokens, logq, [n] * 3, [1, 15], log_tau, [n // 3, n // 2], [3, 5])
