@@ -54,7 +54,7 @@ extern "C" {
 #define GRAFT_MAX_CHAINS  8     /* C: chains returned per sequence                  */
 #define GRAFT_MAX_NGRAM   32    /* n_max: longest suffix matched                    */
 #define GRAFT_PAGE_SIZE   16    /* tokens per KV page                               */
-#define GRAFT_ARGMAX_CHUNKS 16  /* vocabulary chunks per logits row in graft_accept */
+#define GRAFT_ARGMAX_CHUNKS 16  /* most vocabulary chunks per logits row in graft_accept */
 #define GRAFT_MAX_SUCCESSORS 16 /* k: successors per row of the transition matrix   */
 #define GRAFT_MAX_CHECKPOINTS 16 /* pruning checkpoints per call                     */
 
@@ -257,8 +257,8 @@ int32_t graft_accept(const int32_t* parent, const int32_t* tokens, const int32_t
  * graft_accept_noalloc - graft_accept for callers that cannot allocate device memory or
  * carry a workspace: code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc.  Same arguments, outputs, status flags and error codes as graft_accept
- * without the workspace pair.  In logits mode the argmax partials (one (value, index) pair
- * per GRAFT_ARGMAX_CHUNKS-th of every logits row) go to a 1 MiB array that is part of the
+ * without the workspace pair.  In logits mode the argmax partials (up to GRAFT_ARGMAX_CHUNKS
+ * (value, index) pairs for every logits row) go to a 1 MiB array that is part of the
  * library's device image (each GPU the library runs on holds its own copy until the process
  * ends); its address is looked up on the first call per device, on the calling thread's
  * current device.  The call allocates nothing and frees nothing.

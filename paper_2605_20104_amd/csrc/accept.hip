@@ -1,7 +1,7 @@
 // graft_accept: greedy acceptance walk over the verified hybrid tree.
 //
 // Two kernels.  In logits mode an argmax kernel scans every node's logits row
-// once (an HBM scan: V*4 bytes per node), GRAFT_ARGMAX_CHUNKS workgroups per row
+// once (an HBM scan: V*4 bytes per node), up to GRAFT_ARGMAX_CHUNKS workgroups per row
 // so that even one sequence fills the chip; each writes its chunk's (value,
 // first index) to the workspace.  The walk kernel (one 128-thread workgroup per
 // sequence, one thread per node) folds the chunk partials into the target's
@@ -16,6 +16,7 @@ namespace graft {
 constexpr int AM_THREADS = 256;
 constexpr int AM_WAVES = AM_THREADS / 64;
 constexpr int AM_QUADS = 12;                     // 16-byte loads in flight per thread: a whole chunk up to V = 196608
+static_assert(AM_QUADS * AM_THREADS >= ROW_QUADS, "a chunk of the cut is one round");
 constexpr int AC_THREADS = GRAFT_MAX_NODES;
 
 struct ArgPartial { float val; int32_t idx; };
@@ -32,20 +33,21 @@ __device__ __forceinline__ void arg_take(float& bv, int32_t& bi, float v, int32_
 // element before.
 __global__ __launch_bounds__(AM_THREADS) void argmax_chunk_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ n_nodes, int32_t K_max, int32_t V,
-    ArgPartial* __restrict__ partial) {
+    int32_t per, ArgPartial* __restrict__ partial) {
+    const int chunks = gridDim.x;
     const int chunk = blockIdx.x, i = blockIdx.y, b = blockIdx.z;
     const int tid = threadIdx.x;
-    ArgPartial* out = partial + (static_cast<size_t>(b) * K_max + i) * GRAFT_ARGMAX_CHUNKS + chunk;
+    ArgPartial* out = partial + (static_cast<size_t>(b) * K_max + i) * chunks + chunk;
     const int32_t n = n_nodes[b];
     if (i >= n || n > K_max) {                   // padding node: nothing to scan
         if (tid == 0) { out->val = -INFINITY; out->idx = 0x7fffffff; }
         return;
     }
     const float* row = logits + (static_cast<size_t>(b) * K_max + i) * V;
-    const RowChunk c = row_chunk(row, V, chunk);
-    __shared__ float sv[AM_WAVES + 4];
-    __shared__ int32_t si[AM_WAVES + 4];
-    if (tid < c.edge) { sv[AM_WAVES + tid] = row[c.edge_at + tid]; si[AM_WAVES + tid] = c.edge_at + tid; }
+    const RowChunk c = row_chunk(row, V, chunk, chunks, per);
+    __shared__ float sv[AM_WAVES + ROW_EDGES];
+    __shared__ int32_t si[AM_WAVES + ROW_EDGES];
+    if (tid < c.edge) { sv[AM_WAVES + tid] = row[c.edge_at(tid)]; si[AM_WAVES + tid] = c.edge_at(tid); }
     float bv = -INFINITY;                        // the wavefront's maximum so far and its first index
     int32_t bi = 0x7fffffff;
     for (int32_t s0 = c.q0; s0 < c.q1; s0 += AM_QUADS * AM_THREADS) {
@@ -99,7 +101,7 @@ __global__ __launch_bounds__(AM_THREADS) void argmax_chunk_kernel(
 // bits below it), where one thread used to walk the path again.
 __global__ __launch_bounds__(AC_THREADS) void accept_walk_kernel(
     const int32_t* __restrict__ parent, const int32_t* __restrict__ tokens,
-    const int32_t* __restrict__ n_nodes, const ArgPartial* __restrict__ partial,
+    const int32_t* __restrict__ n_nodes, const ArgPartial* __restrict__ partial, int32_t chunks,
     int32_t* __restrict__ target_ids, int32_t K_max, int32_t depth_cap,
     int32_t* __restrict__ accept_len, int32_t* __restrict__ best_node, int32_t* __restrict__ path,
     int32_t* __restrict__ out_tokens, int32_t* __restrict__ status) {
@@ -123,7 +125,7 @@ __global__ __launch_bounds__(AC_THREADS) void accept_walk_kernel(
     ArgPartial pr[GRAFT_ARGMAX_CHUNKS];
     if (partial && i < K_max) {
 #pragma unroll
-        for (int c = 0; c < GRAFT_ARGMAX_CHUNKS; ++c) pr[c] = partial[(row + i) * GRAFT_ARGMAX_CHUNKS + c];
+        for (int c = 0; c < GRAFT_ARGMAX_CHUNKS; ++c) pr[c] = partial[(row + i) * chunks + (c < chunks ? c : 0)];   // (one read again does no harm)
     }
     bool bad = !n_ok;
     if (n_ok && i < n) bad = (i == 0) ? (p != -1) : (p < 0 || p >= i);
@@ -239,15 +241,18 @@ static int32_t accept_impl(const int32_t* parent, const int32_t* tokens, const i
                            int32_t depth_cap, int32_t* accept_len, int32_t* best_node, int32_t* path,
                            int32_t* out_tokens, int32_t* status, ArgPartial* ws, hipStream_t s) {
     const ArgPartial* partial = nullptr;
+    int32_t chunks = 0;
     if (logits) {
-        hipLaunchKernelGGL(argmax_chunk_kernel, dim3(GRAFT_ARGMAX_CHUNKS, K_max, B), dim3(AM_THREADS), 0, s,
-                           logits, n_nodes, K_max, V, ws);
+        const RowCut cut = row_cut(static_cast<int64_t>(B) * K_max, V);
+        chunks = cut.chunks;
+        hipLaunchKernelGGL(argmax_chunk_kernel, dim3(chunks, K_max, B), dim3(AM_THREADS), 0, s, logits, n_nodes, K_max, V,
+                           cut.per, ws);
         int32_t rc = check_launch();
         if (rc != GRAFT_OK) return rc;
         partial = ws;
     }
     hipLaunchKernelGGL(accept_walk_kernel, dim3(B), dim3(AC_THREADS), 0, s, parent, tokens, n_nodes, partial,
-                       target_ids, K_max, depth_cap, accept_len, best_node, path, out_tokens, status);
+                       chunks, target_ids, K_max, depth_cap, accept_len, best_node, path, out_tokens, status);
     return check_launch();
 }
 

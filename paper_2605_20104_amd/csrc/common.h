@@ -150,28 +150,52 @@ __device__ __forceinline__ float rows_max_f32(float v) {
 
 // A logits row cut for 16-byte loads whatever its length and address: `head` elements up to the first
 // 16-byte boundary, `quads` aligned groups of four, `tail` elements behind them.  The groups are dealt to
-// GRAFT_ARGMAX_CHUNKS workgroups, the edges (at most three elements each) go to the first and the
+// `chunks` workgroups, `per` to each, the edges (at most three elements each) go to the first and the
 // last of them, one element per thread.  Rows of an odd length used to be read
 // element by element: 8 x 48 rows of 151937 took 84 us in the acceptance, 46 now, as rows of 151936 do;
-// 8 x 64 rows of 50257 took 86 us in the matrix refresh, 40 now (logits from memory, not from a cache).
+// 8 x 64 rows of 50257 took 86 us in the matrix refresh, 40 then (logits from memory, not from a cache).
 struct RowChunk {
     const float4* quad;      // aligned
     int32_t head, q0, q1;    // this workgroup's groups; group q starts at element head + 4 q
-    int32_t edge;            // number of edge elements of this workgroup (threads 0 .. edge - 1), first one's index
-    int32_t edge_at;
+    int32_t edge;            // number of edge elements of this workgroup (threads 0 .. edge - 1), at most six
+    int32_t edge_head, behind;
+    __device__ __forceinline__ int32_t edge_at(int32_t t) const { return t < edge_head ? t : behind + t - edge_head; }
 };
-__device__ __forceinline__ RowChunk row_chunk(const float* row, int32_t V, int chunk) {
+constexpr int ROW_EDGES = 6;
+__device__ __forceinline__ RowChunk row_chunk(const float* row, int32_t V, int chunk, int chunks, int32_t per) {
     const int32_t to_boundary = static_cast<int32_t>((16 - (reinterpret_cast<size_t>(row) & 15)) & 15) / 4;
     RowChunk c;
     c.head = to_boundary < V ? to_boundary : V;
-    const int32_t quads = (V - c.head) / 4, per = (quads + GRAFT_ARGMAX_CHUNKS - 1) / GRAFT_ARGMAX_CHUNKS;
+    const int32_t quads = (V - c.head) / 4;
     c.quad = reinterpret_cast<const float4*>(row + c.head);
     c.q0 = chunk * per < quads ? chunk * per : quads;
     c.q1 = c.q0 + per < quads ? c.q0 + per : quads;
-    const int32_t behind = c.head + 4 * quads;
-    c.edge = chunk == 0 ? c.head : (chunk == GRAFT_ARGMAX_CHUNKS - 1 ? V - behind : 0);
-    c.edge_at = chunk == 0 ? 0 : behind;
+    c.behind = c.head + 4 * quads;
+    c.edge_head = chunk == 0 ? c.head : 0;
+    c.edge = c.edge_head + (chunk == chunks - 1 ? V - c.behind : 0);
     return c;
+}
+
+// Workgroups per row of a scan of `rows` rows, and groups per workgroup.  A workgroup of the scans costs the same set-up and
+// selection whatever it holds, so a row goes to as few as take ROW_QUADS groups each (every row went to
+// GRAFT_ARGMAX_CHUNKS), but to as many as it takes to give the chip ROW_FILL workgroups where the rows are few.
+// us a call in a graph, matrix refresh with k = 8 / acceptance, 16 workgroups a row -> this rule:
+//   16 x 128 rows of 8000 111.4 -> 22.0 / 43.5 -> 16.0    8 x 96 rows of 32000 52.4 -> 27.2 / 23.1 -> 22.3
+//   8 x 24 rows of 32000 19.7 -> 14.3 / 10.4 -> 9.8       16 x 64 rows of 60001 73.0 -> 50.3 / 45.6 -> 44.9
+//   1 x 40 rows of 128256, 8 x 48 of 151936 and 16 x 128 of 128256 (16 workgroups a row either way) as before.
+// ROW_QUADS: all 12 loads of a thread in use (3072) make the refresh of 16 x 128 rows of 128256 180 us instead of 170
+// (11 workgroups a row; they select while nobody loads), 1536 groups that of 16 x 64 rows of 32000 36.4 instead of 32.1.
+// ROW_FILL: with 2048 and 4096 the refresh of 8 x 24 rows of 32000 takes 16.9 and 19.2 us, with 1024 14.3.
+constexpr int32_t ROW_QUADS = 8 * 256;
+constexpr int64_t ROW_FILL = 1024;
+struct RowCut { int32_t chunks, per; };
+inline RowCut row_cut(int64_t rows, int32_t V) {
+    const int32_t quads = V / 4;
+    int64_t chunks = (quads + ROW_QUADS - 1) / ROW_QUADS;
+    const int64_t fill = (ROW_FILL + rows - 1) / rows;
+    if (chunks < fill) chunks = fill;
+    if (chunks > GRAFT_ARGMAX_CHUNKS) chunks = GRAFT_ARGMAX_CHUNKS;
+    return {static_cast<int32_t>(chunks), static_cast<int32_t>((quads + chunks - 1) / chunks)};
 }
 
 }  // namespace graft

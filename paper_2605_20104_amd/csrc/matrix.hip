@@ -8,7 +8,7 @@
 // round trips (nine for the paper's templates), not by bandwidth.
 //
 // The refresh ranks every verified node's logits row.  Like the argmax of the acceptance
-// step it is one HBM scan of the logits (4 V bytes per node): GRAFT_ARGMAX_CHUNKS workgroups
+// step it is one HBM scan of the logits (4 V bytes per node): up to GRAFT_ARGMAX_CHUNKS workgroups
 // per row; a workgroup finds a threshold from its threads' maxima, collects the few elements
 // above it and picks its chunk's k best from those in k rounds.  A key packs (logit,
 // id) into 64 bits so that "larger logit first, then smaller id" is one unsigned compare.
@@ -108,7 +108,7 @@ __device__ __forceinline__ void topk_insert(u64 (&top)[KK], float& worst, float 
 // The scan of one thread's share of a chunk: take(value, id) for every element.
 template <class Take>
 __device__ __forceinline__ void scan_chunk(const float* __restrict__ row, const RowChunk& c, int tid, Take&& take) {
-    if (tid < c.edge) take(row[c.edge_at + tid], c.edge_at + tid);
+    if (tid < c.edge) take(row[c.edge_at(tid)], c.edge_at(tid));
     constexpr int U = 4;                            // 16-byte loads in flight per thread
     for (int32_t qd = c.q0 + tid; qd < c.q1; qd += U * MU_THREADS) {
         float4 x[U];
@@ -170,22 +170,24 @@ __device__ __forceinline__ int select_rounds(u64 (&top)[KK], int k, u64 (&red)[2
 // If the list overflows (long runs of equal values) or the chunk does not fit, the
 // workgroup takes the exact streaming path: per-thread sorted lists of KK >= k keys.
 constexpr int MU_REG_QUADS = 12;                    // covers V <= 196608
+static_assert(MU_REG_QUADS * MU_THREADS >= ROW_QUADS, "a chunk of the cut fits the registers");
 constexpr int MU_LIST = 256;                        // four candidates per lane of the last wavefront
 
 template <int KK>
 __global__ __launch_bounds__(MU_THREADS) void topk_chunk_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ n_nodes, int32_t K_max, int32_t V,
-    int32_t k, u64* __restrict__ partial) {
+    int32_t per, int32_t k, u64* __restrict__ partial) {
+    const int chunks = gridDim.x;
     const int chunk = blockIdx.x, i = blockIdx.y, b = blockIdx.z;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    u64* out = partial + ((static_cast<size_t>(b) * K_max + i) * GRAFT_ARGMAX_CHUNKS + chunk) * k;
+    u64* out = partial + ((static_cast<size_t>(b) * K_max + i) * chunks + chunk) * k;
     const int32_t n = n_nodes[b];
     if (i >= n || n > K_max) {                      // padding node
         if (tid < k) out[tid] = 0;
         return;
     }
     const float* row = logits + (static_cast<size_t>(b) * K_max + i) * V;
-    const RowChunk c = row_chunk(row, V, chunk);
+    const RowChunk c = row_chunk(row, V, chunk, chunks, per);
     const int32_t q0 = c.q0, q1 = c.q1;
     __shared__ u64 red[2][MU_WAVES];
     __shared__ u64 list[MU_LIST];
@@ -194,7 +196,7 @@ __global__ __launch_bounds__(MU_THREADS) void topk_chunk_kernel(
     bool exact = true;
     if (q1 - q0 <= MU_REG_QUADS * MU_THREADS) {                      // uniform over the workgroup
         float4 x[MU_REG_QUADS];
-        const float xe = tid < c.edge ? row[c.edge_at + tid] : -INFINITY;
+        const float xe = tid < c.edge ? row[c.edge_at(tid)] : -INFINITY;
 #pragma unroll
         for (int u = 0; u < MU_REG_QUADS; ++u) {
             const int32_t qu = q0 + tid + u * MU_THREADS;
@@ -218,7 +220,7 @@ __global__ __launch_bounds__(MU_THREADS) void topk_chunk_kernel(
         const float T = __builtin_fmaxf(__builtin_fmaxf(tws[0], tws[1]), __builtin_fmaxf(tws[2], tws[3]));
         if (tid < c.edge && xe >= T) {
             const int slot = atomicAdd(&list_n, 1);
-            if (slot < MU_LIST) list[slot] = rank_key(xe, c.edge_at + tid);
+            if (slot < MU_LIST) list[slot] = rank_key(xe, c.edge_at(tid));
         }
 #pragma unroll
         for (int u = 0; u < MU_REG_QUADS; ++u) {
@@ -270,7 +272,7 @@ __global__ __launch_bounds__(MU_THREADS) void topk_chunk_kernel(
 // One wavefront per node: merge the chunks' keys, write the greedy token and the matrix row.
 __global__ __launch_bounds__(64) void matrix_update_merge_kernel(
     const int32_t* __restrict__ tokens, const int32_t* __restrict__ n_nodes, int32_t V, int32_t B,
-    int32_t K_max, int32_t k, const u64* __restrict__ partial, int32_t* __restrict__ M,
+    int32_t K_max, int32_t k, int32_t chunks, const u64* __restrict__ partial, int32_t* __restrict__ M,
     int32_t* __restrict__ target_ids) {
     const int node = blockIdx.x;                    // b * K_max + i
     const int b = node / K_max, i = node - b * K_max;
@@ -280,9 +282,9 @@ __global__ __launch_bounds__(64) void matrix_update_merge_kernel(
         if (lane == 0) target_ids[node] = -1;
         return;
     }
-    // GRAFT_ARGMAX_CHUNKS * k <= 256 candidates: four per lane, kept sorted
-    const u64* cand = partial + static_cast<size_t>(node) * GRAFT_ARGMAX_CHUNKS * k;
-    const int n_cand = GRAFT_ARGMAX_CHUNKS * k;
+    // chunks * k <= 256 candidates: four per lane, kept sorted
+    const u64* cand = partial + static_cast<size_t>(node) * chunks * k;
+    const int n_cand = chunks * k;
     u64 c[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) c[t] = (lane + 64 * t) < n_cand ? cand[lane + 64 * t] : 0;
@@ -362,13 +364,14 @@ extern "C" int32_t graft_matrix_update(const int32_t* tokens, const int32_t* n_n
         return GRAFT_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     u64* partial = static_cast<u64*>(workspace);
-    dim3 grid(GRAFT_ARGMAX_CHUNKS, K_max, B);
-    if (k <= 4) hipLaunchKernelGGL(topk_chunk_kernel<4>, grid, dim3(MU_THREADS), 0, s, logits, n_nodes, K_max, V, k, partial);
-    else if (k <= 8) hipLaunchKernelGGL(topk_chunk_kernel<8>, grid, dim3(MU_THREADS), 0, s, logits, n_nodes, K_max, V, k, partial);
-    else hipLaunchKernelGGL(topk_chunk_kernel<16>, grid, dim3(MU_THREADS), 0, s, logits, n_nodes, K_max, V, k, partial);
+    const RowCut cut = row_cut(static_cast<int64_t>(B) * K_max, V);
+    dim3 grid(cut.chunks, K_max, B);
+    if (k <= 4) hipLaunchKernelGGL(topk_chunk_kernel<4>, grid, dim3(MU_THREADS), 0, s, logits, n_nodes, K_max, V, cut.per, k, partial);
+    else if (k <= 8) hipLaunchKernelGGL(topk_chunk_kernel<8>, grid, dim3(MU_THREADS), 0, s, logits, n_nodes, K_max, V, cut.per, k, partial);
+    else hipLaunchKernelGGL(topk_chunk_kernel<16>, grid, dim3(MU_THREADS), 0, s, logits, n_nodes, K_max, V, cut.per, k, partial);
     int32_t rc = check_launch();
     if (rc != GRAFT_OK) return rc;
     hipLaunchKernelGGL(matrix_update_merge_kernel, dim3(B * K_max), dim3(64), 0, s, tokens, n_nodes, V, B, K_max, k,
-                       partial, M, target_ids);
+                       cut.chunks, partial, M, target_ids);
     return check_launch();
 }

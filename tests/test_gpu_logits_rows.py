@@ -57,3 +57,44 @@ def test_rows_of_any_length_and_address(V, shift):
     for t, r in rows.items():
         want_M[t] = r                                                      # ids, then -1 where no candidate is left
     assert (M.cpu().numpy() == want_M).all()
+
+
+@pytest.mark.parametrize("V", [1, 2, 3, 6, 1000, 8191, 8192, 8195, 8196, 8199, 16389])
+@pytest.mark.parametrize("shift,rows", [(0, 2048), (1, 2048), (3, 2048), (3, 1024), (2, 192)])
+def test_rows_cut_by_their_number(V, shift, rows):
+    """Many rows go to as few workgroups as take 8192 elements each (both edges in one where it is alone), fewer
+    rows to as many as fill the chip."""
+    rng = np.random.default_rng(V + shift)
+    K, k, used = 64, min(8, V), 3
+    B = rows // K
+    logits = torch.randn(rows * V, generator=torch.Generator(device="cuda").manual_seed(V), device="cuda")
+    buf = torch.full((rows * V + shift + 4,), 100.0, device="cuda")
+    lg = buf[shift:shift + rows * V].view(B, K, V)
+    lg.copy_(logits.view(B, K, V))
+    lg[0, 0, -1] = lg[0, 0, 0] = 9.0                                       # first and last element, equal
+    lg[0, 1, -1] = 11.0
+    lg[0, 2] = lg[0, 2].round()                                            # long runs of equal values
+    lg[1, 0, : V - 1] = -np.inf
+    lg[1, 1, ::2] = np.nan
+    lg[1, 1, V - 1] = 20.0
+    host = lg[:, :used].cpu().numpy()
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda()
+    parent = np.tile(np.arange(-1, K - 1), (B, 1))
+    tokens = rng.integers(0, V, (B, K))
+    n = up([used] * B)
+    want = np.full((B, K), -1)
+    rows_of = {}
+    for b in range(B):
+        for i in range(used):
+            order = best(host[b, i], k)
+            want[b, i] = order[0]
+            rows_of[int(tokens[b, i])] = order                             # the later node's row stays
+    acc = graft.graft_accept(up(parent), up(tokens), n, 8, logits=lg)
+    assert (acc["target_ids"].cpu().numpy() == want).all()
+    M = torch.full((V, k), -7, dtype=torch.int32, device="cuda")
+    ids = graft.graft_matrix_update(up(tokens), n, lg, M)
+    assert (ids.cpu().numpy() == want).all()
+    want_M = np.full((V, k), -7, np.int32)
+    for t, r in rows_of.items():
+        want_M[t] = r
+    assert (M.cpu().numpy() == want_M).all()
