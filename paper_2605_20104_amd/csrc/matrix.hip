@@ -2,10 +2,11 @@
 // ids that the method keeps in GPU memory.
 //
 // Retrieval is a gather along a static template: one 128-thread workgroup per sequence, one
-// thread per template node.  A node can be filled once its parent's token is known, so the
-// template is filled in rounds, one per depth: every round is one dependent lookup in M, and
-// the nodes of a depth are looked up together.  The call is bound by those dependent
-// round trips (nine for the paper's templates), not by bandwidth.
+// thread per template node.  A node's token is reached from the root's by as many dependent lookups in M as the node is
+// deep, and the call is bound by those trips (nine for the paper's templates).  Every thread makes them for itself: it
+// walks up the template once, with the ranks it passes as four bits each, and then down from the root; nodes
+// that share ancestors read the same addresses.  (In rounds, one per depth, with two barriers of the workgroup each
+// and the template requested behind the lengths: 2.5 us more a call for the nine levels, of about 6.)
 //
 // The refresh ranks every verified node's logits row.  Like the argmax of the acceptance
 // step it is one HBM scan of the logits (4 V bytes per node): up to GRAFT_ARGMAX_CHUNKS workgroups
@@ -28,43 +29,51 @@ __global__ __launch_bounds__(MR_THREADS) void matrix_retrieve_kernel(
     const int32_t* __restrict__ tpl_parent, const int32_t* __restrict__ tpl_rank, const int32_t* __restrict__ M, int32_t V, int32_t k,
     int32_t* __restrict__ parent, int32_t* __restrict__ status) {
     const int b = blockIdx.x, u = threadIdx.x;
-    __shared__ int32_t x[GRAFT_MAX_NODES];        // token of template node u
-    __shared__ int32_t done[GRAFT_MAX_NODES];
+    __shared__ int32_t node[GRAFT_MAX_NODES];     // (template parent + 1) << 4 | rank
+    __shared__ int32_t or_bad[2];
+    static_assert(GRAFT_MAX_SUCCESSORS <= 16 && GRAFT_MAX_NODES == 128, "ranks in four bits, two wavefronts");
     int32_t* tok = tokens + static_cast<size_t>(b) * K_max;
     int32_t* par = parent + static_cast<size_t>(b) * K_max;
-    const int32_t nd = n_nodes[b], nr = n_ret[b];
+    const int32_t nd = n_nodes[b], nr = n_ret[b], root = tok[0];
+    const int32_t f = u < N ? tpl_parent[u] : -1;
+    const int32_t r = u < N ? tpl_rank[u] : 0;
     if (nd < 1 || nr < 0 || nr > N || nd + nr > K_max) {       // uniform over the workgroup
         if (u == 0) status[b] = GRAFT_STATUS_BAD_LENGTH;
         return;
     }
     const bool mine = u < nr;
-    const int32_t f = mine ? tpl_parent[u] : -1;
-    const int32_t r = mine ? tpl_rank[u] : 0;
-    const int bad = mine && (f < -1 || f >= u || r < 0 || r >= k);
-    if (__syncthreads_or(bad)) {
+    node[u] = mine ? ((f + 1) << 4) | (r & 15) : 0;
+    if (workgroup_or_128(mine && (f < -1 || f >= u || r < 0 || r >= k), or_bad)) {
         if (u == 0) status[b] = GRAFT_STATUS_BAD_TREE;
         return;
     }
-    const int32_t root = tok[0];
-    done[u] = 0;
-    __syncthreads();
-    // rounds: a node is filled in the round after its parent's (at most nr rounds; the
-    // workgroup stops as soon as every node is filled)
-    bool filled = !mine;
-    for (int round = 0; round < nr; ++round) {
-        const bool ready = !filled && (f < 0 || done[f] != 0);
-        int32_t from = 0;
-        if (ready) from = f < 0 ? root : x[f];
-        __syncthreads();                            // all reads of done/x of this round before its writes
-        if (ready) {
-            const int32_t v = (from >= 0 && from < V) ? M[static_cast<size_t>(from) * k + r] : -1;
-            x[u] = v;
-            done[u] = 1;
-            tok[nd + u] = v;
-            par[nd + u] = f < 0 ? 0 : nd + f;
-            filled = true;
+    if (mine) {
+        // the walk up: the last sixteen ranks shifted in are those nearest the root, which come first on the way down
+        u64 ranks = 0;
+        int32_t depth = 0;
+        for (int32_t j = u; j >= 0; ++depth) {
+            const int32_t e = node[j];
+            ranks = (ranks << 4) | static_cast<u64>(e & 15);
+            j = (e >> 4) - 1;
         }
-        if (__syncthreads_and(filled)) break;
+        int32_t t = root;
+        for (int32_t at = 0;;) {
+            const int32_t end = depth < at + 16 ? depth : at + 16;
+            for (; at < end; ++at) {
+                t = (t >= 0 && t < V) ? M[static_cast<size_t>(t) * k + static_cast<int32_t>(ranks & 15)] : -1;
+                ranks >>= 4;
+            }
+            if (at >= depth) break;
+            ranks = 0;                              // a deeper node: up again, as far as the next sixteen
+            int32_t j = u;
+            for (int32_t left = depth - at; left > 0; --left) {
+                const int32_t e = node[j];
+                ranks = (ranks << 4) | static_cast<u64>(e & 15);
+                j = (e >> 4) - 1;
+            }
+        }
+        tok[nd + u] = t;
+        par[nd + u] = f < 0 ? 0 : nd + f;
     }
     if (u == 0) {
         n_nodes[b] = nd + nr;

@@ -46,6 +46,21 @@ def test_retrieve_envelope_stages(V, k, seed):
     assert (ref["tokens"][5, 1:2] == -1).all()
 
 
+@pytest.mark.parametrize("N,chain", [(1, 1), (16, 16), (17, 17), (33, 33), (64, 20), (65, 32), (127, 127), (127, 40)])
+def test_retrieve_templates_around_the_sixteen_ranks_of_a_word(N, chain):
+    """A chain of template nodes, the rest hung on any of them; every number of nodes taken from it."""
+    rng = np.random.default_rng(N + chain)
+    V, k, B, K = 300, 16, 4, 128
+    M = rng.integers(0, V, (V, k), dtype=np.int32)
+    M[rng.random((V, k)) < 0.004] = -1
+    tp = np.array([u - 1 if u < chain else rng.integers(-1, u) for u in range(N)], np.int32)
+    tr = rng.integers(0, k, N).astype(np.int32)
+    tokens, parent = rng.integers(0, V, (B, K)).astype(np.int32), np.full((B, K), -1, np.int32)
+    n_ret = np.array([N, N - 1, max(1, N // 2), min(N, 16)], np.int32)
+    ref = _retrieve_both(M, tp, tr, n_ret, tokens, parent, np.ones(B, np.int32))
+    assert ref["status"].tolist() == [0] * B
+
+
 def test_retrieve_error_paths_leave_the_tree_alone():
     M = np.arange(40, dtype=np.int32).reshape(10, 4) % 10
     tokens = np.arange(24, dtype=np.int32).reshape(3, 8) % 10
