@@ -10,9 +10,10 @@
 // is counted directly: score and index make one 64-bit key (the float's bits made monotonic,
 // then the index so that equal scores keep index order, parents before children), a node's rank
 // is the number of larger keys - one 64-bit compare per pair, no sort.  What the two wavefronts have to
-// know of each other (gates opened, candidates, nodes kept) they exchange as ballots, one barrier each; a kept node writes its own entry of the new tree.  us a call in a graph: one tree of 24 nodes
-// 4.29 -> 3.45, 4 of 60 5.87 -> 3.91, 16 of 120 7.68 -> 4.54 (LDS atomics, nine barriers, tokens looked up at the end in
-// a trip of their own, and eight keys per round of the count before).
+// know of each other (gates opened, candidates, nodes kept) they exchange as ballots, one barrier
+// each; a kept node writes its own entry of the new tree.  us a call in a graph: one tree of 24 nodes
+// 4.29 -> 3.45, 4 of 60 5.87 -> 3.91, 16 of 120 7.68 -> 4.54 (LDS atomics, nine barriers, tokens looked up
+// at the end in a trip of their own, and eight keys per round of the count before).
 #include "common.h"
 
 namespace graft {
