@@ -6,8 +6,8 @@
 // rows.  Every wavefront works for itself, without LDS or a barrier: lane l stands for the rows l + 1 and l + 65 of
 // the path, which it requests together with the lengths, checks, and looks up in the page table; the copy loop takes
 // the addresses from the lanes.  (One thread of a workgroup used to check the path entry by entry, between two
-// barriers, and the path was requested behind the lengths: 32 layers of 8 heads of 128 in bf16, a call in a graph, one sequence
-// 4.64 us, 3.70 now; eight 6.57, 5.92 now.)
+// barriers, and the path was requested behind the lengths: 32 layers of 8 heads of 128 in bf16, 4 rows, one sequence 4.75 us a
+// call in a graph, 3.82 like this; 2.95 with the rows of a batch in registers, see Quad.)
 // One lane of the copy owns one 16-byte column of a token row (a fixed KV head and element range)
 // for one sequence and layer and walks the path in order, eight rows at a time: all eight
 // (K and V: sixteen loads) are in flight before the first store.  Doing this in place is safe because the path
@@ -17,9 +17,18 @@
 
 namespace graft {
 
-constexpr int KC_THREADS = 64;                   // one wavefront: they share nothing
+// Wavefronts share nothing, and a workgroup is one as long as all of them start at once.  Past that their number costs: 4096
+// wavefronts of 64 layers and 16 sequences that move nothing take 3.5 us one by one, 2.4 four to a workgroup.  (One long
+// path in 48 layers of 8 heads in fp32, 192 wavefronts, the other way round: 9.4 us one by one, 11.3 four to a workgroup.)
+constexpr int KC_THREADS = 256;
+constexpr int64_t KC_ALONE = 1024;               // wavefronts of a launch up to which each is a workgroup
 constexpr int KC_BATCH = 8;
 static_assert(64 % KC_BATCH == 0 && GRAFT_MAX_NODES <= 128, "a batch stays within one register of the lanes' rows");
+
+// 16 bytes as the compiler's own vector: arrays of HIP's uint4, a class, went to scratch memory (272 bytes a lane), there and back
+// for each row.  us a call in a graph, one sequence, 32 layers of 8 heads of 128 in bf16, 4 / 48 rows 3.82 / 15.4 -> 2.95 / 7.8; 16
+// sequences, 48 layers in fp32, 20.6 / 181 -> 8.7 / 99.
+typedef unsigned Quad __attribute__((ext_vector_type(4)));
 
 struct CompactParams {
     void* k;
@@ -34,7 +43,7 @@ struct CompactParams {
 __global__ __launch_bounds__(KC_THREADS) void kv_compact_kernel(
     const int32_t* __restrict__ prefix_len, const int32_t* __restrict__ accept_len, const int32_t* __restrict__ path,
     const int32_t* __restrict__ block_table, int32_t depth_cap, int32_t K_max, int32_t max_pages, CompactParams p) {
-    const int b = blockIdx.z, layer = blockIdx.y, lane = threadIdx.x;
+    const int b = blockIdx.z, layer = blockIdx.y, lane = threadIdx.x & 63;
     const int32_t* path_b = path + static_cast<size_t>(b) * (depth_cap + 1);
     const int32_t P = __builtin_amdgcn_readfirstlane(prefix_len[b]), a = __builtin_amdgcn_readfirstlane(accept_len[b]);
     const int32_t first = path_b[0];
@@ -56,7 +65,7 @@ __global__ __launch_bounds__(KC_THREADS) void kv_compact_kernel(
     if (P < 0 || a < 0 || a > depth_cap) st = GRAFT_STATUS_BAD_LENGTH;
     else if (__builtin_amdgcn_ballot_w64(bad) != 0) st = GRAFT_STATUS_BAD_TREE;
     else if (__builtin_amdgcn_ballot_w64(outside) != 0) st = GRAFT_STATUS_BAD_LENGTH;
-    if (layer == 0 && blockIdx.x == 0 && lane == 0) {
+    if (layer == 0 && blockIdx.x == 0 && threadIdx.x == 0) {
         p.status[b] = st;
         p.new_prefix_len[b] = st == 0 ? P + a + 1 : P;
     }
@@ -79,7 +88,7 @@ __global__ __launch_bounds__(KC_THREADS) void kv_compact_kernel(
     }
     // all lanes stay for the copy (their offsets are read across lanes); those behind the last column load it and store nothing
     const int cols = p.Hkv << p.cols_shift;
-    const int col = blockIdx.x * KC_THREADS + lane;
+    const int col = blockIdx.x * blockDim.x + threadIdx.x;
     const bool live = col < cols;
     const int at = live ? col : cols - 1;
     const int g = at >> p.cols_shift;
@@ -93,19 +102,19 @@ __global__ __launch_bounds__(KC_THREADS) void kv_compact_kernel(
     };
     for (int k0 = 0; k0 < a; k0 += KC_BATCH) {   // row k of the path is number k - 1 here
         const u64 s = k0 < 64 ? src[0] : src[1], d = k0 < 64 ? dst[0] : dst[1];
-        uint4 kr[KC_BATCH], vr[KC_BATCH];
+        Quad kr[KC_BATCH], vr[KC_BATCH];
 #pragma unroll
         for (int j = 0; j < KC_BATCH; ++j) {     // (no branch around a load; behind the end the last row is read again)
             const u64 off = of_lane(s, (k0 + j < a ? k0 + j : a - 1) & 63);
-            kr[j] = *reinterpret_cast<const uint4*>(kb + off);
-            vr[j] = *reinterpret_cast<const uint4*>(vb + off);
+            kr[j] = *reinterpret_cast<const Quad*>(kb + off);
+            vr[j] = *reinterpret_cast<const Quad*>(vb + off);
         }
 #pragma unroll
         for (int j = 0; j < KC_BATCH; ++j) {
             const u64 off = of_lane(d, (k0 + j) & 63);
             if (live && k0 + j < a) {
-                *reinterpret_cast<uint4*>(kb + off) = kr[j];
-                *reinterpret_cast<uint4*>(vb + off) = vr[j];
+                *reinterpret_cast<Quad*>(kb + off) = kr[j];
+                *reinterpret_cast<Quad*>(vb + off) = vr[j];
             }
         }
     }
@@ -143,8 +152,10 @@ extern "C" int32_t graft_kv_compact(void* k_cache, void* v_cache, int64_t layer_
     const int cols_per_head = D * es / 16;       // 8, 16 or 32
     p.cols_shift = __builtin_ctz(static_cast<unsigned>(cols_per_head));
     const int cols = Hkv * cols_per_head;
-    dim3 grid((cols + KC_THREADS - 1) / KC_THREADS, n_layers, B);
-    hipLaunchKernelGGL(kv_compact_kernel, grid, dim3(KC_THREADS), 0, static_cast<hipStream_t>(stream), prefix_len,
+    const int waves = (cols + 63) / 64;          // per layer and sequence
+    const int threads = static_cast<int64_t>(B) * n_layers * waves <= KC_ALONE ? 64 : (64 * waves < KC_THREADS ? 64 * waves : KC_THREADS);
+    dim3 grid((cols + threads - 1) / threads, n_layers, B);
+    hipLaunchKernelGGL(kv_compact_kernel, grid, dim3(threads), 0, static_cast<hipStream_t>(stream), prefix_len,
                        accept_len, path, block_table, depth_cap, K_max, max_pages, p);
     return check_launch();
 }

@@ -54,6 +54,29 @@ def run_attn(att, dtype, prefix_len, n_nodes, mask, Hkv, layer=0, kv=0):
     return host(out).astype(np.float32)
 
 
+def us_per_call(call, reps=20):
+    """Duration of `call(stream)` on the GPU: the median of seven replays of a graph of `reps` calls."""
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        call(side)
+    side.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(reps):
+            call(torch.cuda.current_stream())
+    times = []
+    graph.replay()
+    for _ in range(7):
+        start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        graph.replay()
+        stop.record()
+        stop.synchronize()
+        times.append(start.elapsed_time(stop) * 1000 / reps)
+    return sorted(times)[3]
+
+
 AttnPlan = collections.namedtuple("AttnPlan", "path row_blocks row_tiles splits")
 
 

@@ -2,6 +2,7 @@
 feed the checker small assembly texts with one planted mistake each (on the CPU), and run it
 over the assembly of the library that is actually built."""
 import os
+import re
 
 import pytest
 
@@ -118,3 +119,14 @@ def test_the_built_library_passes():
         text = f.read()
     assert text.count("v_mfma_f32_16x16x32_bf16") > 500          # the check sees the real kernels
     assert b.check_attention_asm(text) == []
+
+
+def test_no_kernel_of_the_library_uses_scratch_memory():
+    """The kernels' metadata in the built library: an array or a register that went to scratch memory is a trip to memory
+    for every access.  (The value behind the key is a small number, one byte, or marked as a larger one.)"""
+    with open(b.LIB, "rb") as f:
+        data = f.read()
+    key = b".private_segment_fixed_size"
+    sizes = [data[at.end()] for at in re.finditer(re.escape(key), data)]
+    assert len(sizes) >= len(b.SOURCES)
+    assert set(sizes) == {0}, sizes

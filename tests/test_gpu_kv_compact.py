@@ -6,7 +6,7 @@ import torch
 import inputs
 import oracle
 import paper_2605_20104_amd as graft
-from gpu_util import dev, host
+from gpu_util import dev, host, us_per_call
 
 pytestmark = pytest.mark.gpu
 
@@ -130,3 +130,30 @@ def test_compact_at_the_edges_of_batches_and_wavefronts(rows, dtype, Hkv, D):
         c["acc"][b] = rows
     c["path"][1, rows] = 127 if rows < 127 else c["path"][1, rows]      # the last slot of the table
     assert (_both(c)["status"] == 0).all()
+
+
+@pytest.mark.parametrize("B,n_layers,Hkv,dtype,D", [
+    (6, 90, 5, "f32", 64),                     # 1080 wavefronts of 80 columns: two to a workgroup
+    (4, 52, 17, "f32", 64),                    # 1040 of 272: four to a workgroup, the second one of a row nearly empty
+    (2, 52, 9, "f32", 128),                    # 520 of 288: one to a workgroup
+])
+def test_compact_of_many_layers(B, n_layers, Hkv, dtype, D):
+    c = _case(B, dtype, B, Hkv, D, n_layers, [5, 0, 17, 9, 3, 15][:B], 14, 12, False)
+    c["path"][0, :4], c["acc"][0] = [0, 2, 5, 13], 3
+    c["acc"][1] = 0
+    _both(c)
+
+
+def test_many_wavefronts_that_move_nothing():
+    """A call over many layers in which no sequence accepts anything takes hardly longer than one over a single layer
+    (1.5 times as long with a workgroup for each wavefront)."""
+    def us(layers):
+        cache = [torch.zeros(layers * 32 * 16 * 16 * 128, dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+        strides = {"page": 16 * 16 * 128, "token": 128, "head": 16 * 128}
+        table = dev(np.arange(32).reshape(16, 2))
+        lengths, path, none = dev(np.full(16, 7)), dev(np.zeros((16, 9))), dev(np.zeros(16))
+        out = {k: torch.zeros(16, dtype=torch.int32, device="cuda") for k in ("new_prefix_len", "status")}
+        return us_per_call(lambda stream: graft.graft_kv_compact(*cache, cache[0].numel() // layers, layers, strides, table, lengths,
+                                                                 path, none, 16, 16, 128, out=out, stream=stream))
+    one, many = us(1), us(64)
+    assert many < 1.25 * one, (one, many)
