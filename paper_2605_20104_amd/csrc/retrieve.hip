@@ -70,6 +70,14 @@ __device__ __forceinline__ void shift_group(Tok4& g, int32_t i0, int32_t L_max) 
         if (r < i0 - (L_max - 4)) { g.t[0] = g.t[1]; g.t[1] = g.t[2]; g.t[2] = g.t[3]; }
 }
 
+// What a wavefront's lanes have written to LDS is what its lanes read from here on, and the other way round.  (A wavefront's
+// LDS operations complete in order; this keeps the compiler from changing that order.)
+__device__ __forceinline__ void wavefront_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 template <int RT_THREADS>
 __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
     const int32_t* __restrict__ ctx, const int32_t* __restrict__ ctx_len, int32_t L_max,
@@ -151,7 +159,7 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
     __syncthreads();
     if (!streamed && lane < nq)
         q_rev[lane] = qi < L ? ring[qi] : ((qi - L) < RT_THREADS ? tail_s[qi - L] : tail[static_cast<size_t>(b) * tail_max + (qi - L)]);
-    __builtin_amdgcn_wave_barrier();              // (a wavefront's LDS operations complete in order)
+    wavefront_lds_order();
 
     u64 top[GRAFT_MAX_CHAINS];
 #pragma unroll
@@ -346,7 +354,7 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
         }
         if (k0 != 0 && r0 < C) win[r0] = k0;
         if (k1 != 0 && r1 < C) win[r1] = k1;
-        __builtin_amdgcn_wave_barrier();
+        wavefront_lds_order();
     } else {
         // the list overflowed: every wavefront extracts its own best C keys (keys are unique because
         // e is, so exactly one lane owns each maximum and pops it), then wavefront 0 merges the
