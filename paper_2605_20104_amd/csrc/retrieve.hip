@@ -12,7 +12,8 @@
 //      two barriers before the ranking.
 //      A longer one is scanned from the registers it is loaded into, four units of 8192 tokens in
 //      flight, no barrier and no copy in LDS: what bounds it is the compute unit's load path, 64
-//      bytes a cycle.  (All contexts through LDS in chunks of 16384, two barriers each and at most
+//      bytes a cycle.  A wavefront that has candidates copies its tokens to a piece of LDS of its own and walks there.
+//      (All contexts through LDS in chunks of 16384, two barriers each and at most
 //      one chunk in flight: 131072 tokens 14.1 us, 8.9 now; 40000 tokens 7.9, 6.7 now; 16 sequences
 //      of 200000 26.6, 14.6 now.)
 //   2. scan: one compare per token against the query's last token, and a wavefront in which no
@@ -47,6 +48,8 @@ namespace graft {
 constexpr int RT_GROUPS = 4;                          // groups of four consecutive tokens per thread and chunk
 constexpr int RT_LIST = 128;                          // keys the ranking list holds before the tournament takes over
 constexpr int RT_WALK = 8;                            // tokens compared per round of the backward match
+constexpr int RT_FRONT = 32;                          // tokens in front of a position that a walk may read
+static_assert(RT_FRONT % 4 == 0 && RT_FRONT <= 32 && RT_FRONT >= (GRAFT_MAX_NGRAM - 1 + RT_WALK - 1) / RT_WALK * RT_WALK, "whole rounds");
 constexpr int RT_SLOTS = 4;                           // units of the streamed scan in flight
 constexpr int RT_MOST = 1024;                         // threads of the largest workgroup, the one that streams
 constexpr int rt_chunk(int threads) { return threads * 4 * RT_GROUPS; }     // tokens of a chunk
@@ -90,7 +93,10 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
     const int b = blockIdx.x;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    __shared__ __attribute__((aligned(16))) int32_t ring[RT_AHEAD * RT_CHUNK];   // the context; the walks wrap around at its start
+    // the context, behind RT_FRONT slots that a walk reads where it passes the start (and ignores); a context that does not fit
+    // is scanned in pieces of each wavefront's own
+    __shared__ __attribute__((aligned(16))) int32_t front_and_ring[RT_FRONT + RT_AHEAD * RT_CHUNK];
+    int32_t* const ring = front_and_ring + RT_FRONT;
     // the query from its end, one copy per wavefront (no barrier between writing and reading it); the backward match reads
     // up to RT_WALK entries past n_max - 1 and ignores them
     __shared__ int32_t queries[RT_WAVES][GRAFT_MAX_NGRAM + RT_WALK];
@@ -179,10 +185,31 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
             if (key > top[kk]) { const u64 u = top[kk]; top[kk] = key; key = u; }
         }
     };
+    // How many tokens up to the one at `at` match the query's end, that one included, at most cap: RT_WALK are compared at
+    // a time (independent LDS reads, those of the query's first round once for all candidates).
+    int32_t q_first[RT_WALK];
+#pragma unroll
+    for (int jj = 0; jj < RT_WALK; ++jj) q_first[jj] = q_rev[1 + jj];
+    const auto match_length = [&](const int32_t* at, int32_t cap) __attribute__((always_inline)) {
+        int32_t l = 1, run = RT_WALK;             // run: matching tokens at the front of a round
+        const auto compare = [&](int32_t base, const int32_t* q) __attribute__((always_inline)) {
+            unsigned eq = 0;                      // bit jj: token base + jj before the last continues the match
+#pragma unroll
+            for (int jj = 0; jj < RT_WALK; ++jj) eq |= (at[-base - jj] == q[jj] && base + jj < cap) ? 1u << jj : 0u;
+            run = __builtin_ctz(~eq);
+            l += run;
+        };
+        if (cap > 1) compare(1, q_first);
+        for (int32_t base = 1 + RT_WALK; run == RT_WALK && base < cap; base += RT_WALK) compare(base, q_rev + base);
+        return l;
+    };
     if (streamed) {
         // ---- a context that does not fit the ring: scanned from the registers it is loaded into
         const int32_t q_last = q_rev[0], q_prev = nq > 1 ? q_rev[1] : 0;
         const bool one = nq < 2 || n_max < 2;     // a query of one token
+        constexpr int RT_PIECE = RT_FRONT + 256;  // tokens of a group row of one wavefront and those in front of it
+        static_assert(2 * RT_WAVES * RT_PIECE <= RT_FRONT + RT_AHEAD * RT_CHUNK, "the pieces fit");
+        int32_t* const piece = front_and_ring + wave * 2 * RT_PIECE;
         const auto scan = [&](Tok4 (&g)[2], int32_t unit) __attribute__((always_inline)) {
             unsigned cand = 0, longer = 0;        // bit 4 u + j: token j of group u is a candidate, the one before it matches too
 #pragma unroll
@@ -201,25 +228,31 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
                     }
                 }
             }
+            if (__builtin_amdgcn_ballot_w64(cand != 0) == 0) return;
+            // The walks read LDS: with a trip to memory for every candidate, a context that is nothing but candidates took
+            // 2.6 times as long as with the context in LDS (131072 equal tokens, n_max = 32: 886 us, 285 like this; 335
+            // through the ring in chunks).  The wavefront copies what it holds to its piece, and the tokens in front from
+            // memory if a match can begin there.
+            const u64 walks = __builtin_amdgcn_ballot_w64(longer != 0);
+            if (walks != 0) {
+                if ((walks & 0xff) != 0) {        // (those lanes' tokens are less than RT_FRONT from the piece's start)
+                    const int32_t i = unit * RT_UNIT + ((lane >> 5) * RT_THREADS + wave * 64) * 4 - RT_FRONT + (lane & 31);
+                    piece[(lane >> 5) * RT_PIECE + (lane & 31)] = x[i < 0 ? 0 : (i < L ? i : L - 1)];
+                }
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    *reinterpret_cast<int4*>(piece + u * RT_PIECE + RT_FRONT + 4 * lane) = int4{g[u].t[0], g[u].t[1], g[u].t[2], g[u].t[3]};
+                wavefront_lds_order();
+            }
             while (cand != 0) {                   // one candidate per lane and pass
                 const int bit = __builtin_ctz(cand);
                 cand &= cand - 1;
                 const int32_t e = unit * RT_UNIT + ((bit >> 2) * RT_THREADS + tid) * 4 + (bit & 3) + 1;
                 const int32_t cap = (longer >> bit & 1) == 0 ? 1 : (n_max < e ? n_max : e);
-                int32_t l = 1;
-                for (int32_t base = 1; base < cap; base += RT_WALK) {
-                    int32_t before[RT_WALK];
-#pragma unroll
-                    for (int jj = 0; jj < RT_WALK; ++jj) before[jj] = x[e - 1 - base - jj >= 0 ? e - 1 - base - jj : 0];
-                    unsigned eq = 0;
-#pragma unroll
-                    for (int jj = 0; jj < RT_WALK; ++jj) eq |= (before[jj] == q_rev[base + jj] && base + jj < cap) ? 1u << jj : 0u;
-                    const int run = __builtin_ctz(~eq);
-                    l += run;
-                    if (run < RT_WALK) break;
-                }
+                const int32_t l = match_length(piece + (bit >> 2) * RT_PIECE + RT_FRONT + 4 * lane + (bit & 3), cap);
                 if (l >= n_min) hit(l, e);
             }
+            wavefront_lds_order();                // (the next piece's writes stay behind these reads)
         };
         const int32_t n_units = last_i / RT_UNIT + 1;             // of 8192 tokens; the first RT_SLOTS are on their way
         Tok4 slot[RT_SLOTS][2], extra[RT_SLOTS - 1][2];
@@ -295,26 +328,9 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
                 const int bit = __builtin_ctz(cand);
                 cand &= cand - 1;
                 const int32_t i = c * RT_CHUNK + ((bit >> 2) * RT_THREADS + tid) * 4 + (bit & 3);
-                {
-                    const int32_t e = i + 1;
-                    const int32_t cap = n_max < e ? n_max : e;
-                    // token e - 1 matches q_rev[0]; tokens e - 1 - j, j = 1 .. cap - 1, are compared RT_WALK at
-                    // a time (independent LDS reads; they lie at most n_max - 1 before i: this chunk or the one before)
-                    int32_t l = 1;
-                    for (int32_t base = 1; base < cap; base += RT_WALK) {
-                        unsigned eq = 0;                 // bit jj: token e - 1 - (base + jj) continues the match
-#pragma unroll
-                        for (int jj = 0; jj < RT_WALK; ++jj) {
-                            // (positions before the buffer's start wrap to some other token of the ring: masked below)
-                            const unsigned pos = static_cast<unsigned>(e - 1 - base - jj) & (static_cast<unsigned>(RT_AHEAD * RT_CHUNK) - 1u);
-                            eq |= (ring[pos] == q_rev[base + jj] && base + jj < cap) ? 1u << jj : 0u;
-                        }
-                        const int run = __builtin_ctz(~eq);          // matching tokens at the front of this round (<= RT_WALK)
-                        l += run;
-                        if (run < RT_WALK) break;
-                    }
-                    if (l >= n_min) hit(l, e);
-                }
+                const int32_t e = i + 1;
+                const int32_t l = match_length(ring + i, n_max < e ? n_max : e);
+                if (l >= n_min) hit(l, e);
             }
         }
     }

@@ -6,7 +6,7 @@ import torch
 import inputs
 import oracle
 import paper_2605_20104_amd as graft
-from gpu_util import assert_same, dev, host_dict
+from gpu_util import assert_same, dev, host_dict, us_per_call
 
 pytestmark = pytest.mark.gpu
 KEYS = ("chain_tok", "chain_len", "chain_pos", "chain_match", "n_hits", "status")
@@ -145,3 +145,32 @@ def test_as_many_hits_as_the_ranking_list_holds(L, hits):
         gpu, ref = both(ctx, np.array([L], np.int32), 1, 5, C, m, tail, np.array([5], np.int32))
         assert_same(gpu, ref, KEYS)
         assert gpu["n_hits"][0] == hits
+
+
+@pytest.mark.parametrize("n_max", [2, 8, 9, 10, 17, 31, 32])
+def test_long_matches_across_the_pieces_of_a_streamed_context(n_max):
+    """A context that does not fit LDS is compared in pieces of 256 tokens of one wavefront and the 32 in front: matches of
+    every length that end at the first tokens of a piece, a unit and the context, alone and one next to the other."""
+    rng = np.random.default_rng(n_max)
+    L, tail = 60000, np.tile(rng.integers(100, 110, n_max).astype(np.int32), (4, 1))
+    ctx = rng.integers(0, 100, size=(4, L)).astype(np.int32)
+    for b, starts in enumerate(([0, 256, 4096, 32768], [512, 3840, 8192, 40960], [8448, 36864, 45056, L - 40])):
+        for start in starts:
+            for i in range(start + b, start + 39, 3):              # (a later match overwrites part of an earlier one)
+                k = int(min(i + 1, rng.integers(1, n_max + 1)))
+                ctx[b, i - k + 1:i + 1] = tail[b, n_max - k:]
+    ctx[3], tail[3] = 5, 5                                          # and one token all along
+    gpu, ref = both(ctx, np.full(4, L, np.int32), 1, n_max, 8, 6, tail, np.full(4, n_max, np.int32))
+    assert_same(gpu, ref, KEYS)
+    assert (gpu["n_hits"] > 10).all()
+
+
+def test_repetitive_contexts_take_as_long_beyond_the_ring():
+    """One token all along, nothing but candidates: per token, a context that does not fit LDS takes about as long as one that
+    does (2.5 times as long with a trip to memory for every candidate)."""
+    def us(L):
+        ctx, length = dev(np.full((1, L), 7)), dev([L])
+        out = graft.graft_retrieve(ctx, length, 2, 32, 3, 8)
+        return us_per_call(lambda stream: graft.graft_retrieve(ctx, length, 2, 32, 3, 8, out=out, stream=stream)) / L
+    inside, beyond = us(32768), us(65536)
+    assert beyond < 1.5 * inside, (inside, beyond)
