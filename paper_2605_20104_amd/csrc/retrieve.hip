@@ -45,17 +45,19 @@
 
 namespace graft {
 
-constexpr int RT_GROUPS = 4;                          // groups of four consecutive tokens per thread and chunk
 constexpr int RT_LIST = 128;                          // keys the ranking list holds before the tournament takes over
 constexpr int RT_WALK = 8;                            // tokens compared per round of the backward match
 constexpr int RT_FRONT = 32;                          // tokens in front of a position that a walk may read
 static_assert(RT_FRONT % 4 == 0 && RT_FRONT <= 32 && RT_FRONT >= (GRAFT_MAX_NGRAM - 1 + RT_WALK - 1) / RT_WALK * RT_WALK, "whole rounds");
 constexpr int RT_SLOTS = 4;                           // units of the streamed scan in flight
 constexpr int RT_MOST = 1024;                         // threads of the largest workgroup, the one that streams
-constexpr int rt_chunk(int threads) { return threads * 4 * RT_GROUPS; }     // tokens of a chunk
 // Launch and barriers of a workgroup of sixteen wavefronts take longer than those of four, which shows where the tokens
-// are few: the smallest workgroup whose one chunk holds the rows, by L_max; the largest holds two chunks.  us a call
-// at 256 / 4096 tokens: 256 threads 3.7 / 4.1, 1024 threads 4.4 / 4.7; at 8192: 512 threads 4.3, 1024 threads 4.9.
+// are few; but a thread compares its tokens one after the other, which shows where many of them are candidates.  So: the
+// smallest workgroup whose one chunk holds the rows, by L_max, with two groups of four tokens per thread for the smallest
+// (rows of 2048) and four for the others; the largest holds two chunks.  us a call, 256 / 512 / 1024 threads: 2048 tokens
+// 3.7 / 4.0 / 4.4; 4096 tokens 3.84 / 3.77 / 4.7, of them equal, with n_max = 32, 23.6 / 17.5 / 20.5; 8192 tokens - / 4.0 / 4.9.
+constexpr int rt_groups(int threads) { return threads == 256 ? 2 : 4; }     // groups of four consecutive tokens per thread and chunk
+constexpr int rt_chunk(int threads) { return threads * 4 * rt_groups(threads); }     // tokens of a chunk
 constexpr int rt_chunks(int threads) { return threads == RT_MOST ? 2 : 1; }
 // Four consecutive tokens.  The context rows are only known to be 4-byte aligned (L_max is any
 // number), which the hardware's vector loads accept.
@@ -88,7 +90,7 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
     int32_t n_min, int32_t n_max, int32_t C, int32_t m,
     int32_t* __restrict__ chain_tok, int32_t* __restrict__ chain_len, int32_t* __restrict__ chain_pos,
     int32_t* __restrict__ chain_match, int32_t* __restrict__ n_hits, int32_t* __restrict__ status) {
-    constexpr int RT_WAVES = RT_THREADS / 64, RT_CHUNK = rt_chunk(RT_THREADS), RT_AHEAD = rt_chunks(RT_THREADS);
+    constexpr int RT_GROUPS = rt_groups(RT_THREADS), RT_WAVES = RT_THREADS / 64, RT_CHUNK = rt_chunk(RT_THREADS), RT_AHEAD = rt_chunks(RT_THREADS);
     constexpr int RT_UNIT = 8 * RT_THREADS;            // tokens of a unit of the streamed scan, two groups per thread
     const int b = blockIdx.x;
     const int tid = threadIdx.x;
@@ -208,7 +210,7 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
         const int32_t q_last = q_rev[0], q_prev = nq > 1 ? q_rev[1] : 0;
         const bool one = nq < 2 || n_max < 2;     // a query of one token
         constexpr int RT_PIECE = RT_FRONT + 256;  // tokens of a group row of one wavefront and those in front of it
-        static_assert(2 * RT_WAVES * RT_PIECE <= RT_FRONT + RT_AHEAD * RT_CHUNK, "the pieces fit");
+        static_assert(RT_THREADS != RT_MOST || 2 * RT_WAVES * RT_PIECE <= RT_FRONT + RT_AHEAD * RT_CHUNK, "the pieces fit");
         int32_t* const piece = front_and_ring + wave * 2 * RT_PIECE;
         const auto scan = [&](Tok4 (&g)[2], int32_t unit) __attribute__((always_inline)) {
             unsigned cand = 0, longer = 0;        // bit 4 u + j: token j of group u is a candidate, the one before it matches too

@@ -110,9 +110,9 @@ def test_contexts_around_and_beyond_the_ring(L, n_min):
     assert gpu["n_hits"][0] > 0 and gpu["n_hits"][2] > 1000
 
 
-@pytest.mark.parametrize("L", [1, 2, 3, 4, 5, 7, 257, 4095, 4096, 4097, 8191, 8192, 8193, 16387])
+@pytest.mark.parametrize("L", [1, 2, 3, 4, 5, 7, 257, 1023, 1025, 2047, 2048, 2049, 4095, 4096, 4097, 8191, 8192, 8193, 16387])
 def test_rows_around_the_workgroup_sizes(L):
-    """256 threads scan rows of up to 4096 tokens, 512 up to 8192, 1024 what is longer; the last group of four may be cut
+    """256 threads scan rows of up to 2048 tokens, 512 up to 8192, 1024 what is longer; the last group of four may be cut
     short, and the query may lie in context and tail."""
     rng = np.random.default_rng(L)
     B, n_max = 4, 6
@@ -174,3 +174,14 @@ def test_repetitive_contexts_take_as_long_beyond_the_ring():
         return us_per_call(lambda stream: graft.graft_retrieve(ctx, length, 2, 32, 3, 8, out=out, stream=stream)) / L
     inside, beyond = us(32768), us(65536)
     assert beyond < 1.5 * inside, (inside, beyond)
+
+
+def test_repetitive_rows_of_4096_tokens_take_a_larger_workgroup():
+    """One token all along: a thread compares its tokens one after the other, and 16 of them in each thread of a workgroup of
+    256 take 1.33 times as long as slightly longer rows in one of 512."""
+    def us(L):
+        ctx, length = dev(np.full((1, L), 7)), dev([L])
+        out = graft.graft_retrieve(ctx, length, 2, 32, 3, 8)
+        return us_per_call(lambda stream: graft.graft_retrieve(ctx, length, 2, 32, 3, 8, out=out, stream=stream))
+    below, above = us(4096), us(4100)
+    assert below < 1.2 * above, (below, above)
