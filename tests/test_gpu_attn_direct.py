@@ -12,7 +12,7 @@ import torch
 import inputs
 import oracle
 import paper_2605_20104_amd as graft
-from gpu_util import attn_plan, dev, host
+from gpu_util import attn_plan, dev, host, widened
 from test_gpu_attn import check_case, gpu_mask, shape_workload
 
 pytestmark = pytest.mark.gpu
@@ -72,26 +72,63 @@ def test_direct_path(case):
         assert (got[b, n_nodes[b]:] == 0).all()                # rows of absent nodes
 
 
-@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 64)])
-def test_scores_that_keep_rising(dtype, D):
+# Wavefronts with several 16-row blocks: bf16 in blocks of 32 rows through the 32x32 products, fp32 with D = 128 with queries
+# shared through LDS where a row group has several wavefronts.  (case, row blocks, row groups, whether the keys are split
+# over workgroups); 33 x 16, 50, 24 and 60 x 4 rows are no multiples of 32.
+ROW_BLOCKS = [
+    (("bf16", 64, 4, 60, 32, 8, 2048, "token_major", True), 2, 1, False),
+    (("bf16", 64, 4, 33, 64, 4, 700, "head_major", True), 2, 2, False),
+    (("bf16", 64, 3, 128, 64, 4, 100, "head_major", True), 2, 4, False),
+    (("bf16", 64, 6, 97, 64, 4, 100, "token_major", True), 2, 8, False),
+    (("bf16", 64, 3, 50, 8, 8, 5000, "head_major", True), 2, 1, True),
+    (("bf16", 64, 6, 24, 8, 8, 5000, "head_major", True), 2, 1, True),
+    (("bf16", 64, 4, 33, 64, 4, 2048, "head_major", True), 2, 4, True),
+    (("bf16", 64, 2, 128, 64, 4, 3000, "head_major", True), 4, 1, False),
+    (("bf16", 64, 4, 33, 64, 4, 1500, "token_major", True), 4, 1, False),
+    (("bf16", 64, 8, 33, 64, 4, 700, "head_major", True), 4, 2, False),
+    (("bf16", 64, 8, 79, 64, 4, 300, "head_major", True), 4, 4, False),
+    (("bf16", 64, 2, 33, 64, 4, 5000, "head_major", True), 4, 1, True),
+    (("bf16", 64, 6, 97, 32, 8, 5000, "head_major", True), 4, 8, True),
+    (("f32", 128, 4, 33, 32, 8, 700, "head_major", True), 2, 1, False),
+    (("f32", 128, 6, 128, 12, 4, 100, "token_major", True), 2, 2, False),
+    (("f32", 128, 2, 33, 64, 4, 700, "head_major", True), 2, 2, True),
+    (("f32", 128, 4, 33, 64, 4, 700, "head_major", True), 2, 4, True),
+    (("f32", 128, 3, 97, 64, 4, 300, "head_major", True), 2, 8, True),
+]
+
+
+@pytest.mark.parametrize("case,row_blocks,row_groups,split", ROW_BLOCKS, ids=lambda x: "%s_D%d_B%d_K%d_Hq%d_Hkv%d_P%d_%s_%s" % x if isinstance(x, tuple) else str(x))
+def test_several_row_blocks(case, row_blocks, row_groups, split):
+    dtype, D, B, K, Hq, Hkv, P, _, _ = case
+    plan = attn_plan(B, K, Hq, Hkv, D, (P + K + 15) // 16, dtype)
+    blocks = (K * (Hq // Hkv) + 15) // 16
+    assert (plan.path, plan.row_blocks, plan.splits > 1) == ("direct", row_blocks, split)
+    assert plan.row_tiles == -(-blocks // (row_groups * row_blocks))       # as many as that many row groups leave
+    test_direct_path(case)
+
+
+@pytest.mark.parametrize("dtype,D,B,K,Hq,Hkv,row_blocks", [("f32", 64, 1, 24, 4, 2, 1), ("f32", 128, 1, 24, 4, 2, 1), ("bf16", 64, 1, 24, 4, 2, 1),
+                                                           ("bf16", 64, 2, 33, 64, 4, 2), ("f32", 128, 2, 33, 64, 4, 2)])
+def test_scores_that_keep_rising(dtype, D, B, K, Hq, Hkv, row_blocks):
     """Scores rising by far more than the lazy bound along the sequence: the reference is raised again and
     again; falling scores keep the first one.  Bound: a dot product of D equal terms summed in fp32 is off by
     at most D/2 * 2^-24 of itself (D partial sums, half of the full one on average), which moves a weight by
     that fraction of the largest score and the result by as much times the largest |v|; plus, for bf16, the
     rounding of the result."""
-    w = shape_workload(1, 24, 4, 2, D, 1500, dtype=dtype)
+    assert attn_plan(B, K, Hq, Hkv, D, (1500 + K + 15) // 16, dtype).row_blocks == row_blocks
+    w = shape_workload(B, K, Hq, Hkv, D, 1500, dtype=dtype)
     att = inputs.make_attention_inputs(w, seed=3)
     conv = (lambda a: a) if dtype == "f32" else inputs.bf16_bits_to_f32
     back = (lambda a: a.astype(np.float32)) if dtype == "f32" else inputs.f32_to_bf16_bits
     k, q = conv(att["k_cache"][0]).copy(), conv(att["q"][0]).copy()
     for lp in range(att["pages_per_seq"]):
         t = lp * 16 + np.arange(16)
-        k[att["block_table"][0, lp]] = (t * 0.05)[None, :, None]
+        k[att["block_table"][:, lp]] = (t * 0.05)[None, :, None]
     q[:] = 1.0
     q[:, :, 1::2, :] = -1.0
     att["k_cache"], att["q"] = [back(k)], [back(q)]
-    parent = np.stack([inputs.random_recursive_tree(np.random.default_rng(3), w.K, 8)])
-    n, p = np.array([w.K], np.int32), np.array([w.P], np.int32)
+    parent = np.stack([inputs.random_recursive_tree(np.random.default_rng(3), w.K, 8)] * B)
+    n, p = np.full(B, w.K, np.int32), np.full(B, w.P, np.int32)
     for ws in (None, torch.empty(0, dtype=torch.uint8, device="cuda")):
         out = graft.graft_tree_attn(dev(att["q"][0], dtype), dev(att["k_cache"][0], dtype), dev(att["v_cache"][0], dtype),
                                     att["strides"], dev(att["block_table"]), dev(p), dev(n), gpu_mask(parent, n, p), w.Hkv,
@@ -142,19 +179,21 @@ def test_tensors_that_start_at_any_element(dtype, D):
     assert torch.equal(a, b)
 
 
-def test_probabilities_keep_their_32_bits_with_head_64():
+@pytest.mark.parametrize("K,G,H,pages,row_blocks", [(1, 1, 32, 1, 1), (3, 16, 32, 100, 2), (9, 16, 16, 200, 4)])
+def test_probabilities_keep_their_32_bits_with_head_64(K, G, H, pages, row_blocks):
     """Values chosen so that the weighted sum all but cancels: what is left of it shows every bit a probability
     loses on its way into the product with the values.  Four keys, scores that fp32 holds exactly (queries and
     keys have one nonzero element), results far smaller than their terms.  Bound: the exponent x = (s - max) log2 e
     is below 16 with one rounding (16 * 2^-24 ln 2 of p) and exp2 is good to 2^-23, so a probability is off by at
     most 2^-20 of itself, four sums add 2^-22 of the terms; plus the rounding of the result.  Probabilities of
     17 bits are off by up to 2^-17."""
-    B, K, H, D, P = 4, 1, 32, 64, 3
+    B, D, P = 4, 64, 3
+    assert attn_plan(B, K, G * H, H, D, pages, "bf16").row_blocks == row_blocks
     rng = np.random.default_rng(17)
-    w = shape_workload(B, K, H, H, D, P)
+    w = shape_workload(B, K, G * H, H, D, P)
     att = inputs.make_attention_inputs(w, seed=17)
     k, v = np.zeros_like(inputs.bf16_bits_to_f32(att["k_cache"][0])), np.zeros_like(inputs.bf16_bits_to_f32(att["v_cache"][0]))
-    q = np.zeros((B, K, H, D), np.float32)
+    q = np.zeros((B, K, G * H, D), np.float32)
     q[..., 0] = 1.0
     bits = inputs.f32_to_bf16_bits
     round_bf16 = lambda a: inputs.bf16_bits_to_f32(bits(np.asarray(a, np.float32))).astype(np.float64)
@@ -172,24 +211,30 @@ def test_probabilities_keep_their_32_bits_with_head_64():
         k[page, :, :4, 0] = s                                  # [page][head][token][dim]
         v[page, :, :4] = vals
     att["k_cache"], att["v_cache"], att["q"] = [bits(k)], [bits(v)], [bits(q)]
-    parent, n, prefix = np.full((B, K), -1, np.int32), np.full(B, K, np.int32), np.full(B, P, np.int32)
+    # nodes below the root see a fifth key, their own, of score and value zero: it takes from all weights alike (and is a fifth
+    # term of the sums, 2^-21 of the terms together)
+    parent, n, prefix = np.zeros((B, K), np.int32), np.full(B, K, np.int32), np.full(B, P, np.int32)
+    parent[:, 0] = -1
+    att = widened(att, pages)
     out = graft.graft_tree_attn(dev(att["q"][0], "bf16"), dev(att["k_cache"][0], "bf16"), dev(att["v_cache"][0], "bf16"),
                                 att["strides"], dev(att["block_table"]), dev(prefix), dev(n), gpu_mask(parent, n, prefix), H, 1.0)
-    got = host(out).astype(np.float64)[:, 0]
-    for b in range(B):
+    got = host(out).astype(np.float64)
+    for b, i, member in [(b, i, j) for b in range(B) for i in range(K) for j in range(G)]:
         page = att["block_table"][b, 0]
         s, vals = k[page, :, :4, 0].astype(np.float64), v[page, :, :4].astype(np.float64)
+        own = np.zeros(H) if i == 0 else np.exp(-s.max(axis=1))
         p = np.exp(s - s.max(axis=1, keepdims=True))
-        p /= p.sum(axis=1, keepdims=True)
+        p /= (p.sum(axis=1) + own)[:, None]
         ref, size = np.einsum("ht,htd->hd", p, vals), np.einsum("ht,htd->hd", p, np.abs(vals))
-        err = np.abs(got[b] - ref)
-        bound = (2.0 ** -20 + 2.0 ** -22) * size + 2.0 ** -8 * np.abs(ref)
-        print("largest error / bound %.2f, median of result / terms %.1e" % ((err / bound).max(), np.median(np.abs(ref) / size)))
+        err = np.abs(got[b, i, member::G] - ref)
+        bound = (2.0 ** -20 + (2.0 ** -22 if i == 0 else 2.0 ** -21)) * size + 2.0 ** -8 * np.abs(ref)
+        if member == 0:
+            print("largest error / bound %.2f, median of result / terms %.1e" % ((err / bound).max(), np.median(np.abs(ref) / size)))
         assert (err <= bound).all(), (err / bound).max()
 
 
 @pytest.mark.parametrize("dtype,D,K,Hq,P", [("f32", 64, 40, 8, 300), ("f32", 128, 23, 4, 77), ("f32", 128, 128, 64, 1500), ("bf16", 64, 40, 8, 300),
-                                            ("bf16", 64, 128, 64, 3000)])
+                                            ("bf16", 64, 128, 64, 3000), ("bf16", 64, 33, 64, 1500)])
 def test_values_that_are_not_finite_stay_with_the_nodes_that_see_them(dtype, D, K, Hq, P):
     """Infinite and NaN values in tree slots, the last one among them: rows that do not see the slot are those of a run
     without them, rows that do get inf or NaN in that dim alone.  Bound: the walk that keeps such values out takes the exact
@@ -232,11 +277,23 @@ def test_values_that_are_not_finite_stay_with_the_nodes_that_see_them(dtype, D, 
 @pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
 @pytest.mark.parametrize("P,pages,with_ws", [(0, 3, True), (9, 40, True), (300, 22, True), (600, 200, True), (1500, 98, False), (17000, 1100, False)])
 def test_entries_past_a_sequences_last_page_are_not_followed(dtype, D, P, pages, with_ws):
+    check_unused_entries(dtype, D, 20, 2, 2, P, pages, with_ws)
+
+
+@pytest.mark.parametrize("dtype,D,K,Hq,Hkv,P,pages,row_blocks", [
+    ("bf16", 64, 33, 64, 4, 600, 200, 2), ("bf16", 64, 33, 64, 4, 1500, 98, 2), ("bf16", 64, 60, 32, 8, 2000, 130, 2),
+    ("bf16", 64, 33, 64, 4, 17000, 1100, 4), ("f32", 128, 33, 64, 4, 9, 40, 2), ("f32", 128, 60, 32, 8, 2000, 130, 2)])
+def test_entries_past_the_last_page_with_several_row_blocks(dtype, D, K, Hq, Hkv, P, pages, row_blocks):
+    assert attn_plan(3, K, Hq, Hkv, D, pages, dtype).row_blocks == row_blocks
+    check_unused_entries(dtype, D, K, Hq, Hkv, P, pages, True)
+
+
+def check_unused_entries(dtype, D, K, Hq, Hkv, P, pages, with_ws):
     """Table entries are requested before the lengths are known.  Those behind a sequence's last page name a page of NaN
     here: the rows are those of a table that repeats the last page, bit for bit.  Splits that begin elsewhere than in a
     full table, wavefronts with more tiles than the request covers, an odd last page."""
-    B, K, H = 3, 20, 2
-    w = shape_workload(B, K, H, H, D, P, dtype=dtype)
+    B = 3
+    w = shape_workload(B, K, Hq, Hkv, D, P, dtype=dtype)
     att = inputs.make_attention_inputs(w, seed=P + 1)
     n, p = np.array([K, 0, 7], np.int32), np.array([P, P, P // 2], np.int32)
     used = att["block_table"].shape[1]
@@ -254,7 +311,7 @@ def test_entries_past_a_sequences_last_page_are_not_followed(dtype, D, P, pages,
         for b in range(B):
             last = (p[b] + n[b] - 1) // 16 if n[b] else -1
             table[b, last + 1:] = spare[0] if poison else table[b, max(last, 0)]
-        out.append(graft.graft_tree_attn(dev(att["q"][0], dtype), *caches, att["strides"], dev(table), dev(p), dev(n), mask, H, att["scale"],
+        out.append(graft.graft_tree_attn(dev(att["q"][0], dtype), *caches, att["strides"], dev(table), dev(p), dev(n), mask, Hkv, att["scale"],
                                          workspace=None if with_ws else torch.empty(0, dtype=torch.uint8, device="cuda")
                                          if (dtype, D) != ("bf16", 128) else None))
     assert torch.isfinite(out[0]).all()
