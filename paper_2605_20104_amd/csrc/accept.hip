@@ -16,7 +16,7 @@ namespace graft {
 constexpr int AM_THREADS = 256;
 constexpr int AM_WAVES = AM_THREADS / 64;
 constexpr int AM_QUADS = 12;                     // 16-byte loads in flight per thread: a whole chunk up to V = 196608
-static_assert(AM_QUADS * AM_THREADS >= ROW_QUADS, "a chunk of the cut is one round");
+static_assert(AM_QUADS * AM_THREADS >= ROW_QUADS, "a chunk of the cut is one round, for V <= 196608");
 constexpr int AC_THREADS = GRAFT_MAX_NODES;
 
 struct ArgPartial { float val; int32_t idx; };

@@ -37,13 +37,6 @@ struct AttnParams {
     unsigned long long* stamps;   // timing build: AT_STAMPS values per workgroup, or null (always null otherwise)
 };
 
-// Workgroups go to the 8 XCDs (each with its own L2 and its own compute units) round-robin by their
-// linear index.  The row tiles of a unit, one (sequence, KV head, split), read the same keys and
-// values: they get the same XCD and neighbouring slots on it, so that all but the first reader find
-// them in that XCD's L2.  Units are dealt round-robin, eight at a time; the row tiles of what is left
-// over are dealt one by one, so that the XCDs' shares differ by one workgroup at most (with whole
-// units only, 50 units of 5 tiles put 35 workgroups on two XCDs of 32 compute units: a second round
-// for a job that was planned to fill the chip once, 71 us instead of 42).
 // Division by a number that the host knows: x / d == (x * magic31(d)) >> 31 for 0 <= x < 2^24, 1 <= d <= 128.  A
 // division is some thirty dependent instructions, and several stand in front of a workgroup's first requests.
 inline uint32_t magic31(uint32_t d) { return ((1u << 31) + d - 1u) / d; }
@@ -54,6 +47,13 @@ __device__ __forceinline__ int div31(int x, uint32_t magic) {
 __device__ __forceinline__ int div24(int x, int d) {
     return static_cast<int>((static_cast<unsigned>(x) & 0xffffffu) / (static_cast<unsigned>(d) & 0xffffffu));
 }
+// Workgroups go to the 8 XCDs (each with its own L2 and its own compute units) round-robin by their
+// linear index.  The row tiles of a unit, one (sequence, KV head, split), read the same keys and
+// values: they get the same XCD and neighbouring slots on it, so that all but the first reader find
+// them in that XCD's L2.  Units are dealt round-robin, eight at a time; the row tiles of what is left
+// over are dealt one by one, so that the XCDs' shares differ by one workgroup at most (with whole
+// units only, 50 units of 5 tiles put 35 workgroups on two XCDs of 32 compute units: a second round
+// for a job that was planned to fill the chip once, 71 us instead of 42).
 struct WorkItem { int unit, row_tile; };                         // unit < 0: padding of the grid
 inline unsigned xcd_grid(int64_t n_units, int64_t n_row_tiles) {
     return static_cast<unsigned>(8 * ((n_units / 8) * n_row_tiles + (n_units % 8 * n_row_tiles + 7) / 8));

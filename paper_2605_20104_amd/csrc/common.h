@@ -186,6 +186,11 @@ __device__ __forceinline__ RowChunk row_chunk(const float* row, int32_t V, int c
 // ROW_QUADS: all 12 loads of a thread in use (3072) make the refresh of 16 x 128 rows of 128256 180 us instead of 170
 // (11 workgroups a row; they select while nobody loads), 1536 groups that of 16 x 64 rows of 32000 36.4 instead of 32.1.
 // ROW_FILL: with 2048 and 4096 the refresh of 8 x 24 rows of 32000 takes 16.9 and 19.2 us, with 1024 14.3.
+// The rows of absent nodes count although their workgroups leave at once: the host does not know n_nodes.  So the rule is made for
+// slots that are in use, and 16 workgroups a row are faster where hardly any are; rows of 32000, 16 a row / this rule:
+// refresh of 4 x 64 slots, 1, 4, 8, 24, 64 nodes each: 10.0 / 11.4, 10.4 / 11.8, 12.6 / 12.0, 14.9 / 12.0, 22.9 / 13.8 us; acceptance
+// of 8 x 64: 8.5 / 9.1, 8.8 / 9.5, 9.5 / 9.6, 12.8 / 9.7, 20.9 / 14.6.  Of 16 x 128 slots with 8 nodes, rows of 8000: 24.1 / 15.3
+// and 15.0 / 9.6.
 constexpr int32_t ROW_QUADS = 8 * 256;
 constexpr int64_t ROW_FILL = 1024;
 struct RowCut { int32_t chunks, per; };

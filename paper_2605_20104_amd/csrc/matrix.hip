@@ -179,7 +179,7 @@ __device__ __forceinline__ int select_rounds(u64 (&top)[KK], int k, u64 (&red)[2
 // If the list overflows (long runs of equal values) or the chunk does not fit, the
 // workgroup takes the exact streaming path: per-thread sorted lists of KK >= k keys.
 constexpr int MU_REG_QUADS = 12;                    // covers V <= 196608
-static_assert(MU_REG_QUADS * MU_THREADS >= ROW_QUADS, "a chunk of the cut fits the registers");
+static_assert(MU_REG_QUADS * MU_THREADS >= ROW_QUADS, "a chunk of the cut fits the registers, for V <= 196608");
 constexpr int MU_LIST = 256;                        // four candidates per lane of the last wavefront
 
 template <int KK>

@@ -4,18 +4,17 @@
 // KB, so the call is latency-bound, not bandwidth-bound: what matters is one
 // launch, few dependent memory round trips, and an exact total order on the hits.
 //
-//   1. the lengths are requested first and the first 32768 tokens right behind them, before the
-//      lengths are back (every index below L_max is readable); a thread loads groups of four
-//      consecutive tokens with 16-byte loads.  A context of up to 32768 tokens goes to LDS at once
-//      (128 KB of the compute unit's 160), and the query (last n_max tokens of context ++ tail,
+//   1. the lengths are requested first and, by the size of the workgroup, the first 2048, 8192 or 32768 tokens right
+//      behind them, before the lengths are back (every index below L_max is readable); a thread loads groups of four
+//      consecutive tokens with 16-byte loads.  A context of up to that many tokens goes to LDS at once
+//      (at most 128 KB of the compute unit's 160), and the query (last n_max tokens of context ++ tail,
 //      reversed) is read from there, each wavefront into a copy of its own: one memory round trip and
 //      two barriers before the ranking.
 //      A longer one is scanned from the registers it is loaded into, four units of 8192 tokens in
 //      flight, no barrier and no copy in LDS: what bounds it is the compute unit's load path, 64
 //      bytes a cycle.  A wavefront that has candidates copies its tokens to a piece of LDS of its own and walks there.
 //      (All contexts through LDS in chunks of 16384, two barriers each and at most
-//      one chunk in flight: 131072 tokens 14.1 us, 8.9 now; 40000 tokens 7.9, 6.7 now; 16 sequences
-//      of 200000 26.6, 14.6 now.)
+//      one chunk in flight: 131072 tokens 14.1 us, 8.1 now; 40000 tokens 7.9, 6.6 now.)
 //   2. scan: one compare per token against the query's last token, and a wavefront in which no
 //      lane has it goes on (in text it is rare).  Otherwise the lanes test the token before as
 //      well (in a register, or for the first of a group in LDS or from the lane below) where a hit
@@ -28,18 +27,18 @@
 //      key counts how many of the list are larger: that is its rank (keys are unique because e
 //      is).  A list that overflows (periodic text, tiny alphabets) takes the tournament instead:
 //      each wavefront extracts its best C keys (exactly one lane owns a maximum and pops it),
-//      wavefront 0 merges the 16 x C survivors the same way.  C x m threads then copy the chains,
+//      wavefront 0 merges the C survivors of each (4, 8 or 16 of them) the same way.  C x m threads then copy the chains,
 //      from LDS where the context is there.
 //
 // Measured on a 32768-token context (cycle stamps): with one position per lane and load, a
-// dependent query load, a tournament in all 16 wavefronts and a serial backward walk the kernel
+// dependent query load, a tournament in all 16 wavefronts it then had and a serial backward walk the kernel
 // took 10.4 us; 2.3 us of that were the tournament (its vector instructions, issued by 16
 // wavefronts that almost never hold a hit), 2 x 1.5 us the walks of the single wavefront per chunk
 // that had a candidate (250 instructions of signed index arithmetic and per-token branches per
 // round), 0.5 us each the dependent query load, the second chunk's barrier pair and the chain
 // copy from memory.  That form took 6.1 us.  Since then, us a call in a graph: workgroups of four or eight wavefronts
 // for rows of up to 8192 tokens, no branch around each group's load, and query copy and ranking per wavefront in place of
-// two barriers, 2048 tokens 5.3 -> 4.0; all reads of a ranking round in flight (a condition in front of each had
+// two barriers, 2048 tokens 5.2 -> 3.7; all reads of a ranking round in flight (a condition in front of each had
 // made them wait for one another), 4 x 8191 tokens of an alphabet of 20 12.2 -> 7.25.
 #include "common.h"
 
@@ -376,7 +375,7 @@ __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
     } else {
         // the list overflowed: every wavefront extracts its own best C keys (keys are unique because
         // e is, so exactly one lane owns each maximum and pops it), then wavefront 0 merges the
-        // 16 x C survivors.  No memory access between the rounds.
+        // RT_WAVES x C survivors.  No memory access between the rounds.
         for (int c = 0; c < C; ++c) {
             const u64 wmax = wave_max_u64(top[0]);
             if (lane == 0) red[wave * GRAFT_MAX_CHAINS + c] = wmax;

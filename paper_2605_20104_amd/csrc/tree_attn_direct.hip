@@ -7,12 +7,12 @@
 // prefix is spread over the chip with few or no partial results in memory.
 //   fp32 : v_mfma_f32_16x16x4_f32 (full fp32 products and sums, 32 cycles each).  The kernel is
 //          bound by them: 64 (D = 128) or 32 (D = 64) per 16 keys and 16 rows.
-//   bf16 : v_mfma_f32_16x16x32_bf16 on raw Q and K (exact products, fp32 sums); the softmax scale
-//          is applied in fp32.  With D = 64 probabilities enter the second product whole, as the sum of
+//   bf16 : v_mfma_f32_16x16x32_bf16, and with D = 64 and two or four row blocks v_mfma_f32_32x32x16_bf16, on raw
+//          Q and K (exact products, fp32 sums); the softmax scale is applied in fp32.  With D = 64 probabilities enter the second product whole, as the sum of
 //          three bf16 numbers (two, 17 bits, put the results further from a 64-bit reference), with
 //          D = 128 rounded to one, as on the path this stands in for.  Bound by the vector ALUs (exp2 and the
 //          packing of probabilities).
-// Operand layouts (lane = 16 lg + l16).  First product: S^T = K Q^T, A = K (key l16), B = Q^T
+// Operand layouts of blocks of 16 rows (lane = 16 lg + l16); those of 32 rows stand at DirectOps<__bf16, D, 32>.  First product: S^T = K Q^T, A = K (key l16), B = Q^T
 // (row l16), so a lane gets 4 keys (4 lg + i) of one row, and these are the B operand of the
 // second product O^T = V^T P^T without any exchange between lanes: its contraction index runs
 // over the same keys (16 c + 4 lg + i).  Its A operand wants one dim of those keys per lane: in
@@ -927,9 +927,10 @@ static size_t direct_lds_bytes(int mb, int rg, int32_t D, int32_t dtype) {
 // tile of a wavefront.  Cycles of a step (eight wavefronts, one tile each): fp32 4700 / 8200
 // (D = 128, one / two row blocks) and 2650 (D = 64), against 4096 / 8192 and 2048 of MFMAs on a SIMD;
 // bf16 2600 (D = 128) and, for D = 64, 1700 / 2750 / 4550 for one / two / four row blocks.  Measured with
-// 256 workgroups, keys shared by 16 row tiles: 2130 / 3930, 1240, 1360 and 870 / 1340 / 2200 ns, the
-// same at 2 to 2.2 GHz.  Set-up and
-// the merge through LDS take 6500 + 2000 per row block and 64 dims; the merge of splits is a launch of
+// 256 workgroups, keys shared by 16 row tiles: 2130 / 3960, 1130, 1335 and 825 / 1270 / 2045 ns, the
+// same at 2 to 2.3 GHz (the blocks of 32 rows took 2 to 4 % off the steps of 16-row blocks they replaced, 1300 / 2080, and
+// the rest of their gain off the fixed part).  Set-up and the merge through LDS take 6500 + 2000 per row block and 64 dims
+// (bf16 with D = 64, one / two / four row blocks: 4.0 / 4.2 / 7.3 us, launch included); the merge of splits is a launch of
 // its own, 8000 + 600 per split and its traffic, 8 bytes per partial value at 3200 bytes per cycle.
 DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages, int32_t dtype,
                        bool may_split) {
