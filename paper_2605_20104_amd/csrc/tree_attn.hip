@@ -45,127 +45,17 @@
 //
 // (2) fp32 storage, D = 64, and bf16 with D = 128 where the keys are few: tree_attn_direct.hip.
 #include <cstring>
-#include <type_traits>
 
-#include "attn_shared.h"
+#include "attn_mfma.h"
 
 namespace graft {
 
-constexpr int AT_THREADS = 256;
-constexpr int AT_WAVES = 4;
-constexpr int AT_STAGE = 64;        // tokens per LDS stage (4 pages)
-constexpr int AT_SUB = 32;          // tokens per softmax step
-constexpr int AT_D = 128;
-constexpr int AT_ROW_BYTES = AT_D * 2;
 constexpr int AT_MAX_MB = 5;            // 16-row MFMA blocks per wavefront (5 * 48 = 240 of 256 AccVGPRs)
-constexpr int AT_MAX_SPLITS = 64;
 constexpr float AT_LAZY_LOG2 = 24.0f;  // a row keeps its reference while exponents stay below 2^24
-
-// Timing build (-DGRAFT_ATTN_STAMPS, a library of its own: see build.py): the MFMA kernel
-// records when each workgroup passed the points below and writes them to a buffer the caller
-// registered with graft_attn_stamp_buffer().  Times are values of the 100 MHz real-time counter
-// (the first absolute, the others relative to it), two entries are the core-clock counter at
-// both ends of the stage loop, which gives the clock the loop ran at.  Without the flag the
-// macros are empty and the kernel is unchanged.
-constexpr int AT_STAMPS = 24;
-enum AttnStamp {
-    AT_TS_START = 0,          // first instruction of the workgroup (absolute)
-    AT_TS_LENGTHS = 1,        // lengths known
-    AT_TS_TABLE_REQ = 2,      // block-table entries requested
-    AT_TS_Q_DONE = 3,         // Q converted
-    AT_TS_TABLE_LDS = 4,      // table and masks stored to LDS
-    AT_TS_STAGE0_REQ = 5,     // transfers of stage 0 issued
-    AT_TS_ZEROED = 6,         // accumulators zeroed, stage 1 issued (in front of the barrier)
-    AT_TS_LOOP = 7,           // stage loop entered
-    AT_TS_STAGE0 = 8,         // first stage arrived
-    AT_TS_LOOP_END = 9,       // stage loop left
-    AT_TS_END = 10,           // results written
-    AT_TS_CYCLES_LOOP = 11,   // core-clock counter at AT_TS_LOOP
-    AT_TS_CYCLES_END = 12,    // core-clock counter at AT_TS_LOOP_END
-    AT_TS_STAGES = 13,        // stages of this workgroup
-    AT_TS_VALID = 14,         // 1
-    AT_TS_WAIT_CYCLES = 15,   // core-clock cycles wavefront 0 waited for its transfers of a stage, summed
-    AT_TS_BARRIER_CYCLES = 16,  // ... and at the stage barriers (reading the counter costs some 50 cycles itself)
-};
-#ifdef GRAFT_ATTN_STAMPS
-#define GRAFT_STAMPS_BEGIN()                                \
-    unsigned long long at_stamp[AT_STAMPS] = {};            \
-    at_stamp[AT_TS_START] = __builtin_amdgcn_s_memrealtime()
-#define GRAFT_STAMP(k) (at_stamp[k] = __builtin_amdgcn_s_memrealtime() - at_stamp[AT_TS_START])
-#define GRAFT_STAMP_CYCLES(k) (at_stamp[k] = __builtin_readcyclecounter())
-#define GRAFT_SPAN_BEGIN() const unsigned long long at_span0 = __builtin_readcyclecounter()
-#define GRAFT_SPAN_SPLIT(k) const unsigned long long at_span1 = __builtin_readcyclecounter(); at_stamp[k] += at_span1 - at_span0
-#define GRAFT_SPAN_END(k) (at_stamp[k] += __builtin_readcyclecounter() - at_span1)
-#define GRAFT_STAMPS_WRITE(p, n_stages)                                                     \
-    do {                                                                                    \
-        GRAFT_STAMP(AT_TS_END);                                                             \
-        at_stamp[AT_TS_STAGES] = static_cast<unsigned long long>(n_stages);                 \
-        at_stamp[AT_TS_VALID] = 1;                                                          \
-        if (threadIdx.x == 0 && (p).stamps)                                                 \
-            for (int at_k = 0; at_k < AT_STAMPS; ++at_k)                                    \
-                (p).stamps[static_cast<size_t>(blockIdx.x) * AT_STAMPS + at_k] = at_stamp[at_k]; \
-    } while (0)
-#else
-#define GRAFT_STAMPS_BEGIN() ((void)0)
-#define GRAFT_STAMP(k) ((void)0)
-#define GRAFT_STAMP_CYCLES(k) ((void)0)
-#define GRAFT_SPAN_BEGIN() ((void)0)
-#define GRAFT_SPAN_SPLIT(k) ((void)0)
-#define GRAFT_SPAN_END(k) ((void)0)
-#define GRAFT_STAMPS_WRITE(p, n_stages) ((void)0)
-#endif
 
 // ---------------------------------------------------------------------------
 // path (1): MFMA split-KV kernel
 // ---------------------------------------------------------------------------
-struct SplitRange { int st0, st1, P, n, total; };
-
-constexpr int AT_MAX_SPLIT_PAGES = 4096;          // block-table entries of one split kept in LDS
-constexpr int AT_NBUF = 4;                         // LDS stage buffers
-constexpr int AT_STAGE_BYTES = 2 * AT_STAGE * AT_ROW_BYTES;   // K rows then V rows
-constexpr int AT_LOADS_PER_STAGE = 8;              // global->LDS instructions per wavefront per stage
-
-// Global -> LDS without passing through registers: each lane's 16 bytes land at
-// (wavefront-uniform LDS base) + lane * 16, so the swizzled LDS layout is produced by
-// choosing which global chunk each lane fetches.  One instruction moves 4 token rows (1 KB)
-// of K or of V; 4 wavefronts x 4 x (K,V) = one 64-token stage.
-//
-// The transfer is issued through inline assembly on purpose: the kernel keeps several stages
-// in flight and waits for them with explicit s_waitcnt vmcnt(N); transfers the compiler knows
-// about make it drain the whole vector memory counter before every LDS read and barrier.
-__device__ __forceinline__ void load_global_to_lds_b128(const void* gptr, unsigned lds_addr) {
-    // LDS address of lane l = M0 + 16 * l (M0 write needs one wait state before its use).
-    // M0 is a reserved register the compiler sets up itself right before each of its own uses.
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-                 :
-                 : "s"(lds_addr), "v"(gptr)
-                 : "memory");
-}
-
-// Same with the global address given as (wavefront-uniform 64-bit base) + (32-bit byte offset
-// of the lane).
-__device__ __forceinline__ void load_global_to_lds_b128(const void* base, unsigned lane_off, unsigned lds_addr) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :
-                 : "s"(lds_addr), "v"(lane_off), "s"(base)
-                 : "memory");
-}
-
-__device__ __forceinline__ unsigned lds_address(const void* p) {
-    return static_cast<unsigned>(reinterpret_cast<size_t>(
-        (const __attribute__((address_space(3))) unsigned char*)(p)));
-}
-
-// s_waitcnt vmcnt(N) only (expcnt / lgkmcnt fields left at "no wait")
-#define GRAFT_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(0x0F70 | ((N) & 15) | (((N) >> 4) << 14))
-
-// Workgroup barrier that orders LDS traffic only.  __syncthreads() would also drain the
-// vector memory counter and with it the global->LDS transfers of the stages still in flight.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 // ---- MFMA issue through inline assembly, accumulators in fixed AccVGPRs ----------------
 // With 512 registers per lane available the register allocator rotates MFMA accumulators
@@ -191,22 +81,6 @@ __device__ __forceinline__ void lds_barrier() {
 // of a pipeline region, all of the slow path) begins with s_nop 1, and constants used as MFMA
 // sources are made opaque to the compiler.  The build checks the generated assembly for the
 // source-write distance, for compiler use of the hand-managed registers and for spills.
-#define GRAFT_ACC_BLOCK_0 "a0", "a1", "a2", "a3", "a4", "a5", "a6", "a7", "a8", "a9", "a10", "a11", "a12", "a13", "a14", "a15", "a16", "a17", "a18", "a19", "a20", "a21", "a22", "a23", "a24", "a25", "a26", "a27", "a28", "a29", "a30", "a31", "a32", "a33", "a34", "a35", "a36", "a37", "a38", "a39", "a40", "a41", "a42", "a43", "a44", "a45", "a46", "a47"
-#define GRAFT_ACC_BLOCK_1 "a48", "a49", "a50", "a51", "a52", "a53", "a54", "a55", "a56", "a57", "a58", "a59", "a60", "a61", "a62", "a63", "a64", "a65", "a66", "a67", "a68", "a69", "a70", "a71", "a72", "a73", "a74", "a75", "a76", "a77", "a78", "a79", "a80", "a81", "a82", "a83", "a84", "a85", "a86", "a87", "a88", "a89", "a90", "a91", "a92", "a93", "a94", "a95"
-#define GRAFT_ACC_BLOCK_2 "a96", "a97", "a98", "a99", "a100", "a101", "a102", "a103", "a104", "a105", "a106", "a107", "a108", "a109", "a110", "a111", "a112", "a113", "a114", "a115", "a116", "a117", "a118", "a119", "a120", "a121", "a122", "a123", "a124", "a125", "a126", "a127", "a128", "a129", "a130", "a131", "a132", "a133", "a134", "a135", "a136", "a137", "a138", "a139", "a140", "a141", "a142", "a143"
-#define GRAFT_ACC_BLOCK_3 "a144", "a145", "a146", "a147", "a148", "a149", "a150", "a151", "a152", "a153", "a154", "a155", "a156", "a157", "a158", "a159", "a160", "a161", "a162", "a163", "a164", "a165", "a166", "a167", "a168", "a169", "a170", "a171", "a172", "a173", "a174", "a175", "a176", "a177", "a178", "a179", "a180", "a181", "a182", "a183", "a184", "a185", "a186", "a187", "a188", "a189", "a190", "a191"
-#define GRAFT_ACC_BLOCK_4 "a192", "a193", "a194", "a195", "a196", "a197", "a198", "a199", "a200", "a201", "a202", "a203", "a204", "a205", "a206", "a207", "a208", "a209", "a210", "a211", "a212", "a213", "a214", "a215", "a216", "a217", "a218", "a219", "a220", "a221", "a222", "a223", "a224", "a225", "a226", "a227", "a228", "a229", "a230", "a231", "a232", "a233", "a234", "a235", "a236", "a237", "a238", "a239"
-#define GRAFT_ACC_BLOCK_5 "a240", "a241", "a242", "a243", "a244", "a245", "a246", "a247", "a248", "a249", "a250", "a251", "a252", "a253", "a254", "a255"
-
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
-}
-#define GRAFT_CONST(name, ic) constexpr int name = decltype(ic)::value
-
 template <int MB> constexpr int q_in_acc() { return MB; }   // row blocks with Q^T in AccVGPRs (all, for MB <= 5)
 constexpr int L_IN_ACC = 4;                                  // row blocks with their row sums in AccVGPRs
 template <int MB> constexpr int acc_used() { return 32 * MB + 16 * q_in_acc<MB>() + 4 * (MB < L_IN_ACC ? MB : L_IN_ACC); }
@@ -224,23 +98,6 @@ __device__ __forceinline__ void reserve_acc_registers() {
     if constexpr (acc_used<MB>() > 240) asm volatile("" ::: GRAFT_ACC_BLOCK_5);
 }
 
-template <int R> __device__ __forceinline__ void acc_set(float v) {
-    asm volatile("v_accvgpr_write_b32 a[%0], %1" : : "n"(R), "v"(v));
-}
-template <int R> __device__ __forceinline__ void acc_set_bits(unsigned v) {
-    asm volatile("v_accvgpr_write_b32 a[%0], %1" : : "n"(R), "v"(v));
-}
-template <int R> __device__ __forceinline__ float acc_get() {
-    float v;
-    asm volatile("v_accvgpr_read_b32 %0, a[%1]" : "=v"(v) : "n"(R));
-    return v;
-}
-template <int R> __device__ __forceinline__ void acc_scale(float a) {
-    float t;
-    asm volatile("v_accvgpr_read_b32 %0, a[%1]\n\ts_nop 1\n\tv_mul_f32 %0, %0, %2\n\ts_nop 1\n\tv_accvgpr_write_b32 a[%1], %0"
-                 : "=&v"(t)
-                 : "n"(R), "v"(a));
-}
 // The compiler does not know that these asm statements are MFMAs, so it inserts none of the
 // wait states an MFMA needs after a vector ALU write of one of its VGPR sources (2 for the
 // A and B operands, 1 for C: measured on gfx950, a shorter distance makes the MFMA read the
@@ -296,20 +153,6 @@ __device__ __forceinline__ void mfma_rowsum(floatx4& l, const bf16x8& ones, cons
     else
         asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(l) : "v"(ones), "v"(pb));
 }
-// A register holding a bit pattern the compiler cannot see through (so it is kept, not
-// rematerialised in front of an MFMA that reads it).
-__device__ __forceinline__ unsigned opaque_bits(unsigned v) {
-    unsigned r;
-    asm volatile("v_mov_b32 %0, %1" : "=v"(r) : "s"(v));
-    return r;
-}
-#define GRAFT_MFMA_SETTLE() asm volatile("s_nop 15\n\ts_nop 7" ::: "memory")
-// An empty asm that reads x: the registers of x stay allocated up to this point.  Used in the
-// slow path after a group of MFMAs so that their source registers are not reused in between.
-// (Not inside the pipeline regions: a use of an operand buffer after its reload has been
-// issued makes the compiler wait for that reload, which undoes the prefetch.)
-#define GRAFT_KEEP(x) asm volatile("" : : "v"(x))
-
 // What one wavefront keeps in VGPRs for its 16*MB query rows (O^T and Q'^T are in AccVGPRs).
 // Exponents are in log2 units throughout: Q' = bf16(Q * scale * log2 e), so that the MFMA
 // result q'.k - m_ref is directly the argument of exp2.
@@ -541,7 +384,7 @@ __device__ __forceinline__ bool region_pv_max(const unsigned char* __restrict__ 
 // tail): masked entries become -inf; the lane-local maxima are recomputed.
 template <int MB>
 __device__ __forceinline__ bool apply_tree_mask(floatx4 (&x)[MB][2], const WaveRows<MB>& w, float (&lm)[MB],
-                                                int lane, int t_sub0, int P, int n, int r_base, int R, int g_magic,
+                                                int lane, int t_sub0, int P, int n, int slots, int r_base, int R, int g_magic,
                                                 const unsigned* __restrict__ Ms) {
     const int l16 = lane & 15, lg = lane >> 4;
     bool grow = false;
@@ -550,7 +393,7 @@ __device__ __forceinline__ bool apply_tree_mask(floatx4 (&x)[MB][2], const WaveR
         const int r = r_base + rb * 16 + l16;
         const int node = (r * g_magic) >> 16;              // r / G
         const unsigned* row = Ms + 4 * (r < R && node < n ? node : 0);     // (rows of absent nodes: any finite mask will do)
-        const unsigned win = visible_window(t_sub0 - P, n, [&](int k) { return row[k]; }) >> (4 * lg);
+        const unsigned win = visible_window(t_sub0 - P, slots, [&](int k) { return row[k]; }) >> (4 * lg);
         reserve_acc_registers<MB>();                          // no temporaries of the compiler's in the accumulators
         float mx = -INFINITY;
 #pragma unroll
@@ -723,11 +566,6 @@ __device__ __forceinline__ void store_rows(const AttnParams& p, const WaveRows<M
     });
 }
 
-// Rounds q * f to bf16 for two packed bf16 values.
-__device__ __forceinline__ unsigned scale_bf16_pair(unsigned q2, float f) {
-    return pack_bf16(__uint_as_float(q2 << 16) * f, __uint_as_float(q2 & 0xffff0000u) * f);
-}
-
 template <int MB>
 __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(GRAFT_ATTN_ARGS) {
     __shared__ __attribute__((aligned(1024))) unsigned char kv[AT_NBUF][AT_STAGE_BYTES];
@@ -746,63 +584,30 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(GRAFT_ATTN_A
     const int bg = div31(unit, splits_magic), split = unit - bg * n_splits;
     const int b = div24(bg, n_kv_heads), g = bg - b * n_kv_heads;
 
-    // The set-up is a chain of dependent trips to memory (lengths -> block table -> first
-    // keys), so everything that does not depend on the lengths is requested alongside them:
-    // the lengths first (vector memory returns in order, and they are waited for first), then
-    // this wavefront's Q rows and the sequence's ancestor masks.
-    const int b_lane = per_lane(b);              // (requested here, waited for behind the requests below)
-    const int n_lane = n_nodes[b_lane], P_lane = prefix_len[b_lane];
+    const int n_raw = scalar_load(n_nodes, b), P_raw = scalar_load(prefix_len, b);
     await_setup_args(p);
     if (padding) return;
-    // Q rows of this wavefront (rows past R read row 0 and are zeroed when converted)
-    const int r_base = rt * (AT_WAVES * 16 * MB) + wave_u * (16 * MB);
-    uintx4 qd[MB][4];
-#pragma unroll
-    for (int rb = 0; rb < MB; ++rb) {
-        const int r = r_base + rb * 16 + l16;
-        const int rc = r < p.R ? r : 0;
-        const int i = (rc * p.g_magic) >> 16, hl = rc - i * p.G;     // i = rc / G
-        const __bf16* qp = static_cast<const __bf16*>(p.q) +
-            ((static_cast<size_t>(b) * p.K_max + i) * p.Hq + (g * p.G + hl)) * AT_D + lg * 8;
-#pragma unroll
-        for (int ds = 0; ds < 4; ++ds) qd[rb][ds] = *reinterpret_cast<const uintx4*>(qp + 32 * ds);
-    }
-
-    // ancestor masks as 32-bit words: two rounds of 256 cover the 64 nodes x 4 x 64 bits
-    static_assert(GRAFT_MAX_NODES * GRAFT_MASK_WORDS * 2 <= 2 * AT_THREADS, "mask words per thread");
-    const int n_mask_words = p.K_max * GRAFT_MASK_WORDS * 2;
-    const unsigned* mask_words = reinterpret_cast<const unsigned*>(p.mask) + static_cast<size_t>(b) * n_mask_words;
-    const unsigned mw0 = tid < n_mask_words ? mask_words[tid] : 0u;
-    const unsigned mw1 = tid + AT_THREADS < n_mask_words ? mask_words[tid + AT_THREADS] : 0u;
-
+    const unsigned kv_base = __builtin_amdgcn_readfirstlane(lds_address(&kv[0][0]));
+    constexpr int TILE_ROWS = AT_WAVES * 16 * MB;
+    const int r_base = rt * TILE_ROWS + wave_u * (16 * MB);
+    // The queries lie in the ring until they are read, in front of the values of buffer 3 (which are cleared below); with four and
+    // five row blocks they reach into the buffer of stage 1.
+    constexpr unsigned Q_END = AT_NBUF * AT_STAGE_BYTES - AT_STAGE * AT_ROW_BYTES;
+    constexpr unsigned Q_OFF = MB <= 3 ? 2 * AT_STAGE_BYTES : Q_END - TILE_ROWS * AT_ROW_BYTES;
+    constexpr bool Q_OVER_1 = Q_OFF < 2 * AT_STAGE_BYTES;
+    static_assert(Q_OFF >= AT_STAGE_BYTES && Q_OFF + TILE_ROWS * AT_ROW_BYTES <= Q_END, "queries of a tile in the ring");
+    request_masks(p, b, Ms, tid, wave_u);
+    request_queries<TILE_ROWS>(p, b, g, rt * TILE_ROWS, kv_base + Q_OFF, lane, wave_u);
     __builtin_amdgcn_sched_barrier(0);
-    const int n_raw = __builtin_amdgcn_readfirstlane(n_lane), P_raw = __builtin_amdgcn_readfirstlane(P_lane);
-    SplitRange sr;
-    int n = n_raw;
-    if (n < 1 || n > p.K_max) n = 0;
-    const int cap = p.max_pages * GRAFT_PAGE_SIZE;
-    int P = P_raw;
-    P = P < 0 ? 0 : (P > cap ? cap : P);
-    sr.n = n;
-    sr.P = P;
-    sr.total = n ? ((P + n) < cap ? (P + n) : cap) : 0;
-    const int n_stages = (sr.total + AT_STAGE - 1) / AT_STAGE;
-    const int spt = div31(n_stages + n_splits - 1, splits_magic);
-    sr.st0 = split * spt;
-    sr.st1 = (sr.st0 + spt) < n_stages ? (sr.st0 + spt) : n_stages;
-    if (sr.st1 < sr.st0) sr.st1 = sr.st0;
+    const SplitRange sr = split_range(p, n_raw, P_raw, split, n_splits, splits_magic);
     const int n_st = sr.st1 - sr.st0;
 #ifdef GRAFT_ATTN_STAMPS
     asm volatile("" : : "s"(n_st));              // (the stamp is taken when the lengths are there)
 #endif
     GRAFT_STAMP(AT_TS_LENGTHS);
 
-    // this split's block-table entries: the first 1024 are requested before anything is
-    // stored (one trip for all of them), a longer split takes the plain loop for the rest.
-    // The pages of this wavefront's first two stages are also requested on their own, as
-    // scalars: with them the first transfers can be issued without a trip through LDS and a
-    // barrier.
-    int32_t tbv[4];
+    // this split's block-table entries to LDS; the pages of this wavefront's first two stages as scalars: with them the first
+    // transfers can be issued without a trip through LDS and a barrier
     const int n_pg = n_st * (AT_STAGE / GRAFT_PAGE_SIZE);
     const int32_t* table = p.block_table + static_cast<size_t>(b) * p.max_pages;
     const int first_pg = sr.st0 * (AT_STAGE / GRAFT_PAGE_SIZE);
@@ -811,55 +616,39 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(GRAFT_ATTN_A
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         const int pg = first_pg + 4 * u + wave_u;
-        first_pages[u] = (4 * u + wave_u) < n_pg ? table[pg < last_pg ? pg : last_pg] : 0;
+        first_pages[u] = scalar_load(table, (4 * u + wave_u) < n_pg ? (pg < last_pg ? pg : last_pg) : 0);
     }
-    {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int pg = first_pg + tid + u * AT_THREADS;
-            tbv[u] = (tid + u * AT_THREADS) < n_pg ? table[pg < last_pg ? pg : last_pg] : 0;
-        }
+    for (int u = 0; u < n_pg; u += AT_THREADS) {
+        const int pg = first_pg + u + tid;
+        load_global_to_lds_b32(table + (pg < last_pg ? pg : last_pg), __builtin_amdgcn_readfirstlane(lds_address(Tb)) + 4 * u + 256 * wave_u);
     }
     GRAFT_STAMP(AT_TS_TABLE_REQ);
-    // ---- this wavefront's rows: Q' = bf16(Q * scale * log2 e) into AccVGPRs.  Done here, while
-    //      the table entries are on their way (Q was requested before them and vector memory
-    //      returns in order).
-    const float c_log2 = p.scale_log2e;
+    // O^T and the row sums to zero
     WaveRows<MB> w;
     static_for<0, MB>([&](auto rb_) {
         GRAFT_CONST(rb, rb_);
-        const float c_row = (r_base + rb * 16 + l16) < p.R ? c_log2 : 0.0f;
-        static_for<0, 16>([&](auto k_) {
-            GRAFT_CONST(k, k_);
-            acc_set_bits<q_reg<MB>(rb, 0) + k>(scale_bf16_pair(qd[rb][k >> 2][k & 3], c_row));
-        });
         w.thr[rb] = -INFINITY;
         w.thr_min = -INFINITY;
         w.negm[rb] = floatx4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (rb >= L_IN_ACC) w.lsum_v = floatx4{0.f, 0.f, 0.f, 0.f};
+        else
+            static_for<0, 4>([&](auto k_) {
+                GRAFT_CONST(k, k_);
+                acc_set<l_reg<MB>(rb) + k>(0.0f);
+            });
+        static_for<0, 32>([&](auto k_) {
+            GRAFT_CONST(k, k_);
+            acc_set<32 * rb + k>(0.0f);
+        });
     });
-    GRAFT_STAMP(AT_TS_Q_DONE);
-    // Everything that came from memory goes to LDS now, so that no load the compiler tracks is
-    // outstanding when the first transfers are issued (it counts its own loads only, and a
-    // wait for one of them behind the transfers would wait for the transfers as well).
-    // Bits of tree slots that the block table has no room for are dropped (none, if the caller keeps to it): what
-    // lies past the table's end repeats the last token.  (Here and not where the masks are applied: as one more
-    // argument of the loop that cost 1.6 % with three row blocks.)
-    const int left = sr.total - sr.P - 32 * (tid & 3);
-    const unsigned room = left >= 32 ? ~0u : (left <= 0 ? 0u : (1u << left) - 1u);
-    if (tid < n_mask_words) Ms[tid] = mw0 & room;
-    if (tid + AT_THREADS < n_mask_words) Ms[tid + AT_THREADS] = mw1 & room;
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-        if (tid + u * AT_THREADS < n_pg) Tb[tid + u * AT_THREADS] = tbv[u];
-    for (int k = tid + 4 * AT_THREADS; k < n_pg; k += AT_THREADS) {
-        const int pg = first_pg + k;
-        Tb[k] = table[pg < last_pg ? pg : last_pg];
-    }
+    // the first pipeline step multiplies zero probabilities with whatever buffer 3 holds: make it zeros
+    for (int k = tid; k < AT_STAGE * AT_ROW_BYTES / 16; k += AT_THREADS)
+        reinterpret_cast<uint4*>(&kv[AT_NBUF - 1][AT_STAGE * AT_ROW_BYTES])[k] = uint4{0u, 0u, 0u, 0u};
+    GRAFT_STAMP(AT_TS_ZEROED);
 
     // ---- stage pipeline: stage k (split-local) lives in kv[k & 3]; its loads are issued two
     //      stages ahead.  advance(k) = wait for this wavefront's loads of stage k (the next
     //      stage's stay in flight), meet the others, then start stage k + 2.
-    const unsigned kv_base = __builtin_amdgcn_readfirstlane(lds_address(&kv[0][0]));
     const int last_tok = sr.total - 1;
     // A wavefront moves one page per stage: page 4 * stage + wave, 16 token rows of K and of V,
     // four rows (1 KB) per instruction.  Lane (lg, l16) of instruction j fetches 16-byte chunk
@@ -903,41 +692,46 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(GRAFT_ATTN_A
             }
         }
     };
-    // The first stage starts here, before the rest of the set-up: its flight time covers the
-    // zeroing of the accumulators and the barrier.  The second follows after the zeroing: all
-    // workgroups start at the same time, and the memory system delivers their first stages
-    // sooner when the requests for the second ones are not queued in between.
     int next_issue = 0;                          // stages are issued in order, each once
-    GRAFT_STAMP(AT_TS_TABLE_LDS);
     if (n_st > 0) {
-        issue_page(0, __builtin_amdgcn_readfirstlane(first_pages[0]));
+        issue_page(0, first_pages[0]);
         next_issue = 1;
     }
     GRAFT_STAMP(AT_TS_STAGE0_REQ);
-
-    // O^T and the row sums to zero
-    static_for<0, MB>([&](auto rb_) {
-        GRAFT_CONST(rb, rb_);
-        if constexpr (rb >= L_IN_ACC) w.lsum_v = floatx4{0.f, 0.f, 0.f, 0.f};
-        else
-            static_for<0, 4>([&](auto k_) {
-                GRAFT_CONST(k, k_);
-                acc_set<l_reg<MB>(rb) + k>(0.0f);
-            });
-        static_for<0, 32>([&](auto k_) {
-            GRAFT_CONST(k, k_);
-            acc_set<32 * rb + k>(0.0f);
-        });
-    });
-    // the first pipeline step multiplies zero probabilities with whatever buffer 3 holds: make it zeros
-    for (int k = tid; k < AT_STAGE * AT_ROW_BYTES / 16; k += AT_THREADS)
-        reinterpret_cast<uint4*>(&kv[AT_NBUF - 1][AT_STAGE * AT_ROW_BYTES])[k] = uint4{0u, 0u, 0u, 0u};
-    if (n_st > 1) {
-        issue_page(1, __builtin_amdgcn_readfirstlane(first_pages[1]));
+    if (!Q_OVER_1 && n_st > 1) {
+        issue_page(1, first_pages[1]);
         next_issue = 2;
     }
-    GRAFT_STAMP(AT_TS_ZEROED);
+    // Queries, masks and table are there when only the stages are in flight.  Q' = bf16(Q * scale * log2 e) into AccVGPRs, while the
+    // first keys are on their way.
+    if (next_issue == 2) GRAFT_WAIT_VMCNT(2 * AT_LOADS_PER_STAGE);
+    else if (next_issue == 1) GRAFT_WAIT_VMCNT(AT_LOADS_PER_STAGE);
+    else GRAFT_WAIT_VMCNT(0);
     lds_barrier();                               // (LDS only: the transfers stay in flight)
+    GRAFT_STAMP(AT_TS_TABLE_LDS);
+    const float c_log2 = p.scale_log2e;
+    uintx4 qd[MB][4];                            // (all reads in flight)
+#pragma unroll
+    for (int rb = 0; rb < MB; ++rb)
+#pragma unroll
+        for (int ds = 0; ds < 4; ++ds)
+            qd[rb][ds] = __builtin_bit_cast(uintx4, load_k_operand(&kv[0][0] + Q_OFF + (wave_u * (16 * MB) + rb * 16) * AT_ROW_BYTES, ds, l16, lg));
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<0, MB>([&](auto rb_) {
+        GRAFT_CONST(rb, rb_);
+        static_for<0, 16>([&](auto k_) {
+            GRAFT_CONST(k, k_);
+            acc_set_bits<q_reg<MB>(rb, 0) + k>(scale_bf16_pair(qd[rb][k >> 2][k & 3], c_log2));
+        });
+    });
+    GRAFT_STAMP(AT_TS_Q_DONE);
+    if constexpr (Q_OVER_1) {
+        lds_barrier();                           // everybody has read
+        if (n_st > 1) {
+            issue_page(1, first_pages[1]);
+            next_issue = 2;
+        }
+    }
 
     int tb_next = Tb[2 * 4 + wave_u];            // the next stage's table entry is read one stage early
     auto issue_stage = [&](int k) {
@@ -1027,7 +821,7 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(GRAFT_ATTN_A
         // (where the exponents change after region 2 has turned the late row block's into
         //  probabilities, those are redone)
         if (__builtin_expect(t0 + AT_SUB > sr.P, 0)) {
-            grow = apply_tree_mask<MB>(xa, w, lm, lane, t0, sr.P, sr.n, r_base, p.R, p.g_magic, Ms);
+            grow = apply_tree_mask<MB>(xa, w, lm, lane, t0, sr.P, sr.n, sr.total - sr.P, r_base, p.R, p.g_magic, Ms);
             late_probabilities<MB>(xa, pla);
         }
         if (__builtin_expect(grow, 0)) {
@@ -1039,7 +833,7 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(GRAFT_ATTN_A
         region_qk_exp<MB, false>(cur + K_OFF + SUB, cur + V_OFF, w, xb, xa, pb, ring, lane);
         grow = region_pv_max<MB, true>(cur + V_OFF, nullptr, w, pb, pla, plb, xb, ones, ninf, lm, ring, lane);
         if (__builtin_expect(t0 + 2 * AT_SUB > sr.P, 0)) {
-            grow = apply_tree_mask<MB>(xb, w, lm, lane, t0 + AT_SUB, sr.P, sr.n, r_base, p.R, p.g_magic, Ms);
+            grow = apply_tree_mask<MB>(xb, w, lm, lane, t0 + AT_SUB, sr.P, sr.n, sr.total - sr.P, r_base, p.R, p.g_magic, Ms);
             late_probabilities<MB>(xb, plb);
         }
         if (__builtin_expect(grow, 0)) {
@@ -1084,7 +878,7 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(GRAFT_ATTN_A
             }
             const int t_sub0 = sr.st0 * AT_STAGE + j * AT_SUB;
             if (t_sub0 + AT_SUB > sr.P)
-                apply_tree_mask<MB>(xa, w, lm, lane, t_sub0, sr.P, sr.n, r_base, p.R, p.g_magic, Ms);
+                apply_tree_mask<MB>(xa, w, lm, lane, t_sub0, sr.P, sr.n, sr.total - sr.P, r_base, p.R, p.g_magic, Ms);
 #pragma unroll
             for (int rb = 0; rb < MB; ++rb) {
                 float mx = lm[rb];
@@ -1351,7 +1145,7 @@ static AttnPlan make_plan(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int
 // MFMA path wins from there on, up to 1.5 times on large problems.  Both costs are calibrated to about
 // 5 per cent, so the direct path has to be ahead by that much.
 struct PathChoice {
-    bool direct;
+    bool direct, only_direct;
     AttnPlan mfma;
     DirectPlan dir;
     DirectPlan unsplit;             // fp32 and D = 64: for callers without a workspace
@@ -1365,7 +1159,9 @@ static PathChoice make_choice(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv,
         return c;
     }
     c.mfma = make_plan(B, K_max, Hq, Hkv, max_pages);
-    c.direct = c.dir.cost < 0.95 * c.mfma.cost;
+    // (the MFMA path reads a sequence's queries through a buffer descriptor: less than 4 GB of them)
+    c.only_direct = static_cast<int64_t>(K_max) * Hq * AT_ROW_BYTES >= (int64_t{1} << 32);
+    c.direct = c.only_direct || c.dir.cost < 0.95 * c.mfma.cost;
     return c;
 }
 
@@ -1542,7 +1338,7 @@ extern "C" int32_t graft_tree_attn(const void* q, const void* k_cache, const voi
     const auto fits = [&](size_t need) { return need == 0 || (workspace && workspace_bytes >= need); };
     const bool either = dtype == GRAFT_BF16 && D == AT_D;
     // bf16 with D = 128 and a workspace too small for the direct plan: the MFMA path if its own plan needs no more
-    if (choice.direct && (!either || fits(choice.dir.ws_bytes) || !fits(choice.mfma.ws_bytes))) {
+    if (choice.direct && (!either || choice.only_direct || fits(choice.dir.ws_bytes) || !fits(choice.mfma.ws_bytes))) {
         const bool enough = fits(choice.dir.ws_bytes);
         if (!enough && either) return GRAFT_ERR_WORKSPACE;
         // (the other shapes have always run without a workspace: a caller that brings none, or too

@@ -33,9 +33,8 @@ import torch
 import paper_2605_20104_amd as graft
 from paper_2605_20104_amd import build as graft_build
 
-POINTS = ["lengths known", "table entries requested", "Q converted", "table and masks in LDS", "stage 0 requested",
-          "accumulators zeroed, stage 1 requested", "stage loop entered", "first keys arrived", "stage loop left",
-          "results written"]
+POINTS = ["lengths known", "table entries requested", "accumulators zeroed", "stage 0 requested", "table, masks and queries in LDS",
+          "queries converted", "stage loop entered", "first keys arrived", "stage loop left", "results written"]
 
 
 def mfma_calibration(lib):
