@@ -17,7 +17,7 @@ OBJ_DIR = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libgraft.so")
 LIB_TIMING = os.path.join(PKG, "libgraft_timing.so")     # the same library with the attention kernel's time stamps
 NATIVE = os.path.join(PKG, "_native.so")                 # tensor marshalling of the Python binding (csrc/binding.cpp)
-SOURCES = ["api.hip", "retrieve.hip", "tree_mask.hip", "tree_attn.hip", "tree_attn_direct.hip", "accept.hip", "matrix.hip", "kv_compact.hip", "prune.hip"]
+SOURCES = ["api.hip", "retrieve.hip", "tree_mask.hip", "tree_attn.hip", "tree_attn_wide.hip", "tree_attn_direct.hip", "accept.hip", "matrix.hip", "kv_compact.hip", "prune.hip"]
 
 # packed-fp32 code generation is switched off for every device compile; VGPR spills must not
 # land in AccVGPRs (the attention kernel manages those by hand).  Kernel arguments: the first 14 words arrive in
@@ -37,7 +37,14 @@ def _hipcc() -> str:
     return "hipcc"
 
 
-ATTN_ASM = os.path.join(OBJ_DIR, "tree_attn-hip-amdgcn-amd-amdhsa-gfx950.s")
+HAND_SCHEDULED = ["tree_attn.hip", "tree_attn_wide.hip"]          # their device assembly is kept and checked
+
+
+def _asm_of(src: str, directory: str = OBJ_DIR) -> str:
+    return os.path.join(directory, os.path.splitext(src)[0] + "-hip-amdgcn-amd-amdhsa-gfx950.s")
+
+
+ATTN_ASM = _asm_of("tree_attn.hip")
 
 
 def _compile(src: str, extra):
@@ -46,7 +53,7 @@ def _compile(src: str, extra):
 
 
 def _compile_to(src: str, extra, obj: str):
-    keep = ["-save-temps=obj"] if src == "tree_attn.hip" else []    # keeps the device assembly for the check below
+    keep = ["-save-temps=obj"] if src in HAND_SCHEDULED else []    # keeps the device assembly for the check below
     cmd = [_hipcc(), *HIPCC_FLAGS, *extra, *keep, "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if r.returncode != 0:
@@ -71,6 +78,16 @@ def _reg_span(tok: str):
     return None
 
 
+def _managed_accvgprs(symbol: str) -> int:
+    """AccVGPRs that a kernel manages by hand: tree_attn_mfma_kernel<MB> or tree_attn_wide_kernel<NB, MODE>; None for others."""
+    m = re.match(r"_ZN5graft21tree_attn_mfma_kernelILi(\d+)E", symbol)
+    if m:
+        mb = int(m.group(1))
+        return 48 * mb + 4 * min(mb, 4)
+    m = re.match(r"_ZN5graft21tree_attn_wide_kernelILi(\d+)E", symbol)
+    return 64 * int(m.group(1)) + 64 if m else None
+
+
 # Wait states between an MFMA and the first other instruction that may read its result: the
 # passes of the widest MFMA used here (8) plus 3, as for the compiler's own MFMAs, plus one.
 MFMA_RESULT_WAIT = 12
@@ -81,25 +98,27 @@ def check_attention_asm(asm_text: str):
     their hand-placed registers and inline-assembly MFMAs rely on.  Returns a list of
     violations (empty = fine):
       * no scratch memory (register spills) in any of the kernels;
-      * outside the inline-assembly blocks no instruction names an AccVGPR below
-        48 * MB + 4 * min(MB, 4) (the accumulators, the Q operand and the row sums live there
-        and the compiler must not touch them);
+      * outside the inline-assembly blocks no instruction names a hand-managed AccVGPR
+        (_managed_accvgprs: accumulators, Q operand, row sums);
       * no MFMA has a vector ALU instruction writing one of its VGPR sources within the two
         preceding wait states (an s_nop k counts k + 1): the hardware needs them and the
         compiler does not know that the asm statement is an MFMA.  The same holds for a
         v_accvgpr_write of an AccVGPR source;
       * no instruction other than an MFMA reads a register that an MFMA wrote within the
         MFMA_RESULT_WAIT preceding wait states, in program order across labels (the result of a
-        16x16x32 MFMA is written at the end of its passes, and nothing interlocks a vector ALU,
-        LDS or memory instruction, or a v_accvgpr_read, that comes earlier).
+        MFMA is written at the end of its passes, and nothing interlocks a vector ALU,
+        LDS or memory instruction, or a v_accvgpr_read, that comes earlier).  An MFMA issues no sooner
+        than the one in front of it has gone through its passes: those count as wait states too.
     """
     problems = []
     lines = asm_text.split("\n")
-    kernel, mb, in_asm, desc = None, 0, False, ""
+    kernel, managed, in_asm, desc = None, 0, False, ""
     history = []          # (wait states, destination span or None) of the preceding instructions
     results = []          # [wait states since, span] of MFMA results still inside MFMA_RESULT_WAIT
+    last_mfma = [0, 0]    # passes of the last MFMA, wait states since
 
     def age(states):
+        last_mfma[1] += states
         for r in results:
             r[0] += states
         while results and results[0][0] >= MFMA_RESULT_WAIT:
@@ -107,9 +126,10 @@ def check_attention_asm(asm_text: str):
 
     for ln, raw in enumerate(lines, 1):
         text = raw.split(";")[0].strip() if not raw.lstrip().startswith(";") else ""
-        m = re.match(r"^(_ZN5graft21tree_attn_mfma_kernelILi(\d+)E\w*):", raw)
-        if m:
-            kernel, mb, history, results = m.group(1), int(m.group(2)), [(1, ("v", 0, 1 << 20))], []
+        m = re.match(r"^(_Z\w+):", raw)
+        if m and _managed_accvgprs(m.group(1)):
+            kernel, managed, history, results = m.group(1), _managed_accvgprs(m.group(1)), [(1, ("v", 0, 1 << 20))], []
+            last_mfma[:] = [0, 0]
             continue
         if kernel and raw.startswith(".Lfunc_end"):
             kernel = None
@@ -126,7 +146,7 @@ def check_attention_asm(asm_text: str):
             continue
         m = re.match(r"\s*\.amdhsa_private_segment_fixed_size\s+(\d+)", raw)
         if m:
-            if "tree_attn_mfma_kernel" in desc and int(m.group(1)) != 0:
+            if _managed_accvgprs(desc) and int(m.group(1)) != 0:
                 problems.append("%s uses %s bytes of scratch memory (spills)" % (desc, m.group(1)))
             continue
         if not kernel:
@@ -143,7 +163,7 @@ def check_attention_asm(asm_text: str):
         if not in_asm:
             for a in args:
                 sp = _reg_span(a)
-                if sp and sp[0] == "a" and sp[1] < 48 * mb + 4 * min(mb, 4):
+                if sp and sp[0] == "a" and sp[1] < managed:
                     problems.append("line %d (%s): compiler-generated use of a hand-managed AccVGPR: %s"
                                     % (ln, kernel, text))
         if op.startswith("v_mfma"):
@@ -158,7 +178,8 @@ def check_attention_asm(asm_text: str):
                     break
                 states += w
             history.append((1, None))
-            age(1)
+            age(max(1, last_mfma[0] - last_mfma[1]))
+            last_mfma[:] = [8 if "32x32" in op else 4, 0]
             d = _reg_span(args[0]) if args else None
             if d:
                 results.append([0, d])
@@ -190,15 +211,16 @@ def check_attention_asm(asm_text: str):
     return problems
 
 
-def _check_and_clean(asm_path: str, what: str):
-    with open(asm_path) as f:
-        problems = check_attention_asm(f.read())
-    for name in os.listdir(OBJ_DIR):             # the other intermediate files are not needed
+def _check_and_clean(directory: str, what: str):
+    for src in HAND_SCHEDULED:
+        with open(_asm_of(src, directory)) as f:
+            problems = check_attention_asm(f.read())
+        if problems:
+            raise RuntimeError("%s%s: the generated assembly breaks a rule of the hand-scheduled kernels:\n  "
+                               % (src, what) + "\n  ".join(problems[:20]))
+    for name in os.listdir(directory):           # the other intermediate files are not needed
         if name.startswith("tree_attn") and not name.endswith((".o", "gfx950.s")) or name.endswith(".hipfb"):
-            os.remove(os.path.join(OBJ_DIR, name))
-    if problems:
-        raise RuntimeError("%s: the generated assembly breaks a rule of the hand-scheduled kernel:\n  "
-                           % what + "\n  ".join(problems[:20]))
+            os.remove(os.path.join(directory, name))
 
 
 def _link(objects, lib: str) -> str:
@@ -242,7 +264,7 @@ def build(verbose: bool = False, extra_flags=()) -> str:
         for _, w in results:
             if w:
                 print(w)
-    _check_and_clean(ATTN_ASM, "tree_attn.hip")
+    _check_and_clean(OBJ_DIR, "")
     return _link([o for o, _ in results], LIB)
 
 
@@ -250,25 +272,20 @@ def build_timing(verbose: bool = False) -> str:
     """libgraft_timing.so: the library with the attention kernel compiled with -DGRAFT_ATTN_STAMPS
     (time stamps per workgroup, read by `python -m paper_2605_20104_amd.timing`).  The other
     objects are those of the last build(); the stamped kernels pass the same assembly check."""
-    others = [os.path.join(OBJ_DIR, os.path.splitext(s)[0] + ".o") for s in SOURCES if s != "tree_attn.hip"]
+    others = [os.path.join(OBJ_DIR, os.path.splitext(s)[0] + ".o") for s in SOURCES if s not in HAND_SCHEDULED]
     if not all(os.path.exists(o) for o in others):
         build(verbose)
     src_dir = os.path.join(OBJ_DIR, "timing")
     os.makedirs(src_dir, exist_ok=True)
-    obj = os.path.join(src_dir, "tree_attn.o")
-    _, warn = _compile_to("tree_attn.hip", ["-DGRAFT_ATTN_STAMPS"], obj)
-    if verbose and warn:
-        print(warn)
-    asm = os.path.join(src_dir, "tree_attn-hip-amdgcn-amd-amdhsa-gfx950.s")
-    with open(asm) as f:
-        problems = check_attention_asm(f.read())
-    for name in os.listdir(src_dir):
-        if not name.endswith((".o", "gfx950.s")):
-            os.remove(os.path.join(src_dir, name))
-    if problems:
-        raise RuntimeError("tree_attn.hip (timing build): the generated assembly breaks a rule of the "
-                           "hand-scheduled kernel:\n  " + "\n  ".join(problems[:20]))
-    return _link([obj, *others], LIB_TIMING)
+    objects = [os.path.join(src_dir, os.path.splitext(s)[0] + ".o") for s in HAND_SCHEDULED]
+    with ThreadPoolExecutor(max_workers=len(objects)) as ex:
+        results = list(ex.map(lambda x: _compile_to(x[0], ["-DGRAFT_ATTN_STAMPS"], x[1]), zip(HAND_SCHEDULED, objects)))
+    if verbose:
+        for _, warn in results:
+            if warn:
+                print(warn)
+    _check_and_clean(src_dir, " (timing build)")
+    return _link([*objects, *others], LIB_TIMING)
 
 
 if __name__ == "__main__":

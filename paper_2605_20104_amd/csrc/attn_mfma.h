@@ -1,5 +1,5 @@
-// Parts of the MFMA path of graft_tree_attn (tree_attn.hip): sizes, time stamps, set-up, transfers from memory to LDS, accumulators
-// in hand-placed AccVGPRs.
+// What the kernels of the MFMA path of graft_tree_attn share (tree_attn.hip, tree_attn_wide.hip): sizes, time stamps, set-up,
+// transfers from memory to LDS, accumulators in hand-placed AccVGPRs.
 #pragma once
 #include <type_traits>
 
@@ -68,6 +68,9 @@ enum AttnStamp {
 #define GRAFT_SPAN_END(k) ((void)0)
 #define GRAFT_STAMPS_WRITE(p, n_stages) ((void)0)
 #endif
+
+// The kernel with 32-row blocks (tree_attn_wide.hip): tiles of 192, 256 or 384 rows.
+int32_t launch_wide(int32_t tile_rows, const AttnParams& p, hipStream_t s);
 
 struct SplitRange { int st0, st1, P, n, total; };       // stages, prefix length, nodes, tokens
 __device__ __forceinline__ SplitRange split_range(const AttnParams& p, int n_raw, int P_raw, int split, int n_splits, uint32_t splits_magic) {

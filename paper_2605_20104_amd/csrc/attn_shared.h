@@ -25,9 +25,10 @@ struct AttnParams {
     const int32_t* n_nodes;
     const u64* mask;
     // partial rows of the splits.  MFMA path: fp16 [B][Hkv][splits][R_pad/16][D/32] blocks of 1 KB: [lane][2][4],
-    // lane = MFMA accumulator lane, two adjacent 16-dim tiles per block; direct path: fp32 [B][Hkv][splits][R_pad][D]
+    // lane = MFMA accumulator lane, two adjacent 16-dim tiles per block; with 32-row blocks [R_pad/32][D/16] of [lane][8]; direct path: fp32 [B][Hkv][splits][R_pad][D]
     unsigned short* ws_o;
-    // MFMA path: [B][Hkv][splits][R_pad][4] (max in log2 units, sum, scale of the stored row, 0); direct path:
+    // MFMA path: [B][Hkv][splits][R_pad][4] (reference in log2 units, sum, scale of the stored row, 0; with 32-row blocks a
+    // scale for either half of the dims); direct path:
     // [B][Hkv][splits][R_pad][2] (max in log2 units, sum)
     float* ws_ml;
     int64_t page_stride, token_stride, head_stride;

@@ -50,7 +50,6 @@
 
 namespace graft {
 
-constexpr int AT_MAX_MB = 5;            // 16-row MFMA blocks per wavefront (5 * 48 = 240 of 256 AccVGPRs)
 constexpr float AT_LAZY_LOG2 = 24.0f;  // a row keeps its reference while exponents stay below 2^24
 
 // ---------------------------------------------------------------------------
@@ -961,10 +960,11 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(GRAFT_ATTN_A
 // flight, go with U) and has all their loads in flight at once (a split without keys has
 // weight 0 and a zero block); with more than 16 splits, up to four wavefronts share a tile
 // pair and the first of them merges their sums through LDS.
+// WIDE: the partial rows of tree_attn_wide_kernel, in blocks of 32 rows x 16 dims.
 constexpr int CB_MAX_SPLITS = 16;
 constexpr int CB_MAX_WAVES = 8;          // per workgroup; the host picks a multiple of the wavefronts per tile pair
 
-template <int U>
+template <int U, bool WIDE>
 __global__ __launch_bounds__(64 * CB_MAX_WAVES) void tree_attn_combine_kernel(
     const unsigned short* ws_o, const float* ws_ml, const int32_t* n_nodes, int32_t n_tiles, int32_t wpt, int32_t tiles_per_wg, int32_t R,
     int32_t R_pad, int32_t n_splits, int32_t n_kv_heads, AttnParams p) {
@@ -973,14 +973,15 @@ __global__ __launch_bounds__(64 * CB_MAX_WAVES) void tree_attn_combine_kernel(
     // (m, den, acc[8]) per lane of the helper wavefronts (only U = 16 has helpers)
     __shared__ float xch[U == CB_MAX_SPLITS ? CB_MAX_WAVES : 1][10][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int l16 = lane & 15, lg = lane >> 4;
-    const int n_blk = R_pad >> 4;                                           // 16-row blocks per (b, g)
-    const int tile = static_cast<int>(blockIdx.x) * tiles_per_wg + wave / wpt;   // over B*Hkv*n_blk*4
+    constexpr int BLK = WIDE ? 32 : 16, PIECES = AT_D * BLK / 512;          // rows of a block, tile pairs in it
+    const int lr = lane % BLK, lg = lane / BLK;
+    const int n_blk = R_pad / BLK;                                          // row blocks per (b, g)
+    const int tile = static_cast<int>(blockIdx.x) * tiles_per_wg + wave / wpt;   // over B*Hkv*n_blk*PIECES
     const int part_i = wave % wpt;                                            // which CB_SPLITS splits
-    const int dp = tile & 3;                                                  // dims 32 dp .. 32 dp + 31
-    const int bg = (tile >> 2) / n_blk, blk = (tile >> 2) - bg * n_blk;       // b * Hkv + g, row block
+    const int dp = tile % PIECES;                                             // dims 32 dp .. 32 dp + 31 (WIDE: 16 dp ..)
+    const int bg = (tile / PIECES) / n_blk, blk = (tile / PIECES) - bg * n_blk;       // b * Hkv + g, row block
     const int b = bg / n_kv_heads, g = bg - b * n_kv_heads;
-    const int r = blk * 16 + l16;
+    const int r = blk * BLK + lr;
     const bool live = tile < n_tiles && r < R;                              // not a padding row or tile
     const int ns = n_splits;
     const int s0 = part_i * CB_SPLITS;
@@ -990,8 +991,8 @@ __global__ __launch_bounds__(64 * CB_MAX_WAVES) void tree_attn_combine_kernel(
     int n = 0;
     if (live) {
         n = n_nodes[b];                                                     // needed only at the end
-        const size_t base = static_cast<size_t>(bg) * ns * R_pad + blk * 16;     // row index of split 0
-        const float* mlrow = ws_ml + (base + l16) * 4;
+        const size_t base = static_cast<size_t>(bg) * ns * R_pad + blk * BLK;    // row index of split 0
+        const float* mlrow = ws_ml + (base + lr) * 4;
         const size_t ml_stride = static_cast<size_t>(R_pad) * 4;
         const unsigned short* otile = ws_o + base * AT_D + 512 * dp + 8 * lane;
         const size_t o_stride = static_cast<size_t>(R_pad) * AT_D;
@@ -1014,7 +1015,7 @@ __global__ __launch_bounds__(64 * CB_MAX_WAVES) void tree_attn_combine_kernel(
             const bool on = (s0 + u) < ns && ml[u][0] > -INFINITY;
             const float wl = on ? __builtin_amdgcn_exp2f(ml[u][0] - m_run) * ml[u][1] : 0.f;
             den += wl;
-            const float wu = wl * ml[u][2];
+            const float wu = wl * (WIDE && dp >= PIECES / 2 ? ml[u][3] : ml[u][2]);
             const halfx8 h = __builtin_bit_cast(halfx8, ov[u]);
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc[e] += wu * static_cast<float>(h[e]);
@@ -1046,7 +1047,7 @@ __global__ __launch_bounds__(64 * CB_MAX_WAVES) void tree_attn_combine_kernel(
     if (!live) return;
     const int i = (r * p.g_magic) >> 16, hl = r - i * p.G;                     // i = r / G
     unsigned short* outp = static_cast<unsigned short*>(p.out) +
-        ((static_cast<int64_t>(b) * p.K_max + i) * p.Hq + g * p.G + hl) * AT_D + 32 * dp + 4 * lg;
+        ((static_cast<int64_t>(b) * p.K_max + i) * p.Hq + g * p.G + hl) * AT_D + (WIDE ? 16 * dp + 8 * lg : 32 * dp + 4 * lg);
     if (n < 1 || n > p.K_max) n = 0;
     const float inv = den > 0.f ? 1.0f / den : 0.f;
     unsigned o[4];
@@ -1054,6 +1055,12 @@ __global__ __launch_bounds__(64 * CB_MAX_WAVES) void tree_attn_combine_kernel(
     for (int k = 0; k < 4; ++k)
         o[k] = float_to_bf16_bits(acc[2 * k] * inv) | (float_to_bf16_bits(acc[2 * k + 1] * inv) << 16);
     if (i >= n) o[0] = o[1] = o[2] = o[3] = 0u;   // rows of absent nodes are zeros whatever their Q rows held
+    if constexpr (WIDE) {                         // lanes r and r + 32 have dims 4 lg .. +3 and 8 + 4 lg .. +3: eight in a row for either
+        const auto x = __builtin_amdgcn_permlane32_swap(o[0], o[2], false, false);
+        const auto y = __builtin_amdgcn_permlane32_swap(o[1], o[3], false, false);
+        *reinterpret_cast<uintx4*>(outp) = uintx4{x[0], y[0], x[1], y[1]};
+        return;
+    }
     *reinterpret_cast<uint2*>(outp) = uint2{o[0], o[1]};          // dims 32 dp + 4 lg .. +3
     *reinterpret_cast<uint2*>(outp + 16) = uint2{o[2], o[3]};     // dims 32 dp + 16 + 4 lg .. +3
 }
@@ -1062,9 +1069,10 @@ __global__ __launch_bounds__(64 * CB_MAX_WAVES) void tree_attn_combine_kernel(
 // host side
 // ---------------------------------------------------------------------------
 struct AttnPlan {
-    int mb, n_row_tiles, n_splits, r_pad;
+    int mb, n_row_tiles, n_splits, r_pad;       // mb: 64 rows of a tile each
+    bool wide;                                  // tree_attn_wide_kernel
     size_t ws_o_bytes, ws_bytes;
-    double cost;                    // estimated cycles
+    double cost, line;              // estimated cycles; those the direct path is compared with
 };
 
 int device_compute_units() {
@@ -1088,46 +1096,82 @@ static thread_local int g_force_splits = 0, g_force_row_tiles = 0;
 // Launch shape of the MFMA path.  One workgroup per compute unit is resident at a time, so
 // the job runs in ceil(workgroups / CUs) rounds, each as long as one workgroup's pass: a
 // fixed part (set-up, Q conversion, writing the partial results) plus its stages.  The
-// numbers are cycles measured on MI355X (per stage about 680 MB + 1100, fixed about
-// 3300 MB + 8000); the plan takes the row tiling (MB <= 5 row blocks per wavefront) and the
+// numbers are cycles measured on MI355X; the plan takes the row tiling (tiles of 64 mb rows) and the
 // number of splits (<= 64, each with at most AT_MAX_SPLIT_PAGES pages) that make the
 // estimate smallest.  It depends on the capacity max_pages, not on the actual lengths.
+//
+// Which kernel: tiles of 64, 128 and 320 rows have the one with 16-row blocks (per stage about 680 mb + 1100, fixed about 3300 mb + 8000), of
+// 256 and 384 the one with 32-row blocks, of 192 either: its loop is faster, its fixed part (twice the rows a wavefront, a merge
+// through LDS) longer.  us a call, 16-row / 32-row blocks, tiles of 192 rows by stages of a split: 8 stages 25.6 / 26.1 and
+// 24.7 / 25.2, 9 25.2 / 24.0, 17 35.7 / 33.4, 30 60.8 / 60.5 (one tile, memory-bound), 32 57.9 / 54.6, 33 56.6 / 53.3, 257 408 / 367;
+// up to ten stages, where either is ahead by a few per cent, the 16-row kernel keeps them.
+// 256 rows: 5 stages 22.8 / 21.7, 17 43.8 / 43.7, 24 60.6 / 60.5, 63 137.1 / 133.2.  384 rows against two tiles of 192, 16-row
+// blocks not offered: 16 for 32 stages 58.8 / 54.6, 128 for 257 365 / 367 (a round 380 / 399 us).
+// The best shape of either kernel is found first; between them the launch that merges splits counts, and the 32-row kernel has to
+// be ahead by the 3 per cent to which the costs are calibrated.  Tiles of 192 rows that need no split against 320 rows in two:
+// 12 stages 24.5 / 31.9 us, 16 29.2 / 35.5 (8 sequences, 80 x 64 heads on 8).
+constexpr int WIDE_MIN_STAGES = 11;
+struct TileCost { double stage, fixed; };
+static TileCost tile_cost(int mb, bool wide) {
+    if (!wide) return {680.0 * mb + 1100.0, 3300.0 * mb + 8000.0};
+    return mb == 3 ? TileCost{2750.0, 19500.0} : (mb == 4 ? TileCost{3650.0, 21000.0} : TileCost{5300.0, 27000.0});
+}
+static bool has_kernel(int mb, bool wide, int64_t stages_per_split) {
+    return wide ? mb == 4 || mb == 6 || (mb == 3 && stages_per_split >= WIDE_MIN_STAGES) : mb <= 3 || mb == 5;
+}
+// (for the line between this path and the direct one, which was measured with 16-row blocks in tiles of 256 rows too: a shape
+// that moved across it for a few per cent would be further from a 64-bit reference, 2.33e-3 -> 2.37e-3)
+static bool had_kernel(int mb, bool, int64_t) { return mb <= 5; }
 static AttnPlan make_plan(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t max_pages) {
-    AttnPlan pl{};
     const int R = K_max * (Hq / Hkv);
     const int rows_per_mb = AT_WAVES * 16;                       // rows a workgroup covers per MB
     const int64_t stages = (static_cast<int64_t>(max_pages) * GRAFT_PAGE_SIZE + AT_STAGE - 1) / AT_STAGE;
     const int64_t min_splits = (stages * (AT_STAGE / GRAFT_PAGE_SIZE) + AT_MAX_SPLIT_PAGES - 1) / AT_MAX_SPLIT_PAGES;
     const int64_t cus = device_compute_units();
-    const int rt_min = (R + rows_per_mb * AT_MAX_MB - 1) / (rows_per_mb * AT_MAX_MB);
-    const int rt_max = (R + rows_per_mb - 1) / rows_per_mb;
-    double best = -1.0;
-    for (int rt = rt_min; rt <= rt_max && rt <= rt_min + 3; ++rt) {
-        const int mb = (R + rt * rows_per_mb - 1) / (rt * rows_per_mb);
-        const double c_stage = 680.0 * mb + 1100.0, c_fixed = 3300.0 * mb + 8000.0;
-        const int64_t units = static_cast<int64_t>(B) * Hkv * rt;
-        int64_t s_hi = stages < AT_MAX_SPLITS ? stages : AT_MAX_SPLITS;
-        if (s_hi < 1) s_hi = 1;
-        for (int64_t sp = min_splits < 1 ? 1 : min_splits; sp <= s_hi; ++sp) {
-            const int64_t rounds = (units * sp + cus - 1) / cus;
-            const int64_t per = (stages + sp - 1) / sp;
-            const double cost = rounds * (c_fixed + per * c_stage) + 300.0 * sp;
-            if (best < 0.0 || cost < best) {
-                best = cost;
-                pl.n_row_tiles = rt;
-                pl.mb = mb;
-                pl.n_splits = static_cast<int>(sp);
-                pl.cost = cost + (sp > 1 ? 11500.0 - 200.0 * sp : 0.0);   // with the merge launch, as measured
+    const auto best_of = [&](bool wide, bool (*offered)(int, bool, int64_t)) {
+        AttnPlan pl{};
+        const int mb_max = wide ? 6 : 5;
+        const int rt_min = (R + rows_per_mb * mb_max - 1) / (rows_per_mb * mb_max);
+        const int rt_max = (R + rows_per_mb - 1) / rows_per_mb;
+        double best = -1.0;
+        for (int rt = rt_min; rt <= rt_max && rt <= rt_min + 3; ++rt) {
+            const int mb = (R + rt * rows_per_mb - 1) / (rt * rows_per_mb);
+            const TileCost c = tile_cost(mb, wide);
+            const int64_t units = static_cast<int64_t>(B) * Hkv * rt;
+            int64_t s_hi = stages < AT_MAX_SPLITS ? stages : AT_MAX_SPLITS;
+            if (s_hi < 1) s_hi = 1;
+            for (int64_t sp = min_splits < 1 ? 1 : min_splits; sp <= s_hi; ++sp) {
+                const int64_t rounds = (units * sp + cus - 1) / cus;
+                const int64_t per = (stages + sp - 1) / sp;
+                if (!offered(mb, wide, per)) continue;
+                const double cost = rounds * (c.fixed + per * c.stage) + 300.0 * sp;
+                const double total = cost + (sp > 1 ? 11500.0 - 200.0 * sp : 0.0);    // with the merge launch, as measured
+                if (best < 0.0 || (wide ? total : cost) < best) {
+                    best = wide ? total : cost;
+                    pl.n_row_tiles = rt;
+                    pl.mb = mb;
+                    pl.wide = wide;
+                    pl.n_splits = static_cast<int>(sp);
+                    pl.cost = total;
+                }
             }
         }
-    }
+        return pl;
+    };
+    const AttnPlan narrow = best_of(false, has_kernel), wide = best_of(true, has_kernel);
+    AttnPlan pl = wide.mb > 0 && (narrow.mb == 0 || wide.cost < 0.97 * narrow.cost) ? wide : narrow;
+    pl.line = best_of(false, had_kernel).cost;
 #ifdef GRAFT_ATTN_STAMPS
     // timing build: a plan held fixed by the caller (to compare runs that differ in nothing else)
-    if (g_force_splits >= (min_splits < 1 ? 1 : min_splits) && g_force_splits <= (stages < AT_MAX_SPLITS ? stages : AT_MAX_SPLITS) &&
-        g_force_row_tiles >= rt_min && g_force_row_tiles <= rt_max) {
-        pl.n_splits = g_force_splits;
-        pl.n_row_tiles = g_force_row_tiles;
-        pl.mb = (R + pl.n_row_tiles * rows_per_mb - 1) / (pl.n_row_tiles * rows_per_mb);
+    if (g_force_splits >= (min_splits < 1 ? 1 : min_splits) && g_force_splits <= (stages < AT_MAX_SPLITS ? stages : AT_MAX_SPLITS) && g_force_row_tiles >= 1) {
+        const int mb = (R + g_force_row_tiles * rows_per_mb - 1) / (g_force_row_tiles * rows_per_mb);
+        const int64_t per = (stages + g_force_splits - 1) / g_force_splits;
+        if (has_kernel(mb, true, per) || has_kernel(mb, false, per)) {
+            pl.n_splits = g_force_splits;
+            pl.n_row_tiles = g_force_row_tiles;
+            pl.mb = mb;
+            pl.wide = has_kernel(mb, true, per);
+        }
     }
 #endif
     pl.r_pad = pl.n_row_tiles * pl.mb * rows_per_mb;
@@ -1161,7 +1205,7 @@ static PathChoice make_choice(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv,
     c.mfma = make_plan(B, K_max, Hq, Hkv, max_pages);
     // (the MFMA path reads a sequence's queries through a buffer descriptor: less than 4 GB of them)
     c.only_direct = static_cast<int64_t>(K_max) * Hq * AT_ROW_BYTES >= (int64_t{1} << 32);
-    c.direct = c.only_direct || c.dir.cost < 0.95 * c.mfma.cost;
+    c.direct = c.only_direct || c.dir.cost < 0.95 * c.mfma.line;
     return c;
 }
 
@@ -1355,14 +1399,18 @@ extern "C" int32_t graft_tree_attn(const void* q, const void* k_cache, const voi
 #ifdef GRAFT_ATTN_STAMPS
     p.stamps = static_cast<size_t>(grid.x) * AT_STAMPS * sizeof(unsigned long long) <= g_stamps_bytes ? g_stamps : nullptr;
 #endif
-    switch (pl.mb) {
-        case 1: launch_attn(tree_attn_mfma_kernel<1>, grid, dim3(AT_THREADS), 0, s, p, 1, 1); break;
-        case 2: launch_attn(tree_attn_mfma_kernel<2>, grid, dim3(AT_THREADS), 0, s, p, 1, 1); break;
-        case 3: launch_attn(tree_attn_mfma_kernel<3>, grid, dim3(AT_THREADS), 0, s, p, 1, 1); break;
-        case 4: launch_attn(tree_attn_mfma_kernel<4>, grid, dim3(AT_THREADS), 0, s, p, 1, 1); break;
-        default: launch_attn(tree_attn_mfma_kernel<5>, grid, dim3(AT_THREADS), 0, s, p, 1, 1); break;
+    int32_t rc;
+    if (pl.wide) {
+        rc = launch_wide(64 * pl.mb, p, s);
+    } else {
+        switch (pl.mb) {
+            case 1: launch_attn(tree_attn_mfma_kernel<1>, grid, dim3(AT_THREADS), 0, s, p, 1, 1); break;
+            case 2: launch_attn(tree_attn_mfma_kernel<2>, grid, dim3(AT_THREADS), 0, s, p, 1, 1); break;
+            case 3: launch_attn(tree_attn_mfma_kernel<3>, grid, dim3(AT_THREADS), 0, s, p, 1, 1); break;
+            default: launch_attn(tree_attn_mfma_kernel<5>, grid, dim3(AT_THREADS), 0, s, p, 1, 1); break;
+        }
+        rc = check_launch();
     }
-    int32_t rc = check_launch();
     if (rc != GRAFT_OK || pl.n_splits == 1) return rc;
     // wpt wavefronts per tile pair (cb_u splits each); as many tile pairs per workgroup as
     // make the workgroups one round (or, capped, a few whole rounds) over the compute units
@@ -1379,11 +1427,16 @@ extern "C" int32_t graft_tree_attn(const void* q, const void* k_cache, const voi
         hipLaunchKernelGGL(kernel, cgrid, cblock, 0, s, p.ws_o, p.ws_ml, n_nodes, static_cast<int32_t>(n_tiles), wpt, static_cast<int32_t>(tpw), p.R,
                            p.R_pad, p.n_splits, Hkv, p);
     };
-    switch (cb_u) {
-        case 2: combine(tree_attn_combine_kernel<2>); break;
-        case 4: combine(tree_attn_combine_kernel<4>); break;
-        case 8: combine(tree_attn_combine_kernel<8>); break;
-        default: combine(tree_attn_combine_kernel<16>); break;
-    }
+    const auto merge = [&](auto wide_) {
+        constexpr bool WIDE = decltype(wide_)::value;
+        switch (cb_u) {
+            case 2: combine(tree_attn_combine_kernel<2, WIDE>); break;
+            case 4: combine(tree_attn_combine_kernel<4, WIDE>); break;
+            case 8: combine(tree_attn_combine_kernel<8, WIDE>); break;
+            default: combine(tree_attn_combine_kernel<16, WIDE>); break;
+        }
+    };
+    if (pl.wide) merge(std::true_type{});
+    else merge(std::false_type{});
     return check_launch();
 }
