@@ -438,10 +438,9 @@ def attention_kernel_name(w, max_pages):
     from paper_2605_20104_amd import build
     if not os.path.exists(build.LIB_TIMING):
         return "graft_tree_attn main kernel"
-    plan = (ctypes.c_int32 * 4)()
-    rc = ctypes.CDLL(build.LIB_TIMING).graft_attn_plan(w.B, w.K, w.Hq, w.Hkv, w.D, max_pages, 0 if w.dtype == "f32" else 1, plan)
-    assert rc == 0, rc
-    return "tree_attn_mfma_kernel" if plan[0] else "tree_attn_direct_kernel"
+    name = ctypes.CDLL(build.LIB_TIMING).graft_attn_kernel_name
+    name.restype = ctypes.c_char_p
+    return name(w.B, w.K, w.Hq, w.Hkv, w.D, max_pages, 0 if w.dtype == "f32" else 1).decode()
 
 
 def cpu_baseline(w, s, att, att_bytes, budget_s):

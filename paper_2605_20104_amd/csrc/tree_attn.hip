@@ -10,7 +10,7 @@
 //       grid  : one workgroup of 256 threads (4 wavefronts, one per SIMD, 512
 //               registers each) per (row tile, split, KV head, sequence); the
 //               host plan sizes it to about one workgroup per compute unit.
-//       rows  : a wavefront owns 16*MB query rows (MB <= 5 MFMA row blocks).  Its
+//       rows  : a wavefront owns 16*MB query rows (MB = 1, 2, 3 or 5 MFMA row blocks).  Its
 //               O^T accumulators and the Q operand live in hand-placed AccVGPRs
 //               and are only touched by inline-asm MFMAs inside the loop.
 //       K/V   : 64-token stages (4 pages) go global -> LDS directly (no register
@@ -42,6 +42,9 @@
 //     bf16 straight from the accumulators.  Otherwise partials (reference, sum, and
 //     O / sum as fp16 rows with a per-row scale) go to the workspace; a small combine
 //     kernel merges the splits and writes bf16.
+//
+//     Long key ranges with many rows take tiles of 192, 256 or 384 rows in blocks of 32 instead:
+//     tree_attn_wide.hip, with the same stages and workspace sizes; the plan and the merge are here.
 //
 // (2) fp32 storage, D = 64, and bf16 with D = 128 where the keys are few: tree_attn_direct.hip.
 #include <cstring>
@@ -1341,6 +1344,12 @@ extern "C" int32_t graft_attn_plan(int32_t B, int32_t K_max, int32_t Hq, int32_t
     plan[2] = c.direct ? c.dir.n_row_tiles : c.mfma.n_row_tiles;
     plan[3] = c.direct ? c.dir.n_splits : c.mfma.n_splits;
     return GRAFT_OK;
+}
+// The name of the call's main kernel, null where the shape is refused.
+extern "C" const char* graft_attn_kernel_name(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages, int32_t dtype) {
+    if (!graft::attn_shape_ok(B, K_max, Hq, Hkv, D, max_pages)) return nullptr;
+    const graft::PathChoice& c = graft::choose_path(B, K_max, Hq, Hkv, D, max_pages, dtype);
+    return c.direct ? "tree_attn_direct_kernel" : (c.mfma.wide ? "tree_attn_wide_kernel" : "tree_attn_mfma_kernel");
 }
 // Holds the launch plan of this host thread's following calls (workspace query included) at
 // n_splits splits and n_row_tiles row tiles where the shape allows them; zeros give the plan
