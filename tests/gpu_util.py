@@ -77,16 +77,18 @@ def us_per_call(call, reps=20):
     return sorted(times)[3]
 
 
-AttnPlan = collections.namedtuple("AttnPlan", "path row_blocks row_tiles splits")
+AttnPlan = collections.namedtuple("AttnPlan", "path row_blocks row_tiles splits kernel")
 
 
 def attn_plan(B, K, Hq, Hkv, D, max_pages, dtype):
-    """The path ("mfma" or "direct") and launch shape of an attention call, as the timing build tells it: the product
-    library plans with the same code."""
+    """The path ("mfma" or "direct"), launch shape and main kernel of an attention call, as the timing build tells it: the
+    product library plans with the same code."""
     lib = ctypes.CDLL(build.LIB_TIMING)
+    lib.graft_attn_kernel_name.restype = ctypes.c_char_p
+    shape = (B, K, Hq, Hkv, D, max_pages, graft.GRAFT_F32 if dtype == "f32" else graft.GRAFT_BF16)
     plan = (ctypes.c_int32 * 4)()
-    assert lib.graft_attn_plan(B, K, Hq, Hkv, D, max_pages, graft.GRAFT_F32 if dtype == "f32" else graft.GRAFT_BF16, plan) == 0
-    return AttnPlan(("direct", "mfma")[plan[0]], *plan[1:])
+    assert lib.graft_attn_plan(*shape, plan) == 0
+    return AttnPlan(("direct", "mfma")[plan[0]], *plan[1:], lib.graft_attn_kernel_name(*shape).decode())
 
 
 def widened(att, pages):

@@ -1,5 +1,6 @@
 """GPU parity of the MFMA attention kernel with 32-row blocks (tiles of 192, 256 and 384 rows, reported as 3, 4 and 6 times 64)
-against the CPU oracle, at the edges of its tiles, of its score range and of its page table (MI355X only).
+against the CPU oracle, at the edges of its tiles, of its score range and of its page table (MI355X only).  Every test asserts
+that the shape takes this kernel.
 
 Tolerance as for every bf16 test with D = 128: 2e-2 (test_gpu_attn.py says where it comes from)."""
 import numpy as np
@@ -12,21 +13,17 @@ from test_gpu_attn_mfma import compare, reference, run, sample
 
 pytestmark = pytest.mark.gpu
 
-WIDE_MIN_STAGES = 11                # tiles of 192 rows: fewer stages of a split take the 16-row kernel
-
 
 def trees(rng, B, K):
     return np.stack([inputs.random_recursive_tree(rng, K, 8 if b % 2 else K - 1) for b in range(B)])
 
 
-def assert_wide(plan, tile, split, tokens):
-    assert (plan.row_blocks, plan.splits > 1) == (tile, split), plan
-    if tile == 3:
-        assert -(-(-(-tokens // 64)) // plan.splits) >= WIDE_MIN_STAGES, plan
+def assert_wide(plan, tile, split):
+    assert (plan.kernel, plan.row_blocks, plan.splits > 1) == ("tree_attn_wide_kernel", tile, split), plan
 
 
 # (B, K, Hq, Hkv, P, tile rows / 64, keys split over workgroups): with and without a last tile that is full
-SHAPES = [(8, 60, 64, 4, 650, 3, False), (8, 80, 64, 4, 653, 3, False), (2, 128, 24, 2, 5000, 3, True), (2, 96, 64, 4, 3000, 3, True),
+SHAPES = [(8, 60, 64, 4, 650, 3, False), (8, 80, 64, 4, 653, 3, False), (2, 72, 24, 2, 8000, 3, True), (2, 96, 64, 8, 3000, 3, True),
           (16, 100, 32, 2, 650, 4, False), (1, 100, 16, 1, 5000, 4, True), (8, 65, 32, 2, 503, 4, True), (1, 127, 16, 1, 5003, 4, True),
           (16, 96, 64, 4, 650, 6, False), (4, 96, 48, 4, 1500, 6, True), (16, 95, 12, 1, 1489, 6, True)]
 
@@ -46,7 +43,7 @@ def test_tiles(case, layout):
     if B > 4:
         n_nodes[2], prefix[3] = 0, 0
     got, plan = run(w, att, parent, n_nodes, prefix)
-    assert_wide(plan, tile, split, P + K)
+    assert_wide(plan, tile, split)
     compare(w, att, parent, n_nodes, prefix, got, sample(rng, w, n_nodes, 60 // B + 1))
 
 
@@ -82,7 +79,7 @@ def test_score_ranges(case, level):
     n_nodes = np.full(B, K, np.int32)
     prefix = (P - rng.integers(0, P // 4, B)).astype(np.int32)
     got, plan = run(w, att, parent, n_nodes, prefix)
-    assert_wide(plan, tile, split, P + K)
+    assert_wide(plan, tile, split)
     compare(w, att, parent, n_nodes, prefix, got, sample(rng, w, n_nodes, 60 // B + 1))
 
 
@@ -98,26 +95,26 @@ def test_tree_slots_far_below_zero(case):
     n_nodes = rng.integers(K // 2, K + 1, B).astype(np.int32)
     prefix = (np.arange(B) % 3).astype(np.int32)
     got, plan = run(w, att, parent, n_nodes, prefix)
-    assert plan.row_blocks == tile, plan
+    assert_wide(plan, tile, split)
     compare(w, att, parent, n_nodes, prefix, got, sample(rng, w, n_nodes, 60 // B + 1))
 
 
 def test_peaked_softmax():
-    w = shape_workload(2, 96, 64, 4, 128, 3000)
+    w = shape_workload(2, 96, 64, 8, 128, 3000)
     att = inputs.make_attention_inputs(w, seed=12)
     att["q"] = [inputs.f32_to_bf16_bits(inputs.bf16_bits_to_f32(att["q"][0]) * 6.0)]
     rng = np.random.default_rng(12)
     parent = trees(rng, w.B, w.K)
     n_nodes, prefix = np.full(w.B, w.K, np.int32), np.full(w.B, w.P, np.int32)
     got, plan = run(w, att, parent, n_nodes, prefix)
-    assert plan.row_blocks == 3, plan
+    assert_wide(plan, 3, True)
     rows = sample(rng, w, n_nodes, 60)
     ref = reference(w, att, parent, n_nodes, prefix, rows)
     score_scale_tolerance(np.stack([got[r] for r in rows]), ref, float(np.sqrt(w.D) * att["scale"] * 6.0), "peaked softmax")
 
 
 @pytest.mark.parametrize("bits", [0x7fc0, 0x7f80, 0xff7f], ids=["nan", "inf", "lowest"])
-@pytest.mark.parametrize("case", [SHAPES[0], SHAPES[5], SHAPES[9]], ids=lambda c: "tile%d_split%d" % c[5:])
+@pytest.mark.parametrize("case", [SHAPES[0], SHAPES[3], SHAPES[5], SHAPES[9]], ids=lambda c: "tile%d_split%d" % c[5:])
 def test_queries_of_absent_nodes_may_hold_anything(case, bits):
     B, K, Hq, Hkv, P, tile, split = case
     w = shape_workload(B, K, Hq, Hkv, 128, P)
@@ -130,7 +127,7 @@ def test_queries_of_absent_nodes_may_hold_anything(case, bits):
     att["q"] = [q]
     parent, prefix = trees(rng, B, K), np.full(B, P, np.int32)
     got, plan = run(w, att, parent, n_nodes, prefix)
-    assert plan.row_blocks == tile, plan
+    assert_wide(plan, tile, split)
     compare(w, att, parent, n_nodes, prefix, got, sample(rng, w, n_nodes, 60 // B + 1))
 
 
@@ -145,5 +142,5 @@ def test_more_stages_than_a_register_of_pages(B, tile):
     n_nodes, prefix = np.full(B, 24, np.int32), np.full(B, 300000, np.int32)
     prefix[B - 1] -= 4567
     got, plan = run(w, att, parent, n_nodes, prefix)
-    assert plan.row_blocks == tile, plan
+    assert_wide(plan, tile, True)
     compare(w, att, parent, n_nodes, prefix, got, sample(rng, w, n_nodes, 4))
