@@ -44,9 +44,6 @@ def _asm_of(src: str, directory: str = OBJ_DIR) -> str:
     return os.path.join(directory, os.path.splitext(src)[0] + "-hip-amdgcn-amd-amdhsa-gfx950.s")
 
 
-ATTN_ASM = _asm_of("tree_attn.hip")
-
-
 def _compile(src: str, extra):
     obj = os.path.join(OBJ_DIR, os.path.splitext(src)[0] + ".o")
     return _compile_to(src, extra, obj)
@@ -108,9 +105,10 @@ def check_attention_asm(asm_text: str):
         MFMA_RESULT_WAIT preceding wait states, in program order across labels (the result of a
         MFMA is written at the end of its passes, and nothing interlocks a vector ALU,
         LDS or memory instruction, or a v_accvgpr_read, that comes earlier).  An MFMA issues no sooner
-        than the one in front of it has gone through its passes: those count as wait states too.
+        than the one in front of it has gone through its passes: those count as wait states too;
+      * the transfers from memory to LDS have landed where LDS gets another use (_check_transfers).
     """
-    problems = []
+    problems = _check_transfers(asm_text)
     lines = asm_text.split("\n")
     kernel, managed, in_asm, desc = None, 0, False, ""
     history = []          # (wait states, destination span or None) of the preceding instructions
@@ -208,6 +206,60 @@ def check_attention_asm(asm_text: str):
         age(1)
         if len(history) > 8:
             del history[0]
+    return problems
+
+
+def _check_transfers(asm_text: str):
+    """Transfers from memory straight to LDS are inline assembly, and nothing but the kernels' own s_waitcnt waits for them.
+    Behind the last MFMA wavefronts exchange results in the LDS that keys and queries came to.  On every path of the
+    control-flow graph, whatever the lengths, the transfers of all wavefronts must have landed there before LDS is
+    written, which takes a vmcnt(0) and a barrier behind it."""
+    LANDED, MINE_LANDED, IN_FLIGHT = 0, 1, 2
+    problems = []
+    for body in re.finditer(r"^(_Z\w+):[^\n]*\n(.*?)^\.Lfunc_end", asm_text, re.M | re.S):
+        if not _managed_accvgprs(body.group(1)):
+            continue
+        first_line = asm_text.count("\n", 0, body.start(2)) + 1
+        code, label_at = [], {}                    # (line, opcode, text); label -> index of the next instruction
+        for ln, raw in enumerate(body.group(2).split("\n"), first_line):
+            text = raw.split(";")[0].strip()
+            if re.match(r"\.\w+:", text):
+                label_at[text.split(":")[0]] = len(code)
+            elif text and not text.startswith("."):
+                code.append((ln, text.split()[0], text))
+        after = []                                 # indices of the instructions that may follow
+        for i, (_, op, text) in enumerate(code):
+            jump = [label_at[text.split()[1]]] if op.startswith(("s_branch", "s_cbranch")) else []
+            after.append([] if op == "s_endpgm" else jump if op == "s_branch" else jump + [i + 1])
+        before = [[] for _ in code]
+        for i, targets in enumerate(after):
+            for t in targets:
+                before[t].append(i)
+        ahead = {i for i, c in enumerate(code) if c[1].startswith("v_mfma")}        # an MFMA may follow
+        todo = list(ahead)
+        while todo:
+            for i in before[todo.pop()]:
+                if i not in ahead:
+                    ahead.add(i)
+                    todo.append(i)
+        state = [None] * len(code)                 # of the transfers in front of an instruction, the worst of all paths
+        state[0], todo = LANDED, [0]
+        while todo:
+            i = todo.pop()
+            op, text, s = code[i][1], code[i][2], state[i]
+            if "_lds_" in op or op.startswith("buffer_load") and text.endswith(" lds"):
+                s = IN_FLIGHT
+            elif op == "s_waitcnt" and "vmcnt(0)" in text:
+                s = min(s, MINE_LANDED)
+            elif op == "s_barrier" and s == MINE_LANDED:
+                s = LANDED
+            for t in after[i]:
+                if state[t] is None or state[t] < s:
+                    state[t] = s
+                    todo.append(t)
+        for i, (ln, op, text) in enumerate(code):
+            if op.startswith("ds_write") and i not in ahead and state[i]:
+                problems.append("line %d (%s): transfers to LDS may be in flight: %s" % (ln, body.group(1), text))
     return problems
 
 

@@ -534,8 +534,9 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_wide_kernel(GRAFT_ATTN_A
         const auto nothing = [](auto) {};
         phase<S, 0, false, true, true>(w, c_log2, 0u, 0u, nothing);
         phase<S, 1, false, false, true>(w, c_log2, 0u, 0u, nothing);
-        GRAFT_WAIT_VMCNT(0);
     }
+    // Everything has landed: the last stages, or, in a split without a stage, the queries, whose place the exchange below takes.
+    GRAFT_WAIT_VMCNT(0);
     GRAFT_MFMA_SETTLE();
     GRAFT_STAMP(AT_TS_LOOP_END);
     GRAFT_STAMP_CYCLES(AT_TS_CYCLES_END);

@@ -112,12 +112,48 @@ def test_scratch_memory():
     assert len(bad) == 1 and "scratch" in bad[0]
 
 
-def test_the_built_library_passes():
-    if not os.path.exists(b.ATTN_ASM):
+# no stages: straight to the exchange; else the loop, which ends with a wait
+TRANSFERS = """\t;;#ASMSTART
+\tbuffer_load_dwordx4 v3, s[0:3], 0 offen lds
+\t;;#ASMEND
+\ts_cbranch_scc1 .LBB0_2
+%s
+.LBB0_1:
+\ts_nop 1
+""" + MFMA + """
+\ts_cbranch_scc1 .LBB0_1
+\ts_waitcnt vmcnt(0)
+.LBB0_2:
+%s
+\ts_barrier
+\tds_write_b128 v1, v[2:5]
+\ts_endpgm"""
+
+
+@pytest.mark.parametrize("transfer", ["buffer_load_dwordx4 v3, s[0:3], 0 offen lds", "global_load_lds_dword v[4:5], off"])
+def test_lds_written_while_a_transfer_may_be_in_flight(transfer):
+    def check(in_front, at_exchange):
+        return b.check_attention_asm(_asm(TRANSFERS.replace("buffer_load_dwordx4 v3, s[0:3], 0 offen lds", transfer) % (in_front, at_exchange)))
+
+    bad = check("\ts_nop 0", "\ts_nop 0")                        # nothing waits on the path around the loop
+    assert len(bad) == 1 and "in flight" in bad[0] and "ds_write_b128" in bad[0]
+    assert len(check("\ts_waitcnt vmcnt(8)", "\ts_nop 0")) == 1
+    assert len(check("\ts_nop 0", "\ts_waitcnt vmcnt(1) lgkmcnt(0)")) == 1
+    assert check("\ts_nop 0", "\ts_waitcnt vmcnt(0) lgkmcnt(0)") == []
+    # the wavefront's own wait says nothing about the others' without a barrier behind it
+    assert len(check("\ts_nop 0", "\ts_barrier\n\ts_waitcnt vmcnt(0)\n\tds_write_b32 v1, v2")) == 1
+    # LDS writes from which the loop is still to come are its own affair
+    assert check("\tds_write_b128 v1, v[2:5]", "\ts_waitcnt vmcnt(0)") == []
+
+
+@pytest.mark.parametrize("source,mfma", [("tree_attn.hip", "v_mfma_f32_16x16x32_bf16"), ("tree_attn_wide.hip", "v_mfma_f32_32x32x16_bf16")])
+def test_the_built_library_passes(source, mfma):
+    path = b._asm_of(source)
+    if not os.path.exists(path):
         pytest.skip("no assembly kept from a build in this tree")
-    with open(b.ATTN_ASM) as f:
+    with open(path) as f:
         text = f.read()
-    assert text.count("v_mfma_f32_16x16x32_bf16") > 500          # the check sees the real kernels
+    assert text.count(mfma) > 500                                # the check sees the real kernels
     assert b.check_attention_asm(text) == []
 
 

@@ -47,6 +47,30 @@ def test_tiles(case, layout):
     compare(w, att, parent, n_nodes, prefix, got, sample(rng, w, n_nodes, 60 // B + 1))
 
 
+@pytest.mark.parametrize("case", [SHAPES[2], SHAPES[3], SHAPES[6], SHAPES[9], (8, 48, 64, 4, 4096, 3, True)],
+                         ids=lambda c: "B%d_K%d_Hq%d_Hkv%d_P%d_tile%d_split%d" % c)
+@pytest.mark.parametrize("long_one", [False, True], ids=["all_short", "one_long"])
+def test_splits_without_a_stage(case, long_one):
+    """Sequences far shorter than their block table: workgroups whose split has no keys hand on empty rows, whatever the
+    queries that they have requested hold."""
+    B, K, Hq, Hkv, P, tile, split = case
+    w = shape_workload(B, K, Hq, Hkv, 128, P)
+    rng = np.random.default_rng(P + K + 1)
+    att = inputs.make_attention_inputs(w, seed=P + K + 1)
+    parent = trees(rng, B, K)
+    n_nodes, prefix = rng.integers(1, K + 1, B).astype(np.int32), rng.integers(0, 64, B).astype(np.int32)
+    if long_one:
+        n_nodes[0], prefix[0] = K, P
+    q = att["q"][0].copy()
+    for b in range(B):
+        q[b, n_nodes[b]:] = 0x7f80
+    att["q"] = [q]
+    got, plan = run(w, att, parent, n_nodes, prefix)
+    assert_wide(plan, tile, split)
+    assert min(-(-(prefix + n_nodes) // 64)) < plan.splits
+    compare(w, att, parent, n_nodes, prefix, got, sample(rng, w, n_nodes, 120 // B + 1))
+
+
 def scored(w, att, level):
     """Queries of ones and keys that give every row the score level(sequence, token), in natural units; odd heads get it negated."""
     k = inputs.bf16_bits_to_f32(att["k_cache"][0]).copy()
