@@ -22,10 +22,12 @@
 //   sums  : of the probabilities as they leave exp2, in fp32: rounded ones would need an unpacking each or the matrix
 //           cores (v_dot2 holds those too, 18 cycles an instruction).  Queries are not scaled and rounded again: the softmax
 //           scale is applied to the scores in fp32.  Together that is closer to a 64-bit reference than the 16-row kernel.
-//   range : a row's reference is zero while its scores are small, else the maximum of its first sub-tile; behind every stage rows
-//           whose sum has passed 2^24 move theirs up by a power of two (exact).  A wavefront whose sums or products left the
-//           range of fp32 all the same, or whose rows see tokens and have no sum, makes the workgroup go over its
-//           keys once more, that wavefront with the exact running maximum.
+//   range : a row's reference is fixed by the first sub-tile of which it sees anything: zero where the maximum lies in 0 .. 16 (log2
+//           units), else that maximum, so that its sum is never below about one.  Behind every stage rows whose sum has passed
+//           2^24 move theirs up by a power of two (exact).  Sums and products that left the range of fp32 in between are seen
+//           there; what the last two units of a split add is seen behind the loop, where sums from 2^26 on do not pass: below, products
+//           with values of up to 2^100 are finite.  A wavefront with such a row, or with one that sees tokens and has no
+//           sum, makes the workgroup go over its keys once more, that wavefront with the exact running maximum.
 //
 // Measured (MI355X, N(0,1) operands, all compute units busy).  Cycles of a stage of 192 rows 3160 -> 2220, of which 1540 are
 // MFMAs.  The chip lowers its clock with the load (2.38 -> 1.9 GHz on 33 stages, 1.85 -> 1.55 on 257), so the time follows the
@@ -41,7 +43,8 @@ namespace graft {
 enum WideMode { WIDE_ROWS = 1, WIDE_KEYS = 2 };
 constexpr int WD_BLOCK = 32;                    // query rows of a row block
 constexpr float WD_LAZY_SUM = 16777216.0f;      // a row keeps its reference while its sum stays below 2^24
-constexpr float WD_SMALL_SCORE = 16.0f;         // rows whose first scores stay below this (log2 units) need no reference
+constexpr float WD_SMALL_SCORE = 16.0f;         // rows whose first scores stay below this (log2 units), and reach zero, need no reference
+constexpr float WD_MIN_SUM = 0.5f, WD_MAX_SUM = 67108864.0f;    // sums that need no second pass (2^26; regular ones end below 2 x 2^24)
 
 template <int NB_, int MODE_> struct WideShape {
     static constexpr int NB = NB_, MODE = MODE_;
@@ -500,11 +503,13 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_wide_kernel(GRAFT_ATTN_A
                         const int lz = opaque_lane();
                         mask_scores(w.s[QB], row_window(r_tile + S::row0(QB, wave_u) + (lz & 31), t_sub, sr.P, sr.n, slots, p.R, p.g_magic, Ms), lz >> 5);
                     }
-                    if constexpr (FIRST && S::visit(J) == 0) {
+                    // (the sum holds all of the block's earlier units: other blocks' units lie between)
+                    const bool unseen = FIRST && S::visit(J) == 0 ? true : pair_sum(w.l[QB]) == 0.f;
+                    if (__builtin_amdgcn_ballot_w64(unseen) != 0) {
                         settle(w.s[QB]);
                         const float mx = score_max(w.s[QB]) * c_log2;
-                        const bool large = mx > WD_SMALL_SCORE || (mx < -WD_SMALL_SCORE && mx > -INFINITY);
-                        w.negm[QB] = large ? -mx : 0.f;
+                        const bool large = mx > WD_SMALL_SCORE || (mx < 0.f && mx > -INFINITY);
+                        w.negm[QB] = unseen ? (large ? -mx : 0.f) : w.negm[QB];
                     }
                 }
             });
@@ -541,7 +546,7 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_wide_kernel(GRAFT_ATTN_A
     GRAFT_STAMP(AT_TS_LOOP_END);
     GRAFT_STAMP_CYCLES(AT_TS_CYCLES_END);
 
-    // ---- rows whose sum is no ordinary number although they see something: once more, with the exact running maximum
+    // ---- rows whose sum is out of bounds although they see something: once more, with the exact running maximum
     const int lane_end = opaque_lane();
     {
         const int l32 = lane_end & 31, half = lane_end >> 5;
@@ -550,7 +555,7 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_wide_kernel(GRAFT_ATTN_A
             GRAFT_CONST(rb, rb_);
             const float lt = pair_sum(w.l[rb]);
             const int r = r_tile + S::row0(rb, wave_u) + l32;
-            bool odd = !(lt > 0x1p-100f && lt < 0x1p100f) && r < p.R && ((r * p.g_magic) >> 16) < sr.n && n_st > 0;
+            bool odd = !(lt >= WD_MIN_SUM && lt < WD_MAX_SUM) && r < p.R && ((r * p.g_magic) >> 16) < sr.n && n_st > 0;
             if (__builtin_amdgcn_ballot_w64(odd) != 0) {          // does it see anything?
                 unsigned seen = 0;
                 for (int k = 0; k < n_st; ++k)
@@ -652,8 +657,12 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_wide_kernel(GRAFT_ATTN_A
                 *reinterpret_cast<uintx4*>(op + 1024 * e + 512 * j) = t;
             }
         if (ohalf == 0) {
+            // (sums between one and two, their power of two with the reference: 64 splits' sums of up to 2^26 times values of up to
+            //  2^100 would overflow in the merge)
+            const int le = static_cast<int>((__float_as_uint(l) >> 23) & 0xffu) - 127, shift = le > -126 && le < 127 ? le : 0;
             float* ml = p.ws_ml + (part + r0 + o32) * 4;
-            if (with_ml) *reinterpret_cast<float2*>(ml) = float2{l > 0.f ? m : -INFINITY, l};
+            if (with_ml) *reinterpret_cast<float2*>(ml) =
+                float2{l > 0.f ? m + static_cast<float>(shift) : -INFINITY, l * __uint_as_float(static_cast<unsigned>(127 - shift) << 23)};
             ml[2 + h] = pow2e;
         }
     };

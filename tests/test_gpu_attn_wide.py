@@ -8,7 +8,7 @@ import pytest
 
 import inputs
 from gpu_util import attn_plan
-from test_gpu_attn import score_scale_tolerance, shape_workload
+from test_gpu_attn import TOL_BF16, score_scale_tolerance, shape_workload
 from test_gpu_attn_mfma import compare, reference, run, sample
 
 pytestmark = pytest.mark.gpu
@@ -121,6 +121,82 @@ def test_tree_slots_far_below_zero(case):
     got, plan = run(w, att, parent, n_nodes, prefix)
     assert_wide(plan, tile, split)
     compare(w, att, parent, n_nodes, prefix, got, sample(rng, w, n_nodes, 60 // B + 1))
+
+
+# every tile, with one split and with several
+RANGES = [SHAPES[0], SHAPES[3], SHAPES[4], SHAPES[6], SHAPES[8], SHAPES[9]]
+
+
+def with_values(att, log2_scale):
+    v = inputs.bf16_bits_to_f32(att["v_cache"][0]) * np.float32(2.0 ** log2_scale)        # (exact)
+    assert np.abs(v).max() < 2.0 ** 100
+    return dict(att, v_cache=[inputs.f32_to_bf16_bits(v)])
+
+
+def compare_scaled(w, att, parent, n_nodes, prefix, got, rows, log2_scale):
+    ref = reference(w, att, parent, n_nodes, prefix, rows)
+    assert np.isfinite(got).all()
+    err = np.abs(np.stack([got[r] for r in rows]) - ref).max() * 2.0 ** -log2_scale
+    print("%d rows, max abs err %.3e of 2^%d" % (len(rows), err, log2_scale))
+    assert err <= TOL_BF16
+
+
+@pytest.mark.parametrize("case", RANGES, ids=lambda c: "tile%d_split%d" % c[5:])
+@pytest.mark.parametrize("log2_scale", [-100, 97])
+@pytest.mark.parametrize("scores", ["random", "all at -15", "all at 10.9"])
+def test_value_magnitudes(case, log2_scale, scores):
+    """Values up to the 2^100 that the interface allows and down to the other end, with scores around zero, and, in log2 units, just
+    above the bound up to which a reference is zero and as far below."""
+    B, K, Hq, Hkv, P, tile, split = case
+    w = shape_workload(B, K, Hq, Hkv, 128, P)
+    rng = np.random.default_rng(22)
+    att = with_values(inputs.make_attention_inputs(w, seed=22), log2_scale)
+    if scores != "random":
+        att = scored(w, att, lambda b, t: float(scores.split()[-1]) + 0.0 * t)
+    parent = trees(rng, B, K)
+    n_nodes = rng.integers(K // 2, K + 1, B).astype(np.int32)
+    prefix = (P - rng.integers(0, P // 4, B)).astype(np.int32)
+    got, plan = run(w, att, parent, n_nodes, prefix)
+    assert_wide(plan, tile, split)
+    compare_scaled(w, att, parent, n_nodes, prefix, got, sample(rng, w, n_nodes, 60 // B + 1), log2_scale)
+
+
+@pytest.mark.parametrize("case", RANGES, ids=lambda c: "tile%d_split%d" % c[5:])
+@pytest.mark.parametrize("jump,log2_scale", [(21, 97), (42, 70), (65, 97)])
+@pytest.mark.parametrize("last", [32, 64, 0], ids=["last_32", "last_64", "tree"])
+def test_last_tokens_far_above_all_others(case, jump, log2_scale, last):
+    """Scores that jump in a sequence's last sub-tiles, behind the last look at the sums, under values whose products with them leave
+    the range of fp32."""
+    B, K, Hq, Hkv, P, tile, split = case
+    w = shape_workload(B, K, Hq, Hkv, 128, P)
+    rng = np.random.default_rng(23)
+    n_nodes = rng.integers(K // 2, K + 1, B).astype(np.int32)
+    prefix = (P - rng.integers(0, P // 4, B)).astype(np.int32)
+    first = prefix + n_nodes - last if last else prefix - 2
+    att = scored(w, with_values(inputs.make_attention_inputs(w, seed=23), log2_scale), lambda b, t: np.where(t >= first[b], float(jump), 0.0))
+    parent = trees(rng, B, K)
+    got, plan = run(w, att, parent, n_nodes, prefix)
+    assert_wide(plan, tile, split)
+    rows = sample(rng, w, n_nodes, 30 // B + 1) + [(b, int(n_nodes[b]) - 1 - i, 2 * i) for b in range(B) for i in range(3)]
+    compare_scaled(w, att, parent, n_nodes, prefix, got, rows, log2_scale)
+
+
+@pytest.mark.parametrize("case", RANGES, ids=lambda c: "tile%d_split%d" % c[5:])
+@pytest.mark.parametrize("level", [-8, -30, -62])
+@pytest.mark.parametrize("log2_scale", [-100, 97])
+def test_rows_that_see_late_tokens_with_low_scores_only(case, level, log2_scale):
+    """No prefix: nodes see a few slots behind a wavefront's first sub-tile, whose scores would be nothing against a
+    reference of zero times small values."""
+    B, K, Hq, Hkv, P, tile, split = case
+    w = shape_workload(B, K, Hq, Hkv, 128, P)
+    rng = np.random.default_rng(24)
+    att = scored(w, with_values(inputs.make_attention_inputs(w, seed=24), log2_scale), lambda b, t: level - 0.03125 * t)
+    parent = trees(rng, B, K)
+    n_nodes, prefix = np.full(B, K, np.int32), (np.arange(B) % 3).astype(np.int32)
+    got, plan = run(w, att, parent, n_nodes, prefix)
+    assert_wide(plan, tile, split)
+    rows = sample(rng, w, n_nodes, 30 // B + 1) + [(b, K - 1 - i, 2 * i) for b in range(B) for i in range(4)]
+    compare_scaled(w, att, parent, n_nodes, prefix, got, rows, log2_scale)
 
 
 def test_peaked_softmax():
