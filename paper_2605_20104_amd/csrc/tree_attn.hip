@@ -1010,6 +1010,15 @@ __global__ __launch_bounds__(64 * CB_MAX_WAVES) void tree_attn_combine_kernel(
                 ml[u] = *reinterpret_cast<const floatx4*>(mlrow + (s0 + u) * ml_stride);
             }
         }
+        // (picked by value: of two elements of the array the compiler selects the index, and goes through all of it for every split)
+        float scale[CB_SPLITS];
+        if constexpr (WIDE) {
+#pragma unroll
+            for (int u = 0; u < CB_SPLITS; ++u) {
+                const float low = ml[u][2], high = ml[u][3];
+                scale[u] = dp < PIECES / 2 ? low : high;
+            }
+        }
 #pragma unroll
         for (int u = 0; u < CB_SPLITS; ++u)
             if ((s0 + u) < ns) m_run = fmaxf(m_run, ml[u][0]);
@@ -1018,7 +1027,7 @@ __global__ __launch_bounds__(64 * CB_MAX_WAVES) void tree_attn_combine_kernel(
             const bool on = (s0 + u) < ns && ml[u][0] > -INFINITY;
             const float wl = on ? __builtin_amdgcn_exp2f(ml[u][0] - m_run) * ml[u][1] : 0.f;
             den += wl;
-            const float wu = wl * (WIDE && dp >= PIECES / 2 ? ml[u][3] : ml[u][2]);
+            const float wu = wl * (WIDE ? scale[u] : ml[u][2]);
             const halfx8 h = __builtin_bit_cast(halfx8, ov[u]);
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc[e] += wu * static_cast<float>(h[e]);

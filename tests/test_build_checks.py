@@ -157,6 +157,20 @@ def test_the_built_library_passes(source, mfma):
     assert b.check_attention_asm(text) == []
 
 
+@pytest.mark.parametrize("splits", [2, 4, 8, 16])
+def test_the_merge_picks_its_scales_by_value(splits):
+    """Partial rows in 32-row blocks have two scales, one for either half of the dims.  Picked as one of two elements of the
+    splits' array they became a chain of selects over all of it, for every split: 275 instructions for 23, 2.4 us of 7.6."""
+    path = b._asm_of("tree_attn.hip")
+    if not os.path.exists(path):
+        pytest.skip("no assembly kept from a build in this tree")
+    with open(path) as f:
+        text = f.read()
+    selects = [len(re.findall(r"v_cndmask", re.search(r"^_ZN5graft24tree_attn_combine_kernelILi%dELb%dE\w*:(.*?)^\.Lfunc_end" % (splits, wide), text, re.M | re.S).group(1)))
+               for wide in (0, 1)]
+    assert selects[1] <= selects[0] + 2 * splits, selects
+
+
 def test_no_kernel_of_the_library_uses_scratch_memory():
     """The kernels' metadata in the built library: an array or a register that went to scratch memory is a trip to memory
     for every access.  (The value behind the key is a small number, one byte, or marked as a larger one.)"""
