@@ -1131,58 +1131,61 @@ static TileCost tile_cost(int mb, bool wide) {
 static bool has_kernel(int mb, bool wide, int64_t stages_per_split) {
     return wide ? mb == 4 || mb == 6 || (mb == 3 && stages_per_split >= WIDE_MIN_STAGES) : mb <= 3 || mb == 5;
 }
-// (for the line between this path and the direct one, which was measured with 16-row blocks in tiles of 256 rows too: a shape
-// that moved across it for a few per cent would be further from a 64-bit reference, 2.33e-3 -> 2.37e-3)
-static bool had_kernel(int mb, bool, int64_t) { return mb <= 5; }
 static AttnPlan make_plan(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t max_pages) {
     const int R = K_max * (Hq / Hkv);
     const int rows_per_mb = AT_WAVES * 16;                       // rows a workgroup covers per MB
     const int64_t stages = (static_cast<int64_t>(max_pages) * GRAFT_PAGE_SIZE + AT_STAGE - 1) / AT_STAGE;
     const int64_t min_splits = (stages * (AT_STAGE / GRAFT_PAGE_SIZE) + AT_MAX_SPLIT_PAGES - 1) / AT_MAX_SPLIT_PAGES;
     const int64_t cus = device_compute_units();
-    const auto best_of = [&](bool wide, bool (*offered)(int, bool, int64_t)) {
-        AttnPlan pl{};
-        const int mb_max = wide ? 6 : 5;
+    const int s_lo = static_cast<int>(min_splits < 1 ? 1 : min_splits), s_hi = static_cast<int>(stages < 1 ? 1 : (stages < AT_MAX_SPLITS ? stages : AT_MAX_SPLITS));
+    int64_t per[AT_MAX_SPLITS + 1];                              // stages of a split
+    for (int sp = s_lo; sp <= s_hi; ++sp) per[sp] = (stages + sp - 1) / sp;
+    // line: what the direct path is compared with, 16-row blocks only, in tiles of 256 rows too, as when it was measured.  With the costs of
+    // what runs now 7 of 4000 shapes (drawn from 1 to 16 sequences of 32 to 64K keys) would change to 32-row blocks without a
+    // split: 17.6 .. 24.2 -> 16.1 .. 20.4 us, and an error against 64 bits of 2.35e-3 instead of 2.33e-3.
+    struct Best {
+        double key = -1.0, cost = 0.0;
+        int mb = 0, row_tiles = 0, splits = 0;
+    };
+    Best narrow, wide, line;
+    const auto search = [&](bool w) {
+        const int mb_max = w ? 6 : 5;
         const int rt_min = (R + rows_per_mb * mb_max - 1) / (rows_per_mb * mb_max);
         const int rt_max = (R + rows_per_mb - 1) / rows_per_mb;
-        double best = -1.0;
         for (int rt = rt_min; rt <= rt_max && rt <= rt_min + 3; ++rt) {
             const int mb = (R + rt * rows_per_mb - 1) / (rt * rows_per_mb);
-            const TileCost c = tile_cost(mb, wide);
+            const TileCost c = tile_cost(mb, w);
             const int64_t units = static_cast<int64_t>(B) * Hkv * rt;
-            int64_t s_hi = stages < AT_MAX_SPLITS ? stages : AT_MAX_SPLITS;
-            if (s_hi < 1) s_hi = 1;
-            for (int64_t sp = min_splits < 1 ? 1 : min_splits; sp <= s_hi; ++sp) {
+            const double least = c.fixed + c.stage * static_cast<double>(units * stages) / static_cast<double>(cus);    // (all units busy all the time)
+            if (narrow.mb > 0 && (w ? least >= 0.97 * narrow.cost : least >= narrow.key && least >= line.key)) continue;
+            for (int sp = s_lo; sp <= s_hi; ++sp) {
                 const int64_t rounds = (units * sp + cus - 1) / cus;
-                const int64_t per = (stages + sp - 1) / sp;
-                if (!offered(mb, wide, per)) continue;
-                const double cost = rounds * (c.fixed + per * c.stage) + 300.0 * sp;
+                const double cost = rounds * (c.fixed + per[sp] * c.stage) + 300.0 * sp;
                 const double total = cost + (sp > 1 ? 11500.0 - 200.0 * sp : 0.0);    // with the merge launch, as measured
-                if (best < 0.0 || (wide ? total : cost) < best) {
-                    best = wide ? total : cost;
-                    pl.n_row_tiles = rt;
-                    pl.mb = mb;
-                    pl.wide = wide;
-                    pl.n_splits = static_cast<int>(sp);
-                    pl.cost = total;
-                }
+                const double key = w ? total : cost;
+                const auto take = [&](Best& best) {
+                    if (best.key < 0.0 || key < best.key) best = {key, total, mb, rt, sp};
+                };
+                if (has_kernel(mb, w, per[sp])) take(w ? wide : narrow);
+                if (!w) take(line);
             }
         }
-        return pl;
     };
-    const AttnPlan narrow = best_of(false, has_kernel), wide = best_of(true, has_kernel);
-    AttnPlan pl = wide.mb > 0 && (narrow.mb == 0 || wide.cost < 0.97 * narrow.cost) ? wide : narrow;
-    pl.line = best_of(false, had_kernel).cost;
+    search(false);
+    search(true);
+    const bool use_wide = wide.mb > 0 && (narrow.mb == 0 || wide.cost < 0.97 * narrow.cost);
+    const Best& best = use_wide ? wide : narrow;
+    AttnPlan pl{best.mb, best.row_tiles, best.splits, 0, use_wide, 0, 0, best.cost, line.cost};
 #ifdef GRAFT_ATTN_STAMPS
     // timing build: a plan held fixed by the caller (to compare runs that differ in nothing else)
     if (g_force_splits >= (min_splits < 1 ? 1 : min_splits) && g_force_splits <= (stages < AT_MAX_SPLITS ? stages : AT_MAX_SPLITS) && g_force_row_tiles >= 1) {
         const int mb = (R + g_force_row_tiles * rows_per_mb - 1) / (g_force_row_tiles * rows_per_mb);
-        const int64_t per = (stages + g_force_splits - 1) / g_force_splits;
-        if (has_kernel(mb, true, per) || has_kernel(mb, false, per)) {
+        const int64_t stages_of_split = (stages + g_force_splits - 1) / g_force_splits;
+        if (has_kernel(mb, true, stages_of_split) || has_kernel(mb, false, stages_of_split)) {
             pl.n_splits = g_force_splits;
             pl.n_row_tiles = g_force_row_tiles;
             pl.mb = mb;
-            pl.wide = has_kernel(mb, true, per);
+            pl.wide = has_kernel(mb, true, stages_of_split);
         }
     }
 #endif
@@ -1222,9 +1225,9 @@ static PathChoice make_choice(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv,
 }
 
 // The choices of the last eight shapes are kept per host thread: all layers of a model ask for the same one, a
-// draft and a target model or two batch sizes take turns, and working the cost models out takes about a
-// microsecond, a sixth of a small launch (two shapes in turn, workspace query through ctypes: 1.2 to 1.4 us with one
-// kept choice, 0.33 with eight).  The reference returned is good until the thread's next call.
+// draft and a target model or two batch sizes take turns, and working the cost models out takes one to two
+// microseconds, a sixth of a small launch (workspace query through ctypes, three shapes with a new table size each time: 2.0
+// to 2.5 us; of a kept choice 0.9).  The reference returned is good until the thread's next call.
 static const PathChoice& choose_path(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages, int32_t dtype) {
     struct Kept {
         int32_t key[8];
