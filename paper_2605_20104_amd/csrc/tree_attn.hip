@@ -1114,11 +1114,14 @@ static thread_local int g_force_splits = 0, g_force_row_tiles = 0;
 //
 // Which kernel: tiles of 64, 128 and 320 rows have the one with 16-row blocks (per stage about 680 mb + 1100, fixed about 3300 mb + 8000), of
 // 256 and 384 the one with 32-row blocks, of 192 either: its loop is faster, its fixed part (twice the rows a wavefront, a merge
-// through LDS) longer.  us a call, 16-row / 32-row blocks, tiles of 192 rows by stages of a split: 8 stages 25.6 / 26.1 and
-// 24.7 / 25.2, 9 25.2 / 24.0, 17 35.7 / 33.4, 30 60.8 / 60.5 (one tile, memory-bound), 32 57.9 / 54.6, 33 56.6 / 53.3, 257 408 / 367;
-// up to ten stages, where either is ahead by a few per cent, the 16-row kernel keeps them.
+// through LDS) longer.  Tiles of 192 rows, time with 32-row blocks over time with 16-row blocks at the same plan, by stages of a split
+// (of the geometric mean, over 540 plans of 230 drawn shapes): several splits, under 8 stages 1.03, 8 to 10 1.01, 11 to 13 0.98, 14 to 18
+// 0.96, 26 to 40 0.94, above 0.93; one split 1.01, 0.94, 0.95, 0.90, 0.89, 0.86.  Hence the 11 stages.  A sequence with an eighth of the keys its
+// table has room for takes 1.0 to 1.1 times as long with 32-row blocks there.
 // 256 rows: 5 stages 22.8 / 21.7, 17 43.8 / 43.7, 24 60.6 / 60.5, 63 137.1 / 133.2.  384 rows against two tiles of 192, 16-row
-// blocks not offered: 16 for 32 stages 58.8 / 54.6, 128 for 257 365 / 367 (a round 380 / 399 us).
+// blocks not offered: 16 for 32 stages 58.8 / 54.6, 128 for 257 365 / 367 (a round 380 / 399 us).  In splits of few stages their partial rows,
+// up to two and a half times as many, cost more than the model has: 14 drawn shapes with splits of 5 to 8 stages took 0.97 to 1.18 times
+// (geometric mean 1.07) what they took with the 16-row kernel, and take 0.85 to 0.98 times as long in what they get with the 11 stages asked here too.
 // The best shape of either kernel is found first; between them the launch that merges splits counts, and the 32-row kernel has to
 // be ahead by the 3 per cent to which the costs are calibrated.  Tiles of 192 rows that need no split against 320 rows in two:
 // 12 stages 24.5 / 31.9 us, 16 29.2 / 35.5 (8 sequences, 80 x 64 heads on 8).
@@ -1128,8 +1131,10 @@ static TileCost tile_cost(int mb, bool wide) {
     if (!wide) return {680.0 * mb + 1100.0, 3300.0 * mb + 8000.0};
     return mb == 3 ? TileCost{2750.0, 19500.0} : (mb == 4 ? TileCost{3650.0, 21000.0} : TileCost{5300.0, 27000.0});
 }
-static bool has_kernel(int mb, bool wide, int64_t stages_per_split) {
-    return wide ? mb == 4 || mb == 6 || (mb == 3 && stages_per_split >= WIDE_MIN_STAGES) : mb <= 3 || mb == 5;
+static bool has_kernel(int mb, bool wide, int splits, int64_t stages_per_split) {
+    if (!wide) return mb <= 3 || mb == 5;
+    const bool enough = stages_per_split >= WIDE_MIN_STAGES;
+    return mb == 4 || (mb == 3 && enough) || (mb == 6 && (splits == 1 || enough));
 }
 static AttnPlan make_plan(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t max_pages) {
     const int R = K_max * (Hq / Hkv);
@@ -1166,7 +1171,7 @@ static AttnPlan make_plan(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int
                 const auto take = [&](Best& best) {
                     if (best.key < 0.0 || key < best.key) best = {key, total, mb, rt, sp};
                 };
-                if (has_kernel(mb, w, per[sp])) take(w ? wide : narrow);
+                if (has_kernel(mb, w, sp, per[sp])) take(w ? wide : narrow);
                 if (!w) take(line);
             }
         }
@@ -1181,11 +1186,11 @@ static AttnPlan make_plan(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int
     if (g_force_splits >= (min_splits < 1 ? 1 : min_splits) && g_force_splits <= (stages < AT_MAX_SPLITS ? stages : AT_MAX_SPLITS) && g_force_row_tiles >= 1) {
         const int mb = (R + g_force_row_tiles * rows_per_mb - 1) / (g_force_row_tiles * rows_per_mb);
         const int64_t stages_of_split = (stages + g_force_splits - 1) / g_force_splits;
-        if (has_kernel(mb, true, stages_of_split) || has_kernel(mb, false, stages_of_split)) {
+        if (has_kernel(mb, true, g_force_splits, stages_of_split) || has_kernel(mb, false, g_force_splits, stages_of_split)) {
             pl.n_splits = g_force_splits;
             pl.n_row_tiles = g_force_row_tiles;
             pl.mb = mb;
-            pl.wide = has_kernel(mb, true, stages_of_split);
+            pl.wide = has_kernel(mb, true, g_force_splits, stages_of_split);
         }
     }
 #endif

@@ -25,7 +25,7 @@ def assert_wide(plan, tile, split):
 # (B, K, Hq, Hkv, P, tile rows / 64, keys split over workgroups): with and without a last tile that is full
 SHAPES = [(8, 60, 64, 4, 650, 3, False), (8, 80, 64, 4, 653, 3, False), (2, 72, 24, 2, 8000, 3, True), (2, 96, 64, 8, 3000, 3, True),
           (16, 100, 32, 2, 650, 4, False), (1, 100, 16, 1, 5000, 4, True), (8, 65, 32, 2, 503, 4, True), (1, 127, 16, 1, 5003, 4, True),
-          (16, 96, 64, 4, 650, 6, False), (4, 96, 48, 4, 1500, 6, True), (16, 95, 12, 1, 1489, 6, True)]
+          (16, 96, 64, 4, 650, 6, False), (3, 96, 48, 4, 5000, 6, True), (6, 95, 24, 2, 5003, 6, True)]
 
 
 @pytest.mark.parametrize("case", SHAPES, ids=lambda c: "B%d_K%d_Hq%d_Hkv%d_P%d_tile%d_split%d" % c)
