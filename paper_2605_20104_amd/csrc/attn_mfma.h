@@ -100,18 +100,10 @@ constexpr int AT_LOADS_PER_STAGE = 8;              // global->LDS instructions p
 // The transfer is issued through inline assembly on purpose: the kernel keeps several stages
 // in flight and waits for them with explicit s_waitcnt vmcnt(N); transfers the compiler knows
 // about make it drain the whole vector memory counter before every LDS read and barrier.
-__device__ __forceinline__ void load_global_to_lds_b128(const void* gptr, unsigned lds_addr) {
+// The global address is (wavefront-uniform 64-bit base) + (32-bit byte offset of the lane).
+__device__ __forceinline__ void load_global_to_lds_b128(const void* base, unsigned lane_off, unsigned lds_addr) {
     // LDS address of lane l = M0 + 16 * l (M0 write needs one wait state before its use).
     // M0 is a reserved register the compiler sets up itself right before each of its own uses.
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-                 :
-                 : "s"(lds_addr), "v"(gptr)
-                 : "memory");
-}
-
-// Same with the global address given as (wavefront-uniform 64-bit base) + (32-bit byte offset
-// of the lane).
-__device__ __forceinline__ void load_global_to_lds_b128(const void* base, unsigned lane_off, unsigned lds_addr) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :
                  : "s"(lds_addr), "v"(lane_off), "s"(base)
@@ -149,8 +141,8 @@ __device__ __forceinline__ unsigned lds_address(const void* p) {
 // whose completion the compiler waits for is in flight with the transfers, which its counts do not know.
 // Bound by those trips: with lengths, table entries and queries as vector loads, which return in order, the first keys were
 // requested only when all queries had arrived and were converted, us after a workgroup's start: 3.4 -> 1.5 with 48 rows a
-// wavefront (8 sequences of 4K keys), 1.3 -> 1.0 with 16 (one of 2K).  A round of 32 layers with 2K keys 438.8 -> 427.6 us, one
-// layer with 32K keys 64.7 -> 63.9.
+// wavefront (8 sequences of 4K keys), 1.3 -> 1.0 with 16 (one of 2K).  A round of 32 layers with 2K keys 442.0 -> 430.8 us, one
+// layer with 32K keys 66.7 -> 64.7.
 typedef const int32_t __attribute__((address_space(4)))* scalar_ptr;
 __device__ __forceinline__ int scalar_load(const int32_t* p, int i) { return reinterpret_cast<scalar_ptr>(reinterpret_cast<size_t>(p))[i]; }
 
