@@ -26,6 +26,11 @@ def run(w, att, parent, n_nodes, prefix):
     return host(out).astype(np.float64), plan
 
 
+def main_kernel(row_blocks):
+    """Tiles of 256 rows have the kernel with 32-row blocks only; those of 192 here have too few stages for it."""
+    return "tree_attn_wide_kernel" if row_blocks == 4 else "tree_attn_mfma_kernel"
+
+
 def reference(w, att, parent, n_nodes, prefix, rows=None):
     return oracle.tree_attn(att["q"][0], att["k_cache"][0], att["v_cache"][0], "bf16", att["strides"], att["block_table"], prefix,
                             n_nodes, parent, w.Hq, w.Hkv, w.D, w.page_size, att["scale"], rows=rows)
@@ -65,7 +70,7 @@ def test_every_number_of_row_blocks(case, layout):
     n_nodes, prefix = np.full(B, K, np.int32), np.full(B, P, np.int32)
     n_nodes[1:], prefix[1:] = rng.integers(1, K + 1, B - 1), rng.integers(P // 2, P + 1, B - 1)
     got, plan = run(w, att, parent, n_nodes, prefix)
-    assert plan.row_blocks == mb, plan
+    assert (plan.row_blocks, plan.kernel) == (mb, main_kernel(mb)), plan
     compare(w, att, parent, n_nodes, prefix, got, sample(rng, w, n_nodes, 60 // B + 1))
 
 
@@ -144,7 +149,7 @@ def test_scores_that_outgrow_the_reference(case):
     parent = np.stack([inputs.random_recursive_tree(rng, K, 8) for _ in range(B)])
     n_nodes = np.full(B, K, np.int32)
     got, plan = run(w, att, parent, n_nodes, prefix)
-    assert plan.row_blocks == mb, plan
+    assert (plan.row_blocks, plan.kernel) == (mb, main_kernel(mb)), plan
     assert rise * (P // 2) * w.D * att["scale"] * 1.44 > 2 * 24              # twice the lazy bound in log2 units
     compare(w, att, parent, n_nodes, prefix, got, sample(rng, w, n_nodes, 80 // B + 1))
 
