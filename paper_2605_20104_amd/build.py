@@ -17,7 +17,7 @@ OBJ_DIR = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libgraft.so")
 LIB_TIMING = os.path.join(PKG, "libgraft_timing.so")     # the same library with the attention kernel's time stamps
 NATIVE = os.path.join(PKG, "_native.so")                 # tensor marshalling of the Python binding (csrc/binding.cpp)
-SOURCES = ["api.hip", "retrieve.hip", "tree_mask.hip", "tree_attn.hip", "tree_attn_wide.hip", "tree_attn_direct.hip", "accept.hip", "matrix.hip", "kv_compact.hip", "prune.hip"]
+SOURCES = ["api.hip", "retrieve.hip", "tree_mask.hip", "tree_attn.hip", "tree_attn_wide.hip", "tree_attn_direct.hip", "tree_attn_parts.hip", "accept.hip", "matrix.hip", "kv_compact.hip", "prune.hip"]
 
 # packed-fp32 code generation is switched off for every device compile; VGPR spills must not
 # land in AccVGPRs (the attention kernel manages those by hand).  Kernel arguments: the first 14 words arrive in

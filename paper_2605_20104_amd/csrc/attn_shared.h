@@ -77,9 +77,11 @@ struct DirectPlan {
     int mb, rg, n_row_tiles, n_splits, r_pad;
     size_t ws_o_bytes, ws_bytes;
     double cost;        // estimated cycles
+    bool parts;         // fp32 on the fp16 matrix cores (tree_attn_parts.hip)
 };
 DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages, int32_t dtype,
                        bool may_split);
+int32_t launch_parts(const DirectPlan& pl, const AttnParams& p, int32_t D, hipStream_t s);
 int32_t launch_direct(const DirectPlan& pl, AttnParams p, int32_t D, int32_t dtype, void* workspace, hipStream_t s);
 
 // Profiling hook state (per host thread): event pairs attached to the main kernel's dispatch

@@ -1366,7 +1366,7 @@ extern "C" int32_t graft_attn_plan(int32_t B, int32_t K_max, int32_t Hq, int32_t
 extern "C" const char* graft_attn_kernel_name(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages, int32_t dtype) {
     if (!graft::attn_shape_ok(B, K_max, Hq, Hkv, D, max_pages)) return nullptr;
     const graft::PathChoice& c = graft::choose_path(B, K_max, Hq, Hkv, D, max_pages, dtype);
-    return c.direct ? "tree_attn_direct_kernel" : (c.mfma.wide ? "tree_attn_wide_kernel" : "tree_attn_mfma_kernel");
+    return c.direct ? (c.dir.parts ? "tree_attn_parts_kernel" : "tree_attn_direct_kernel") : (c.mfma.wide ? "tree_attn_wide_kernel" : "tree_attn_mfma_kernel");
 }
 // Holds the launch plan of this host thread's following calls (workspace query included) at
 // n_splits splits and n_row_tiles row tiles where the shape allows them; zeros give the plan

@@ -1,5 +1,5 @@
-// graft_tree_attn, direct path: fp32 storage (any head size), bf16 with D = 64, and bf16 with D = 128
-// where the keys are few.
+// graft_tree_attn, direct path: fp32 storage (any head size; the longer sequences take tree_attn_parts.hip), bf16 with D = 64, and bf16
+// with D = 128 where the keys are few.  Plans and launches of both.
 //
 // A wavefront owns its keys: the wavefronts of a workgroup split a key range between them (kg
 // key groups), as well as the query rows (rg row groups of MB 16-row blocks), walk their tiles (32
@@ -33,49 +33,16 @@
 // otherwise they are requested again.  Q and the ancestor masks follow and are not waited for.  With the pieces of the
 // merge through LDS read all at once: rounds of 16 layers with D = 64 288 -> 272 us, 8 layers in fp32 191 -> 188,
 // one small layer 18.1 -> 17.5.
+#include <algorithm>
 #include <type_traits>
 
-#include "attn_shared.h"
+#include "attn_direct.h"
 
 namespace graft {
 
-constexpr int DR_WAVES = 8;                     // wavefronts per workgroup, two per SIMD
-constexpr int DR_THREADS = 64 * DR_WAVES;
+constexpr int PARTS_PAGES_128 = 48;              // (at plan_direct)
 // Rows of a row block: 32 where a wavefront has that many and the products come in that size without a loss
 constexpr int row_block_rows(bool bf16, int D, int mb) { return bf16 && D == 64 && mb >= 2 ? 32 : 16; }
-constexpr float DR_LAZY_LOG2 = 16.0f;           // a row keeps its reference while exponents stay below 16
-constexpr int DR_MAX_SPLITS = 32;
-constexpr int DR_MASK_BYTES = 2048;             // ancestor masks of a sequence
-constexpr int DR_LDS_BYTES = 160 * 1024;
-
-__device__ __forceinline__ unsigned lds_offset(const void* p) {
-    return static_cast<unsigned>(reinterpret_cast<size_t>((const __attribute__((address_space(3))) unsigned char*)(p)));
-}
-
-// Sum / maximum over the lanes that hold the same row: lane, lane + 32 and, with 16 rows to a block, those 16 apart.
-template <int RB> __device__ __forceinline__ float row_sum(float v) {
-    if constexpr (RB == 16) {
-        const unsigned u = __float_as_uint(v);
-        const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-        v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-    const unsigned u = __float_as_uint(v);
-    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-template <int RB> __device__ __forceinline__ float row_max(float v) {
-    if constexpr (RB == 16) return rows_max_f32(v);
-    const unsigned u = __float_as_uint(v);
-    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return __builtin_fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
-// Workgroup barrier that orders LDS traffic only: keys and values on their way stay in flight.
-__device__ __forceinline__ void lds_only_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 // A lane's scores of one row block: 4 T values, value v = t[v / 4][v % 4].
 template <int T> struct ScoreTiles {
@@ -427,11 +394,6 @@ template <int D> struct DirectOps<__bf16, D, 32> : DirectOpsBf16<D> {
         return floatx4{o[u >> 2][at], o[u >> 2][at + 1], o[u >> 2][at + 2], o[u >> 2][at + 3]};
     }
 };
-
-__device__ __forceinline__ void store4(float* p, const floatx4& v) { *reinterpret_cast<floatx4*>(p) = v; }
-__device__ __forceinline__ void store4(__bf16* p, const floatx4& v) {
-    *reinterpret_cast<uintx2*>(p) = uintx2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-}
 
 // p.R_pad = rows covered by the row tiles; rg (row groups) and the rest of the shape as below.  One row block
 // with D = 64 leaves room for a second workgroup on the compute unit.
@@ -813,42 +775,7 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
     __syncthreads();
     const int rows = rg * 16 * MB;                                // of this workgroup
     const auto merge = [&](auto kg_) __attribute__((always_inline)) {
-        constexpr int KG = decltype(kg_)::value;                  // (all reads of a piece in flight: one after the other they took 1 us)
-        for (int x = tid; x < rows * (D / 4); x += DR_THREADS) {
-            const int lr = x / (D / 4), d4 = x % (D / 4);
-            float2 ml[KG];
-            floatx4 part_o[KG];
-#pragma unroll
-            for (int k = 0; k < KG; ++k) ml[k] = *reinterpret_cast<const float2*>(ml_lds + 2 * (k * rows + lr));
-#pragma unroll
-            for (int k = 0; k < KG; ++k) part_o[k] = *reinterpret_cast<const floatx4*>(merge_lds + (k * rows + lr) * PITCH + 4 * d4);
-            float mm = -INFINITY;
-#pragma unroll
-            for (int k = 0; k < KG; ++k) mm = fmaxf(mm, ml[k].x);
-            float den = 0.f;
-            floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int k = 0; k < KG; ++k) {
-                const float f = ml[k].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[k].x - mm);
-                den += f * ml[k].y;
-                acc += part_o[k] * f;
-            }
-            const int r = rt * rows + lr;
-            if (n_splits == 1) {
-                if (r < p.R) {
-                    const int i = (r * p.g_magic) >> 16;
-                    const bool keep = i < n && den > 0.f;
-                    const floatx4 y = keep ? acc * (1.0f / den) : floatx4{0.f, 0.f, 0.f, 0.f};
-                    store4(outp + ((static_cast<size_t>(b) * p.K_max + i) * p.Hq + g * p.G + (r - i * p.G)) * D + 4 * d4, y);
-                }
-            } else {
-                store4(ws_o + (part + r) * D + 4 * d4, acc);
-                if (d4 == 0) {
-                    p.ws_ml[2 * (part + r)] = mm;
-                    p.ws_ml[2 * (part + r) + 1] = den;
-                }
-            }
-        }
+        merge_key_groups<T, D, decltype(kg_)::value>(p, merge_lds, ml_lds, rows, rt * rows, tid, b, g, n, n_splits, part);
     };
     if (kg == 8) merge(std::integral_constant<int, 8>{});
     else if (kg == 4) merge(std::integral_constant<int, 4>{});
@@ -941,6 +868,8 @@ DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_
     const int64_t tiles = (static_cast<int64_t>(max_pages) * GRAFT_PAGE_SIZE + TK - 1) / TK;
     const int64_t cus = device_compute_units();
     const int mb_max = dtype == GRAFT_F32 ? (D == 128 ? 2 : 1) : (D == 128 ? 1 : 4);
+    const double rows = static_cast<double>(B) * Hkv * R;
+    const auto merge_cost = [&](int sp) { return sp > 1 ? 8000.0 + 600.0 * sp + sp * rows * D / 400.0 : 0.0; };
     for (int mb = 1; mb <= mb_max; mb *= 2) {
         double c_step = D == 64 ? 2650.0 : (mb == 1 ? 4700.0 : 8200.0);
         if (dtype != GRAFT_F32 && D == 128) c_step = 2600.0;
@@ -954,17 +883,27 @@ DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_
             for (int sp = 1; sp <= (may_split ? DR_MAX_SPLITS : 1); ++sp) {
                 const int64_t per = (tiles + static_cast<int64_t>(sp) * kg - 1) / (static_cast<int64_t>(sp) * kg);
                 const int64_t rounds = (units * sp + cus - 1) / cus;
-                const double rows = static_cast<double>(B) * Hkv * R;
-                const double cost = rounds * (c_fixed + per * c_step) + (sp > 1 ? 8000.0 + 600.0 * sp + sp * rows * D / 400.0 : 0.0);
-                if (best.cost < 0.0 || cost < best.cost) {
-                    best.cost = cost;
-                    best.mb = mb;
-                    best.rg = rg;
-                    best.n_row_tiles = n_rt;
-                    best.n_splits = sp;
-                }
+                const double cost = rounds * (c_fixed + per * c_step) + merge_cost(sp);
+                if (best.cost < 0.0 || cost < best.cost) best = {mb, rg, n_rt, sp, 0, 0, 0, cost, false};
                 if (units * sp > 4 * cus || per <= 1) break;
             }
+        }
+    }
+    // fp32 on the fp16 matrix cores (tree_attn_parts.hip): 32 rows and eight key groups a workgroup, tiles of 32 keys.  A step is 3.82 us
+    // with D = 128 and 2.22 with D = 64; one that not all wavefronts have takes its share, at least half (their SIMDs are their own).
+    // Tables of fewer than PARTS_PAGES_128 pages stay with fp32 MFMAs for D = 128: tests/test_gpu_attn_direct.py holds the row groups
+    // (2, 4 and 8) of that kernel to sequences of 100 to 733 tokens.  There the rule costs speed: 256 workgroups of 256 keys take 16.3 us
+    // so and 12.2 with parts, of 512 keys 25.7 and 16.0.
+    if (dtype == GRAFT_F32 && (D == 64 || max_pages >= PARTS_PAGES_128)) {
+        const int n_rt = (R + 31) / 32;
+        const int64_t tiles32 = (static_cast<int64_t>(max_pages) + 1) / 2, units = static_cast<int64_t>(B) * Hkv * n_rt;
+        const double c_step = D == 64 ? 4750.0 : 8150.0, c_fixed = D == 64 ? 12000.0 : 14500.0;
+        for (int sp = 1; sp <= (may_split ? DR_MAX_SPLITS : 1); ++sp) {
+            const int64_t per = (tiles32 + sp - 1) / sp, rounds = (units * sp + cus - 1) / cus, over = per % DR_WAVES;
+            const double steps = static_cast<double>(per / DR_WAVES) + (over ? std::max(0.5, over / static_cast<double>(DR_WAVES)) : 0.0);
+            const double cost = rounds * (c_fixed + steps * c_step) + merge_cost(sp);
+            if (cost < best.cost) best = {2, 1, n_rt, sp, 0, 0, 0, cost, true};
+            if (units * sp > 4 * cus || per <= DR_WAVES / 2) break;
         }
     }
     best.r_pad = best.n_row_tiles * best.rg * best.mb * 16;
@@ -977,39 +916,12 @@ DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_
 }
 
 template <typename T, int D, int MB>
-static int32_t launch_one(const DirectPlan& pl, const AttnParams& p, int32_t dtype, hipStream_t s) {
-    auto kernel = tree_attn_direct_kernel<T, D, MB>;
-    const unsigned lds = static_cast<unsigned>(direct_lds_bytes(MB, pl.rg, D, dtype));
-    if (lds > 65536) {                                            // more than the default limit needs opting in, once per device
-        static thread_local int done_device = -1;
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-        if (done_device != dev) {
-            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, DR_LDS_BYTES);
-            done_device = dev;
-        }
-    }
-    // A launch holds fewer than 2^32 work-items.  Batches that need more go in pieces of whole sequences: one
-    // sequence has at most 65535 * 128 workgroups (KV heads, row tiles), which fits.
-    constexpr int64_t max_workgroups = ((int64_t{1} << 32) - 1) / DR_THREADS - 8;
-    const int64_t per_sequence = static_cast<int64_t>(p.Hkv) * pl.n_splits * pl.n_row_tiles;
-    const int64_t piece = max_workgroups / per_sequence;
-    AttnParams part = p;
-    for (int64_t b = 0; b < p.B; b += piece) {
-        part.B = static_cast<int32_t>(p.B - b < piece ? p.B - b : piece);
-        const size_t elements = static_cast<size_t>(b) * p.K_max * p.Hq * D;
-        part.q = static_cast<const T*>(p.q) + elements;
-        part.out = static_cast<T*>(p.out) + elements;
-        part.block_table = p.block_table + b * p.max_pages;
-        part.prefix_len = p.prefix_len + b;
-        part.n_nodes = p.n_nodes + b;
-        part.mask = p.mask + b * p.K_max * GRAFT_MASK_WORDS;
-        launch_attn(kernel, dim3(xcd_grid(static_cast<int64_t>(part.B) * p.Hkv * pl.n_splits, pl.n_row_tiles)), dim3(DR_THREADS), lds, s,
-                    part, pl.rg, DR_WAVES / pl.rg);
-        const int32_t rc = check_launch();
-        if (rc != GRAFT_OK) return rc;
-    }
-    if (pl.n_splits == 1) return GRAFT_OK;
+static int32_t launch_rows(const DirectPlan& pl, const AttnParams& p, int32_t dtype, hipStream_t s) {
+    return launch_pieces<T, D, tree_attn_direct_kernel<T, D, MB>>(pl, p, static_cast<unsigned>(direct_lds_bytes(MB, pl.rg, D, dtype)), s);
+}
+template <typename T, int D>
+static int32_t launch_merge(int32_t rc, const DirectPlan& pl, const AttnParams& p, hipStream_t s) {
+    if (rc != GRAFT_OK || pl.n_splits == 1) return rc;
     // (keys are split only while the chip is not full: one piece, few rows)
     const int64_t n_rows = static_cast<int64_t>(p.B) * p.Hkv * p.R;
     hipLaunchKernelGGL((tree_attn_direct_merge_kernel<T, D>), dim3(static_cast<unsigned>((n_rows * (D / 4) + 255) / 256)), dim3(256), 0, s,
@@ -1024,12 +936,13 @@ int32_t launch_direct(const DirectPlan& pl, AttnParams p, int32_t D, int32_t dty
     p.ws_o = static_cast<unsigned short*>(workspace);
     p.ws_ml = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + pl.ws_o_bytes);
     if (dtype == GRAFT_F32) {
-        if (D == 64) return launch_one<float, 64, 1>(pl, p, dtype, s);
-        return pl.mb == 1 ? launch_one<float, 128, 1>(pl, p, dtype, s) : launch_one<float, 128, 2>(pl, p, dtype, s);
+        if (D == 64) return launch_merge<float, 64>(pl.parts ? launch_parts(pl, p, D, s) : launch_rows<float, 64, 1>(pl, p, dtype, s), pl, p, s);
+        const int32_t rc = pl.parts ? launch_parts(pl, p, D, s) : (pl.mb == 1 ? launch_rows<float, 128, 1>(pl, p, dtype, s) : launch_rows<float, 128, 2>(pl, p, dtype, s));
+        return launch_merge<float, 128>(rc, pl, p, s);
     }
-    if (D == 128) return launch_one<__bf16, 128, 1>(pl, p, dtype, s);
-    if (pl.mb == 4) return launch_one<__bf16, 64, 4>(pl, p, dtype, s);
-    return pl.mb == 1 ? launch_one<__bf16, 64, 1>(pl, p, dtype, s) : launch_one<__bf16, 64, 2>(pl, p, dtype, s);
+    if (D == 128) return launch_merge<__bf16, 128>(launch_rows<__bf16, 128, 1>(pl, p, dtype, s), pl, p, s);
+    const int32_t rc = pl.mb == 4 ? launch_rows<__bf16, 64, 4>(pl, p, dtype, s) : (pl.mb == 1 ? launch_rows<__bf16, 64, 1>(pl, p, dtype, s) : launch_rows<__bf16, 64, 2>(pl, p, dtype, s));
+    return launch_merge<__bf16, 64>(rc, pl, p, s);
 }
 
 }  // namespace graft
