@@ -31,6 +31,7 @@ __device__ __forceinline__ void arg_take(float& bv, int32_t& bi, float v, int32_
 // has it.  8 x 48 rows of 151936 (233 MB): 36 us, 6.5 TB/s; the call, with the walk kernel and the gap before it,
 // 48.1 -> 45.4 us, 0.6 of it the walk kernel's; four loads in flight and an (index, value) pair kept per
 // element before.
+template <bool ONCE>
 __global__ __launch_bounds__(AM_THREADS) void argmax_chunk_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ n_nodes, int32_t K_max, int32_t V,
     int32_t per, ArgPartial* __restrict__ partial) {
@@ -55,7 +56,7 @@ __global__ __launch_bounds__(AM_THREADS) void argmax_chunk_kernel(
 #pragma unroll
         for (int u = 0; u < AM_QUADS; ++u) {
             const int32_t qu = s0 + tid + u * AM_THREADS;
-            x[u] = qu < c.q1 ? c.quad[qu] : float4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+            x[u] = qu < c.q1 ? load_logits<ONCE>(c.quad + qu) : float4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
         }
         float m = -INFINITY;                     // (fmax passes over NaN, as the comparisons do)
 #pragma unroll
@@ -245,8 +246,8 @@ static int32_t accept_impl(const int32_t* parent, const int32_t* tokens, const i
     if (logits) {
         const RowCut cut = row_cut(static_cast<int64_t>(B) * K_max, V);
         chunks = cut.chunks;
-        hipLaunchKernelGGL(argmax_chunk_kernel, dim3(chunks, K_max, B), dim3(AM_THREADS), 0, s, logits, n_nodes, K_max, V,
-                           cut.per, ws);
+        const auto scan = read_once(static_cast<int64_t>(B) * K_max, V) ? argmax_chunk_kernel<true> : argmax_chunk_kernel<false>;
+        hipLaunchKernelGGL(scan, dim3(chunks, K_max, B), dim3(AM_THREADS), 0, s, logits, n_nodes, K_max, V, cut.per, ws);
         int32_t rc = check_launch();
         if (rc != GRAFT_OK) return rc;
         partial = ws;

@@ -148,6 +148,18 @@ __device__ __forceinline__ float rows_max_f32(float v) {
     return v;
 }
 
+// Sixteen bytes of logits, ONCE: with a load that says that they are not needed again.  Where the rows are more than the
+// 256 MB Infinity Cache still holds behind whoever wrote them, that is faster: acceptance of 8 x 48 rows of 151936 (233 MB), written in
+// front of it, 55.7 -> 49.7 us, 16 x 64 of 60001 (246 MB) 59.2 -> 49.7, matrix refresh of 16 x 128 of 128256 178.5 -> 165.5.  Below it is
+// slower where they have just been written: 80 MB 19.6 / 20.5, 100 MB 22.4 / 23.6, 184 MB 35.5 / 35.2, 210 MB 42.9 / 43.8.
+template <bool ONCE> __device__ __forceinline__ float4 load_logits(const float4* p) {
+    if constexpr (!ONCE) return *p;
+    typedef float float4_t __attribute__((ext_vector_type(4)));
+    const float4_t x = __builtin_nontemporal_load(reinterpret_cast<const float4_t*>(p));
+    return float4{x[0], x[1], x[2], x[3]};
+}
+inline bool read_once(int64_t rows, int32_t V) { return rows * V * 4 > (int64_t{208} << 20); }
+
 // A logits row cut for 16-byte loads whatever its length and address: `head` elements up to the first
 // 16-byte boundary, `quads` aligned groups of four, `tail` elements behind them.  The groups are dealt to
 // `chunks` workgroups, `per` to each, the edges (at most three elements each) go to the first and the

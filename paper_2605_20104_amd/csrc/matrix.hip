@@ -15,6 +15,8 @@
 // id) into 64 bits so that "larger logit first, then smaller id" is one unsigned compare.
 // A one-wavefront kernel per node then merges the chunks, writes the greedy token and, if
 // no later node carries the same token, the matrix row.
+#include <type_traits>
+
 #include "common.h"
 
 namespace graft {
@@ -182,7 +184,7 @@ constexpr int MU_REG_QUADS = 12;                    // covers V <= 196608
 static_assert(MU_REG_QUADS * MU_THREADS >= ROW_QUADS, "a chunk of the cut fits the registers, for V <= 196608");
 constexpr int MU_LIST = 256;                        // four candidates per lane of the last wavefront
 
-template <int KK>
+template <int KK, bool ONCE>
 __global__ __launch_bounds__(MU_THREADS) void topk_chunk_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ n_nodes, int32_t K_max, int32_t V,
     int32_t per, int32_t k, u64* __restrict__ partial) {
@@ -209,7 +211,7 @@ __global__ __launch_bounds__(MU_THREADS) void topk_chunk_kernel(
 #pragma unroll
         for (int u = 0; u < MU_REG_QUADS; ++u) {
             const int32_t qu = q0 + tid + u * MU_THREADS;
-            x[u] = qu < q1 ? c.quad[qu] : float4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+            x[u] = qu < q1 ? load_logits<ONCE>(c.quad + qu) : float4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
         }
         if (tid == 0) list_n = 0;
         float m = -INFINITY;
@@ -375,9 +377,13 @@ extern "C" int32_t graft_matrix_update(const int32_t* tokens, const int32_t* n_n
     u64* partial = static_cast<u64*>(workspace);
     const RowCut cut = row_cut(static_cast<int64_t>(B) * K_max, V);
     dim3 grid(cut.chunks, K_max, B);
-    if (k <= 4) hipLaunchKernelGGL(topk_chunk_kernel<4>, grid, dim3(MU_THREADS), 0, s, logits, n_nodes, K_max, V, cut.per, k, partial);
-    else if (k <= 8) hipLaunchKernelGGL(topk_chunk_kernel<8>, grid, dim3(MU_THREADS), 0, s, logits, n_nodes, K_max, V, cut.per, k, partial);
-    else hipLaunchKernelGGL(topk_chunk_kernel<16>, grid, dim3(MU_THREADS), 0, s, logits, n_nodes, K_max, V, cut.per, k, partial);
+    const auto scan = [&](auto once_) {
+        constexpr bool ONCE = decltype(once_)::value;
+        const auto kernel = k <= 4 ? topk_chunk_kernel<4, ONCE> : (k <= 8 ? topk_chunk_kernel<8, ONCE> : topk_chunk_kernel<16, ONCE>);
+        hipLaunchKernelGGL(kernel, grid, dim3(MU_THREADS), 0, s, logits, n_nodes, K_max, V, cut.per, k, partial);
+    };
+    if (read_once(static_cast<int64_t>(B) * K_max, V)) scan(std::true_type{});
+    else scan(std::false_type{});
     int32_t rc = check_launch();
     if (rc != GRAFT_OK) return rc;
     hipLaunchKernelGGL(matrix_update_merge_kernel, dim3(B * K_max), dim3(64), 0, s, tokens, n_nodes, V, B, K_max, k,
