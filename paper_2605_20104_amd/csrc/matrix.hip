@@ -11,10 +11,13 @@
 // The refresh ranks every verified node's logits row.  Like the argmax of the acceptance
 // step it is one HBM scan of the logits (4 V bytes per node): up to GRAFT_ARGMAX_CHUNKS workgroups
 // per row; a workgroup finds a threshold from its threads' maxima, collects the few elements
-// above it and picks its chunk's k best from those in k rounds.  A key packs (logit,
+// above it and picks its chunk's k best from those.  A key packs (logit,
 // id) into 64 bits so that "larger logit first, then smaller id" is one unsigned compare.
 // A one-wavefront kernel per node then merges the chunks, writes the greedy token and, if
 // no later node carries the same token, the matrix row.
+// The threshold and the ranking of the few are one count of larger ones per lane each (kth_of, best_of) where k rounds of a wavefront
+// maximum stood.  us a call in a graph, before / now: 1 x 40 rows of 128256 13.5 / 11.3, 8 x 24 of 32000 14.2 / 11.5, 8 x 128 of 32000
+// 32.5 / 29.4, 4 x 64 of 65536 with k = 16 27.1 / 21.3, 16 x 16 of 8000 with k = 4 9.0 / 7.9.
 #include <type_traits>
 
 #include "common.h"
@@ -117,20 +120,20 @@ __device__ __forceinline__ void topk_insert(u64 (&top)[KK], float& worst, float 
 }
 
 // The scan of one thread's share of a chunk: take(value, id) for every element.
-template <class Take>
+template <int THREADS, class Take>
 __device__ __forceinline__ void scan_chunk(const float* __restrict__ row, const RowChunk& c, int tid, Take&& take) {
     if (tid < c.edge) take(row[c.edge_at(tid)], c.edge_at(tid));
     constexpr int U = 4;                            // 16-byte loads in flight per thread
-    for (int32_t qd = c.q0 + tid; qd < c.q1; qd += U * MU_THREADS) {
+    for (int32_t qd = c.q0 + tid; qd < c.q1; qd += U * THREADS) {
         float4 x[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int32_t qu = qd + u * MU_THREADS;
+            const int32_t qu = qd + u * THREADS;
             x[u] = c.quad[qu < c.q1 ? qu : qd];     // a lane past the end re-reads its first quad (skipped below)
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int32_t qu = qd + u * MU_THREADS;
+            const int32_t qu = qd + u * THREADS;
             if (qu < c.q1) {
                 const int32_t e = c.head + qu * 4;
                 take(x[u].x, e);
@@ -143,28 +146,78 @@ __device__ __forceinline__ void scan_chunk(const float* __restrict__ row, const 
 }
 
 // k rounds over the workgroup: every wavefront offers its best remaining key, the owner of
-// the round's winner (keys are unique: the id is part of them) pops it.  Returns how many of
-// this thread's keys were taken.
-template <int KK>
-__device__ __forceinline__ int select_rounds(u64 (&top)[KK], int k, u64 (&red)[2][MU_WAVES], u64* out,
-                                             int tid, int lane, int wave) {
-    int taken = 0;
+// the round's winner (keys are unique: the id is part of them) pops it.
+template <int KK, int WAVES>
+__device__ __forceinline__ void select_rounds(u64 (&top)[KK], int k, u64 (&red)[2][WAVES], u64* out,
+                                              int tid, int lane, int wave) {
     for (int j = 0; j < k; ++j) {
         const u64 wmax = wave_max_u64(top[0]);
         if (lane == 0) red[j & 1][wave] = wmax;
         __syncthreads();
         u64 gmax = red[j & 1][0];
 #pragma unroll
-        for (int w = 1; w < MU_WAVES; ++w) gmax = red[j & 1][w] > gmax ? red[j & 1][w] : gmax;
+        for (int w = 1; w < WAVES; ++w) gmax = red[j & 1][w] > gmax ? red[j & 1][w] : gmax;
         if (tid == 0) out[j] = gmax;
         if (gmax != 0 && top[0] == gmax) {
 #pragma unroll
             for (int t = 0; t + 1 < KK; ++t) top[t] = top[t + 1];
             top[KK - 1] = 0;
-            ++taken;
         }
     }
-    return taken;
+}
+
+// Maximum over 8 or 16 neighbouring lanes, all of them get it.
+template <int N> __device__ __forceinline__ float lanes_max(float v) {
+    static_assert(N == 8 || N == 16, "groups of a DPP row");
+    v = __builtin_fmaxf(v, dpp_f32<0xB1>(v));
+    v = __builtin_fmaxf(v, dpp_f32<0x4E>(v));
+    v = __builtin_fmaxf(v, dpp_f32<0x141>(v));
+    return N == 8 ? v : __builtin_fmaxf(v, dpp_f32<0x140>(v));
+}
+// The k-th largest of N maxima of disjoint groups of elements (in LDS): at least k elements are no smaller.  A lane counts what is larger
+// than its own one; the smallest of those with fewer than k above them is the k-th.  (k rounds of a wavefront maximum, on which this
+// stood before, took 8 to 16 times a chain of six dependent lane exchanges.)
+template <int N> __device__ __forceinline__ float kth_of(const float* maxima, int k, int lane) {
+    static_assert(N >= GRAFT_MAX_SUCCESSORS && N <= 64 && N % 4 == 0, "one a lane, k of them");
+    const float own = maxima[lane % N];
+    int above = 0;
+#pragma unroll 1
+    for (int t = 0; t < N / 4; ++t) {
+        const float4 x = reinterpret_cast<const float4*>(maxima)[t];
+        above += (x.x > own) + (x.y > own) + (x.z > own) + (x.w > own);
+    }
+    return -wave_max_f32(above < k ? -own : -INFINITY);
+}
+// The k best of n <= 256 keys in LDS by one wavefront, best first, 0 (no key) where there are fewer; put(j, key) by one lane each.
+// Keys are unique, so a key's place is the number of larger ones, which every lane counts for its own where one a lane is enough.
+template <class Put> __device__ __forceinline__ void best_of(const u64* keys, int n, int k, int lane, Put&& put) {
+    if (n <= 64) {                                  // uniform
+        const u64 own = lane < n ? keys[lane] : 0;
+        int above = 0;
+        for (int t = 0; t < n; t += 8) {
+            u64 x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = keys[t + u];          // (behind the last one: whatever is there, not counted)
+#pragma unroll
+            for (int u = 0; u < 8; ++u) above += (t + u < n && x[u] > own) ? 1 : 0;
+        }
+        if (own != 0 && above < k) put(above, own);
+        if (lane >= __builtin_popcountll(__builtin_amdgcn_ballot_w64(own != 0)) && lane < k) put(lane, 0);
+        return;
+    }
+    u64 c[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) c[t] = (lane + t * 64) < n ? keys[lane + t * 64] : 0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int t = 0; t + 1 < 4 - a; ++t)
+            if (c[t + 1] > c[t]) { const u64 sw = c[t]; c[t] = c[t + 1]; c[t + 1] = sw; }
+    for (int j = 0; j < k; ++j) {
+        const u64 gmax = wave_max_key(c[0]);
+        if (lane == 0) put(j, gmax);
+        if (gmax != 0 && c[0] == gmax) { c[0] = c[1]; c[1] = c[2]; c[2] = c[3]; c[3] = 0; }
+    }
 }
 
 // Chunk scan: workgroup (chunk, node, sequence) -> its chunk's k best keys, best first.
@@ -172,12 +225,10 @@ __device__ __forceinline__ int select_rounds(u64 (&top)[KK], int k, u64 (&red)[2
 // Fast path (chunks that fit in registers, MU_REG_QUADS 16-byte loads per thread and at most one
 // edge element, all issued before anything else):
 //   1. every thread takes the maximum of its elements (one max3 per two elements);
-//   2. every wavefront finds the k-th largest of its 64 maxima (k rounds of a float max in
-//      registers; equal maxima leave together, which only lowers the result) and T is the
-//      largest of the four: at least k elements are >= T, so every one of the chunk's k
-//      best is >= T;
+//   2. T is the k-th largest of the maxima of 16 or 32 groups of threads: at least k elements are >= T, so every one
+//      of the chunk's k best is >= T;
 //   3. the elements >= T (normally a dozen or two) are appended to a list in LDS as keys;
-//   4. one wavefront picks the result from the list in k rounds.
+//   4. one wavefront ranks the list.
 // If the list overflows (long runs of equal values) or the chunk does not fit, the
 // workgroup takes the exact streaming path: per-thread sorted lists of KK >= k keys.
 constexpr int MU_REG_QUADS = 12;                    // covers V <= 196608
@@ -219,16 +270,13 @@ __global__ __launch_bounds__(MU_THREADS) void topk_chunk_kernel(
         for (int u = 0; u < MU_REG_QUADS; ++u)
             m = __builtin_fmaxf(__builtin_fmaxf(__builtin_fmaxf(m, x[u].x), __builtin_fmaxf(x[u].y, x[u].z)), x[u].w);
         m = __builtin_fmaxf(m, xe);                                  // (last: it was requested last)
-        // T = the largest over the wavefronts of "k-th largest of the wavefront's maxima"
-        float mm = m, tw = -INFINITY;
-        for (int j = 0; j < k; ++j) {
-            tw = wave_max_f32(mm);
-            if (mm == tw) mm = -INFINITY;
-        }
-        __shared__ float tws[MU_WAVES];
-        if (lane == 0) tws[wave] = tw;
+        // T = the k-th largest maximum of 16 groups of threads, of 32 where k is above 8 (the smallest of 16 would let in 50 elements)
+        constexpr int GROUP = KK > 8 ? 8 : 16;
+        __shared__ __attribute__((aligned(16))) float tops[MU_THREADS / GROUP];
+        const float top = lanes_max<GROUP>(m);
+        if (lane % GROUP == 0) tops[tid / GROUP] = top;
         __syncthreads();                                             // also orders list_n = 0 before the appends
-        const float T = __builtin_fmaxf(__builtin_fmaxf(tws[0], tws[1]), __builtin_fmaxf(tws[2], tws[3]));
+        const float T = kth_of<MU_THREADS / GROUP>(tops, k, lane);
         if (tid < c.edge && xe >= T) {
             const int slot = atomicAdd(&list_n, 1);
             if (slot < MU_LIST) list[slot] = rank_key(xe, c.edge_at(tid));
@@ -250,21 +298,7 @@ __global__ __launch_bounds__(MU_THREADS) void topk_chunk_kernel(
         __syncthreads();
         const int32_t nl = list_n;
         if (nl <= MU_LIST) {                                         // uniform
-            if (wave == 0) {
-                u64 c4[4];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) c4[t] = (lane + t * 64) < nl ? list[lane + t * 64] : 0;
-#pragma unroll
-                for (int a = 0; a < 3; ++a)
-#pragma unroll
-                    for (int t = 0; t + 1 < 4 - a; ++t)
-                        if (c4[t + 1] > c4[t]) { const u64 sw = c4[t]; c4[t] = c4[t + 1]; c4[t + 1] = sw; }
-                for (int j = 0; j < k; ++j) {
-                    const u64 gmax = wave_max_key(c4[0]);
-                    if (lane == 0) out[j] = gmax;
-                    if (gmax != 0 && c4[0] == gmax) { c4[0] = c4[1]; c4[1] = c4[2]; c4[2] = c4[3]; c4[3] = 0; }
-                }
-            }
+            if (wave == 0) best_of(list, nl, k, lane, [&](int j, u64 key) { out[j] = key; });
             exact = false;
         }
         __syncthreads();
@@ -276,8 +310,8 @@ __global__ __launch_bounds__(MU_THREADS) void topk_chunk_kernel(
 #pragma unroll
     for (int j = 0; j < KK; ++j) top[j] = 0;
     float worst = -INFINITY;
-    scan_chunk(row, c, tid, [&](float v, int32_t id) { topk_insert<KK>(top, worst, v, id); });
-    select_rounds<KK>(top, k, red, out, tid, lane, wave);
+    scan_chunk<MU_THREADS>(row, c, tid, [&](float v, int32_t id) { topk_insert<KK>(top, worst, v, id); });
+    select_rounds(top, k, red, out, tid, lane, wave);
 }
 
 // One wavefront per node: merge the chunks' keys, write the greedy token and the matrix row.
@@ -293,17 +327,12 @@ __global__ __launch_bounds__(64) void matrix_update_merge_kernel(
         if (lane == 0) target_ids[node] = -1;
         return;
     }
-    // chunks * k <= 256 candidates: four per lane, kept sorted
     const u64* cand = partial + static_cast<size_t>(node) * chunks * k;
     const int n_cand = chunks * k;
+    __shared__ u64 keys[GRAFT_ARGMAX_CHUNKS * GRAFT_MAX_SUCCESSORS];
     u64 c[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) c[t] = (lane + 64 * t) < n_cand ? cand[lane + 64 * t] : 0;
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int t = 0; t + 1 < 4 - a; ++t)
-            if (c[t + 1] > c[t]) { const u64 s = c[t]; c[t] = c[t + 1]; c[t + 1] = s; }
     // is this the last node (largest b, then i) carrying its token?
     const int32_t x = tokens[node];
     // The tokens of eight nodes per lane are requested at once, and only where one matches is the node looked at
@@ -328,15 +357,15 @@ __global__ __launch_bounds__(64) void matrix_update_merge_kernel(
         }
     }
     const bool write_row = x >= 0 && x < V && __builtin_amdgcn_ballot_w64(later) == 0;
-    for (int j = 0; j < k; ++j) {
-        const u64 gmax = wave_max_key(c[0]);
-        if (lane == 0) {
-            const int32_t id = gmax != 0 ? key_id(gmax) : -1;
-            if (j == 0) target_ids[node] = id;
-            if (write_row) M[static_cast<size_t>(x) * k + j] = id;
-        }
-        if (gmax != 0 && c[0] == gmax) { c[0] = c[1]; c[1] = c[2]; c[2] = c[3]; c[3] = 0; }
-    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        if (lane + 64 * t < n_cand) keys[lane + 64 * t] = c[t];
+    __syncthreads();                                // (one wavefront: LDS in order)
+    best_of(keys, n_cand, k, lane, [&](int j, u64 key) {
+        const int32_t id = key != 0 ? key_id(key) : -1;
+        if (j == 0) target_ids[node] = id;
+        if (write_row) M[static_cast<size_t>(x) * k + j] = id;
+    });
 }
 
 }  // namespace graft
