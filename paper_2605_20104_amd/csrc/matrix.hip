@@ -14,10 +14,10 @@
 // above it and picks its chunk's k best from those.  A key packs (logit,
 // id) into 64 bits so that "larger logit first, then smaller id" is one unsigned compare.
 // A one-wavefront kernel per node then merges the chunks, writes the greedy token and, if
-// no later node carries the same token, the matrix row.
+// no later node carries the same token, the matrix row.  Few short rows go to one workgroup each, which does all of it.
 // The threshold and the ranking of the few are one count of larger ones per lane each (kth_of, best_of) where k rounds of a wavefront
-// maximum stood.  us a call in a graph, before / now: 1 x 40 rows of 128256 13.5 / 11.3, 8 x 24 of 32000 14.2 / 11.5, 8 x 128 of 32000
-// 32.5 / 29.4, 4 x 64 of 65536 with k = 16 27.1 / 21.3, 16 x 16 of 8000 with k = 4 9.0 / 7.9.
+// maximum stood.  us a call in a graph, before / now: 1 x 40 rows of 128256 13.5 / 11.3, 8 x 24 of 32000 14.2 / 8.7, 8 x 128 of 32000
+// 32.5 / 29.4, 4 x 64 of 65536 with k = 16 27.1 / 21.3, 16 x 16 of 8000 with k = 4 9.0 / 5.9.
 #include <type_traits>
 
 #include "common.h"
@@ -368,6 +368,99 @@ __global__ __launch_bounds__(64) void matrix_update_merge_kernel(
     });
 }
 
+// One launch for few rows that are short: a workgroup has a whole row, all of it on the way at once, ranks it as above and writes the
+// greedy token and the matrix row itself.
+constexpr int MW_THREADS = 1024;
+constexpr int MW_QUADS = 8;                         // 16-byte loads in flight per thread: rows of up to MW_MAX elements
+constexpr int32_t MW_MAX = 4 * MW_QUADS * MW_THREADS;
+constexpr int64_t MW_ROWS = 256;
+
+template <int KK>
+__global__ __launch_bounds__(MW_THREADS) void topk_row_kernel(
+    const int32_t* __restrict__ n_nodes, const int32_t* __restrict__ tokens, const float* __restrict__ logits, int32_t K_max, int32_t V,
+    int32_t B, int32_t k, int32_t* __restrict__ M, int32_t* __restrict__ target_ids) {
+    const int i = blockIdx.x, b = blockIdx.y, node = b * K_max + i;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int32_t n = n_nodes[b];
+    if (i >= n || n > K_max) {                      // padding node
+        if (tid == 0) target_ids[node] = -1;
+        return;
+    }
+    __shared__ u64 red[2][MW_THREADS / 64];
+    __shared__ u64 list[MU_LIST];
+    __shared__ u64 best[GRAFT_MAX_SUCCESSORS];
+    __shared__ __attribute__((aligned(16))) float tops[MW_THREADS / 16];
+    __shared__ int32_t list_n, later;
+    const float* row = logits + static_cast<size_t>(node) * V;
+    const RowChunk c = row_chunk(row, V, 0, 1, V / 4);
+    const float xe = tid < c.edge ? row[c.edge_at(tid)] : -INFINITY;
+    float4 x[MW_QUADS];
+#pragma unroll
+    for (int u = 0; u < MW_QUADS; ++u) {
+        const int32_t qu = tid + u * MW_THREADS;
+        x[u] = qu < c.q1 ? c.quad[qu] : float4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    }
+    const int32_t t_own = tokens[node];
+    if (tid == 0) list_n = later = 0;
+    float m = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < MW_QUADS; ++u)
+        m = __builtin_fmaxf(__builtin_fmaxf(__builtin_fmaxf(m, x[u].x), __builtin_fmaxf(x[u].y, x[u].z)), x[u].w);
+    m = __builtin_fmaxf(m, xe);
+    const float top = lanes_max<16>(m);
+    if ((lane & 15) == 0) tops[tid >> 4] = top;
+    __syncthreads();                                // also orders list_n = later = 0 before what follows
+    const float T = kth_of<MW_THREADS / 16>(tops, k, lane);
+    const auto append = [&](float v, int32_t id) __attribute__((always_inline)) {
+        if (v >= T) {
+            const int slot = atomicAdd(&list_n, 1);
+            if (slot < MU_LIST) list[slot] = rank_key(v, id);
+        }
+    };
+    if (tid < c.edge) append(xe, c.edge_at(tid));
+    if (m >= T) {                                   // (few threads)
+#pragma unroll
+        for (int u = 0; u < MW_QUADS; ++u) {
+            const int32_t qu = tid + u * MW_THREADS, e = c.head + qu * 4;
+            if (qu < c.q1) {
+                append(x[u].x, e);
+                append(x[u].y, e + 1);
+                append(x[u].z, e + 2);
+                append(x[u].w, e + 3);
+            }
+        }
+    }
+    // is this the last node (largest b, then i) carrying its token?
+    for (int o = node + 1 + tid; o < B * K_max; o += MW_THREADS) {
+        if (tokens[o] == t_own) {
+            const int ob = o / K_max;
+            const int32_t on = n_nodes[ob];
+            if (o - ob * K_max < on && on <= K_max) later = 1;
+        }
+    }
+    __syncthreads();
+    const int32_t nl = list_n;
+    if (nl <= MU_LIST) {
+        if (wave > 0) return;
+        best_of(list, nl, k, lane, [&](int j, u64 key) { best[j] = key; });
+    } else {                                        // long runs of equal values: exact, per-thread sorted lists
+        u64 own[KK];
+#pragma unroll
+        for (int j = 0; j < KK; ++j) own[j] = 0;
+        float worst = -INFINITY;
+        scan_chunk<MW_THREADS>(row, c, tid, [&](float v, int32_t id) { topk_insert<KK>(own, worst, v, id); });
+        select_rounds(own, k, red, best, tid, lane, wave);
+        __syncthreads();
+        if (wave > 0) return;
+    }
+    if (lane < k) {
+        const u64 key = best[lane];
+        const int32_t id = key != 0 ? key_id(key) : -1;
+        if (lane == 0) target_ids[node] = id;
+        if (t_own >= 0 && t_own < V && later == 0) M[static_cast<size_t>(t_own) * k + lane] = id;
+    }
+}
+
 }  // namespace graft
 
 extern "C" int32_t graft_matrix_retrieve(const int32_t* M, int32_t V, int32_t k,
@@ -404,6 +497,18 @@ extern "C" int32_t graft_matrix_update(const int32_t* tokens, const int32_t* n_n
         return GRAFT_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     u64* partial = static_cast<u64*>(workspace);
+    // A row a workgroup, or several and a merge launch.  us a call in a graph, two launches / one:
+    //   1 x 40 rows of 32000 8.8 / 8.2, 4 x 48 of 32000 11.5 / 9.7, 4 x 64 of 32000 with k = 16 14.1 / 11.1, 1 x 40 of 8000 8.8 / 5.4;
+    //   longer rows, in two or more batches of loads, 1 x 40 of 50257 9.4 / 11.3, of 128256 11.3 / 14.0 (a compute unit on its own draws
+    //   60 GB/s from memory); more rows than compute units, 8 x 48 of 8000 9.4 / 10.7, 16 x 64 12.9 / 20.1.
+    // The host's side of a call 6.1 / 3.4 us.
+    if (static_cast<int64_t>(B) * K_max <= MW_ROWS && V <= MW_MAX) {
+        const dim3 grid(K_max, B);
+        if (k <= 4) hipLaunchKernelGGL(topk_row_kernel<4>, grid, dim3(MW_THREADS), 0, s, n_nodes, tokens, logits, K_max, V, B, k, M, target_ids);
+        else if (k <= 8) hipLaunchKernelGGL(topk_row_kernel<8>, grid, dim3(MW_THREADS), 0, s, n_nodes, tokens, logits, K_max, V, B, k, M, target_ids);
+        else hipLaunchKernelGGL(topk_row_kernel<16>, grid, dim3(MW_THREADS), 0, s, n_nodes, tokens, logits, K_max, V, B, k, M, target_ids);
+        return check_launch();
+    }
     const RowCut cut = row_cut(static_cast<int64_t>(B) * K_max, V);
     dim3 grid(cut.chunks, K_max, B);
     const auto scan = [&](auto once_) {
