@@ -153,10 +153,9 @@ __device__ __forceinline__ float keep_visible(float x, unsigned window, int bit)
     return __uint_as_float((__float_as_uint(x) & m) | (0xff800000u & ~m));
 }
 
-__device__ __forceinline__ unsigned short float_to_bf16_bits(float f) {
-    unsigned u = __float_as_uint(f);
-    u += 0x7fffu + ((u >> 16) & 1u);           // round to nearest even (finite inputs)
-    return static_cast<unsigned short>(u >> 16);
+// Loads of a merge, through a buffer descriptor: zeros, without a trip to memory, where the offset lies behind its end.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t merge_buffer(const void* base, unsigned bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, static_cast<int>(bytes), 0x00020000);
 }
 // Two fp32 -> one packed pair of bf16 (round to nearest even): v_cvt_pk_bf16_f32.
 __device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {

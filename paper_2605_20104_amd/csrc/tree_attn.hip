@@ -959,79 +959,85 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(GRAFT_ATTN_A
 // fp16 rows.  Lane (l16, lg) owns row l16, dims 4 lg .. +3 of both tiles, exactly the 16 bytes
 // it wrote of every split's block, so a split is one 1 KB read per wavefront.  The kernel is
 // a chain of memory round trips, not a stream, so a wavefront takes at most U splits (U = 2,
-// 4, 8 or 16, the smallest that covers them: registers, and with them the wavefronts in
-// flight, go with U) and has all their loads in flight at once (a split without keys has
+// 4, 8, 12 or 16, the smallest that covers them: registers, and the instructions, which are cold
+// here, go with U) and has all their loads in flight at once (a split without keys has
 // weight 0 and a zero block); with more than 16 splits, up to four wavefronts share a tile
 // pair and the first of them merges their sums through LDS.
+// All loads at once needs buffer loads, which return zeros behind the last split: with a condition
+// around every pair the first one was waited for in front of the second.  Requested with the
+// arguments that only the end needs, and without the divisions in front: 32 layers of 2K keys
+// (9 splits) 430 -> 408 us a round (404 -> 395 of it from 12 splits' loads instead of 16), one of
+// 32K keys (31 splits) 65.6 -> 63.9.  Two splits of 8 sequences of 4K keys take 5.8 us either way, and
+// with four tile pairs a wavefront: there it is 19 MB through the Infinity Cache.
 // WIDE: the partial rows of tree_attn_wide_kernel, in blocks of 32 rows x 16 dims.
 constexpr int CB_MAX_SPLITS = 16;
 constexpr int CB_MAX_WAVES = 8;          // per workgroup; the host picks a multiple of the wavefronts per tile pair
 
+// shape: wavefronts per tile pair, tile pairs per workgroup (8 bits each), ceil(256 / the former).  n_blk_magic: magic31 of the row blocks
+// of a (b, g), at most 140 (exact for tile / PIECES < 2^31 / 140: more rows than that have more than 300 GB of queries and results).
 template <int U, bool WIDE>
 __global__ __launch_bounds__(64 * CB_MAX_WAVES) void tree_attn_combine_kernel(
-    const unsigned short* ws_o, const float* ws_ml, const int32_t* n_nodes, int32_t n_tiles, int32_t wpt, int32_t tiles_per_wg, int32_t R,
-    int32_t R_pad, int32_t n_splits, int32_t n_kv_heads, AttnParams p) {
+    const unsigned short* ws_o, const float* ws_ml, const int32_t* n_nodes, int32_t n_tiles, int32_t shape, int32_t R, int32_t R_pad,
+    int32_t n_splits, uint32_t n_blk_magic, int32_t n_kv_heads, AttnParams p) {
     typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
-    constexpr int CB_SPLITS = U;
     // (m, den, acc[8]) per lane of the helper wavefronts (only U = 16 has helpers)
     __shared__ float xch[U == CB_MAX_SPLITS ? CB_MAX_WAVES : 1][10][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wpt = shape & 255, tiles_per_wg = shape >> 8 & 255, pair = wave * (shape >> 16) >> 8;      // wave / wpt
     constexpr int BLK = WIDE ? 32 : 16, PIECES = AT_D * BLK / 512;          // rows of a block, tile pairs in it
     const int lr = lane % BLK, lg = lane / BLK;
     const int n_blk = R_pad / BLK;                                          // row blocks per (b, g)
-    const int tile = static_cast<int>(blockIdx.x) * tiles_per_wg + wave / wpt;   // over B*Hkv*n_blk*PIECES
-    const int part_i = wave % wpt;                                            // which CB_SPLITS splits
-    const int dp = tile % PIECES;                                             // dims 32 dp .. 32 dp + 31 (WIDE: 16 dp ..)
-    const int bg = (tile / PIECES) / n_blk, blk = (tile / PIECES) - bg * n_blk;       // b * Hkv + g, row block
-    const int b = bg / n_kv_heads, g = bg - b * n_kv_heads;
+    const int tile = static_cast<int>(blockIdx.x) * tiles_per_wg + pair;         // over B*Hkv*n_blk*PIECES
+    const int tile_c = tile < n_tiles ? tile : 0;
+    const int part_i = wave - pair * wpt;                                        // which U splits
+    const int dp = static_cast<unsigned>(tile_c) % PIECES;                                              // dims 32 dp .. 32 dp + 31 (WIDE: 16 dp ..)
+    const int bg = div31(tile_c / PIECES, n_blk_magic), blk = tile_c / PIECES - bg * n_blk;   // b * Hkv + g, row block
     const int r = blk * BLK + lr;
     const bool live = tile < n_tiles && r < R;                              // not a padding row or tile
-    const int ns = n_splits;
-    const int s0 = part_i * CB_SPLITS;
+    const int s0 = part_i * U;
 
+    // the rows of a (b, g), all splits: what lies behind the last one is read as zeros
+    const unsigned rows = tile < n_tiles ? static_cast<unsigned>(n_splits) * R_pad : 0u;
+    const size_t row0 = static_cast<size_t>(bg) * n_splits * R_pad;
+    const auto o_rows = merge_buffer(ws_o + row0 * AT_D, rows * (AT_D * 2)), ml_rows = merge_buffer(ws_ml + row0 * 4, rows * 16);
+    const unsigned ml_at = (s0 * R_pad + r) * 16, o_at = (s0 * R_pad + blk * BLK) * (AT_D * 2) + 1024 * dp + 16 * lane;
+    floatx4 ml[U];
+    uintx4 ov[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if constexpr (WIDE) {
+            ml[u] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(ml_rows, ml_at + u * (R_pad * 16), 0, 0));
+        } else {                                // (the fourth number is not used: a register that is free in front of its load is waited for)
+            const auto x = __builtin_amdgcn_raw_buffer_load_b96(ml_rows, ml_at + u * (R_pad * 16), 0, 0);
+            ml[u] = floatx4{__uint_as_float(x[0]), __uint_as_float(x[1]), __uint_as_float(x[2]), 0.f};
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) ov[u] = __builtin_amdgcn_raw_buffer_load_b128(o_rows, o_at + u * (R_pad * (AT_D * 2)), 0, 0);
+    __builtin_amdgcn_sched_barrier(0);                                      // (all of them in flight: the compiler would save registers)
+    const int b = div24(bg, n_kv_heads), g = bg - b * n_kv_heads;
+    int n = scalar_load(n_nodes, b);                                        // (needed only at the end, like the arguments)
+    asm volatile("" : "+s"(n) : "s"(p.out), "s"(p.K_max), "s"(p.Hq), "s"(p.G), "s"(p.g_magic));
     float m_run = -INFINITY, den = 0.f;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    int n = 0;
-    if (live) {
-        n = n_nodes[b];                                                     // needed only at the end
-        const size_t base = static_cast<size_t>(bg) * ns * R_pad + blk * BLK;    // row index of split 0
-        const float* mlrow = ws_ml + (base + lr) * 4;
-        const size_t ml_stride = static_cast<size_t>(R_pad) * 4;
-        const unsigned short* otile = ws_o + base * AT_D + 512 * dp + 8 * lane;
-        const size_t o_stride = static_cast<size_t>(R_pad) * AT_D;
-        uintx4 ov[CB_SPLITS];
-        floatx4 ml[CB_SPLITS];
 #pragma unroll
-        for (int u = 0; u < CB_SPLITS; ++u) {
-            ov[u] = uintx4{0u, 0u, 0u, 0u};
-            ml[u] = floatx4{-INFINITY, 0.f, 0.f, 0.f};
-            if ((s0 + u) < ns) {                                              // uniform: nothing is read twice
-                ov[u] = *reinterpret_cast<const uintx4*>(otile + (s0 + u) * o_stride);
-                ml[u] = *reinterpret_cast<const floatx4*>(mlrow + (s0 + u) * ml_stride);
-            }
-        }
-        // (picked by value: of two elements of the array the compiler selects the index, and goes through all of it for every split)
-        float scale[CB_SPLITS];
-        if constexpr (WIDE) {
+    for (int u = 0; u < U; ++u) {
+        if (s0 + u >= n_splits) ml[u][0] = -INFINITY;
+        m_run = fmaxf(m_run, ml[u][0]);
+    }
+    float wu[U];
 #pragma unroll
-            for (int u = 0; u < CB_SPLITS; ++u) {
-                const float low = ml[u][2], high = ml[u][3];
-                scale[u] = dp < PIECES / 2 ? low : high;
-            }
-        }
+    for (int u = 0; u < U; ++u) {
+        const float wl = ml[u][0] > -INFINITY ? __builtin_amdgcn_exp2f(ml[u][0] - m_run) * ml[u][1] : 0.f;
+        den += wl;
+        const float low = ml[u][2], high = ml[u][3];                        // (picked by value, not by index)
+        wu[u] = wl * (WIDE && dp >= PIECES / 2 ? high : low);
+    }
 #pragma unroll
-        for (int u = 0; u < CB_SPLITS; ++u)
-            if ((s0 + u) < ns) m_run = fmaxf(m_run, ml[u][0]);
+    for (int u = 0; u < U; ++u) {
+        const halfx8 h = __builtin_bit_cast(halfx8, ov[u]);
 #pragma unroll
-        for (int u = 0; u < CB_SPLITS; ++u) {
-            const bool on = (s0 + u) < ns && ml[u][0] > -INFINITY;
-            const float wl = on ? __builtin_amdgcn_exp2f(ml[u][0] - m_run) * ml[u][1] : 0.f;
-            den += wl;
-            const float wu = wl * (WIDE ? scale[u] : ml[u][2]);
-            const halfx8 h = __builtin_bit_cast(halfx8, ov[u]);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc[e] += wu * static_cast<float>(h[e]);
-        }
+        for (int e = 0; e < 8; ++e) acc[e] += wu[u] * static_cast<float>(h[e]);
     }
     if (U == CB_MAX_SPLITS && wpt > 1) {                                      // uniform over the workgroup
         if (part_i > 0) {
@@ -1065,7 +1071,7 @@ __global__ __launch_bounds__(64 * CB_MAX_WAVES) void tree_attn_combine_kernel(
     unsigned o[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-        o[k] = float_to_bf16_bits(acc[2 * k] * inv) | (float_to_bf16_bits(acc[2 * k + 1] * inv) << 16);
+        o[k] = pack_bf16(acc[2 * k] * inv, acc[2 * k + 1] * inv);
     if (i >= n) o[0] = o[1] = o[2] = o[3] = 0u;   // rows of absent nodes are zeros whatever their Q rows held
     if constexpr (WIDE) {                         // lanes r and r + 32 have dims 4 lg .. +3 and 8 + 4 lg .. +3: eight in a row for either
         const auto x = __builtin_amdgcn_permlane32_swap(o[0], o[2], false, false);
@@ -1442,7 +1448,7 @@ extern "C" int32_t graft_tree_attn(const void* q, const void* k_cache, const voi
     // make the workgroups one round (or, capped, a few whole rounds) over the compute units
     const int64_t n_tiles = static_cast<int64_t>(B) * Hkv * (pl.r_pad / 16) * (AT_D / 32);
     if (n_tiles > (1 << 30)) return GRAFT_ERR_SHAPE;
-    const int cb_u = pl.n_splits > 8 ? 16 : (pl.n_splits > 4 ? 8 : (pl.n_splits > 2 ? 4 : 2));
+    const int cb_u = pl.n_splits > 12 ? 16 : pl.n_splits > 8 ? 12 : (pl.n_splits > 4 ? 8 : (pl.n_splits > 2 ? 4 : 2));
     const int wpt = (pl.n_splits + cb_u - 1) / cb_u;                       // 1 .. 4
     const int64_t cus = device_compute_units();
     int64_t tpw = (n_tiles + cus - 1) / cus;                               // tile pairs per workgroup
@@ -1450,8 +1456,9 @@ extern "C" int32_t graft_tree_attn(const void* q, const void* k_cache, const voi
     tpw = tpw < 1 ? 1 : (tpw > tpw_max ? tpw_max : tpw);
     const dim3 cgrid(static_cast<unsigned>((n_tiles + tpw - 1) / tpw)), cblock(static_cast<unsigned>(64 * tpw * wpt));
     const auto combine = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, cgrid, cblock, 0, s, p.ws_o, p.ws_ml, n_nodes, static_cast<int32_t>(n_tiles), wpt, static_cast<int32_t>(tpw), p.R,
-                           p.R_pad, p.n_splits, Hkv, p);
+        hipLaunchKernelGGL(kernel, cgrid, cblock, 0, s, p.ws_o, p.ws_ml, n_nodes, static_cast<int32_t>(n_tiles),
+                           static_cast<int32_t>(wpt | tpw << 8 | (256 + wpt - 1) / wpt << 16), p.R, p.R_pad, p.n_splits,
+                           magic31(static_cast<uint32_t>(p.R_pad / (pl.wide ? 32 : 16))), Hkv, p);
     };
     const auto merge = [&](auto wide_) {
         constexpr bool WIDE = decltype(wide_)::value;
@@ -1459,6 +1466,7 @@ extern "C" int32_t graft_tree_attn(const void* q, const void* k_cache, const voi
             case 2: combine(tree_attn_combine_kernel<2, WIDE>); break;
             case 4: combine(tree_attn_combine_kernel<4, WIDE>); break;
             case 8: combine(tree_attn_combine_kernel<8, WIDE>); break;
+            case 12: combine(tree_attn_combine_kernel<12, WIDE>); break;
             default: combine(tree_attn_combine_kernel<16, WIDE>); break;
         }
     };
