@@ -17,7 +17,7 @@ OBJ_DIR = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libgraft.so")
 LIB_TIMING = os.path.join(PKG, "libgraft_timing.so")     # the same library with the attention kernel's time stamps
 NATIVE = os.path.join(PKG, "_native.so")                 # tensor marshalling of the Python binding (csrc/binding.cpp)
-SOURCES = ["api.hip", "retrieve.hip", "tree_mask.hip", "tree_attn.hip", "tree_attn_wide.hip", "tree_attn_direct.hip", "tree_attn_parts.hip", "accept.hip", "matrix.hip", "kv_compact.hip", "prune.hip"]
+SOURCES = ["api.hip", "retrieve.hip", "tree_mask.hip", "tree_attn.hip", "tree_attn_wide.hip", "tree_attn_wide_128.hip", "tree_attn_direct.hip", "tree_attn_parts.hip", "accept.hip", "matrix.hip", "kv_compact.hip", "prune.hip"]
 
 # packed-fp32 code generation is switched off for every device compile; VGPR spills must not
 # land in AccVGPRs (the attention kernel manages those by hand).  Kernel arguments: the first 14 words arrive in
@@ -37,7 +37,7 @@ def _hipcc() -> str:
     return "hipcc"
 
 
-HAND_SCHEDULED = ["tree_attn.hip", "tree_attn_wide.hip"]          # their device assembly is kept and checked
+HAND_SCHEDULED = ["tree_attn.hip", "tree_attn_wide.hip", "tree_attn_wide_128.hip"]          # their device assembly is kept and checked
 
 
 def _asm_of(src: str, directory: str = OBJ_DIR) -> str:
@@ -76,12 +76,13 @@ def _reg_span(tok: str):
 
 
 def _managed_accvgprs(symbol: str) -> int:
-    """AccVGPRs that a kernel manages by hand: tree_attn_mfma_kernel<MB> or tree_attn_wide_kernel<NB, MODE>; None for others."""
+    """AccVGPRs that a kernel manages by hand: tree_attn_mfma_kernel<MB>, tree_attn_wide_kernel<NB, MODE> or tree_attn_wide_128_kernel<NB, MODE>;
+    None for others."""
     m = re.match(r"_ZN5graft21tree_attn_mfma_kernelILi(\d+)E", symbol)
     if m:
         mb = int(m.group(1))
         return 48 * mb + 4 * min(mb, 4)
-    m = re.match(r"_ZN5graft21tree_attn_wide_kernelILi(\d+)E", symbol)
+    m = re.match(r"_ZN5graft\d+tree_attn_wide(?:_128)?_kernelILi(\d+)E", symbol)
     return 64 * int(m.group(1)) + 64 if m else None
 
 

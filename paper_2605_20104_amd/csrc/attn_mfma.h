@@ -71,6 +71,7 @@ enum AttnStamp {
 
 // The kernel with 32-row blocks (tree_attn_wide.hip): tiles of 192, 256 or 384 rows.
 int32_t launch_wide(int32_t tile_rows, const AttnParams& p, hipStream_t s);
+int32_t launch_wide_128(const AttnParams& p, hipStream_t s);
 
 struct SplitRange { int st0, st1, P, n, total; };       // stages, prefix length, nodes, tokens
 __device__ __forceinline__ SplitRange split_range(const AttnParams& p, int n_raw, int P_raw, int split, int n_splits, uint32_t splits_magic) {

@@ -1118,8 +1118,8 @@ static thread_local int g_force_splits = 0, g_force_row_tiles = 0;
 // number of splits (<= 64, each with at most AT_MAX_SPLIT_PAGES pages) that make the
 // estimate smallest.  It depends on the capacity max_pages, not on the actual lengths.
 //
-// Which kernel: tiles of 64, 128 and 320 rows have the one with 16-row blocks (per stage about 680 mb + 1100, fixed about 3300 mb + 8000), of
-// 256 and 384 the one with 32-row blocks, of 192 either: its loop is faster, its fixed part (twice the rows a wavefront, a merge
+// Which kernel: tiles of 64 and 320 rows have the one with 16-row blocks (per stage about 680 mb + 1100, fixed about 3300 mb + 8000), of
+// 256 and 384 the one with 32-row blocks, of 128 and 192 either: its loop is faster, its fixed part (twice the rows a wavefront, a merge
 // through LDS) longer.  Tiles of 192 rows, time with 32-row blocks over time with 16-row blocks at the same plan, by stages of a split
 // (of the geometric mean, over 540 plans of 230 drawn shapes): several splits, under 8 stages 1.03, 8 to 10 1.01, 11 to 13 0.98, 14 to 18
 // 0.96, 26 to 40 0.94, above 0.93; one split 1.01, 0.94, 0.95, 0.90, 0.89, 0.86.  Hence the 11 stages.  A sequence with an eighth of the keys its
@@ -1128,6 +1128,11 @@ static thread_local int g_force_splits = 0, g_force_row_tiles = 0;
 // blocks not offered: 16 for 32 stages 58.8 / 54.6, 128 for 257 365 / 367 (a round 380 / 399 us).  In splits of few stages their partial rows,
 // up to two and a half times as many, cost more than the model has: 14 drawn shapes with splits of 5 to 8 stages took 0.97 to 1.18 times
 // (geometric mean 1.07) what they took with the 16-row kernel, and take 0.85 to 0.98 times as long in what they get with the 11 stages asked here too.
+// 128 rows, two to five row tiles, same plan, by stages of a split: 3 stages 1.08, 5 0.99 to 1.01, 8 0.95, 11 0.92 to 0.94, 14 0.89 to 0.92, 20
+// 0.86 to 0.89, 33 0.87, 64 0.81 to 0.93.  One row tile has a stage's keys to itself and is bound by their arrival: 3 to 14 stages 1.00 to
+// 1.08, 20 to 64 0.93 to 1.04, so it keeps the 16-row kernel.  The 129 of 3000 drawn shapes whose plan changes with this tile, a third of them from
+// one of 256 rows and twice the splits: 0.91 times the time with a full table (0.76 .. 1.00), 0.93 with half the keys (0.70 .. 1.10),
+// 0.93 with an eighth (0.62 .. 1.35: the set-up and exchange of 32-row blocks where a split has one stage).
 // The best shape of either kernel is found first; between them the launch that merges splits counts, and the 32-row kernel has to
 // be ahead by the 3 per cent to which the costs are calibrated.  Tiles of 192 rows that need no split against 320 rows in two:
 // 12 stages 24.5 / 31.9 us, 16 29.2 / 35.5 (8 sequences, 80 x 64 heads on 8).
@@ -1135,12 +1140,13 @@ constexpr int WIDE_MIN_STAGES = 11;
 struct TileCost { double stage, fixed; };
 static TileCost tile_cost(int mb, bool wide) {
     if (!wide) return {680.0 * mb + 1100.0, 3300.0 * mb + 8000.0};
+    if (mb == 2) return {2150.0, 14500.0};
     return mb == 3 ? TileCost{2750.0, 19500.0} : (mb == 4 ? TileCost{3650.0, 21000.0} : TileCost{5300.0, 27000.0});
 }
-static bool has_kernel(int mb, bool wide, int splits, int64_t stages_per_split) {
+static bool has_kernel(int mb, bool wide, int row_tiles, int splits, int64_t stages_per_split) {
     if (!wide) return mb <= 3 || mb == 5;
     const bool enough = stages_per_split >= WIDE_MIN_STAGES;
-    return mb == 4 || (mb == 3 && enough) || (mb == 6 && (splits == 1 || enough));
+    return mb == 4 || (mb == 2 && row_tiles > 1 && enough) || (mb == 3 && enough) || (mb == 6 && (splits == 1 || enough));
 }
 static AttnPlan make_plan(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t max_pages) {
     const int R = K_max * (Hq / Hkv);
@@ -1177,7 +1183,7 @@ static AttnPlan make_plan(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int
                 const auto take = [&](Best& best) {
                     if (best.key < 0.0 || key < best.key) best = {key, total, mb, rt, sp};
                 };
-                if (has_kernel(mb, w, sp, per[sp])) take(w ? wide : narrow);
+                if (has_kernel(mb, w, rt, sp, per[sp])) take(w ? wide : narrow);
                 if (!w) take(line);
             }
         }
@@ -1192,11 +1198,11 @@ static AttnPlan make_plan(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int
     if (g_force_splits >= (min_splits < 1 ? 1 : min_splits) && g_force_splits <= (stages < AT_MAX_SPLITS ? stages : AT_MAX_SPLITS) && g_force_row_tiles >= 1) {
         const int mb = (R + g_force_row_tiles * rows_per_mb - 1) / (g_force_row_tiles * rows_per_mb);
         const int64_t stages_of_split = (stages + g_force_splits - 1) / g_force_splits;
-        if (has_kernel(mb, true, g_force_splits, stages_of_split) || has_kernel(mb, false, g_force_splits, stages_of_split)) {
+        if (has_kernel(mb, true, g_force_row_tiles, g_force_splits, stages_of_split) || has_kernel(mb, false, g_force_row_tiles, g_force_splits, stages_of_split)) {
             pl.n_splits = g_force_splits;
             pl.n_row_tiles = g_force_row_tiles;
             pl.mb = mb;
-            pl.wide = has_kernel(mb, true, g_force_splits, stages_of_split);
+            pl.wide = has_kernel(mb, true, g_force_row_tiles, g_force_splits, stages_of_split);
         }
     }
 #endif
@@ -1372,7 +1378,8 @@ extern "C" int32_t graft_attn_plan(int32_t B, int32_t K_max, int32_t Hq, int32_t
 extern "C" const char* graft_attn_kernel_name(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages, int32_t dtype) {
     if (!graft::attn_shape_ok(B, K_max, Hq, Hkv, D, max_pages)) return nullptr;
     const graft::PathChoice& c = graft::choose_path(B, K_max, Hq, Hkv, D, max_pages, dtype);
-    return c.direct ? (c.dir.parts ? "tree_attn_parts_kernel" : "tree_attn_direct_kernel") : (c.mfma.wide ? "tree_attn_wide_kernel" : "tree_attn_mfma_kernel");
+    if (c.direct) return c.dir.parts ? "tree_attn_parts_kernel" : "tree_attn_direct_kernel";
+    return c.mfma.wide ? (c.mfma.mb == 2 ? "tree_attn_wide_128_kernel" : "tree_attn_wide_kernel") : "tree_attn_mfma_kernel";
 }
 // Holds the launch plan of this host thread's following calls (workspace query included) at
 // n_splits splits and n_row_tiles row tiles where the shape allows them; zeros give the plan

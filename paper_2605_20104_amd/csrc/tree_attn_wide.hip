@@ -1,4 +1,5 @@
-// graft_tree_attn, MFMA path with row blocks of 32 (bf16, D = 128): tiles of 192, 256 and 384 rows.
+// graft_tree_attn, MFMA path with row blocks of 32 (bf16, D = 128): tiles of 192, 256 and 384 rows, and of 128 as a kernel of its own
+// (tree_attn_wide_128.hip, which compiles this file once more).
 //
 // The same split-KV scheme as tree_attn_mfma_kernel (tree_attn.hip: 256 threads, one workgroup per compute unit, 64-token
 // stages from memory straight to an LDS ring of four, partial rows for the merge kernel), with another loop.
@@ -33,10 +34,17 @@
 // MFMAs.  The chip lowers its clock with the load (2.38 -> 1.9 GHz on 33 stages, 1.85 -> 1.55 on 257), so the time follows the
 // energy as much as the cycles.  us a call, 16-row kernel -> this one: 8 sequences of 4096 keys, 48 x 64 heads on 4: 56.6 -> 53.3
 // (1024 keys: 25.2 -> 24.0); 4 of 65536, 96 x 32 heads on 8: 408 -> 365 (384 rows); one of 16384: 35.7 -> 33.4; 8 of 16000, 64 x 32
-// heads on 8 (256 rows): 137.1 -> 133.2.  Tried and dropped: 320 rows as two blocks a wavefront and a third for every other
-// sub-tile (62 against 77 thousand cycles for 17 stages, and 65.4 against 63.9 us a round with 32K keys: the clock); 128 rows;
+// heads on 8 (256 rows): 137.1 -> 133.2; 4 of 20440, 40 x 32 heads on 4 (three tiles of 128 rows): 82.7 -> 67.0.  Tried and dropped: 320 rows as two blocks a wavefront and a third for every other
+// sub-tile (62 against 77 thousand cycles for 17 stages, and 65.4 against 63.9 us a round with 32K keys: the clock);
 // row sums through v_dot2_f32_bf16 or 4x4x4 MFMAs (678 and 596 cycles a phase, 530 with additions).
 #include "attn_mfma.h"
+
+// (the body in a function of its own, called by both kernels, cost the others 2.5 per cent: other registers)
+#ifdef GRAFT_WIDE_128
+#define GRAFT_WIDE_KERNEL tree_attn_wide_128_kernel
+#else
+#define GRAFT_WIDE_KERNEL tree_attn_wide_kernel
+#endif
 
 namespace graft {
 
@@ -281,7 +289,7 @@ __device__ __forceinline__ void exact_unit(WideState<S::NB>& w, unsigned k_addr,
 }
 
 template <int NB, int MODE>
-__global__ __launch_bounds__(AT_THREADS) void tree_attn_wide_kernel(GRAFT_ATTN_ARGS) {
+__global__ __launch_bounds__(AT_THREADS) void GRAFT_WIDE_KERNEL(GRAFT_ATTN_ARGS) {
     using S = WideShape<NB, MODE>;
     constexpr int UNITS = S::UNITS;
     __shared__ __attribute__((aligned(1024))) unsigned char kv[AT_NBUF][AT_STAGE_BYTES];
@@ -735,8 +743,16 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_wide_kernel(GRAFT_ATTN_A
     GRAFT_STAMPS_WRITE(p, n_st);
 }
 
+#ifdef GRAFT_WIDE_128
+int32_t launch_wide_128(const AttnParams& p, hipStream_t s) {
+    const dim3 grid(xcd_grid(static_cast<int64_t>(p.B) * p.Hkv * p.n_splits, p.n_row_tiles));
+    launch_attn(tree_attn_wide_128_kernel<2, WIDE_KEYS>, grid, dim3(AT_THREADS), 0, s, p, 1, 1);
+    return check_launch();
+}
+#else
 int32_t launch_wide(int32_t tile_rows, const AttnParams& p, hipStream_t s) {
     const dim3 grid(xcd_grid(static_cast<int64_t>(p.B) * p.Hkv * p.n_splits, p.n_row_tiles));
+    if (tile_rows == 128) return launch_wide_128(p, s);
     switch (tile_rows) {
         case 192: launch_attn(tree_attn_wide_kernel<3, WIDE_KEYS>, grid, dim3(AT_THREADS), 0, s, p, 1, 1); break;
         case 256: launch_attn(tree_attn_wide_kernel<2, WIDE_ROWS>, grid, dim3(AT_THREADS), 0, s, p, 1, 1); break;
@@ -744,5 +760,6 @@ int32_t launch_wide(int32_t tile_rows, const AttnParams& p, hipStream_t s) {
     }
     return check_launch();
 }
+#endif
 
 }  // namespace graft
