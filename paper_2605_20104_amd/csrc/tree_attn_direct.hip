@@ -40,7 +40,7 @@
 
 namespace graft {
 
-constexpr int PARTS_PAGES_128 = 48;              // (at plan_direct)
+constexpr int PARTS_PAGES_128 = 48, PARTS_PAGES_128_RG1 = 30, PARTS_STEPS_128 = 5;              // (at plan_direct)
 // Rows of a row block: 32 where a wavefront has that many and the products come in that size without a loss
 constexpr int row_block_rows(bool bf16, int D, int mb) { return bf16 && D == 64 && mb >= 2 ? 32 : 16; }
 
@@ -903,19 +903,24 @@ DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_
     }
     // fp32 on the fp16 matrix cores (tree_attn_parts.hip): 32 rows and eight key groups a workgroup, tiles of 32 keys.  A step is 3.82 us
     // with D = 128 and 2.22 with D = 64; one that not all wavefronts have takes its share, at least half (their SIMDs are their own).
-    // Tables of fewer than PARTS_PAGES_128 pages stay with fp32 MFMAs for D = 128: tests/test_gpu_attn_direct.py holds the row groups
-    // (2, 4 and 8) of that kernel to sequences of 100 to 733 tokens.  There the rule costs speed: 256 workgroups of 256 keys take 16.3 us
-    // so and 12.2 with parts, of 512 keys 25.7 and 16.0.
-    if (dtype == GRAFT_F32 && (D == 64 || max_pages >= PARTS_PAGES_128)) {
-        const int n_rt = (R + 31) / 32;
-        const int64_t tiles32 = (static_cast<int64_t>(max_pages) + 1) / 2, units = static_cast<int64_t>(B) * Hkv * n_rt;
+    // D = 128 with short tables: us a call with fp32 MFMAs / with parts.  Of PARTS_STEPS_128 steps a compute unit or more, 16 x 443 tokens, 1936 rows,
+    // 74.7 / 43.0, 30 of 438 x 676 68.7 / 41.6, 56 of 240 x 645 76.2 / 55.7, 128 of 200 x 1600 328 / 263.  Of fewer, with one row group in the fp32 plan: from
+    // PARTS_PAGES_128_RG1 pages on 12.0 / 10.7 (572 tokens, 630 rows), 24.2 / 14.7 (346, 1694), 23.8 / 14.6 (395, 896); of 25 to 27 pages
+    // 12.7 / 13.4, 13.0 / 13.5.  With several row groups they stay with fp32 MFMAs: tests/test_gpu_attn_direct.py holds the row groups (2, 4
+    // and 8) of that kernel to such shapes, which costs speed there: 256 workgroups of 256 keys take 16.3 us so and 12.2 with parts.
+    const int n_rt32 = (R + 31) / 32;
+    const int64_t tiles32 = (static_cast<int64_t>(max_pages) + 1) / 2, units32 = static_cast<int64_t>(B) * Hkv * n_rt32;
+    const bool parts_128 = max_pages >= PARTS_PAGES_128 || (best.rg == 1 && max_pages >= PARTS_PAGES_128_RG1) ||
+                           units32 * tiles32 >= PARTS_STEPS_128 * DR_WAVES * cus;
+    if (dtype == GRAFT_F32 && (D == 64 || parts_128)) {
         const double c_step = D == 64 ? 4750.0 : 8150.0, c_fixed = D == 64 ? 12000.0 : 14500.0;
+        const double ahead = D == 64 || max_pages >= PARTS_PAGES_128 ? 1.0 : 0.95;      // (16 of 523 tokens x 1590 rows, 1 per cent ahead by these costs: 48.4 / 49.1)
         for (int sp = 1; sp <= (may_split ? DR_MAX_SPLITS : 1); ++sp) {
-            const int64_t per = (tiles32 + sp - 1) / sp, rounds = (units * sp + cus - 1) / cus, over = per % DR_WAVES;
+            const int64_t per = (tiles32 + sp - 1) / sp, rounds = (units32 * sp + cus - 1) / cus, over = per % DR_WAVES;
             const double steps = static_cast<double>(per / DR_WAVES) + (over ? std::max(0.5, over / static_cast<double>(DR_WAVES)) : 0.0);
             const double cost = rounds * (c_fixed + steps * c_step) + merge_cost(sp);
-            if (cost < best.cost) best = {2, 1, n_rt, sp, 0, 0, 0, cost, true};
-            if (units * sp > 4 * cus || per <= DR_WAVES / 2) break;
+            if (cost < (best.parts ? 1.0 : ahead) * best.cost) best = {2, 1, n_rt32, sp, 0, 0, 0, cost, true};
+            if (units32 * sp > 4 * cus || per <= DR_WAVES / 2) break;
         }
     }
     best.r_pad = best.n_row_tiles * best.rg * best.mb * 16;
