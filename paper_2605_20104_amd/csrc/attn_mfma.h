@@ -69,7 +69,7 @@ enum AttnStamp {
 #define GRAFT_STAMPS_WRITE(p, n_stages) ((void)0)
 #endif
 
-// The kernel with 32-row blocks (tree_attn_wide.hip): tiles of 192, 256 or 384 rows.
+// The kernel with 32-row blocks (tree_attn_wide.hip): tiles of 128, 192, 256 or 384 rows.
 int32_t launch_wide(int32_t tile_rows, const AttnParams& p, hipStream_t s);
 int32_t launch_wide_128(const AttnParams& p, hipStream_t s);
 
