@@ -10,8 +10,8 @@
 //   range : fp16 ends at 2^16 and loses bits below 2^-14, so numbers are taken times powers of two (exact).  Queries: a row's largest is
 //           brought to 2^8.  Keys: as they are if one of the tile is 2 or more (what is lost below 2^-25 then moves a score by less
 //           than fp32 sums do), else the tile's largest to 2^8.  Values: every dim has its own factor, which brings the largest of
-//           the wavefront's first tile to 2^4: a dim of small values keeps its bits beside one of large ones, and there is room for
-//           2^11 times as much.  Probabilities: a row's reference lies 2^8 below its largest exponent, and is raised
+//           the wavefront's first tile to 2^8: a dim of small values keeps its bits beside one of large ones, values down to 2^-10 of
+//           that one keep all of theirs, and there is room for 2^7 times as much.  Probabilities: a row's reference lies 2^8 below its largest exponent, and is raised
 //           when one passes 2^15.5.
 //   beyond: what does not fit (keys past 65504, values past the room above, infinities, NaN) makes sums infinite or NaN.  Such a
 //           wavefront takes its tiles once more with v_mfma_f32_32x32x2_f32 on the same registers, and keys with values that are
@@ -36,7 +36,7 @@ namespace graft {
 
 constexpr int PT_TK = 32;                       // keys of a tile
 constexpr int PT_ROWS = 32;                     // query rows of a workgroup
-constexpr int PT_TOP = 8, PT_TOP_V = 4;          // largest magnitudes are brought to 2^8 .. 2^9, of the first values to 2^4 .. 2^5
+constexpr int PT_TOP = 8;                       // largest magnitudes are brought to 2^8 .. 2^9, values by the first tile's
 constexpr float PT_LAZY_LOG2 = 15.5f;           // a row keeps its reference while exponents stay below it (fp16 ends at 2^16)
 
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
@@ -77,11 +77,11 @@ __device__ __forceinline__ unsigned or_bits(unsigned acc, const half8_t& h) {
 __device__ __forceinline__ floatx16 mfma_f16(const half8_t& a, const half8_t& b, const floatx16& c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
 }
-// The power of two that takes a largest magnitude to 2^TOP .. 2^(TOP + 1); 2^TOP for zero and for what is not finite.
-template <int TOP = PT_TOP> __device__ __forceinline__ int scale_exponent(float largest) {
+// The power of two that takes a largest magnitude to 2^PT_TOP .. 2^(PT_TOP + 1); 2^PT_TOP for zero and for what is not finite.
+__device__ __forceinline__ int scale_exponent(float largest) {
     const int e = static_cast<int>((__float_as_uint(largest) >> 23) & 0xffu);
-    const int s = TOP - (e - 127);
-    return e == 0 || e == 255 ? TOP : (s > 100 ? 100 : (s < -100 ? -100 : s));
+    const int s = PT_TOP - (e - 127);
+    return e == 0 || e == 255 ? PT_TOP : (s > 100 ? 100 : (s < -100 ? -100 : s));
 }
 __device__ __forceinline__ float pow2(int e) { return __uint_as_float(static_cast<unsigned>(e + 127) << 23); }
 
@@ -431,7 +431,7 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_parts_kernel(GRAFT_AT
                     float t = 0.f;
 #pragma unroll
                     for (int v = 0; v < 16; ++v) t = __builtin_fmaxf(t, __builtin_fabsf(vt[v][j]));
-                    v_scale[j] = pow2(scale_exponent<PT_TOP_V>(row_max<32>(t)));
+                    v_scale[j] = pow2(scale_exponent(row_max<32>(t)));
                 }
             }
             const auto values = [&](int kk, int j) __attribute__((always_inline)) {

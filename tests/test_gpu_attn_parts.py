@@ -137,3 +137,24 @@ def test_keys_that_are_not_finite(D):
     none[at(30)] = -1e30
     got, want = run(w, dict(att, k_cache=[bad]), parent, n, p), run(w, dict(att, k_cache=[none]), parent, n, p)
     assert np.isfinite(got).all() and np.abs(got - want).max() <= 2e-5
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_small_values_behind_large_ones(D):
+    """Rows that see one token whose values are 2^-9 of all others'.  A factor takes the largest of 32 values, below 2^9 * 2^2.5, to 2^8 at least, so a
+    value is off by at most 2^-25 * 2^3.5, a third of that squared on average (2e-7), beside 2^-23 of itself and the sums' roundings."""
+    w, att, parent, rng = setup(1, 40, 32, 8, D, 1500)
+    n, p, t = np.array([40], np.int32), np.array([1500], np.int32), 300
+    q, k, v = (np.array(att[x][0]) for x in ("q", "k_cache", "v_cache"))
+    q[:] = q[0, 0, 0]
+    page = att["block_table"][0, t // 16]
+    k[page, :, t % 16] = q[0, 0, 0] * np.float32(60 / (att["scale"] * (q[0, 0, 0].astype(np.float64) ** 2).sum()))
+    small = v[page, :, t % 16].copy()
+    v *= np.float32(512)
+    v[page, :, t % 16] = small
+    att = dict(att, q=[q], k_cache=[k], v_cache=[v])
+    got = run(w, att, parent, n, p)
+    ref, _ = reference(w, att, parent, n, p)
+    rel = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    print("relative error %.2e" % rel)
+    assert rel <= 5e-7
