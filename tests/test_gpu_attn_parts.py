@@ -55,6 +55,8 @@ CASES = [
     (128, 1, 128, 32, 2, 900, "head_major", 0, True), (128, 1, 40, 32, 8, 8500, "head_major", 0, False), (128, 2, 33, 64, 4, 5000, "head_major", 0, True),
     (64, 1, 40, 32, 8, 2047, "head_major", 0, True), (64, 2, 61, 16, 4, 5000, "token_major", 0, True), (64, 4, 64, 32, 8, 33, "head_major", 96, True),
     (64, 1, 33, 16, 2, 9000, "head_major", 0, False),
+    # a last tile of one token, taken first, whose missing keys borrow the values of the next one
+    (128, 1, 40, 32, 8, 2009, "head_major", 0, False), (64, 2, 33, 16, 2, 4064, "token_major", 0, False), (128, 5, 126, 18, 2, 611, "head_major", 0, True),
     # tables of fewer than 48 pages with D = 128: 30 pages and one row group of the other kernel's, five steps a compute unit
     (128, 1, 121, 56, 4, 346, "head_major", 0, True), (128, 1, 70, 20, 2, 581, "token_major", 0, True), (128, 15, 52, 26, 2, 438, "head_major", 0, True),
     (128, 14, 43, 60, 4, 240, "token_major", 0, False),
