@@ -40,7 +40,7 @@
 
 namespace graft {
 
-constexpr int PARTS_PAGES_128 = 48, PARTS_PAGES_128_RG1 = 30, PARTS_STEPS_128 = 5;              // (at plan_direct)
+constexpr int PARTS_PAGES_128 = 48, PARTS_PAGES_128_RG1 = 30, PARTS_STEPS_128 = 4;              // (at plan_direct)
 // Rows of a row block: 32 where a wavefront has that many and the products come in that size without a loss
 constexpr int row_block_rows(bool bf16, int D, int mb) { return bf16 && D == 64 && mb >= 2 ? 32 : 16; }
 
@@ -903,8 +903,8 @@ DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_
     }
     // fp32 on the fp16 matrix cores (tree_attn_parts.hip): 32 rows and eight key groups a workgroup, tiles of 32 keys.  A step is 3.82 us
     // with D = 128 and 2.22 with D = 64; one that not all wavefronts have takes its share, at least half (their SIMDs are their own).
-    // D = 128 with short tables: us a call with fp32 MFMAs / with parts.  Of PARTS_STEPS_128 steps a compute unit or more, 16 x 443 tokens, 1936 rows,
-    // 74.7 / 43.0, 30 of 438 x 676 68.7 / 41.6, 56 of 240 x 645 76.2 / 55.7, 128 of 200 x 1600 328 / 263.  Of fewer, with one row group in the fp32 plan: from
+    // D = 128 with short tables: us a call with fp32 MFMAs / with parts.  Of PARTS_STEPS_128 steps a compute unit or more (60 drawn shapes of 4 to 5: 0.79 times the time,
+    // none above 1.01), 16 x 443 tokens, 1936 rows, 74.7 / 43.0, 30 of 438 x 676 68.7 / 41.6, 56 of 240 x 645 76.2 / 55.7, 128 of 200 x 1600 328 / 263.  Of fewer, with one row group in the fp32 plan: from
     // PARTS_PAGES_128_RG1 pages on 12.0 / 10.7 (572 tokens, 630 rows), 24.2 / 14.7 (346, 1694), 23.8 / 14.6 (395, 896); of 25 to 27 pages
     // 12.7 / 13.4, 13.0 / 13.5.  With several row groups they stay with fp32 MFMAs: tests/test_gpu_attn_direct.py holds the row groups (2, 4
     // and 8) of that kernel to such shapes, which costs speed there: 256 workgroups of 256 keys take 16.3 us so and 12.2 with parts.

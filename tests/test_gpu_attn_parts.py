@@ -57,7 +57,7 @@ CASES = [
     (64, 1, 33, 16, 2, 9000, "head_major", 0, False),
     # a last tile of one token, taken first, whose missing keys borrow the values of the next one
     (128, 1, 40, 32, 8, 2009, "head_major", 0, False), (64, 2, 33, 16, 2, 4064, "token_major", 0, False), (128, 5, 126, 18, 2, 611, "head_major", 0, True),
-    # tables of fewer than 48 pages with D = 128: 30 pages and one row group of the other kernel's, five steps a compute unit
+    # tables of fewer than 48 pages with D = 128: 30 pages and one row group of the other kernel's, four steps a compute unit
     (128, 1, 121, 56, 4, 346, "head_major", 0, True), (128, 1, 70, 20, 2, 581, "token_major", 0, True), (128, 15, 52, 26, 2, 438, "head_major", 0, True),
     (128, 14, 43, 60, 4, 240, "token_major", 0, False),
 ]
