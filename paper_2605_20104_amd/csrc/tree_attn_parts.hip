@@ -232,20 +232,19 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_parts_kernel(GRAFT_AT
             transfer(kc + page_base(it, j * RPI / 16), row_off(it, j * RPI / 16, j * RPI % 16 + x / CPR) + key_chunk(x, j), j);
         // A wavefront's first tile gives the dims their factors.  Where it reaches past the end, its missing keys have the values of the
         // next tile's: those of a single last token can be any amount smaller than what follows (one such dim, and the tiles are taken
-        // again: 5 sequences of 737 tokens, 1134 rows on 2 heads, 72 us so, 38 now).
-        if (it == 0 && count > 1 && (tile_at(0) + 1) * PT_TK > total) {
+        // again: 5 sequences of 737 tokens, 1134 rows on 2 heads, 72 us so, 36 now).
+        const bool borrow = it == 0 && count > 1 && (tile_at(0) + 1) * PT_TK > total;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int k = 8 * (v >> 2 & 1) + 4 * (x >> 5) + (v & 3);
-                const int64_t page = tile_at(0) * PT_TK + 16 * (v >> 3) + k <= last ? page_base(0, v >> 3) : page_base(1, v >> 3);
-                vt[v] = *reinterpret_cast<const floatj*>(vc + page + (static_cast<unsigned>(k) * ts + (x & 31) * (NJ * 4)));
+        for (int pg = 0; pg < 2; ++pg) {
+            const int64_t own = page_base(it, pg), other = borrow ? page_base(1, pg) : own;
+            const int lim = last - (tile_at(it) * PT_TK + 16 * pg), lim_own = tile_at(it) * PT_TK + 16 * pg <= last ? lim : last & 15;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int k = 8 * (u >> 2) + 4 * (x >> 5) + (u & 3);
+                const unsigned row = static_cast<unsigned>(borrow || k < lim_own ? k : lim_own) * ts;
+                vt[8 * pg + u] = *reinterpret_cast<const floatj*>(vc + (k <= lim ? own : other) + (row + (x & 31) * (NJ * 4)));
             }
-            return;
         }
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-            vt[v] = *reinterpret_cast<const floatj*>(vc + page_base(it, v >> 3) +
-                                                     (row_off(it, v >> 3, 8 * (v >> 2 & 1) + 4 * (x >> 5) + (v & 3)) + (x & 31) * (NJ * 4)));
     };
     const float sc = p.scale_log2e;
     if (count > 0) load_clamped(0);
