@@ -174,11 +174,12 @@ int32_t graft_build_tree_mask(const int32_t* parent, const int32_t* n_nodes, con
  *                             reaches nodes that do not see its slot, as 0 * inf; and values
  *                             past 2^100 may overflow.
  * scale                       softmax scale, normally 1/sqrt(D)
- * dtype                       GRAFT_F32: fp32 storage, softmax and sums; where sequences are
- *                             long or launches large, factors enter a product as the sum of
- *                             two fp16 numbers times a power of two (23 bits; results lie
- *                             closer to a 64-bit reference than with fp32 products).  Keys
- *                             and values that such sums cannot hold take fp32 products.
+ * dtype                       GRAFT_F32: fp32 storage, softmax and sums.  Where sequences are long or
+ *                             launches large, products are made of 16-bit ones: queries and
+ *                             keys enter them as the sum of two fp16 numbers times a power of
+ *                             two (23 bits), probabilities and values as three bf16 numbers
+ *                             whose sum they are; up to 2^-22 of a product is left out.  Queries
+ *                             and keys past fp16's largest number take fp32 products.
  *                             GRAFT_BF16: bf16 storage, fp32 scores/softmax/accumulation,
  *                             probabilities rounded to bf16 for the P.V product (D = 128
  *                             only: D = 64 keeps them whole); where, with D = 128, the

@@ -77,7 +77,7 @@ struct DirectPlan {
     int mb, rg, n_row_tiles, n_splits, r_pad;
     size_t ws_o_bytes, ws_bytes;
     double cost;        // estimated cycles
-    bool parts;         // fp32 on the fp16 matrix cores (tree_attn_parts.hip)
+    bool parts;         // fp32 on the 16-bit matrix cores (tree_attn_parts.hip)
 };
 DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_t D, int32_t max_pages, int32_t dtype,
                        bool may_split);

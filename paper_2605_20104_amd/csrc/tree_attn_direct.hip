@@ -901,20 +901,23 @@ DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_
             }
         }
     }
-    // fp32 on the fp16 matrix cores (tree_attn_parts.hip): 32 rows and eight key groups a workgroup, tiles of 32 keys.  A step is 3.82 us
-    // with D = 128 and 2.22 with D = 64; one that not all wavefronts have takes its share, at least half (their SIMDs are their own).
-    // D = 128 with short tables: us a call with fp32 MFMAs / with parts.  Of PARTS_STEPS_128 steps a compute unit or more (60 drawn shapes of 4 to 5: 0.79 times the time,
-    // none above 1.01), 16 x 443 tokens, 1936 rows, 74.7 / 43.0, 30 of 438 x 676 68.7 / 41.6, 56 of 240 x 645 76.2 / 55.7, 128 of 200 x 1600 328 / 263.  Of fewer, with one row group in the fp32 plan: from
-    // PARTS_PAGES_128_RG1 pages on 12.0 / 10.7 (572 tokens, 630 rows), 24.2 / 14.7 (346, 1694), 23.8 / 14.6 (395, 896); of 25 to 27 pages
-    // 12.7 / 13.4, 13.0 / 13.5.  With several row groups they stay with fp32 MFMAs: tests/test_gpu_attn_direct.py holds the row groups (2, 4
-    // and 8) of that kernel to such shapes, which costs speed there: 256 workgroups of 256 keys take 16.3 us so and 12.2 with parts.
+    // fp32 on the 16-bit matrix cores (tree_attn_parts.hip): 32 rows and eight key groups a workgroup, tiles of 32 keys.  A step is 5.05 us
+    // with D = 128 and 2.95 with D = 64; one that not all wavefronts have takes its share, at least half (their SIMDs are their own).  At the
+    // fp32 costs' 2133 a us that is 10800 and 6250, but those plans take longer than their costs by as much: 110 drawn shapes of 4 to 40
+    // steps a compute unit take 0.828 of the time with fp32 products where the choice is made with 8150, 0.828 with 8800, 0.836 with 9500
+    // and 0.849 with 10800; 40 with D = 64 0.827, 0.828, 0.825, 0.827.
+    // D = 128 with short tables: us a call with fp32 MFMAs / with parts.  Of PARTS_STEPS_128 steps a compute unit or more, 10 x 564 tokens, 1936
+    // rows, 74.2 / 52.0, 30 of 490 x 676 69.0 / 46.3, 56 of 283 x 645 76.5 / 57.2, 28 of 669 x 1176 150 / 94.  Of fewer, with one row group in the
+    // fp32 plan: from PARTS_PAGES_128_RG1 pages on 24.2 / 16.1 (467 tokens, 1694 rows on 4 heads); of 26 pages 12.6 / 14.5 (410, 630 on 2) and
+    // 13.7 / 15.4 (414, 896 on 4).  With several row groups they stay with fp32 MFMAs: tests/test_gpu_attn_direct.py holds the row groups (2, 4
+    // and 8) of that kernel to such shapes, which costs speed there: 256 workgroups of 256 keys take 15.5 us so and 11.9 with parts.
     const int n_rt32 = (R + 31) / 32;
     const int64_t tiles32 = (static_cast<int64_t>(max_pages) + 1) / 2, units32 = static_cast<int64_t>(B) * Hkv * n_rt32;
     const bool parts_128 = max_pages >= PARTS_PAGES_128 || (best.rg == 1 && max_pages >= PARTS_PAGES_128_RG1) ||
                            units32 * tiles32 >= PARTS_STEPS_128 * DR_WAVES * cus;
     if (dtype == GRAFT_F32 && (D == 64 || parts_128)) {
         const double c_step = D == 64 ? 4750.0 : 8150.0, c_fixed = D == 64 ? 12000.0 : 14500.0;
-        const double ahead = D == 64 || max_pages >= PARTS_PAGES_128 ? 1.0 : 0.95;      // (16 of 523 tokens x 1590 rows, 1 per cent ahead by these costs: 48.4 / 49.1)
+        const double ahead = D == 64 || max_pages >= PARTS_PAGES_128 ? 1.0 : 0.95;      // (a step or two a compute unit: the costs are no better than that)
         for (int sp = 1; sp <= (may_split ? DR_MAX_SPLITS : 1); ++sp) {
             const int64_t per = (tiles32 + sp - 1) / sp, rounds = (units32 * sp + cus - 1) / cus, over = per % DR_WAVES;
             const double steps = static_cast<double>(per / DR_WAVES) + (over ? std::max(0.5, over / static_cast<double>(DR_WAVES)) : 0.0);

@@ -1,21 +1,21 @@
-// graft_tree_attn, direct path: fp32 storage with the products on the fp16 matrix cores.
+// graft_tree_attn, direct path: fp32 storage with the products on the 16-bit matrix cores.
 //
 // The shape is that of tree_attn_direct_kernel with two row blocks and one row group: a workgroup has 32 query rows, its eight
 // wavefronts take every eighth tile of 32 keys each, without a barrier, and merge through LDS at the end.
-//   why   : v_mfma_f32_16x16x4_f32 binds that kernel (8192 of a step's 8200 cycles), at a sixteenth of the fp16 rate.  Here a number
-//           is the sum of two fp16 numbers, h the nearest one and m the nearest one to what h leaves: 23 bits.  A product is
-//           h h + h m + m h (m m is below 2^-24 of it), each of them exact and their sums fp32, in 24 roundings a score where four
-//           numbers at a time took 32.  Mean relative error against 64 bits over eleven shapes of 256 to 16384 tokens 4.8e-7 -> 3.3e-7,
-//           smaller in every one.
-//   range : fp16 ends at 2^16 and loses bits below 2^-14, so numbers are taken times powers of two (exact).  Queries: a row's largest is
-//           brought to 2^8.  Keys: as they are if one of the tile is 2 or more (what is lost below 2^-25 then moves a score by less
-//           than fp32 sums do), else the tile's largest to 2^8.  Values: every dim has its own factor, which brings the largest of
-//           the wavefront's first tile to 2^8: a dim of small values keeps its bits beside one of large ones, values down to 2^-10 of
-//           that one keep all of theirs, and there is room for 2^7 times as much.  Probabilities: a row's reference lies 2^8 below its largest exponent, and is raised
-//           when one passes 2^15.5.
-//   beyond: what does not fit (keys past 65504, values past the room above, infinities, NaN) makes sums infinite or NaN.  Such a
-//           wavefront takes its tiles once more with v_mfma_f32_32x32x2_f32 on the same registers, and keys with values that are
-//           not finite kept out of the product.
+//   why   : v_mfma_f32_16x16x4_f32 binds that kernel (8192 of a step's 8200 cycles), at a sixteenth of the 16-bit rate.  Here a number is
+//           the sum of 16-bit ones, and a product the sum of theirs: each of them exact, their sums fp32.  Mean relative error against 64
+//           bits over seven shapes of 200 to 700 tokens 4.2e-7 with fp32 products, 2.7e-7 so, smaller in every one.
+//   S     : queries and keys are two fp16 numbers, h the nearest one and m the nearest one to what h leaves: 23 bits.  A product is h h +
+//           h m + m h (m m is below 2^-24 of it), 24 roundings a score where four numbers at a time took 32.  fp16 ends at 2^16 and
+//           loses bits below 2^-14, so numbers are taken times powers of two (exact): a row's largest query is brought to 2^8, and
+//           the keys of a tile are taken as they are if one of them is 2 or more, else with the largest at 2^8.
+//   O     : probabilities and values are three bf16 numbers whose sum they are, eight bits each, and a product six of the nine (the rest is
+//           below 2^-23 of it): the exponents are those of fp32, so there is nothing to scale and nothing to lose, whatever the
+//           values of a dim have been before and whatever other rows see.  (Two fp16 numbers with a factor a dim from the wavefront's
+//           first tile: 4.0 us a step, and wrong results behind values of another size, by 7e-3 and without end.)
+//   beyond: what fp16 does not hold (keys past 65504, infinities, NaN) makes sums infinite or NaN.  Such a wavefront takes its
+//           tiles once more with v_mfma_f32_32x32x2_f32 on the same registers, and keys with values that are not finite kept out
+//           of the product.
 //   K     : straight from memory to a wavefront-private piece of LDS, 16-byte chunks XOR-swizzled with the row; a lane reads
 //           8 dims of its key and splits them as it goes.
 //   V     : straight to registers.  Lane (half, l32) holds keys 8 (v / 4) + 4 half + v % 4, v < 16, in D / 32 dims from l32 D / 32
@@ -24,21 +24,22 @@
 //   order : the products of a step and the split of the next one's numbers take turns (sched_group_barrier): without, the wavefront
 //           waits for LDS and the matrix cores in turn (bf16 parts, three a number, 6.3 us a step without and 6.0 with).
 //
-// Measured (MI355X).  A step, 256 keys of a row tile, 256 workgroups whose keys come from the caches: D = 128 7.69 -> 3.82 us, D = 64
-// 4.71 -> 2.22.  us a call, before / now: 1 sequence of 2048 keys, 40 x 32 heads on 8, 22.4 / 17.8; 8192, 64 x 40 on 8, 96.7 / 55.5; 4 of
-// 1024, 40 x 32 on 8, 41.0 / 22.0; D = 64, 2 of 5000, 60 x 16 on 4, 31.1 / 20.9.  What is left: vector instructions 63 % of the cycles
-// (split 4 of 7 of them), matrix cores 32 %; without a step's transfers it takes 3.3 us instead of 4.1.
-// Tried and dropped: three bf16 parts a number and six products (any range, no factors; 5.96 us a step); the fp16 split by
-// v_fma_mixlo_f16 and its high half (two instructions a number with the factor, but at half the rate: 4.16 us).
+// Measured (MI355X), fp32 products / this kernel.  A step, 256 keys of a row tile, 256 workgroups whose keys come from the caches: D = 128
+// 7.69 / 5.05 us, D = 64 4.66 / 2.95.  us a call: 1 sequence of 2048 keys, 40 x 32 heads on 8, 22.6 / 18.1; 8192, 64 x 40 on 8, 96.8 / 65.5; 4 of
+// 1024, 40 x 32 on 8, 41.3 / 25.4; D = 64, 2 of 5000, 60 x 16 on 4, 31.9 / 22.5.  Keys of 0.05, which are scaled: 22.0 / 20.1, 96.5 / 71.8,
+// 41.4 / 29.9, 30.7 / 25.2.
+// Tried and dropped: three bf16 numbers for queries and keys too (20.2 us instead of 18.1, 78.2 instead of 65.5); the bf16 split by
+// v_dot2_f32_bf16, three and a half instructions a number instead of five and a half but at a lower rate (19.4, 72); the fp16 split by
+// v_fma_mixlo_f16 and its high half (two instructions a number with the factor, but at half the rate).
 #include "attn_direct.h"
 
 namespace graft {
 
 constexpr int PT_TK = 32;                       // keys of a tile
 constexpr int PT_ROWS = 32;                     // query rows of a workgroup
-constexpr int PT_TOP = 8;                       // largest magnitudes are brought to 2^8 .. 2^9, values by the first tile's
-constexpr float PT_LAZY_LOG2 = 15.5f;           // a row keeps its reference while exponents stay below it (fp16 ends at 2^16)
+constexpr int PT_TOP = 8;                       // largest queries of a row, and keys of a tile that is scaled, are brought to 2^8 .. 2^9
 
+typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 
@@ -74,8 +75,40 @@ __device__ __forceinline__ unsigned or_bits(unsigned acc, const half8_t& h) {
     const uintx4 u = __builtin_bit_cast(uintx4, h);
     return (acc | u[0] | u[1]) | u[2] | u[3];
 }
+// Eight numbers of a lane as three bf16 operands, whose sum they are: eight bits of a number, eight of what they leave, and what those
+// leave.  (Infinities leave NaN.)  NEAREST: rounded, not cut off, which makes what a product leaves out a quarter and of either sign, but
+// takes v_cvt_pk_bf16_f32 where a v_perm_b32 does.
+struct Thirds { bf8_t h, m, l; };
+template <bool NEAREST> __device__ __forceinline__ Thirds split_exactly(const float (&x)[8]) {
+    uintx4 h, m, l;
+    const auto upper = [](unsigned v) __attribute__((always_inline)) { return __uint_as_float(v & 0xffff0000u); };
+    const auto uppers = [](float a, float b) __attribute__((always_inline)) {
+        return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+    };
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float a = x[2 * j], b = x[2 * j + 1];
+        float a1, b1, a2, b2;
+        if constexpr (NEAREST) {
+            h[j] = pack_bf16(a, b);
+            a1 = a - __uint_as_float(h[j] << 16), b1 = b - upper(h[j]);
+            m[j] = pack_bf16(a1, b1);
+            a2 = a1 - __uint_as_float(m[j] << 16), b2 = b1 - upper(m[j]);
+        } else {
+            h[j] = uppers(a, b);
+            a1 = a - upper(__float_as_uint(a)), b1 = b - upper(__float_as_uint(b));
+            m[j] = uppers(a1, b1);
+            a2 = a1 - upper(__float_as_uint(a1)), b2 = b1 - upper(__float_as_uint(b1));
+        }
+        l[j] = uppers(a2, b2);
+    }
+    return Thirds{__builtin_bit_cast(bf8_t, h), __builtin_bit_cast(bf8_t, m), __builtin_bit_cast(bf8_t, l)};
+}
 __device__ __forceinline__ floatx16 mfma_f16(const half8_t& a, const half8_t& b, const floatx16& c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ floatx16 mfma_bf16(const bf8_t& a, const bf8_t& b, const floatx16& c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 // The power of two that takes a largest magnitude to 2^PT_TOP .. 2^(PT_TOP + 1); 2^PT_TOP for zero and for what is not finite.
 __device__ __forceinline__ int scale_exponent(float largest) {
@@ -154,13 +187,10 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_parts_kernel(GRAFT_AT
 
     float m, l;
     int k_exp = 0;                               // keys of a tile are taken times 2 to this,
-    float v_scale[NJ];                           // the values of a lane's dims times these powers of two
     floatx16 o[NJ];                              // o[j][u]: dim NJ (8 (u / 4) + 4 half + u % 4) + j of row l32
     auto clear_rows = [&]() __attribute__((always_inline)) {
         m = -INFINITY;
         l = 0.f;
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) v_scale[j] = 1.f;
 #pragma unroll
         for (int j = 0; j < NJ; ++j) o[j] = floatx16{};
     };
@@ -230,25 +260,14 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_parts_kernel(GRAFT_AT
 #pragma unroll
         for (int j = 0; j < NK; ++j)
             transfer(kc + page_base(it, j * RPI / 16), row_off(it, j * RPI / 16, j * RPI % 16 + x / CPR) + key_chunk(x, j), j);
-        // A wavefront's first tile gives the dims their factors.  Where it reaches past the end, its missing keys have the values of the
-        // next tile's: those of a single last token can be any amount smaller than what follows (one such dim, and the tiles are taken
-        // again: 5 sequences of 737 tokens, 1134 rows on 2 heads, 72 us so, 36 now).
-        const bool borrow = it == 0 && count > 1 && (tile_at(0) + 1) * PT_TK > total;
 #pragma unroll
-        for (int pg = 0; pg < 2; ++pg) {
-            const int64_t own = page_base(it, pg), other = borrow ? page_base(1, pg) : own;
-            const int lim = last - (tile_at(it) * PT_TK + 16 * pg), lim_own = tile_at(it) * PT_TK + 16 * pg <= last ? lim : last & 15;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int k = 8 * (u >> 2) + 4 * (x >> 5) + (u & 3);
-                const unsigned row = static_cast<unsigned>(borrow || k < lim_own ? k : lim_own) * ts;
-                vt[8 * pg + u] = *reinterpret_cast<const floatj*>(vc + (k <= lim ? own : other) + (row + (x & 31) * (NJ * 4)));
-            }
-        }
+        for (int v = 0; v < 16; ++v)
+            vt[v] = *reinterpret_cast<const floatj*>(vc + page_base(it, v >> 3) +
+                (row_off(it, v >> 3, 8 * (v >> 2 & 1) + 4 * (x >> 5) + (v & 3)) + (x & 31) * (NJ * 4)));
     };
     const float sc = p.scale_log2e;
     if (count > 0) load_clamped(0);
-    // queries and masks to LDS (behind the first keys' request)
+    // queries and masks to LDS
     if (tid < p.K_max * 4) reinterpret_cast<unsigned*>(lds)[tid] = mask_word;
     // (a row's largest query: every wavefront has its step's)
     float* const q_top = reinterpret_cast<float*>(Ks0 + DR_WAVES * KEYS_BYTES);
@@ -383,8 +402,8 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_parts_kernel(GRAFT_AT
         const float f = careful ? sc : s_scale;
         mx *= f;
         // (rare) a row without a reference, or one that outgrew it: raise it to the maximum seen
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(mx > m + (careful ? 0.f : PT_LAZY_LOG2)) != 0, 0)) {
-            const float mn = fmaxf(m, row_max<32>(mx) - (careful ? 0.f : static_cast<float>(PT_TOP)));
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(mx > m + (careful ? 0.f : DR_LAZY_LOG2)) != 0, 0)) {
+            const float mn = fmaxf(m, row_max<32>(mx));
             const float a = mn == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m - mn);
             m = mn;
             l *= a;
@@ -435,40 +454,34 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_parts_kernel(GRAFT_AT
                 float x[8];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) x[i] = s[8 * kk + i];
-                return split8(x);
+                return split_exactly<true>(x);
             };
-            if (it == 0) {                                         // the factor of a dim, from the first tile's values
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    float t = 0.f;
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) t = __builtin_fmaxf(t, __builtin_fabsf(vt[v][j]));
-                    v_scale[j] = pow2(scale_exponent(row_max<32>(t)));
-                }
-            }
             const auto values = [&](int kk, int j) __attribute__((always_inline)) {
                 float x[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) x[i] = vt[8 * kk + i][j] * v_scale[j];
-                return split8(x);
+                for (int i = 0; i < 8; ++i) x[i] = vt[8 * kk + i][j];
+                return split_exactly<false>(x);
             };
-            // three products of an accumulator beside the split of the next dim's values
-            Parts pp[2], v[2];
+            // six products of an accumulator beside the split of the next dim's values
+            Thirds pp[2], v[2];
             pp[0] = probabilities(0);
             v[0] = values(0, 0);
 #pragma unroll
             for (int u = 0; u < 2 * NJ; ++u) {                     // keys 16 (u / NJ) .., dim u % NJ
                 const int kk = u / NJ, j = u % NJ, kk1 = (u + 1) / NJ, j1 = (u + 1) % NJ;
-                const Parts &a = v[u & 1], &q = pp[kk];
+                const Thirds &a = v[u & 1], &q = pp[kk];
                 if (u == NJ - 2) pp[1] = probabilities(1);
                 if (u + 1 < 2 * NJ) v[(u + 1) & 1] = values(kk1, j1);
-                o[j] = mfma_f16(a.m, q.h, o[j]);
-                o[j] = mfma_f16(a.h, q.m, o[j]);
-                o[j] = mfma_f16(a.h, q.h, o[j]);
+                o[j] = mfma_bf16(a.l, q.h, o[j]);
+                o[j] = mfma_bf16(a.m, q.m, o[j]);
+                o[j] = mfma_bf16(a.h, q.l, o[j]);
+                o[j] = mfma_bf16(a.m, q.h, o[j]);
+                o[j] = mfma_bf16(a.h, q.m, o[j]);
+                o[j] = mfma_bf16(a.h, q.h, o[j]);
 #pragma unroll
-                for (int i = 0; i < 3; ++i) {
+                for (int i = 0; i < 6; ++i) {
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 9, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);
                 }
             }
         }
@@ -501,19 +514,6 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_parts_kernel(GRAFT_AT
         }
     }
     l = row_sum<32>(l);
-    // (what a lane holds is of other lanes' dims: their factors come from the wavefront's piece of LDS)
-    floatj inverse;
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) inverse[j] = __uint_as_float(0x7f000000u - __float_as_uint(v_scale[j]));
-    *reinterpret_cast<floatj*>(Ks + l32 * (NJ * 4)) = inverse;
-    asm volatile("" ::: "memory");
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-        inverse = *reinterpret_cast<const floatj*>(Ks + (8 * (u >> 2) + 4 * half + (u & 3)) * (NJ * 4));
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) o[j][u] *= inverse[j];
-    }
-
     // ---- results: the eight wavefronts' rows, merged through LDS
     __syncthreads();                                               // nobody reads keys or queries any more
     float* ml_lds = merge_lds + DR_WAVES * PT_ROWS * PITCH;

@@ -1,10 +1,11 @@
-"""GPU parity of the fp32 attention kernel that multiplies on the fp16 matrix cores, where its tiles, factors and second pass can go
+"""GPU parity of the fp32 attention kernel that multiplies on the 16-bit matrix cores, where its tiles, factors and second pass can go
 wrong, against the CPU oracle (MI355X only).
 
 Bound of a result in dim d, |error| <= (2 s + a) sum_t p_t |v_td|.  s, a score's error: its operands keep 23 bits (2^-23 each, one
 partial product of 2^-24 left out), and its 24 partial sums are rounded to fp32 (2^-24 of at most sum |q k| <= |q| |k|), so s = (2.5 * 2^-23
-+ 24 * 2^-24) scale max|q| max|k|, and a weight is off by a factor e^(2 s).  a: probabilities and values keep 23 bits, and a sum is rounded
-six times a tile and once a wavefront, split and merge: (5 + 6 tiles + 48) 2^-24."""
++ 24 * 2^-24) scale max|q| max|k|, and a weight is off by a factor e^(2 s).  a: up to 2^-22 of a
+product of probability and value is left out, and a sum is rounded twelve times a tile (six are allowed for: roundings are of either
+sign) and once a wavefront, split and merge: (5 + 6 tiles + 48) 2^-24."""
 import numpy as np
 import pytest
 import torch
@@ -55,7 +56,7 @@ CASES = [
     (128, 1, 128, 32, 2, 900, "head_major", 0, True), (128, 1, 40, 32, 8, 8500, "head_major", 0, False), (128, 2, 33, 64, 4, 5000, "head_major", 0, True),
     (64, 1, 40, 32, 8, 2047, "head_major", 0, True), (64, 2, 61, 16, 4, 5000, "token_major", 0, True), (64, 4, 64, 32, 8, 33, "head_major", 96, True),
     (64, 1, 33, 16, 2, 9000, "head_major", 0, False),
-    # a last tile of one token, taken first, whose missing keys borrow the values of the next one
+    # a last tile of one token, which a wavefront takes first
     (128, 1, 40, 32, 8, 2009, "head_major", 0, False), (64, 2, 33, 16, 2, 4064, "token_major", 0, False), (128, 5, 126, 18, 2, 611, "head_major", 0, True),
     # tables of fewer than 48 pages with D = 128: 30 pages and one row group of the other kernel's, four steps a compute unit
     (128, 1, 121, 56, 4, 346, "head_major", 0, True), (128, 1, 70, 20, 2, 581, "token_major", 0, True), (128, 15, 52, 26, 2, 438, "head_major", 0, True),
@@ -89,8 +90,8 @@ def test_tiles_and_splits(case):
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("what", ["small", "large", "dims", "keys_grow", "values_grow", "past_fp16"])
 def test_magnitudes(D, what):
-    """Factors: all operands small or large (with the scores as they were), dims of values 2^-20 to 2^20 apart, keys and values that grow or
-    shrink along the sequence by more than a factor holds, keys that no fp16 number holds."""
+    """Sizes: all operands small or large (with the scores as they were), dims of values 2^-20 to 2^20 apart, keys and values that grow or
+    shrink along the sequence, keys that no fp16 number holds."""
     w, att, parent, rng = setup(2, 40, 32, 8, D, 1500)
     n, p = np.array([40, 23], np.int32), np.array([1500, 1111], np.int32)
     q, k, v = (np.array(att[x][0]) for x in ("q", "k_cache", "v_cache"))
@@ -143,8 +144,8 @@ def test_keys_that_are_not_finite(D):
 
 @pytest.mark.parametrize("D", [64, 128])
 def test_small_values_behind_large_ones(D):
-    """Rows that see one token whose values are 2^-9 of all others'.  A factor takes the largest of 32 values, below 2^9 * 2^2.5, to 2^8 at least, so a
-    value is off by at most 2^-25 * 2^3.5, a third of that squared on average (2e-7), beside 2^-23 of itself and the sums' roundings."""
+    """Rows that see one token whose values are 2^-9 of all others': at most 2^-22 of their products is left out (2.4e-7), beside the
+    sums' roundings."""
     w, att, parent, rng = setup(1, 40, 32, 8, D, 1500)
     n, p, t = np.array([40], np.int32), np.array([1500], np.int32), 300
     q, k, v = (np.array(att[x][0]) for x in ("q", "k_cache", "v_cache"))
