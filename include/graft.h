@@ -179,7 +179,9 @@ int32_t graft_build_tree_mask(const int32_t* parent, const int32_t* n_nodes, con
  *                             keys enter them as the sum of two fp16 numbers times a power of
  *                             two (23 bits), probabilities and values as three bf16 numbers
  *                             whose sum they are; up to 2^-22 of a product is left out.  Queries
- *                             and keys past fp16's largest number take fp32 products.
+ *                             and keys that fp16 numbers cannot hold, or hold with so few bits
+ *                             that a score may be off by 2^-22 (in powers of two, or of the
+ *                             row's largest, root mean square), take fp32 products.
  *                             GRAFT_BF16: bf16 storage, fp32 scores/softmax/accumulation,
  *                             probabilities rounded to bf16 for the P.V product (D = 128
  *                             only: D = 64 keeps them whole); where, with D = 128, the

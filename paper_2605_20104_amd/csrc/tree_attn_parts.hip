@@ -8,14 +8,20 @@
 //   S     : queries and keys are two fp16 numbers, h the nearest one and m the nearest one to what h leaves: 23 bits.  A product is h h +
 //           h m + m h (m m is below 2^-24 of it), 24 roundings a score where four numbers at a time took 32.  fp16 ends at 2^16 and
 //           loses bits below 2^-14, so numbers are taken times powers of two (exact): a row's largest query is brought to 2^8, and
-//           the keys of a tile are taken as they are if one of them is 2 or more, else with the largest at 2^8.
+//           the keys of a tile are taken as they are or, where they are small, with the largest at 2^8.
+//           What is lost even so, up to 2^-25 of a scaled number, counts where small operands stand beside large ones that meet
+//           zeros.  So a wavefront keeps the smallest factor and the largest key of its tiles, and behind the last of them has for
+//           every row a bound of it: scale * 2^-25 (|q| / factor of the keys + sqrt(D) * largest key / factor of the queries), the
+//           2-norm and not the sum of |q|, as the errors of D numbers are independent.  It may be 2^-22 (of a weight, as much as the
+//           rounding of an exponent of 4) or that part of the row's largest score (at least as far from zero as its reference is, or 16
+//           less: a reference is kept that long), which fp32 sums of D products are off by too.
 //   O     : probabilities and values are three bf16 numbers whose sum they are, eight bits each, and a product six of the nine (the rest is
 //           below 2^-23 of it): the exponents are those of fp32, so there is nothing to scale and nothing to lose, whatever the
 //           values of a dim have been before and whatever other rows see.  (Two fp16 numbers with a factor a dim from the wavefront's
 //           first tile: 4.0 us a step, and wrong results behind values of another size, by 7e-3 and without end.)
-//   beyond: what fp16 does not hold (keys past 65504, infinities, NaN) makes sums infinite or NaN.  Such a wavefront takes its
-//           tiles once more with v_mfma_f32_32x32x2_f32 on the same registers, and keys with values that are not finite kept out
-//           of the product.
+//   beyond: what fp16 does not hold (keys past 65504, infinities, NaN) makes sums infinite or NaN.  Such a wavefront, and one
+//           with a row past the bound above, takes its tiles once more with v_mfma_f32_32x32x2_f32 on the same registers, and keys
+//           with values that are not finite kept out of the product.
 //   K     : straight from memory to a wavefront-private piece of LDS, 16-byte chunks XOR-swizzled with the row; a lane reads
 //           8 dims of its key and splits them as it goes.
 //   V     : straight to registers.  Lane (half, l32) holds keys 8 (v / 4) + 4 half + v % 4, v < 16, in D / 32 dims from l32 D / 32
@@ -38,6 +44,8 @@ namespace graft {
 constexpr int PT_TK = 32;                       // keys of a tile
 constexpr int PT_ROWS = 32;                     // query rows of a workgroup
 constexpr int PT_TOP = 8;                       // largest queries of a row, and keys of a tile that is scaled, are brought to 2^8 .. 2^9
+constexpr float PT_KEY_MIN = 0.25f;             // a tile whose half keys (a lane's dims of one) all reach it is taken as it is
+constexpr float PT_LOST = 0x1p-22f;             // what lost bits may move a score by, or that part of the row's reference
 
 typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
@@ -70,10 +78,20 @@ template <bool SCALED> __device__ __forceinline__ Parts split8(const float (&x)[
     for (int i = 0; i < 8; ++i) y[i] = SCALED ? x[i] * c : x[i];
     return split8(y);
 }
-// All bits that are set in any of the numbers: bit 14 of either half tells whether one is 2 or more.
-__device__ __forceinline__ unsigned or_bits(unsigned acc, const half8_t& h) {
-    const uintx4 u = __builtin_bit_cast(uintx4, h);
-    return (acc | u[0] | u[1]) | u[2] | u[3];
+// Largest and smallest numbers of an operand, pair by pair.  (Of the fp16 ones, which are there for the products anyway: a maximum over the
+// fp32 ones kept those in registers, 72 of which went to memory.)
+__device__ __forceinline__ void widest(half2_t& hi, half2_t& lo, const half8_t& h) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const half2_t x{h[2 * i], h[2 * i + 1]};
+        hi = __builtin_elementwise_maximum(hi, x);
+        lo = __builtin_elementwise_minimum(lo, x);
+    }
+}
+__device__ __forceinline__ float max_abs(float acc, const float (&x)[8]) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc = __builtin_fmaxf(acc, __builtin_fabsf(x[i]));
+    return acc;
 }
 // Eight numbers of a lane as three bf16 operands, whose sum they are: eight bits of a number, eight of what they leave, and what those
 // leave.  (Infinities leave NaN.)  NEAREST: rounded, not cut off, which makes what a product leaves out a quarter and of either sign, but
@@ -187,6 +205,8 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_parts_kernel(GRAFT_AT
 
     float m, l;
     int k_exp = 0;                               // keys of a tile are taken times 2 to this,
+    int k_low = 127;                             // least of these exponents
+    float k_top = 0.f;                           // largest key of a lane
     floatx16 o[NJ];                              // o[j][u]: dim NJ (8 (u / 4) + 4 half + u % 4) + j of row l32
     auto clear_rows = [&]() __attribute__((always_inline)) {
         m = -INFINITY;
@@ -273,17 +293,19 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_parts_kernel(GRAFT_AT
     float* const q_top = reinterpret_cast<float*>(Ks0 + DR_WAVES * KEYS_BYTES);
     const float x[8] = {q0[0], q0[1], q0[2], q0[3], q1[0], q1[1], q1[2], q1[3]};
     if (wave < STEPS) {
-        float t = 0.f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) t = __builtin_fmaxf(t, __builtin_fabsf(x[i]));
-        q_top[wave * 32 + l32] = row_max<32>(t);
+        q_top[wave * 32 + l32] = row_max<32>(max_abs(0.f, x));
     }
     lds_only_barrier();
     float q_max = 0.f;
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) q_max = __builtin_fmaxf(q_max, q_top[s * 32 + l32]);
     const int q_exp = scale_exponent(q_max);
+    float* const q_squares = q_top + STEPS * 32;                   // sums of the scaled queries' squares, likewise
     if (wave < STEPS) {
+        float t = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) t += (x[i] * pow2(q_exp)) * (x[i] * pow2(q_exp));
+        q_squares[wave * 32 + l32] = row_sum<32>(t);
         const Parts q = split8<true>(x, pow2(q_exp));
         *reinterpret_cast<half8_t*>(Qs + wave * 1024 + lane * 16) = q.h;
         *reinterpret_cast<half8_t*>(Qs + (STEPS + wave) * 1024 + lane * 16) = q.m;
@@ -332,20 +354,20 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_parts_kernel(GRAFT_AT
             const auto products = [&](auto scaled_) __attribute__((always_inline)) {
                 constexpr bool SCALED = decltype(scaled_)::value;
                 const float c = pow2(k_exp);
-                unsigned bits = 0;
+                half2_t hi{}, lo{};
                 s = floatx16{};
                 float x[2][8];
                 Parts ks[2], qs[2];
                 key_dims(0, x[0]);
                 qs[0] = query_dims(0);
-                if constexpr (STEPS > 1) key_dims(1, x[1]);
+                key_dims(1, x[1]);
                 ks[0] = split8<SCALED>(x[0], c);
 #pragma unroll
                 for (int d = 0; d < STEPS; ++d) {
                     const Parts &k = ks[d & 1], &q = qs[d & 1];
                     if (d + 1 < STEPS) qs[(d + 1) & 1] = query_dims(d + 1);
                     if (d + 2 < STEPS) key_dims(d + 2, x[d & 1]);
-                    bits = or_bits(bits, k.h);
+                    widest(hi, lo, k.h);
                     if (d + 1 < STEPS) ks[(d + 1) & 1] = split8<SCALED>(x[(d + 1) & 1], c);
                     s = mfma_f16(k.m, q.h, s);
                     s = mfma_f16(k.h, q.m, s);
@@ -357,21 +379,27 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_parts_kernel(GRAFT_AT
                         __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
                     }
                 }
-                return __builtin_amdgcn_ballot_w64((bits & 0x40004000u) != 0) != 0;
+                const half2_t both = __builtin_elementwise_maximum(hi, -lo);
+                const float top = static_cast<float>(__builtin_elementwise_maximum(both[0], both[1])) * (SCALED ? pow2(-k_exp) : 1.f);
+                k_top = __builtin_elementwise_maximum(k_top, top);
+                return __builtin_amdgcn_ballot_w64(top < PT_KEY_MIN) == 0;
             };
             if (__builtin_expect(!(k_exp == 0 && products(std::false_type{})), 0)) {
                 float t = 0.f, x[8];
 #pragma unroll 1
                 for (int d = 0; d < STEPS; ++d) {
                     key_dims(d, x);
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) t = __builtin_fmaxf(t, __builtin_fabsf(x[i]));
+                    t = max_abs(t, x);
                 }
                 t = wave_max_f32(t);
-                k_exp = t >= 2.f && t < 32768.f ? 0 : scale_exponent(t);        // (zero: the next tile is tried as it is again)
-                s_scale = row_scale * pow2(-k_exp);
-                (void)products(std::true_type{});
+                const int e = t >= 0x1p9f && t < 0x1p15f ? 0 : scale_exponent(t);
+                if (e != 0 || k_exp != 0) {
+                    k_exp = e;                                     // (zero: the next tile is tried as it is again)
+                    s_scale = row_scale * pow2(-k_exp);
+                    (void)products(std::true_type{});
+                }
             }
+            k_low = k_exp < k_low ? k_exp : k_low;
         }
         unsigned odd = 0;                                          // keys with an infinite or NaN value
         if constexpr (careful) {
@@ -503,7 +531,13 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_parts_kernel(GRAFT_AT
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
             for (int u = 0; u < 16; ++u) t = __builtin_elementwise_maximum(t, __builtin_fabsf(o[j][u]));
-        const bool odd = !(t < INFINITY) && row_node(r_base + (lane_now() & 31)) < n;              // (queries of absent nodes may be anything)
+        float squares = 0.f;
+#pragma unroll
+        for (int d = 0; d < STEPS; ++d) squares += q_squares[d * 32 + l32];
+        const float lost = __builtin_amdgcn_ldexpf(__builtin_amdgcn_sqrtf(squares), -25 - k_low) +
+                           __builtin_sqrtf(static_cast<float>(D)) * 0x1p-25f * wave_max_f32(k_top);
+        const bool fine = t < INFINITY && __builtin_fabsf(row_scale) * lost <= PT_LOST * __builtin_fmaxf(1.f, __builtin_fmaxf(m, -m - DR_LAZY_LOG2));
+        const bool odd = !fine && row_node(r_base + (lane_now() & 31)) < n;              // (queries of absent nodes may be anything)
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd) != 0, 0)) {
             clear_rows();
             for (int it = 0; it < count; ++it) {
@@ -535,7 +569,7 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_parts_kernel(GRAFT_AT
 
 // LDS of a workgroup: masks, then queries and keys, or the merge
 static constexpr size_t parts_lds_bytes(int32_t D) {
-    const size_t loop = 2 * (D / 16) * 1024 + static_cast<size_t>(DR_WAVES) * PT_TK * D * 4 + (D / 16) * 32 * sizeof(float);
+    const size_t loop = 2 * (D / 16) * 1024 + static_cast<size_t>(DR_WAVES) * PT_TK * D * 4 + 2 * (D / 16) * 32 * sizeof(float);
     const size_t merge = static_cast<size_t>(DR_WAVES) * PT_ROWS * (D + 4 + 2) * sizeof(float);
     return DR_MASK_BYTES + (loop > merge ? loop : merge);
 }

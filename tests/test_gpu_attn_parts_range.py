@@ -1,9 +1,11 @@
 """fp32 attention on the matrix cores where operands of very different size meet in a tile, against 64-bit arithmetic (MI355X only).
 
 Bound of a result in dim d of a row, every part of it for that row alone.  A score is off by at most 29 * 2^-24 of sum |q k| (operands
-of 23 bits, 24 partial sums), a weight p by that part of itself, and the weights' sum by the weighted mean of it.  Probabilities
-and values keep their 24 bits, of their products up to 2^-22 is left out, and a sum is rounded twelve times a tile and once a wavefront,
-split and merge: (5 + 12 tiles + 48) 2^-24 of sum p |v|, and 2^-140 where numbers end."""
+of 23 bits, 24 partial sums) and, where operands lose bits below fp16's, by what the kernel lets pass: 2^-22 of the largest score in
+units of ln 2, at least 2^-22, as a root mean square; four times that here.  A weight p is off by that part of itself, and the
+weights' sum by the weighted mean of it.  Probabilities and values keep their 24 bits, of their products up to 2^-22 is left out,
+and a sum is rounded twelve times a tile and once a wavefront, split and merge: (5 + 12 tiles + 48) 2^-24 of sum p |v|, and 2^-140
+where numbers end."""
 import numpy as np
 import pytest
 
@@ -36,7 +38,7 @@ def check(w, att, parent, n, p, with_ws=True):
             m = s.max(-1, keepdims=True)
             e = np.exp(s - m)
             pr = e / e.sum(-1, keepdims=True)
-            off = 29 * 2.0 ** -24 * att["scale"] * (np.abs(q) @ np.abs(k).T)
+            off = 29 * 2.0 ** -24 * att["scale"] * (np.abs(q) @ np.abs(k).T) + 4 * 2.0 ** -22 * np.maximum(LN2, np.abs(m))
             off = np.where(pr > 0, off, 0.0)
             a = (5 + 12 * (-(-total // 256) + 1) + 48) * 2.0 ** -24
             bound = (pr * (off + (pr * off).sum(-1, keepdims=True))) @ np.abs(v) + a * (pr @ np.abs(v)) + 2.0 ** -140
@@ -111,3 +113,42 @@ def test_one_large_score_over_many_small_weights(D):
     v = np.abs(v)
     v[a, :, c] = 0
     check(w, dict(att, q=[q], k_cache=[k], v_cache=[v]), parent, n, p, with_ws=False)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("size", [1e-1, 1e-2, 1e-3, 1e-4, 1e-5, 1e-8])
+@pytest.mark.parametrize("where", ["every_key", "one_key"])
+def test_small_keys_beside_large_ones(D, size, where):
+    """One dim of the keys, of every one or of one in a tile, is large where the queries are nearly zero; the others are small, and the
+    queries so large that the scores have ordinary sizes."""
+    w, att, parent, rng, (q, k, v), n, p = arrays(D)
+    q, k = q / np.float32(size), k * np.float32(size)
+    q[..., 3] = rng.standard_normal(q.shape[:-1]) * 1e-3
+    if where == "every_key":
+        k[..., 3] = 4 + rng.random(k.shape[:-1])
+    else:
+        for a, c in zip(*tokens(att, 0, 2088)):
+            k[a, :, c, 3] = 4.5 if c == 9 else 0
+    check(w, dict(att, q=[q], k_cache=[k], v_cache=[v]), parent, n, p)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("power", [10, 16, 24, 40])
+@pytest.mark.parametrize("only", [None, 0, 3, 30, 61])
+def test_small_queries_beside_a_large_one(D, power, only):
+    """A row's largest query by far meets keys of zero; keys that are zero but in one dim, too."""
+    w, att, parent, rng, (q, k, v), n, p = arrays(D)
+    if only is not None:
+        k[..., [d for d in range(D) if d != only]] = 0
+    q[..., 11] = np.float32(2.0 ** power)
+    k[..., 11] = 0
+    check(w, dict(att, q=[q], k_cache=[k], v_cache=[v]), parent, n, p)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("what", ["queries", "keys"])
+def test_scores_of_the_smallest_and_largest_numbers(D, what):
+    """Queries of 2^-110 with keys of 2^110, and the other way round: past what the factors reach."""
+    w, att, parent, rng, (q, k, v), n, p = arrays(D)
+    f = np.float32(2.0 ** (-110 if what == "queries" else 110))
+    check(w, dict(att, q=[q * f], k_cache=[k / f], v_cache=[v]), parent, n, p)
