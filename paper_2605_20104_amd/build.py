@@ -37,7 +37,7 @@ def _hipcc() -> str:
     return "hipcc"
 
 
-HAND_SCHEDULED = ["tree_attn.hip", "tree_attn_wide.hip", "tree_attn_wide_128.hip"]          # their device assembly is kept and checked
+HAND_SCHEDULED = ["tree_attn.hip", "tree_attn_wide.hip", "tree_attn_wide_128.hip", "tree_attn_parts.hip"]     # their device assembly is kept and checked
 
 
 def _asm_of(src: str, directory: str = OBJ_DIR) -> str:
@@ -107,7 +107,8 @@ def check_attention_asm(asm_text: str):
         MFMA is written at the end of its passes, and nothing interlocks a vector ALU,
         LDS or memory instruction, or a v_accvgpr_read, that comes earlier).  An MFMA issues no sooner
         than the one in front of it has gone through its passes: those count as wait states too;
-      * the transfers from memory to LDS have landed where LDS gets another use (_check_transfers).
+      * the transfers from memory to LDS have landed where LDS gets another use (_check_transfers), and in tree_attn_parts_kernel
+        where its keys are read (_check_counted_waits).
     """
     problems = _check_transfers(asm_text)
     lines = asm_text.split("\n")
@@ -210,6 +211,32 @@ def check_attention_asm(asm_text: str):
     return problems
 
 
+def _counts_transfers(symbol: str) -> bool:
+    """Whether a kernel waits for its transfers to LDS by the number of loads that it has requested behind them."""
+    return re.match(r"_ZN5graft\d+tree_attn_parts_kernelI", symbol) is not None
+
+
+def _is_transfer(op: str, text: str) -> bool:
+    return "_lds_" in op or op.startswith("buffer_load") and text.endswith(" lds")
+
+
+def _control_flow(body: str, first_line: int):
+    """Instructions of a kernel as (line, opcode, text, in inline assembly), and of each the indices of those that may follow it."""
+    code, label_at, in_asm = [], {}, False         # label -> index of the next instruction
+    for ln, raw in enumerate(body.split("\n"), first_line):
+        in_asm = ("ASMSTART" in raw or in_asm) and "ASMEND" not in raw
+        text = raw.split(";")[0].strip()
+        if re.match(r"\.\w+:", text):
+            label_at[text.split(":")[0]] = len(code)
+        elif text and not text.startswith("."):
+            code.append((ln, text.split()[0], text, in_asm))
+    after = []
+    for i, (_, op, text, _) in enumerate(code):
+        jump = [label_at[text.split()[1]]] if op.startswith(("s_branch", "s_cbranch")) else []
+        after.append([] if op == "s_endpgm" else jump if op == "s_branch" else jump + [i + 1])
+    return code, after
+
+
 def _check_transfers(asm_text: str):
     """Transfers from memory straight to LDS are inline assembly, and nothing but the kernels' own s_waitcnt waits for them.
     Behind the last MFMA wavefronts exchange results in the LDS that keys and queries came to.  On every path of the
@@ -218,20 +245,10 @@ def _check_transfers(asm_text: str):
     LANDED, MINE_LANDED, IN_FLIGHT = 0, 1, 2
     problems = []
     for body in re.finditer(r"^(_Z\w+):[^\n]*\n(.*?)^\.Lfunc_end", asm_text, re.M | re.S):
-        if not _managed_accvgprs(body.group(1)):
+        counts = _counts_transfers(body.group(1))
+        if not counts and not _managed_accvgprs(body.group(1)):
             continue
-        first_line = asm_text.count("\n", 0, body.start(2)) + 1
-        code, label_at = [], {}                    # (line, opcode, text); label -> index of the next instruction
-        for ln, raw in enumerate(body.group(2).split("\n"), first_line):
-            text = raw.split(";")[0].strip()
-            if re.match(r"\.\w+:", text):
-                label_at[text.split(":")[0]] = len(code)
-            elif text and not text.startswith("."):
-                code.append((ln, text.split()[0], text))
-        after = []                                 # indices of the instructions that may follow
-        for i, (_, op, text) in enumerate(code):
-            jump = [label_at[text.split()[1]]] if op.startswith(("s_branch", "s_cbranch")) else []
-            after.append([] if op == "s_endpgm" else jump if op == "s_branch" else jump + [i + 1])
+        code, after = _control_flow(body.group(2), asm_text.count("\n", 0, body.start(2)) + 1)
         before = [[] for _ in code]
         for i, targets in enumerate(after):
             for t in targets:
@@ -243,12 +260,15 @@ def _check_transfers(asm_text: str):
                 if i not in ahead:
                     ahead.add(i)
                     todo.append(i)
+        if counts:
+            problems += _check_counted_waits(body.group(1), code, after, set(range(len(code))) - ahead)
+            continue
         state = [None] * len(code)                 # of the transfers in front of an instruction, the worst of all paths
         state[0], todo = LANDED, [0]
         while todo:
             i = todo.pop()
             op, text, s = code[i][1], code[i][2], state[i]
-            if "_lds_" in op or op.startswith("buffer_load") and text.endswith(" lds"):
+            if _is_transfer(op, text):
                 s = IN_FLIGHT
             elif op == "s_waitcnt" and "vmcnt(0)" in text:
                 s = min(s, MINE_LANDED)
@@ -258,10 +278,119 @@ def _check_transfers(asm_text: str):
                 if state[t] is None or state[t] < s:
                     state[t] = s
                     todo.append(t)
-        for i, (ln, op, text) in enumerate(code):
+        for i, (ln, op, text, _) in enumerate(code):
             if op.startswith("ds_write") and i not in ahead and state[i]:
                 problems.append("line %d (%s): transfers to LDS may be in flight: %s" % (ln, body.group(1), text))
     return problems
+
+
+def _span(token: str):
+    """Scalar registers of an operand: 's7' -> (7, 7), 's[2:3]' -> (2, 3), vcc -> (-1, -1), none -> None."""
+    m = re.fullmatch(r"s(\d+)|s\[(\d+):(\d+)\]", token)
+    if m:
+        return int(m.group(1) or m.group(2)), int(m.group(1) or m.group(3))
+    return (-1, -1) if token.startswith("vcc") else None
+
+
+def _written_scalars(op: str, args):
+    """Spans of the scalar registers that an instruction may write."""
+    if op.startswith(("s_cmp", "s_bitcmp", "s_cbranch", "s_branch", "s_waitcnt", "s_barrier", "s_nop", "s_endpgm", "s_sleep", "s_setprio",
+                      "ds_", "global_", "buffer_", "flat_", "scratch_")):
+        return []
+    spans = [x for x in map(_span, args[:2 if op.startswith("v_") else 1]) if x]
+    return spans + ([(-1, -1)] if op.startswith("v_cmp") and op.endswith("e32") else [])
+
+
+class _Facts:
+    """What a path knows of scalar conditions.  A condition is (relation, whether it holds where the relation does); relations are of
+    registers as they are: a write of one ends what is known of it.  Few are kept, the newest."""
+    __slots__ = ("vcc", "scc", "pairs", "known")
+
+    def __init__(self, vcc=None, scc=None, pairs=(), known=()):
+        self.vcc, self.scc, self.pairs, self.known = vcc, scc, pairs, known
+
+    def key(self):
+        return self.vcc, self.scc, self.pairs, self.known
+
+    def after(self, op: str, args):
+        vcc, scc, pairs, known = self.key()
+        if op.startswith("s_") and not op.startswith(("s_cselect", "s_mov", "s_cbranch", "s_waitcnt", "s_nop", "s_load", "s_barrier", "s_mul_i32")):
+            scc = None                             # (most of them write it)
+        new_pair, new_vcc = None, None
+        if op == "s_cselect_b64" and self.scc and args[1:] in (["-1", "0"], ["0", "-1"]):
+            new_pair = self.scc[0], self.scc[1] == (args[1] == "-1")
+        if op in ("s_and_b64", "s_andn2_b64") and args[:2] == ["vcc", "exec"]:
+            of = dict(pairs).get(_span(args[2]), (("bits", args[2]), True))
+            new_vcc = of[0], of[1] == (op == "s_and_b64")
+        for lo, hi in _written_scalars(op, args):
+            hit = lambda c: any(x and x[0] <= hi and lo <= x[1] for x in map(_span, c[0][1:]))
+            pairs = tuple((r, c) for r, c in pairs if (hi < r[0] or r[1] < lo) and not hit(c))
+            known = tuple(c for c in known if not hit(c))
+            vcc = None if lo < 0 or vcc and hit(vcc) else vcc
+            scc = None if scc and hit(scc) else scc
+        if new_pair:
+            pairs = (pairs + ((_span(args[0]), new_pair),))[-3:]
+        vcc = new_vcc or vcc
+        m = re.fullmatch(r"s_cmp_(lt|ge|gt|le|eq|lg)_([iu]\d+)", op)
+        if m:
+            x, y = args if m.group(1) in ("lt", "ge", "eq", "lg") else args[::-1]
+            scc = ("eq" if m.group(1) in ("eq", "lg") else "lt_" + m.group(2), x, y), m.group(1) in ("lt", "gt", "eq")
+        return _Facts(vcc, scc, pairs, known)
+
+    def branch(self, op: str, taken: bool):
+        """The facts behind a branch, or None where what is known rules it out."""
+        cond = self.vcc if "vcc" in op else self.scc if "scc" in op else None
+        if cond is None:
+            return self
+        holds = (taken == op.endswith(("nz", "scc1"))) == cond[1]
+        if (cond[0], not holds) in self.known:
+            return None
+        return _Facts(self.vcc, self.scc, self.pairs, (tuple(c for c in self.known if c[0] != cond[0]) + ((cond[0], holds),))[-3:])
+
+
+def _check_counted_waits(kernel: str, code, after, behind_mfma):
+    """The kernel's own s_waitcnt vmcnt(N) stand for "the transfers have landed, the loads behind them may be on their way": on every
+    path at least N loads or stores must have been requested behind the last transfer, or a shorter wait must stand in between.  And where
+    LDS is written behind the last MFMA, all wavefronts' transfers must have landed: a barrier behind such a wait.
+    Paths are those that scalar conditions allow: the next tile's keys and, behind the products, its values are requested by one."""
+    LANDED = 1 << 10
+    # of every instruction: facts -> (requests behind the last transfer, whether a barrier has followed its landing), the worst of
+    # all paths that arrive with them
+    states, start = [{} for _ in code], _Facts()
+    states[0][start.key()] = (LANDED, True)
+    todo, problems, waits = [(0, start)], {}, 0
+    while todo:
+        i, facts = todo.pop()
+        ln, op, text, in_asm = code[i]
+        count, synced = states[i][facts.key()]
+        wait = re.search(r"vmcnt\((\d+)\)", text) if op == "s_waitcnt" else None
+        if wait and in_asm:
+            waits += 1
+            if count < int(wait.group(1)):
+                problems[i] = "only %d requests behind the last transfer" % count
+        if op.startswith("ds_write") and i in behind_mfma and not synced:
+            problems[i] = "transfers to LDS may be in flight"
+        if _is_transfer(op, text):
+            count, synced = 0, False
+        elif op.startswith(("global_", "buffer_", "flat_", "scratch_")):
+            count = min(count + 1, LANDED)
+        elif wait and count >= int(wait.group(1)):
+            count = LANDED
+        elif op == "s_barrier" and count == LANDED:
+            synced = True
+        facts = facts.after(op, text.replace(",", " ").split()[1:])
+        for n, t in enumerate(after[i]):
+            there = facts.branch(op, n == 0) if len(after[i]) == 2 else facts            # (the first one is where a branch goes)
+            if there is None:
+                continue
+            old = states[t].get(there.key(), (LANDED + 1, True))
+            worst = (min(old[0], count), old[1] and synced)
+            if worst != old:
+                states[t][there.key()] = worst
+                todo.append((t, there))
+    if not waits and any(_is_transfer(op, text) for _, op, text, _ in code):
+        return ["%s: no wait for its transfers found" % kernel]
+    return ["line %d (%s): %s: %s" % (code[i][0], kernel, what, code[i][2]) for i, what in sorted(problems.items())]
 
 
 def _check_and_clean(directory: str, what: str):

@@ -549,6 +549,7 @@ __global__ __launch_bounds__(DR_THREADS, 2) void tree_attn_parts_kernel(GRAFT_AT
     }
     l = row_sum<32>(l);
     // ---- results: the eight wavefronts' rows, merged through LDS
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");               // (nothing is on its way by now: so it stays, whatever the loop becomes)
     __syncthreads();                                               // nobody reads keys or queries any more
     float* ml_lds = merge_lds + DR_WAVES * PT_ROWS * PITCH;
     {

@@ -182,3 +182,92 @@ def test_no_kernel_of_the_library_uses_scratch_memory():
     sizes = [data[at.end()] for at in re.finditer(re.escape(key), data)]
     assert len(sizes) >= len(b.SOURCES)
     assert set(sizes) == {0}, sizes
+
+
+# ---- waits that count the requests behind a transfer
+COUNTED = "_ZN5graft22tree_attn_parts_kernelILi64EEEvPKiS2_"
+MORE = "\ts_cmp_ge_i32 s4, s5\n\ts_cselect_b64 s[6:7], -1, 0\n\ts_and_b64 vcc, exec, s[6:7]\n\ts_cbranch_vccnz .LBB0_%d"
+LOOP = """\tglobal_load_lds_dwordx4 v1, s[0:1]
+\tglobal_load_dwordx4 v[2:5], v1, s[2:3]
+\tglobal_load_dwordx4 v[6:9], v1, s[2:3]
+.LBB0_1:
+\t;;#ASMSTART
+\ts_waitcnt vmcnt(2)
+\t;;#ASMEND
+\tds_read_b128 v[20:23], v0
+\tv_mfma_f32_32x32x16_f16 v[40:55], v[20:23], v[24:27], v[40:55]
+\ts_waitcnt vmcnt(0)
+%(first)s
+\tglobal_load_lds_dwordx4 v1, s[0:1]
+.LBB0_2:
+\tv_mfma_f32_32x32x16_f16 v[40:55], v[2:5], v[6:9], v[40:55]
+%(second)s
+\tglobal_load_dwordx4 v[2:5], v1, s[2:3]
+%(last)s
+.LBB0_3:
+%(back)s
+\ts_branch .LBB0_1
+.LBB0_4:
+%(end)s
+\tds_write_b128 v0, v[40:43]"""
+WAY = dict(first=MORE % 2, second="\ts_and_b64 vcc, exec, s[6:7]\n\ts_cbranch_vccnz .LBB0_3", last="\tglobal_load_dwordx4 v[6:9], v1, s[2:3]",
+           back="\ts_cmp_lt_i32 s4, s5\n\ts_cbranch_scc0 .LBB0_4", end="\ts_barrier")
+
+
+def _counted(**other):
+    return b.check_attention_asm(_asm(LOOP % dict(WAY, **other)).replace(KERNEL, COUNTED))
+
+
+def test_a_wait_that_counts_the_requests_behind_a_transfer():
+    assert _counted() == []
+    assert _counted(last="\tbuffer_store_dword v6, v1, s[0:3], 0 offen") == []           # what is stored counts too
+    # a load too few, in the loop or in front of it
+    bad = _counted(last="\ts_nop 0")
+    assert len(bad) == 1 and "only 1 requests" in bad[0]
+    assert any("only 0 requests" in x for x in _counted(last="\tglobal_load_lds_dwordx4 v1, s[0:1]"))
+    # a shorter wait in between is enough
+    assert _counted(last="\ts_waitcnt vmcnt(1)") == []
+    assert _counted(last="\ts_waitcnt lgkmcnt(0)") != []
+
+
+def test_paths_that_a_condition_allows():
+    # the loads behind the transfer go by another condition, or by one whose registers are others by then
+    other = "\ts_and_b64 vcc, exec, s[8:9]\n\ts_cbranch_vccnz .LBB0_3"
+    assert any("only 0 requests" in x for x in _counted(second=other))
+    for write in ("\ts_mov_b64 s[6:7], s[8:9]", "\tv_cmp_gt_f32_e64 s[6:7], v1, v2", "\ts_add_i32 s7, s8, 1"):
+        assert any("only 0 requests" in x for x in _counted(second=write + "\n" + WAY["second"]))
+    assert _counted(second=WAY["second"].replace("s_and_b64", "s_andn2_b64")) != []
+    # the same condition the other way round, and another compare of the same numbers
+    inverse = "\ts_cmp_lt_i32 s4, s5\n\ts_cselect_b64 s[8:9], -1, 0\n\ts_andn2_b64 vcc, exec, s[8:9]\n\ts_cbranch_vccnz .LBB0_3"
+    assert _counted(second=inverse) == []
+    assert _counted(second="\ts_add_i32 s4, s4, 1\n" + inverse) != []                     # of other numbers
+    assert _counted(second="\ts_cmp_gt_i32 s5, s4\n\ts_cbranch_scc0 .LBB0_3") == []
+
+
+def test_the_exchange_behind_counted_transfers():
+    bad = _counted(end="\ts_nop 0")
+    assert len(bad) == 1 and "in flight" in bad[0]
+    # the loop is left with a transfer that nobody has waited for
+    assert any("in flight" in x for x in _counted(back="\ts_cbranch_execz .LBB0_4"))
+    assert "no wait" in b.check_attention_asm(_asm((LOOP % WAY).replace(";;#ASMSTART", "").replace(";;#ASMEND", "")).replace(KERNEL, COUNTED))[0]
+
+
+def test_the_waits_of_the_built_library():
+    path = b._asm_of("tree_attn_parts.hip")
+    if not os.path.exists(path):
+        pytest.skip("no assembly kept from a build in this tree")
+    with open(path) as f:
+        text = f.read()
+    assert text.count("global_load_lds_dwordx4") > 50 and b.check_attention_asm(text) == []
+    # one of the sixteen loads behind a tile's transfers goes: the first of every run of sixteen, one at a time (the first tile's are
+    # waited for in front of the loop, so that it can do without)
+    lines, run, starts = text.split("\n"), 0, []
+    for i, line in enumerate(lines):
+        if line.startswith("\tglobal_load_lds"):
+            run = 1
+        elif run and line.startswith("\tglobal_load_dwordx"):
+            starts.append(i)
+            run = 0
+    assert len(starts) == 8                                      # first tile, first of a table register's, loop and second pass, D = 64 and 128
+    missed = [lines[i] for i in starts if not any("only 15 requests" in x for x in b.check_attention_asm("\n".join(lines[:i] + lines[i + 1:])))]
+    assert len(missed) <= 2, missed
