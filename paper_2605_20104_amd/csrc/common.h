@@ -132,6 +132,14 @@ __device__ __forceinline__ u64 wave_max_key(u64 v) {
     return (static_cast<u64>(top) << 32) | low;
 }
 
+// What a wavefront's lanes have written to LDS is what its lanes read from here on, and the other way round.  (A wavefront's
+// LDS operations complete in order; this keeps the compiler from changing that order.)
+__device__ __forceinline__ void wavefront_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // Maximum over the four lanes l, l + 16, l + 32, l + 48 (the four 16-lane rows of a wavefront),
 // all four get it: the two lane swaps of gfx950, no trip through the LDS crossbar.
 __device__ __forceinline__ float rows_max_f32(float v) {

@@ -443,6 +443,7 @@ __global__ __launch_bounds__(MW_THREADS) void topk_row_kernel(
     if (nl <= MU_LIST) {
         if (wave > 0) return;
         best_of(list, nl, k, lane, [&](int j, u64 key) { best[j] = key; });
+        wavefront_lds_order();
     } else {                                        // long runs of equal values: exact, per-thread sorted lists
         u64 own[KK];
 #pragma unroll

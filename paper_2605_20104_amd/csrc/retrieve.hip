@@ -74,14 +74,6 @@ __device__ __forceinline__ void shift_group(Tok4& g, int32_t i0, int32_t L_max) 
         if (r < i0 - (L_max - 4)) { g.t[0] = g.t[1]; g.t[1] = g.t[2]; g.t[2] = g.t[3]; }
 }
 
-// What a wavefront's lanes have written to LDS is what its lanes read from here on, and the other way round.  (A wavefront's
-// LDS operations complete in order; this keeps the compiler from changing that order.)
-__device__ __forceinline__ void wavefront_lds_order() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-}
-
 template <int RT_THREADS>
 __global__ __launch_bounds__(RT_THREADS) void retrieve_kernel(
     const int32_t* __restrict__ ctx, const int32_t* __restrict__ ctx_len, int32_t L_max,
