@@ -38,11 +38,22 @@ struct AttnParams {
     unsigned long long* stamps;   // timing build: AT_STAMPS values per workgroup, or null (always null otherwise)
 };
 
-// Division by a number that the host knows: x / d == (x * magic31(d)) >> 31 for 0 <= x < 2^24, 1 <= d <= 128.  A
-// division is some thirty dependent instructions, and several stand in front of a workgroup's first requests.
+// Division by a number that the host knows: x / d == (x * magic31(d)) >> 31 for x >= 0, d >= 1 with x (d - 1) < 2^31 (m d - 2^31 is
+// at most d - 1, so x m / 2^31 is past x / d by at most x (d - 1) / (2^31 d), which must stay below 1 / d).  A division is some
+// thirty dependent instructions, and several stand in front of a workgroup's first requests.
 inline uint32_t magic31(uint32_t d) { return ((1u << 31) + d - 1u) / d; }
-__device__ __forceinline__ int div31(int x, uint32_t magic) {
+__host__ __device__ __forceinline__ int div31(int x, uint32_t magic) {
     return static_cast<int>((static_cast<u64>(static_cast<unsigned>(x)) * magic) >> 31);
+}
+// The same for 0 <= x < 2^31 and any d: 2^shift, the least power of two from d on, leaves the multiplier 31 bits and more.
+struct Magic { uint32_t m; int32_t shift; };
+inline Magic magic_any(uint32_t d) {
+    int32_t shift = 0;
+    while ((u64{1} << shift) < d) ++shift;
+    return {static_cast<uint32_t>(((u64{1} << (31 + shift)) + d - 1) / d), shift};
+}
+__host__ __device__ __forceinline__ int div_any(int x, uint32_t magic, int shift) {
+    return static_cast<int>((static_cast<u64>(static_cast<unsigned>(x)) * magic) >> (31 + shift));
 }
 // x / d for x, d < 2^24, by a number that has no such bound.
 __device__ __forceinline__ int div24(int x, int d) {

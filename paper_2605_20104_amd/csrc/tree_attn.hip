@@ -973,8 +973,8 @@ __global__ __launch_bounds__(AT_THREADS) void tree_attn_mfma_kernel(GRAFT_ATTN_A
 constexpr int CB_MAX_SPLITS = 16;
 constexpr int CB_MAX_WAVES = 8;          // per workgroup; the host picks a multiple of the wavefronts per tile pair
 
-// shape: wavefronts per tile pair, tile pairs per workgroup (8 bits each), ceil(256 / the former).  n_blk_magic: magic31 of the row blocks
-// of a (b, g), at most 140 (exact for tile / PIECES < 2^31 / 140: more rows than that have more than 300 GB of queries and results).
+// shape: wavefronts per tile pair, tile pairs per workgroup (8 bits each), ceil(256 / the former) (9 bits), and the shift of the magic_any of
+// the row blocks of a (b, g), at most 140 of them; n_blk_magic: its multiplier.
 template <int U, bool WIDE>
 __global__ __launch_bounds__(64 * CB_MAX_WAVES) void tree_attn_combine_kernel(
     const unsigned short* ws_o, const float* ws_ml, const int32_t* n_nodes, int32_t n_tiles, int32_t shape, int32_t R, int32_t R_pad,
@@ -983,7 +983,7 @@ __global__ __launch_bounds__(64 * CB_MAX_WAVES) void tree_attn_combine_kernel(
     // (m, den, acc[8]) per lane of the helper wavefronts (only U = 16 has helpers)
     __shared__ float xch[U == CB_MAX_SPLITS ? CB_MAX_WAVES : 1][10][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wpt = shape & 255, tiles_per_wg = shape >> 8 & 255, pair = wave * (shape >> 16) >> 8;      // wave / wpt
+    const int wpt = shape & 255, tiles_per_wg = shape >> 8 & 255, pair = wave * (shape >> 16 & 511) >> 8;      // wave / wpt
     constexpr int BLK = WIDE ? 32 : 16, PIECES = AT_D * BLK / 512;          // rows of a block, tile pairs in it
     const int lr = lane % BLK, lg = lane / BLK;
     const int n_blk = R_pad / BLK;                                          // row blocks per (b, g)
@@ -991,7 +991,7 @@ __global__ __launch_bounds__(64 * CB_MAX_WAVES) void tree_attn_combine_kernel(
     const int tile_c = tile < n_tiles ? tile : 0;
     const int part_i = wave - pair * wpt;                                        // which U splits
     const int dp = static_cast<unsigned>(tile_c) % PIECES;                                              // dims 32 dp .. 32 dp + 31 (WIDE: 16 dp ..)
-    const int bg = div31(tile_c / PIECES, n_blk_magic), blk = tile_c / PIECES - bg * n_blk;   // b * Hkv + g, row block
+    const int bg = div_any(tile_c / PIECES, n_blk_magic, shape >> 25), blk = tile_c / PIECES - bg * n_blk;   // b * Hkv + g, row block
     const int r = blk * BLK + lr;
     const bool live = tile < n_tiles && r < R;                              // not a padding row or tile
     const int s0 = part_i * U;
@@ -1462,10 +1462,11 @@ extern "C" int32_t graft_tree_attn(const void* q, const void* k_cache, const voi
     const int64_t tpw_max = CB_MAX_WAVES / wpt;
     tpw = tpw < 1 ? 1 : (tpw > tpw_max ? tpw_max : tpw);
     const dim3 cgrid(static_cast<unsigned>((n_tiles + tpw - 1) / tpw)), cblock(static_cast<unsigned>(64 * tpw * wpt));
+    const Magic n_blk = magic_any(static_cast<uint32_t>(p.R_pad / (pl.wide ? 32 : 16)));
     const auto combine = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, cgrid, cblock, 0, s, p.ws_o, p.ws_ml, n_nodes, static_cast<int32_t>(n_tiles),
-                           static_cast<int32_t>(wpt | tpw << 8 | (256 + wpt - 1) / wpt << 16), p.R, p.R_pad, p.n_splits,
-                           magic31(static_cast<uint32_t>(p.R_pad / (pl.wide ? 32 : 16))), Hkv, p);
+                           static_cast<int32_t>(wpt | tpw << 8 | (256 + wpt - 1) / wpt << 16 | n_blk.shift << 25), p.R, p.R_pad, p.n_splits,
+                           n_blk.m, Hkv, p);
     };
     const auto merge = [&](auto wide_) {
         constexpr bool WIDE = decltype(wide_)::value;

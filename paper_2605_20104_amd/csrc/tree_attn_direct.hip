@@ -784,7 +784,8 @@ __global__ __launch_bounds__(DR_THREADS, MB * D == 64 ? 4 : 2) void tree_attn_di
 
 // Merge of the splits: one thread per four dims of a row, the splits' pieces requested U at a time, all of them in flight: buffer
 // loads, zeros where there is no split (with a condition around each, a split was waited for before the next was requested).  8 layers of
-// 2K keys in fp32 (6 splits) 165.9 -> 157.3 us.  R_magic: magic31(R), exact for the rows of a job that is split (2^19 at most, R <= 2048).
+// 2K keys in fp32 (6 splits) 165.9 -> 157.3 us.  R_magic: magic31(R), exact as a
+// job is split only while it has at most 4 units a compute unit, of 512 rows at most (2^19 rows, R <= 2048).
 template <typename T, int D, int U>
 __global__ __launch_bounds__(256) void tree_attn_direct_merge_kernel(
     const unsigned short* ws_bits, const float* ws_ml, const int32_t* n_nodes, int32_t n_rows, int32_t R, uint32_t R_magic, int32_t R_pad,
