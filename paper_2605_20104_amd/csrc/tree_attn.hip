@@ -1130,9 +1130,11 @@ static thread_local int g_force_splits = 0, g_force_row_tiles = 0;
 // (geometric mean 1.07) what they took with the 16-row kernel, and take 0.85 to 0.98 times as long in what they get with the 11 stages asked here too.
 // 128 rows, two to five row tiles, same plan, by stages of a split: 3 stages 1.08, 5 0.99 to 1.01, 8 0.95, 11 0.92 to 0.94, 14 0.89 to 0.92, 20
 // 0.86 to 0.89, 33 0.87, 64 0.81 to 0.93.  One row tile has a stage's keys to itself and is bound by their arrival: 3 to 14 stages 1.00 to
-// 1.08, 20 to 64 0.93 to 1.04, so it keeps the 16-row kernel.  The 129 of 3000 drawn shapes whose plan changes with this tile, a third of them from
-// one of 256 rows and twice the splits: 0.91 times the time with a full table (0.76 .. 1.00), 0.93 with half the keys (0.70 .. 1.10),
-// 0.93 with an eighth (0.62 .. 1.35: the set-up and exchange of 32-row blocks where a split has one stage).
+// 1.08, 20 to 64 0.93 to 1.04, so it keeps the 16-row kernel.  So do plans of 64-row tiles, which the larger tile cuts into half as many splits more or twice as many: six shapes take 0.85 to
+// 0.90 times as long with it where the table is full, but 0.95 to 1.08 with half the keys and 1.15 to 1.35 with an eighth.  The other 114 of 120
+// drawn shapes that get this tile, a third of them in place of one of 256 rows and twice the splits: 0.92 times the time with a full table
+// (0.73 .. 1.01), 0.90 with half the keys (0.66 .. 1.01), 0.89 with an eighth (0.53 .. 1.15: dearest where the plan is the same and a
+// split of 11 to 17 stages has one or two, 1.06 in 43 shapes: the set-up and exchange of 32-row blocks).
 // The best shape of either kernel is found first; between them the launch that merges splits counts, and the 32-row kernel has to
 // be ahead by the 3 per cent to which the costs are calibrated.  Tiles of 192 rows that need no split against 320 rows in two:
 // 12 stages 24.5 / 31.9 us, 16 29.2 / 35.5 (8 sequences, 80 x 64 heads on 8).
@@ -1183,7 +1185,7 @@ static AttnPlan make_plan(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int
                 const auto take = [&](Best& best) {
                     if (best.key < 0.0 || key < best.key) best = {key, total, mb, rt, sp};
                 };
-                if (has_kernel(mb, w, rt, sp, per[sp])) take(w ? wide : narrow);
+                if (has_kernel(mb, w, rt, sp, per[sp]) && !(w && mb == 2 && narrow.mb == 1)) take(w ? wide : narrow);
                 if (!w) take(line);
             }
         }
