@@ -883,11 +883,15 @@ DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_
     const int mb_max = dtype == GRAFT_F32 ? (D == 128 ? 2 : 1) : (D == 128 ? 1 : 4);
     const double rows = static_cast<double>(B) * Hkv * R;
     const auto merge_cost = [&](int sp) { return sp > 1 ? 8000.0 + 600.0 * sp + sp * rows * D / 400.0 : 0.0; };
-    for (int mb = 1; mb <= mb_max; mb *= 2) {
+    const auto rounds_of = [&](int64_t workgroups) { return static_cast<double>((workgroups + cus - 1) / cus); };
+    const auto plan_cost = [&](int mb, int64_t per, int64_t workgroups, int sp) {
         double c_step = D == 64 ? 2650.0 : (mb == 1 ? 4700.0 : 8200.0);
         if (dtype != GRAFT_F32 && D == 128) c_step = 2600.0;
         else if (dtype != GRAFT_F32) c_step = mb == 4 ? 4550.0 : (mb == 2 ? 2750.0 : 1700.0);
         const double c_fixed = 6500.0 + 2000.0 * mb * (D / 64);
+        return rounds_of(workgroups) * (c_fixed + per * c_step) + merge_cost(sp);
+    };
+    for (int mb = 1; mb <= mb_max; mb *= 2) {
         for (int rg = 1; rg <= DR_WAVES; rg *= 2) {
             const int kg = DR_WAVES / rg;
             const int n_rt = (blocks + rg * mb - 1) / (rg * mb);
@@ -895,8 +899,7 @@ DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_
             const int64_t units = static_cast<int64_t>(B) * Hkv * n_rt;
             for (int sp = 1; sp <= (may_split ? DR_MAX_SPLITS : 1); ++sp) {
                 const int64_t per = (tiles + static_cast<int64_t>(sp) * kg - 1) / (static_cast<int64_t>(sp) * kg);
-                const int64_t rounds = (units * sp + cus - 1) / cus;
-                const double cost = rounds * (c_fixed + per * c_step) + merge_cost(sp);
+                const double cost = plan_cost(mb, per, units * sp, sp);
                 if (best.cost < 0.0 || cost < best.cost) best = {mb, rg, n_rt, sp, 0, 0, 0, cost, false};
                 if (units * sp > 4 * cus || per <= 1) break;
             }
@@ -906,7 +909,7 @@ DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_
     // with D = 128 and 2.95 with D = 64; one that not all wavefronts have takes its share, at least half (their SIMDs are their own).  At the
     // fp32 costs' 2133 a us that is 10800 and 6250, but those plans take longer than their costs by as much: 110 drawn shapes of 4 to 40
     // steps a compute unit take 0.828 of the time with fp32 products where the choice is made with 8150, 0.828 with 8800, 0.836 with 9500
-    // and 0.849 with 10800; 40 with D = 64 0.827, 0.828, 0.825, 0.827.
+    // and 0.849 with 10800; with D = 64 5300 (by 4750, 2 of 88 drawn shapes that take 1.10 and 1.11 times the time so).
     // D = 128 with short tables: us a call with fp32 MFMAs / with parts.  Of PARTS_STEPS_128 steps a compute unit or more, 10 x 564 tokens, 1936
     // rows, 74.2 / 52.0, 30 of 490 x 676 69.0 / 46.3, 56 of 283 x 645 76.5 / 57.2, 28 of 669 x 1176 150 / 94.  Of fewer, with one row group in the
     // fp32 plan: from PARTS_PAGES_128_RG1 pages on 24.2 / 16.1 (467 tokens, 1694 rows on 4 heads); of 26 pages 12.6 / 14.5 (410, 630 on 2) and
@@ -917,14 +920,28 @@ DirectPlan plan_direct(int32_t B, int32_t K_max, int32_t Hq, int32_t Hkv, int32_
     const bool parts_128 = max_pages >= PARTS_PAGES_128 || (best.rg == 1 && max_pages >= PARTS_PAGES_128_RG1) ||
                            units32 * tiles32 >= PARTS_STEPS_128 * DR_WAVES * cus;
     if (dtype == GRAFT_F32 && (D == 64 || parts_128)) {
-        const double c_step = D == 64 ? 4750.0 : 8150.0, c_fixed = D == 64 ? 12000.0 : 14500.0;
+        const double c_step = D == 64 ? 5300.0 : 8150.0, c_fixed = D == 64 ? 12000.0 : 14500.0;
         const double ahead = D == 64 || max_pages >= PARTS_PAGES_128 ? 1.0 : 0.95;      // (a step or two a compute unit: the costs are no better than that)
-        for (int sp = 1; sp <= (may_split ? DR_MAX_SPLITS : 1); ++sp) {
-            const int64_t per = (tiles32 + sp - 1) / sp, rounds = (units32 * sp + cus - 1) / cus, over = per % DR_WAVES;
+        const auto parts_cost = [&](int sp, int64_t of) {
+            const int64_t per = (of + sp - 1) / sp, over = per % DR_WAVES;
             const double steps = static_cast<double>(per / DR_WAVES) + (over ? std::max(0.5, over / static_cast<double>(DR_WAVES)) : 0.0);
-            const double cost = rounds * (c_fixed + steps * c_step) + merge_cost(sp);
+            return rounds_of(units32 * sp) * (c_fixed + steps * c_step) + merge_cost(sp);
+        };
+        const DirectPlan fp32 = best;
+        for (int sp = 1; sp <= (may_split ? DR_MAX_SPLITS : 1); ++sp) {
+            const double cost = parts_cost(sp, tiles32);
             if (cost < (best.parts ? 1.0 : ahead) * best.cost) best = {2, 1, n_rt32, sp, 0, 0, 0, cost, true};
-            if (units32 * sp > 4 * cus || per <= DR_WAVES / 2) break;
+            if (units32 * sp > 4 * cus || (tiles32 + sp - 1) / sp <= DR_WAVES / 2) break;
+        }
+        // Not split, a workgroup's fixed part (5.6 us with D = 64, 6.8 with 128) is what the other kernel's short steps are compared with, and a
+        // table seldom is full: less than 9 per cent ahead here, it has to be ahead with half the keys too.  170 drawn shapes of 32 to 16384 tokens, time
+        // over that with fp32 products with a full table / half the keys / an eighth: without this (and 4750 for the step with D = 64) 0.740 (largest
+        // 1.11) / 0.804 (1.25) / 0.916 (1.71), with it 0.741 (1.02) / 0.799 (1.24) / 0.906
+        // (1.42); 170 shapes that the line was not drawn by 0.741 (1.02) / 0.797 (1.18) / 0.902 (1.54).
+        if (best.parts && best.n_splits == 1 && best.cost >= 0.91 * fp32.cost) {
+            const int64_t each = static_cast<int64_t>(fp32.n_splits) * (DR_WAVES / fp32.rg), units = static_cast<int64_t>(B) * Hkv * fp32.n_row_tiles;
+            const double half = plan_cost(fp32.mb, ((tiles + 1) / 2 + each - 1) / each, units * fp32.n_splits, fp32.n_splits);
+            if (parts_cost(1, (tiles32 + 1) / 2) >= half) best = fp32;
         }
     }
     best.r_pad = best.n_row_tiles * best.rg * best.mb * 16;
