@@ -178,7 +178,7 @@ int32_t graft_build_tree_mask(const int32_t* parent, const int32_t* n_nodes, con
  *                             launches large, products are made of 16-bit ones: queries and
  *                             keys enter them as the sum of two fp16 numbers times a power of
  *                             two (23 bits), probabilities and values as three bf16 numbers
- *                             whose sum they are; up to 2^-22 of a product is left out.  Queries
+ *                             whose sum they are (bits below 2^-133 aside); up to 2^-22 of a product is left out.  Queries
  *                             and keys that fp16 numbers cannot hold, or hold with so few bits
  *                             that a score may be off by 2^-22 (in powers of two, or of the
  *                             row's largest, root mean square), take fp32 products.

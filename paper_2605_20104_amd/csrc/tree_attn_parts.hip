@@ -16,8 +16,8 @@
 //           rounding of an exponent of 4) or that part of the row's largest score (at least as far from zero as its reference is, or 16
 //           less: a reference is kept that long), which fp32 sums of D products are off by too.
 //   O     : probabilities and values are three bf16 numbers whose sum they are, eight bits each, and a product six of the nine (the rest is
-//           below 2^-23 of it): the exponents are those of fp32, so there is nothing to scale and nothing to lose, whatever the
-//           values of a dim have been before and whatever other rows see.  (Two fp16 numbers with a factor a dim from the wavefront's
+//           below 2^-23 of it): the exponents are those of fp32, so there is nothing to scale and nothing to lose (above 2^-133, where
+//           bf16 numbers end), whatever the values of a dim have been before and whatever other rows see.  (Two fp16 numbers with a factor a dim from the wavefront's
 //           first tile: 4.0 us a step, and wrong results behind values of another size, by 7e-3 and without end.)
 //   beyond: what fp16 does not hold (keys past 65504, infinities, NaN) makes sums infinite or NaN.  Such a wavefront, and one
 //           with a row past the bound above, takes its tiles once more with v_mfma_f32_32x32x2_f32 on the same registers, and keys
